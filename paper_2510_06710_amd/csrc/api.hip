@@ -127,7 +127,11 @@ static Workspace plan_workspace(const vla_config &c, char *base, int n_seq, int 
     w.a_rows = (int)Mp;
     w.X = (float *)take(M * H * 4);
     w.Nrm = take(Mp * H * es);
-    w.QKV = (float *)take(M * 3 * H * 4);
+    // (the head's partial logits use the same buffer: its rows come after the layers that read the projection)
+    size_t qkvb = M * 3 * H * 4;
+    for (int rows : {head_rows, head_rows < VLA_HEAD_PARTIAL_ROWS ? head_rows : VLA_HEAD_PARTIAL_ROWS})
+        if (head_scratch_bytes(rows, c.hidden) > qkvb) qkvb = head_scratch_bytes(rows, c.hidden);
+    w.QKV = (float *)take(qkvb);
     w.Q = take(M * H * es);
     w.AO = take(Mp * H * es);
     w.ACT = take(Mp * F * es);
@@ -521,7 +525,7 @@ static int decode_impl(vla_model *m, void *kvbuf, void *wsbuf, const float *h_la
         for (int j = 0; j < A; j++) {
             bool more = j + 1 < A;
             if ((rc = launch_head_sample<T>(h, head, B, H, temperature, gumbel, nullptr, bins, logp, entropy, logits, A, j,
-                                            more ? ws.X : nullptr, (const T *)m->w.embed, c.vocab, st))) return rc;
+                                            more ? ws.X : nullptr, (const T *)m->w.embed, c.vocab, ws.QKV, st))) return rc;
             if (!more) break;
             RowsArgs ra{B, 1, S + j, 0x7fffffff};
             if ((rc = run_layers<T>(m, ws, ra, kv, false, st))) return rc;
@@ -535,7 +539,7 @@ static int decode_impl(vla_model *m, void *kvbuf, void *wsbuf, const float *h_la
         if ((rc = run_layers<T>(m, ws, ra, kv, false, st))) return rc;
         if ((rc = launch_final_norm_rows(ws.Hb, ws.X, (const float *)m->w.final_norm, B, A, 0, A, H, c.rms_eps, st))) return rc;
         if ((rc = launch_head_sample<T>(ws.Hb, head, B * A, H, temperature, gumbel, nullptr, bins, logp, entropy, logits, 1, 0,
-                                        nullptr, (const T *)nullptr, c.vocab, st))) return rc;
+                                        nullptr, (const T *)nullptr, c.vocab, ws.QKV, st))) return rc;
     }
     return 0;
 }
@@ -573,7 +577,7 @@ static int recompute_impl(vla_model *m, void *wsbuf, const void *patch, const in
         if ((rc = launch_final_norm_rows(ws.Hb, Xh, (const float *)m->w.final_norm, n, rows_h, first_h, A, H, c.rms_eps, st))) return rc;
         size_t o = (size_t)n0 * A;
         if ((rc = launch_head_sample<T>(ws.Hb, head, n * A, H, temperature, nullptr, bins + o, nullptr, logp + o, entropy + o,
-                                        logits ? logits + o * VLA_N_BINS : nullptr, 1, 0, nullptr, (const T *)nullptr, c.vocab, st))) return rc;
+                                        logits ? logits + o * VLA_N_BINS : nullptr, 1, 0, nullptr, (const T *)nullptr, c.vocab, ws.QKV, st))) return rc;
         if (value) {
             float *hv = ws.Hb + (size_t)mb * A * H;
             if ((rc = launch_final_norm_rows(hv, Xh, (const float *)m->w.final_norm, n, rows_h, value_row, 1, H, c.rms_eps, st))) return rc;

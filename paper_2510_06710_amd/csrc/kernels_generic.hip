@@ -314,94 +314,7 @@ __global__ void __launch_bounds__(256) attention_generic_kernel(T *out, const T 
     }
 }
 
-// ---------------------------------------------------------------------------------- head + sampler
-// One 256-thread block per row.  Logits over the 256 action bins (one bin per thread), then wave 0
-// reduces the softmax statistics and the Gumbel-max choice with four bins per lane (bins lane, lane+64, +128, +192).
-template <typename T>
-__global__ void __launch_bounds__(256) head_sample_kernel(const float *h, const T *Wb, int H, float temperature,
-                                                         const float *gumbel, const int32_t *given,
-                                                         int32_t *bins_out, float *logp, float *ent,
-                                                         float *logits, int out_stride, int out_off,
-                                                         float *X_next, const T *embed, int vocab) {
-    extern __shared__ float smem[];
-    float *hs = smem;               // [H]
-    float *z = smem + H;            // [256]
-    __shared__ int chosen;
-    int row = blockIdx.x;
-    size_t o = (size_t)row * out_stride + out_off;
-    int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const float *hr = h + (size_t)row * H;
-    for (int i = threadIdx.x; i < H; i += 256) hs[i] = hr[i];
-    __syncthreads();
-    {   // thread k owns bin k: its weight row is walked in 16-byte pieces, h is broadcast from LDS
-        const int k = threadIdx.x;
-        const T *w = Wb + (size_t)k * H;
-        constexpr int V = 16 / sizeof(T);
-        float a0 = 0.f, a1 = 0.f;
-        int i = 0;
-        if (H % V == 0) {
-            typedef T vec_t __attribute__((ext_vector_type(V)));
-            for (; i + 2 * V <= H; i += 2 * V) {
-                vec_t w0 = *(const vec_t *)(w + i), w1 = *(const vec_t *)(w + i + V);
-#pragma unroll
-                for (int e = 0; e < V; e++) { a0 += hs[i + e] * to_f(w0[e]); a1 += hs[i + V + e] * to_f(w1[e]); }
-            }
-        }
-        for (; i < H; i++) a0 += hs[i] * to_f(w[i]);
-        z[k] = a0 + a1;
-    }
-    __syncthreads();
-    if (logits) logits[o * VLA_N_BINS + threadIdx.x] = z[threadIdx.x];
-    if (wave == 0) {
-        float y[4], t[4];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            int k = lane + 64 * j;
-            y[j] = z[k] / temperature;
-            t[j] = gumbel ? y[j] + gumbel[o * VLA_N_BINS + k] : y[j];
-            mx = fmaxf(mx, y[j]);
-        }
-        mx = wave_max(mx);
-        float se = 0.f, sy = 0.f;
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            float e = expf(y[j] - mx);
-            se += e;
-            sy += e * y[j];
-        }
-        se = wave_sum(se);
-        sy = wave_sum(sy);
-        float lse = mx + logf(se);
-        // argmax of t, lowest bin index on ties
-        float bt = t[0];
-        int bk = lane;
-#pragma unroll
-        for (int j = 1; j < 4; j++)
-            if (t[j] > bt) { bt = t[j]; bk = lane + 64 * j; }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            float ot = __shfl_xor(bt, off, 64);
-            int ok = __shfl_xor(bk, off, 64);
-            if (ot > bt || (ot == bt && ok < bk)) { bt = ot; bk = ok; }
-        }
-        int bin = bk;
-        if (given) bin = min(max(given[o], 0), VLA_N_BINS - 1);
-        if (lane == 0) {
-            if (bins_out) bins_out[o] = bin;
-            logp[o] = z[bin] / temperature - lse;
-            ent[o] = lse - sy / se;
-            chosen = bin;
-        }
-    }
-    if (X_next) {
-        __syncthreads();
-        const T *src = embed + (size_t)(vocab - VLA_N_BINS + chosen) * H;
-        float *dst = X_next + (size_t)row * H;
-        for (int i = threadIdx.x; i < H; i += 256) dst[i] = to_f(src[i]);
-    }
-}
-
+// ---------------------------------------------------------------------------------- value head
 // value[row, c] = w[c] . h[row] + b + bias[c]; one workgroup per (row, c).
 __global__ void value_head_kernel(float *value, const float *h, const float *w, float b, const float *bias, int H,
                                   int h_stride) {
@@ -531,19 +444,6 @@ int launch_attention_generic(T *out, const T *q, const KvView &kv, int layer, co
         out, q, kc, vc, ra.n_seq, ra.R, ra.pos0, ra.full_from, kv.n_heads, kv.d, kv.pos_stride, H);
     return vla_check_launch("attention_generic");
 }
-template <typename T>
-int launch_head_sample(const float *h, const T *lm_head_bins, int n_rows, int H, float temperature,
-                       const float *gumbel, const int32_t *given_bins, int32_t *bins_out, float *logp,
-                       float *ent, float *logits, int out_stride, int out_off, float *X_next,
-                       const T *embed, int vocab, hipStream_t st) {
-    if (n_rows == 0) return 0;
-    ProfScope ps("head_sample", 2.0 * n_rows * H * VLA_N_BINS, st);
-    size_t lds = (size_t)(H + VLA_N_BINS) * sizeof(float);
-    head_sample_kernel<T><<<n_rows, 256, lds, st>>>(h, lm_head_bins, H, temperature, gumbel, given_bins,
-                                                    bins_out, logp, ent, logits, out_stride, out_off,
-                                                    X_next, embed, vocab);
-    return vla_check_launch("head_sample");
-}
 int launch_value_head(float *value, const float *h, const float *w, float b, const float *bias, int vd, int n,
                       int H, int h_stride, hipStream_t st) {
     if (n == 0) return 0;
@@ -564,9 +464,6 @@ int launch_value_head(float *value, const float *h, const float *w, float b, con
                                          const RowsArgs &, int, hipStream_t);                                                        \
     template int launch_attention_generic<T>(T *, const T *, const KvView &, int, const RowsArgs &, int,      \
                                              hipStream_t);                                                    \
-    template int launch_rope_q<T>(T *, const float *, const float2 *, int, int, int, int, int, int, hipStream_t); \
-    template int launch_head_sample<T>(const float *, const T *, int, int, float, const float *,              \
-                                       const int32_t *, int32_t *, float *, float *, float *, int, int,       \
-                                       float *, const T *, int, hipStream_t);
+    template int launch_rope_q<T>(T *, const float *, const float2 *, int, int, int, int, int, int, hipStream_t);
 INSTANTIATE(float)
 INSTANTIATE(bf16_t)

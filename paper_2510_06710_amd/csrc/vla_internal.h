@@ -111,7 +111,10 @@ template <typename T>
 int launch_head_sample(const float *h, const T *lm_head_bins, int n_rows, int H, float temperature,
                        const float *gumbel, const int32_t *given_bins, int32_t *bins_out, float *logp,
                        float *ent, float *logits, int out_stride, int out_off, float *X_next,
-                       const T *embed, int vocab, hipStream_t st);
+                       const T *embed, int vocab, float *scratch, hipStream_t st);
+// scratch of launch_head_sample for n_rows rows (device, fp32 partial logits; none above VLA_HEAD_PARTIAL_ROWS rows)
+constexpr int VLA_HEAD_PARTIAL_ROWS = 4096;
+size_t head_scratch_bytes(int n_rows, int H);
 int launch_value_head(float *value, const float *h, const float *w, float b, const float *bias, int vd, int n,
                       int H, int h_stride, hipStream_t st);
 
