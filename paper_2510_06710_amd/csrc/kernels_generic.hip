@@ -6,6 +6,8 @@
 
 namespace {
 
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // caller-owned fp32 arrays: element alignment
+
 __device__ __forceinline__ float to_f(float v) { return v; }
 __device__ __forceinline__ float to_f(bf16_t v) { return (float)v; }
 template <typename T> __device__ __forceinline__ T from_f(float v);
@@ -72,31 +74,55 @@ __global__ void embed_slots_kernel(float *X, const T *slot_embed, int A, int row
 }
 
 // ---------------------------------------------------------------------------------- RMSNorm
-// n_i = x_i / sqrt(mean(x^2) + eps) * g_i; one 256-thread block per row.
+// n_i = x_i / sqrt(mean(x^2) + eps) * g_i; one 256-thread block per row, which stays in registers between the sum and
+// the scaling (H is a multiple of 16 and at most 8192: up to eight 16-byte pieces per thread).  All loads are in flight
+// at once: with one element per thread and step the final norm of one row of 4096 took 9.2 us, a chain of sixteen
+// memory latencies, now 5 us.
 template <typename T>
-__global__ void rmsnorm_kernel(T *out, const float *X, const float *gain, int H, float eps) {
-    __shared__ float red[4];
-    const float *x = X + (size_t)blockIdx.x * H;
+__device__ __forceinline__ void norm_row(T *o, const float *x, const float *gain, int H, float eps, float *red) {
+    f32x4_t v[8], g[8];
     float ss = 0.f;
-    for (int i = threadIdx.x; i < H; i += 256) ss += x[i] * x[i];
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+        const int i = (j * 256 + threadIdx.x) * 4;
+        if (i < H) {
+            v[j] = *(const f32x4_t *)(x + i);
+            g[j] = *(const f32x4_u *)(gain + i);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 8; j++)
+        if ((j * 256 + (int)threadIdx.x) * 4 < H) {
+#pragma unroll
+            for (int e = 0; e < 4; e++) ss += v[j][e] * v[j][e];
+        }
     ss = block_sum_256(ss, red);
-    float r = 1.0f / sqrtf(ss / (float)H + eps);
-    T *o = out + (size_t)blockIdx.x * H;
-    for (int i = threadIdx.x; i < H; i += 256) o[i] = from_f<T>(x[i] * r * gain[i]);
+    const float r = 1.0f / sqrtf(ss / (float)H + eps);
+    typedef T t4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+        const int i = (j * 256 + threadIdx.x) * 4;
+        if (i < H) {
+            t4 w;
+#pragma unroll
+            for (int e = 0; e < 4; e++) w[e] = from_f<T>(v[j][e] * r * g[j][e]);
+            *(t4 *)(o + i) = w;
+        }
+    }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) rmsnorm_kernel(T *out, const float *X, const float *gain, int H, float eps) {
+    __shared__ float red[4];
+    norm_row<T>(out + (size_t)blockIdx.x * H, X + (size_t)blockIdx.x * H, gain, H, eps, red);
 }
 
 // Final norm of selected rows: out row (s * n_rows + j) = norm(X[s * rows_per_seq + row0 + j]).
-__global__ void final_norm_rows_kernel(float *out, const float *X, const float *gain, int rows_per_seq,
-                                       int row0, int n_rows, int H, float eps) {
+__global__ void __launch_bounds__(256) final_norm_rows_kernel(float *out, const float *X, const float *gain, int rows_per_seq,
+                                                             int row0, int n_rows, int H, float eps) {
     __shared__ float red[4];
-    int s = blockIdx.x / n_rows, j = blockIdx.x % n_rows;
-    const float *x = X + ((size_t)s * rows_per_seq + row0 + j) * H;
-    float ss = 0.f;
-    for (int i = threadIdx.x; i < H; i += 256) ss += x[i] * x[i];
-    ss = block_sum_256(ss, red);
-    float r = 1.0f / sqrtf(ss / (float)H + eps);
-    float *o = out + (size_t)blockIdx.x * H;
-    for (int i = threadIdx.x; i < H; i += 256) o[i] = x[i] * r * gain[i];
+    const int s = blockIdx.x / n_rows, j = blockIdx.x % n_rows;
+    norm_row<float>(out + (size_t)blockIdx.x * H, X + ((size_t)s * rows_per_seq + row0 + j) * H, gain, H, eps, red);
 }
 
 // ---------------------------------------------------------------------------------- GEMM
