@@ -203,6 +203,96 @@ __global__ void __launch_bounds__(256) gemm_generic_kernel(const T *A, const T *
     }
 }
 
+// The same product where 64 x 64 tiles are too few to fill the chip: one workgroup per 16 x 16 outputs, K dealt to its
+// eight waves in blocks of 16 and added in wave order through LDS.  fp32 MFMA (a lane's four consecutive K elements take
+// turns as v_mfma_f32_16x16x4_f32's one element per lane), operands straight from global memory with every load of a
+// wave in flight at once: such a problem is bound by latency, of which the 64 x 64 kernel pays one per 16 columns of K.
+// At 8 x 256 x 688 (down projection of the tiny decoder) 5 us against 155 us, at 8 x 768 x 256 4.4 against 39 us.
+template <typename T, bool VEC>
+__device__ __forceinline__ f32x4_t load4(const T *p, int k, int K) {
+    f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+    if (VEC) {
+        if (k < K) {
+            typedef T t4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+            const t4 w = *(const t4 *)(p + k);
+#pragma unroll
+            for (int e = 0; e < 4; e++) v[e] = to_f(w[e]);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+            if (k + e < K) v[e] = to_f(p[k + e]);
+    }
+    return v;
+}
+
+template <typename T, int EPI, bool VEC>
+__global__ void __launch_bounds__(512) gemm_small_kernel(const T *A, const T *W0, const T *W1, const T *W2, int segN, void *Cv,
+                                                         int M, int N, int K) {
+    constexpr int NW = 8, NB = (EPI == EPI_SWIGLU) ? 2 : 1;
+    __shared__ __attribute__((aligned(16))) f32x4_t part[NW][NB][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
+    const int m = blockIdx.y * 16 + l16, n0 = blockIdx.x * 16;
+    const int n = min(n0 + l16, N - 1);                   // weight row of this lane (past the end: loaded, not stored)
+    const T *a = A + (size_t)min(m, M - 1) * K, *w, *u = nullptr;
+    if (EPI == EPI_SWIGLU) {
+        w = W0 + (size_t)n * K;
+        u = W1 + (size_t)n * K;
+    } else {
+        const int seg = n / segN, nn = n % segN;
+        w = (seg == 0 ? W0 : (seg == 1 ? W1 : W2)) + (size_t)nn * K;
+    }
+    f32x4_t acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; b++) acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    constexpr int UN = 4;
+#pragma unroll 1
+    for (int g = wave * 16; g < K; g += NW * 16 * UN) {
+        f32x4_t av[UN], wv[UN], uv[UN];
+#pragma unroll
+        for (int i = 0; i < UN; i++) {
+            const int k = g + i * NW * 16 + kq * 4;       // (past K: zeros)
+            av[i] = load4<T, VEC>(a, k, K);
+            wv[i] = load4<T, VEC>(w, k, K);
+            if (EPI == EPI_SWIGLU) uv[i] = load4<T, VEC>(u, k, K);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < UN; i++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[i][e], av[i][e], acc[0], 0, 0, 0);
+                if (EPI == EPI_SWIGLU) acc[NB - 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[i][e], av[i][e], acc[NB - 1], 0, 0, 0);
+            }
+    }
+#pragma unroll
+    for (int b = 0; b < NB; b++) part[wave][b][lane] = acc[b];
+    __syncthreads();
+    if (wave != 0 || m >= M) return;
+#pragma unroll
+    for (int b = 0; b < NB; b++)
+#pragma unroll
+        for (int s = 1; s < NW; s++) {
+            const f32x4_t v = part[s][b][lane];
+#pragma unroll
+            for (int r = 0; r < 4; r++) acc[b][r] += v[r];
+        }
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        const int col = n0 + kq * 4 + r;
+        if (col >= N) continue;
+        const size_t o = (size_t)m * N + col;
+        if (EPI == EPI_RESIDUAL) {
+            ((float *)Cv)[o] += acc[0][r];
+        } else if (EPI == EPI_SWIGLU) {
+            const float g = acc[0][r];
+            ((T *)Cv)[o] = from_f<T>(g / (1.0f + expf(-g)) * acc[NB - 1][r]);
+        } else {
+            ((float *)Cv)[o] = acc[0][r];
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------------- rotary
 // table[r][i] = (cos, sin)(phi), phi = (pos0 + r) * theta^(-2i/d), evaluated in fp64.
 __global__ void rope_table_kernel(float2 *table, int R, int pos0, int d, float theta) {
@@ -394,19 +484,28 @@ int launch_final_norm_rows(float *out, const float *X, const float *gain, int n_
     final_norm_rows_kernel<<<n_seq * n_rows, 256, 0, st>>>(out, X, gain, rows_per_seq, row0, n_rows, H, eps);
     return vla_check_launch("final_norm_rows");
 }
+template <typename T, int EPI>
+static void gemm_generic_epi(const GemmArgs &g, int N, hipStream_t st) {
+    const T *A = (const T *)g.A, *W0 = (const T *)g.W[0], *W1 = (const T *)g.W[1], *W2 = (const T *)g.W[2];
+    const dim3 big((N + 63) / 64, (g.M + 63) / 64);
+    // Below two 64 x 64 tiles per CU the small kernel is the faster one (fp32, K = 256: 512 x 768 15 against 53 us).
+    // Its grid has at most 16 times as many workgroups, far from the limits.
+    if ((size_t)big.x * big.y < 512) {
+        const dim3 small((N + 15) / 16, (g.M + 15) / 16);
+        if (g.K % 4 == 0) gemm_small_kernel<T, EPI, true><<<small, 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, g.M, N, g.K);
+        else gemm_small_kernel<T, EPI, false><<<small, 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, g.M, N, g.K);
+        return;
+    }
+    gemm_generic_kernel<T, EPI><<<big, 256, 0, st>>>(A, W0, W1, W2, g.segN, g.C, g.M, N, g.K);
+}
 template <typename T>
 int launch_gemm_generic(const GemmArgs &g, hipStream_t st) {
     if (g.M == 0) return 0;
     ProfScope ps("gemm_generic", 2.0 * g.M * g.K * g.n_seg * g.segN, st);
-    int N = (g.epilogue == EPI_SWIGLU) ? g.segN : g.n_seg * g.segN;
-    dim3 grid((N + 63) / 64, (g.M + 63) / 64);
-    const T *A = (const T *)g.A, *W0 = (const T *)g.W[0], *W1 = (const T *)g.W[1], *W2 = (const T *)g.W[2];
-    if (g.epilogue == EPI_STORE)
-        gemm_generic_kernel<T, EPI_STORE><<<grid, 256, 0, st>>>(A, W0, W1, W2, g.segN, g.C, g.M, N, g.K);
-    else if (g.epilogue == EPI_RESIDUAL)
-        gemm_generic_kernel<T, EPI_RESIDUAL><<<grid, 256, 0, st>>>(A, W0, W1, W2, g.segN, g.C, g.M, N, g.K);
-    else
-        gemm_generic_kernel<T, EPI_SWIGLU><<<grid, 256, 0, st>>>(A, W0, W1, W2, g.segN, g.C, g.M, N, g.K);
+    const int N = (g.epilogue == EPI_SWIGLU) ? g.segN : g.n_seg * g.segN;
+    if (g.epilogue == EPI_STORE) gemm_generic_epi<T, EPI_STORE>(g, N, st);
+    else if (g.epilogue == EPI_RESIDUAL) gemm_generic_epi<T, EPI_RESIDUAL>(g, N, st);
+    else gemm_generic_epi<T, EPI_SWIGLU>(g, N, st);
     return vla_check_launch("gemm_generic");
 }
 int launch_rope_table(float2 *table, int R, int pos0, int d, float theta, hipStream_t st) {
