@@ -126,88 +126,16 @@ __global__ void __launch_bounds__(256) final_norm_rows_kernel(float *out, const 
 }
 
 // ---------------------------------------------------------------------------------- GEMM
-// C[M, N] = A[M, K] . W^T with W given as n_seg row blocks [segN, K].  64 x 64 output tile per
-// 256-thread block, 4 x 4 outputs per thread, K stepped by 16 through LDS; every load and store is
-// bounds checked.  EPI_SWIGLU computes silu(A.Wg^T) * (A.Wu^T) with both products in one pass.
-template <typename T, int EPI>
-__global__ void __launch_bounds__(256) gemm_generic_kernel(const T *A, const T *W0, const T *W1,
-                                                           const T *W2, int segN, void *Cv, int M, int N,
-                                                           int K) {
-    constexpr int BM = 64, BN = 64, BK = 16;
-    __shared__ float As[BK][BM + 1];
-    __shared__ float Ws[BK][BN + 1];
-    __shared__ float Us[(EPI == EPI_SWIGLU) ? BK : 1][BN + 1];
-    int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    float acc[4][4] = {}, acu[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += BK) {
-        for (int e = threadIdx.x; e < BM * BK; e += 256) {
-            int r = e / BK, kk = e % BK;
-            int m = m0 + r, k = k0 + kk;
-            As[kk][r] = (m < M && k < K) ? to_f(A[(size_t)m * K + k]) : 0.f;
-            int n = n0 + r;
-            float w = 0.f, u = 0.f;
-            if (n < N && k < K) {
-                if (EPI == EPI_SWIGLU) {
-                    w = to_f(W0[(size_t)n * K + k]);
-                    u = to_f(W1[(size_t)n * K + k]);
-                } else {
-                    int seg = n / segN, nn = n % segN;
-                    const T *Wp = seg == 0 ? W0 : (seg == 1 ? W1 : W2);
-                    w = to_f(Wp[(size_t)nn * K + k]);
-                }
-            }
-            Ws[kk][r] = w;
-            if (EPI == EPI_SWIGLU) Us[kk][r] = u;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < BK; kk++) {
-            float a[4], w[4], u[4];
-#pragma unroll
-            for (int i = 0; i < 4; i++) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; j++) w[j] = Ws[kk][tx * 4 + j];
-            if (EPI == EPI_SWIGLU) {
-#pragma unroll
-                for (int j = 0; j < 4; j++) u[j] = Us[kk][tx * 4 + j];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-#pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    acc[i][j] += a[i] * w[j];
-                    if (EPI == EPI_SWIGLU) acu[i][j] += a[i] * u[j];
-                }
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        int m = m0 + ty * 4 + i;
-        if (m >= M) continue;
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            int n = n0 + tx * 4 + j;
-            if (n >= N) continue;
-            size_t o = (size_t)m * N + n;
-            if (EPI == EPI_RESIDUAL) {
-                ((float *)Cv)[o] += acc[i][j];
-            } else if (EPI == EPI_SWIGLU) {
-                float g = acc[i][j];
-                ((T *)Cv)[o] = from_f<T>(g / (1.0f + expf(-g)) * acu[i][j]);
-            } else {
-                ((float *)Cv)[o] = acc[i][j];
-            }
-        }
-    }
-}
-
-// The same product where 64 x 64 tiles are too few to fill the chip: one workgroup per 16 x 16 outputs, K dealt to its
-// eight waves in blocks of 16 and added in wave order through LDS.  fp32 MFMA (a lane's four consecutive K elements take
-// turns as v_mfma_f32_16x16x4_f32's one element per lane), operands straight from global memory with every load of a
-// wave in flight at once: such a problem is bound by latency, of which the 64 x 64 kernel pays one per 16 columns of K.
-// At 8 x 256 x 688 (down projection of the tiny decoder) 5 us against 155 us, at 8 x 768 x 256 4.4 against 39 us.
+// C[M, N] = A[M, K] . W^T with W given as n_seg row blocks [segN, K], any sizes.  EPI_SWIGLU computes
+// silu(A.Wg^T) * (A.Wu^T) with both products in one pass.
+//
+// fp32 MFMA (a lane's four consecutive K elements take turns as v_mfma_f32_16x16x4_f32's one element per lane), operands
+// straight from global memory.  A workgroup owns MB x NBK blocks of 16 x 16 outputs; K is dealt to its eight waves in
+// blocks of 16 and the waves' sums are added in wave order through LDS, so an output's additions are the same whatever
+// the tile.  Few outputs (1 x 1 blocks) are bound by latency: every load of a wave is in flight at once, and a tile of
+// 16 x 16 makes enough workgroups.  Many outputs (4 x 2) share the operands.  Measured in fp32 against a 64 x 64 tile
+// on the vector ALU that paid one memory latency per 16 columns of K: 8 x 256 x 688 (M x N x K, down projection of the
+// tiny decoder) 155 -> 5 us, 8 x 768 x 256 39 -> 3.5 us, 512 x 768 x 256 53 -> 9 us.
 template <typename T, bool VEC>
 __device__ __forceinline__ f32x4_t load4(const T *p, int k, int K) {
     f32x4_t v = {0.f, 0.f, 0.f, 0.f};
@@ -226,69 +154,94 @@ __device__ __forceinline__ f32x4_t load4(const T *p, int k, int K) {
     return v;
 }
 
-template <typename T, int EPI, bool VEC>
-__global__ void __launch_bounds__(512) gemm_small_kernel(const T *A, const T *W0, const T *W1, const T *W2, int segN, void *Cv,
-                                                         int M, int N, int K) {
-    constexpr int NW = 8, NB = (EPI == EPI_SWIGLU) ? 2 : 1;
-    __shared__ __attribute__((aligned(16))) f32x4_t part[NW][NB][64];
+template <typename T, int EPI, bool VEC, int MB, int NBK>
+__global__ void __launch_bounds__(512) gemm_generic_kernel(const T *A, const T *W0, const T *W1, const T *W2, int segN, void *Cv,
+                                                           int M, int N, int K) {
+    constexpr int NW = 8, NP = (EPI == EPI_SWIGLU) ? 2 : 1, UN = MB * NBK > 1 ? 1 : 4;
+    __shared__ __attribute__((aligned(16))) f32x4_t part[NW][NP * MB * NBK][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
-    const int m = blockIdx.y * 16 + l16, n0 = blockIdx.x * 16;
-    const int n = min(n0 + l16, N - 1);                   // weight row of this lane (past the end: loaded, not stored)
-    const T *a = A + (size_t)min(m, M - 1) * K, *w, *u = nullptr;
-    if (EPI == EPI_SWIGLU) {
-        w = W0 + (size_t)n * K;
-        u = W1 + (size_t)n * K;
-    } else {
-        const int seg = n / segN, nn = n % segN;
-        w = (seg == 0 ? W0 : (seg == 1 ? W1 : W2)) + (size_t)nn * K;
-    }
-    f32x4_t acc[NB];
+    const int m0 = blockIdx.y * (16 * MB), n0 = blockIdx.x * (16 * NBK);
+    const T *a[MB], *w[NP][NBK];
 #pragma unroll
-    for (int b = 0; b < NB; b++) acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    constexpr int UN = 4;
+    for (int i = 0; i < MB; i++) a[i] = A + (size_t)min(m0 + i * 16 + l16, M - 1) * K;
+#pragma unroll
+    for (int j = 0; j < NBK; j++) {
+        const int n = min(n0 + j * 16 + l16, N - 1);      // (past the end: loaded, not stored)
+        if (EPI == EPI_SWIGLU) {
+            w[0][j] = W0 + (size_t)n * K;
+            w[NP - 1][j] = W1 + (size_t)n * K;
+        } else {
+            const int seg = n / segN, nn = n % segN;
+            w[0][j] = (seg == 0 ? W0 : (seg == 1 ? W1 : W2)) + (size_t)nn * K;
+        }
+    }
+    f32x4_t acc[NP][MB][NBK];
+#pragma unroll
+    for (int b = 0; b < NP; b++)
+#pragma unroll
+        for (int i = 0; i < MB; i++)
+#pragma unroll
+            for (int j = 0; j < NBK; j++) acc[b][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
     for (int g = wave * 16; g < K; g += NW * 16 * UN) {
-        f32x4_t av[UN], wv[UN], uv[UN];
+        f32x4_t av[UN][MB], wv[UN][NP][NBK];
 #pragma unroll
         for (int i = 0; i < UN; i++) {
             const int k = g + i * NW * 16 + kq * 4;       // (past K: zeros)
-            av[i] = load4<T, VEC>(a, k, K);
-            wv[i] = load4<T, VEC>(w, k, K);
-            if (EPI == EPI_SWIGLU) uv[i] = load4<T, VEC>(u, k, K);
+#pragma unroll
+            for (int x = 0; x < MB; x++) av[i][x] = load4<T, VEC>(a[x], k, K);
+#pragma unroll
+            for (int b = 0; b < NP; b++)
+#pragma unroll
+                for (int j = 0; j < NBK; j++) wv[i][b][j] = load4<T, VEC>(w[b][j], k, K);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < UN; i++)
 #pragma unroll
-            for (int e = 0; e < 4; e++) {
-                acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[i][e], av[i][e], acc[0], 0, 0, 0);
-                if (EPI == EPI_SWIGLU) acc[NB - 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[i][e], av[i][e], acc[NB - 1], 0, 0, 0);
-            }
+            for (int e = 0; e < 4; e++)
+#pragma unroll
+                for (int b = 0; b < NP; b++)
+#pragma unroll
+                    for (int x = 0; x < MB; x++)
+#pragma unroll
+                        for (int j = 0; j < NBK; j++)
+                            acc[b][x][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[i][b][j][e], av[i][x][e], acc[b][x][j], 0, 0, 0);
     }
 #pragma unroll
-    for (int b = 0; b < NB; b++) part[wave][b][lane] = acc[b];
-    __syncthreads();
-    if (wave != 0 || m >= M) return;
+    for (int b = 0; b < NP; b++)
 #pragma unroll
-    for (int b = 0; b < NB; b++)
+        for (int x = 0; x < MB; x++)
+#pragma unroll
+            for (int j = 0; j < NBK; j++) part[wave][(b * MB + x) * NBK + j][lane] = acc[b][x][j];
+    __syncthreads();
+    // block (x, j) of the tile is finished by wave x * NBK + j: lane = row l16, columns 4 * kq .. + 3
+    if (wave >= MB * NBK) return;
+    const int x = wave / NBK, j = wave % NBK, m = m0 + x * 16 + l16;
+    if (m >= M) return;
+    f32x4_t sum[NP];
+#pragma unroll
+    for (int b = 0; b < NP; b++) {
+        sum[b] = part[0][(b * MB + x) * NBK + j][lane];
 #pragma unroll
         for (int s = 1; s < NW; s++) {
-            const f32x4_t v = part[s][b][lane];
+            const f32x4_t v = part[s][(b * MB + x) * NBK + j][lane];
 #pragma unroll
-            for (int r = 0; r < 4; r++) acc[b][r] += v[r];
+            for (int r = 0; r < 4; r++) sum[b][r] += v[r];
         }
+    }
 #pragma unroll
     for (int r = 0; r < 4; r++) {
-        const int col = n0 + kq * 4 + r;
+        const int col = n0 + j * 16 + kq * 4 + r;
         if (col >= N) continue;
         const size_t o = (size_t)m * N + col;
         if (EPI == EPI_RESIDUAL) {
-            ((float *)Cv)[o] += acc[0][r];
+            ((float *)Cv)[o] += sum[0][r];
         } else if (EPI == EPI_SWIGLU) {
-            const float g = acc[0][r];
-            ((T *)Cv)[o] = from_f<T>(g / (1.0f + expf(-g)) * acc[NB - 1][r]);
+            const float g = sum[0][r];
+            ((T *)Cv)[o] = from_f<T>(g / (1.0f + expf(-g)) * sum[NP - 1][r]);
         } else {
-            ((float *)Cv)[o] = acc[0][r];
+            ((float *)Cv)[o] = sum[0][r];
         }
     }
 }
@@ -484,19 +437,22 @@ int launch_final_norm_rows(float *out, const float *X, const float *gain, int n_
     final_norm_rows_kernel<<<n_seq * n_rows, 256, 0, st>>>(out, X, gain, rows_per_seq, row0, n_rows, H, eps);
     return vla_check_launch("final_norm_rows");
 }
+template <typename T, int EPI, bool VEC>
+static void gemm_generic_tile(const GemmArgs &g, int N, hipStream_t st) {
+    constexpr int MB = (EPI == EPI_SWIGLU) ? 2 : 4, NBK = 2;
+    const T *A = (const T *)g.A, *W0 = (const T *)g.W[0], *W1 = (const T *)g.W[1], *W2 = (const T *)g.W[2];
+    const dim3 big((N + 16 * NBK - 1) / (16 * NBK), (g.M + 16 * MB - 1) / (16 * MB));
+    // The large tile wants two workgroups per CU; its sums are those of the small one.  (Fewer than 512 large tiles are
+    // at most 4096 + a few rows of small ones.)
+    if ((size_t)big.x * big.y < 512)
+        gemm_generic_kernel<T, EPI, VEC, 1, 1><<<dim3((N + 15) / 16, (g.M + 15) / 16), 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, g.M, N, g.K);
+    else
+        gemm_generic_kernel<T, EPI, VEC, MB, NBK><<<big, 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, g.M, N, g.K);
+}
 template <typename T, int EPI>
 static void gemm_generic_epi(const GemmArgs &g, int N, hipStream_t st) {
-    const T *A = (const T *)g.A, *W0 = (const T *)g.W[0], *W1 = (const T *)g.W[1], *W2 = (const T *)g.W[2];
-    const dim3 big((N + 63) / 64, (g.M + 63) / 64);
-    // Below two 64 x 64 tiles per CU the small kernel is the faster one (fp32, K = 256: 512 x 768 15 against 53 us).
-    // Its grid has at most 16 times as many workgroups, far from the limits.
-    if ((size_t)big.x * big.y < 512) {
-        const dim3 small((N + 15) / 16, (g.M + 15) / 16);
-        if (g.K % 4 == 0) gemm_small_kernel<T, EPI, true><<<small, 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, g.M, N, g.K);
-        else gemm_small_kernel<T, EPI, false><<<small, 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, g.M, N, g.K);
-        return;
-    }
-    gemm_generic_kernel<T, EPI><<<big, 256, 0, st>>>(A, W0, W1, W2, g.segN, g.C, g.M, N, g.K);
+    if (g.K % 4 == 0) gemm_generic_tile<T, EPI, true>(g, N, st);
+    else gemm_generic_tile<T, EPI, false>(g, N, st);
 }
 template <typename T>
 int launch_gemm_generic(const GemmArgs &g, hipStream_t st) {
