@@ -141,3 +141,33 @@ def test_grpo_groups_of_equal_inexact_returns_are_filtered():
     assert keep.cpu().numpy().astype(bool).tolist() == rk.tolist()
     assert np.max(np.abs(adv.cpu().numpy() - ra)) < 1e-5
     assert (adv.cpu().numpy()[:2 * G] == 0).all()
+
+
+@pytest.mark.parametrize("n,T", [(5, 63), (4, 64), (9, 65), (1, 128), (6, 129)])
+def test_gae_at_the_edges_of_64_steps(n, T):
+    """The scan takes 64 steps at a time from the last one down: a done flag and a carry on either side of each edge."""
+    rng = np.random.default_rng(n * 1000 + T)
+    r, v = rng.standard_normal((n, T)).astype(np.float32), rng.standard_normal((n, T + 1)).astype(np.float32)
+    d = np.zeros((n, T), dtype=np.int32)
+    d[0, [0, T // 2, T - 1]] = 1
+    d[n - 1, [t for t in (T - 64, T - 65) if t >= 0]] = 1
+    adv, ret = torch.empty(n, T, device=DEV), torch.empty(n, T, device=DEV)
+    vb.vla_gae(dev(r), dev(v), dev(d, torch.int32), n, T, 0.99, 0.95, adv, ret)
+    torch.cuda.synchronize()
+    ra, rr = ro.ogae(r, v, d, 0.99, 0.95)
+    scale = max(1.0, np.abs(ra).max())
+    assert np.max(np.abs(adv.cpu().numpy() - ra)) < 1e-5 * scale
+    assert np.max(np.abs(ret.cpu().numpy() - rr)) < 1e-5 * scale
+
+
+@pytest.mark.parametrize("n_groups,G", [(5, 64), (3, 65), (2, 200)])
+def test_grpo_advantage_of_groups_wider_than_a_wave(n_groups, G):
+    R = np.random.default_rng(G).standard_normal(n_groups * G).astype(np.float32)
+    R[:G] = 0.1                                              # identical returns, not exact in fp32
+    adv, keep = torch.empty(n_groups * G, device=DEV), torch.empty(n_groups, dtype=torch.int32, device=DEV)
+    vb.vla_grpo_advantage(dev(R), n_groups, G, adv, keep)
+    torch.cuda.synchronize()
+    ra, rk = ro.ogrpo_advantage(R[G:], G)
+    assert keep[0].item() == 0 and not adv[:G].any().item()
+    assert np.array_equal(keep.cpu().numpy().astype(bool)[1:], rk)
+    assert np.max(np.abs(adv.cpu().numpy()[G:] - ra)) < 1e-5
