@@ -39,6 +39,7 @@
 #include "vla_internal.h"
 
 #include <type_traits>
+#include <utility>
 
 namespace {
 
@@ -100,6 +101,82 @@ __device__ __forceinline__ void acc_settle() { asm volatile("s_nop 15\n\ts_nop 1
 // row-wise reads free of bank conflicts.
 __device__ __forceinline__ float *panel_at(float *panel, int row, int cb) { return panel + row * 128 + ((cb ^ row) << 2); }
 
+// One 16-row block of a wave's QKV output, from its panel: the wave's 128 columns are one head of q, k or v (head_dim 128).
+__device__ __forceinline__ void qkv_block_out(const DmaGemmParams &p, float *panel, int mblock, int n0, int lane) {
+    const int seg_in = n0 / p.H, head = (n0 - seg_in * p.H) >> 7, seg = seg_in + p.seg0;
+    if (seg == 2) {
+#pragma unroll
+        for (int it = 0; it < 4; it++) {
+            const int row = it * 4 + (lane >> 4), c = lane & 15, m = mblock + row;
+            f32x4_t a = *(const f32x4_t *)panel_at(panel, row, 2 * c);
+            f32x4_t b = *(const f32x4_t *)panel_at(panel, row, 2 * c + 1);
+            bf16x8_t o;
+#pragma unroll
+            for (int e = 0; e < 4; e++) { o[e] = (bf16_t)a[e]; o[4 + e] = (bf16_t)b[e]; }
+            if (m < p.M) {
+                const int sq = m / p.R, pos = p.pos0 + (m - sq * p.R);
+                *(bf16x8_t *)(p.vc + (((size_t)sq * p.n_heads + head) * p.pos_stride + pos) * 128 + c * 8) = o;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int it = 0; it < 2; it++) {
+            // q: consecutive lanes take consecutive chunks of a row; k: consecutive positions of a chunk
+            const int item = it * 64 + lane;
+            const int row = (seg == 0) ? (item >> 3) : (item & 15);
+            const int c = (seg == 0) ? (item & 7) : (item >> 4);
+            const int m = mblock + row;
+            f32x4_t lo0 = *(const f32x4_t *)panel_at(panel, row, 2 * c), lo1 = *(const f32x4_t *)panel_at(panel, row, 2 * c + 1);
+            f32x4_t hi0 = *(const f32x4_t *)panel_at(panel, row, 16 + 2 * c), hi1 = *(const f32x4_t *)panel_at(panel, row, 17 + 2 * c);
+            if (m < p.M) {
+                const int sq = m / p.R, rr = m - sq * p.R, pos = p.pos0 + rr;
+                const f32x4_t *tb = (const f32x4_t *)(p.table + (size_t)rr * 64 + c * 8);
+                bf16x8_t olo, ohi;
+#pragma unroll
+                for (int e2 = 0; e2 < 4; e2++) {
+                    const f32x4_t cs = tb[e2];        // (cos, sin) of dims 2 e2 and 2 e2 + 1 of the chunk
+#pragma unroll
+                    for (int u = 0; u < 2; u++) {
+                        const int e = 2 * e2 + u;
+                        const float co = cs[2 * u], si = cs[2 * u + 1];
+                        const float a = e < 4 ? lo0[e & 3] : lo1[e & 3], b = e < 4 ? hi0[e & 3] : hi1[e & 3];
+                        olo[e] = (bf16_t)(a * co - b * si);
+                        ohi[e] = (bf16_t)(b * co + a * si);
+                    }
+                }
+                if (seg == 0) {
+                    bf16_t *q = p.q_out + (size_t)m * p.H + head * 128 + c * 8;
+                    *(bf16x8_t *)q = olo;
+                    *(bf16x8_t *)(q + 64) = ohi;
+                } else {
+                    const size_t hb = ((size_t)sq * p.n_heads + head) * 16;
+                    *(bf16x8_t *)(p.kc + ((hb + c) * p.pos_stride + pos) * 8) = olo;
+                    *(bf16x8_t *)(p.kc + ((hb + 8 + c) * p.pos_stride + pos) * 8) = ohi;
+                }
+            }
+        }
+    }
+}
+
+// One 16-row block of a wave's 64 SwiGLU output columns from c0 = tn * 128 + wn * 64, from its panel: row-major [M, N], or
+// k-blocked: column c of row m at ((c / 32) * a_rows + m) * 32 + c % 32.
+template <bool KB>
+__device__ __forceinline__ void swiglu_block_out(const DmaGemmParams &p, float *panel, int mblock, int c0, int lane) {
+    c0 += (lane & 7) * 8;
+    bf16_t *out = (bf16_t *)p.C + (KB ? (size_t)(c0 >> 5) * p.a_rows * 32 + (c0 & 31) : (size_t)c0);
+    const size_t row_stride = KB ? 32 : (size_t)p.N;
+#pragma unroll
+    for (int it = 0; it < 2; it++) {
+        const int row = it * 8 + (lane >> 3), c2 = lane & 7, m = mblock + row;
+        f32x4_t a = *(const f32x4_t *)panel_at(panel, row, 2 * c2);
+        f32x4_t b = *(const f32x4_t *)panel_at(panel, row, 2 * c2 + 1);
+        bf16x8_t o;
+#pragma unroll
+        for (int e = 0; e < 4; e++) { o[e] = (bf16_t)a[e]; o[4 + e] = (bf16_t)b[e]; }
+        if (m < p.M) *(bf16x8_t *)(out + (size_t)m * row_stride) = o;
+    }
+}
+
 // Output of one wave.  Per 16-row activation block i a lane holds row (lane % 16) and, per weight block j
 // and register r, column 16 j + 4 (lane / 16) + r.  Each block goes through the panel and leaves as whole
 // rows.
@@ -108,79 +185,20 @@ __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][8], const DmaGemmPara
                                          int lane, float *panel, size_t c_off) {
     const int l16 = lane & 15, kq = lane >> 4;
     if (EPI == EPI_QKV_ROPE) {
-        // the wave's 128 columns are one head of q, k or v (head_dim 128)
         const int n0 = tn * BN + wn * 128;
-        const int seg_in = n0 / p.H, head = (n0 - seg_in * p.H) >> 7, seg = seg_in + p.seg0;
 #pragma unroll
         for (int i = 0; i < 8; i++) {
-            const int mblock = m0 + wm * 128 + i * 16;
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < 8; j++) *(f32x4_t *)panel_at(panel, l16, j * 4 + kq) = acc_read4(acc[j][i]);
-            if (seg == 2) {
-#pragma unroll
-                for (int it = 0; it < 4; it++) {
-                    const int row = it * 4 + (lane >> 4), c = lane & 15, m = mblock + row;
-                    f32x4_t a = *(const f32x4_t *)panel_at(panel, row, 2 * c);
-                    f32x4_t b = *(const f32x4_t *)panel_at(panel, row, 2 * c + 1);
-                    bf16x8_t o;
-#pragma unroll
-                    for (int e = 0; e < 4; e++) { o[e] = (bf16_t)a[e]; o[4 + e] = (bf16_t)b[e]; }
-                    if (m < p.M) {
-                        const int sq = m / p.R, pos = p.pos0 + (m - sq * p.R);
-                        *(bf16x8_t *)(p.vc + (((size_t)sq * p.n_heads + head) * p.pos_stride + pos) * 128 + c * 8) = o;
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int it = 0; it < 2; it++) {
-                    // q: consecutive lanes take consecutive chunks of a row; k: consecutive positions of a chunk
-                    const int item = it * 64 + lane;
-                    const int row = (seg == 0) ? (item >> 3) : (item & 15);
-                    const int c = (seg == 0) ? (item & 7) : (item >> 4);
-                    const int m = mblock + row;
-                    f32x4_t lo0 = *(const f32x4_t *)panel_at(panel, row, 2 * c), lo1 = *(const f32x4_t *)panel_at(panel, row, 2 * c + 1);
-                    f32x4_t hi0 = *(const f32x4_t *)panel_at(panel, row, 16 + 2 * c), hi1 = *(const f32x4_t *)panel_at(panel, row, 17 + 2 * c);
-                    if (m < p.M) {
-                        const int sq = m / p.R, rr = m - sq * p.R, pos = p.pos0 + rr;
-                        const f32x4_t *tb = (const f32x4_t *)(p.table + (size_t)rr * 64 + c * 8);
-                        bf16x8_t olo, ohi;
-#pragma unroll
-                        for (int e2 = 0; e2 < 4; e2++) {
-                            const f32x4_t cs = tb[e2];        // (cos, sin) of dims 2 e2 and 2 e2 + 1 of the chunk
-#pragma unroll
-                            for (int u = 0; u < 2; u++) {
-                                const int e = 2 * e2 + u;
-                                const float co = cs[2 * u], si = cs[2 * u + 1];
-                                const float a = e < 4 ? lo0[e & 3] : lo1[e & 3], b = e < 4 ? hi0[e & 3] : hi1[e & 3];
-                                olo[e] = (bf16_t)(a * co - b * si);
-                                ohi[e] = (bf16_t)(b * co + a * si);
-                            }
-                        }
-                        if (seg == 0) {
-                            bf16_t *q = p.q_out + (size_t)m * p.H + head * 128 + c * 8;
-                            *(bf16x8_t *)q = olo;
-                            *(bf16x8_t *)(q + 64) = ohi;
-                        } else {
-                            const size_t hb = ((size_t)sq * p.n_heads + head) * 16;
-                            *(bf16x8_t *)(p.kc + ((hb + c) * p.pos_stride + pos) * 8) = olo;
-                            *(bf16x8_t *)(p.kc + ((hb + 8 + c) * p.pos_stride + pos) * 8) = ohi;
-                        }
-                    }
-                }
-            }
+            qkv_block_out(p, panel, m0 + wm * 128 + i * 16, n0, lane);
         }
         return;
     }
     if (EPI == EPI_SWIGLU) {
         // weight blocks 0..3 are gate rows, 4..7 the matching up rows: 64 output columns per wave
-        // row-major [M, N], or k-blocked: column c of row m at ((c / 32) * a_rows + m) * 32 + c % 32
-        const int c0 = tn * 128 + wn * 64 + (lane & 7) * 8;
-        bf16_t *out = (bf16_t *)p.C + (KB ? (size_t)(c0 >> 5) * p.a_rows * 32 + (c0 & 31) : (size_t)c0);
-        const size_t row_stride = KB ? 32 : (size_t)p.N;
 #pragma unroll
         for (int i = 0; i < 8; i++) {
-            const int mblock = m0 + wm * 128 + i * 16;
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < 4; j++) {
@@ -190,16 +208,7 @@ __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][8], const DmaGemmPara
                 for (int e = 0; e < 4; e++) v[e] = vla_silu_mul(g[e], u[e]);
                 *(f32x4_t *)panel_at(panel, l16, j * 4 + kq) = v;
             }
-#pragma unroll
-            for (int it = 0; it < 2; it++) {
-                const int row = it * 8 + (lane >> 3), c2 = lane & 7, m = mblock + row;
-                f32x4_t a = *(const f32x4_t *)panel_at(panel, row, 2 * c2);
-                f32x4_t b = *(const f32x4_t *)panel_at(panel, row, 2 * c2 + 1);
-                bf16x8_t o;
-#pragma unroll
-                for (int e = 0; e < 4; e++) { o[e] = (bf16_t)a[e]; o[4 + e] = (bf16_t)b[e]; }
-                if (m < p.M) *(bf16x8_t *)(out + (size_t)m * row_stride) = o;
-            }
+            swiglu_block_out<KB>(p, panel, m0 + wm * 128 + i * 16, tn * 128 + wn * 64, lane);
         }
         return;
     }
@@ -532,6 +541,189 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     }
 }
 
+
+template <int BASE, int STRIDE, int... I>
+__device__ __forceinline__ void read_frags(bf16x8_t (&f)[sizeof...(I)], int addr, std::integer_sequence<int, I...>) {
+    ((f[I] = lds_read<BASE + I * STRIDE>(addr)), ...);
+}
+template <int N>
+__device__ __forceinline__ void pass_frags(bf16x8_t (&f)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; i++) asm volatile("" : "+v"(f[i]));
+}
+
+// Small-tile form for products whose 256 x 256 tiles would leave most of the chip idle: BMT x BNT outputs (SwiGLU: half of
+// them gate, half up rows), 4 waves of a quarter each, one tile per workgroup, one or two workgroups per CU.  Same
+// operands, same v_mfma_f32_16x16x32_bf16 over K in the same order and the same epilogue arithmetic as the 256 x 256
+// kernel: results are identical bit for bit, so the choice between them (choose_tile) is one of speed alone.
+//
+// K moves in units of 64 through a ring of NS stages of (BMT + BNT) x 128 bytes: per unit one wait for this wave's loads,
+// one barrier, the load instructions of unit u + NS - 1, then the two halves' fragment reads, each under the other half's
+// MFMAs.  Bound by the loads: without any MFMA the kernel takes the same time, 51 GB/s per CU with one workgroup and
+// 72 GB/s with two (a CU on its own streams 58 GB/s from HBM however deep its ring), so what counts is the bytes per CU.
+// Workgroups of one XCD take neighbouring tile columns with all their tile rows: a weight panel is then fetched into one
+// L2 only (the activations, few rows, into all).
+template <int EPI, bool KB, int BMT, int BNT, int NS>
+__global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    constexpr int MB = BMT / 32, NB = BNT / 32;          // 16-row / 16-column blocks per wave
+    constexpr int A_HALF = BMT * 64, W_HALF = BNT * 64, SSTAGE = 2 * (A_HALF + W_HALF);
+    constexpr int NA = BMT / 32, NWI = BNT / 32;                // load instructions per wave and unit
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, kq = lane >> 4;
+    const int K = p.K, units = K / 64;
+    const int total = p.tiles_m * p.tiles_n, per_xcd = (total + 7) >> 3;
+    const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per_xcd || tile >= total || units < NS) return;
+    const int tn = tile / p.tiles_m, tm = tile - tn * p.tiles_m;
+
+    // ---- loads: an instruction covers 16 rows of one half (see the 256 x 256 kernel for the swizzle)
+    const int chunk_off = ((lane & 3) ^ ((lane >> 3) & 3)) << 4;
+    const int row_bytes = KB ? 64 : K * 2;
+    const unsigned a_half = KB ? (unsigned)p.a_rows * 64u : 64u, w_half = KB ? (unsigned)p.w_rows * 64u : 64u;
+    const int thread_off = (lane >> 2) * row_bytes + chunk_off;
+    const bf16_t *Wp;
+    int w_row0;
+    if (EPI == EPI_SWIGLU) {
+        Wp = (wave & 1) ? p.W1 : p.W0;                   // instruction blocks 0..3 gate rows, 4..7 up rows
+        w_row0 = tn * 64;
+    } else {
+        const int n = tn * BNT, seg = n / p.segN;
+        Wp = seg == 0 ? p.W0 : (seg == 1 ? p.W1 : p.W2);
+        w_row0 = n - seg * p.segN + (wave & 1) * (BNT / 2);
+    }
+    const size_t row_elems = KB ? 32 : (size_t)K;
+    const unsigned nh1 = (unsigned)(K / HK - 1);
+    const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(p.A + (size_t)tm * BMT * row_elems), (short)0, KB ? (int)(nh1 * a_half + BMT * 64u) : BMT * K * 2, 0x00020000);
+    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(Wp + (size_t)w_row0 * row_elems), (short)0, KB ? (int)(nh1 * w_half + BNT * 32u) : BNT * K, 0x00020000);   // (half the tile's rows: one wave's share)
+    auto load_unit = [&](int u, int stage) {
+        char *base = lds + stage * SSTAGE;
+#pragma unroll
+        for (int i = 0; i < NA; i++) {
+            const int q = wave * NA + i, half = q / (BMT / 16), blk = q % (BMT / 16);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)(base + half * A_HALF + blk * 1024), 16, thread_off,
+                                                     (int)((unsigned)(2 * u + half) * a_half) + blk * 16 * row_bytes, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < NWI; i++) {
+            const int half = wave >> 1, blk = (wave & 1) * NWI + i;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(base + 2 * A_HALF + half * W_HALF + blk * 1024), 16, thread_off,
+                                                     (int)((unsigned)(2 * u + half) * w_half) + i * 16 * row_bytes, 0, 0);
+        }
+    };
+
+    const int fsw = (l16 >> 1) & 3;
+    const int lds0 = (int)(size_t)(lds_void *)lds;
+    const int a_base = lds0 + (wm * (BMT / 2) + l16) * 64 + ((kq ^ fsw) << 4);
+    const int w_base = lds0 + 2 * A_HALF + (wn * (BNT / 2) + l16) * 64 + ((kq ^ fsw) << 4);
+    f32x4_t acc[NB][MB];
+#pragma unroll
+    for (int j = 0; j < NB; j++)
+#pragma unroll
+        for (int i = 0; i < MB; i++) acc[j][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    bf16x8_t af[2][MB], wf[2][NB];                       // (the first multiply, before any second half, adds zeros)
+#pragma unroll
+    for (int i = 0; i < MB; i++)
+#pragma unroll
+        for (int e = 0; e < 8; e++) af[1][i][e] = (bf16_t)0.f;
+#pragma unroll
+    for (int j = 0; j < NB; j++)
+#pragma unroll
+        for (int e = 0; e < 8; e++) wf[1][j][e] = (bf16_t)0.f;
+    auto multiply = [&](int h) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < NB; j++)
+#pragma unroll
+            for (int i = 0; i < MB; i++) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[h][j], af[h][i], acc[j][i], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // this wave's fragment reads have landed; the fragments pass through, so that no MFMA moves above the wait
+    auto wait_frags = [&](int h) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        pass_frags(wf[h]);
+        pass_frags(af[h]);
+    };
+
+#pragma unroll
+    for (int u = 0; u < NS - 1; u++) load_unit(u, u);
+    int stage = 0;
+    for (int u = 0; u < units; u++) {
+        // unit u has landed when at most the NS - 2 units after it are in flight (towards the end: when nothing is)
+        if (u + NS - 2 < units) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * (NA + NWI)) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        asm volatile("s_barrier" ::: "memory");         // ... for every wave, and everyone's reads of unit u - 1 are done
+        const int prev = stage == 0 ? NS - 1 : stage - 1;
+        if (u + NS - 1 < units) load_unit(u + NS - 1, prev);
+        const int so = stage * SSTAGE;
+        // first half's fragments while the second half of unit u - 1 multiplies, then the other way round
+        read_frags<0, 1024>(wf[0], w_base + so, std::make_integer_sequence<int, NB>{});
+        read_frags<0, 1024>(af[0], a_base + so, std::make_integer_sequence<int, MB>{});
+        multiply(1);
+        wait_frags(0);
+        read_frags<W_HALF, 1024>(wf[1], w_base + so, std::make_integer_sequence<int, NB>{});
+        read_frags<A_HALF, 1024>(af[1], a_base + so, std::make_integer_sequence<int, MB>{});
+        multiply(0);
+        wait_frags(1);
+        stage = stage == NS - 1 ? 0 : stage + 1;
+    }
+    multiply(1);
+    // ---- output: the whole tile as fp32 through LDS, then each wave takes 16-row blocks
+    asm volatile("s_barrier" ::: "memory");
+    float *panel = (float *)lds;
+#pragma unroll
+    for (int j = 0; j < NB; j++)
+#pragma unroll
+        for (int i = 0; i < MB; i++)
+            *(f32x4_t *)panel_at(panel + (wm * MB + i) * 16 * 128, l16, wn * (NB * 4) + j * 4 + kq) = acc[j][i];
+    __syncthreads();
+    const int m0 = tm * BMT;
+#pragma unroll
+    for (int b = wave; b < BMT / 16; b += 4) {
+        float *pb = panel + b * 16 * 128;
+        const int mblock = m0 + b * 16;
+        if (mblock >= p.M) break;
+        if (EPI == EPI_QKV_ROPE) {
+            qkv_block_out(p, pb, mblock, tn * 128, lane);
+        } else if (EPI == EPI_SWIGLU) {
+#pragma unroll
+            for (int it = 0; it < 2; it++) {
+                const int row = it * 8 + (lane >> 3), c2 = lane & 7;
+#pragma unroll
+                for (int u = 0; u < 2; u++) {            // a lane's own eight columns, in place
+                    float *gp = panel_at(pb, row, 2 * c2 + u);
+                    f32x4_t g = *(const f32x4_t *)gp;
+                    const f32x4_t up = *(const f32x4_t *)panel_at(pb, row, 16 + 2 * c2 + u);
+#pragma unroll
+                    for (int e = 0; e < 4; e++) g[e] = vla_silu_mul(g[e], up[e]);
+                    *(f32x4_t *)gp = g;
+                }
+            }
+            swiglu_block_out<KB>(p, pb, mblock, tn * 64, lane);
+        } else {
+            constexpr int LPR = BNT / 4, RPI = 64 / LPR;      // lanes per row, rows per instruction
+            float *out = (float *)p.C + (size_t)mblock * p.N + (size_t)tn * BNT + (lane % LPR) * 4;
+#pragma unroll
+            for (int it = 0; it < 16 / RPI; it++) {
+                const int row = it * RPI + lane / LPR;
+                f32x4_t v = *(const f32x4_t *)panel_at(pb, row, lane % LPR);
+                if (mblock + row < p.M) {
+                    f32x4_t *dst = (f32x4_t *)(out + (size_t)row * p.N);
+                    if (EPI == EPI_RESIDUAL) {
+                        const f32x4_t x = *dst;
+#pragma unroll
+                        for (int e = 0; e < 4; e++) v[e] += x[e];
+                    }
+                    *dst = v;
+                }
+            }
+        }
+    }
+}
+
 template <int EPI, bool KB, bool UB = false>
 int launch_plain(const DmaGemmParams &p, hipStream_t st) {
     static bool attr_set = false;
@@ -569,8 +761,68 @@ int launch(const DmaGemmParams &p, hipStream_t st) {
     return launch_plain<EPI, KB, UB>(p, st);
 }
 
+template <int EPI, bool KB, int BMT, int BNT, int NS>
+int launch_small(DmaGemmParams p, hipStream_t st) {
+    static bool attr_set = false;
+    const size_t lds = (size_t)NS * 2 * (BMT * 64 + BNT * 64);
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_small_kernel<EPI, KB, BMT, BNT, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) {
+            vla_set_error("hipFuncSetAttribute(gemm_bf16_small) failed: %s", hipGetErrorString(e));
+            return VLA_EHIP;
+        }
+        attr_set = true;
+    }
+    p.tiles_m = (p.M + BMT - 1) / BMT;
+    p.tiles_n = EPI == EPI_SWIGLU ? p.N / (BNT / 2) : p.N / BNT;
+    const int per_xcd = (p.tiles_m * p.tiles_n + 7) / 8;
+    gemm_bf16_small_kernel<EPI, KB, BMT, BNT, NS><<<8 * per_xcd, 256, lds, st>>>(p);
+    int rc = vla_check_launch("gemm_bf16_small");
+    return rc ? rc : 1;
+}
+
+// Which kernel takes a product of M rows, N columns (tile columns are 128 weight rows; SwiGLU counts gate and up) and K:
+// 0 the 256 x 256 one, else a small tile.  All give the same bits; the rule compares estimates in ns, fitted to what the
+// four projections of the 7B shape took at 64 .. 6912 rows (per unit of K = 64 and launch):
+//   256 x 256       a round of 256 tiles 1350 per unit + 8000 (prologue and epilogue)
+//   64 x 64         310 up to 150 tiles, then 120 + 1.25 per tile (plain and residual outputs only)
+//   64 x 128        470 up to 276 tiles, then 1.7 per tile
+//   128 x 128       640 with one workgroup per CU (3 stages of LDS), 950 for every 512 with two (2 stages)
+// E.g. 288 rows, K = 4096: QKV 99 -> 55 us, O 89 -> 33, gate/up 109 -> 100, down (K = 11008) 217 -> 79; 1728 rows: O 96 -> 71.
+enum SmallTile { TILE_256 = 0, TILE_64x64, TILE_64x128, TILE_128x128_1, TILE_128x128_2 };
+template <int EPI>
+SmallTile choose_tile(const DmaGemmParams &p) {
+    const long units = p.K / 64, cols = EPI == EPI_SWIGLU ? 2L * p.N : p.N;
+    const long t256 = (p.M + 255L) / 256 * (cols / 256), t64 = (p.M + 63L) / 64 * (cols / 128), t128 = (p.M + 127L) / 128 * (cols / 128);
+    SmallTile best = TILE_256;
+    long best_ns = (t256 + 255) / 256 * (1350 * units + 8000);
+    auto offer = [&](SmallTile tile, long ns) {
+        if (ns < best_ns) { best = tile; best_ns = ns; }
+    };
+    if (EPI == EPI_STORE || EPI == EPI_RESIDUAL) offer(TILE_64x64, units * (2 * t64 <= 150 ? 310 : 120 + 5 * (2 * t64) / 4));
+    offer(TILE_64x128, units * (t64 <= 276 ? 470 : 17 * t64 / 10));
+    if (t128 <= 256) offer(TILE_128x128_1, units * 640);
+    offer(TILE_128x128_2, units * 950 * ((t128 + 511) / 512));
+    return best;
+}
+
+template <int EPI, bool KB>
+int launch_tile(const DmaGemmParams &p, SmallTile tile, hipStream_t st) {
+    const double flops = 2.0 * p.M * p.K * (EPI == EPI_SWIGLU ? 2.0 * p.N : (double)p.N);
+    ProfScope ps(EPI == EPI_SWIGLU ? "gemm_small<swiglu>" : EPI == EPI_RESIDUAL ? "gemm_small<residual>"
+                 : EPI == EPI_QKV_ROPE ? "gemm_small<qkv_rope>" : "gemm_small<store>", flops, st);
+    if constexpr (EPI == EPI_STORE || EPI == EPI_RESIDUAL) {
+        if (tile == TILE_64x64) return launch_small<EPI, KB, 64, 64, 4>(p, st);
+    }
+    if (tile == TILE_64x128) return launch_small<EPI, KB, 64, 128, 3>(p, st);
+    if (tile == TILE_128x128_1) return launch_small<EPI, KB, 128, 128, 3>(p, st);
+    return launch_small<EPI, KB, 128, 128, 2>(p, st);
+}
+
 template <int EPI>
 int launch_kb(const DmaGemmParams &p, bool kb, hipStream_t st) {
+    const SmallTile tile = choose_tile<EPI>(p);
+    if (tile != TILE_256) return kb ? launch_tile<EPI, true>(p, tile, st) : launch_tile<EPI, false>(p, tile, st);
     // The unit-barrier schedule pays for the gate/up projection (3.7 % faster at M = 73728: 10.03 against 10.41 ms);
     // the QKV and down projections run the same with either and the O projection, whose short tiles end in the
     // heaviest epilogue, 5 % slower.
