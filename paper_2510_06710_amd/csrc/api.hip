@@ -232,6 +232,8 @@ static int run_gemm(const vla_config &c, GemmArgs g, void *skinny_scratch, hipSt
                 r = try_gemm_bf16_dma_splitk(g, skinny_scratch, sb, st);
                 if (r == 0) r = try_gemm_bf16_mid(g, skinny_scratch, sb, st);
             }
+            // (not for the tail rows of a recompute, whose result must not depend on how many rollouts share the pass)
+            if (r == 0 && g.step) r = try_gemm_bf16_stream(g, st);
             if (r == 0) r = try_gemm_bf16_skinny(g, skinny_scratch, st);
         }
         if (r != 0) return r < 0 ? r : 0;
@@ -410,6 +412,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         GemmArgs g{};
         g.A = ws.Nrm; g.W[0] = lw.wq; g.W[1] = lw.wk; g.W[2] = lw.wv; g.n_seg = 3; g.segN = H;
         g.C = ws.QKV; g.M = M; g.K = H; g.epilogue = EPI_STORE; g.a_rows = ws.a_rows;
+        g.step = ra.R == 1;
         if (pk) { g.Wkb[0] = pk->wq; g.Wkb[1] = pk->wk; g.Wkb[2] = pk->wv; }
         // multi-row bf16 forwards at head_dim 128: rotation and KV write ride the projection's epilogue
         int fused = 0;
@@ -440,6 +443,8 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         if (!done && (rc = launch_attention_generic<T>((T *)ws.AO, (const T *)ws.Q, kv, kl, ra, H, st))) return rc;
         g = GemmArgs{};
         g.A = ws.AO; g.W[0] = lw.wo; g.n_seg = 1; g.segN = H; g.C = ws.X; g.M = M; g.K = H; g.epilogue = EPI_RESIDUAL; g.a_rows = ws.a_rows;
+        g.step = ra.R == 1;
+        if (pk) g.Wkb[0] = pk->wo;
         ds = 0;
         if (fuse_reduce) g.deferred_splits = &ds;
         if ((rc = run_gemm<T>(c, g, ws.skinny, st))) return rc;
@@ -451,10 +456,13 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         g = GemmArgs{};
         g.A = ws.Nrm; g.W[0] = lw.w_gate; g.W[1] = lw.w_up; g.n_seg = 2; g.segN = F; g.C = ws.ACT; g.M = M; g.K = H;
         g.epilogue = EPI_SWIGLU; g.a_rows = ws.a_rows;
+        g.step = ra.R == 1;
         if (pk) { g.Wkb[0] = pk->w_gate; g.Wkb[1] = pk->w_up; }
         if ((rc = run_gemm<T>(c, g, ws.skinny, st))) return rc;
         g = GemmArgs{};
         g.A = ws.ACT; g.W[0] = lw.w_down; g.n_seg = 1; g.segN = H; g.C = ws.X; g.M = M; g.K = F; g.epilogue = EPI_RESIDUAL; g.a_rows = ws.a_rows;
+        g.step = ra.R == 1;
+        if (pk) g.Wkb[0] = pk->w_down;
         ds = 0;
         if (fuse_reduce) g.deferred_splits = &ds;
         if ((rc = run_gemm<T>(c, g, ws.skinny, st))) return rc;

@@ -65,6 +65,7 @@ struct GemmArgs {
                             // on its own) and a SwiGLU output are stored [K / 32][rows][32]: direct-to-LDS kernel only
     int a_rows;             // rows of A that may be read (>= M; contents past M arbitrary): the MFMA kernel
                             // loads whole 256-row tiles and declines if the buffer does not cover them
+    int step;               // a decode step (one row per sequence): the weight-streaming kernel of few rows may take it
     int *deferred_splits;   // not NULL (EPI_STORE and EPI_RESIDUAL of the split-K kernels): the kernel leaves its n
                             // partial products [n][M][N] at the start of the scratch buffer, puts n here and does not
                             // reduce them (the caller's next kernel adds them in order); 0 here: C is complete
@@ -180,6 +181,7 @@ int try_reduce_residual_rmsnorm_bf16(bf16_t *out, float *X, const float *P, int 
                                      float eps, hipStream_t st);
 // kb_rows = 0: row-major output [M, H]; else k-blocked [H / 32][kb_rows][32]
 int try_rmsnorm_bf16(bf16_t *out, const float *X, const float *gain, int M, int H, float eps, int kb_rows, hipStream_t st);
+int try_gemm_bf16_stream(const GemmArgs &g, hipStream_t st);
 int try_gemm_bf16_skinny(const GemmArgs &g, void *scratch, hipStream_t st);
 int try_gemm_bf16_mid(const GemmArgs &g, void *scratch, size_t scratch_bytes, hipStream_t st);
 int launch_splitk_reduce(int epilogue, void *C, const float *P, int splits, int M, int N, hipStream_t st);
