@@ -27,35 +27,74 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
-// One 256-thread workgroup per (sequence, head) pair; its four waves split the keys.
-template <int D>
-__global__ void __launch_bounds__(256) attn_decode_kernel(bf16_t *out, const bf16_t *qbuf, const bf16_t *kc,
-                                                         const bf16_t *vc, int n_heads, int nk, int pos_stride,
-                                                         int H) {
+// What the projection left for this step (FUSE): `splits` partial copies of the fp32 [n_seq, 3H] QKV rows, added in order.
+struct FusedQkv {
+    const float *qkv;
+    int splits;
+    size_t split_stride;
+    const float2 *table;       // (cos, sin) of this position
+};
+
+// One workgroup of NWV waves per (sequence, head) pair; the waves split the keys.  FUSE: the workgroup also adds up its
+// head's q, k, v, rotates q and k and writes k and v to the cache (the rounding of rope_kv_write_bf16_kernel); the new
+// position's k and v are then taken from LDS.
+template <int D, int NWV, bool FUSE>
+__global__ void __launch_bounds__(64 * NWV) attn_decode_kernel(bf16_t *out, const bf16_t *qbuf, bf16_t *kc, bf16_t *vc, FusedQkv f,
+                                                              int n_heads, int nk, int pos_stride, int H) {
     constexpr int DC = D / 8;        // 16-byte chunks per head vector
     constexpr int RPI = 64 / DC;     // V rows per wave load instruction
-    constexpr int CPW = MAXCH / 4;   // key chunks of 64 per wave (chunk index = 4 * it + wave)
+    constexpr int CPW = MAXCH / NWV; // key chunks of 64 per wave (chunk index = NWV * it + wave)
     __shared__ __attribute__((aligned(16))) float qs[D];
+    __shared__ __attribute__((aligned(16))) bf16_t knew[D], vnew[D];
     __shared__ float ps[MAXCH * 64];
-    __shared__ float red[8];
-    __shared__ __attribute__((aligned(16))) float part[4][D];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ float red[2 * NWV];
+    __shared__ __attribute__((aligned(16))) float part[NWV][D];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int item = blockIdx.x;
     const int s = item / n_heads, h = item - s * n_heads;
-    const bf16_t *q = qbuf + (size_t)s * H + (size_t)h * D;
     const float scale = 1.0f / sqrtf((float)D);
-    if (threadIdx.x < D) qs[threadIdx.x] = (float)q[threadIdx.x] * scale;
+    bf16_t *kh = kc + (size_t)item * D * pos_stride;
+    bf16_t *vh = vc + (size_t)item * pos_stride * D;
+    const int n_old = FUSE ? nk - 1 : nk;                   // positions read from the cache
+    if (FUSE) {
+        float *raw = &part[0][0];                           // q, k of the head before the rotation (D floats each)
+        static_assert(NWV >= 2, "raw needs two rows of `part`");
+        float v = 0.f;
+        if (t < D) {
+            const float *src = f.qkv + (size_t)s * 3 * H + (size_t)h * D + t;
+            float q = src[0], k = src[H];
+            v = src[2 * (size_t)H];
+            for (int i = 1; i < f.splits; i++) {
+                const float *p = src + (size_t)i * f.split_stride;
+                q += p[0]; k += p[H]; v += p[2 * (size_t)H];
+            }
+            raw[t] = q; raw[D + t] = k;
+        }
+        __syncthreads();
+        if (t < D) {
+            const int half = D / 2, i = t & (half - 1);
+            const float2 cs = f.table[i];
+            const float qa = raw[i], qb = raw[i + half], ka = raw[D + i], kb = raw[D + i + half];
+            const bf16_t qr = (bf16_t)(t < half ? qa * cs.x - qb * cs.y : qb * cs.x + qa * cs.y);
+            const bf16_t kr = (bf16_t)(t < half ? ka * cs.x - kb * cs.y : kb * cs.x + ka * cs.y);
+            qs[t] = (float)qr * scale;
+            knew[t] = kr; vnew[t] = (bf16_t)v;
+            kh[((size_t)(t >> 3) * pos_stride + nk - 1) * 8 + (t & 7)] = kr;
+            vh[(size_t)(nk - 1) * D + t] = (bf16_t)v;
+        }
+    } else if (t < D) {
+        qs[t] = (float)qbuf[(size_t)s * H + (size_t)h * D + t] * scale;
+    }
     __syncthreads();
 
-    // ---- 1. scores: wave w owns key chunks w, w + 4, ...; lane p one position of each --------------
-    const bf16_t *kh = kc + (size_t)item * D * pos_stride;
+    // ---- 1. scores: wave w owns key chunks w, w + NWV, ...; lane p one position of each --------------
     float sc[CPW];
     float mx = -INFINITY;
 #pragma unroll
     for (int it = 0; it < CPW; it++) {
         sc[it] = -INFINITY;
-        const int p = (it * 4 + wave) * 64 + lane;
-        if (p < nk) {
+        const int p = (it * NWV + wave) * 64 + lane;
+        if (p < n_old) {
             float a = 0.f;
 #pragma unroll
             for (int c = 0; c < DC; c++) {
@@ -71,11 +110,21 @@ __global__ void __launch_bounds__(256) attn_decode_kernel(bf16_t *out, const bf1
             mx = fmaxf(mx, a);
         }
     }
+    if (FUSE && (n_old >> 6) % NWV == wave) {               // the new position: the wave that owns it, dims across the lanes
+        float a = 0.f;
+#pragma unroll
+        for (int i = 0; i < D; i += 64) a += qs[i + lane] * (float)knew[i + lane];
+        a = wave_sum(a);
+#pragma unroll
+        for (int it = 0; it < CPW; it++)
+            if (it == (n_old >> 6) / NWV && lane == (n_old & 63)) { sc[it] = a; mx = fmaxf(mx, a); }
+    }
     // ---- 2. softmax over all keys of the workgroup ---------------------------------------------------
     mx = wave_max(mx);
     if (lane == 0) red[wave] = mx;
     __syncthreads();
-    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));     // key 0 exists, so this is finite
+#pragma unroll
+    for (int w = 0; w < NWV; w++) mx = fmaxf(mx, red[w]);          // key 0 exists, so this is finite
     float sum = 0.f;
 #pragma unroll
     for (int it = 0; it < CPW; it++) {
@@ -84,24 +133,32 @@ __global__ void __launch_bounds__(256) attn_decode_kernel(bf16_t *out, const bf1
         sum += e;
     }
     sum = wave_sum(sum);
-    if (lane == 0) red[4 + wave] = sum;
+    if (lane == 0) red[NWV + wave] = sum;
     __syncthreads();
-    const float inv = 1.0f / (red[4] + red[5] + red[6] + red[7]);
+    float tot = red[NWV];
+#pragma unroll
+    for (int w = 1; w < NWV; w++) tot += red[NWV + w];
+    const float inv = 1.0f / tot;
 #pragma unroll
     for (int it = 0; it < CPW; it++) {
-        const int p = (it * 4 + wave) * 64 + lane;
+        const int p = (it * NWV + wave) * 64 + lane;
         if (p < nk) ps[p] = sc[it] * inv;
     }
     __syncthreads();
 
-    // ---- 3. P.V: the workgroup covers 4 * RPI rows per step, wave w rows w * RPI + g ------------------
-    const bf16_t *vh = vc + (size_t)item * pos_stride * D;
+    // ---- 3. P.V: the workgroup covers NWV * RPI rows per step, wave w rows w * RPI + g ------------------
     const int c = lane % DC, g = lane / DC;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-    for (int pos = wave * RPI + g; pos < nk; pos += 4 * RPI) {
+    for (int pos = wave * RPI + g; pos < n_old; pos += NWV * RPI) {
         bf16x8_t v = *(const bf16x8_t *)(vh + (size_t)pos * D + c * 8);
         const float pr = ps[pos];
+#pragma unroll
+        for (int e = 0; e < 8; e++) acc[e] += pr * (float)v[e];
+    }
+    if (FUSE && wave == 0 && g == 0) {
+        const bf16x8_t v = *(const bf16x8_t *)&vnew[c * 8];
+        const float pr = ps[n_old];
 #pragma unroll
         for (int e = 0; e < 8; e++) acc[e] += pr * (float)v[e];
     }
@@ -114,33 +171,64 @@ __global__ void __launch_bounds__(256) attn_decode_kernel(bf16_t *out, const bf1
         for (int e = 0; e < 8; e++) part[wave][c * 8 + e] = acc[e];
     }
     __syncthreads();
-    if (threadIdx.x < DC) {
+    if (t < DC) {
         bf16x8_t o;
 #pragma unroll
         for (int e = 0; e < 8; e++) {
-            const int i = threadIdx.x * 8 + e;
-            o[e] = (bf16_t)((part[0][i] + part[1][i]) + (part[2][i] + part[3][i]));
+            const int i = t * 8 + e;
+            float v[NWV];
+#pragma unroll
+            for (int w = 0; w < NWV; w++) v[w] = part[w][i];
+#pragma unroll
+            for (int st = 1; st < NWV; st *= 2)
+#pragma unroll
+                for (int w = 0; w + st < NWV; w += 2 * st) v[w] += v[w + st];
+            o[e] = (bf16_t)v[0];
         }
-        *(bf16x8_t *)(out + (size_t)s * H + (size_t)h * D + threadIdx.x * 8) = o;
+        *(bf16x8_t *)(out + (size_t)s * H + (size_t)h * D + t * 8) = o;
     }
 }
 
+// Few pairs: eight waves each, with the projection's sum, rotation and KV write on board.  The step of one environment (32
+// pairs, 290 keys) is a chain of launches and memory latencies: 14.5 us with four waves and 9.5 in the kernel before, 8.6 us
+// now; 13 environments 17.4 + 9.5 -> 18 us.  From FEW_PAIRS on the chip is full with four waves, and the extra
+// latency ahead of the first key costs more than the launch (2048 pairs 62 + 5 against 74 us, 8192 225 + 13 against 271).
+constexpr int FEW_PAIRS = 1024;
+
 }  // namespace
+
+static bool decode_shape_ok(const KvView &kv, const RowsArgs &ra) {
+    return ra.R == 1 && ra.pos0 + 1 <= MAXCH * 64 && (kv.d == 64 || kv.d == 128);
+}
 
 int try_attention_decode_bf16(bf16_t *out, const bf16_t *q, const KvView &kv, int layer, const RowsArgs &ra,
                               int H, hipStream_t st) {
-    const int nk = ra.pos0 + 1;
-    if (ra.R != 1 || nk > MAXCH * 64 || (kv.d != 64 && kv.d != 128)) return 0;
-    const int n_items = ra.n_seq * kv.n_heads;
+    if (!decode_shape_ok(kv, ra)) return 0;
+    const int nk = ra.pos0 + 1, n_items = ra.n_seq * kv.n_heads;
     if (n_items == 0) return 1;
-    const bf16_t *kc = (const bf16_t *)kv.k + (size_t)layer * kv.layer_elems;
-    const bf16_t *vc = (const bf16_t *)kv.v + (size_t)layer * kv.layer_elems;
+    bf16_t *kc = (bf16_t *)kv.k + (size_t)layer * kv.layer_elems, *vc = (bf16_t *)kv.v + (size_t)layer * kv.layer_elems;
     // algorithmic bytes: K and V tiles of every (sequence, head) pair, read once
     ProfScope ps("attn_decode", 2.0 * n_items * (double)nk * kv.d * 2.0, st);
-    if (kv.d == 128)
-        attn_decode_kernel<128><<<n_items, 256, 0, st>>>(out, q, kc, vc, kv.n_heads, nk, kv.pos_stride, H);
-    else
-        attn_decode_kernel<64><<<n_items, 256, 0, st>>>(out, q, kc, vc, kv.n_heads, nk, kv.pos_stride, H);
+    if (kv.d == 128) attn_decode_kernel<128, 4, false><<<n_items, 256, 0, st>>>(out, q, kc, vc, FusedQkv{}, kv.n_heads, nk, kv.pos_stride, H);
+    else attn_decode_kernel<64, 4, false><<<n_items, 256, 0, st>>>(out, q, kc, vc, FusedQkv{}, kv.n_heads, nk, kv.pos_stride, H);
     int rc = vla_check_launch("attn_decode");
     return rc ? rc : 1;
+}
+
+bool attention_decode_fuses_qkv(const KvView &kv, const RowsArgs &ra) {
+    return decode_shape_ok(kv, ra) && ra.n_seq * kv.n_heads < FEW_PAIRS;
+}
+
+// The decode step's attention straight from the QKV projection: `splits` partial copies of the fp32 [n_seq, 3H] rows,
+// `split_stride` floats apart.  Only where attention_decode_fuses_qkv().
+int launch_attention_decode_qkv(bf16_t *out, const float *qkv, int splits, size_t split_stride, const float2 *table, const KvView &kv,
+                                int layer, const RowsArgs &ra, int H, hipStream_t st) {
+    const int nk = ra.pos0 + 1, n_items = ra.n_seq * kv.n_heads;
+    if (n_items == 0) return 0;
+    bf16_t *kc = (bf16_t *)kv.k + (size_t)layer * kv.layer_elems, *vc = (bf16_t *)kv.v + (size_t)layer * kv.layer_elems;
+    ProfScope ps("attn_decode", 2.0 * n_items * (double)nk * kv.d * 2.0, st);
+    const FusedQkv f{qkv, splits, split_stride, table};
+    if (kv.d == 128) attn_decode_kernel<128, 8, true><<<n_items, 512, 0, st>>>(out, nullptr, kc, vc, f, kv.n_heads, nk, kv.pos_stride, H);
+    else attn_decode_kernel<64, 8, true><<<n_items, 512, 0, st>>>(out, nullptr, kc, vc, f, kv.n_heads, nk, kv.pos_stride, H);
+    return vla_check_launch("attn_decode_qkv");
 }

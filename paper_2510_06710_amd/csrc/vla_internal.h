@@ -191,6 +191,9 @@ int try_attention_prefill_bf16(bf16_t *out, const bf16_t *q, const KvView &kv, i
                                const RowsArgs &ra, int H, void *vt_scratch, int out_kb_rows, hipStream_t st);
 int try_attention_decode_bf16(bf16_t *out, const bf16_t *q, const KvView &kv, int layer,
                               const RowsArgs &ra, int H, hipStream_t st);
+bool attention_decode_fuses_qkv(const KvView &kv, const RowsArgs &ra);
+int launch_attention_decode_qkv(bf16_t *out, const float *qkv, int splits, size_t split_stride, const float2 *table, const KvView &kv,
+                                int layer, const RowsArgs &ra, int H, hipStream_t st);
 size_t attention_prefill_scratch_bytes(int n_seq, int n_heads, int d, int n_keys);
 
 int vla_check_launch(const char *what);
