@@ -234,6 +234,7 @@ static int run_gemm(const vla_config &c, GemmArgs g, void *skinny_scratch, hipSt
             }
             // (not for the tail rows of a recompute, whose result must not depend on how many rollouts share the pass)
             if (r == 0 && g.step) r = try_gemm_bf16_stream(g, st);
+            if (r == 0 && g.step) r = try_gemm_bf16_dma_step(g, st);
             if (r == 0) r = try_gemm_bf16_skinny(g, skinny_scratch, st);
         }
         if (r != 0) return r < 0 ? r : 0;

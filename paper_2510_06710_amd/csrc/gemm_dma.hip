@@ -563,7 +563,7 @@ __device__ __forceinline__ void pass_frags(bf16x8_t (&f)[N]) {
 // 72 GB/s with two (a CU on its own streams 58 GB/s from HBM however deep its ring), so what counts is the bytes per CU.
 // Workgroups of one XCD take neighbouring tile columns with all their tile rows: a weight panel is then fetched into one
 // L2 only (the activations, few rows, into all).
-template <int EPI, bool KB, int BMT, int BNT, int NS>
+template <int EPI, bool KB, bool WKB, int BMT, int BNT, int NS>
 __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int MB = BMT / 32, NB = BNT / 32;          // 16-row / 16-column blocks per wave
@@ -579,9 +579,9 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
 
     // ---- loads: an instruction covers 16 rows of one half (see the 256 x 256 kernel for the swizzle)
     const int chunk_off = ((lane & 3) ^ ((lane >> 3) & 3)) << 4;
-    const int row_bytes = KB ? 64 : K * 2;
-    const unsigned a_half = KB ? (unsigned)p.a_rows * 64u : 64u, w_half = KB ? (unsigned)p.w_rows * 64u : 64u;
-    const int thread_off = (lane >> 2) * row_bytes + chunk_off;
+    const int row_bytes = KB ? 64 : K * 2, w_row_bytes = WKB ? 64 : K * 2;
+    const unsigned a_half = KB ? (unsigned)p.a_rows * 64u : 64u, w_half = WKB ? (unsigned)p.w_rows * 64u : 64u;
+    const int thread_off = (lane >> 2) * row_bytes + chunk_off, w_thread_off = (lane >> 2) * w_row_bytes + chunk_off;
     const bf16_t *Wp;
     int w_row0;
     if (EPI == EPI_SWIGLU) {
@@ -592,12 +592,12 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
         Wp = seg == 0 ? p.W0 : (seg == 1 ? p.W1 : p.W2);
         w_row0 = n - seg * p.segN + (wave & 1) * (BNT / 2);
     }
-    const size_t row_elems = KB ? 32 : (size_t)K;
+    const size_t row_elems = KB ? 32 : (size_t)K, w_row_elems = WKB ? 32 : (size_t)K;
     const unsigned nh1 = (unsigned)(K / HK - 1);
     const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(p.A + (size_t)tm * BMT * row_elems), (short)0, KB ? (int)(nh1 * a_half + BMT * 64u) : BMT * K * 2, 0x00020000);
     const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(Wp + (size_t)w_row0 * row_elems), (short)0, KB ? (int)(nh1 * w_half + BNT * 32u) : BNT * K, 0x00020000);   // (half the tile's rows: one wave's share)
+        (void *)(Wp + (size_t)w_row0 * w_row_elems), (short)0, WKB ? (int)(nh1 * w_half + BNT * 32u) : BNT * K, 0x00020000);   // (half the tile's rows: one wave's share)
     auto load_unit = [&](int u, int stage) {
         char *base = lds + stage * SSTAGE;
 #pragma unroll
@@ -609,8 +609,8 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
 #pragma unroll
         for (int i = 0; i < NWI; i++) {
             const int half = wave >> 1, blk = (wave & 1) * NWI + i;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(base + 2 * A_HALF + half * W_HALF + blk * 1024), 16, thread_off,
-                                                     (int)((unsigned)(2 * u + half) * w_half) + i * 16 * row_bytes, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(base + 2 * A_HALF + half * W_HALF + blk * 1024), 16, w_thread_off,
+                                                     (int)((unsigned)(2 * u + half) * w_half) + i * 16 * w_row_bytes, 0, 0);
         }
     };
 
@@ -761,12 +761,12 @@ int launch(const DmaGemmParams &p, hipStream_t st) {
     return launch_plain<EPI, KB, UB>(p, st);
 }
 
-template <int EPI, bool KB, int BMT, int BNT, int NS>
+template <int EPI, bool KB, bool WKB, int BMT, int BNT, int NS>
 int launch_small(DmaGemmParams p, hipStream_t st) {
     static bool attr_set = false;
     const size_t lds = (size_t)NS * 2 * (BMT * 64 + BNT * 64);
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_small_kernel<EPI, KB, BMT, BNT, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_small_kernel<EPI, KB, WKB, BMT, BNT, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) {
             vla_set_error("hipFuncSetAttribute(gemm_bf16_small) failed: %s", hipGetErrorString(e));
             return VLA_EHIP;
@@ -776,7 +776,7 @@ int launch_small(DmaGemmParams p, hipStream_t st) {
     p.tiles_m = (p.M + BMT - 1) / BMT;
     p.tiles_n = EPI == EPI_SWIGLU ? p.N / (BNT / 2) : p.N / BNT;
     const int per_xcd = (p.tiles_m * p.tiles_n + 7) / 8;
-    gemm_bf16_small_kernel<EPI, KB, BMT, BNT, NS><<<8 * per_xcd, 256, lds, st>>>(p);
+    gemm_bf16_small_kernel<EPI, KB, WKB, BMT, BNT, NS><<<8 * per_xcd, 256, lds, st>>>(p);
     int rc = vla_check_launch("gemm_bf16_small");
     return rc ? rc : 1;
 }
@@ -786,7 +786,7 @@ int launch_small(DmaGemmParams p, hipStream_t st) {
 // four projections of the 7B shape took at 64 .. 6912 rows (per unit of K = 64 and launch):
 //   256 x 256       a round of 256 tiles 1350 per unit + 8000 (prologue and epilogue)
 //   64 x 64         310 up to 150 tiles, then 120 + 1.25 per tile (plain and residual outputs only)
-//   64 x 128        470 up to 276 tiles, then 1.7 per tile
+//   64 x 128        470 up to 276 tiles, then 1.7 per tile (SwiGLU, two weight panels per tile: 620, at least 1000)
 //   128 x 128       640 with one workgroup per CU (3 stages of LDS), 950 for every 512 with two (2 stages)
 // E.g. 288 rows, K = 4096: QKV 99 -> 55 us, O 89 -> 33, gate/up 109 -> 100, down (K = 11008) 217 -> 79; 1728 rows: O 96 -> 71.
 enum SmallTile { TILE_256 = 0, TILE_64x64, TILE_64x128, TILE_128x128_1, TILE_128x128_2 };
@@ -800,23 +800,24 @@ SmallTile choose_tile(const DmaGemmParams &p) {
         if (ns < best_ns) { best = tile; best_ns = ns; }
     };
     if (EPI == EPI_STORE || EPI == EPI_RESIDUAL) offer(TILE_64x64, units * (2 * t64 <= 150 ? 310 : 120 + 5 * (2 * t64) / 4));
-    offer(TILE_64x128, units * (t64 <= 276 ? 470 : 17 * t64 / 10));
+    if (EPI == EPI_SWIGLU) offer(TILE_64x128, units * (t64 <= 276 ? 620 : t64 <= 588 ? 1000 : 17 * t64 / 10));
+    else offer(TILE_64x128, units * (t64 <= 276 ? 470 : 17 * t64 / 10));
     if (t128 <= 256) offer(TILE_128x128_1, units * 640);
     offer(TILE_128x128_2, units * 950 * ((t128 + 511) / 512));
     return best;
 }
 
-template <int EPI, bool KB>
+template <int EPI, bool KB, bool WKB = KB>
 int launch_tile(const DmaGemmParams &p, SmallTile tile, hipStream_t st) {
     const double flops = 2.0 * p.M * p.K * (EPI == EPI_SWIGLU ? 2.0 * p.N : (double)p.N);
     ProfScope ps(EPI == EPI_SWIGLU ? "gemm_small<swiglu>" : EPI == EPI_RESIDUAL ? "gemm_small<residual>"
                  : EPI == EPI_QKV_ROPE ? "gemm_small<qkv_rope>" : "gemm_small<store>", flops, st);
     if constexpr (EPI == EPI_STORE || EPI == EPI_RESIDUAL) {
-        if (tile == TILE_64x64) return launch_small<EPI, KB, 64, 64, 4>(p, st);
+        if (tile == TILE_64x64) return launch_small<EPI, KB, WKB, 64, 64, 4>(p, st);
     }
-    if (tile == TILE_64x128) return launch_small<EPI, KB, 64, 128, 3>(p, st);
-    if (tile == TILE_128x128_1) return launch_small<EPI, KB, 128, 128, 3>(p, st);
-    return launch_small<EPI, KB, 128, 128, 2>(p, st);
+    if (tile == TILE_64x128) return launch_small<EPI, KB, WKB, 64, 128, 3>(p, st);
+    if (tile == TILE_128x128_1) return launch_small<EPI, KB, WKB, 128, 128, 3>(p, st);
+    return launch_small<EPI, KB, WKB, 128, 128, 2>(p, st);
 }
 
 template <int EPI>
@@ -880,6 +881,33 @@ int try_gemm_bf16_dma(const GemmArgs &g, hipStream_t st) {
     p.N = g.n_seg * g.segN;
     p.tiles_n = p.N / BN;
     return g.epilogue == EPI_RESIDUAL ? launch_kb<EPI_RESIDUAL>(p, kb, st) : launch_kb<EPI_STORE>(p, kb, st);
+}
+
+// QKV and gate/up projections of decode steps of 33 .. 128 rows on the small tiles: row-major activations, the repacked
+// weights where the model has them, no partial sums.  64 rows of the 7B shape against the split-K form and its reductions:
+// QKV 30 + 12 -> 27 + 7 us (with rotation and KV write), gate/up 57 + 10 -> 40; 128 rows 41 + 14 -> 35 + 8 and 75 + 17 -> 49.  The
+// O and down projections have too few tiles (64 rows: 38 us and a norm of 6, split-K 25 and 7) and stay there.  Returns 1
+// if handled, 0 if declined, < 0 on a launch error.
+int try_gemm_bf16_dma_step(const GemmArgs &g, hipStream_t st) {
+    if (g.epilogue != EPI_STORE && g.epilogue != EPI_SWIGLU) return 0;
+    if (g.kblocked || g.M < 1 || g.M > 128 || g.K % 64 != 0 || g.K < 256 || g.a_rows < 256) return 0;
+    if (g.epilogue == EPI_SWIGLU ? g.segN % 128 != 0 : g.segN % BN != 0) return 0;
+    const int n_seg = g.epilogue == EPI_SWIGLU ? 2 : g.n_seg;
+    bool wkb = (size_t)(g.segN + VLA_KB_PAD_ROWS) * g.K * 2 < ((size_t)1 << 31);
+    for (int i = 0; i < n_seg; i++) wkb = wkb && g.Wkb[i];
+    const void *const *W = wkb ? g.Wkb : g.W;
+    DmaGemmParams p{};
+    p.A = (const bf16_t *)g.A;
+    p.W0 = (const bf16_t *)W[0]; p.W1 = (const bf16_t *)W[1]; p.W2 = (const bf16_t *)W[2];
+    p.C = g.C; p.M = g.M; p.K = g.K; p.segN = g.segN; p.a_rows = g.a_rows; p.w_rows = g.segN + VLA_KB_PAD_ROWS;
+    p.N = g.epilogue == EPI_SWIGLU ? g.segN : n_seg * g.segN;
+    auto go = [&](auto epi) {
+        constexpr int EPI = decltype(epi)::value;
+        const SmallTile tile = choose_tile<EPI>(p);
+        if (tile == TILE_256) return 0;
+        return wkb ? launch_tile<EPI, false, true>(p, tile, st) : launch_tile<EPI, false, false>(p, tile, st);
+    };
+    return g.epilogue == EPI_SWIGLU ? go(std::integral_constant<int, EPI_SWIGLU>{}) : go(std::integral_constant<int, EPI_STORE>{});
 }
 
 // Split-K form for forwards of at most 256 rows (one tile row): the K range is cut into 2, 4 or 8 equal parts so

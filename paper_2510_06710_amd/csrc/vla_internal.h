@@ -169,6 +169,7 @@ __device__ __forceinline__ void vla_tile_of_block(int pid, int tiles_m, int tile
 // ---- gfx950 fast paths (bf16, aligned shapes); each returns 1 if it handled the call, 0 if the
 // shape is outside what it supports (caller then uses the generic kernel), <0 on launch error ----
 int try_gemm_bf16_dma(const GemmArgs &g, hipStream_t st);
+int try_gemm_bf16_dma_step(const GemmArgs &g, hipStream_t st);
 int try_gemm_bf16_dma_splitk(const GemmArgs &g, void *scratch, size_t scratch_bytes, hipStream_t st);
 int try_gemm_bf16_dma_splitk_rows(const GemmArgs &g, void *scratch, size_t scratch_bytes, hipStream_t st);
 int launch_weight_kblock(bf16_t *dst, const bf16_t *src, int N, int K, hipStream_t st);
