@@ -268,9 +268,8 @@ int vla_logp_aggregate(const float *logp, size_t n_out, int inner, float *out, v
  * vla_lora_layer_grads: DEVICE fp32 outputs of the same shapes, overwritten.
  * vla_logprob_backward: teacher-forced forward over the N stored rollouts exactly as vla_logprob_recompute (same
  *   arguments, same modes), then the backward.  lora, grads: HOST arrays of n_layers entries.  coef DEVICE fp32 [N, A].
- *   logp DEVICE fp32 [N, A] out or NULL: the forward's log-probabilities of the stored bins (the kernels of
- *   vla_logprob_recompute with every row taken through the last layer, so equal to its output up to the rounding
- *   differences of two evaluations).  Rollouts are processed in
+ *   logp DEVICE fp32 [N, A] out or NULL: the forward's log-probabilities of the stored bins (equal to the output of
+ *   vla_logprob_recompute up to the rounding differences of two evaluations).  Rollouts are processed in
  *   micro-batches of max_batch; gradients are summed over micro-batches in order, every sum in a fixed order, so the
  *   result is reproducible bit for bit.  Gradient operands of the GEMMs are rounded to the storage dtype.
  *   keep_activations = 0: the first pass is the forward of vla_logprob_recompute keeping the residual stream at every

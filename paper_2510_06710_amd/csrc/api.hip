@@ -602,17 +602,18 @@ static int recompute_impl(vla_model *m, void *wsbuf, const void *patch, const in
     return 0;
 }
 
-size_t vla_forward_streams_bytes(const vla_config &c, int n_max, int R) {
-    return plan_workspace(c, nullptr, n_max, R, R, 0, true, 0).total;
+size_t vla_forward_streams_bytes(const vla_config &c, int n_max, int R, int tail_rows) {
+    return plan_workspace(c, nullptr, n_max, R, R, 0, true, tail_rows).total;
 }
 
 template <typename T>
 static int forward_streams_impl(vla_model *m, void *fw_ws, int n_max, const void *patch, const int32_t *ids, const int32_t *bins, int n,
-                                int P, int T_, int A, int mode, const void *slot_embed, float *keep, const float **x_final, hipStream_t st) {
+                                int P, int T_, int A, int mode, const void *slot_embed, int tail_rows, float *keep, const float **x_final,
+                                hipStream_t st) {
     const vla_config &c = m->cfg;
     const int S = P + T_, H = c.hidden, R = (mode == VLA_MODE_AR) ? S + A - 1 : S + A;
     int rc;
-    Workspace ws = plan_workspace(c, (char *)fw_ws, n_max, R, R, 0, true, 0);
+    Workspace ws = plan_workspace(c, (char *)fw_ws, n_max, R, R, 0, true, tail_rows);
     if ((rc = launch_embed_prefix<T>(ws.X, (const T *)patch, ids, (const T *)m->w.embed, n, P, T_, R, H, c.vocab, st))) return rc;
     if (mode == VLA_MODE_AR) {
         if ((rc = launch_embed_tokens<T>(ws.X, bins, A, A - 1, (const T *)m->w.embed, n, R, S, H, c.vocab, st))) return rc;
@@ -621,16 +622,17 @@ static int forward_streams_impl(vla_model *m, void *fw_ws, int n_max, const void
     KvView kv;
     kv.layer_elems = kv_layer_elems(c, n_max);
     kv.k = ws.kvs_k; kv.v = ws.kvs_v; kv.n_seq = n; kv.n_heads = c.n_heads; kv.d = H / c.n_heads; kv.pos_stride = c.max_seq;
-    if ((rc = run_layers<T>(m, ws, ra, kv, true, st, nullptr, keep))) return rc;
-    *x_final = ws.X;
+    const TailSpec tail{R - tail_rows, tail_rows};
+    if ((rc = run_layers<T>(m, ws, ra, kv, true, st, tail_rows ? &tail : nullptr, keep))) return rc;
+    *x_final = tail_rows ? ws.tX : ws.X;
     return 0;
 }
 
 int vla_forward_streams(vla_model *m, void *fw_ws, int n_max, const void *patch, const int32_t *ids, const int32_t *bins, int n,
-                        int P, int T, int A, int mode, const void *slot_embed, float *keep, const float **x_final, hipStream_t st) {
+                        int P, int T, int A, int mode, const void *slot_embed, int tail_rows, float *keep, const float **x_final, hipStream_t st) {
     return m->cfg.dtype == VLA_DTYPE_F32
-               ? forward_streams_impl<float>(m, fw_ws, n_max, patch, ids, bins, n, P, T, A, mode, slot_embed, keep, x_final, st)
-               : forward_streams_impl<bf16_t>(m, fw_ws, n_max, patch, ids, bins, n, P, T, A, mode, slot_embed, keep, x_final, st);
+               ? forward_streams_impl<float>(m, fw_ws, n_max, patch, ids, bins, n, P, T, A, mode, slot_embed, tail_rows, keep, x_final, st)
+               : forward_streams_impl<bf16_t>(m, fw_ws, n_max, patch, ids, bins, n, P, T, A, mode, slot_embed, tail_rows, keep, x_final, st);
 }
 
 // ------------------------------------------------------------------------------------------ C ABI

@@ -291,9 +291,10 @@ __global__ void cast_rows_kernel(T *out, const float *in, size_t M, int cols, in
 
 // Rotary on the q and k thirds of the fp32 [M, 3H] projection (pairs (i, i + d/2), angle of the row's position from
 // the table), v copied; everything rounded to the storage type once, after the rotation.  sign = -1 applies the
-// transpose of the rotation (the backward of q and k; v passes through).
+// transpose of the rotation (the backward of q and k; v passes through).  Rows below q_first of a sequence have no q
+// (its gradient is zero there): written as zeros, not read.
 template <typename T>
-__global__ void rope_rows_kernel(T *out, const float *in, const float2 *table, size_t M, int R, int H, int d, float sign) {
+__global__ void rope_rows_kernel(T *out, const float *in, const float2 *table, size_t M, int R, int H, int d, float sign, int q_first) {
     const int half = d >> 1;
     const size_t per_row = (size_t)3 * (H >> 1);                 // pairs in q and k, pairs of plain elements in v
     const size_t total = M * per_row;
@@ -303,6 +304,7 @@ __global__ void rope_rows_kernel(T *out, const float *in, const float2 *table, s
         const int seg = e / (H >> 1), w = e - seg * (H >> 1);   // pair w of segment seg
         const int h = w / half, i = w - h * half;
         const size_t base = m * 3 * (size_t)H + (size_t)seg * H + (size_t)h * d;
+        if (seg == 0 && (int)(m % R) < q_first) { out[base + i] = cvt<T>(0.f); out[base + i + half] = cvt<T>(0.f); continue; }
         const float a = in[base + i], b = in[base + i + half];
         if (seg == 2) { out[base + i] = cvt<T>(a); out[base + i + half] = cvt<T>(b); continue; }
         const float2 cs = table[(size_t)(m % R) * half + i];
@@ -312,12 +314,13 @@ __global__ void rope_rows_kernel(T *out, const float *in, const float2 *table, s
     }
 }
 
-// In-place masked softmax of the score rows of one (sequence, head), rows ldp floats apart: row i sees keys 0..i, or
-// all R keys from row full_from on.  One wave per row; entries outside the mask become 0.
-__global__ void __launch_bounds__(256) attn_softmax_kernel(float *SP, size_t n_rows, int R, int ldp, int full_from) {
+// In-place masked softmax of the score rows of one (sequence, head), rows ldp floats apart, `rows` of them per head, the
+// first at position pos0: position i sees keys 0..i, or all R keys from full_from on.  One wave per row; entries outside
+// the mask become 0.
+__global__ void __launch_bounds__(256) attn_softmax_kernel(float *SP, size_t n_rows, int rows, int pos0, int R, int ldp, int full_from) {
     const size_t row = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= n_rows) return;
-    const int lane = threadIdx.x & 63, i = (int)(row % R);
+    const int lane = threadIdx.x & 63, i = pos0 + (int)(row % rows);
     const int nk = i >= full_from ? R : i + 1;
     float *s = SP + row * ldp;
     float mx = -INFINITY;
@@ -331,10 +334,10 @@ __global__ void __launch_bounds__(256) attn_softmax_kernel(float *SP, size_t n_r
 }
 
 // dS = P (dP - sum_j P dP) in place on dP; masked entries (P = 0) become 0.
-__global__ void __launch_bounds__(256) attn_ds_kernel(float *dP, const float *P, size_t n_rows, int R, int ldp, int full_from) {
+__global__ void __launch_bounds__(256) attn_ds_kernel(float *dP, const float *P, size_t n_rows, int rows, int pos0, int R, int ldp, int full_from) {
     const size_t row = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= n_rows) return;
-    const int lane = threadIdx.x & 63, i = (int)(row % R);
+    const int lane = threadIdx.x & 63, i = pos0 + (int)(row % rows);
     const int nk = i >= full_from ? R : i + 1;
     float *d = dP + row * ldp;
     const float *p = P + row * ldp;
@@ -371,9 +374,12 @@ __global__ void swiglu_bwd_kernel(T *dGU, const float *d_act, const float *GU, s
 }
 
 // dX[m] += r (g dn) - x r^3 mean(x g dn), r = (mean(x^2) + eps)^(-1/2): the backward of n = RMSNorm(x) g.  The new
-// dX is also written in the storage type to dXb (the operand of the GEMMs that follow).
+// dX is also written in the storage type to dXb (the operand of the GEMMs that follow).  prev: the gradient that the
+// norm's is added to, rows_prev rows for each sequence's last positions out of `rows` (zero for the others); dX itself when
+// rows_prev == rows.
 template <typename T>
-__global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(float *dX, T *dXb, const float *X, const float *gain, const float *dn, int H, float eps) {
+__global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(float *dX, T *dXb, const float *prev, int rows, int rows_prev, const float *X,
+                                                         const float *gain, const float *dn, int H, float eps) {
     __shared__ float red[4];
     const float *x = X + (size_t)blockIdx.x * H, *d = dn + (size_t)blockIdx.x * H;
     float ss = 0.f, xd = 0.f;
@@ -384,8 +390,10 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(float *dX, T *dXb, con
     const float k = r * r * r * xd / (float)H;
     float *o = dX + (size_t)blockIdx.x * H;
     T *ob = dXb + (size_t)blockIdx.x * H;
+    const int sq = blockIdx.x / rows, row = blockIdx.x - sq * rows - (rows - rows_prev);
+    const float *pv = row >= 0 ? prev + ((size_t)sq * rows_prev + row) * H : nullptr;
     for (int i = threadIdx.x; i < H; i += 256) {
-        const float v = o[i] + (r * gain[i] * d[i] - x[i] * k);
+        const float v = (pv ? pv[i] : 0.f) + (r * gain[i] * d[i] - x[i] * k);
         o[i] = v;
         ob[i] = cvt<T>(v);
     }
@@ -411,9 +419,15 @@ __global__ void __launch_bounds__(256) head_bwd_kernel(float *dX, float *logp_ou
     const float r = 1.0f / sqrtf(ss / (float)H + eps);
     for (int i = t; i < H; i += 256) hs[i] = x[i] * r * gain[i];
     __syncthreads();
+    typedef T t8 __attribute__((ext_vector_type(8), aligned(sizeof(T))));       // (H is a multiple of 16)
     const T *w = Wb + (size_t)t * H;
     float z = 0.f;
-    for (int i = 0; i < H; i++) z += hs[i] * ld(w + i);
+#pragma unroll 4
+    for (int i = 0; i < H; i += 8) {
+        const t8 v = *(const t8 *)(w + i);
+#pragma unroll
+        for (int e = 0; e < 8; e++) z += hs[i + e] * (float)v[e];
+    }
     const float y = z * inv_tau;
     dz[t] = y;
     __syncthreads();
@@ -433,15 +447,23 @@ __global__ void __launch_bounds__(256) head_bwd_kernel(float *dX, float *logp_ou
     __syncthreads();
     dz[t] = c * inv_tau * ((t == bin ? 1.0f : 0.0f) - expf(y - lse));
     __syncthreads();
-    // d h_i = sum_k dz_k W[k][i], then the norm's backward; a thread owns columns t, t + 256, ...
+    // d h_i = sum_k dz_k W[k][i], then the norm's backward; a thread owns columns 8 t .. 8 t + 7, then 2048 further on, ...
     float xd = 0.f;
-    for (int i = t; i < H; i += 256) {
-        float dh = 0.f;
-        for (int k = 0; k < VLA_N_BINS; k++) dh += dz[k] * ld(Wb + (size_t)k * H + i);
-        hs[i] = gain[i] * dh;                       // g dh (h itself is no longer needed)
-        xd += x[i] * hs[i];
+    for (int i = t * 8; i < H; i += 2048) {
+        float dh[8] = {};
+#pragma unroll 8
+        for (int k = 0; k < VLA_N_BINS; k++) {
+            const t8 v = *(const t8 *)(Wb + (size_t)k * H + i);
+#pragma unroll
+            for (int e = 0; e < 8; e++) dh[e] += dz[k] * (float)v[e];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            hs[i + e] = gain[i + e] * dh[e];        // g dh (h itself is no longer needed)
+            xd += x[i + e] * hs[i + e];
+        }
     }
-    xd = bsum256(xd, red);
+    xd = bsum256(xd, red);                          // (its barriers also publish hs)
     const float k3 = r * r * r * xd / (float)H;
     float *o = dX + m * H;
     for (int i = t; i < H; i += 256) o[i] = r * hs[i] - x[i] * k3;
@@ -563,7 +585,7 @@ struct Acts {
 };
 
 struct BwSpace {
-    float *X, *dX, *ckpt, *QKV, *Tmp, *dP, *UV, *Cab;
+    float *X, *dX, *dXt, *ckpt, *QKV, *Tmp, *dP, *UV, *Cab;
     void *dGU, *dXb, *dQKVb, *Wt, *Wa, *Wb, *UVt, *Xt, *dYt;
     // keep = false: one Acts set, refilled per layer by running the layer again from ckpt[l] (the first pass is the
     // recompute's fused forward, its scratch is fw).  keep = true: one set per layer, filled by the first pass.
@@ -600,7 +622,10 @@ Acts plan_acts(const vla_config &c, char *base, size_t M, size_t Mp, int mb, int
     return a;
 }
 
-BwSpace plan_bw(const vla_config &c, char *base, int mb, int R, int /*rank*/, bool keep) {
+// Whether the top layer works on its last A rows per sequence alone (run_layers' rule for the forward's tail form).
+bool tail_form(int R, int A) { return A >= 1 && A * 4 <= R; }
+
+BwSpace plan_bw(const vla_config &c, char *base, int mb, int R, int A, bool keep) {
     BwSpace w;
     size_t off = 0;
     const size_t es = c.dtype == VLA_DTYPE_F32 ? 4 : 2, M = (size_t)mb * R, H = c.hidden, F = c.ffn, L = c.n_layers;
@@ -611,6 +636,7 @@ BwSpace plan_bw(const vla_config &c, char *base, int mb, int R, int /*rank*/, bo
     w.keep = keep;
     w.X = (float *)take(M * H * 4);
     w.dX = (float *)take(M * H * 4);
+    w.dXt = tail_form(R, A) ? (float *)take((size_t)mb * A * H * 4) : nullptr;
     w.QKV = (float *)take(M * 3 * H * 4);
     w.Tmp = (float *)take(M * (F > 3 * H ? F : 3 * H) * 4);
     w.dP = (float *)take((size_t)mb * c.n_heads * R * Rp * 4);
@@ -647,7 +673,7 @@ BwSpace plan_bw(const vla_config &c, char *base, int mb, int R, int /*rank*/, bo
         w.acts_base = nullptr;
         w.acts_stride = 0;
         w.ckpt = (float *)take(L * M * H * 4);
-        w.fw = take(vla_forward_streams_bytes(c, mb, R));
+        w.fw = take(vla_forward_streams_bytes(c, mb, R, tail_form(R, A) ? A : 0));
     }
     w.total = off;
     return w;
@@ -663,13 +689,16 @@ struct Backward {
     BwSpace ws;
     hipStream_t st;
     int n, R, M, H, F, d, nh, full_from, rank;
+    int A;           // the loss reads the last A rows of every sequence
+    int L;
+    bool tail;       // the top layer works on those rows alone where it can (see below)
     float scale;
     int ws_mb;       // rollouts per micro-batch the workspace is laid out for
     static constexpr bool MF = sizeof(T) == 2;      // bf16 storage: attention matrices on the matrix cores
 
-    int gemm(const void *A, const void *W0, const void *W1, const void *W2, int n_seg, int segN, float *C, int K, int epilogue = EPI_STORE) {
+    int gemm(const void *A, const void *W0, const void *W1, const void *W2, int n_seg, int segN, float *C, int K, int rows, int epilogue = EPI_STORE) {
         GemmArgs g{};
-        g.A = A; g.W[0] = W0; g.W[1] = W1; g.W[2] = W2; g.n_seg = n_seg; g.segN = segN; g.C = C; g.M = M; g.K = K;
+        g.A = A; g.W[0] = W0; g.W[1] = W1; g.W[2] = W2; g.n_seg = n_seg; g.segN = segN; g.C = C; g.M = rows; g.K = K;
         g.epilogue = epilogue; g.a_rows = ws.a_rows;
         return vla_gemm_dispatch(c, g, st);
     }
@@ -685,8 +714,8 @@ struct Backward {
         transpose_kernel<T><<<grid, 256, 0, st>>>((T *)ws.Wt, (const T *)W, N, K, ldt, col0);
         return vla_check_launch("transpose");
     }
-    int cast(void *out, const float *in, int cols, int ld_out, int ld_in) {
-        cast_rows_kernel<T><<<blocks_for((size_t)M * cols), 256, 0, st>>>((T *)out, in, (size_t)M, cols, ld_out, ld_in);
+    int cast(void *out, const float *in, int cols, int rows) {
+        cast_rows_kernel<T><<<blocks_for((size_t)rows * cols), 256, 0, st>>>((T *)out, in, (size_t)rows, cols, cols, cols);
         return vla_check_launch("cast_rows");
     }
     BgemmArgs heads(const void *A, int lda, long sA1, long sA2, const void *B, int ldb, long sB1, long sB2, float *C, int ldc,
@@ -709,11 +738,18 @@ struct Backward {
         a.x_mid = ws.X;
         return a;
     }
-    int copy_stream(float *dst, const float *src) {
+    int copy_stream(float *dst, const float *src, int rows) {
         if (dst == src) return 0;
-        if (hipMemcpyAsync(dst, src, (size_t)M * H * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) { vla_set_error("backward: copy failed"); return VLA_EHIP; }
+        if (hipMemcpyAsync(dst, src, (size_t)rows * H * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) { vla_set_error("backward: copy failed"); return VLA_EHIP; }
         return 0;
     }
+
+    // The top layer.  Its output is read on the last A rows of every sequence only, so everything after its K and V is
+    // computed, and differentiated, for those rows alone, packed [n * A, ...]: queries, attention, O projection, feed-forward
+    // block and their gradients (zero elsewhere).  K, V, the q | k | v gradients and the gradient of the layer's input stay
+    // [n * R, ...].  One layer in L is then as cheap as its K and V: two layers of the 7B shape, 32 rollouts, 29.7 -> 18.7 ms (the
+    // input gradient of the first layer, which nothing reads, is left out as well).
+    int rows_of(int l) const { return tail && l == L - 1 ? A : R; }      // rows per sequence after K and V
 
     // Layer l forward on the stream in ws.X with unfused kernels that leave in `a` everything its backward reads.
     // with_down = false stops at the SwiGLU output (a layer run again for its backward: nothing reads its output) and
@@ -721,32 +757,34 @@ struct Backward {
     int layer_forward(int l, const Acts &a, bool with_down) {
         const vla_layer_weights &lw = m->layers[l];
         const T *Q = (const T *)a.QKVr;
-        const int Rp = (R + 3) & ~3;
-        const long RR = (long)R * Rp, rowsH3 = (long)R * 3 * H;
-        const bool causal = full_from >= R;
+        const int Rp = (R + 3) & ~3, Rq = rows_of(l), Mq = n * Rq;
+        const long RR = (long)Rq * Rp, rowsH3 = (long)R * 3 * H;
+        const bool causal = full_from >= R && Rq == R;
         int rc;
-        if (ws.keep && (rc = copy_stream(a.x_in, ws.X))) return rc;          // (otherwise ws.X was loaded from there)
+        if (ws.keep && (rc = copy_stream(a.x_in, ws.X, M))) return rc;       // (otherwise ws.X was loaded from there)
         if ((rc = launch_rmsnorm<T>((T *)a.Nrm, ws.X, (const float *)lw.attn_norm, M, H, c.rms_eps, st))) return rc;
-        if ((rc = gemm(a.Nrm, lw.wq, lw.wk, lw.wv, 3, H, ws.QKV, H))) return rc;
-        rope_rows_kernel<T><<<blocks_for((size_t)M * 3 * (H / 2)), 256, 0, st>>>((T *)a.QKVr, ws.QKV, ws.rope, (size_t)M, R, H, d, 1.0f);
+        if ((rc = gemm(a.Nrm, lw.wq, lw.wk, lw.wv, 3, H, ws.QKV, H, M))) return rc;
+        rope_rows_kernel<T><<<blocks_for((size_t)M * 3 * (H / 2)), 256, 0, st>>>((T *)a.QKVr, ws.QKV, ws.rope, (size_t)M, R, H, d, 1.0f, 0);
         if ((rc = vla_check_launch("rope_rows"))) return rc;
         // scores = q k^T / sqrt(d) per (sequence, head); softmax under the mask; output = P v
-        BgemmArgs g = heads(Q, 3 * H, rowsH3, d, Q + H, 3 * H, rowsH3, d, a.SP, Rp, RR * nh, RR, R, R, d, 0, 1, 1.0f / sqrtf((float)d), causal ? 2 : 0);
+        BgemmArgs g = heads(Q + (size_t)(R - Rq) * 3 * H, 3 * H, rowsH3, d, Q + H, 3 * H, rowsH3, d, a.SP, Rp, RR * nh, RR, Rq, R, d, 0, 1,
+                            1.0f / sqrtf((float)d), causal ? 2 : 0);
         if ((rc = bgemm<T, T, MF>(g, n * nh, st))) return rc;
-        attn_softmax_kernel<<<(unsigned)(((size_t)n * nh * R + 3) / 4), 256, 0, st>>>(a.SP, (size_t)n * nh * R, R, Rp, full_from);
+        attn_softmax_kernel<<<(unsigned)(((size_t)n * nh * Rq + 3) / 4), 256, 0, st>>>(a.SP, (size_t)n * nh * Rq, Rq, R - Rq, R, Rp, full_from);
         if ((rc = vla_check_launch("attn_softmax"))) return rc;
-        g = heads(a.SP, Rp, RR * nh, RR, Q + 2 * H, 3 * H, rowsH3, d, MF ? (float *)a.AO : ws.Tmp, H, (long)R * H, d, R, d, R, 0, 0, 1.0f, causal ? 1 : 0);
+        g = heads(a.SP, Rp, RR * nh, RR, Q + 2 * H, 3 * H, rowsH3, d, MF ? (float *)a.AO : ws.Tmp, H, (long)Rq * H, d, Rq, d, R, 0, 0, 1.0f, causal ? 1 : 0);
         g.c_bf16 = MF;                               // the matrix-core kernel rounds the output to the storage type itself
         if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
-        if (!MF && (rc = cast(a.AO, ws.Tmp, H, H, H))) return rc;
-        if ((rc = gemm(a.AO, lw.wo, nullptr, nullptr, 1, H, ws.X, H, EPI_RESIDUAL))) return rc;     // x_mid = x_in + O(...)
-        if ((rc = copy_stream(a.x_mid, ws.X))) return rc;
-        if ((rc = launch_rmsnorm<T>((T *)a.Nrm2, ws.X, (const float *)lw.ffn_norm, M, H, c.rms_eps, st))) return rc;
-        if ((rc = gemm(a.Nrm2, lw.w_gate, lw.w_up, nullptr, 2, F, a.GU, H))) return rc;
-        swiglu_fwd_kernel<T><<<blocks_for((size_t)M * F), 256, 0, st>>>((T *)a.ACT, a.GU, (size_t)M, F);
+        if (!MF && (rc = cast(a.AO, ws.Tmp, H, Mq))) return rc;
+        if (Rq != R && (rc = launch_gather_rows(ws.X, a.x_in, n, R, R - Rq, Rq, H, st))) return rc;
+        if ((rc = gemm(a.AO, lw.wo, nullptr, nullptr, 1, H, ws.X, H, Mq, EPI_RESIDUAL))) return rc;     // x_mid = x_in + O(...)
+        if ((rc = copy_stream(a.x_mid, ws.X, Mq))) return rc;
+        if ((rc = launch_rmsnorm<T>((T *)a.Nrm2, ws.X, (const float *)lw.ffn_norm, Mq, H, c.rms_eps, st))) return rc;
+        if ((rc = gemm(a.Nrm2, lw.w_gate, lw.w_up, nullptr, 2, F, a.GU, H, Mq))) return rc;
+        swiglu_fwd_kernel<T><<<blocks_for((size_t)Mq * F), 256, 0, st>>>((T *)a.ACT, a.GU, (size_t)Mq, F);
         if ((rc = vla_check_launch("swiglu_fwd"))) return rc;
         if (!with_down) return 0;
-        return gemm(a.ACT, lw.w_down, nullptr, nullptr, 1, H, ws.X, F, EPI_RESIDUAL);
+        return gemm(a.ACT, lw.w_down, nullptr, nullptr, 1, H, ws.X, F, Mq, EPI_RESIDUAL);
     }
 
     // LoRA gradients of a group of projections that share their input X [M, in] (storage type, contiguous rows) and
@@ -762,8 +800,8 @@ struct Backward {
         g.split_scratch = ws.split; g.split_scratch_bytes = ws.split_bytes;     // few output tiles: cut K into parts
         return vla_gemm_dispatch(c, g, st);
     }
-    int lora_group(LoraGroup lg, const void *X, const void *dY, bool first) {
-        const int in = lg.in, wout = lg.n_p * lg.out, kp = ws.kp;
+    int lora_group(LoraGroup lg, const void *X, const void *dY, bool first, int M) {        // M rows
+        const int in = lg.in, wout = lg.n_p * lg.out, kp = M == this->M ? ws.kp : kp_of(M);
         const int pad_rows = 256 + VLA_KB_PAD_ROWS;
         float *U = ws.UV, *V = ws.UV + (size_t)M * 256, *Cb = ws.Cab, *Ca = ws.Cab + (size_t)((wout + 255) / 256 * 256 + VLA_KB_PAD_ROWS) * 256;
         T *Ut = (T *)ws.UVt, *Vt = Ut + (size_t)pad_rows * kp;
@@ -793,6 +831,8 @@ struct Backward {
         unpack_grads_kernel<<<blocks_for((size_t)lg.n_p * rank * (lg.out + in)), 256, 0, st>>>(lg, Cb, Ca, rank, scale, first ? 0 : 1);
         return vla_check_launch("unpack_grads");
     }
+    // rows of a contraction rounded up to what a GEMM's K extent accepts
+    static int kp_of(size_t rows) { return (int)(rows < 256 ? 256 : (rows + 63) / 64 * 64); }
     static LoraGroup group_of(int n_p, const vla_lora_factor *f, const vla_lora_grad *g, int in, int out) {
         LoraGroup lg{};
         lg.n_p = n_p; lg.in = in; lg.out = out;
@@ -800,56 +840,58 @@ struct Backward {
         return lg;
     }
 
-    // Backward of layer l: on entry ws.dX (and ws.dXb, its copy in the storage type) = d L / d x_out; on exit
-    // d L / d x_in.
-    int layer_backward(int l, const vla_lora_layer &lo, const vla_lora_layer_grads &gr, bool first) {
+    // Backward of layer l: on entry dx (and ws.dXb, its copy in the storage type) = d L / d x_out on the layer's rows
+    // ([n * rows_of(l), H]; ws.dX where those are all); on exit ws.dX, ws.dXb = d L / d x_in.  Nothing reads the latter
+    // below the first layer, which stops at its LoRA gradients.
+    int layer_backward(int l, const vla_lora_layer &lo, const vla_lora_layer_grads &gr, bool first, float *dx) {
         const vla_layer_weights &lw = m->layers[l];
         const Acts a = acts(l);
-        const T *Q = (const T *)a.QKVr;
-        const int Rp = (R + 3) & ~3;
-        const long RR = (long)R * Rp, rowsH3 = (long)R * 3 * H;
-        const bool causal = full_from >= R;
+        const T *Q = (const T *)a.QKVr, *Qt = Q + (size_t)(R - rows_of(l)) * 3 * H;      // Qt: the first row that has a query
+        const int Rp = (R + 3) & ~3, Rq = rows_of(l), Mq = n * Rq;
+        const long RR = (long)Rq * Rp, rowsH3 = (long)R * 3 * H;
+        const bool causal = full_from >= R && Rq == R;
         const float isd = 1.0f / sqrtf((float)d);
         int rc;
         if (!ws.keep) {                              // run the layer again from its kept input
-            if ((rc = copy_stream(ws.X, a.x_in))) return rc;
+            if ((rc = copy_stream(ws.X, a.x_in, M))) return rc;
             if ((rc = layer_forward(l, a, false))) return rc;
         }
-        // ---- down projection and SwiGLU (ws.dXb: ws.dX in the storage type, left by the head or the layer above)
-        if ((rc = lora_group(group_of(1, &lo.down, &gr.down, F, H), a.ACT, ws.dXb, first))) return rc;
+        // ---- down projection and SwiGLU (ws.dXb: dx in the storage type, left by the head or the layer above)
+        if ((rc = lora_group(group_of(1, &lo.down, &gr.down, F, H), a.ACT, ws.dXb, first, Mq))) return rc;
         if ((rc = transpose(lw.w_down, H, F, H, 0))) return rc;                               // [F, H]
-        if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, F, ws.Tmp, H))) return rc;          // d act [M, F]
-        swiglu_bwd_kernel<T><<<blocks_for((size_t)M * F), 256, 0, st>>>((T *)ws.dGU, ws.Tmp, a.GU, (size_t)M, F);
+        if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, F, ws.Tmp, H, Mq))) return rc;      // d act [Mq, F]
+        swiglu_bwd_kernel<T><<<blocks_for((size_t)Mq * F), 256, 0, st>>>((T *)ws.dGU, ws.Tmp, a.GU, (size_t)Mq, F);
         if ((rc = vla_check_launch("swiglu_bwd"))) return rc;
-        if ((rc = lora_group(group_of(2, &lo.gate, &gr.gate, H, F), a.Nrm2, ws.dGU, first))) return rc;   // gate, up adjacent in the structs
+        if ((rc = lora_group(group_of(2, &lo.gate, &gr.gate, H, F), a.Nrm2, ws.dGU, first, Mq))) return rc;   // gate, up adjacent in the structs
         if ((rc = transpose(lw.w_gate, F, H, 2 * F, 0)) || (rc = transpose(lw.w_up, F, H, 2 * F, F))) return rc;   // [H, 2F]
-        if ((rc = gemm(ws.dGU, ws.Wt, nullptr, nullptr, 1, H, ws.Tmp, 2 * F))) return rc;      // d n2 [M, H]
-        rmsnorm_bwd_kernel<T><<<M, 256, 0, st>>>(ws.dX, (T *)ws.dXb, a.x_mid, (const float *)lw.ffn_norm, ws.Tmp, H, c.rms_eps);
+        if ((rc = gemm(ws.dGU, ws.Wt, nullptr, nullptr, 1, H, ws.Tmp, 2 * F, Mq))) return rc;  // d n2 [Mq, H]
+        rmsnorm_bwd_kernel<T><<<Mq, 256, 0, st>>>(dx, (T *)ws.dXb, dx, Rq, Rq, a.x_mid, (const float *)lw.ffn_norm, ws.Tmp, H, c.rms_eps);
         if ((rc = vla_check_launch("rmsnorm_bwd"))) return rc;
-        // ---- O projection and attention (ws.dX, ws.dXb are now d L / d x_mid)
-        if ((rc = lora_group(group_of(1, &lo.o, &gr.o, H, H), a.AO, ws.dXb, first))) return rc;
+        // ---- O projection and attention (dx, ws.dXb are now d L / d x_mid)
+        if ((rc = lora_group(group_of(1, &lo.o, &gr.o, H, H), a.AO, ws.dXb, first, Mq))) return rc;
         if ((rc = transpose(lw.wo, H, H, H, 0))) return rc;
-        float *d_ao = a.GU;                          // [M, H] fp32; the gate / up pre-activations are no longer needed
-        if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, H, d_ao, H))) return rc;
+        float *d_ao = a.GU;                          // [Mq, H] fp32; the gate / up pre-activations are no longer needed
+        if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, H, d_ao, H, Mq))) return rc;
         float *dqkv = ws.Tmp;                        // [M, 3H] fp32: d q | d k | d v (q, k still in the rotated frame)
         // dP = dO v^T ; dV = P^T dO ; dS = P (dP - rowsum(P dP)) ; dQ = dS k / sqrt(d) ; dK = dS^T q / sqrt(d)
-        BgemmArgs g = heads(d_ao, H, (long)R * H, d, Q + 2 * H, 3 * H, rowsH3, d, ws.dP, Rp, RR * nh, RR, R, R, d, 0, 1, 1.0f, causal ? 2 : 0);
+        BgemmArgs g = heads(d_ao, H, (long)Rq * H, d, Q + 2 * H, 3 * H, rowsH3, d, ws.dP, Rp, RR * nh, RR, Rq, R, d, 0, 1, 1.0f, causal ? 2 : 0);
         if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
-        g = heads(a.SP, Rp, RR * nh, RR, d_ao, H, (long)R * H, d, dqkv + 2 * H, 3 * H, rowsH3, d, R, d, R, 1, 0, 1.0f, 0);
+        g = heads(a.SP, Rp, RR * nh, RR, d_ao, H, (long)Rq * H, d, dqkv + 2 * H, 3 * H, rowsH3, d, R, d, Rq, 1, 0, 1.0f, 0);
         if ((rc = bgemm<float, float, MF>(g, n * nh, st))) return rc;
-        attn_ds_kernel<<<(unsigned)(((size_t)n * nh * R + 3) / 4), 256, 0, st>>>(ws.dP, a.SP, (size_t)n * nh * R, R, Rp, full_from);
+        attn_ds_kernel<<<(unsigned)(((size_t)n * nh * Rq + 3) / 4), 256, 0, st>>>(ws.dP, a.SP, (size_t)n * nh * Rq, Rq, R - Rq, R, Rp, full_from);
         if ((rc = vla_check_launch("attn_ds"))) return rc;
-        g = heads(ws.dP, Rp, RR * nh, RR, Q + H, 3 * H, rowsH3, d, dqkv, 3 * H, rowsH3, d, R, d, R, 0, 0, isd, causal ? 1 : 0);
+        g = heads(ws.dP, Rp, RR * nh, RR, Q + H, 3 * H, rowsH3, d, dqkv + (size_t)(R - Rq) * 3 * H, 3 * H, rowsH3, d, Rq, d, R, 0, 0, isd, causal ? 1 : 0);
         if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
-        g = heads(ws.dP, Rp, RR * nh, RR, Q, 3 * H, rowsH3, d, dqkv + H, 3 * H, rowsH3, d, R, d, R, 1, 0, isd, 0);
+        g = heads(ws.dP, Rp, RR * nh, RR, Qt, 3 * H, rowsH3, d, dqkv + H, 3 * H, rowsH3, d, R, d, Rq, 1, 0, isd, 0);
         if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
-        rope_rows_kernel<T><<<blocks_for((size_t)M * 3 * (H / 2)), 256, 0, st>>>((T *)ws.dQKVb, dqkv, ws.rope, (size_t)M, R, H, d, -1.0f);
+        rope_rows_kernel<T><<<blocks_for((size_t)M * 3 * (H / 2)), 256, 0, st>>>((T *)ws.dQKVb, dqkv, ws.rope, (size_t)M, R, H, d, -1.0f, R - Rq);
         if ((rc = vla_check_launch("rope_rows (transpose)"))) return rc;
         // ---- Q / K / V projections and the attention norm
-        if ((rc = lora_group(group_of(3, &lo.q, &gr.q, H, H), a.Nrm, ws.dQKVb, first))) return rc;       // q, k, v adjacent
+        if ((rc = lora_group(group_of(3, &lo.q, &gr.q, H, H), a.Nrm, ws.dQKVb, first, M))) return rc;    // q, k, v adjacent
+        if (l == 0) return 0;
         if ((rc = transpose(lw.wq, H, H, 3 * H, 0)) || (rc = transpose(lw.wk, H, H, 3 * H, H)) || (rc = transpose(lw.wv, H, H, 3 * H, 2 * H))) return rc;
-        if ((rc = gemm(ws.dQKVb, ws.Wt, nullptr, nullptr, 1, H, a.GU, 3 * H))) return rc;      // d n [M, H]
-        rmsnorm_bwd_kernel<T><<<M, 256, 0, st>>>(ws.dX, (T *)ws.dXb, a.x_in, (const float *)lw.attn_norm, a.GU, H, c.rms_eps);
+        if ((rc = gemm(ws.dQKVb, ws.Wt, nullptr, nullptr, 1, H, a.GU, 3 * H, M))) return rc;   // d n [M, H]
+        rmsnorm_bwd_kernel<T><<<M, 256, 0, st>>>(ws.dX, (T *)ws.dXb, dx, R, Rq, a.x_in, (const float *)lw.attn_norm, a.GU, H, c.rms_eps);
         return vla_check_launch("rmsnorm_bwd");
     }
 };
@@ -865,8 +907,8 @@ int backward_impl(vla_model *m, void *wsbuf, bool keep, const void *patch, const
     const int mb = bw_micro_batch(c, N);
     const T *head = (const T *)m->w.lm_head + (size_t)(c.vocab - VLA_N_BINS) * H;
     int rc;
-    Backward<T> bw{m, c, plan_bw(c, (char *)wsbuf, mb, R, rank, keep), st, 0, R, 0, H, c.ffn, H / c.n_heads, c.n_heads,
-                   mode == VLA_MODE_AR ? 0x7fffffff : S, rank, scale, mb};
+    Backward<T> bw{m, c, plan_bw(c, (char *)wsbuf, mb, R, A, keep), st, 0, R, 0, H, c.ffn, H / c.n_heads, c.n_heads,
+                   mode == VLA_MODE_AR ? 0x7fffffff : S, rank, A, L, tail_form(R, A), scale, mb};
     if ((rc = launch_rope_table(bw.ws.rope, R, 0, bw.d, c.rope_theta, st))) return rc;
     bool first = true;
     for (int n0 = 0; n0 < N; n0 += mb, first = false) {
@@ -887,17 +929,22 @@ int backward_impl(vla_model *m, void *wsbuf, bool keep, const void *patch, const
             x_final = bw.ws.X;
         } else {
             // (1) the forward pass of the recompute itself (its fused kernels), keeping every layer's input
-            if ((rc = vla_forward_streams(m, bw.ws.fw, mb, pp, ii, bins + (size_t)n0 * A, n, P, T_, A, mode, slot_embed, bw.ws.ckpt, &x_final, st))) return rc;
+            if ((rc = vla_forward_streams(m, bw.ws.fw, mb, pp, ii, bins + (size_t)n0 * A, n, P, T_, A, mode, slot_embed, bw.tail ? A : 0, bw.ws.ckpt, &x_final, st))) return rc;
         }
-        fill_kernel<<<blocks_for(MH), 256, 0, st>>>(bw.ws.dX, MH, 0.f);
-        if ((rc = vla_check_launch("fill"))) return rc;
+        // the head's gradient: on the read rows, packed, or in the full ws.dX (zero elsewhere)
+        float *dx = bw.tail ? bw.ws.dXt : bw.ws.dX;
+        const int rows_h = bw.tail ? A : R, first_h = bw.tail ? 0 : first_row;
+        if (!bw.tail) {
+            fill_kernel<<<blocks_for(MH), 256, 0, st>>>(dx, MH, 0.f);
+            if ((rc = vla_check_launch("fill"))) return rc;
+        }
         head_bwd_kernel<T><<<n * A, 256, (size_t)(H + VLA_N_BINS) * sizeof(float), st>>>(
-            bw.ws.dX, logp ? logp + (size_t)n0 * A : nullptr, x_final, (const float *)m->w.final_norm, head, bins + (size_t)n0 * A,
-            coef + (size_t)n0 * A, A, R, first_row, H, c.rms_eps, 1.0f / temperature);
+            dx, logp ? logp + (size_t)n0 * A : nullptr, x_final, (const float *)m->w.final_norm, head, bins + (size_t)n0 * A,
+            coef + (size_t)n0 * A, A, rows_h, first_h, H, c.rms_eps, 1.0f / temperature);
         if ((rc = vla_check_launch("head_bwd"))) return rc;
-        if ((rc = bw.cast(bw.ws.dXb, bw.ws.dX, H, H, H))) return rc;
+        if ((rc = bw.cast(bw.ws.dXb, dx, H, n * rows_h))) return rc;
         for (int l = L - 1; l >= 0; l--)
-            if ((rc = bw.layer_backward(l, lora[l], grads[l], first))) return rc;
+            if ((rc = bw.layer_backward(l, lora[l], grads[l], first, l == L - 1 ? dx : bw.ws.dX))) return rc;
     }
     return 0;
 }
@@ -919,7 +966,7 @@ size_t vla_backward_workspace_bytes(const vla_config *cfg, int N, int S, int A, 
     if (N <= 0 || S <= 0 || A <= 0 || rank <= 0) { vla_set_error("N, S, A and rank must be positive"); return 0; }
     if (S + A > cfg->max_seq + 1) { vla_set_error("S + A exceeds capacity"); return 0; }
     const int R = (S + A <= cfg->max_seq) ? S + A : S + A - 1;
-    return plan_bw(*cfg, nullptr, bw_micro_batch(*cfg, N), R, rank, false).total;
+    return plan_bw(*cfg, nullptr, bw_micro_batch(*cfg, N), R, A, false).total;
 }
 
 size_t vla_backward_keep_workspace_bytes(const vla_config *cfg, int N, int S, int A, int rank) {
@@ -927,7 +974,7 @@ size_t vla_backward_keep_workspace_bytes(const vla_config *cfg, int N, int S, in
     if (N <= 0 || S <= 0 || A <= 0 || rank <= 0) { vla_set_error("N, S, A and rank must be positive"); return 0; }
     if (S + A > cfg->max_seq + 1) { vla_set_error("S + A exceeds capacity"); return 0; }
     const int R = (S + A <= cfg->max_seq) ? S + A : S + A - 1;
-    return plan_bw(*cfg, nullptr, bw_micro_batch(*cfg, N), R, rank, true).total;
+    return plan_bw(*cfg, nullptr, bw_micro_batch(*cfg, N), R, A, true).total;
 }
 
 int vla_logprob_backward(vla_model *m, void *ws, size_t ws_bytes, const void *patch, const int32_t *ids, const int32_t *bins,
@@ -950,7 +997,7 @@ int vla_logprob_backward(vla_model *m, void *ws, size_t ws_bytes, const void *pa
     if (3 * rank > 256) { vla_set_error("rank %d unsupported (at most 85: three stacked factors fill 256 rows)", rank); return VLA_ESHAPE; }
     if (int rc = vla_check_rows_per_pass(c, mb, R)) return rc;
     const bool keep = keep_activations != 0;
-    const size_t need = plan_bw(c, nullptr, mb, R, rank, keep).total;
+    const size_t need = plan_bw(c, nullptr, mb, R, A, keep).total;
     if (ws_bytes < need) { vla_set_error("workspace %zu bytes, need %zu", ws_bytes, need); return VLA_EWORKSPACE; }
     hipStream_t st = (hipStream_t)stream;
     return c.dtype == VLA_DTYPE_F32

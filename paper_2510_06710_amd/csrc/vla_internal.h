@@ -211,13 +211,14 @@ int vla_check_config(const vla_config *c);                                   // 
 int vla_check_rows_per_pass(const vla_config &c, long n_seq, long rows_per_seq);
 // C = A . W^T of a multi-row forward (row-major operands): the MFMA kernels where the shape allows, else the generic one
 int vla_gemm_dispatch(const vla_config &c, const GemmArgs &g, hipStream_t st);
-// The teacher-forced forward of the log-prob recompute over n rollouts (the kernels vla_logprob_recompute runs, every
-// row through every layer), keeping the fp32 residual stream at the input of layer l in keep + l * n * R * H
-// ([n * R, H] each).  *x_final: the residual stream after the last layer ([n * R, H], inside fw_ws).  fw_ws: device
-// scratch of vla_forward_streams_bytes(c, n_max, R) bytes with n <= n_max.
-size_t vla_forward_streams_bytes(const vla_config &c, int n_max, int R);
+// The teacher-forced forward of the log-prob recompute over n rollouts (the kernels vla_logprob_recompute runs), keeping
+// the fp32 residual stream at the input of layer l in keep + l * n * R * H ([n * R, H] each).  tail_rows: 0, or how many of
+// every rollout's last rows the caller reads after the last layer, which then computes those alone (at most a quarter of the
+// rows, see run_layers).  *x_final: the residual stream after the last layer ([n * R, H], or [n * tail_rows, H] packed,
+// inside fw_ws).  fw_ws: device scratch of vla_forward_streams_bytes(c, n_max, R, tail_rows) bytes with n <= n_max.
+size_t vla_forward_streams_bytes(const vla_config &c, int n_max, int R, int tail_rows);
 int vla_forward_streams(vla_model *m, void *fw_ws, int n_max, const void *patch, const int32_t *ids, const int32_t *bins, int n,
-                        int P, int T, int A, int mode, const void *slot_embed, float *keep, const float **x_final, hipStream_t st);
+                        int P, int T, int A, int mode, const void *slot_embed, int tail_rows, float *keep, const float **x_final, hipStream_t st);
 
 // Profiling scope: when profiling is enabled, records an event pair around the launches issued
 // during its lifetime, tagged with `label` (a string literal) and the algorithmic work.

@@ -1,0 +1,18 @@
+"""The backward's top layer on the read rows alone: both sides of the rule (a quarter of the rows) and at it, both modes,
+more micro-batches than one, against the fp64 oracle (fp32 storage: 2e-4 of each gradient's largest entry, as elsewhere)."""
+import pytest
+
+import vla_inputs as vi
+from test_gpu_backward import _compare, _oracle, _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("keep", [False, True])
+@pytest.mark.parametrize("mode,S,A", [(0, 10, 3), (0, 9, 3), (0, 40, 7), (1, 9, 3), (1, 8, 3), (1, 33, 4)])
+def test_tail_rows(mode, S, A, keep):
+    wl = vi.scaled(vi.WORKLOADS["cfg1_tiny_fp32"], batch=3, n_patches=S - 2, n_instr=2, n_action=A, mode=mode)
+    case, lora, bins, coef, grads, logp = _run(wl, 21, 4, 0.5, max_batch=2, keep=keep)
+    ref = _oracle(wl, 21, lora, bins, coef, 3, 0.5)
+    ref = ref[0] if isinstance(ref, tuple) else ref
+    _compare(grads, ref, 2e-4)
