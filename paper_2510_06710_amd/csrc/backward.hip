@@ -611,7 +611,7 @@ Acts plan_acts(const vla_config &c, char *base, size_t M, size_t Mp, int mb, int
     const size_t es = c.dtype == VLA_DTYPE_F32 ? 4 : 2, H = c.hidden, F = c.ffn, Rp = ((size_t)R + 3) & ~(size_t)3;
     auto take = [&](size_t b) { char *p = base ? base + off : nullptr; off += al(b); return (void *)p; };
     if (with_streams) { a.x_in = (float *)take(M * H * 4); a.x_mid = (float *)take(M * H * 4); }
-    a.GU = (float *)take(M * 2 * F * 4);
+    a.GU = (float *)take(M * (2 * F > H ? 2 * F : H) * 4);         // (also [M, H] of gradients, layer_backward's d_ao and d n)
     a.SP = (float *)take((size_t)mb * c.n_heads * R * Rp * 4);     // score rows start 16-byte aligned
     a.Nrm = take(Mp * H * es);
     a.QKVr = take(Mp * 3 * H * es);

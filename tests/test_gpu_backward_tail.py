@@ -16,3 +16,18 @@ def test_tail_rows(mode, S, A, keep):
     ref = _oracle(wl, 21, lora, bins, coef, 3, 0.5)
     ref = ref[0] if isinstance(ref, tuple) else ref
     _compare(grads, ref, 2e-4)
+
+
+@pytest.mark.parametrize("hidden,heads,ffn,S,A,mode", [
+    (1040, 5, 330, 12, 5, 0),      # head_dim 208; more columns than one piece of the head's gradient; ffn not a multiple of 4
+    (1040, 5, 332, 21, 5, 1),      # ... read rows alone, 10 of them (not a multiple of 4), ffn a multiple of 4 alone
+    (32, 2, 48, 508, 4, 0),        # 511 and 513 rows per sequence: both sides of the softmax's register form
+    (32, 2, 48, 510, 4, 0),
+])
+def test_odd_sizes(hidden, heads, ffn, S, A, mode):
+    wl = vi.Workload("odd_bw", vi.ModelShape(n_layers=2, hidden=hidden, n_heads=heads, ffn=ffn, vocab=640, dtype="f32"),
+                     batch=2, n_patches=S - 2, n_instr=2, n_action=A, mode=mode)
+    case, lora, bins, coef, grads, logp = _run(wl, 22, 4, 0.5, max_batch=2, keep=True)
+    ref = _oracle(wl, 22, lora, bins, coef, 2, 0.5)
+    ref = ref[0] if isinstance(ref, tuple) else ref
+    _compare(grads, ref, 2e-4)
