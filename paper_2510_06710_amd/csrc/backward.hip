@@ -292,37 +292,67 @@ __global__ void cast_rows_kernel(T *out, const float *in, size_t M, int cols, in
 // Rotary on the q and k thirds of the fp32 [M, 3H] projection (pairs (i, i + d/2), angle of the row's position from
 // the table), v copied; everything rounded to the storage type once, after the rotation.  sign = -1 applies the
 // transpose of the rotation (the backward of q and k; v passes through).  Rows below q_first of a sequence have no q
-// (its gradient is zero there): written as zeros, not read.
+// (its gradient is zero there): written as zeros, not read.  Bound by memory: a division and a 2-byte store per pair took
+// 205 us for 9,408 rows of 3 x 4096, a workgroup per row with four pairs per thread 165 (4.1 TB/s).
 template <typename T>
-__global__ void rope_rows_kernel(T *out, const float *in, const float2 *table, size_t M, int R, int H, int d, float sign, int q_first) {
-    const int half = d >> 1;
-    const size_t per_row = (size_t)3 * (H >> 1);                 // pairs in q and k, pairs of plain elements in v
-    const size_t total = M * per_row;
-    for (size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (size_t)gridDim.x * 256) {
-        const size_t m = idx / per_row;
-        const int e = (int)(idx - m * per_row);
-        const int seg = e / (H >> 1), w = e - seg * (H >> 1);   // pair w of segment seg
-        const int h = w / half, i = w - h * half;
-        const size_t base = m * 3 * (size_t)H + (size_t)seg * H + (size_t)h * d;
-        if (seg == 0 && (int)(m % R) < q_first) { out[base + i] = cvt<T>(0.f); out[base + i + half] = cvt<T>(0.f); continue; }
-        const float a = in[base + i], b = in[base + i + half];
-        if (seg == 2) { out[base + i] = cvt<T>(a); out[base + i + half] = cvt<T>(b); continue; }
-        const float2 cs = table[(size_t)(m % R) * half + i];
-        const float s = sign * cs.y;
-        out[base + i] = cvt<T>(a * cs.x - b * s);
-        out[base + i + half] = cvt<T>(b * cs.x + a * s);
+__global__ void __launch_bounds__(256) rope_rows_kernel(T *out, const float *in, const float2 *table, int R, int H, int d, float sign, int q_first) {
+    typedef T t4 __attribute__((ext_vector_type(4)));
+    // one workgroup per row, four consecutive pairs per thread and step (d is a multiple of 16)
+    const int half = d >> 1, quads = half >> 2, per_seg = (H / d) * quads;
+    const size_t m = blockIdx.x, row = m * 3 * (size_t)H;
+    const int r = (int)(m % R);
+    for (int e = threadIdx.x; e < 3 * per_seg; e += 256) {
+        const int seg = e / per_seg, w = e - seg * per_seg, h = w / quads, i = (w - h * quads) * 4;
+        const size_t base = row + (size_t)seg * H + h * d + i;
+        t4 lo, hi;
+        if (seg == 0 && r < q_first) {
+#pragma unroll
+            for (int u = 0; u < 4; u++) { lo[u] = cvt<T>(0.f); hi[u] = cvt<T>(0.f); }
+        } else {
+            const f32x4_t a = *(const f32x4_t *)(in + base), b = *(const f32x4_t *)(in + base + half);
+            const float2 *cs = table + (size_t)r * half + i;
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const float co = seg == 2 ? 1.f : cs[u].x, si = seg == 2 ? 0.f : sign * cs[u].y;
+                lo[u] = cvt<T>(seg == 2 ? a[u] : a[u] * co - b[u] * si);
+                hi[u] = cvt<T>(seg == 2 ? b[u] : b[u] * co + a[u] * si);
+            }
+        }
+        *(t4 *)(out + base) = lo;
+        *(t4 *)(out + base + half) = hi;
     }
 }
 
 // In-place masked softmax of the score rows of one (sequence, head), rows ldp floats apart, `rows` of them per head, the
 // first at position pos0: position i sees keys 0..i, or all R keys from full_from on.  One wave per row; entries outside
-// the mask become 0.
+// the mask become 0.  Up to 512 keys the row stays in registers, one read and one write (32 x 32 heads x 294 rows: 249 us
+// with three passes, now 132).
 __global__ void __launch_bounds__(256) attn_softmax_kernel(float *SP, size_t n_rows, int rows, int pos0, int R, int ldp, int full_from) {
     const size_t row = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= n_rows) return;
     const int lane = threadIdx.x & 63, i = pos0 + (int)(row % rows);
     const int nk = i >= full_from ? R : i + 1;
     float *s = SP + row * ldp;
+    if (R <= 64 * 8) {                           // the row stays in registers: one read, one write
+        float v[8], m8 = -INFINITY, sum8 = 0.f;
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            const int j = u * 64 + lane;
+            v[u] = j < nk ? s[j] : -INFINITY;
+            m8 = fmaxf(m8, v[u]);
+        }
+        m8 = wmax(m8);
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            v[u] = u * 64 + lane < nk ? expf(v[u] - m8) : 0.f;
+            sum8 += v[u];
+        }
+        const float inv8 = 1.0f / wsum(sum8);
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+            if (u * 64 + lane < R) s[u * 64 + lane] = v[u] * inv8;
+        return;
+    }
     float mx = -INFINITY;
     for (int j = lane; j < nk; j += 64) mx = fmaxf(mx, s[j]);
     mx = wmax(mx);
@@ -347,29 +377,45 @@ __global__ void __launch_bounds__(256) attn_ds_kernel(float *dP, const float *P,
     for (int j = lane; j < R; j += 64) d[j] = j < nk ? p[j] * (d[j] - dot) : 0.f;
 }
 
-// act = silu(gate) * up from the fp32 [M, 2F] projection (gate columns, then up columns)
-template <typename T>
-__global__ void swiglu_fwd_kernel(T *act, const float *GU, size_t M, int F) {
-    const size_t total = M * (size_t)F;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-        const size_t m = i / F;
-        const int f = (int)(i - m * F);
-        const float g = GU[m * 2 * F + f], u = GU[m * 2 * F + F + f];
-        act[m * F + f] = cvt<T>(g / (1.0f + expf(-g)) * u);
+// act = silu(gate) * up from the fp32 [M, 2F] projection (gate columns, then up columns); grid (column pieces, rows), V
+// columns per thread (4 where F is a multiple of 4).  Rows beyond the grid's limit follow in steps of gridDim.y.
+// (9,408 rows of F = 11008: 290 us with one element per thread and a division, now 198; the backward below 330, now 317
+// = 5.2 TB/s.)
+template <typename T, int V>
+__global__ void __launch_bounds__(256) swiglu_fwd_kernel(T *act, const float *GU, int M, int F) {
+    typedef T tv __attribute__((ext_vector_type(V)));
+    typedef float fv __attribute__((ext_vector_type(V)));
+    const int f = (blockIdx.x * 256 + threadIdx.x) * V;
+    if (f >= F) return;
+    for (int m = blockIdx.y; m < M; m += gridDim.y) {
+        const float *src = GU + (size_t)m * 2 * F + f;
+        const fv g = *(const fv *)src, u = *(const fv *)(src + F);
+        tv o;
+#pragma unroll
+        for (int e = 0; e < V; e++) o[e] = cvt<T>(g[e] / (1.0f + expf(-g[e])) * u[e]);
+        *(tv *)(act + (size_t)m * F + f) = o;
     }
 }
 
 // d gate = d act * up * silu'(gate), d up = d act * silu(gate); silu'(t) = s (1 + t (1 - s)), s = sigmoid(t)
-template <typename T>
-__global__ void swiglu_bwd_kernel(T *dGU, const float *d_act, const float *GU, size_t M, int F) {
-    const size_t total = M * (size_t)F;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-        const size_t m = i / F;
-        const int f = (int)(i - m * F);
-        const float g = GU[m * 2 * F + f], u = GU[m * 2 * F + F + f], da = d_act[i];
-        const float s = 1.0f / (1.0f + expf(-g));
-        dGU[m * 2 * F + f] = cvt<T>(da * u * s * (1.0f + g * (1.0f - s)));
-        dGU[m * 2 * F + F + f] = cvt<T>(da * g * s);
+template <typename T, int V>
+__global__ void __launch_bounds__(256) swiglu_bwd_kernel(T *dGU, const float *d_act, const float *GU, int M, int F) {
+    typedef T tv __attribute__((ext_vector_type(V)));
+    typedef float fv __attribute__((ext_vector_type(V)));
+    const int f = (blockIdx.x * 256 + threadIdx.x) * V;
+    if (f >= F) return;
+    for (int m = blockIdx.y; m < M; m += gridDim.y) {
+        const size_t o = (size_t)m * 2 * F + f;
+        const fv g = *(const fv *)(GU + o), u = *(const fv *)(GU + o + F), da = *(const fv *)(d_act + (size_t)m * F + f);
+        tv dg, du;
+#pragma unroll
+        for (int e = 0; e < V; e++) {
+            const float s = 1.0f / (1.0f + expf(-g[e]));
+            dg[e] = cvt<T>(da[e] * u[e] * s * (1.0f + g[e] * (1.0f - s)));
+            du[e] = cvt<T>(da[e] * g[e] * s);
+        }
+        *(tv *)(dGU + o) = dg;
+        *(tv *)(dGU + o + F) = du;
     }
 }
 
@@ -738,6 +784,12 @@ struct Backward {
         a.x_mid = ws.X;
         return a;
     }
+    template <typename L_>
+    void swiglu(const L_ &launch, int rows) {
+        const unsigned y = rows < 65535 ? rows : 65535;
+        if (F % 4 == 0) launch(std::integral_constant<int, 4>{}, dim3((F / 4 + 255) / 256, y));
+        else launch(std::integral_constant<int, 1>{}, dim3((F + 255) / 256, y));
+    }
     int copy_stream(float *dst, const float *src, int rows) {
         if (dst == src) return 0;
         if (hipMemcpyAsync(dst, src, (size_t)rows * H * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) { vla_set_error("backward: copy failed"); return VLA_EHIP; }
@@ -764,7 +816,7 @@ struct Backward {
         if (ws.keep && (rc = copy_stream(a.x_in, ws.X, M))) return rc;       // (otherwise ws.X was loaded from there)
         if ((rc = launch_rmsnorm<T>((T *)a.Nrm, ws.X, (const float *)lw.attn_norm, M, H, c.rms_eps, st))) return rc;
         if ((rc = gemm(a.Nrm, lw.wq, lw.wk, lw.wv, 3, H, ws.QKV, H, M))) return rc;
-        rope_rows_kernel<T><<<blocks_for((size_t)M * 3 * (H / 2)), 256, 0, st>>>((T *)a.QKVr, ws.QKV, ws.rope, (size_t)M, R, H, d, 1.0f, 0);
+        rope_rows_kernel<T><<<M, 256, 0, st>>>((T *)a.QKVr, ws.QKV, ws.rope, R, H, d, 1.0f, 0);
         if ((rc = vla_check_launch("rope_rows"))) return rc;
         // scores = q k^T / sqrt(d) per (sequence, head); softmax under the mask; output = P v
         BgemmArgs g = heads(Q + (size_t)(R - Rq) * 3 * H, 3 * H, rowsH3, d, Q + H, 3 * H, rowsH3, d, a.SP, Rp, RR * nh, RR, Rq, R, d, 0, 1,
@@ -781,7 +833,7 @@ struct Backward {
         if ((rc = copy_stream(a.x_mid, ws.X, Mq))) return rc;
         if ((rc = launch_rmsnorm<T>((T *)a.Nrm2, ws.X, (const float *)lw.ffn_norm, Mq, H, c.rms_eps, st))) return rc;
         if ((rc = gemm(a.Nrm2, lw.w_gate, lw.w_up, nullptr, 2, F, a.GU, H, Mq))) return rc;
-        swiglu_fwd_kernel<T><<<blocks_for((size_t)Mq * F), 256, 0, st>>>((T *)a.ACT, a.GU, (size_t)Mq, F);
+        swiglu([&](auto v, dim3 grid) { swiglu_fwd_kernel<T, decltype(v)::value><<<grid, 256, 0, st>>>((T *)a.ACT, a.GU, Mq, F); }, Mq);
         if ((rc = vla_check_launch("swiglu_fwd"))) return rc;
         if (!with_down) return 0;
         return gemm(a.ACT, lw.w_down, nullptr, nullptr, 1, H, ws.X, F, Mq, EPI_RESIDUAL);
@@ -860,7 +912,7 @@ struct Backward {
         if ((rc = lora_group(group_of(1, &lo.down, &gr.down, F, H), a.ACT, ws.dXb, first, Mq))) return rc;
         if ((rc = transpose(lw.w_down, H, F, H, 0))) return rc;                               // [F, H]
         if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, F, ws.Tmp, H, Mq))) return rc;      // d act [Mq, F]
-        swiglu_bwd_kernel<T><<<blocks_for((size_t)Mq * F), 256, 0, st>>>((T *)ws.dGU, ws.Tmp, a.GU, (size_t)Mq, F);
+        swiglu([&](auto v, dim3 grid) { swiglu_bwd_kernel<T, decltype(v)::value><<<grid, 256, 0, st>>>((T *)ws.dGU, ws.Tmp, a.GU, Mq, F); }, Mq);
         if ((rc = vla_check_launch("swiglu_bwd"))) return rc;
         if ((rc = lora_group(group_of(2, &lo.gate, &gr.gate, H, F), a.Nrm2, ws.dGU, first, Mq))) return rc;   // gate, up adjacent in the structs
         if ((rc = transpose(lw.w_gate, F, H, 2 * F, 0)) || (rc = transpose(lw.w_up, F, H, 2 * F, F))) return rc;   // [H, 2F]
@@ -884,7 +936,7 @@ struct Backward {
         if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
         g = heads(ws.dP, Rp, RR * nh, RR, Qt, 3 * H, rowsH3, d, dqkv + H, 3 * H, rowsH3, d, R, d, Rq, 1, 0, isd, 0);
         if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
-        rope_rows_kernel<T><<<blocks_for((size_t)M * 3 * (H / 2)), 256, 0, st>>>((T *)ws.dQKVb, dqkv, ws.rope, (size_t)M, R, H, d, -1.0f, R - Rq);
+        rope_rows_kernel<T><<<M, 256, 0, st>>>((T *)ws.dQKVb, dqkv, ws.rope, R, H, d, -1.0f, R - Rq);
         if ((rc = vla_check_launch("rope_rows (transpose)"))) return rc;
         // ---- Q / K / V projections and the attention norm
         if ((rc = lora_group(group_of(3, &lo.q, &gr.q, H, H), a.Nrm, ws.dQKVb, first, M))) return rc;    // q, k, v adjacent
@@ -914,7 +966,6 @@ int backward_impl(vla_model *m, void *wsbuf, bool keep, const void *patch, const
     for (int n0 = 0; n0 < N; n0 += mb, first = false) {
         const int n = (N - n0 < mb) ? N - n0 : mb;
         bw.n = n; bw.M = n * R;
-        const size_t MH = (size_t)bw.M * H;
         const T *pp = patch ? (const T *)patch + (size_t)n0 * P * H : nullptr;
         const int32_t *ii = ids ? ids + (size_t)n0 * T_ : nullptr;
         const float *x_final = nullptr;
@@ -932,6 +983,7 @@ int backward_impl(vla_model *m, void *wsbuf, bool keep, const void *patch, const
             if ((rc = vla_forward_streams(m, bw.ws.fw, mb, pp, ii, bins + (size_t)n0 * A, n, P, T_, A, mode, slot_embed, bw.tail ? A : 0, bw.ws.ckpt, &x_final, st))) return rc;
         }
         // the head's gradient: on the read rows, packed, or in the full ws.dX (zero elsewhere)
+        const size_t MH = (size_t)bw.M * H;
         float *dx = bw.tail ? bw.ws.dXt : bw.ws.dX;
         const int rows_h = bw.tail ? A : R, first_h = bw.tail ? 0 : first_row;
         if (!bw.tail) {
