@@ -445,74 +445,72 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(float *dX, T *dXb, con
     }
 }
 
-// Head forward + backward of one read-out row (one workgroup, thread k = bin k): h = RMSNorm(x) g_f, z = h . W_bins^T,
-// y = z / tau, logp = y_bin - logsumexp(y); d z_k = coef / tau * ([k = bin] - p_k); d h = d z . W_bins; d x by the norm's
-// backward.  Writes logp (if asked) and the row of dX (which is zero elsewhere).
-template <typename T>
-__global__ void __launch_bounds__(256) head_bwd_kernel(float *dX, float *logp_out, const float *X, const float *gain, const T *Wb,
-                                                      const int32_t *bins, const float *coef, int A, int rows_per_seq, int row0,
-                                                      int H, float eps, float inv_tau) {
-    extern __shared__ float smem[];
-    float *hs = smem, *dz = smem + H;          // [H], [256]
-    __shared__ float red[4];
-    __shared__ float stat[2];
-    const int s = blockIdx.x / A, j = blockIdx.x - s * A, t = threadIdx.x;
-    const size_t m = (size_t)s * rows_per_seq + row0 + j;
-    const float *x = X + m * H;
-    float ss = 0.f;
-    for (int i = t; i < H; i += 256) ss += x[i] * x[i];
-    ss = bsum256(ss, red);
-    const float r = 1.0f / sqrtf(ss / (float)H + eps);
-    for (int i = t; i < H; i += 256) hs[i] = x[i] * r * gain[i];
-    __syncthreads();
-    typedef T t8 __attribute__((ext_vector_type(8), aligned(sizeof(T))));       // (H is a multiple of 16)
-    const T *w = Wb + (size_t)t * H;
-    float z = 0.f;
-#pragma unroll 4
-    for (int i = 0; i < H; i += 8) {
-        const t8 v = *(const t8 *)(w + i);
-#pragma unroll
-        for (int e = 0; e < 8; e++) z += hs[i + e] * (float)v[e];
-    }
+// Head forward + backward of the read-out rows: h = RMSNorm(x) g_f and z = h . W_bins^T by the forward's kernels (partial
+// logits per K chunk), then y = z / tau, logp = y_bin - logsumexp(y), d z_k = coef / tau * ([k = bin] - p_k) here (one
+// workgroup per row, thread k = bin k), d h = d z . W_bins, and d x by rmsnorm_bwd_kernel.  (All of it in one workgroup per
+// row walked the 2 MB of W twice alone: 222 us for 224 rows and 212 for 49, now 40
+// in five launches.)
+__global__ void __launch_bounds__(256) head_dz_kernel(float *dz, float *logp_out, const float *P, int n_part, const int32_t *bins,
+                                                     const float *coef, float inv_tau) {
+    __shared__ float red[4], zmax[4];
+    const int row = blockIdx.x, M = gridDim.x, t = threadIdx.x;
+    const float *src = P + (size_t)row * VLA_N_BINS + t;
+    float z = src[0];
+#pragma unroll 15
+    for (int c = 1; c < n_part; c++) z += src[(size_t)c * M * VLA_N_BINS];
     const float y = z * inv_tau;
-    dz[t] = y;
+    const float mw = wmax(y);
+    if ((t & 63) == 0) zmax[t >> 6] = mw;
     __syncthreads();
-    if (t < 64) {
-        float mx = fmaxf(fmaxf(dz[t], dz[t + 64]), fmaxf(dz[t + 128], dz[t + 192]));
-        mx = wmax(mx);
-        float sum = expf(dz[t] - mx) + expf(dz[t + 64] - mx) + expf(dz[t + 128] - mx) + expf(dz[t + 192] - mx);
-        sum = wsum(sum);
-        if (t == 0) { stat[0] = mx; stat[1] = logf(sum) + mx; }
-    }
-    __syncthreads();
-    const float lse = stat[1];
-    int bin = bins[(size_t)s * A + j];
-    bin = min(max(bin, 0), VLA_N_BINS - 1);
-    const float c = coef[(size_t)s * A + j];
-    if (logp_out && t == bin) logp_out[(size_t)s * A + j] = y - lse;
-    __syncthreads();
-    dz[t] = c * inv_tau * ((t == bin ? 1.0f : 0.0f) - expf(y - lse));
-    __syncthreads();
-    // d h_i = sum_k dz_k W[k][i], then the norm's backward; a thread owns columns 8 t .. 8 t + 7, then 2048 further on, ...
-    float xd = 0.f;
-    for (int i = t * 8; i < H; i += 2048) {
-        float dh[8] = {};
-#pragma unroll 8
-        for (int k = 0; k < VLA_N_BINS; k++) {
-            const t8 v = *(const t8 *)(Wb + (size_t)k * H + i);
+    const float mx = fmaxf(fmaxf(zmax[0], zmax[1]), fmaxf(zmax[2], zmax[3]));
+    const float lse = logf(bsum256(expf(y - mx), red)) + mx;
+    const int bin = min(max(bins[row], 0), VLA_N_BINS - 1);
+    if (logp_out && t == bin) logp_out[row] = y - lse;
+    dz[(size_t)row * VLA_N_BINS + t] = coef[row] * inv_tau * ((t == bin ? 1.0f : 0.0f) - expf(y - lse));
+}
+
+// dh[row][i] = sum_k dz[row][k] W[k][i]: four rows x 256 columns per workgroup, four columns per lane, a quarter of the
+// bins per wave (one chain over all of them took 59 us for 49 rows, this 13).
+template <typename T>
+__global__ void __launch_bounds__(256) head_dh_kernel(float *dh, const float *dz, const T *Wb, int M, int H) {
+    typedef T t4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));       // (H is a multiple of 16)
+    __shared__ float s[4][VLA_N_BINS];
+    __shared__ f32x4_t part[3][4][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, m0 = blockIdx.y * 4, i = (blockIdx.x * 64 + lane) * 4;
 #pragma unroll
-            for (int e = 0; e < 8; e++) dh[e] += dz[k] * (float)v[e];
-        }
+    for (int r = 0; r < 4; r++) s[r][threadIdx.x] = dz[(size_t)min(m0 + r, M - 1) * VLA_N_BINS + threadIdx.x];
+    __syncthreads();
+    f32x4_t acc[4] = {};
+    if (i < H) {
+#pragma unroll 32
+        for (int k = wave * 64; k < wave * 64 + 64; k++) {
+            const t4 w = *(const t4 *)(Wb + (size_t)k * H + i);
 #pragma unroll
-        for (int e = 0; e < 8; e++) {
-            hs[i + e] = gain[i + e] * dh[e];        // g dh (h itself is no longer needed)
-            xd += x[i + e] * hs[i + e];
+            for (int r = 0; r < 4; r++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) acc[r][e] += s[r][k] * (float)w[e];
         }
     }
-    xd = bsum256(xd, red);                          // (its barriers also publish hs)
-    const float k3 = r * r * r * xd / (float)H;
-    float *o = dX + m * H;
-    for (int i = t; i < H; i += 256) o[i] = r * hs[i] - x[i] * k3;
+    if (wave)
+#pragma unroll
+        for (int r = 0; r < 4; r++) part[wave - 1][r][lane] = acc[r];
+    __syncthreads();
+    if (wave || i >= H) return;
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+        if (m0 + r < M) *(f32x4_t *)(dh + (size_t)(m0 + r) * H + i) = acc[r] + part[0][r][lane] + part[1][r][lane] + part[2][r][lane];
+}
+
+// Packed rows (the last A of every sequence's R) into the full [M, H], zeros elsewhere, in fp32 and in the storage type.
+template <typename T>
+__global__ void __launch_bounds__(256) scatter_rows_kernel(float *dX, T *dXb, const float *packed, int R, int A, int H) {
+    const int sq = blockIdx.x / R, row = blockIdx.x - sq * R - (R - A);
+    const float *src = packed + ((size_t)sq * A + row) * H;
+    for (int i = threadIdx.x; i < H; i += 256) {
+        const float v = row >= 0 ? src[i] : 0.f;
+        dX[(size_t)blockIdx.x * H + i] = v;
+        dXb[(size_t)blockIdx.x * H + i] = cvt<T>(v);
+    }
 }
 
 // Wt[k][col0 + n] = W[n][k]: the weight matrix [N, K] transposed into a [K, ldt] matrix at column col0 (32 x 32 tiles
@@ -684,7 +682,10 @@ BwSpace plan_bw(const vla_config &c, char *base, int mb, int R, int A, bool keep
     w.dX = (float *)take(M * H * 4);
     w.dXt = tail_form(R, A) ? (float *)take((size_t)mb * A * H * 4) : nullptr;
     w.QKV = (float *)take(M * 3 * H * 4);
-    w.Tmp = (float *)take(M * (F > 3 * H ? F : 3 * H) * 4);
+    // (the head's rows use Tmp first: norm output and its gradient, d z, partial logits)
+    size_t tmp = M * (F > 3 * H ? F : 3 * H);
+    const size_t hd = (size_t)mb * A * (2 * H + (1 + head_chunks(c.hidden)) * (size_t)VLA_N_BINS);
+    w.Tmp = (float *)take((tmp > hd ? tmp : hd) * 4);
     w.dP = (float *)take((size_t)mb * c.n_heads * R * Rp * 4);
     // LoRA products (see lora_group): U | V [2][M, 256] fp32, their rounded transposes [2][256 + pad, kp], the stacked
     // factors, the transposed activations / output gradients and the two [dim, 256] results
@@ -955,7 +956,6 @@ int backward_impl(vla_model *m, void *wsbuf, bool keep, const void *patch, const
     const vla_config &c = m->cfg;
     const int S = P + T_, H = c.hidden, L = c.n_layers;
     const int R = (mode == VLA_MODE_AR) ? S + A - 1 : S + A;
-    const int first_row = (mode == VLA_MODE_AR) ? S - 1 : S;
     const int mb = bw_micro_batch(c, N);
     const T *head = (const T *)m->w.lm_head + (size_t)(c.vocab - VLA_N_BINS) * H;
     int rc;
@@ -982,19 +982,30 @@ int backward_impl(vla_model *m, void *wsbuf, bool keep, const void *patch, const
             // (1) the forward pass of the recompute itself (its fused kernels), keeping every layer's input
             if ((rc = vla_forward_streams(m, bw.ws.fw, mb, pp, ii, bins + (size_t)n0 * A, n, P, T_, A, mode, slot_embed, bw.tail ? A : 0, bw.ws.ckpt, &x_final, st))) return rc;
         }
-        // the head's gradient: on the read rows, packed, or in the full ws.dX (zero elsewhere)
-        const size_t MH = (size_t)bw.M * H;
-        float *dx = bw.tail ? bw.ws.dXt : bw.ws.dX;
-        const int rows_h = bw.tail ? A : R, first_h = bw.tail ? 0 : first_row;
+        // the head's gradient on the read rows, packed; without the tail form spread over the full ws.dX (zero elsewhere)
+        const int Mh = n * A, rows_h = bw.tail ? A : R;
+        float *hb = bw.ws.Tmp, *dh = hb + (size_t)Mh * H, *dz = dh + (size_t)Mh * H, *part = dz + (size_t)Mh * VLA_N_BINS;
+        const float *xh = x_final;
+        float *dx = bw.tail ? bw.ws.dXt : bw.ws.QKV;
         if (!bw.tail) {
-            fill_kernel<<<blocks_for(MH), 256, 0, st>>>(dx, MH, 0.f);
-            if ((rc = vla_check_launch("fill"))) return rc;
+            float *xp = bw.ws.QKV + (size_t)Mh * H;
+            if ((rc = launch_gather_rows(xp, x_final, n, R, R - A, A, H, st))) return rc;
+            xh = xp;
         }
-        head_bwd_kernel<T><<<n * A, 256, (size_t)(H + VLA_N_BINS) * sizeof(float), st>>>(
-            dx, logp ? logp + (size_t)n0 * A : nullptr, x_final, (const float *)m->w.final_norm, head, bins + (size_t)n0 * A,
-            coef + (size_t)n0 * A, A, rows_h, first_h, H, c.rms_eps, 1.0f / temperature);
-        if ((rc = vla_check_launch("head_bwd"))) return rc;
-        if ((rc = bw.cast(bw.ws.dXb, dx, H, n * rows_h))) return rc;
+        if ((rc = launch_final_norm_rows(hb, x_final, (const float *)m->w.final_norm, n, rows_h, rows_h - A, A, H, c.rms_eps, st))) return rc;
+        if ((rc = launch_head_logits<T>(hb, head, part, Mh, H, st))) return rc;
+        head_dz_kernel<<<Mh, 256, 0, st>>>(dz, logp ? logp + (size_t)n0 * A : nullptr, part, head_chunks(H), bins + (size_t)n0 * A,
+                                           coef + (size_t)n0 * A, 1.0f / temperature);
+        if ((rc = vla_check_launch("head_dz"))) return rc;
+        head_dh_kernel<T><<<dim3((H + 255) / 256, (Mh + 3) / 4), 256, 0, st>>>(dh, dz, head, Mh, H);
+        if ((rc = vla_check_launch("head_dh"))) return rc;
+        rmsnorm_bwd_kernel<T><<<Mh, 256, 0, st>>>(dx, (T *)bw.ws.dXb, nullptr, 1, 0, xh, (const float *)m->w.final_norm, dh, H, c.rms_eps);
+        if ((rc = vla_check_launch("head rmsnorm_bwd"))) return rc;
+        if (!bw.tail) {
+            scatter_rows_kernel<T><<<bw.M, 256, 0, st>>>(bw.ws.dX, (T *)bw.ws.dXb, dx, R, A, H);
+            if ((rc = vla_check_launch("scatter_rows"))) return rc;
+            dx = bw.ws.dX;
+        }
         for (int l = L - 1; l >= 0; l--)
             if ((rc = bw.layer_backward(l, lora[l], grads[l], first, l == L - 1 ? dx : bw.ws.dX))) return rc;
     }

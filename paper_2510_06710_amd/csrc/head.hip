@@ -298,8 +298,19 @@ __global__ void __launch_bounds__(256) head_whole_kernel(const float *h, const T
 
 }  // namespace
 
+static int chunks_of(int H) { return (H + CHUNK - 1) / CHUNK; }
 size_t head_scratch_bytes(int n_rows, int H) {
-    return n_rows > VLA_HEAD_PARTIAL_ROWS ? 0 : (size_t)((H + CHUNK - 1) / CHUNK) * n_rows * VLA_N_BINS * sizeof(float);
+    return n_rows > VLA_HEAD_PARTIAL_ROWS ? 0 : (size_t)chunks_of(H) * n_rows * VLA_N_BINS * sizeof(float);
+}
+
+int head_chunks(int H) { return chunks_of(H); }
+
+// Partial logits alone: P[chunk][n_rows][256], to be added in chunk order.
+template <typename T>
+int launch_head_logits(const float *h, const T *lm_head_bins, float *P, int n_rows, int H, hipStream_t st) {
+    if (n_rows == 0) return 0;
+    head_partial_kernel<T><<<dim3(head_chunks(H), (n_rows + 15) / 16, 4), 128, 0, st>>>(h, lm_head_bins, P, n_rows, H);
+    return vla_check_launch("head_logits");
 }
 
 template <typename T>
@@ -314,14 +325,13 @@ int launch_head_sample(const float *h, const T *lm_head_bins, int n_rows, int H,
         head_whole_kernel<T><<<(n_rows + 31) / 32, 256, 0, st>>>(h, lm_head_bins, a, X_next, embed, vocab, n_rows, H);
         return vla_check_launch("head_sample");
     }
-    const int chunks = (H + CHUNK - 1) / CHUNK;
-    head_partial_kernel<T><<<dim3(chunks, (n_rows + 15) / 16, 4), 128, 0, st>>>(h, lm_head_bins, scratch, n_rows, H);
-    if (int rc = vla_check_launch("head_partial")) return rc;
-    sample_kernel<T><<<n_rows, 256, 0, st>>>(scratch, chunks, a, X_next, embed, vocab, H);
+    if (int rc = launch_head_logits<T>(h, lm_head_bins, scratch, n_rows, H, st)) return rc;
+    sample_kernel<T><<<n_rows, 256, 0, st>>>(scratch, head_chunks(H), a, X_next, embed, vocab, H);
     return vla_check_launch("head_sample");
 }
 
 #define INSTANTIATE(T)                                                                                        \
+    template int launch_head_logits<T>(const float *, const T *, float *, int, int, hipStream_t);             \
     template int launch_head_sample<T>(const float *, const T *, int, int, float, const float *,              \
                                        const int32_t *, int32_t *, float *, float *, float *, int, int,       \
                                        float *, const T *, int, float *, hipStream_t);

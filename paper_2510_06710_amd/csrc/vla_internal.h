@@ -113,6 +113,10 @@ int launch_head_sample(const float *h, const T *lm_head_bins, int n_rows, int H,
                        const float *gumbel, const int32_t *given_bins, int32_t *bins_out, float *logp,
                        float *ent, float *logits, int out_stride, int out_off, float *X_next,
                        const T *embed, int vocab, float *scratch, hipStream_t st);
+// Partial logits h . W^T of n_rows rows, P[head_chunks(H)][n_rows][256] to be added in chunk order.
+int head_chunks(int H);
+template <typename T>
+int launch_head_logits(const float *h, const T *lm_head_bins, float *P, int n_rows, int H, hipStream_t st);
 // scratch of launch_head_sample for n_rows rows (device, fp32 partial logits; none above VLA_HEAD_PARTIAL_ROWS rows)
 constexpr int VLA_HEAD_PARTIAL_ROWS = 4096;
 size_t head_scratch_bytes(int n_rows, int H);
