@@ -238,6 +238,7 @@ static int run_gemm(const vla_config &c, GemmArgs g, void *skinny_scratch, hipSt
             if (r == 0) r = try_gemm_bf16_skinny(g, skinny_scratch, st);
         }
         if (r != 0) return r < 0 ? r : 0;
+        if (g.norm_x) { vla_set_error("internal: the norm in the GEMM was declined"); return VLA_ESHAPE; }
         if (g.split_scratch && !(force_generic() & 1)) r = try_gemm_bf16_dma_splitk_rows(g, g.split_scratch, g.split_scratch_bytes, st);
         if (r != 0) return r < 0 ? r : 0;
         r = (force_generic() & 1) ? 0 : try_gemm_bf16_large(g, st);
@@ -390,6 +391,10 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
     // in the order the stand-alone reduction would.
     const bool fuse_reduce = c.dtype == VLA_DTYPE_BF16 && ra.R == 1 && ws.skinny && !(force_generic() & (2 | 16)) &&
                              H % 1024 == 0 && H <= 8192;
+    // Steps of few rows: the QKV and gate/up GEMMs form the norm of their input themselves
+    const bool norms = c.dtype == VLA_DTYPE_BF16 && ra.R == 1 && ws.skinny && !(force_generic() & (2 | 16));
+    const bool qkv_norms = norms && gemm_stream_norms(M, H, H), ffn_norms = norms && gemm_stream_norms(M, H, F);
+    auto give_norm = [&](GemmArgs &g, const void *gain) { g.norm_x = ws.X; g.norm_gain = (const float *)gain; g.norm_eps = c.rms_eps; };
     bool have_nrm = false;                 // the previous layer's down projection already wrote this layer's Nrm
     const bool tail_form = use_tail(tail, ra.R) && ws.tail_rows == tail->count && ra.R > 1;
     for (int l = 0; l < c.n_layers; l++) {
@@ -405,7 +410,8 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
             if ((rc = run_layer_kblocked(m, ws, ra, kv, l, kl, st))) return rc;
             continue;
         }
-        if (!have_nrm && (rc = run_rmsnorm<T>(c, ws.Nrm, ws.X, lw.attn_norm, M, 0, st))) return rc;
+        const bool qkv_norm = qkv_norms && !have_nrm;
+        if (!have_nrm && !qkv_norm && (rc = run_rmsnorm<T>(c, ws.Nrm, ws.X, lw.attn_norm, M, 0, st))) return rc;
         have_nrm = false;
         // single-row forwards stream the weights from HBM: hand the GEMMs the repacked copies as well, where they exist
         const vla_layer_weights *pk = (ra.R == 1 && !m->packed.empty() && kblocked_shape_ok(c)) ? &m->packed[l] : nullptr;
@@ -414,6 +420,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         g.A = ws.Nrm; g.W[0] = lw.wq; g.W[1] = lw.wk; g.W[2] = lw.wv; g.n_seg = 3; g.segN = H;
         g.C = ws.QKV; g.M = M; g.K = H; g.epilogue = EPI_STORE; g.a_rows = ws.a_rows;
         g.step = ra.R == 1;
+        if (qkv_norm) give_norm(g, lw.attn_norm);
         if (pk) { g.Wkb[0] = pk->wq; g.Wkb[1] = pk->wk; g.Wkb[2] = pk->wv; }
         // multi-row bf16 forwards at head_dim 128: rotation and KV write ride the projection's epilogue
         int fused = 0;
@@ -459,11 +466,13 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
             rc = try_reduce_residual_rmsnorm_bf16((bf16_t *)ws.Nrm, ws.X, (const float *)ws.skinny, ds, M, H, (const float *)lw.ffn_norm, c.rms_eps, st);
             if (rc == 0) { vla_set_error("internal: fused reduction declined"); return VLA_ESHAPE; }
             if (rc < 0) return rc;
-        } else if ((rc = run_rmsnorm<T>(c, ws.Nrm, ws.X, lw.ffn_norm, M, 0, st))) return rc;
+        } else if (!ffn_norms && (rc = run_rmsnorm<T>(c, ws.Nrm, ws.X, lw.ffn_norm, M, 0, st))) return rc;
+        const bool ffn_norm = ffn_norms && !ds;
         g = GemmArgs{};
         g.A = ws.Nrm; g.W[0] = lw.w_gate; g.W[1] = lw.w_up; g.n_seg = 2; g.segN = F; g.C = ws.ACT; g.M = M; g.K = H;
         g.epilogue = EPI_SWIGLU; g.a_rows = ws.a_rows;
         g.step = ra.R == 1;
+        if (ffn_norm) give_norm(g, lw.ffn_norm);
         if (pk) { g.Wkb[0] = pk->w_gate; g.Wkb[1] = pk->w_up; }
         if ((rc = run_gemm<T>(c, g, ws.skinny, st))) return rc;
         g = GemmArgs{};

@@ -66,6 +66,8 @@ struct GemmArgs {
     int a_rows;             // rows of A that may be read (>= M; contents past M arbitrary): the MFMA kernel
                             // loads whole 256-row tiles and declines if the buffer does not cover them
     int step;               // a decode step (one row per sequence): the weight-streaming kernel of few rows may take it
+    const float *norm_x, *norm_gain;   // not NULL (steps for which gemm_stream_norms): A is RMSNorm(norm_x) norm_gain, formed by
+    float norm_eps;                    // the kernel from the fp32 rows [M, K]
     int *deferred_splits;   // not NULL (EPI_STORE and EPI_RESIDUAL of the split-K kernels): the kernel leaves its n
                             // partial products [n][M][N] at the start of the scratch buffer, puts n here and does not
                             // reduce them (the caller's next kernel adds them in order); 0 here: C is complete
@@ -186,6 +188,7 @@ int try_reduce_residual_rmsnorm_bf16(bf16_t *out, float *X, const float *P, int 
                                      float eps, hipStream_t st);
 // kb_rows = 0: row-major output [M, H]; else k-blocked [H / 32][kb_rows][32]
 int try_rmsnorm_bf16(bf16_t *out, const float *X, const float *gain, int M, int H, float eps, int kb_rows, hipStream_t st);
+bool gemm_stream_norms(int M, int K, int segN);
 int try_gemm_bf16_stream(const GemmArgs &g, hipStream_t st);
 int try_gemm_bf16_skinny(const GemmArgs &g, void *scratch, hipStream_t st);
 int try_gemm_bf16_mid(const GemmArgs &g, void *scratch, size_t scratch_bytes, hipStream_t st);
