@@ -7,17 +7,17 @@
 // final one and no reduction kernel follows.  Weights go from memory straight into MFMA operand registers: in the
 // repacked layout ([K / 32][rows][32]) a fragment of 16 rows x 32 columns is 1 KB in a row, one load instruction; row-major
 // weights take the same instruction with 64-byte pieces.  Activations (L2) come the same way, shared by the R row blocks.
-// The grid is all resident at once (up to four workgroups per CU), which is what keeps HBM busy: a CU streams up to
-// 58 GB/s, 256 of them 6 TB/s.
+// One (O, down) to three workgroups share a CU; a CU streams up to 58 GB/s, 256 of them 6 TB/s together.
 // Measured at one row on the 7B shape against the split-K form (gemm_skinny.hip) and the reductions that follow it: QKV 23.4
 // -> 18.7 us, O and down 27.8 + 5.3 -> 13.6 + 3.9 (mean, with the norm), gate/up 43.1 + 4.6 -> 32.6 us (5.5 TB/s).  The
-// activations' L2 traffic (every workgroup reads all of them) grows with the rows: 16 rows 27 / 19 / 41 us, 32 rows 33 /
+// activations' L2 traffic (every workgroup reads all of them) grows with the rows: 16 rows 27 / 19 / 39 us, 32 rows 33 /
 // 24 / 47 us, where both forms cost the same per layer; 64 rows 49 / 40 / 69 against 32 / 25 / 57 us, so the rule ends at 32.
 //
 // NORM rows (1, or up to 4): the activations are RMSNorm(x) g of fp32 rows x of at most 4096 columns (eight per thread),
 // which every workgroup forms for itself in LDS while its first weights are on the way.  At one row the two norms of a layer
 // took 9.4 us in launches of their own; the GEMMs with them take 31.7 us for gate/up (32.7 without: fewer registers, two
-// workgroups per CU) and 19.1 for QKV (18.0).
+// workgroups per CU) and 19.1 for QKV (18.0).  With four rows, norm included, 37 and 26 against 34 + 6 and 21 + 6; the rows
+// that a thread holds end the rule there.
 #include "vla_internal.h"
 
 namespace {
@@ -191,11 +191,13 @@ __global__ void __launch_bounds__(512) gemm_stream_kernel(StreamParams p) {
 
 template <int EPI>
 void launch_rows(const StreamParams &p, hipStream_t st) {
-    constexpr int UN = EPI == EPI_SWIGLU ? 6 : 8;
+    // Steps in flight: as many as leave at most 128 registers, two workgroups per CU (gate/up at 13 rows: 6 steps, 140 registers
+    // 37.5 us, 5 steps 34.5; 3 or 4 steps the same)
+    constexpr int UN = EPI == EPI_SWIGLU ? 5 : 8, UN_NORM = EPI == EPI_SWIGLU ? 6 : 8;
     if constexpr (EPI != EPI_RESIDUAL) {
         const size_t lds = (size_t)p.M * (p.K + 32) * sizeof(bf16_t);
-        if (p.x && p.M == 1) { gemm_stream_kernel<EPI, 1, 1, UN, 1><<<p.N / 16, 512, lds, st>>>(p); return; }
-        if (p.x) { gemm_stream_kernel<EPI, 1, 1, UN, 4><<<p.N / 16, 512, lds, st>>>(p); return; }
+        if (p.x && p.M == 1) { gemm_stream_kernel<EPI, 1, 1, UN_NORM, 1><<<p.N / 16, 512, lds, st>>>(p); return; }
+        if (p.x) { gemm_stream_kernel<EPI, 1, 1, UN_NORM, 4><<<p.N / 16, 512, lds, st>>>(p); return; }
     }
     if (p.M <= 16) gemm_stream_kernel<EPI, 1, 1, UN, 0><<<p.N / 16, 512, 0, st>>>(p);
     else if (EPI == EPI_RESIDUAL) gemm_stream_kernel<EPI, 2, 1, 4, 0><<<p.N / 16, 512, 0, st>>>(p);
