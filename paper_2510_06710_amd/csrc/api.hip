@@ -215,18 +215,17 @@ static size_t prepack_layer_bytes(const vla_config &c) {
 // The large-tile GEMM (declines K below 256 or not a multiple of 64: the generic kernel then takes the call).
 static int try_gemm_bf16_large(const GemmArgs &g, hipStream_t st) { return try_gemm_bf16_dma(g, st); }
 
-// Kernel choice depends on the storage type, on whether the forward has one row per sequence (decode) and, for
-// decode forwards, on the batch: up to 128 rows stream the weights through the skinny kernel, larger batches use
-// the split-K tile kernels.  The K ranges, and with them the order in which a row's products are summed, therefore
-// differ between batch sizes on either side of 128 (each configuration by itself is deterministic, and within one
-// call a row's result does not depend on the other rows).
+// Kernel choice depends on the storage type, on whether the forward has one row per sequence and, for these, on the rows:
+// decode steps of up to 32 rows take the weight-streaming kernel (whole K per workgroup), up to 128 rows the small tiles (QKV,
+// gate/up) and the skinny split-K kernel (O, down), larger ones and all tail rows the split-K kernels.  The K ranges, and with
+// them the order in which a row's products are summed, therefore differ between batch sizes on either side of 32 and 128 (each
+// configuration by itself is deterministic, and within one call a row's result does not depend on the other rows).
 template <typename T>
 static int run_gemm(const vla_config &c, GemmArgs g, void *skinny_scratch, hipStream_t st) {
     if (c.dtype == VLA_DTYPE_BF16) {
         int r = 0;
         if (skinny_scratch && !(force_generic() & 2)) {
-            // single-row forwards: up to 128 rows stream the weights through the skinny kernel; above
-            // that the work is MFMA bound and the large tile with split K does better
+            // above 128 rows the work is MFMA bound and the large tile with split K does better
             if (g.M > 128 && !(force_generic() & 1)) {
                 const size_t sb = gemm_skinny_scratch_bytes(g.M, 2 * c.ffn > 3 * c.hidden ? 2 * c.ffn : 3 * c.hidden);
                 r = try_gemm_bf16_dma_splitk(g, skinny_scratch, sb, st);
