@@ -274,10 +274,6 @@ int bgemm(const BgemmArgs &g, int batch, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------------------------- elementwise pieces
-__global__ void fill_kernel(float *p, size_t n, float v) {
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = v;
-}
-
 // rows [M, cols] fp32 -> storage type, row strides given
 template <typename T>
 __global__ void cast_rows_kernel(T *out, const float *in, size_t M, int cols, int ld_out, int ld_in) {
