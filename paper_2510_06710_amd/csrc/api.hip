@@ -423,7 +423,8 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         if (pk) { g.Wkb[0] = pk->wq; g.Wkb[1] = pk->wk; g.Wkb[2] = pk->wv; }
         // multi-row bf16 forwards at head_dim 128: rotation and KV write ride the projection's epilogue
         int fused = 0;
-        bool attended = false;
+        // single-row forwards of few pairs: the attention kernel takes the projection as it is (rotation, KV write)
+        const bool attends = c.dtype == VLA_DTYPE_BF16 && !(force_generic() & (8 | 16)) && attention_decode_fuses_qkv(kv, ra);
         if (c.dtype == VLA_DTYPE_BF16 && ra.R > 1 && d == 128 && !(force_generic() & (1 | 16))) {
             QkvRopeArgs qa{ws.Q, ws.rope, &kv, kl, &ra};
             GemmArgs gf = g;
@@ -432,20 +433,16 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
             if (fused < 0) return fused;
         }
         if (!fused) {
-            if (fuse_reduce) g.deferred_splits = &ds;
+            if (fuse_reduce && !attends) g.deferred_splits = &ds;
             if ((rc = run_gemm<T>(c, g, ws.skinny, st))) return rc;
-            if (c.dtype == VLA_DTYPE_BF16 && !(force_generic() & (8 | 16)) && attention_decode_fuses_qkv(kv, ra)) {
-                // single-row forwards: the attention kernel takes the projection as it is (sum of the parts, rotation, KV write)
-                attended = true;
-                rc = launch_attention_decode_qkv((bf16_t *)ws.AO, ds ? (const float *)ws.skinny : ws.QKV, ds ? ds : 1, (size_t)M * 3 * H,
-                                                 ws.rope, kv, kl, ra, H, st);
-            } else if (c.dtype == VLA_DTYPE_BF16 && !(force_generic() & 16))
+            if (attends) rc = launch_attention_decode_qkv((bf16_t *)ws.AO, ws.QKV, ws.rope, kv, kl, ra, H, st);
+            else if (c.dtype == VLA_DTYPE_BF16 && !(force_generic() & 16))
                 rc = launch_rope_kv_write_bf16((bf16_t *)ws.Q, ds ? (const float *)ws.skinny : ws.QKV, ds ? ds : 1, (size_t)M * 3 * H,
                                                ws.rope, kv, kl, ra, H, st);
             else rc = launch_rope_kv_write<T>((T *)ws.Q, ws.QKV, ws.rope, kv, kl, ra, H, st);
             if (rc) return rc;
         }
-        int done = attended ? 1 : 0;
+        int done = attends ? 1 : 0;
         if (c.dtype == VLA_DTYPE_BF16 && !done) {
             if (ra.R == 1)
                 done = (force_generic() & 8) ? 0 : try_attention_decode_bf16((bf16_t *)ws.AO, (const bf16_t *)ws.Q, kv, kl, ra, H, st);

@@ -10,6 +10,7 @@
 //   3. P.V: V is stored [position][d]; 8 (d = 64) or 16 (d = 128) lanes cover one V row with 16-byte
 //      loads, the wave covers 8 / 4 rows per instruction (1 KB contiguous), probabilities come from
 //      LDS, and the row groups are summed by lane-xor steps and a four-way add through LDS.
+// Of few pairs each gets eight waves (see FEW_PAIRS), half the V columns per lane.
 #include "vla_internal.h"
 
 namespace {
@@ -27,22 +28,28 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
-// What the projection left for this step (FUSE): `splits` partial copies of the fp32 [n_seq, 3H] QKV rows, added in order.
+// What the projection left for this step (FUSE): the fp32 [n_seq, 3H] QKV rows.
 struct FusedQkv {
     const float *qkv;
-    int splits;
-    size_t split_stride;
     const float2 *table;       // (cos, sin) of this position
 };
 
-// One workgroup of NWV waves per (sequence, head) pair; the waves split the keys.  FUSE: the workgroup also adds up its
-// head's q, k, v, rotates q and k and writes k and v to the cache (the rounding of rope_kv_write_bf16_kernel); the new
+// One workgroup of NWV waves (4 or 8) per (sequence, head) pair; the waves split the keys.  FUSE: the workgroup also
+// rotates its head's q and k and writes k and v to the cache (the rounding of rope_kv_write_bf16_kernel); the new
 // position's k and v are then taken from LDS.
+// All forms give the same bits, so that a sequence's result does not depend on how many share the step: a score is one
+// chain over the dims; the softmax's sum adds key chunks w and w + 4 lane by lane, then the lanes, then w = 0..3; P.V has
+// one chain for every 4 * (512 / D) th position (eight waves hold the same chains with half the columns per lane) and a
+// fixed tree over the chains.
 template <int D, int NWV, bool FUSE>
 __global__ void __launch_bounds__(64 * NWV) attn_decode_kernel(bf16_t *out, const bf16_t *qbuf, bf16_t *kc, bf16_t *vc, FusedQkv f,
                                                               int n_heads, int nk, int pos_stride, int H) {
+    static_assert(NWV == 4 || (NWV == 8 && MAXCH == 8), "the order of the sums");
     constexpr int DC = D / 8;        // 16-byte chunks per head vector
-    constexpr int RPI = 64 / DC;     // V rows per wave load instruction
+    constexpr int VPL = 32 / NWV;    // V columns per lane
+    constexpr int LPR = D / VPL;     // lanes per V row
+    constexpr int RPI = 64 / LPR;    // V rows per wave load instruction
+    typedef bf16_t bf16v __attribute__((ext_vector_type(VPL)));
     constexpr int CPW = MAXCH / NWV; // key chunks of 64 per wave (chunk index = NWV * it + wave)
     __shared__ __attribute__((aligned(16))) float qs[D];
     __shared__ __attribute__((aligned(16))) bf16_t knew[D], vnew[D];
@@ -58,25 +65,19 @@ __global__ void __launch_bounds__(64 * NWV) attn_decode_kernel(bf16_t *out, cons
     const int n_old = FUSE ? nk - 1 : nk;                   // positions read from the cache
     if (FUSE) {
         float *raw = &part[0][0];                           // q, k of the head before the rotation (D floats each)
-        static_assert(NWV >= 2, "raw needs two rows of `part`");
         float v = 0.f;
         if (t < D) {
             const float *src = f.qkv + (size_t)s * 3 * H + (size_t)h * D + t;
-            float q = src[0], k = src[H];
+            raw[t] = src[0]; raw[D + t] = src[H];
             v = src[2 * (size_t)H];
-            for (int i = 1; i < f.splits; i++) {
-                const float *p = src + (size_t)i * f.split_stride;
-                q += p[0]; k += p[H]; v += p[2 * (size_t)H];
-            }
-            raw[t] = q; raw[D + t] = k;
         }
         __syncthreads();
         if (t < D) {
             const int half = D / 2, i = t & (half - 1);
             const float2 cs = f.table[i];
             const float qa = raw[i], qb = raw[i + half], ka = raw[D + i], kb = raw[D + i + half];
-            const bf16_t qr = (bf16_t)(t < half ? qa * cs.x - qb * cs.y : qb * cs.x + qa * cs.y);
-            const bf16_t kr = (bf16_t)(t < half ? ka * cs.x - kb * cs.y : kb * cs.x + ka * cs.y);
+            const bf16_t qr = (bf16_t)(t < half ? vla_rotate_lo(qa, qb, cs.x, cs.y) : vla_rotate_hi(qa, qb, cs.x, cs.y));
+            const bf16_t kr = (bf16_t)(t < half ? vla_rotate_lo(ka, kb, cs.x, cs.y) : vla_rotate_hi(ka, kb, cs.x, cs.y));
             qs[t] = (float)qr * scale;
             knew[t] = kr; vnew[t] = (bf16_t)v;
             kh[((size_t)(t >> 3) * pos_stride + nk - 1) * 8 + (t & 7)] = kr;
@@ -94,30 +95,28 @@ __global__ void __launch_bounds__(64 * NWV) attn_decode_kernel(bf16_t *out, cons
     for (int it = 0; it < CPW; it++) {
         sc[it] = -INFINITY;
         const int p = (it * NWV + wave) * 64 + lane;
-        if (p < n_old) {
+        if (p < nk) {
+            bf16x8_t kv[DC];
+            if (!FUSE || p < n_old) {
+#pragma unroll
+                for (int c = 0; c < DC; c++) kv[c] = *(const bf16x8_t *)(kh + ((size_t)c * pos_stride + p) * 8);
+            } else {
+#pragma unroll
+                for (int c = 0; c < DC; c++) kv[c] = *(const bf16x8_t *)&knew[c * 8];
+            }
             float a = 0.f;
 #pragma unroll
             for (int c = 0; c < DC; c++) {
-                bf16x8_t kv = *(const bf16x8_t *)(kh + ((size_t)c * pos_stride + p) * 8);
                 f32x4_t q0 = *(const f32x4_t *)&qs[c * 8];
                 f32x4_t q1 = *(const f32x4_t *)&qs[c * 8 + 4];
 #pragma unroll
-                for (int e = 0; e < 4; e++) a += q0[e] * (float)kv[e];
+                for (int e = 0; e < 4; e++) a += q0[e] * (float)kv[c][e];
 #pragma unroll
-                for (int e = 0; e < 4; e++) a += q1[e] * (float)kv[4 + e];
+                for (int e = 0; e < 4; e++) a += q1[e] * (float)kv[c][4 + e];
             }
             sc[it] = a;
             mx = fmaxf(mx, a);
         }
-    }
-    if (FUSE && (n_old >> 6) % NWV == wave) {               // the new position: the wave that owns it, dims across the lanes
-        float a = 0.f;
-#pragma unroll
-        for (int i = 0; i < D; i += 64) a += qs[i + lane] * (float)knew[i + lane];
-        a = wave_sum(a);
-#pragma unroll
-        for (int it = 0; it < CPW; it++)
-            if (it == (n_old >> 6) / NWV && lane == (n_old & 63)) { sc[it] = a; mx = fmaxf(mx, a); }
     }
     // ---- 2. softmax over all keys of the workgroup ---------------------------------------------------
     mx = wave_max(mx);
@@ -131,44 +130,52 @@ __global__ void __launch_bounds__(64 * NWV) attn_decode_kernel(bf16_t *out, cons
         const float e = __expf(sc[it] - mx);                       // exp(-inf) = 0 for positions >= nk
         sc[it] = e;
         sum += e;
+        if (NWV == 8) ps[(it * NWV + wave) * 64 + lane] = e;
+    }
+    if (NWV == 8) {
+        __syncthreads();
+        sum = ps[(wave & 3) * 64 + lane] + ps[((wave & 3) + 4) * 64 + lane];
     }
     sum = wave_sum(sum);
-    if (lane == 0) red[NWV + wave] = sum;
+    if (lane == 0) red[NWV + wave] = sum;                          // (of eight waves, 4..7 repeat 0..3)
     __syncthreads();
     float tot = red[NWV];
 #pragma unroll
-    for (int w = 1; w < NWV; w++) tot += red[NWV + w];
+    for (int w = 1; w < 4; w++) tot += red[NWV + w];
     const float inv = 1.0f / tot;
+    if (NWV == 4) {
 #pragma unroll
-    for (int it = 0; it < CPW; it++) {
-        const int p = (it * NWV + wave) * 64 + lane;
-        if (p < nk) ps[p] = sc[it] * inv;
+        for (int it = 0; it < CPW; it++) {
+            const int p = (it * NWV + wave) * 64 + lane;
+            if (p < nk) ps[p] = sc[it] * inv;
+        }
+        __syncthreads();
     }
-    __syncthreads();
 
     // ---- 3. P.V: the workgroup covers NWV * RPI rows per step, wave w rows w * RPI + g ------------------
-    const int c = lane % DC, g = lane / DC;
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const int c = lane % LPR, g = lane / LPR, slot = wave * RPI + g;
+    auto probability = [&](int pos) { return NWV == 4 ? ps[pos] : ps[pos] * inv; };
+    float acc[VPL] = {};
 #pragma unroll 4
-    for (int pos = wave * RPI + g; pos < n_old; pos += NWV * RPI) {
-        bf16x8_t v = *(const bf16x8_t *)(vh + (size_t)pos * D + c * 8);
-        const float pr = ps[pos];
+    for (int pos = slot; pos < n_old; pos += NWV * RPI) {
+        const bf16v v = *(const bf16v *)(vh + (size_t)pos * D + c * VPL);
+        const float pr = probability(pos);
 #pragma unroll
-        for (int e = 0; e < 8; e++) acc[e] += pr * (float)v[e];
+        for (int e = 0; e < VPL; e++) acc[e] += pr * (float)v[e];
     }
-    if (FUSE && wave == 0 && g == 0) {
-        const bf16x8_t v = *(const bf16x8_t *)&vnew[c * 8];
-        const float pr = ps[n_old];
+    if (FUSE && n_old % (NWV * RPI) == slot) {
+        const bf16v v = *(const bf16v *)&vnew[c * VPL];
+        const float pr = probability(n_old);
 #pragma unroll
-        for (int e = 0; e < 8; e++) acc[e] += pr * (float)v[e];
+        for (int e = 0; e < VPL; e++) acc[e] += pr * (float)v[e];
     }
 #pragma unroll
-    for (int off = DC; off < 64; off <<= 1)
+    for (int off = LPR; off < 64; off <<= 1)
 #pragma unroll
-        for (int e = 0; e < 8; e++) acc[e] += __shfl_xor(acc[e], off, 64);
-    if (lane < DC) {
+        for (int e = 0; e < VPL; e++) acc[e] += __shfl_xor(acc[e], off, 64);
+    if (lane < LPR) {
 #pragma unroll
-        for (int e = 0; e < 8; e++) part[wave][c * 8 + e] = acc[e];
+        for (int e = 0; e < VPL; e++) part[wave][c * VPL + e] = acc[e];
     }
     __syncthreads();
     if (t < DC) {
@@ -219,15 +226,15 @@ bool attention_decode_fuses_qkv(const KvView &kv, const RowsArgs &ra) {
     return decode_shape_ok(kv, ra) && ra.n_seq * kv.n_heads < FEW_PAIRS;
 }
 
-// The decode step's attention straight from the QKV projection: `splits` partial copies of the fp32 [n_seq, 3H] rows,
-// `split_stride` floats apart.  Only where attention_decode_fuses_qkv().
-int launch_attention_decode_qkv(bf16_t *out, const float *qkv, int splits, size_t split_stride, const float2 *table, const KvView &kv,
-                                int layer, const RowsArgs &ra, int H, hipStream_t st) {
+// The decode step's attention straight from the QKV projection, fp32 [n_seq, 3H] rows.  Only where
+// attention_decode_fuses_qkv().
+int launch_attention_decode_qkv(bf16_t *out, const float *qkv, const float2 *table, const KvView &kv, int layer, const RowsArgs &ra,
+                                int H, hipStream_t st) {
     const int nk = ra.pos0 + 1, n_items = ra.n_seq * kv.n_heads;
     if (n_items == 0) return 0;
     bf16_t *kc = (bf16_t *)kv.k + (size_t)layer * kv.layer_elems, *vc = (bf16_t *)kv.v + (size_t)layer * kv.layer_elems;
     ProfScope ps("attn_decode", 2.0 * n_items * (double)nk * kv.d * 2.0, st);
-    const FusedQkv f{qkv, splits, split_stride, table};
+    const FusedQkv f{qkv, table};
     if (kv.d == 128) attn_decode_kernel<128, 8, true><<<n_items, 512, 0, st>>>(out, nullptr, kc, vc, f, kv.n_heads, nk, kv.pos_stride, H);
     else attn_decode_kernel<64, 8, true><<<n_items, 512, 0, st>>>(out, nullptr, kc, vc, f, kv.n_heads, nk, kv.pos_stride, H);
     return vla_check_launch("attn_decode_qkv");

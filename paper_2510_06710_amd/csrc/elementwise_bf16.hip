@@ -66,10 +66,10 @@ __global__ void __launch_bounds__(256) rope_kv_write_bf16_kernel(bf16_t *q_out, 
 #pragma unroll
     for (int e = 0; e < 8; e++) {
         const float co = cs[2 * e], si = cs[2 * e + 1];
-        qlo[e] = qa[e] * co - qb[e] * si;
-        qhi[e] = qb[e] * co + qa[e] * si;
-        klo[e] = ka[e] * co - kb[e] * si;
-        khi[e] = kb[e] * co + ka[e] * si;
+        qlo[e] = vla_rotate_lo(qa[e], qb[e], co, si);
+        qhi[e] = vla_rotate_hi(qa[e], qb[e], co, si);
+        klo[e] = vla_rotate_lo(ka[e], kb[e], co, si);
+        khi[e] = vla_rotate_hi(ka[e], kb[e], co, si);
     }
     bf16_t *qo = q_out + m * (size_t)H + (size_t)h * d + c * 8;
     *(bf16x8_t *)qo = pack8(qlo);

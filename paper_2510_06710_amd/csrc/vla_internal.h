@@ -125,6 +125,11 @@ size_t head_scratch_bytes(int n_rows, int H);
 int launch_value_head(float *value, const float *h, const float *w, float b, const float *bias, int vd, int n,
                       int H, int h_stride, hipStream_t st);
 
+// One pair (a, b) rotated by (cos, sin), rounded once after one fused multiply-add each: written out where two kernels must
+// agree bit for bit (the compiler fuses either product of a sum of two).
+__device__ __forceinline__ float vla_rotate_lo(float a, float b, float co, float si) { return __builtin_fmaf(a, co, -(b * si)); }
+__device__ __forceinline__ float vla_rotate_hi(float a, float b, float co, float si) { return __builtin_fmaf(b, co, a * si); }
+
 // silu(gate) * up of the bf16 fast paths: hardware exponential and reciprocal (1 ulp each, far below
 // the bf16 rounding that follows); one formula for the prefill and the decode GEMMs so that both
 // round the same way.
@@ -200,8 +205,8 @@ int try_attention_prefill_bf16(bf16_t *out, const bf16_t *q, const KvView &kv, i
 int try_attention_decode_bf16(bf16_t *out, const bf16_t *q, const KvView &kv, int layer,
                               const RowsArgs &ra, int H, hipStream_t st);
 bool attention_decode_fuses_qkv(const KvView &kv, const RowsArgs &ra);
-int launch_attention_decode_qkv(bf16_t *out, const float *qkv, int splits, size_t split_stride, const float2 *table, const KvView &kv,
-                                int layer, const RowsArgs &ra, int H, hipStream_t st);
+int launch_attention_decode_qkv(bf16_t *out, const float *qkv, const float2 *table, const KvView &kv, int layer, const RowsArgs &ra,
+                                int H, hipStream_t st);
 size_t attention_prefill_scratch_bytes(int n_seq, int n_heads, int d, int n_keys);
 
 int vla_check_launch(const char *what);

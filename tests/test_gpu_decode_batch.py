@@ -1,0 +1,44 @@
+"""A decode step's result for an environment does not depend, bit for bit, on how many others share the step, up to 128 of
+them: whichever kernels the row count selects add in one order."""
+import functools
+
+import pytest
+import torch
+
+import vla_inputs as vi
+from paper_2510_06710_amd.harness import Rollout
+
+pytestmark = pytest.mark.gpu
+MANY, S, A = 128, 300, 4
+SHAPES = {
+    # head_dim 64, K in four parts of 8 and 11 tiles
+    "h2048": vi.ModelShape(n_layers=2, hidden=2048, n_heads=32, ffn=2816, vocab=640, dtype="bf16"),
+    # the 7B width: eight parts, two for the down projection, repacked weights
+    "h4096": vi.ModelShape(n_layers=1, hidden=4096, n_heads=32, ffn=1152, vocab=640, dtype="bf16"),
+}
+
+
+@functools.lru_cache(maxsize=1)
+def _rollout(name):
+    shape = SHAPES[name]
+    wl = vi.Workload("batch", shape, batch=MANY, n_patches=S - 2, n_instr=2, n_action=A)
+    run = Rollout(vi.SynthModel(shape, 8, device="cuda:0"), MANY, S + A)
+    patch, ids = vi.observation(wl, 8, device="cuda:0")
+    noise = vi.gumbel_noise(wl, 8, device="cuda:0")
+
+    @functools.lru_cache(maxsize=None)
+    def outputs(n):
+        h, _ = run.prefill(patch[:n], ids[:n], want_value=False)
+        out = run.decode(h, S, A, gumbel=noise[:n].contiguous())
+        torch.cuda.synchronize()
+        return h, *out
+    return outputs
+
+
+# 31 | 32: 1024 (environment, head) pairs, where the attention's split of the keys changes
+@pytest.mark.parametrize("few,many", [(31, 32)])
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_few_and_many_environments(name, few, many):
+    outputs = _rollout(name)
+    for x, y in zip(outputs(few), outputs(many)):
+        assert torch.equal(x, y[:few])
