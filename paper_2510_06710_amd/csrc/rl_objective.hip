@@ -19,6 +19,9 @@ __device__ __forceinline__ float block_sum_256(float v, float *red) {
 // time from the last one down (lane l = step t1 - 1 - l) and composes the affine maps x -> b + a x of its lanes in six
 // shuffle steps; the carry enters last.  The next 64 steps are loaded meanwhile.  (A thread walking its trajectory alone
 // paid a memory latency per step: 45 us for 256 x 80 steps, now 3.2 us, about a launch.)
+// The composed a is a product of up to 64 factors gamma lambda.  Where that leaves fp32 (above 1 it may overflow, below 1/4
+// vanish: 1/4^64 is still a denormal number), inf * 0 would put NaN where the recursion has none: there the lanes' steps
+// are taken one by one.
 __global__ void __launch_bounds__(256) gae_kernel(const float *rewards, const float *values, const int32_t *dones, int n, int T,
                                                   float gamma, float lambda, float *adv, float *returns) {
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -31,24 +34,33 @@ __global__ void __launch_bounds__(256) gae_kernel(const float *rewards, const fl
         if (t >= 0) { s.r = r[t]; s.v = v[t]; s.v1 = v[t + 1]; s.done = d ? d[t] : 0; }
         return s;
     };
+    const float factor = fabsf(gamma * lambda);
+    const bool compose = factor == 0.f || (factor >= 0.25f && factor <= 1.f);
     float next = 0.f;
     Step cur = load(T - 1 - lane);
     for (int t1 = T; t1 > 0; t1 -= 64) {
         const int t = t1 - 1 - lane;
         const Step ahead = load(t - 64);
         const float cont = cur.done ? 0.f : 1.f;
-        float b = cur.r + gamma * cur.v1 * cont - cur.v, a = gamma * lambda * cont;
+        float b = cur.r + gamma * cur.v1 * cont - cur.v, a = gamma * lambda * cont, x = 0.f;
+        if (compose) {
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const float pa = __shfl_up(a, o, 64), pb = __shfl_up(b, o, 64);      // the map of the steps after this one's
-            if (lane >= o) { b += a * pb; a *= pa; }
+            for (int o = 1; o < 64; o <<= 1) {
+                const float pa = __shfl_up(a, o, 64), pb = __shfl_up(b, o, 64);  // the map of the steps after this one's
+                if (lane >= o) { b += a * pb; a *= pa; }
+            }
+            x = b + a * next;
+            next = __shfl(x, 63, 64);         // (used only when all 64 lanes held a step)
+        } else {
+            for (int l = 0; l < 64; l++) {
+                next = __shfl(b, l, 64) + __shfl(a, l, 64) * next;
+                if (lane == l) x = next;
+            }
         }
-        const float x = b + a * next;
         if (t >= 0) {
             adv[(size_t)i * T + t] = x;
             if (returns) returns[(size_t)i * T + t] = x + cur.v;
         }
-        next = __shfl(x, 63, 64);             // (used only when all 64 lanes held a step)
         cur = ahead;
     }
 }

@@ -171,3 +171,22 @@ def test_grpo_advantage_of_groups_wider_than_a_wave(n_groups, G):
     assert keep[0].item() == 0 and not adv[:G].any().item()
     assert np.array_equal(keep.cpu().numpy().astype(bool)[1:], rk)
     assert np.max(np.abs(adv.cpu().numpy()[G:] - ra)) < 1e-5
+
+
+@pytest.mark.parametrize("gl,last", [(4.0, 0.0), (6.0, 0.0), (-4.0, 0.0), (0.01, np.inf), (0.01, -np.inf), (0.0, 1.0)])
+def test_gae_where_a_product_of_64_factors_leaves_fp32(gl, last):
+    """gamma lambda whose 64th power overflows or underflows: the recursion itself stays finite (or infinite, not NaN)."""
+    n, T = 3, 64
+    r = 1e-3 * np.random.default_rng(5).standard_normal((n, T)).astype(np.float32)
+    v = np.zeros((n, T + 1), dtype=np.float32)
+    r[0] = 0.0                                               # no reward at all: zeros
+    r[1:, :60] *= 1e-30 if abs(gl) > 1 else 1.0
+    r[1:, 60:] = 1e-12 if abs(gl) > 1 else 0.5
+    r[1:, T - 1] += last
+    adv, ret = torch.empty(n, T, device=DEV), torch.empty(n, T, device=DEV)
+    vb.vla_gae(dev(r), dev(v), None, n, T, gl, 1.0, adv, ret)
+    torch.cuda.synchronize()
+    ra, _ = ro.ogae(r, v, None, gl, 1.0)
+    got, fin = adv.cpu().numpy(), np.isfinite(ra)
+    assert np.array_equal(got[~fin], ra[~fin].astype(np.float32), equal_nan=True)
+    assert np.isfinite(got[fin]).all() and np.all(np.abs(got[fin] - ra[fin]) <= 1e-5 * np.abs(ra[fin]) + 1e-37)
