@@ -5,8 +5,10 @@
 // the matrix cores over tiles of 16 rows and is cut along K into chunks of 256: at one row per call (decode at batch 1)
 // 64 workgroups share the 2 MB that one workgroup used to walk alone.  bf16 weights: h enters as three bf16 parts
 // (8 + 8 + 8 significant bits, i.e. all 24 of the fp32 value), three v_mfma_f32_16x16x32_bf16 per block, products exact
-// in fp32.  fp32 weights: v_mfma_f32_16x16x4_f32.  Sums run over one chunk at a time and the chunks are added in order,
-// the same for every row count and both forms below, so a row's result does not depend on the rows around it.
+// in fp32.  (An infinite weight meets the first part alone: a later part of zero would make its product NaN, one of the
+// other sign the sum.  A chunk that comes out NaN is formed again that way.)  fp32 weights: v_mfma_f32_16x16x4_f32.  Sums
+// run over one chunk at a time and the chunks are added in order, the same for every row count and both forms below, so a
+// row's result does not depend on the rows around it.
 //   partial form: one workgroup per (16 rows, chunk, 64 bins), fp32 partial logits to scratch, a second kernel samples;
 //   whole form (above VLA_HEAD_PARTIAL_ROWS rows, where 16 copies of the logits would be traffic of their own): a
 //   workgroup walks all chunks for 32 rows and samples them from LDS.
@@ -44,8 +46,9 @@ __device__ __forceinline__ void split3(float x, bf16_t &hi, bf16_t &mid, bf16_t 
 // Products of one chunk [k0, k1) (a multiple of 16 long) for 16 * RB rows and 16 * CB bins from bin0:
 // acc[rb][cb][r] = bin bin0 + cb * 16 + 4 * (lane / 16) + r of row rb * 16 + lane % 16.
 // UN steps are loaded together ahead of their products (a call of few rows is a chain of memory latencies: one per
-// group of steps).  FULL: the chunk is CHUNK long; otherwise the steps past k1 count as zeros.
-template <int RB, int CB, bool FULL, int UN>
+// group of steps).  FULL: the chunk is CHUNK long; otherwise the steps past k1 count as zeros.  TAME: infinite weights
+// meet the first part of h only.
+template <int RB, int CB, bool FULL, int UN, bool TAME = false>
 __device__ __forceinline__ void chunk_product(f32x4_t (&acc)[RB][CB], const float *const (&hrow)[RB], const bf16_t *const (&wrow)[CB],
                                               int k0, int k1, int kq) {
 #pragma unroll 1
@@ -74,7 +77,16 @@ __device__ __forceinline__ void chunk_product(f32x4_t (&acc)[RB][CB], const floa
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < UN; i++)
+        for (int i = 0; i < UN; i++) {
+            bf16x8_t wt[CB];
+#pragma unroll
+            for (int cb = 0; cb < CB; cb++) {
+                wt[cb] = w[i][cb];
+                if (TAME)
+#pragma unroll
+                    for (int e = 0; e < 8; e++)
+                        if (__builtin_isinf((float)wt[cb][e])) wt[cb][e] = (bf16_t)0.f;
+            }
 #pragma unroll
             for (int rb = 0; rb < RB; rb++) {
                 bf16x8_t hi, mid, lo;
@@ -85,12 +97,13 @@ __device__ __forceinline__ void chunk_product(f32x4_t (&acc)[RB][CB], const floa
                     hi[e] = a; mid[e] = b; lo[e] = c;
                 }
 #pragma unroll
-                for (int cb = 0; cb < CB; cb++) acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i][cb], lo, acc[rb][cb], 0, 0, 0);
+                for (int cb = 0; cb < CB; cb++) acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[cb], lo, acc[rb][cb], 0, 0, 0);
 #pragma unroll
-                for (int cb = 0; cb < CB; cb++) acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i][cb], mid, acc[rb][cb], 0, 0, 0);
+                for (int cb = 0; cb < CB; cb++) acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[cb], mid, acc[rb][cb], 0, 0, 0);
 #pragma unroll
                 for (int cb = 0; cb < CB; cb++) acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i][cb], hi, acc[rb][cb], 0, 0, 0);
             }
+        }
     }
 }
 template <int RB, int CB, bool FULL, int UN>
@@ -218,13 +231,29 @@ __device__ __forceinline__ void tile_logits(f32x4_t (&total)[RB][CB], const floa
     for (int rb = 0; rb < RB; rb++) hrow[rb] = h + (size_t)min(m0 + rb * 16 + l16, M - 1) * H;
     for (int c = c0; c < c1; c++) {
         f32x4_t acc[RB][CB];
+        auto clear = [&]() {
 #pragma unroll
-        for (int rb = 0; rb < RB; rb++)
+            for (int rb = 0; rb < RB; rb++)
 #pragma unroll
-            for (int cb = 0; cb < CB; cb++) acc[rb][cb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                for (int cb = 0; cb < CB; cb++) acc[rb][cb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        };
+        clear();
         const int k0 = c * CHUNK, k1 = min(H, k0 + CHUNK);
         if (k1 - k0 == CHUNK) chunk_product<RB, CB, true, UN>(acc, hrow, wrow, k0, k1, kq);
         else chunk_product<RB, CB, false, 1>(acc, hrow, wrow, k0, k1, kq);
+        if constexpr (sizeof(T) == 2) {
+            bool nan = false;
+#pragma unroll
+            for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+                for (int cb = 0; cb < CB; cb++)
+#pragma unroll
+                    for (int r = 0; r < 4; r++) nan = nan || __builtin_isnan(acc[rb][cb][r]);
+            if (__any(nan)) {
+                clear();
+                chunk_product<RB, CB, false, 1, true>(acc, hrow, wrow, k0, k1, kq);
+            }
+        }
 #pragma unroll
         for (int rb = 0; rb < RB; rb++)
 #pragma unroll
