@@ -216,10 +216,13 @@ static size_t prepack_layer_bytes(const vla_config &c) {
 static int try_gemm_bf16_large(const GemmArgs &g, hipStream_t st) { return try_gemm_bf16_dma(g, st); }
 
 // Kernel choice depends on the storage type, on whether the forward has one row per sequence and, for these, on the rows:
-// decode steps of up to 32 rows take the weight-streaming kernel (whole K per workgroup), up to 128 rows the small tiles (QKV,
-// gate/up) and the skinny split-K kernel (O, down), larger ones and all tail rows the split-K kernels.  The K ranges, and with
-// them the order in which a row's products are summed, therefore differ between batch sizes on either side of 32 and 128 (each
-// configuration by itself is deterministic, and within one call a row's result does not depend on the other rows).
+// decode steps of up to 32 rows take the weight-streaming kernel, up to 128 rows the small tiles (QKV, gate/up) and the skinny
+// split-K kernel (O, down); up to 128 tail rows the skinny kernel.  All of these add K in the same parts and in the same order
+// (gemm_decode_parts), so a row's result does not depend, bit for bit, on how many rows share the step, and shapes that one of
+// them declines are declined by all (the generic kernel then takes them, which also has one order for all row counts).  Larger
+// steps and 129 to 256 tail rows take the split-K tile kernels, whose K ranges differ: on either side of 128 rows the sums, and
+// the bf16 roundings after them, are not the same (each configuration by itself is deterministic, and within one call a row's
+// result does not depend on the other rows).
 template <typename T>
 static int run_gemm(const vla_config &c, GemmArgs g, void *skinny_scratch, hipStream_t st) {
     if (c.dtype == VLA_DTYPE_BF16) {
@@ -231,7 +234,6 @@ static int run_gemm(const vla_config &c, GemmArgs g, void *skinny_scratch, hipSt
                 r = try_gemm_bf16_dma_splitk(g, skinny_scratch, sb, st);
                 if (r == 0) r = try_gemm_bf16_mid(g, skinny_scratch, sb, st);
             }
-            // (not for the tail rows of a recompute, whose result must not depend on how many rollouts share the pass)
             if (r == 0 && g.step) r = try_gemm_bf16_stream(g, st);
             if (r == 0 && g.step) r = try_gemm_bf16_dma_step(g, st);
             if (r == 0) r = try_gemm_bf16_skinny(g, skinny_scratch, st);

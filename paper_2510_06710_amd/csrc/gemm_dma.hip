@@ -67,6 +67,7 @@ struct DmaGemmParams {
     int group;
     int splits;      // > 1: K is cut into `splits` equal ranges; item = range * tiles + tile, and range r of an
                      // EPI_STORE launch writes its fp32 partial product to C + r * M * N
+    int parts;       // small tiles of a decode step: the parts of K whose sums are added in order (gemm_decode_parts)
     int wkb;         // row-major activations with k-blocked (repacked) weights: the decode forwards, whose weight
                      // stream comes from HBM and then moves as whole cache lines (w_rows as in the k-blocked layout)
 };
@@ -563,7 +564,10 @@ __device__ __forceinline__ void pass_frags(bf16x8_t (&f)[N]) {
 // 72 GB/s with two (a CU on its own streams 58 GB/s from HBM however deep its ring), so what counts is the bytes per CU.
 // Workgroups of one XCD take neighbouring tile columns with all their tile rows: a weight panel is then fetched into one
 // L2 only (the activations, few rows, into all).
-template <int EPI, bool KB, bool WKB, int BMT, int BNT, int NS>
+//
+// STEP (QKV and gate/up of decode steps): instead the sums of gemm_skinny.hip, bit for bit: v_mfma_f32_32x32x16_bf16 on its
+// columns (operand j of a unit: 8 j .. + 7 of either half), K in p.parts parts that are added in order.
+template <int EPI, bool KB, bool WKB, int BMT, int BNT, int NS, bool STEP>
 __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int MB = BMT / 32, NB = BNT / 32;          // 16-row / 16-column blocks per wave
@@ -618,11 +622,25 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
     const int lds0 = (int)(size_t)(lds_void *)lds;
     const int a_base = lds0 + (wm * (BMT / 2) + l16) * 64 + ((kq ^ fsw) << 4);
     const int w_base = lds0 + 2 * A_HALF + (wn * (BNT / 2) + l16) * 64 + ((kq ^ fsw) << 4);
-    f32x4_t acc[NB][MB];
+    // STEP: lane l reads row l % 32 of a 32-row block, from half l / 32 of the unit
+    constexpr int MB2 = MB / 2, NB2 = NB / 2;
+    const int l32 = lane & 31, hh = lane >> 5, fsw32 = (l32 >> 1) & 3;
+    const int a_step = lds0 + hh * A_HALF + (wm * (BMT / 2) + l32) * 64, w_step = lds0 + 2 * A_HALF + hh * W_HALF + (wn * (BNT / 2) + l32) * 64;
+    f32x4_t acc[STEP ? 1 : NB][STEP ? 1 : MB];
+    f32x16_t acc32[STEP ? NB2 : 1][STEP ? MB2 : 1], sum32[STEP ? NB2 : 1][STEP ? MB2 : 1];
+    if constexpr (STEP) {
 #pragma unroll
-    for (int j = 0; j < NB; j++)
+        for (int j = 0; j < NB2; j++)
 #pragma unroll
-        for (int i = 0; i < MB; i++) acc[j][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < MB2; i++)
+#pragma unroll
+                for (int r = 0; r < 16; r++) acc32[j][i][r] = 0.f;
+    } else {
+#pragma unroll
+        for (int j = 0; j < NB; j++)
+#pragma unroll
+            for (int i = 0; i < MB; i++) acc[j][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
 
     bf16x8_t af[2][MB], wf[2][NB];                       // (the first multiply, before any second half, adds zeros)
 #pragma unroll
@@ -635,12 +653,52 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
         for (int e = 0; e < 8; e++) wf[1][j][e] = (bf16_t)0.f;
     auto multiply = [&](int h) {
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (STEP) {
 #pragma unroll
-        for (int j = 0; j < NB; j++)
+            for (int q = 0; q < 2; q++)
 #pragma unroll
-            for (int i = 0; i < MB; i++) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[h][j], af[h][i], acc[j][i], 0, 0, 0);
+                for (int j = 0; j < NB2; j++)
+#pragma unroll
+                    for (int i = 0; i < MB2; i++)
+                        acc32[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[h][q * NB2 + j], af[h][q * MB2 + i], acc32[j][i], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NB; j++)
+#pragma unroll
+                for (int i = 0; i < MB; i++) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[h][j], af[h][i], acc[j][i], 0, 0, 0);
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
+    // the fragments of half h of a unit (STEP: its operands 2 h and 2 h + 1)
+    auto read_half = [&](auto h_c, int so) {
+        constexpr int h = decltype(h_c)::value;
+        if constexpr (STEP) {
+#pragma unroll
+            for (int q = 0; q < 2; q++) {
+                const int c = ((2 * h + q) ^ fsw32) << 4;
+#pragma unroll
+                for (int j = 0; j < NB2; j++) wf[h][q * NB2 + j] = lds_read<0>(w_step + so + c + j * 2048);
+#pragma unroll
+                for (int i = 0; i < MB2; i++) af[h][q * MB2 + i] = lds_read<0>(a_step + so + c + i * 2048);
+            }
+        } else {
+            read_frags<h * W_HALF, 1024>(wf[h], w_base + so, std::make_integer_sequence<int, NB>{});
+            read_frags<h * A_HALF, 1024>(af[h], a_base + so, std::make_integer_sequence<int, MB>{});
+        }
+    };
+    // STEP: the sums of a part join those of the parts before
+    auto close_part = [&](bool first) {
+#pragma unroll
+        for (int j = 0; j < NB2; j++)
+#pragma unroll
+            for (int i = 0; i < MB2; i++)
+#pragma unroll
+                for (int r = 0; r < 16; r++) {
+                    sum32[j][i][r] = first ? acc32[j][i][r] : sum32[j][i][r] + acc32[j][i][r];
+                    acc32[j][i][r] = 0.f;
+                }
+    };
+    int part_end = STEP ? units / p.parts : 0, part = 0;         // part y ends before unit (y + 1) units / parts
     // this wave's fragment reads have landed; the fragments pass through, so that no MFMA moves above the wait
     auto wait_frags = [&](int h) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -660,25 +718,42 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
         if (u + NS - 1 < units) load_unit(u + NS - 1, prev);
         const int so = stage * SSTAGE;
         // first half's fragments while the second half of unit u - 1 multiplies, then the other way round
-        read_frags<0, 1024>(wf[0], w_base + so, std::make_integer_sequence<int, NB>{});
-        read_frags<0, 1024>(af[0], a_base + so, std::make_integer_sequence<int, MB>{});
+        read_half(std::integral_constant<int, 0>{}, so);
         multiply(1);
+        if constexpr (STEP) {
+            if (u == part_end) {
+                close_part(part == 0);
+                part++;
+                part_end = (int)((long)(part + 1) * units / p.parts);
+            }
+        }
         wait_frags(0);
-        read_frags<W_HALF, 1024>(wf[1], w_base + so, std::make_integer_sequence<int, NB>{});
-        read_frags<A_HALF, 1024>(af[1], a_base + so, std::make_integer_sequence<int, MB>{});
+        read_half(std::integral_constant<int, 1>{}, so);
         multiply(0);
         wait_frags(1);
         stage = stage == NS - 1 ? 0 : stage + 1;
     }
     multiply(1);
+    if constexpr (STEP) close_part(part == 0);
     // ---- output: the whole tile as fp32 through LDS, then each wave takes 16-row blocks
     asm volatile("s_barrier" ::: "memory");
     float *panel = (float *)lds;
+    if constexpr (STEP) {                                // lane l: row l % 32 of a block, columns 8 g + 4 hh .. + 3 in registers 4 g .. + 3
 #pragma unroll
-    for (int j = 0; j < NB; j++)
+        for (int j = 0; j < NB2; j++)
 #pragma unroll
-        for (int i = 0; i < MB; i++)
-            *(f32x4_t *)panel_at(panel + (wm * MB + i) * 16 * 128, l16, wn * (NB * 4) + j * 4 + kq) = acc[j][i];
+            for (int i = 0; i < MB2; i++)
+#pragma unroll
+                for (int g = 0; g < 4; g++)
+                    *(f32x4_t *)panel_at(panel + (wm * MB + 2 * i + (l32 >> 4)) * 16 * 128, l16, wn * (NB * 4) + j * 8 + 2 * g + hh) =
+                        f32x4_t{sum32[j][i][4 * g], sum32[j][i][4 * g + 1], sum32[j][i][4 * g + 2], sum32[j][i][4 * g + 3]};
+    } else {
+#pragma unroll
+        for (int j = 0; j < NB; j++)
+#pragma unroll
+            for (int i = 0; i < MB; i++)
+                *(f32x4_t *)panel_at(panel + (wm * MB + i) * 16 * 128, l16, wn * (NB * 4) + j * 4 + kq) = acc[j][i];
+    }
     __syncthreads();
     const int m0 = tm * BMT;
 #pragma unroll
@@ -761,12 +836,12 @@ int launch(const DmaGemmParams &p, hipStream_t st) {
     return launch_plain<EPI, KB, UB>(p, st);
 }
 
-template <int EPI, bool KB, bool WKB, int BMT, int BNT, int NS>
+template <int EPI, bool KB, bool WKB, int BMT, int BNT, int NS, bool STEP>
 int launch_small(DmaGemmParams p, hipStream_t st) {
     static bool attr_set = false;
     const size_t lds = (size_t)NS * 2 * (BMT * 64 + BNT * 64);
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_small_kernel<EPI, KB, WKB, BMT, BNT, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_small_kernel<EPI, KB, WKB, BMT, BNT, NS, STEP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) {
             vla_set_error("hipFuncSetAttribute(gemm_bf16_small) failed: %s", hipGetErrorString(e));
             return VLA_EHIP;
@@ -776,7 +851,7 @@ int launch_small(DmaGemmParams p, hipStream_t st) {
     p.tiles_m = (p.M + BMT - 1) / BMT;
     p.tiles_n = EPI == EPI_SWIGLU ? p.N / (BNT / 2) : p.N / BNT;
     const int per_xcd = (p.tiles_m * p.tiles_n + 7) / 8;
-    gemm_bf16_small_kernel<EPI, KB, WKB, BMT, BNT, NS><<<8 * per_xcd, 256, lds, st>>>(p);
+    gemm_bf16_small_kernel<EPI, KB, WKB, BMT, BNT, NS, STEP><<<8 * per_xcd, 256, lds, st>>>(p);
     int rc = vla_check_launch("gemm_bf16_small");
     return rc ? rc : 1;
 }
@@ -807,17 +882,17 @@ SmallTile choose_tile(const DmaGemmParams &p) {
     return best;
 }
 
-template <int EPI, bool KB, bool WKB = KB>
+template <int EPI, bool KB, bool WKB = KB, bool STEP = false>
 int launch_tile(const DmaGemmParams &p, SmallTile tile, hipStream_t st) {
     const double flops = 2.0 * p.M * p.K * (EPI == EPI_SWIGLU ? 2.0 * p.N : (double)p.N);
     ProfScope ps(EPI == EPI_SWIGLU ? "gemm_small<swiglu>" : EPI == EPI_RESIDUAL ? "gemm_small<residual>"
                  : EPI == EPI_QKV_ROPE ? "gemm_small<qkv_rope>" : "gemm_small<store>", flops, st);
     if constexpr (EPI == EPI_STORE || EPI == EPI_RESIDUAL) {
-        if (tile == TILE_64x64) return launch_small<EPI, KB, WKB, 64, 64, 4>(p, st);
+        if (tile == TILE_64x64) return launch_small<EPI, KB, WKB, 64, 64, 4, STEP>(p, st);
     }
-    if (tile == TILE_64x128) return launch_small<EPI, KB, WKB, 64, 128, 3>(p, st);
-    if (tile == TILE_128x128_1) return launch_small<EPI, KB, WKB, 128, 128, 3>(p, st);
-    return launch_small<EPI, KB, WKB, 128, 128, 2>(p, st);
+    if (tile == TILE_64x128) return launch_small<EPI, KB, WKB, 64, 128, 3, STEP>(p, st);
+    if (tile == TILE_128x128_1) return launch_small<EPI, KB, WKB, 128, 128, 3, STEP>(p, st);
+    return launch_small<EPI, KB, WKB, 128, 128, 2, STEP>(p, st);
 }
 
 template <int EPI>
@@ -884,10 +959,11 @@ int try_gemm_bf16_dma(const GemmArgs &g, hipStream_t st) {
 }
 
 // QKV and gate/up projections of decode steps of 33 .. 128 rows on the small tiles: row-major activations, the repacked
-// weights where the model has them, no partial sums.  64 rows of the 7B shape against the split-K form and its reductions:
-// QKV 30 + 12 -> 27 + 7 us (with rotation and KV write), gate/up 57 + 10 -> 40; 128 rows 41 + 14 -> 35 + 8 and 75 + 17 -> 49.  The
-// O and down projections have too few tiles (64 rows: 38 us and a norm of 6, split-K 25 and 7) and stay there.  Returns 1
-// if handled, 0 if declined, < 0 on a launch error.
+// weights where the model has them, no partial sums in memory, the sums of the split-K form.  64 rows of the 7B shape against
+// that form and its reductions: QKV 31 + 12 -> 28 + 7 us (with rotation and KV write), gate/up 57 + 10 -> 41; 128 rows 41 + 14
+// -> 37 + 8 and 75 + 16 -> 53.  (On the instruction and order of the 256 x 256 tiles QKV takes 27 and 35 us, gate/up 40 and 49.)
+// The O and down projections have too few tiles (64 rows: 38 us and a norm of 6, split-K 25 and 7) and stay there.  Returns 1 if
+// handled, 0 if declined, < 0 on a launch error.
 int try_gemm_bf16_dma_step(const GemmArgs &g, hipStream_t st) {
     if (g.epilogue != EPI_STORE && g.epilogue != EPI_SWIGLU) return 0;
     if (g.kblocked || g.M < 1 || g.M > 128 || g.K % 64 != 0 || g.K < 256 || g.a_rows < 256) return 0;
@@ -901,11 +977,12 @@ int try_gemm_bf16_dma_step(const GemmArgs &g, hipStream_t st) {
     p.W0 = (const bf16_t *)W[0]; p.W1 = (const bf16_t *)W[1]; p.W2 = (const bf16_t *)W[2];
     p.C = g.C; p.M = g.M; p.K = g.K; p.segN = g.segN; p.a_rows = g.a_rows; p.w_rows = g.segN + VLA_KB_PAD_ROWS;
     p.N = g.epilogue == EPI_SWIGLU ? g.segN : n_seg * g.segN;
+    p.parts = gemm_decode_parts(p.N, p.K);
     auto go = [&](auto epi) {
         constexpr int EPI = decltype(epi)::value;
         const SmallTile tile = choose_tile<EPI>(p);
         if (tile == TILE_256) return 0;
-        return wkb ? launch_tile<EPI, false, true>(p, tile, st) : launch_tile<EPI, false, false>(p, tile, st);
+        return wkb ? launch_tile<EPI, false, true, true>(p, tile, st) : launch_tile<EPI, false, false, true>(p, tile, st);
     };
     return g.epilogue == EPI_SWIGLU ? go(std::integral_constant<int, EPI_SWIGLU>{}) : go(std::integral_constant<int, EPI_STORE>{});
 }

@@ -269,7 +269,14 @@ int launch_splitk_reduce(int epilogue, void *C, const float *P, int splits, int 
     return vla_check_launch("splitk_reduce");
 }
 
-static int skinny_target_wgs() { return 512; }      // two workgroups per CU keep the weight stream of 256 CUs busy
+// Parts into which a decode step's GEMM of up to 128 rows cuts K, whatever its kernel and its rows (part y of n: the 64-wide
+// tiles from y tiles / n on): enough for 512 workgroups of 128 columns, two per CU, at least 8 tiles each.
+int gemm_decode_parts(int N, int K) {
+    const int n_tiles = N / 128, ktiles = K / BK;
+    int parts = 1;
+    while (parts < 8 && n_tiles * parts < 512 && ktiles / (parts * 2) >= 8) parts *= 2;
+    return parts;
+}
 
 size_t gemm_skinny_scratch_bytes(int M, int max_n) {
     return (size_t)8 * M * max_n * sizeof(float);     // at most 8 K-splits of an [M, max_n] fp32 panel
@@ -286,10 +293,7 @@ int try_gemm_bf16_skinny(const GemmArgs &g, void *scratch, hipStream_t st) {
     p.C = g.C; p.P = (float *)scratch; p.M = g.M; p.K = g.K; p.segN = g.segN;
     p.N = (g.epilogue == EPI_SWIGLU) ? g.segN : g.n_seg * g.segN;
     const int n_tiles = p.N / 128;
-    const int ktiles = g.K / BK;
-    // enough workgroups to keep the weight stream of all 256 CUs busy, at least 8 K tiles per split
-    int splits = 1;
-    while (splits < 8 && n_tiles * splits < skinny_target_wgs() && ktiles / (splits * 2) >= 8) splits *= 2;
+    const int splits = gemm_decode_parts(p.N, p.K);
     p.splits = splits;
     const double wbytes = 2.0 * g.K * (g.epilogue == EPI_SWIGLU ? 2.0 * p.N : (double)p.N);
     int rc;

@@ -1,26 +1,30 @@
-// bf16 GEMM for forwards of at most 32 rows (decode steps of up to 32 environments, few tail rows):
-// C[M, N] = A[M, K] . W[N, K]^T, bound by the weight bytes from HBM.
+// bf16 GEMM for decode steps of at most 32 environments: C[M, N] = A[M, K] . W[N, K]^T, bound by the weight bytes from HBM.
 //
-// One workgroup of eight waves per 16 * R weight rows (SwiGLU: 16 * R gate and the matching up rows) and the whole of K:
-// the waves take the 32-wide K steps in turn, each on its own, without barriers, with UN steps of loads in flight, and their
-// sums are added in wave order through LDS at the end.  So no partial sums travel through memory, the epilogue is the
-// final one and no reduction kernel follows.  Weights go from memory straight into MFMA operand registers: in the
-// repacked layout ([K / 32][rows][32]) a fragment of 16 rows x 32 columns is 1 KB in a row, one load instruction; row-major
-// weights take the same instruction with 64-byte pieces.  Activations (L2) come the same way, shared by the R row blocks.
-// One (O, down) to three workgroups share a CU; a CU streams up to 58 GB/s, 256 of them 6 TB/s together.
-// Measured at one row on the 7B shape against the split-K form (gemm_skinny.hip) and the reductions that follow it: QKV 23.4
-// -> 18.7 us, O and down 27.8 + 5.3 -> 13.6 + 3.9 (mean, with the norm), gate/up 43.1 + 4.6 -> 32.6 us (5.5 TB/s).  The
-// activations' L2 traffic (every workgroup reads all of them) grows with the rows: 16 rows 27 / 19 / 39 us, 32 rows 33 /
-// 24 / 47 us, where both forms cost the same per layer; 64 rows 49 / 40 / 69 against 32 / 25 / 57 us, so the rule ends at 32.
+// One workgroup of eight waves per 16 output columns (SwiGLU: 16 gate and the matching up rows of the weights) and the whole
+// of K: each wave takes one of the parts into which a decode step cuts K (gemm_decode_parts; with fewer parts a workgroup has
+// more columns) and walks it alone, without barriers; the parts are added in order through LDS at the end.  So no partial sums
+// travel through memory, the epilogue is the final one and no reduction kernel follows.
+//
+// The sums are those of gemm_skinny.hip bit for bit: v_mfma_f32_32x32x16_bf16 on the same columns (8 j .. + 7 of either half
+// of a 64-column tile) in the same order.  That operand is a 16-byte piece of every 64: a lane that loaded it alone would
+// leave the rest of the line to three more instructions.  Two loads fetch the whole lines of 16 rows instead and the pieces
+// change places between lane rows afterwards (v_permlane16_swap).  With 16 activation rows half of the instruction's columns
+// are idle, with 16 weight rows half of its rows: the matrix cores have the time.
+//
+// What counts is the number of waves with loads in flight, not the loads per wave: with one tile each in flight, 64
+// registers, three to four workgroups share a CU.  Measured on the 7B shape with repacked weights (time between events around
+// the launch, at 1 / 16 / 32 rows): QKV 24 / 26 / 32 us, O and down 16 / 20 / 23 (mean), gate/up 35 / 38 / 46; two or three
+// tiles in flight cost gate/up 0 / 2 / 5 us more.  The split-K form takes 25 / 26 / 27, 22 / 23 / 23 and 45 / 47 / 50 us and
+// leaves 26 to 33 us of reductions a layer that this one does not need.
 //
 // NORM rows (1, or up to 4): the activations are RMSNorm(x) g of fp32 rows x of at most 4096 columns (eight per thread),
-// which every workgroup forms for itself in LDS while its first weights are on the way.  At one row the two norms of a layer
-// took 9.4 us in launches of their own; the GEMMs with them take 31.7 us for gate/up (32.7 without: fewer registers, two
-// workgroups per CU) and 19.1 for QKV (18.0).  With four rows, norm included, 37 and 26 against 34 + 6 and 21 + 6; the rows
-// that a thread holds end the rule there.
+// which every workgroup forms for itself in LDS while its first weights are on the way: 0 to 2 us more in the kernel for a
+// launch of 6 us less.  The rows that a thread holds end the rule at four.
 #include "vla_internal.h"
 
 namespace {
+
+constexpr int NW = 8;                  // waves of a workgroup
 
 struct StreamParams {
     const bf16_t *A;
@@ -29,64 +33,87 @@ struct StreamParams {
     const float *x, *gain;     // NORM: the fp32 rows and the norm's gain, instead of A
     float eps;
     int M, N, K, segN;
+    int parts;                 // K parts of the sums (1, 2, 4 or 8), one wave each
     size_t w_row, w_step;      // elements between weight rows and between 32-column steps of one row
 };
 
-template <int EPI, int MBK, int R, int UN, int NORM>
-__global__ void __launch_bounds__(512) gemm_stream_kernel(StreamParams p) {
-    constexpr int NW = 8, NP = (EPI == EPI_SWIGLU) ? 2 : 1;
-    __shared__ __attribute__((aligned(16))) f32x4_t part[NW][NP * R * MBK][64];
-    __shared__ float squares[NORM ? NORM : 1][NW];
-    extern __shared__ __attribute__((aligned(16))) bf16_t xs[];         // NORM: [M][K + 32], a 16-bank shift per row
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
-    const int K = p.K, steps = K / 32, n0 = blockIdx.x * (16 * R);
-    const bf16_t *a[MBK], *w[NP][R];
+// A 64-column tile of 16 * B rows as it was loaded (x[c][b]: lane l holds columns 32 (l / 32) + 16 c + 8 (l / 16 % 2) .. + 7 of row
+// l % 16 of block b, so that both loads of a block use the same whole cache lines) -> the operands of four 32 x 32 x 16
+// instructions: op[j], lane l = columns 32 (l / 32) + 8 j .. + 7 of row l % 32 (B = 1: of row l % 16).
+template <int B>
+__device__ __forceinline__ void operands(bf16x8_t (&op)[4], const bf16x8_t (&x)[2][B]) {
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-    for (int i = 0; i < MBK; i++) a[i] = (NORM ? xs + min(l16, p.M - 1) * (K + 32) : p.A + (size_t)min(i * 16 + l16, p.M - 1) * K) + kq * 8;
-    if (EPI == EPI_SWIGLU) {
+    for (int c = 0; c < 2; c++) {
+        const u4 v0 = __builtin_bit_cast(u4, x[c][0]), v1 = __builtin_bit_cast(u4, x[c][B - 1]);
+        u4 o0, o1;
 #pragma unroll
-        for (int r = 0; r < R; r++) {
-            w[0][r] = p.W0 + (size_t)(n0 + r * 16 + l16) * p.w_row + kq * 8;
-            w[NP - 1][r] = p.W1 + (size_t)(n0 + r * 16 + l16) * p.w_row + kq * 8;
+        for (int d = 0; d < 4; d++) {                   // lane rows of 16: second 8 columns of block 0 <-> first 8 of block 1
+            const auto r = __builtin_amdgcn_permlane16_swap(v0[d], v1[d], false, false);
+            o0[d] = r[0]; o1[d] = r[1];
         }
-    } else {
-        const int seg = n0 / p.segN;                     // (segN is a multiple of 16 * R)
-        const bf16_t *W = (seg == 0 ? p.W0 : (seg == 1 ? p.W1 : p.W2)) + (size_t)(n0 - seg * p.segN + l16) * p.w_row + kq * 8;
-#pragma unroll
-        for (int r = 0; r < R; r++) w[0][r] = W + (size_t)(r * 16) * p.w_row;
+        op[2 * c] = __builtin_bit_cast(bf16x8_t, o0);
+        op[2 * c + 1] = __builtin_bit_cast(bf16x8_t, o1);
     }
-    f32x4_t acc[NP][R][MBK];
+}
+
+// A wave multiplies 32 weight rows (SwiGLU: 16 gate and the matching up rows; NB = 1: 16 rows, twice) by 16 * MB activation
+// rows.  UN: tiles of 64 columns in flight, NORM: activation rows that the kernel norms itself (0: none).
+template <int EPI, int NB, int MB, int UN, int NORM>
+__global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
+    constexpr bool SW = EPI == EPI_SWIGLU;
+    constexpr int COLS = SW ? 16 : 16 * NB, LDW = 16 * NB + 4;          // output columns, floats of a row of sums
+    __shared__ float squares[NORM ? NORM : 1][NW];
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    float *part = (float *)lds;                                         // [wave][M][LDW]
+    bf16_t *xs = (bf16_t *)(lds + (size_t)NW * p.M * LDW * 4);          // NORM: [M][K + 32], a 16-bank shift per row
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l32 = lane & 31, hh = lane >> 5, c1 = (lane >> 4) & 1;
+    const int K = p.K, blocks = p.N / COLS, group = wave / p.parts, y = wave - group * p.parts;
+    const int block = blockIdx.x * (NW / p.parts) + group, n0 = min(block, blocks - 1) * COLS;
+    const bf16_t *a[MB], *w[NB];
 #pragma unroll
-    for (int b = 0; b < NP; b++)
+    for (int i = 0; i < MB; i++) a[i] = p.A + (size_t)min(i * 16 + l16, p.M - 1) * K + hh * 32 + c1 * 8;
+    const bf16_t *xrow = xs + min(l32, p.M - 1) * (K + 32) + hh * 32;
+    const size_t w_off = hh * p.w_step + c1 * 8 + (size_t)l16 * p.w_row;
+    if (SW) {
+        w[0] = p.W0 + (size_t)n0 * p.w_row + w_off;
+        w[NB - 1] = p.W1 + (size_t)n0 * p.w_row + w_off;
+    } else {
+        const int seg = n0 / p.segN;                     // (segN is a multiple of 128)
+        const bf16_t *W = (seg == 0 ? p.W0 : (seg == 1 ? p.W1 : p.W2)) + (size_t)(n0 - seg * p.segN) * p.w_row + w_off;
 #pragma unroll
-        for (int r = 0; r < R; r++)
+        for (int r = 0; r < NB; r++) w[r] = W + (size_t)(r * 16) * p.w_row;
+    }
+    f32x16_t acc;
 #pragma unroll
-            for (int i = 0; i < MBK; i++) acc[b][r][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    bf16x8_t wf[UN][NP][R], af[UN][MBK];
-    auto load = [&](int u, int s) {
-        const size_t wo = (size_t)s * p.w_step, ao = (size_t)s * 32;
+    for (int e = 0; e < 16; e++) acc[e] = 0.f;
+    bf16x8_t wf[UN][2][NB], af[UN][2][MB];
+    auto load = [&](int u, int kt) {
+        const size_t wo = (size_t)(2 * kt) * p.w_step, ao = (size_t)kt * 64;
 #pragma unroll
-        for (int b = 0; b < NP; b++)
+        for (int c = 0; c < 2; c++)
 #pragma unroll
-            for (int r = 0; r < R; r++) wf[u][b][r] = *(const bf16x8_t *)(w[b][r] + wo);
+            for (int r = 0; r < NB; r++) wf[u][c][r] = *(const bf16x8_t *)(w[r] + wo + c * 16);
+        if (!NORM)
 #pragma unroll
-        for (int i = 0; i < MBK; i++)
-            if (!NORM) af[u][i] = *(const bf16x8_t *)(a[i] + ao);
+            for (int c = 0; c < 2; c++)
+#pragma unroll
+                for (int i = 0; i < MB; i++) af[u][c][i] = *(const bf16x8_t *)(a[i] + ao + c * 16);
     };
-    auto multiply = [&](int u, int s) {
-        if (NORM) af[u][0] = *(const bf16x8_t *)(a[0] + s * 32);
+    auto multiply = [&](int u, int kt) {
+        bf16x8_t ao[4], wo[4];
+        if (NORM) {
 #pragma unroll
-        for (int b = 0; b < NP; b++)
+            for (int j = 0; j < 4; j++) ao[j] = *(const bf16x8_t *)(xrow + kt * 64 + j * 8);
+        } else {
+            operands<MB>(ao, af[u]);
+        }
+        operands<NB>(wo, wf[u]);
 #pragma unroll
-            for (int r = 0; r < R; r++)
-#pragma unroll
-                for (int i = 0; i < MBK; i++)
-                    acc[b][r][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[u][b][r], af[u][i], acc[b][r][i], 0, 0, 0);
+        for (int j = 0; j < 4; j++) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wo[j], ao[j], acc, 0, 0, 0);
     };
-    // The waves take pairs of steps in turn (a pair is one 128-byte line of a row-major row): step i of this wave is
-    // step_of(i), `mine` of them.  UN are in flight, each slot reloaded as soon as it is used.
-    auto step_of = [&](int i) { return ((i >> 1) * NW + wave) * 2 + (i & 1); };
-    const int pairs = steps >> 1, mine = 2 * ((pairs - wave + NW - 1) / NW) + ((steps & 1) && pairs % NW == wave ? 1 : 0);
+    // This wave's tiles: part y of the K range, one after the other.  UN are in flight, each slot reloaded as soon as it is used.
+    const int tiles = K / 64, kt0 = (int)((long)y * tiles / p.parts), mine = block < blocks ? (int)((long)(y + 1) * tiles / p.parts) - kt0 : 0;
     // NORM: this thread's eight columns of every row, asked for ahead of the weights (loads return in order)
     typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
     f32x4_t xv[NORM ? NORM : 1][2], gv[2];
@@ -102,7 +129,7 @@ __global__ void __launch_bounds__(512) gemm_stream_kernel(StreamParams p) {
     }
 #pragma unroll
     for (int u = 0; u < UN; u++)
-        if (u < mine) load(u, step_of(u));
+        if (u < mine) load(u, kt0 + u);
     if (NORM) {
         __builtin_amdgcn_sched_barrier(0);
         const int k = threadIdx.x * 8;
@@ -134,87 +161,99 @@ __global__ void __launch_bounds__(512) gemm_stream_kernel(StreamParams p) {
     for (; i0 + 2 * UN <= mine; i0 += UN) {
 #pragma unroll
         for (int u = 0; u < UN; u++) {
-            multiply(u, step_of(i0 + u));
-            load(u, step_of(i0 + UN + u));
+            multiply(u, kt0 + i0 + u);
+            load(u, kt0 + i0 + UN + u);
         }
     }
-    // the last one or two groups: at most 2 UN - 1 steps
+    // the last one or two groups: at most 2 UN - 1 tiles
 #pragma unroll
     for (int u = 0; u < UN; u++) {
         if (i0 + u < mine) {
-            multiply(u, step_of(i0 + u));
-            if (i0 + UN + u < mine) load(u, step_of(i0 + UN + u));
+            multiply(u, kt0 + i0 + u);
+            if (i0 + UN + u < mine) load(u, kt0 + i0 + UN + u);
         }
     }
 #pragma unroll
     for (int u = 0; u < UN; u++)
-        if (i0 + UN + u < mine) multiply(u, step_of(i0 + UN + u));
+        if (i0 + UN + u < mine) multiply(u, kt0 + i0 + UN + u);
+    // lane l holds activation row l % 32, weight rows 8 g + 4 (l / 32) .. + 3 in registers 4 g .. + 3
+    if (l32 < p.M && (MB > 1 || l32 < 16)) {
 #pragma unroll
-    for (int b = 0; b < NP; b++)
-#pragma unroll
-        for (int r = 0; r < R; r++)
-#pragma unroll
-            for (int i = 0; i < MBK; i++) part[wave][(b * R + r) * MBK + i][lane] = acc[b][r][i];
+        for (int g = 0; g < 2 * NB; g++)
+            *(f32x4_t *)(part + (wave * p.M + l32) * LDW + 8 * g + 4 * hh) = f32x4_t{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+    }
     __syncthreads();
-    // block (r, i): lane holds row i * 16 + l16, columns n0 + r * 16 + 4 kq .. + 3
-    for (int blk = wave; blk < R * MBK; blk += NW) {
-        const int r = blk / MBK, i = blk - r * MBK, m = i * 16 + l16;
-        if (m >= p.M) continue;
-        f32x4_t sum[NP];
+    // the parts of a block are added in K order: four columns of one row per thread
+    constexpr int QUADS = COLS / 4;
+    for (int item = threadIdx.x; item < NW / p.parts * p.M * QUADS; item += 64 * NW) {
+        const int q = item % QUADS, gm = item / QUADS, gr = gm / p.M, m = gm - gr * p.M;
+        const int blk = blockIdx.x * (NW / p.parts) + gr;
+        if (blk >= blocks) break;
+        const float *src = part + (gr * p.parts * p.M + m) * LDW + q * 4;
+        auto sum_of = [&](int off) {
+            f32x4_t sum = *(const f32x4_t *)(src + off);
+            for (int k = 1; k < p.parts; k++) {
+                const f32x4_t v = *(const f32x4_t *)(src + off + k * p.M * LDW);
 #pragma unroll
-        for (int b = 0; b < NP; b++) {
-            sum[b] = part[0][(b * R + r) * MBK + i][lane];
-#pragma unroll
-            for (int k = 1; k < NW; k++) {
-                const f32x4_t v = part[k][(b * R + r) * MBK + i][lane];
-#pragma unroll
-                for (int e = 0; e < 4; e++) sum[b][e] += v[e];
+                for (int e = 0; e < 4; e++) sum[e] += v[e];
             }
-        }
-        const size_t o = (size_t)m * p.N + n0 + r * 16 + kq * 4;
-        if (EPI == EPI_SWIGLU) {
+            return sum;
+        };
+        f32x4_t sum = sum_of(0);
+        const size_t o = (size_t)m * p.N + blk * COLS + q * 4;
+        if (SW) {
+            const f32x4_t up = sum_of(16);
             bf16x4_t v;
 #pragma unroll
-            for (int e = 0; e < 4; e++) v[e] = (bf16_t)vla_silu_mul(sum[0][e], sum[NP - 1][e]);
+            for (int e = 0; e < 4; e++) v[e] = (bf16_t)vla_silu_mul(sum[e], up[e]);
             *(bf16x4_t *)((bf16_t *)p.C + o) = v;
         } else {
             f32x4_t *dst = (f32x4_t *)((float *)p.C + o);
             if (EPI == EPI_RESIDUAL) {
                 const f32x4_t x = *dst;
 #pragma unroll
-                for (int e = 0; e < 4; e++) sum[0][e] += x[e];
+                for (int e = 0; e < 4; e++) sum[e] += x[e];
             }
-            *dst = sum[0];
+            *dst = sum;
         }
     }
 }
 
+template <int EPI, int NB, int MB, int UN, int NORM>
+int launch(const StreamParams &p, hipStream_t st) {
+    // (at most 37 KB of sums, or 5 KB and 34 KB of normed rows)
+    const size_t lds = (size_t)NW * p.M * (16 * NB + 4) * 4 + (NORM ? (size_t)p.M * (p.K + 32) * sizeof(bf16_t) : 0);
+    const int blocks = p.N / (EPI == EPI_SWIGLU ? 16 : 16 * NB), per_wg = NW / p.parts;
+    gemm_stream_kernel<EPI, NB, MB, UN, NORM><<<(blocks + per_wg - 1) / per_wg, 64 * NW, lds, st>>>(p);
+    return vla_check_launch("gemm_stream");
+}
+
 template <int EPI>
-void launch_rows(const StreamParams &p, hipStream_t st) {
-    // Steps in flight: as many as leave at most 128 registers, two workgroups per CU (gate/up at 13 rows: 6 steps, 140 registers
-    // 37.5 us, 5 steps 34.5; 3 or 4 steps the same)
-    constexpr int UN = EPI == EPI_SWIGLU ? 5 : 8, UN_NORM = EPI == EPI_SWIGLU ? 6 : 8;
-    if constexpr (EPI != EPI_RESIDUAL) {
-        const size_t lds = (size_t)p.M * (p.K + 32) * sizeof(bf16_t);
-        if (p.x && p.M == 1) { gemm_stream_kernel<EPI, 1, 1, UN_NORM, 1><<<p.N / 16, 512, lds, st>>>(p); return; }
-        if (p.x) { gemm_stream_kernel<EPI, 1, 1, UN_NORM, 4><<<p.N / 16, 512, lds, st>>>(p); return; }
+int launch_rows(const StreamParams &p, hipStream_t st) {
+    if constexpr (EPI == EPI_RESIDUAL) {                 // 256 workgroups at N = 4096: one per CU, so two tiles in flight
+        if (p.M <= 16) return launch<EPI, 1, 1, 2, 0>(p, st);
+        return launch<EPI, 1, 2, 1, 0>(p, st);
+    } else {
+        constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;
+        if (p.x && p.M == 1) return launch<EPI, NB, 1, 1, 1>(p, st);
+        if (p.x) return launch<EPI, NB, 1, 1, 4>(p, st);
+        if (p.M <= 16) return launch<EPI, NB, 1, 1, 0>(p, st);
+        return launch<EPI, 2, 2, 1, 0>(p, st);
     }
-    if (p.M <= 16) gemm_stream_kernel<EPI, 1, 1, UN, 0><<<p.N / 16, 512, 0, st>>>(p);
-    else if (EPI == EPI_RESIDUAL) gemm_stream_kernel<EPI, 2, 1, 4, 0><<<p.N / 16, 512, 0, st>>>(p);
-    else gemm_stream_kernel<EPI, 2, 2, 4, 0><<<p.N / 32, 512, 0, st>>>(p);     // wide outputs: two row blocks share the activations
 }
 
 }  // namespace
 
 // Whether a step's GEMM of these sizes forms its activations' norm itself: a row in one pass of the workgroup's threads.
 bool gemm_stream_norms(int M, int K, int segN) {
-    return M >= 1 && M <= 4 && K % 32 == 0 && segN % 32 == 0 && K <= 4096;
+    return M >= 1 && M <= 4 && K % 64 == 0 && segN % 128 == 0 && K <= 4096;
 }
 
-// Takes up to 32 rows (above that the activations' L2 traffic costs more than it saves), K a multiple of 32, segments a multiple of 16 rows; prefers the repacked weights.  Returns 1 if
-// handled, 0 if declined, < 0 on a launch error.
+// Takes up to 32 rows (above that the activations' L2 traffic costs more than it saves) of the shapes that the split-K form
+// takes (K a multiple of 64, segments of 128 rows), so that either both can form a product or neither; prefers the repacked
+// weights.  Returns 1 if handled, 0 if declined, < 0 on a launch error.
 int try_gemm_bf16_stream(const GemmArgs &g, hipStream_t st) {
-    if (g.kblocked || g.M < 1 || g.M > 32 || g.K % 32 != 0 || g.segN % 32 != 0) return 0;
+    if (g.kblocked || g.M < 1 || g.M > 32 || g.K % 64 != 0 || g.segN % 128 != 0) return 0;
     if (g.epilogue != EPI_STORE && g.epilogue != EPI_RESIDUAL && g.epilogue != EPI_SWIGLU) return 0;
     if (g.norm_x && (g.epilogue == EPI_RESIDUAL || !gemm_stream_norms(g.M, g.K, g.segN))) return 0;
     const int n_seg = g.epilogue == EPI_SWIGLU ? 2 : g.n_seg;
@@ -229,12 +268,11 @@ int try_gemm_bf16_stream(const GemmArgs &g, hipStream_t st) {
     p.w_step = kb ? (size_t)(g.segN + VLA_KB_PAD_ROWS) * 32 : 32;
     p.C = g.C; p.M = g.M; p.K = g.K; p.segN = g.segN;
     p.N = g.epilogue == EPI_SWIGLU ? g.segN : g.n_seg * g.segN;
+    p.parts = gemm_decode_parts(p.N, p.K);
     const double wbytes = 2.0 * g.K * (double)n_seg * g.segN;
     ProfScope ps(g.epilogue == EPI_SWIGLU ? "gemm_stream<swiglu>" : g.epilogue == EPI_RESIDUAL ? "gemm_stream<residual>"
                                                                                               : "gemm_stream<store>", wbytes, st);
-    if (g.epilogue == EPI_SWIGLU) launch_rows<EPI_SWIGLU>(p, st);
-    else if (g.epilogue == EPI_RESIDUAL) launch_rows<EPI_RESIDUAL>(p, st);
-    else launch_rows<EPI_STORE>(p, st);
-    const int rc = vla_check_launch("gemm_stream");
+    const int rc = g.epilogue == EPI_SWIGLU ? launch_rows<EPI_SWIGLU>(p, st)
+                   : g.epilogue == EPI_RESIDUAL ? launch_rows<EPI_RESIDUAL>(p, st) : launch_rows<EPI_STORE>(p, st);
     return rc ? rc : 1;
 }

@@ -193,6 +193,7 @@ int try_reduce_residual_rmsnorm_bf16(bf16_t *out, float *X, const float *P, int 
                                      float eps, hipStream_t st);
 // kb_rows = 0: row-major output [M, H]; else k-blocked [H / 32][kb_rows][32]
 int try_rmsnorm_bf16(bf16_t *out, const float *X, const float *gain, int M, int H, float eps, int kb_rows, hipStream_t st);
+int gemm_decode_parts(int N, int K);       // (N: output columns, gate columns alone for SwiGLU)
 bool gemm_stream_norms(int M, int K, int segN);
 int try_gemm_bf16_stream(const GemmArgs &g, hipStream_t st);
 int try_gemm_bf16_skinny(const GemmArgs &g, void *scratch, hipStream_t st);
