@@ -958,7 +958,7 @@ int try_gemm_bf16_dma(const GemmArgs &g, hipStream_t st) {
     return g.epilogue == EPI_RESIDUAL ? launch_kb<EPI_RESIDUAL>(p, kb, st) : launch_kb<EPI_STORE>(p, kb, st);
 }
 
-// QKV and gate/up projections of decode steps of 33 .. 128 rows on the small tiles: row-major activations, the repacked
+// QKV and gate/up projections of decode steps of 17 .. 128 rows on the small tiles: row-major activations, the repacked
 // weights where the model has them, no partial sums in memory, the sums of the split-K form.  64 rows of the 7B shape against
 // that form and its reductions: QKV 31 + 12 -> 28 + 7 us (with rotation and KV write), gate/up 57 + 10 -> 41; 128 rows 41 + 14
 // -> 37 + 8 and 75 + 16 -> 53.  (On the instruction and order of the 256 x 256 tiles QKV takes 27 and 35 us, gate/up 40 and 49.)

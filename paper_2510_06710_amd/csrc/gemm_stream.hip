@@ -1,4 +1,4 @@
-// bf16 GEMM for decode steps of at most 32 environments: C[M, N] = A[M, K] . W[N, K]^T, bound by the weight bytes from HBM.
+// bf16 GEMM for decode steps of at most 16 environments (O and down projection: 32): C[M, N] = A[M, K] . W[N, K]^T, bound by the weight bytes from HBM.
 //
 // One workgroup of eight waves per 16 output columns (SwiGLU: 16 gate and the matching up rows of the weights) and the whole
 // of K: each wave takes one of the parts into which a decode step cuts K (gemm_decode_parts; with fewer parts a workgroup has
@@ -13,9 +13,9 @@
 //
 // What counts is the number of waves with loads in flight, not the loads per wave: with one tile each in flight, 64
 // registers, three to four workgroups share a CU.  Measured on the 7B shape with repacked weights (time between events around
-// the launch, at 1 / 16 / 32 rows): QKV 24 / 26 / 32 us, O and down 16 / 20 / 23 (mean), gate/up 35 / 38 / 46; two or three
-// tiles in flight cost gate/up 0 / 2 / 5 us more.  The split-K form takes 25 / 26 / 27, 22 / 23 / 23 and 45 / 47 / 50 us and
-// leaves 26 to 33 us of reductions a layer that this one does not need.
+// the launch, at 1 / 16 rows): QKV 24 / 26 us, O and down 16 / 20 (mean; 23 at 32 rows), gate/up 35 / 38; two or three tiles in
+// flight cost gate/up 0 / 2 us more.  The split-K form takes 25 / 26, 22 / 23 (23) and 45 / 47 us and leaves 26 to 33 us of
+// reductions a layer that this one does not need.
 //
 // NORM rows (1, or up to 4): the activations are RMSNorm(x) g of fp32 rows x of at most 4096 columns (eight per thread),
 // which every workgroup forms for itself in LDS while its first weights are on the way: 0 to 2 us more in the kernel for a
@@ -237,8 +237,7 @@ int launch_rows(const StreamParams &p, hipStream_t st) {
         constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;
         if (p.x && p.M == 1) return launch<EPI, NB, 1, 1, 1>(p, st);
         if (p.x) return launch<EPI, NB, 1, 1, 4>(p, st);
-        if (p.M <= 16) return launch<EPI, NB, 1, 1, 0>(p, st);
-        return launch<EPI, 2, 2, 1, 0>(p, st);
+        return launch<EPI, NB, 1, 1, 0>(p, st);
     }
 }
 
@@ -249,11 +248,14 @@ bool gemm_stream_norms(int M, int K, int segN) {
     return M >= 1 && M <= 4 && K % 64 == 0 && segN % 128 == 0 && K <= 4096;
 }
 
-// Takes up to 32 rows (above that the activations' L2 traffic costs more than it saves) of the shapes that the split-K form
+// Takes up to 16 rows of QKV and gate/up, up to 32 of O and down of the shapes that the split-K form
 // takes (K a multiple of 64, segments of 128 rows), so that either both can form a product or neither; prefers the repacked
-// weights.  Returns 1 if handled, 0 if declined, < 0 on a launch error.
+// weights.  Above those rows the activations' L2 traffic costs more than it saves: QKV and gate/up take 26 + 38 us at 16 rows,
+// 28 + 39 at 17 and 33 + 46 at 32, on the small tiles 27 + 40 at all of these (row-major weights: 30 + 42, 31 + 45, 36 + 53
+// against 29 + 45); O and down 23 at 32 rows, in the split-K form 23 and a reduction.  Returns 1 if handled, 0 if declined, < 0 on
+// a launch error.
 int try_gemm_bf16_stream(const GemmArgs &g, hipStream_t st) {
-    if (g.kblocked || g.M < 1 || g.M > 32 || g.K % 64 != 0 || g.segN % 128 != 0) return 0;
+    if (g.kblocked || g.M < 1 || g.M > (g.epilogue == EPI_RESIDUAL ? 32 : 16) || g.K % 64 != 0 || g.segN % 128 != 0) return 0;
     if (g.epilogue != EPI_STORE && g.epilogue != EPI_RESIDUAL && g.epilogue != EPI_SWIGLU) return 0;
     if (g.norm_x && (g.epilogue == EPI_RESIDUAL || !gemm_stream_norms(g.M, g.K, g.segN))) return 0;
     const int n_seg = g.epilogue == EPI_SWIGLU ? 2 : g.n_seg;
