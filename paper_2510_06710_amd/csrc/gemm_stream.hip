@@ -17,9 +17,9 @@
 // flight cost gate/up 0 / 2 us more.  The split-K form takes 25 / 26, 22 / 23 (23) and 45 / 47 us and leaves 26 to 33 us of
 // reductions a layer that this one does not need.
 //
-// NORM rows (1, or up to 4): the activations are RMSNorm(x) g of fp32 rows x of at most 4096 columns (eight per thread),
-// which every workgroup forms for itself in LDS while its first weights are on the way: 0 to 2 us more in the kernel for a
-// launch of 6 us less.  The rows that a thread holds end the rule at four.
+// NORM rows (1, or up to 4): the activations are RMSNorm(x) g of fp32 rows x of at most 4096 columns, which every workgroup
+// forms for itself in LDS, with the sums of the norm kernels, while its first weights are on the way: 0 to 2 us more in the
+// kernel for a launch of 6 us less.  The rows that a thread holds end the rule at four.
 #include "vla_internal.h"
 
 namespace {
@@ -63,7 +63,7 @@ template <int EPI, int NB, int MB, int UN, int NORM>
 __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
     constexpr bool SW = EPI == EPI_SWIGLU;
     constexpr int COLS = SW ? 16 : 16 * NB, LDW = 16 * NB + 4;          // output columns, floats of a row of sums
-    __shared__ float squares[NORM ? NORM : 1][NW];
+    __shared__ float squares[NORM ? NORM : 1][4], chain[NORM ? NORM : 1][256];
     extern __shared__ __attribute__((aligned(16))) char lds[];
     float *part = (float *)lds;                                         // [wave][M][LDW]
     bf16_t *xs = (bf16_t *)(lds + (size_t)NW * p.M * LDW * 4);          // NORM: [M][K + 32], a 16-bank shift per row
@@ -114,16 +114,19 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
     };
     // This wave's tiles: part y of the K range, one after the other.  UN are in flight, each slot reloaded as soon as it is used.
     const int tiles = K / 64, kt0 = (int)((long)y * tiles / p.parts), mine = block < blocks ? (int)((long)(y + 1) * tiles / p.parts) - kt0 : 0;
-    // NORM: this thread's eight columns of every row, asked for ahead of the weights (loads return in order)
+    // NORM: this thread's two pieces of every row, asked for ahead of the weights (loads return in order).  The sums are those
+    // of the norm kernels' 256 threads, of which thread t adds the pieces of columns 4 (256 j + t) .. + 3 for j = 0, 1, ..: here
+    // thread t has the first two, thread 256 + t goes on with the other two.
     typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    const int t256 = threadIdx.x & 255, half = threadIdx.x >> 8;
     f32x4_t xv[NORM ? NORM : 1][2], gv[2];
     if (NORM) {
-        const int k = min((int)threadIdx.x * 8, K - 8);
 #pragma unroll
         for (int h = 0; h < 2; h++) {
-            gv[h] = *(const f4u *)(p.gain + k + h * 4);
+            const int k = min(((2 * half + h) * 256 + t256) * 4, K - 4);
+            gv[h] = *(const f4u *)(p.gain + k);
 #pragma unroll
-            for (int m = 0; m < NORM; m++) xv[m][h] = *(const f32x4_t *)(p.x + (size_t)min(m, p.M - 1) * K + k + h * 4);
+            for (int m = 0; m < NORM; m++) xv[m][h] = *(const f32x4_t *)(p.x + (size_t)min(m, p.M - 1) * K + k);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -132,28 +135,43 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
         if (u < mine) load(u, kt0 + u);
     if (NORM) {
         __builtin_amdgcn_sched_barrier(0);
-        const int k = threadIdx.x * 8;
+        float ss[NORM ? NORM : 1];
+        auto add = [&](int m) {
 #pragma unroll
-        for (int m = 0; m < NORM; m++) {
-            float ss = 0.f;
-            if (k < K)
+            for (int h = 0; h < 2; h++)
+                if (((2 * half + h) * 256 + t256) * 4 < K) {
 #pragma unroll
-                for (int e = 0; e < 8; e++) ss += xv[m][e >> 2][e & 3] * xv[m][e >> 2][e & 3];
+                    for (int e = 0; e < 4; e++) ss[m] += xv[m][h][e] * xv[m][h][e];
+                }
+        };
+        if (half == 0) {
 #pragma unroll
-            for (int o = 32; o; o >>= 1) ss += __shfl_xor(ss, o, 64);
-            if (lane == 0) squares[m][wave] = ss;
+            for (int m = 0; m < NORM; m++) { ss[m] = 0.f; add(m); chain[m][t256] = ss[m]; }
+        }
+        __syncthreads();
+        if (half == 1) {
+#pragma unroll
+            for (int m = 0; m < NORM; m++) {
+                ss[m] = chain[m][t256];
+                add(m);
+#pragma unroll
+                for (int o = 32; o; o >>= 1) ss[m] += __shfl_xor(ss[m], o, 64);
+                if (lane == 0) squares[m][wave & 3] = ss[m];
+            }
         }
         __syncthreads();
 #pragma unroll
         for (int m = 0; m < NORM; m++) {
-            float sq = 0.f;
+            const float *sq = squares[m];
+            const float r_rms = 1.0f / sqrtf((sq[0] + sq[1] + sq[2] + sq[3]) / (float)K + p.eps);
 #pragma unroll
-            for (int i = 0; i < NW; i++) sq += squares[m][i];
-            const float r_rms = 1.0f / sqrtf(sq / (float)K + p.eps);
-            bf16x8_t v;
+            for (int h = 0; h < 2; h++) {
+                const int k = ((2 * half + h) * 256 + t256) * 4;
+                bf16x4_t v;
 #pragma unroll
-            for (int e = 0; e < 8; e++) v[e] = (bf16_t)(xv[m][e >> 2][e & 3] * r_rms * gv[e >> 2][e & 3]);
-            if (m < p.M && k < K) *(bf16x8_t *)(xs + m * (K + 32) + k) = v;
+                for (int e = 0; e < 4; e++) v[e] = (bf16_t)(xv[m][h][e] * r_rms * gv[h][e]);
+                if (m < p.M && k < K) *(bf16x4_t *)(xs + m * (K + 32) + k) = v;
+            }
         }
         __syncthreads();
     }

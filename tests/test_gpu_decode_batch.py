@@ -15,6 +15,8 @@ SHAPES = {
     "h2048": vi.ModelShape(n_layers=2, hidden=2048, n_heads=32, ffn=2816, vocab=640, dtype="bf16"),
     # the 7B width: eight parts, two for the down projection, repacked weights
     "h4096": vi.ModelShape(n_layers=1, hidden=4096, n_heads=32, ffn=1152, vocab=640, dtype="bf16"),
+    # a width that the vectorised norm does not take, three parts of four pieces filled
+    "h640": vi.ModelShape(n_layers=1, hidden=640, n_heads=5, ffn=1152, vocab=640, dtype="bf16"),
     # FFN no multiple of 64: the generic kernel for these products, at all row counts
     "h256": vi.ModelShape(n_layers=1, hidden=256, n_heads=2, ffn=544, vocab=640, dtype="bf16"),
 }
@@ -37,9 +39,9 @@ def _rollout(name):
     return outputs
 
 
-# 31 | 32: 1024 (environment, head) pairs, where the attention's split of the keys changes; 16 | 17, 32 | 33, 64 | 65: where the
-# GEMMs' kernels or tiles do
-@pytest.mark.parametrize("few,many", [(31, 32), (5, 16), (16, 17), (32, 33), (64, 65), (17, MANY)])
+# 4 | 5: where the norm leaves the GEMMs; 31 | 32: 1024 (environment, head) pairs, where the attention's split of the keys
+# changes; 16 | 17, 32 | 33, 64 | 65: where the GEMMs' kernels or tiles do
+@pytest.mark.parametrize("few,many", [(1, 2), (3, 4), (4, 5), (31, 32), (5, 16), (16, 17), (32, 33), (64, 65), (17, MANY), (1, MANY)])
 @pytest.mark.parametrize("name", list(SHAPES))
 def test_few_and_many_environments(name, few, many):
     outputs = _rollout(name)
