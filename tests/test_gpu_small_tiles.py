@@ -1,32 +1,49 @@
 """The large GEMM's small-tile kernels (64 x 64, 64 x 128, 128 x 128 outputs, chosen by the number of tiles) sum in the same
 order as its 256 x 256 tiles: what a sequence gets must not depend, bit for bit, on how many others share the call, and
-must match the oracle at row counts around the tile edges.  Width 1024: the few-row calls take the small tiles, and the
-9,000 and more rows of the large batches 256 x 256 ones (36 tile rows x 12, x 4 and x 22 tile columns)."""
+must match the oracle at row counts around the tile edges.  The large batch fills its 256 x 256 tiles (127 x 129 rows are 64
+tile rows, with 24, 16 and 8 tile columns whole rounds of 256 tiles) and takes them for every product of the prefill, the small
+ones take small tiles: both read from the labels of the launches."""
+import ctypes
 import dataclasses
 
 import pytest
 import torch
 
 import vla_inputs as vi
+from paper_2510_06710_amd import binding as vb
 from paper_2510_06710_amd.harness import Rollout
 from parity import GpuCase, compare_rollout, oracle_rollout
 
 pytestmark = pytest.mark.gpu
 SHAPE = vi.ModelShape(n_layers=2, hidden=1024, n_heads=8, ffn=2816, vocab=640, dtype="bf16")
+EPILOGUES = {"<qkv_rope>", "<residual>", "<swiglu>"}
+WIDE = vi.ModelShape(n_layers=2, hidden=2048, n_heads=16, ffn=2048, vocab=640, dtype="bf16")
+
+
+def _large_gemms():
+    """Labels of the large GEMM's launches since profiling was switched on; switches it off."""
+    buf = ctypes.create_string_buffer(1 << 14)
+    vb.lib().vla_profile_report(buf, len(buf))
+    vb.lib().vla_profile_enable(0)
+    return {n for n in (line.split(" ")[0] for line in buf.value.decode().splitlines()) if n.startswith(("gemm_bf16_dma<", "gemm_small<"))}
 
 
 @pytest.mark.parametrize("prepack", [True, False])
 @pytest.mark.parametrize("B", [1, 2, 3, 7, 20])
 def test_a_row_does_not_depend_on_the_batch(B, prepack):
-    big, P, T, A = 70, 115, 14, 33                           # 129 prefix rows, 33 slots
-    wl = vi.Workload("tiles", SHAPE, batch=big, n_patches=P, n_instr=T, n_action=A, mode=1)
+    big, P, T, A = 127, 115, 14, 33                          # 129 prefix rows, 33 slots
+    wl = vi.Workload("tiles", WIDE, batch=big, n_patches=P, n_instr=T, n_action=A, mode=1)
     patch, ids = vi.observation(wl, 5, device="cuda:0")
-    synth = vi.SynthModel(SHAPE, 5, device="cuda:0")
+    synth = vi.SynthModel(WIDE, 5, device="cuda:0")
     slot = synth.slot_embed(A)
     run = Rollout(synth, big, P + T + A, prepack=prepack)
     got = []
     for n in (big, B):
+        vb.lib().vla_profile_enable(1)
         h, _ = run.prefill(patch[:n], ids[:n], want_value=False)
+        # (20: 11 tile rows leave little of a round empty, but for O, down and the last layer's K and V)
+        large, small = {big: (EPILOGUES, set()), 20: ({"<qkv_rope>", "<swiglu>"}, {"<qkv_rope>", "<residual>"})}.get(n, (set(), EPILOGUES))
+        assert _large_gemms() == {"gemm_bf16_dma" + e for e in large} | {"gemm_small" + e for e in small}
         bins, logp, ent, logits = run.decode(h, P + T, A, 1, slot)
         got.append([x[:B].clone() for x in (logits, logp, ent, bins)])
     torch.cuda.synchronize()
