@@ -216,7 +216,7 @@ static size_t prepack_layer_bytes(const vla_config &c) {
 static int try_gemm_bf16_large(const GemmArgs &g, hipStream_t st) { return try_gemm_bf16_dma(g, st); }
 
 // Kernel choice depends on the storage type, on whether the forward has one row per sequence and, for these, on the rows:
-// decode steps take the weight-streaming kernel (QKV, gate/up to 16 rows, O, down to 32), up to 128 rows the small tiles (QKV,
+// decode steps of up to 32 rows take the weight-streaming kernel (wide QKV and gate/up: 16), up to 128 rows the small tiles (QKV,
 // gate/up) and the skinny split-K kernel (O, down); up to 128 tail rows the skinny kernel.  All of these add K in the same parts and in the same order
 // (gemm_decode_parts), so a row's result does not depend, bit for bit, on how many rows share the step, and shapes that one of
 // them declines are declined by all (the generic kernel then takes them, which also has one order for all row counts).  Larger

@@ -1,5 +1,6 @@
 // Weight-streaming bf16 GEMM with split K: C[M, N] = A[M, K] . W[N, K]^T with M <= 256 (one row per environment: the O and
-// down projections of decode steps of 33 to 128 rows; all projections of up to 128 tail rows).  Every weight byte is read from HBM exactly once, so the kernel is laid
+// down projections of decode steps of 33 to 128 rows; all projections of up to 128 tail rows).  Its sums are what every kernel
+// of a decode step of up to 128 rows forms (see run_gemm).  Every weight byte is read from HBM exactly once, so the kernel is laid
 // out around that stream:
 //   - a wave owns 32 weight rows (plus the 32 matching "up" rows for the SwiGLU projection) and reads
 //     them straight from global memory into MFMA row-operand registers: per 64-wide K tile a lane

@@ -1,8 +1,8 @@
-// bf16 GEMM for decode steps of at most 16 environments (O and down projection: 32): C[M, N] = A[M, K] . W[N, K]^T, bound by the weight bytes from HBM.
+// bf16 GEMM for decode steps of at most 32 environments: C[M, N] = A[M, K] . W[N, K]^T, bound by the weight bytes from HBM.
 //
 // One workgroup of eight waves per 16 output columns (SwiGLU: 16 gate and the matching up rows of the weights) and the whole
-// of K: each wave takes one of the parts into which a decode step cuts K (gemm_decode_parts; with fewer parts a workgroup has
-// more columns) and walks it alone, without barriers; the parts are added in order through LDS at the end.  So no partial sums
+// of K: each wave takes one of the parts into which a decode step cuts K (gemm_decode_parts; with fewer parts a workgroup may
+// have more columns) and walks it alone, without barriers; the parts are added in order through LDS at the end.  So no partial sums
 // travel through memory, the epilogue is the final one and no reduction kernel follows.
 //
 // The sums are those of gemm_skinny.hip bit for bit: v_mfma_f32_32x32x16_bf16 on the same columns (8 j .. + 7 of either half
@@ -11,8 +11,8 @@
 // change places between lane rows afterwards (v_permlane16_swap).  With 16 activation rows half of the instruction's columns
 // are idle, with 16 weight rows half of its rows: the matrix cores have the time.
 //
-// What counts is the number of waves with loads in flight, not the loads per wave: with one tile each in flight, 64
-// registers, three to four workgroups share a CU.  Measured on the 7B shape with repacked weights (time between events around
+// What counts is the number of waves with loads in flight, not the loads per wave: with one tile each in flight, about 64
+// registers, three or four workgroups share a CU.  Measured on the 7B shape with repacked weights (time between events around
 // the launch, at 1 / 16 rows): QKV 24 / 26 us, O and down 16 / 20 (mean; 23 at 32 rows), gate/up 35 / 38; two or three tiles in
 // flight cost gate/up 0 / 2 us more.  The split-K form takes 25 / 26, 22 / 23 (23) and 45 / 47 us and leaves 26 to 33 us of
 // reductions a layer that this one does not need.
@@ -34,6 +34,7 @@ struct StreamParams {
     float eps;
     int M, N, K, segN;
     int parts;                 // K parts of the sums (1, 2, 4 or 8), one wave each
+    int groups;                // blocks of columns per workgroup, at most NW / parts (waves beyond them only help with the norm)
     size_t w_row, w_step;      // elements between weight rows and between 32-column steps of one row
 };
 
@@ -69,7 +70,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
     bf16_t *xs = (bf16_t *)(lds + (size_t)NW * p.M * LDW * 4);          // NORM: [M][K + 32], a 16-bank shift per row
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l32 = lane & 31, hh = lane >> 5, c1 = (lane >> 4) & 1;
     const int K = p.K, blocks = p.N / COLS, group = wave / p.parts, y = wave - group * p.parts;
-    const int block = blockIdx.x * (NW / p.parts) + group, n0 = min(block, blocks - 1) * COLS;
+    const int block = group < p.groups ? blockIdx.x * p.groups + group : blocks, n0 = min(block, blocks - 1) * COLS;
     const bf16_t *a[MB], *w[NB];
 #pragma unroll
     for (int i = 0; i < MB; i++) a[i] = p.A + (size_t)min(i * 16 + l16, p.M - 1) * K + hh * 32 + c1 * 8;
@@ -203,9 +204,9 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
     __syncthreads();
     // the parts of a block are added in K order: four columns of one row per thread
     constexpr int QUADS = COLS / 4;
-    for (int item = threadIdx.x; item < NW / p.parts * p.M * QUADS; item += 64 * NW) {
+    for (int item = threadIdx.x; item < p.groups * p.M * QUADS; item += 64 * NW) {
         const int q = item % QUADS, gm = item / QUADS, gr = gm / p.M, m = gm - gr * p.M;
-        const int blk = blockIdx.x * (NW / p.parts) + gr;
+        const int blk = blockIdx.x * p.groups + gr;
         if (blk >= blocks) break;
         const float *src = part + (gr * p.parts * p.M + m) * LDW + q * 4;
         auto sum_of = [&](int off) {
@@ -237,26 +238,30 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
     }
 }
 
-template <int EPI, int NB, int MB, int UN, int NORM>
-int launch(const StreamParams &p, hipStream_t st) {
-    // (at most 37 KB of sums, or 5 KB and 34 KB of normed rows)
+template <int EPI, int NB, int MB, int NORM>
+int launch(StreamParams p, hipStream_t st) {
+    // (at most 21 KB of sums, or 5 KB and 34 KB of normed rows)
     const size_t lds = (size_t)NW * p.M * (16 * NB + 4) * 4 + (NORM ? (size_t)p.M * (p.K + 32) * sizeof(bf16_t) : 0);
-    const int blocks = p.N / (EPI == EPI_SWIGLU ? 16 : 16 * NB), per_wg = NW / p.parts;
-    gemm_stream_kernel<EPI, NB, MB, UN, NORM><<<(blocks + per_wg - 1) / per_wg, 64 * NW, lds, st>>>(p);
+    const int blocks = p.N / (EPI == EPI_SWIGLU ? 16 : 16 * NB);
+    // One block per workgroup until every CU has one, then as many as there are waves for: width 1024, FFN 2816 (two parts) at
+    // 1 row 44 -> 37 us a layer.  One workgroup per CU has the registers for a second tile in flight: 37 -> 34 (above 16 rows
+    // each tile brings twice the activations, and one is better: 7B shape, O and down at 32 rows 23 us against 25).
+    p.groups = (blocks + 255) / 256 < NW / p.parts ? (blocks + 255) / 256 : NW / p.parts;
+    const int grid = (blocks + p.groups - 1) / p.groups;
+    if (MB == 1 && grid <= 256) gemm_stream_kernel<EPI, NB, MB, MB == 1 ? 2 : 1, NORM><<<grid, 64 * NW, lds, st>>>(p);
+    else gemm_stream_kernel<EPI, NB, MB, 1, NORM><<<grid, 64 * NW, lds, st>>>(p);
     return vla_check_launch("gemm_stream");
 }
 
 template <int EPI>
 int launch_rows(const StreamParams &p, hipStream_t st) {
-    if constexpr (EPI == EPI_RESIDUAL) {                 // 256 workgroups at N = 4096: one per CU, so two tiles in flight
-        if (p.M <= 16) return launch<EPI, 1, 1, 2, 0>(p, st);
-        return launch<EPI, 1, 2, 1, 0>(p, st);
-    } else {
-        constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;
-        if (p.x && p.M == 1) return launch<EPI, NB, 1, 1, 1>(p, st);
-        if (p.x) return launch<EPI, NB, 1, 1, 4>(p, st);
-        return launch<EPI, NB, 1, 1, 0>(p, st);
+    constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;
+    if constexpr (EPI != EPI_RESIDUAL) {
+        if (p.x && p.M == 1) return launch<EPI, NB, 1, 1>(p, st);
+        if (p.x) return launch<EPI, NB, 1, 4>(p, st);
     }
+    if (p.M <= 16) return launch<EPI, NB, 1, 0>(p, st);
+    return launch<EPI, NB, 2, 0>(p, st);
 }
 
 }  // namespace
@@ -266,14 +271,17 @@ bool gemm_stream_norms(int M, int K, int segN) {
     return M >= 1 && M <= 4 && K % 64 == 0 && segN % 128 == 0 && K <= 4096;
 }
 
-// Takes up to 16 rows of QKV and gate/up, up to 32 of O and down of the shapes that the split-K form
-// takes (K a multiple of 64, segments of 128 rows), so that either both can form a product or neither; prefers the repacked
-// weights.  Above those rows the activations' L2 traffic costs more than it saves: QKV and gate/up take 26 + 38 us at 16 rows,
-// 28 + 39 at 17 and 33 + 46 at 32, on the small tiles 27 + 40 at all of these (row-major weights: 30 + 42, 31 + 45, 36 + 53
-// against 29 + 45); O and down 23 at 32 rows, in the split-K form 23 and a reduction.  Returns 1 if handled, 0 if declined, < 0 on
-// a launch error.
+// Takes up to 32 rows (QKV and gate/up of more than 8192 columns: 16) of the shapes that the split-K form takes (K a multiple of
+// 64, segments of 128 rows), so that either both can form a product or neither; prefers the repacked weights.  Above those rows
+// the activations' traffic, which grows with the columns, costs more than it saves.  7B shape: QKV and gate/up take 26 + 38 us at
+// 16 rows, 28 + 39 at 17 and 33 + 46 at 32, on the small tiles 27 + 40 at all of these (row-major weights: 30 + 42, 31 + 45,
+// 36 + 53 against 29 + 45); O and down 23 at 32 rows, in the split-K form 23 and a reduction.  Whole decode of 6 steps x 4
+// layers at 24 / 32 rows, here against the small tiles: width 1024 1.06 / 1.09 against 1.13 / 1.16 ms, width 2048 with FFN 5504
+// 1.58 / 1.70 against 1.78 / 1.84 and with FFN 8192 1.89 / 2.15 against 2.06 / 2.21, width 5120 5.37 / 5.89 against 4.55 / 4.80.
+// Returns 1 if handled, 0 if declined, < 0 on a launch error.
 int try_gemm_bf16_stream(const GemmArgs &g, hipStream_t st) {
-    if (g.kblocked || g.M < 1 || g.M > (g.epilogue == EPI_RESIDUAL ? 32 : 16) || g.K % 64 != 0 || g.segN % 128 != 0) return 0;
+    const bool narrow = g.epilogue == EPI_RESIDUAL || (g.epilogue == EPI_SWIGLU ? 1 : g.n_seg) * (long)g.segN <= 8192;
+    if (g.kblocked || g.M < 1 || g.M > (narrow ? 32 : 16) || g.K % 64 != 0 || g.segN % 128 != 0) return 0;
     if (g.epilogue != EPI_STORE && g.epilogue != EPI_RESIDUAL && g.epilogue != EPI_SWIGLU) return 0;
     if (g.norm_x && (g.epilogue == EPI_RESIDUAL || !gemm_stream_norms(g.M, g.K, g.segN))) return 0;
     const int n_seg = g.epilogue == EPI_SWIGLU ? 2 : g.n_seg;
