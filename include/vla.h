@@ -115,8 +115,8 @@ int vla_destroy(vla_model *model);
  * vla_prepack: enqueues the repack of all layers on `stream` into `buffer` (DEVICE, 256-byte aligned, at least
  *   vla_prepack_bytes bytes, caller owned) and makes the model use it from then on; the caller orders later
  *   calls after it (same stream, or events) and keeps the buffer alive and unchanged while the model uses it.
- *   buffer = NULL detaches.  The original weights stay in use for single-row (decode) forwards.  Results
- *   with and without the copy are bit-identical. */
+ *   buffer = NULL detaches.  Decode forwards stream the copy too where they can, the original weights stay in use
+ *   elsewhere (tail rows, the backward).  Results with and without the copy are bit-identical. */
 size_t vla_prepack_bytes(const vla_config *cfg);
 int vla_prepack(vla_model *model, void *buffer, size_t bytes, void *stream);
 

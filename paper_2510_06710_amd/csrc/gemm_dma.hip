@@ -962,8 +962,9 @@ int try_gemm_bf16_dma(const GemmArgs &g, hipStream_t st) {
 // weights where the model has them, no partial sums in memory, the sums of the split-K form.  64 rows of the 7B shape against
 // that form and its reductions: QKV 31 + 12 -> 28 + 7 us (with rotation and KV write), gate/up 57 + 10 -> 41; 128 rows 41 + 14
 // -> 37 + 8 and 75 + 16 -> 53.  (On the instruction and order of the 256 x 256 tiles QKV takes 27 and 35 us, gate/up 40 and 49.)
-// The O and down projections have too few tiles (64 rows: 38 us and a norm of 6, split-K 25 and 7) and stay there.  Returns 1 if
-// handled, 0 if declined, < 0 on a launch error.
+// The O and down projections have too few tiles (64 rows: 38 us and a norm of 6, split-K 25 and 7) and stay there.  Above 128
+// rows the split-K form of the large tiles is faster: at 129 rows QKV 43 + 11 us against 55 + 8 here and gate/up 66 + 7 against 83,
+// at 256 rows 45 + 15 against 51 + 10 and 70 + 10 against 81.  Returns 1 if handled, 0 if declined, < 0 on a launch error.
 int try_gemm_bf16_dma_step(const GemmArgs &g, hipStream_t st) {
     if (g.epilogue != EPI_STORE && g.epilogue != EPI_SWIGLU) return 0;
     if (g.kblocked || g.M < 1 || g.M > 128 || g.K % 64 != 0 || g.K < 256 || g.a_rows < 256) return 0;

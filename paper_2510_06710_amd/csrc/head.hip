@@ -9,9 +9,12 @@
 // other sign the sum.  A chunk that comes out NaN is formed again that way.)  fp32 weights: v_mfma_f32_16x16x4_f32.  Sums
 // run over one chunk at a time and the chunks are added in order, the same for every row count and both forms below, so a
 // row's result does not depend on the rows around it.
-//   partial form: one workgroup per (16 rows, chunk, 64 bins), fp32 partial logits to scratch, a second kernel samples;
-//   whole form (above VLA_HEAD_PARTIAL_ROWS rows, where 16 copies of the logits would be traffic of their own): a
-//   workgroup walks all chunks for 32 rows and samples them from LDS.
+//   partial form: one workgroup per (16 rows, chunk, 64 bins), fp32 partial logits to scratch, a second kernel samples: its
+//   time grows with the rows, for the partial logits of every chunk are written and read;
+//   whole form (above VLA_HEAD_PARTIAL_ROWS rows): a workgroup walks all chunks for 32 rows and samples them from LDS, a chain
+//   of the same length for any rows that fit the chip at once.
+// Where they meet, in bf16: 3072 / 4096 / 5120 rows take 101 / 131 / 161 us in the partial form and 129 / 129 / 130 in the whole
+// one at H = 4096, 34 / 42 / 49 and 46 / 47 / 48 at H = 1024.
 // Measured at H = 4096 in bf16: 1 .. 256 rows took 131-140 us and 7168 rows 3450 us with one workgroup per row and a bin
 // per thread (every row fetched the 2 MB again); now (both kernels) 10 us at 1 row, 17 us at 256 and 133 us at 7168, of which a
 // kernel launch is about 3.
@@ -350,7 +353,7 @@ int launch_head_sample(const float *h, const T *lm_head_bins, int n_rows, int H,
     if (n_rows == 0) return 0;
     ProfScope ps("head_sample", 2.0 * n_rows * H * VLA_N_BINS, st);
     const SampleArgs a{temperature, gumbel, given_bins, bins_out, logp, ent, logits, out_stride, out_off};
-    if (n_rows > VLA_HEAD_PARTIAL_ROWS) {       // enough 32-row workgroups to fill the chip
+    if (n_rows > VLA_HEAD_PARTIAL_ROWS) {
         head_whole_kernel<T><<<(n_rows + 31) / 32, 256, 0, st>>>(h, lm_head_bins, a, X_next, embed, vocab, n_rows, H);
         return vla_check_launch("head_sample");
     }

@@ -23,10 +23,10 @@ SHAPES = {
 
 
 @functools.lru_cache(maxsize=1)
-def _rollout(name):
+def _rollout(name, prepack=True):
     shape = SHAPES[name]
     wl = vi.Workload("batch", shape, batch=MANY, n_patches=S - 2, n_instr=2, n_action=A)
-    run = Rollout(vi.SynthModel(shape, 8, device="cuda:0"), MANY, S + A)
+    run = Rollout(vi.SynthModel(shape, 8, device="cuda:0"), MANY, S + A, prepack=prepack)
     patch, ids = vi.observation(wl, 8, device="cuda:0")
     noise = vi.gumbel_noise(wl, 8, device="cuda:0")
 
@@ -47,3 +47,10 @@ def test_few_and_many_environments(name, few, many):
     outputs = _rollout(name)
     for x, y in zip(outputs(few), outputs(many)):
         assert torch.equal(x, y[:few])
+
+
+@pytest.mark.parametrize("n", [3, 16, 24, 100])
+def test_with_and_without_repacked_weights(n):
+    packed = _rollout("h4096")(n)
+    for x, y in zip(packed, _rollout("h4096", prepack=False)(n)):
+        assert torch.equal(x, y)
