@@ -8,24 +8,28 @@
 // operand and the activation rows its column operand: a lane ends up with activation row (lane % 16) of
 // a block and four consecutive output columns.
 //
-// K moves in half tiles of 32 through a ring of four 32 KB LDS stages.  `buffer_load ... lds` writes
+// K moves in half tiles of 32 through a ring of five 32 KB LDS stages (all 160 KB).  `buffer_load ... lds` writes
 // the operands straight into LDS (no staging registers, no ds_write): a wave instruction fills 1 KB
 // linearly, i.e. 16 tile rows of 64 bytes; chunk c (16 bytes) of row r sits at position
 // c ^ ((r >> 1) & 3), chosen on the global side by which chunk a lane fetches, so that the fragment
 // reads are free of bank conflicts: a ds_read_b128 is served eight lanes (128 bytes) at a time, and the eight
 // 64-byte rows of such a group then cover the eight 16-byte slots of 128 bytes (with (r >> 2) & 3, which would
-// suit 256 bytes per step, SQ_LDS_BANK_CONFLICT showed every read taking twice as long).  The loads of half tile g + 3 are issued while half tile g is read.
+// suit 256 bytes per step, SQ_LDS_BANK_CONFLICT showed every read taking twice as long).
 //
-// Schedule of one iteration g (one barrier): wait for this wave's loads of half tile g, barrier, then 16
-// groups of {one ds_read_b128 of half tile g into fragment buffer g % 2, four MFMAs of half tile g - 1 from
-// the other buffer}, with the eight load instructions of half tile g + 3 spread between them.  The
-// fragment reads are inline assembly with explicit waits: the compiler would otherwise wait for every
-// outstanding LDS-bound load before any LDS read.
+// Schedule.  Half tile g is read into fragment buffer g % 2 while half tile g - 1 multiplies from the other buffer.  One
+// barrier per pair of half tiles (g even): before it each wave waits for its loads of g and g + 1 (those of g + 2, eight
+// instructions, may still be in flight), after it the stages of g - 2 and g - 1 are free for g + 3 and g + 4, whose loads are
+// spread evenly over the pair.  With one wave per SIMD whatever the wave issues between two MFMAs beyond 12 cycles leaves the
+// matrix pipe idle, so the loop holds no branch but its own and at most one other instruction, or a load with its two
+// scalar ones, after an MFMA: the fragment reads after every second MFMA of a half tile's first 32, the loads after every
+// eighth; consecutive loads differ in the instruction's own offset, and the cursor's step to the next tile is outside.  At
+// 73,728 rows of the 7B shape, against the same tiles with the loads and their branches in clusters between groups of four
+// MFMAs: QKV 5.33 -> 4.80 ms (1420 TFLOP/s), O and down 3.46 -> 3.12 on average, gate/up 10.0 -> 8.8 (1515; the vendor
+// library's product of the same shape 1509).  A barrier per half tile with a ring of four: 1.5 % slower; a barrier per pair
+// with a ring of four, 16 loads in the pair's first half: 6 %; loads after every fourth or sixth MFMA, reads after every third: the same.
 //
-// Unit-barrier variant of that schedule (UB, used by the gate/up projection): one wait and one barrier per pair of
-// half tiles.  At the start of even iteration g the pair (g, g + 1) has landed and every wave has finished reading
-// (g - 2, g - 1), whose two stages take the sixteen load instructions of (g + 2, g + 3), all issued during
-// iteration g: half the barriers, for a prefetch distance of two half tiles instead of three.
+// The fragment reads, and the MFMAs with them, are inline assembly with explicit waits: the compiler would otherwise wait for
+// every outstanding LDS-bound load before any LDS read, and copies the accumulators where two paths meet.
 //
 // Operand layout.  Row-major operands are fetched as 64-byte pieces of 16 rows per instruction, i.e. half
 // cache lines; in the k-blocked layout (KB: [K / 32][rows][32] for the activations and for repacked weights)
@@ -34,8 +38,9 @@
 //
 // One workgroup per CU walks its tiles in turn (tile i of a workgroup = id + grid * i, which keeps the
 // XCD-contiguous tile order); the half-tile stream simply continues into the next tile, so that only the
-// first tile pays an empty pipeline.  A tile's last MFMAs run in the next tile's first iteration; the
-// epilogue follows that iteration and uses the LDS stage just read as its staging panel.
+// first tile pays an empty pipeline.  A tile's last MFMAs run in the next tile's first iteration, whose loads go out as
+// usual; the epilogue follows that iteration and uses the LDS stage just read as its staging panel, and the next
+// tile's sums start with an MFMA that adds to zero.
 #include "vla_internal.h"
 
 #include <type_traits>
@@ -46,7 +51,7 @@ namespace {
 constexpr int BM = 256, BN = 256, HK = 32;
 constexpr int REGION = 256 * HK * 2;     // 16 KB per operand per stage
 constexpr int STAGE = 2 * REGION;        // 32 KB
-constexpr int NSTAGES = 4;
+constexpr int NSTAGES = 5;
 
 typedef __attribute__((address_space(3))) void lds_void;
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
@@ -102,18 +107,47 @@ __device__ __forceinline__ void acc_settle() { asm volatile("s_nop 15\n\ts_nop 1
 // row-wise reads free of bank conflicts.
 __device__ __forceinline__ float *panel_at(float *panel, int row, int cb) { return panel + row * 128 + ((cb ^ row) << 2); }
 
+// The panel is read and written by assembly: the next tile's loads are on their way into other stages meanwhile, and the
+// compiler would wait for every LDS-bound load before each access it knows of.
+__device__ __forceinline__ int lds_addr(const void *p) { return (int)(size_t)(lds_void *)p; }
+__device__ __forceinline__ f32x4_t panel_get(float *panel, int row, int cb) {
+    f32x4_t v;
+    asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(lds_addr(panel_at(panel, row, cb))) : "memory");
+    return v;
+}
+__device__ __forceinline__ void panel_put(float *panel, int row, int cb, f32x4_t v) {
+    asm volatile("ds_write_b128 %0, %1" ::"v"(lds_addr(panel_at(panel, row, cb))), "v"(v) : "memory");
+}
+__device__ __forceinline__ void panel_put_acc(float *panel, int row, int cb, const f32x4_t &v) {
+    asm volatile("ds_write_b128 %0, %1" ::"v"(lds_addr(panel_at(panel, row, cb))), "a"(v) : "memory");
+}
+__device__ __forceinline__ void panel_written() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// everything read so far has landed; what is read passes through, so that no use moves above the wait
+template <int N>
+__device__ __forceinline__ void panel_wait(f32x4_t (&v)[N]) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < N; i++) asm volatile("" : "+v"(v[i]));
+}
+
 // One 16-row block of a wave's QKV output, from its panel: the wave's 128 columns are one head of q, k or v (head_dim 128).
 __device__ __forceinline__ void qkv_block_out(const DmaGemmParams &p, float *panel, int mblock, int n0, int lane) {
     const int seg_in = n0 / p.H, head = (n0 - seg_in * p.H) >> 7, seg = seg_in + p.seg0;
+    f32x4_t v[8];
     if (seg == 2) {
 #pragma unroll
         for (int it = 0; it < 4; it++) {
+            const int row = it * 4 + (lane >> 4), c = lane & 15;
+            v[2 * it] = panel_get(panel, row, 2 * c);
+            v[2 * it + 1] = panel_get(panel, row, 2 * c + 1);
+        }
+        panel_wait(v);
+#pragma unroll
+        for (int it = 0; it < 4; it++) {
             const int row = it * 4 + (lane >> 4), c = lane & 15, m = mblock + row;
-            f32x4_t a = *(const f32x4_t *)panel_at(panel, row, 2 * c);
-            f32x4_t b = *(const f32x4_t *)panel_at(panel, row, 2 * c + 1);
             bf16x8_t o;
 #pragma unroll
-            for (int e = 0; e < 4; e++) { o[e] = (bf16_t)a[e]; o[4 + e] = (bf16_t)b[e]; }
+            for (int e = 0; e < 4; e++) { o[e] = (bf16_t)v[2 * it][e]; o[4 + e] = (bf16_t)v[2 * it + 1][e]; }
             if (m < p.M) {
                 const int sq = m / p.R, pos = p.pos0 + (m - sq * p.R);
                 *(bf16x8_t *)(p.vc + (((size_t)sq * p.n_heads + head) * p.pos_stride + pos) * 128 + c * 8) = o;
@@ -126,9 +160,19 @@ __device__ __forceinline__ void qkv_block_out(const DmaGemmParams &p, float *pan
             const int item = it * 64 + lane;
             const int row = (seg == 0) ? (item >> 3) : (item & 15);
             const int c = (seg == 0) ? (item & 7) : (item >> 4);
+            v[4 * it] = panel_get(panel, row, 2 * c);
+            v[4 * it + 1] = panel_get(panel, row, 2 * c + 1);
+            v[4 * it + 2] = panel_get(panel, row, 16 + 2 * c);
+            v[4 * it + 3] = panel_get(panel, row, 17 + 2 * c);
+        }
+        panel_wait(v);
+#pragma unroll
+        for (int it = 0; it < 2; it++) {
+            const int item = it * 64 + lane;
+            const int row = (seg == 0) ? (item >> 3) : (item & 15);
+            const int c = (seg == 0) ? (item & 7) : (item >> 4);
             const int m = mblock + row;
-            f32x4_t lo0 = *(const f32x4_t *)panel_at(panel, row, 2 * c), lo1 = *(const f32x4_t *)panel_at(panel, row, 2 * c + 1);
-            f32x4_t hi0 = *(const f32x4_t *)panel_at(panel, row, 16 + 2 * c), hi1 = *(const f32x4_t *)panel_at(panel, row, 17 + 2 * c);
+            const f32x4_t lo0 = v[4 * it], lo1 = v[4 * it + 1], hi0 = v[4 * it + 2], hi1 = v[4 * it + 3];
             if (m < p.M) {
                 const int sq = m / p.R, rr = m - sq * p.R, pos = p.pos0 + rr;
                 const f32x4_t *tb = (const f32x4_t *)(p.table + (size_t)rr * 64 + c * 8);
@@ -166,14 +210,20 @@ __device__ __forceinline__ void swiglu_block_out(const DmaGemmParams &p, float *
     c0 += (lane & 7) * 8;
     bf16_t *out = (bf16_t *)p.C + (KB ? (size_t)(c0 >> 5) * p.a_rows * 32 + (c0 & 31) : (size_t)c0);
     const size_t row_stride = KB ? 32 : (size_t)p.N;
+    f32x4_t v[4];
 #pragma unroll
     for (int it = 0; it < 2; it++) {
-        const int row = it * 8 + (lane >> 3), c2 = lane & 7, m = mblock + row;
-        f32x4_t a = *(const f32x4_t *)panel_at(panel, row, 2 * c2);
-        f32x4_t b = *(const f32x4_t *)panel_at(panel, row, 2 * c2 + 1);
+        const int row = it * 8 + (lane >> 3), c2 = lane & 7;
+        v[2 * it] = panel_get(panel, row, 2 * c2);
+        v[2 * it + 1] = panel_get(panel, row, 2 * c2 + 1);
+    }
+    panel_wait(v);
+#pragma unroll
+    for (int it = 0; it < 2; it++) {
+        const int m = mblock + it * 8 + (lane >> 3);
         bf16x8_t o;
 #pragma unroll
-        for (int e = 0; e < 4; e++) { o[e] = (bf16_t)a[e]; o[4 + e] = (bf16_t)b[e]; }
+        for (int e = 0; e < 4; e++) { o[e] = (bf16_t)v[2 * it][e]; o[4 + e] = (bf16_t)v[2 * it + 1][e]; }
         if (m < p.M) *(bf16x8_t *)(out + (size_t)m * row_stride) = o;
     }
 }
@@ -191,7 +241,8 @@ __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][8], const DmaGemmPara
         for (int i = 0; i < 8; i++) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int j = 0; j < 8; j++) *(f32x4_t *)panel_at(panel, l16, j * 4 + kq) = acc_read4(acc[j][i]);
+            for (int j = 0; j < 8; j++) panel_put_acc(panel, l16, j * 4 + kq, acc[j][i]);
+            panel_written();
             qkv_block_out(p, panel, m0 + wm * 128 + i * 16, n0, lane);
         }
         return;
@@ -207,8 +258,9 @@ __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][8], const DmaGemmPara
                 f32x4_t v;
 #pragma unroll
                 for (int e = 0; e < 4; e++) v[e] = vla_silu_mul(g[e], u[e]);
-                *(f32x4_t *)panel_at(panel, l16, j * 4 + kq) = v;
+                panel_put(panel, l16, j * 4 + kq, v);
             }
+            panel_written();
             swiglu_block_out<KB>(p, panel, m0 + wm * 128 + i * 16, tn * 128 + wn * 64, lane);
         }
         return;
@@ -228,9 +280,9 @@ __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][8], const DmaGemmPara
     // computed once, before the main loop, and held in registers across it)
     auto load_x = [&](i32x4_t (&xb)[8], int i) {
         int r2 = row2;
-        asm volatile("" : "+v"(r2));
+        asm volatile("" : "+s"(r2));
 #pragma unroll
-        for (int it = 0; it < 8; it++) xb[it] = __builtin_amdgcn_raw_buffer_load_b128(c_rsrc, voff + (i * 8 + it) * r2, 0, 0);
+        for (int it = 0; it < 8; it++) xb[it] = __builtin_amdgcn_raw_buffer_load_b128(c_rsrc, voff, (i * 8 + it) * r2, 0);
     };
     if (EPI == EPI_RESIDUAL) {
 #pragma unroll
@@ -240,25 +292,43 @@ __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][8], const DmaGemmPara
     for (int i = 0; i < 8; i++) {
         __builtin_amdgcn_sched_barrier(0);
         int r2 = row2;
-        asm volatile("" : "+v"(r2));
+        asm volatile("" : "+s"(r2));
 #pragma unroll
-        for (int j = 0; j < 8; j++) *(f32x4_t *)panel_at(panel, l16, j * 4 + kq) = acc_read4(acc[j][i]);
+        for (int j = 0; j < 8; j++) panel_put_acc(panel, l16, j * 4 + kq, acc[j][i]);
+        panel_written();
+        f32x4_t v[8];
+#pragma unroll
+        for (int it = 0; it < 8; it++) v[it] = panel_get(panel, it * 2 + (lane >> 5), lane & 31);
+        panel_wait(v);
 #pragma unroll
         for (int it = 0; it < 8; it++) {
-            const int row = it * 2 + (lane >> 5);
-            f32x4_t v = *(const f32x4_t *)panel_at(panel, row, lane & 31);
             if (EPI == EPI_RESIDUAL) {
                 const f32x4_t xv = __builtin_bit_cast(f32x4_t, x[i % XD][it]);
 #pragma unroll
-                for (int e = 0; e < 4; e++) v[e] += xv[e];
+                for (int e = 0; e < 4; e++) v[it][e] += xv[e];
             }
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4_t, v), c_rsrc, voff + (i * 8 + it) * r2, 0, 0);
         }
         if (EPI == EPI_RESIDUAL && i + XD < 8) load_x(x[i % XD], i + XD);
+#pragma unroll
+        for (int it = 0; it < 8; it++)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4_t, v[it]), c_rsrc, voff, (i * 8 + it) * r2, 0);
     }
 }
 
-template <int EPI, bool KB, bool UB = false>
+// f(integral_constant<int, i>) for every i of the sequence
+template <typename F, int... I>
+__device__ __forceinline__ void for_each_index(F f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// One MFMA that adds to its sums in place, and one that starts them.
+__device__ __forceinline__ void mfma_add(f32x4_t &c, const bf16x8_t &a, const bf16x8_t &b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_start(f32x4_t &c, const bf16x8_t &a, const bf16x8_t &b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
+}
+template <int EPI, bool KB>
 __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -267,7 +337,8 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     const int n_items = n_tiles * p.splits;
     const int K = p.K;
     const int nh = K / HK / p.splits;            // half tiles per item; even: the host sees to it
-    int item = blockIdx.x;
+    int item = blockIdx.x, grid = (int)gridDim.x;
+    asm volatile("" : "+s"(grid));           // (kept in a register: else read from memory again at every tile)
     if (item >= n_items || (nh & 1) || nh < 8) return;      // (the host never launches such a K)
 
     // ---- load cursor -------------------------------------------------------------------------------------
@@ -285,7 +356,8 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     // distance of consecutive half tiles: 64 bytes along the row, or one 32-column block of all rows
     const unsigned a_half = KB ? (unsigned)p.a_rows * 64u : 64u, w_half = WKB ? (unsigned)p.w_rows * 64u : 64u;
     __amdgpu_buffer_rsrc_t a_rsrc, w_rsrc;
-    int ld_item, ld_h;
+    int ld_item;
+    unsigned a_soff, w_soff;
     int nx_tm, nx_tn, nx_split;
     auto setup_load = [&](int it) {
         int tm, tn;
@@ -308,24 +380,29 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
             else w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(Wp + (size_t)(n - seg * p.segN) * K + w_k0), (short)0, tile_bytes, 0x00020000);
         }
         ld_item = it;
-        ld_h = 0;
+        a_soff = w_soff = 0;
         nx_tm = tm; nx_tn = tn; nx_split = split;
     };
-    // instruction pair i (0..3) of the cursor's half tile into LDS stage `stage`
-    auto dma = [&](int stage, int i) {
-        char *base = lds + stage * STAGE + wave * 4096 + i * 1024;
-        const int blk = i * 16 * row_bytes, w_blk = i * 16 * w_row_bytes;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)base, 16, a_thread_off, (int)((unsigned)ld_h * a_half) + blk, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(base + REGION), 16, w_thread_off, (int)((unsigned)ld_h * w_half) + w_blk, 0, 0);
-    };
-    // next half tile, else the next item's first, else stay (the last half tile is fetched again, never used)
-    auto advance = [&]() {
-        ld_h++;
-        if (ld_h == nh) {
-            const int nxt = ld_item + (int)gridDim.x;
-            if (nxt < n_items) setup_load(nxt);
-            else ld_h--;
+    // piece i (0..3: activations, 4..7: weights) of the cursor's half tile into the stage at byte `st`; in the k-blocked layout
+    // the instruction's own offset moves both the address in memory and the one in LDS
+    auto dma = [&](auto i_c, int st) {
+        constexpr int i = decltype(i_c)::value, q = i & 3;
+        char *base = lds + st + wave * 4096 + (i < 4 ? 0 : REGION);
+        if (i < 4) {
+            if (KB) __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)base, 16, a_thread_off, (int)a_soff, q * 1024, 0);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)(base + q * 1024), 16, a_thread_off, (int)a_soff + q * 16 * row_bytes, 0, 0);
+        } else {
+            if (KB) __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)base, 16, w_thread_off, (int)w_soff, q * 1024, 0);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(base + q * 1024), 16, w_thread_off, (int)w_soff + q * 16 * w_row_bytes, 0, 0);
         }
+        if (i == 7) { a_soff += a_half; w_soff += w_half; }
+    };
+    // the item's half tiles have all been issued: on to the next item; behind the last one the same half tiles are fetched again
+    // (never used)
+    auto next_item = [&]() {
+        const int nxt = ld_item + grid;
+        if (nxt < n_items) setup_load(nxt);
+        else a_soff = w_soff = 0;
     };
 
     // ---- fragments -----------------------------------------------------------------------------------------
@@ -335,211 +412,83 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     const int w_base = lds0 + REGION + (wn * 128 + l16) * 64 + ((kq ^ fsw) << 4);
     f32x4_t acc[8][8];                  // [weight block][activation block]
     bf16x8_t af[2][8], wf[2][8];
-#pragma unroll
-    for (int b = 0; b < 2; b++)
-#pragma unroll
-        for (int i = 0; i < 8; i++)
-#pragma unroll
-            for (int e = 0; e < 8; e++) { af[b][i][e] = (bf16_t)0.f; wf[b][i][e] = (bf16_t)0.f; }
-    auto zero_acc = [&]() {
-#pragma unroll
-        for (int j = 0; j < 8; j++)
-#pragma unroll
-            for (int i = 0; i < 8; i++)
-#pragma unroll
-                for (int r = 0; r < 4; r++) acc[j][i][r] = 0.f;
-    };
-    zero_acc();
 
 #define VLA_SB() __builtin_amdgcn_sched_barrier(0)
-#define VLA_Q(n) std::integral_constant<int, n> {}
-    // group q (0..15): fragment reads into buffer B and four MFMAs from buffer B ^ 1 (weight block q / 2,
-    // activation blocks 4 (q % 2) .. + 3).  Fragment f (0..15; even: weight block f / 2, odd: activation block
-    // f / 2) is read in group f / 2 for f < 8 and in group f - 4 after that: all reads are issued by group 11,
-    // so that the last sixteen MFMAs cover their latency before the end-of-iteration wait.
-    auto read_frag = [&](auto b_c, auto f_c, int soff) {
-        constexpr int B = decltype(b_c)::value, f = decltype(f_c)::value;
-        constexpr int blk = f >> 1;
-        if (f & 1) af[B][blk] = lds_read<blk * 1024>(a_base + soff);
-        else wf[B][blk] = lds_read<blk * 1024>(w_base + soff);
-    };
-    auto group = [&](auto b_c, auto q_c, int soff) {
-        constexpr int B = decltype(b_c)::value, q = decltype(q_c)::value;
-        if (q < 4) {
-            read_frag(b_c, std::integral_constant<int, (q < 4 ? 2 * q : 0)>{}, soff);
-            read_frag(b_c, std::integral_constant<int, (q < 4 ? 2 * q + 1 : 0)>{}, soff);
-        } else if (q < 12) {
-            read_frag(b_c, std::integral_constant<int, (q >= 4 && q < 12 ? q + 4 : 0)>{}, soff);
-        }
-        constexpr int j = q >> 1, i0 = (q & 1) * 4;
-#pragma unroll
-        for (int i = i0; i < i0 + 4; i++)
-            acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[B ^ 1][j], af[B ^ 1][i], acc[j][i], 0, 0, 0);
-    };
-    // this wave's fragment reads have landed; the fragments pass through so that no MFMA moves above the wait
-    auto wait_frags = [&](int B) {
+    // Iteration: reads half tile g (stage at byte `rd`) into fragment buffer B, multiplies half tile g - 1 from the other buffer
+    // (MUL 0: nothing to multiply yet, 1: add, 2: start the sums) and issues the eight loads of the cursor's half tile
+    // into the stage at byte `to`.
+    auto iteration = [&](auto b_c, auto mul_c, int rd, int to) {
+        constexpr int B = decltype(b_c)::value, MUL = decltype(mul_c)::value;
+        const int va = a_base + rd, vw = w_base + rd;
+        for_each_index([&](auto m_c) {
+            constexpr int m = decltype(m_c)::value, j = m >> 3, i = m & 7;
+            if constexpr (MUL == 1) mfma_add(acc[j][i], wf[B ^ 1][j], af[B ^ 1][i]);
+            if constexpr (MUL == 2) mfma_start(acc[j][i], wf[B ^ 1][j], af[B ^ 1][i]);
+            VLA_SB();
+            if constexpr (m % 2 == 0 && m < 32) {        // fragment m / 2: weight blocks and activation blocks in turn
+                constexpr int f = m / 2, blk = f >> 1;
+                if constexpr (f & 1) af[B][blk] = lds_read<blk * 1024>(va);
+                else wf[B][blk] = lds_read<blk * 1024>(vw);
+                VLA_SB();
+            }
+            if constexpr (m % 8 == 1) {
+                dma(std::integral_constant<int, m / 8>{}, to);
+                VLA_SB();
+            }
+        }, std::make_integer_sequence<int, 64>{});
+        // this wave's fragment reads have landed; the fragments pass through so that no MFMA moves above the wait
         asm volatile("s_waitcnt lgkmcnt(0)"
                      : "+v"(af[B][0]), "+v"(af[B][1]), "+v"(af[B][2]), "+v"(af[B][3]), "+v"(af[B][4]), "+v"(af[B][5]),
                        "+v"(af[B][6]), "+v"(af[B][7]), "+v"(wf[B][0]), "+v"(wf[B][1]), "+v"(wf[B][2]), "+v"(wf[B][3]),
                        "+v"(wf[B][4]), "+v"(wf[B][5]), "+v"(wf[B][6]), "+v"(wf[B][7]));
+        VLA_SB();
     };
-    // iteration g of the workgroup's half-tile stream: reads half tile g into buffer b, multiplies half tile
-    // g - 1 from the other buffer, and (unless `defer`) issues the loads of half tile g + 3
-    auto iteration = [&](auto b_c, int g, bool defer) {
-        const int soff = (g & 3) * STAGE, sn = (g + 3) & 3;
-        // vmcnt counts in issue order: at most the 16 load instructions of half tiles g + 1 and g + 2 may still be
-        // in flight (right after an epilogue this also waits for the epilogue's own stores)
-        asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        asm volatile("s_barrier" ::: "memory");   // everyone's loads of g have landed, everyone's reads of g - 1 are done
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    int s0 = 0, s1 = STAGE, s2 = 2 * STAGE, s3 = 3 * STAGE, s4 = 4 * STAGE;   // stages of half tiles g .. g + 4, g the pair's first
+    // the pair's two half tiles have landed: at most the eight loads of g + 2 may still be in flight (vmcnt counts in issue
+    // order; right after an epilogue this also waits for its stores)
+    auto arrive = [&]() {
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         VLA_SB();
-        group(b_c, VLA_Q(0), soff); VLA_SB();
-        group(b_c, VLA_Q(1), soff); VLA_SB();
-        if (!defer) dma(sn, 0);
-        VLA_SB();
-        group(b_c, VLA_Q(2), soff); VLA_SB();
-        group(b_c, VLA_Q(3), soff); VLA_SB();
-        group(b_c, VLA_Q(4), soff); VLA_SB();
-        group(b_c, VLA_Q(5), soff); VLA_SB();
-        if (!defer) dma(sn, 1);
-        VLA_SB();
-        group(b_c, VLA_Q(6), soff); VLA_SB();
-        group(b_c, VLA_Q(7), soff); VLA_SB();
-        group(b_c, VLA_Q(8), soff); VLA_SB();
-        group(b_c, VLA_Q(9), soff); VLA_SB();
-        if (!defer) dma(sn, 2);
-        VLA_SB();
-        group(b_c, VLA_Q(10), soff); VLA_SB();
-        group(b_c, VLA_Q(11), soff); VLA_SB();
-        group(b_c, VLA_Q(12), soff); VLA_SB();
-        group(b_c, VLA_Q(13), soff); VLA_SB();
-        if (!defer) { dma(sn, 3); advance(); }
-        VLA_SB();
-        group(b_c, VLA_Q(14), soff); VLA_SB();
-        group(b_c, VLA_Q(15), soff); VLA_SB();
-        wait_frags(decltype(b_c)::value);
-        VLA_SB();
+    };
+    auto first_half = [&](auto mul_c) { iteration(I0{}, mul_c, s0, s3); };
+    auto second_half = [&](auto mul_c) {
+        iteration(I1{}, mul_c, s1, s4);
+        const int t0 = s0, t1 = s1;
+        s0 = s2; s1 = s3; s2 = s4; s3 = t0; s4 = t1;
     };
 
-    using B0 = std::integral_constant<int, 0>;
-    using B1 = std::integral_constant<int, 1>;
-    if constexpr (UB) {
-        // Unit-barrier schedule: one wait and one barrier per pair of half tiles.  At the start of even iteration g
-        // half tiles g and g + 1 have landed and every wave has finished reading g - 2 and g - 1, whose stages take
-        // the loads of g + 2 and g + 3, all issued during iteration g.
-        auto iteration_ub = [&](auto b_c, int g, bool defer) {
-            constexpr int B = decltype(b_c)::value;
-            const int soff = (g & 3) * STAGE, s2 = (g + 2) & 3, s3 = (g + 3) & 3;
-            if (B == 0) {
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                asm volatile("s_barrier" ::: "memory");
-            }
-            VLA_SB();
-            group(b_c, VLA_Q(0), soff); VLA_SB();
-            group(b_c, VLA_Q(1), soff); VLA_SB();
-            if (B == 0 && !defer) dma(s2, 0);
-            VLA_SB();
-            group(b_c, VLA_Q(2), soff); VLA_SB();
-            group(b_c, VLA_Q(3), soff); VLA_SB();
-            if (B == 0 && !defer) dma(s2, 1);
-            VLA_SB();
-            group(b_c, VLA_Q(4), soff); VLA_SB();
-            group(b_c, VLA_Q(5), soff); VLA_SB();
-            if (B == 0 && !defer) dma(s2, 2);
-            VLA_SB();
-            group(b_c, VLA_Q(6), soff); VLA_SB();
-            group(b_c, VLA_Q(7), soff); VLA_SB();
-            if (B == 0 && !defer) { dma(s2, 3); advance(); }
-            VLA_SB();
-            group(b_c, VLA_Q(8), soff); VLA_SB();
-            group(b_c, VLA_Q(9), soff); VLA_SB();
-            if (B == 0 && !defer) dma(s3, 0);
-            VLA_SB();
-            group(b_c, VLA_Q(10), soff); VLA_SB();
-            group(b_c, VLA_Q(11), soff); VLA_SB();
-            if (B == 0 && !defer) dma(s3, 1);
-            VLA_SB();
-            group(b_c, VLA_Q(12), soff); VLA_SB();
-            group(b_c, VLA_Q(13), soff); VLA_SB();
-            if (B == 0 && !defer) dma(s3, 2);
-            VLA_SB();
-            group(b_c, VLA_Q(14), soff); VLA_SB();
-            group(b_c, VLA_Q(15), soff); VLA_SB();
-            if (B == 0 && !defer) { dma(s3, 3); advance(); }
-            VLA_SB();
-            wait_frags(B);
-            VLA_SB();
-        };
-        setup_load(item);
-        int tm = nx_tm, tn = nx_tn, split = nx_split;
-#pragma unroll
-        for (int d = 0; d < 2; d++) {
-#pragma unroll
-            for (int i = 0; i < 4; i++) dma(d, i);
-            advance();
-        }
-        const int n_mine = (n_items - item + (int)gridDim.x - 1) / (int)gridDim.x;
-        const int g_end = n_mine * nh;
-        int next_done = nh;
-        for (int g = 0;; g += 2) {
-            const bool boundary = (g == next_done);
-            iteration_ub(B0{}, g, boundary && g != g_end);
-            if (boundary) {
-                asm volatile("s_barrier" ::: "memory");
-                acc_settle();
-                float *panel = (float *)(lds + (g & 3) * STAGE) + wave * (16 * 128);
-                epilogue<EPI, KB>(acc, p, tm * BM, tn, wm, wn, lane, panel, (size_t)split * p.M * p.N);
-                if (g == g_end) break;
-                zero_acc();
-                // the loads this boundary iteration held back (half tiles g + 2 and g + 3, both of the next item)
-#pragma unroll
-                for (int i = 0; i < 4; i++) dma((g + 2) & 3, i);
-                advance();
-#pragma unroll
-                for (int i = 0; i < 4; i++) dma((g + 3) & 3, i);
-                advance();
-                tm = nx_tm; tn = nx_tn; split = nx_split;
-                next_done += nh;
-            }
-            iteration_ub(B1{}, g + 1, false);
-        }
-    } else {
     setup_load(item);
     int tm = nx_tm, tn = nx_tn, split = nx_split;
-#pragma unroll
-    for (int d = 0; d < 3; d++) {
-#pragma unroll
-        for (int i = 0; i < 4; i++) dma(d, i);
-        advance();
-    }
-    // Half tile h of the workgroup's n-th item is stream element g = n * nh + h; it is read in iteration g and
-    // multiplied in iteration g + 1, so an item is complete after the first iteration of the next one (or after
-    // one extra iteration at the end of the stream).  nh is even, so that iteration is always an even one.
-    int n_mine = (n_items - item + (int)gridDim.x - 1) / (int)gridDim.x;
-    const int g_end = n_mine * nh;
-    int next_done = nh;                          // the even iteration after which the current item is complete
-    for (int g = 0;; g += 2) {
-        const bool boundary = (g == next_done);
-        iteration(B0{}, g, boundary && g != g_end);
-        if (boundary) {
-            // every wave is done reading stage g % 4: it becomes the panel
-            asm volatile("s_barrier" ::: "memory");
-            acc_settle();
-            float *panel = (float *)(lds + (g & 3) * STAGE) + wave * (16 * 128);
-            epilogue<EPI, KB>(acc, p, tm * BM, tn, wm, wn, lane, panel, (size_t)split * p.M * p.N);
-            if (g == g_end) break;
-            zero_acc();
-            tm = nx_tm; tn = nx_tn; split = nx_split;   // the cursor moved on to the next item four iterations ago
-            next_done += nh;
-            const int sn = (g + 3) & 3;          // the loads this boundary iteration held back
-#pragma unroll
-            for (int i = 0; i < 4; i++) dma(sn, i);
-            advance();
+    for (int s = 0; s < 3; s++) for_each_index([&](auto i_c) { dma(i_c, s * STAGE); }, std::make_integer_sequence<int, 8>{});
+    // Half tile h of the workgroup's n-th item is stream element g = n * nh + h; it is read in iteration g and multiplied in
+    // iteration g + 1, so an item is complete after the first iteration of the next one (behind the last item: of the half tiles
+    // fetched again).  nh is even, so that iteration is always a pair's first.
+    const int np = nh / 2;
+    arrive();
+    first_half(I0{});
+    for (;;) {
+        second_half(I2{});
+        for (int pr = 1; pr < np; pr++) {
+            arrive();
+            first_half(I1{});
+            if (pr == np - 2) next_item();           // the cursor is four half tiles ahead in a pair's second half
+            second_half(I1{});
         }
-        iteration(B1{}, g + 1, false);
+        item += grid;
+        arrive();
+        first_half(I1{});
+        // every wave is done reading stage s0: it becomes the panel
+        asm volatile("s_barrier" ::: "memory");
+        acc_settle();
+        epilogue<EPI, KB>(acc, p, tm * BM, tn, wm, wn, lane, (float *)(lds + s0) + wave * (16 * 128), (size_t)split * p.M * p.N);
+        if (item >= n_items) break;
+        tm = nx_tm; tn = nx_tn; split = nx_split;
     }
-    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // no load may reach the LDS after the workgroup's end
 }
 
 
@@ -777,6 +726,7 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
                     *(f32x4_t *)gp = g;
                 }
             }
+            panel_written();
             swiglu_block_out<KB>(p, pb, mblock, tn * 64, lane);
         } else {
             constexpr int LPR = BNT / 4, RPI = 64 / LPR;      // lanes per row, rows per instruction
@@ -799,13 +749,13 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
     }
 }
 
-template <int EPI, bool KB, bool UB = false>
+template <int EPI, bool KB>
 int launch_plain(const DmaGemmParams &p, hipStream_t st) {
     static bool attr_set = false;
     static int n_cu = 0;
     const size_t lds = NSTAGES * (size_t)STAGE;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_dma_kernel<EPI, KB, UB>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_dma_kernel<EPI, KB>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) {
             vla_set_error("hipFuncSetAttribute(gemm_bf16_dma) failed: %s", hipGetErrorString(e));
             return VLA_EHIP;
@@ -818,22 +768,22 @@ int launch_plain(const DmaGemmParams &p, hipStream_t st) {
         }
         attr_set = true;
     }
-    // one workgroup per CU (128 KB of LDS, 512 registers per lane); blockIdx % 8 is the XCD, and a stride of a
+    // one workgroup per CU (160 KB of LDS, 512 registers per lane); blockIdx % 8 is the XCD, and a stride of a
     // multiple of 8 keeps every workgroup's items on its own XCD's share of the tile order
     const int n_items = p.tiles_m * p.tiles_n * p.splits;
     int grid = n_items;
     if (n_cu % 8 == 0 && n_items > n_cu) grid = n_cu;
-    gemm_bf16_dma_kernel<EPI, KB, UB><<<grid, 256, lds, st>>>(p);
+    gemm_bf16_dma_kernel<EPI, KB><<<grid, 256, lds, st>>>(p);
     int rc = vla_check_launch("gemm_bf16_dma");
     return rc ? rc : 1;
 }
 
-template <int EPI, bool KB, bool UB = false>
+template <int EPI, bool KB>
 int launch(const DmaGemmParams &p, hipStream_t st) {
     const double flops = 2.0 * p.M * p.K * (EPI == EPI_SWIGLU ? 2.0 * p.N : (double)p.N);
     ProfScope ps(EPI == EPI_SWIGLU ? "gemm_bf16_dma<swiglu>" : EPI == EPI_RESIDUAL ? "gemm_bf16_dma<residual>"
                  : EPI == EPI_QKV_ROPE ? "gemm_bf16_dma<qkv_rope>" : "gemm_bf16_dma<store>", flops, st);
-    return launch_plain<EPI, KB, UB>(p, st);
+    return launch_plain<EPI, KB>(p, st);
 }
 
 template <int EPI, bool KB, bool WKB, int BMT, int BNT, int NS, bool STEP>
@@ -859,18 +809,18 @@ int launch_small(DmaGemmParams p, hipStream_t st) {
 // Which kernel takes a product of M rows, N columns (tile columns are 128 weight rows; SwiGLU counts gate and up) and K:
 // 0 the 256 x 256 one, else a small tile.  All give the same bits; the rule compares estimates in ns, fitted to what the
 // four projections of the 7B shape took at 64 .. 6912 rows (per unit of K = 64 and launch):
-//   256 x 256       a round of 256 tiles 1350 per unit + 8000 (prologue and epilogue)
+//   256 x 256       a round of 256 tiles 1190 per unit + 8000 (prologue and epilogue)
 //   64 x 64         310 up to 150 tiles, then 120 + 1.25 per tile (plain and residual outputs only)
 //   64 x 128        470 up to 276 tiles, then 1.7 per tile (SwiGLU, two weight panels per tile: 620, at least 1000)
 //   128 x 128       640 with one workgroup per CU (3 stages of LDS), 950 for every 512 with two (2 stages)
-// E.g. 288 rows, K = 4096: QKV 99 -> 55 us, O 89 -> 33, gate/up 109 -> 100, down (K = 11008) 217 -> 79; 1728 rows: O 96 -> 71.
+// E.g. 288 rows, K = 4096: QKV 86 -> 55 us, O 76 -> 33, down (K = 11008) 190 -> 79; gate/up 86 with 256 x 256, 100 with 64 x 128.
 enum SmallTile { TILE_256 = 0, TILE_64x64, TILE_64x128, TILE_128x128_1, TILE_128x128_2 };
 template <int EPI>
 SmallTile choose_tile(const DmaGemmParams &p) {
     const long units = p.K / 64, cols = EPI == EPI_SWIGLU ? 2L * p.N : p.N;
     const long t256 = (p.M + 255L) / 256 * (cols / 256), t64 = (p.M + 63L) / 64 * (cols / 128), t128 = (p.M + 127L) / 128 * (cols / 128);
     SmallTile best = TILE_256;
-    long best_ns = (t256 + 255) / 256 * (1350 * units + 8000);
+    long best_ns = (t256 + 255) / 256 * (1190 * units + 8000);
     auto offer = [&](SmallTile tile, long ns) {
         if (ns < best_ns) { best = tile; best_ns = ns; }
     };
@@ -899,12 +849,6 @@ template <int EPI>
 int launch_kb(const DmaGemmParams &p, bool kb, hipStream_t st) {
     const SmallTile tile = choose_tile<EPI>(p);
     if (tile != TILE_256) return kb ? launch_tile<EPI, true>(p, tile, st) : launch_tile<EPI, false>(p, tile, st);
-    // The unit-barrier schedule pays for the gate/up projection (3.7 % faster at M = 73728: 10.03 against 10.41 ms);
-    // the QKV and down projections run the same with either and the O projection, whose short tiles end in the
-    // heaviest epilogue, 5 % slower.
-    if constexpr (EPI == EPI_SWIGLU) {
-        if (kb) return launch<EPI, true, true>(p, st);
-    }
     return kb ? launch<EPI, true>(p, st) : launch<EPI, false>(p, st);
 }
 
