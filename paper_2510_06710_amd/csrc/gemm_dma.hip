@@ -31,10 +31,12 @@
 // The fragment reads, and the MFMAs with them, are inline assembly with explicit waits: the compiler would otherwise wait for
 // every outstanding LDS-bound load before any LDS read, and copies the accumulators where two paths meet.
 //
-// Operand layout.  Row-major operands are fetched as 64-byte pieces of 16 rows per instruction, i.e. half
-// cache lines; in the k-blocked layout (KB: [K / 32][rows][32] for the activations and for repacked weights)
-// a half tile of 256 rows is one contiguous 16 KB block and every instruction reads 1 KB of whole lines,
-// which is worth about 10 % of the kernel's time.  The SwiGLU output is then written k-blocked as well.
+// Operand layout.  In the k-blocked layout (KB: [K / 32][rows][32] for the activations and for repacked weights) a half tile
+// of 256 rows is one contiguous 16 KB block and every instruction reads 1 KB of whole lines; the SwiGLU output is then written
+// k-blocked as well.  Row-major operands are fetched as whole 128-byte lines too, 8 rows an instruction: a stage then holds both
+// half tiles of a pair for half of the tile's rows instead of one half tile of all rows.  (As 64-byte pieces of 16 rows, streaming
+// alone runs at 46-53 GB/s per CU where lines reach 65-84.  9,408 rows, fp32 output: 940 -> 817 us on average over the
+// gradient products of the 7B shape.)
 //
 // One workgroup per CU walks its tiles in turn (tile i of a workgroup = id + grid * i, which keeps the
 // XCD-contiguous tile order); the half-tile stream simply continues into the next tile, so that only the
@@ -73,8 +75,6 @@ struct DmaGemmParams {
     int splits;      // > 1: K is cut into `splits` equal ranges; item = range * tiles + tile, and range r of an
                      // EPI_STORE launch writes its fp32 partial product to C + r * M * N
     int parts;       // small tiles of a decode step: the parts of K whose sums are added in order (gemm_decode_parts)
-    int wkb;         // row-major activations with k-blocked (repacked) weights: the decode forwards, whose weight
-                     // stream comes from HBM and then moves as whole cache lines (w_rows as in the k-blocked layout)
 };
 
 template <int OFF>
@@ -231,26 +231,26 @@ __device__ __forceinline__ void swiglu_block_out(const DmaGemmParams &p, float *
 // Output of one wave.  Per 16-row activation block i a lane holds row (lane % 16) and, per weight block j
 // and register r, column 16 j + 4 (lane / 16) + r.  Each block goes through the panel and leaves as whole
 // rows.
-template <int EPI, bool KB>
-__device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][8], const DmaGemmParams &p, int m0, int tn, int wm, int wn,
+template <int EPI, bool KB, int MB>
+__device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][MB], const DmaGemmParams &p, int m0, int tn, int wn,
                                          int lane, float *panel, size_t c_off) {
     const int l16 = lane & 15, kq = lane >> 4;
     if (EPI == EPI_QKV_ROPE) {
         const int n0 = tn * BN + wn * 128;
 #pragma unroll
-        for (int i = 0; i < 8; i++) {
+        for (int i = 0; i < MB; i++) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < 8; j++) panel_put_acc(panel, l16, j * 4 + kq, acc[j][i]);
             panel_written();
-            qkv_block_out(p, panel, m0 + wm * 128 + i * 16, n0, lane);
+            qkv_block_out(p, panel, m0 + i * 16, n0, lane);
         }
         return;
     }
     if (EPI == EPI_SWIGLU) {
         // weight blocks 0..3 are gate rows, 4..7 the matching up rows: 64 output columns per wave
 #pragma unroll
-        for (int i = 0; i < 8; i++) {
+        for (int i = 0; i < MB; i++) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < 4; j++) {
@@ -261,16 +261,16 @@ __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][8], const DmaGemmPara
                 panel_put(panel, l16, j * 4 + kq, v);
             }
             panel_written();
-            swiglu_block_out<KB>(p, panel, m0 + wm * 128 + i * 16, tn * 128 + wn * 64, lane);
+            swiglu_block_out<KB>(p, panel, m0 + i * 16, tn * 128 + wn * 64, lane);
         }
         return;
     }
     // fp32 store, or read-modify-write of the fp32 residual stream: whole 512-byte rows, two rows per instruction,
-    // through a buffer descriptor over this wave's 128 x 128 block (rows past M fall outside it: their loads
+    // through a buffer descriptor over this wave's block (rows past M fall outside it: their loads
     // return zero and their stores are dropped, so no clamp and no predicate).  x is read XD 16-row blocks ahead of
     // the block being staged, so that a memory latency is paid once per tile and not once per block.
-    const int rows_in = min(128, p.M - (m0 + wm * 128));
-    float *wave_out = (float *)p.C + c_off + (size_t)(m0 + wm * 128) * p.N + (size_t)tn * BN + wn * 128;
+    const int rows_in = min(16 * MB, p.M - m0);
+    float *wave_out = (float *)p.C + c_off + (size_t)m0 * p.N + (size_t)tn * BN + wn * 128;
     __amdgpu_buffer_rsrc_t c_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)wave_out, (short)0, rows_in > 0 ? rows_in * p.N * 4 : 0, 0x00020000);
     const int voff = ((lane >> 5) * p.N + (lane & 31) * 4) * 4;
     const int row2 = 2 * p.N * 4;                      // bytes between the row pairs of consecutive instructions
@@ -289,7 +289,7 @@ __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][8], const DmaGemmPara
         for (int i = 0; i < XD; i++) load_x(x[i], i);
     }
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
+    for (int i = 0; i < MB; i++) {
         __builtin_amdgcn_sched_barrier(0);
         int r2 = row2;
         asm volatile("" : "+s"(r2));
@@ -308,7 +308,7 @@ __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][8], const DmaGemmPara
                 for (int e = 0; e < 4; e++) v[it][e] += xv[e];
             }
         }
-        if (EPI == EPI_RESIDUAL && i + XD < 8) load_x(x[i % XD], i + XD);
+        if (EPI == EPI_RESIDUAL && i + XD < MB) load_x(x[i % XD], i + XD);
 #pragma unroll
         for (int it = 0; it < 8; it++)
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4_t, v[it]), c_rsrc, voff, (i * 8 + it) * r2, 0);
@@ -328,9 +328,16 @@ __device__ __forceinline__ void mfma_add(f32x4_t &c, const bf16x8_t &a, const bf
 __device__ __forceinline__ void mfma_start(f32x4_t &c, const bf16x8_t &a, const bf16x8_t &b) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
 }
-template <int EPI, bool KB>
+template <int N>
+__device__ __forceinline__ void pass_frags(bf16x8_t (&f)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; i++) asm volatile("" : "+v"(f[i]));
+}
+
+template <int EPI, bool KB, bool WKB, int MB>
 __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    constexpr int ROWS = 32 * MB, NA = (MB + 1) / 2, NL = NA + 4;     // tile rows; load instructions per wave and half tile
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const int n_tiles = p.tiles_m * p.tiles_n;
@@ -342,19 +349,24 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     if (item >= n_items || (nh & 1) || nh < 8) return;      // (the host never launches such a K)
 
     // ---- load cursor -------------------------------------------------------------------------------------
-    // A wave instruction covers 16 tile rows: lane l -> row l / 4, position l % 4 of the 64-byte row, which
-    // holds chunk (l % 4) ^ ((row / 2) % 4).  This wave loads tile rows wave * 64 .. + 63 of both operands, four
-    // instructions each; SwiGLU tiles interleave 64 gate and 64 up rows per wave of the multiply side, so
-    // loading wave w takes 64 rows of W0 (w even) or W1 (w odd).
-    const int chunk_off = ((lane & 3) ^ ((lane >> 3) & 3)) << 4;
-    const bool WKB = KB ? true : (p.wkb != 0);   // the weights' layout (a compile-time constant in the k-blocked kernels)
-    const int row_bytes = KB ? 64 : K * 2;       // distance of consecutive tile rows of one half tile
-    const int w_row_bytes = WKB ? 64 : K * 2;
-    const int a_thread_off = (wave * 64 + (lane >> 2)) * row_bytes + chunk_off;
-    const int w_thread_off = (((EPI == EPI_SWIGLU) ? (wave >> 1) * 64 : wave * 64) + (lane >> 2)) * w_row_bytes + chunk_off;
-    const int tile_bytes = BM * K * 2;
-    // distance of consecutive half tiles: 64 bytes along the row, or one 32-column block of all rows
-    const unsigned a_half = KB ? (unsigned)p.a_rows * 64u : 64u, w_half = WKB ? (unsigned)p.w_rows * 64u : 64u;
+    // k-blocked: a stage holds one half tile, a wave instruction 16 tile rows of 64 bytes: lane l -> row l / 4, position l % 4
+    // of the row, which holds chunk (l % 4) ^ ((row / 2) % 4).  Row-major: a stage holds both half tiles of the tile rows
+    // (of either operand) that one half of the waves multiplies, an instruction 8 of them, a whole 128-byte line each: lane l
+    // -> row l / 8, position l % 8, which holds chunk (l % 8) ^ (row % 8).  Per stage a wave loads a quarter of the weight rows,
+    // four instructions, and 16 NA (8 NA) activation rows, for an odd MB more than the tile has.  SwiGLU tiles interleave 64
+    // gate and 64 up rows per half of the weight rows, so a wave's share comes from one of the two matrices.  Mixed (k-blocked
+    // weights, row-major activations): the weights' part of a stage is the two half tiles of 128 rows one behind the other, two
+    // waves load one of them each.
+    const int chunk_off = KB ? ((lane & 3) ^ ((lane >> 3) & 3)) << 4 : ((lane & 7) ^ (lane >> 3)) << 4;
+    const int row_bytes = KB ? 64 : K * 2;       // distance of consecutive tile rows
+    const int up = KB ? wave & 1 : wave >> 1;    // SwiGLU: which matrix this wave loads from, and which 64 (32) of its rows
+    const int a_thread_off = KB ? (wave * 16 * NA + (lane >> 2)) * 64 + chunk_off : (wave * 8 * NA + (lane >> 3)) * row_bytes + chunk_off;
+    const int w_part = EPI == EPI_SWIGLU ? (KB ? wave >> 1 : wave & 1) : wave;
+    const int w_thread_off = KB ? (w_part * 64 + (lane >> 2)) * 64 + chunk_off
+                             : WKB ? ((wave & 1) * 64 + (lane >> 2)) * 64 + (((lane & 3) ^ ((lane >> 3) & 3)) << 4) + (wave >> 1) * p.w_rows * 64
+                                   : (w_part * 32 + (lane >> 3)) * row_bytes + chunk_off;
+    // distance of what the cursor steps over: one 32-column block of all rows (mixed: two), or 128 bytes along the row
+    const unsigned a_step = KB ? (unsigned)p.a_rows * 64u : 128u, w_step = WKB ? (unsigned)p.w_rows * (KB ? 64u : 128u) : 128u;
     __amdgpu_buffer_rsrc_t a_rsrc, w_rsrc;
     int ld_item;
     unsigned a_soff, w_soff;
@@ -363,39 +375,44 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
         int tm, tn;
         const int split = __builtin_amdgcn_readfirstlane(it / n_tiles);
         vla_tile_of_block(it - split * n_tiles, p.tiles_m, p.tiles_n, tm, tn, p.group);
-        // first element of this item's K range within a row panel: k-blocked, whole 32-column blocks; row-major, columns
-        const size_t a_k0 = KB ? (size_t)split * nh * (a_half / 2) : (size_t)split * nh * HK;
-        const size_t w_k0 = WKB ? (size_t)split * nh * (w_half / 2) : (size_t)split * nh * HK;
-        if (KB) a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(p.A + (size_t)tm * BM * 32 + a_k0), (short)0, (int)((unsigned)(nh - 1) * a_half + 16384u), 0x00020000);
-        else a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(p.A + (size_t)tm * BM * K + a_k0), (short)0, tile_bytes, 0x00020000);
-        if (EPI == EPI_SWIGLU) {
-            const bf16_t *Wp = (wave & 1) ? p.W1 : p.W0;
-            if (WKB) w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(Wp + (size_t)(tn * 128) * 32 + w_k0), (short)0, (int)((unsigned)(nh - 1) * w_half + 8192u), 0x00020000);
-            else w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(Wp + (size_t)(tn * 128) * K + w_k0), (short)0, tile_bytes / 2, 0x00020000);
-        } else {
-            const int n = tn * BN;
-            const int seg = __builtin_amdgcn_readfirstlane(n / p.segN);
-            const bf16_t *Wp = seg == 0 ? p.W0 : (seg == 1 ? p.W1 : p.W2);
-            if (WKB) w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(Wp + (size_t)(n - seg * p.segN) * 32 + w_k0), (short)0, (int)((unsigned)(nh - 1) * w_half + 16384u), 0x00020000);
-            else w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(Wp + (size_t)(n - seg * p.segN) * K + w_k0), (short)0, tile_bytes, 0x00020000);
+        const bf16_t *Wp;
+        int w_row;
+        if (EPI == EPI_SWIGLU) { Wp = up ? p.W1 : p.W0; w_row = tn * 128; }
+        else {
+            const int n = tn * BN, seg = __builtin_amdgcn_readfirstlane(n / p.segN);
+            Wp = seg == 0 ? p.W0 : (seg == 1 ? p.W1 : p.W2);
+            w_row = n - seg * p.segN;
         }
+        // (rows behind the activation buffer's last: the range check takes the scalar offset into account, those loads return zero)
+        const unsigned w_tile_rows = EPI == EPI_SWIGLU ? 128u : 256u;
+        if (KB) {            // first element of this item's K range: whole 32-column blocks
+            const unsigned avail = MB == 8 ? 256u : (unsigned)min(64 * NA, p.a_rows - tm * ROWS);
+            a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(p.A + (size_t)tm * ROWS * 32 + (size_t)split * nh * (a_step / 2)), (short)0, (int)((unsigned)(nh - 1) * a_step + avail * 64u), 0x00020000);
+        } else {             // ... columns
+            const unsigned k0 = (unsigned)split * nh * HK, avail = MB == 8 ? 256u : (unsigned)min(16 * MB + 32 * NA, p.a_rows - tm * ROWS);
+            a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(p.A + (size_t)tm * ROWS * K + k0), (short)0, (int)(avail * (unsigned)K * 2u - k0 * 2u), 0x00020000);
+            if (!WKB) w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(Wp + (size_t)w_row * K + k0), (short)0, (int)(w_tile_rows * (unsigned)K * 2u - k0 * 2u), 0x00020000);
+        }
+        if (WKB) w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(Wp + (size_t)w_row * 32 + (size_t)split * nh * p.w_rows * 32), (short)0, (int)((unsigned)(nh - 1) * p.w_rows * 64u + w_tile_rows * 64u), 0x00020000);
         ld_item = it;
         a_soff = w_soff = 0;
         nx_tm = tm; nx_tn = tn; nx_split = split;
     };
-    // piece i (0..3: activations, 4..7: weights) of the cursor's half tile into the stage at byte `st`; in the k-blocked layout
-    // the instruction's own offset moves both the address in memory and the one in LDS
-    auto dma = [&](auto i_c, int st) {
-        constexpr int i = decltype(i_c)::value, q = i & 3;
-        char *base = lds + st + wave * 4096 + (i < 4 ? 0 : REGION);
-        if (i < 4) {
-            if (KB) __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)base, 16, a_thread_off, (int)a_soff, q * 1024, 0);
-            else __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)(base + q * 1024), 16, a_thread_off, (int)a_soff + q * 16 * row_bytes, 0, 0);
+    // piece i (below NA: activations, then weights) of the cursor's next stage (row-major: of row half RH) into the stage at byte
+    // `st`.  In the k-blocked layout the instruction's own offset moves both the address in memory and the one in LDS.
+    auto dma = [&](auto i_c, auto rh_c, int st) {
+        constexpr int i = decltype(i_c)::value, q = i < NA ? i : i - NA, RH = decltype(rh_c)::value;
+        char *base = lds + st + (i < NA ? wave * (1024 * NA) : wave * 4096 + REGION);
+        if (KB) {
+            if (i < NA) __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)base, 16, a_thread_off, (int)a_soff, q * 1024, 0);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)base, 16, w_thread_off, (int)w_soff, q * 1024, 0);
         } else {
-            if (KB) __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)base, 16, w_thread_off, (int)w_soff, q * 1024, 0);
-            else __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(base + q * 1024), 16, w_thread_off, (int)w_soff + q * 16 * w_row_bytes, 0, 0);
+            constexpr int a_row = RH * 16 * MB + q * 8, w_row = RH * (EPI == EPI_SWIGLU ? 64 : 128) + q * 8;
+            if (i < NA) __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)(base + q * 1024), 16, a_thread_off, (int)a_soff + a_row * row_bytes, 0, 0);
+            else if (WKB) __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)base, 16, w_thread_off, (int)w_soff + RH * 128 * 64, q * 1024, 0);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(base + q * 1024), 16, w_thread_off, (int)w_soff + w_row * row_bytes, 0, 0);
         }
-        if (i == 7) { a_soff += a_half; w_soff += w_half; }
+        if (i == NL - 1 && (KB || RH == 1)) { a_soff += a_step; w_soff += w_step; }
     };
     // the item's half tiles have all been issued: on to the next item; behind the last one the same half tiles are fetched again
     // (never used)
@@ -406,64 +423,71 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     };
 
     // ---- fragments -----------------------------------------------------------------------------------------
-    const int l16 = lane & 15, kq = lane >> 4, fsw = (l16 >> 1) & 3;
+    // k-blocked: half tile h of a pair lies in its own stage, blocks of 16 rows 1 KB apart.  Row-major: both lie in the stage of the
+    // wave's row half, the chunks of the second 64 bytes behind those of the first, blocks 2 KB apart.
+    const int l16 = lane & 15, kq = lane >> 4;
     const int lds0 = (int)(size_t)(lds_void *)lds;
-    const int a_base = lds0 + (wm * 128 + l16) * 64 + ((kq ^ fsw) << 4);
-    const int w_base = lds0 + REGION + (wn * 128 + l16) * 64 + ((kq ^ fsw) << 4);
-    f32x4_t acc[8][8];                  // [weight block][activation block]
-    bf16x8_t af[2][8], wf[2][8];
+    const int kb_off = l16 * 64 + ((kq ^ ((l16 >> 1) & 3)) << 4), rm_off = l16 * 128 + ((kq ^ (l16 & 7)) << 4);
+    const int a_base = lds0 + (KB ? wm * 16 * MB * 64 + kb_off : rm_off), w_base = lds0 + REGION + (KB ? wn * 128 * 64 : 0) + (WKB ? kb_off : rm_off);
+    constexpr int A_BLK = KB ? 1024 : 2048, W_BLK = WKB ? 1024 : 2048;
+    f32x4_t acc[8][MB];                  // [weight block][activation block]
+    bf16x8_t af[2][MB], wf[2][8];
 
 #define VLA_SB() __builtin_amdgcn_sched_barrier(0)
-    // Iteration: reads half tile g (stage at byte `rd`) into fragment buffer B, multiplies half tile g - 1 from the other buffer
-    // (MUL 0: nothing to multiply yet, 1: add, 2: start the sums) and issues the eight loads of the cursor's half tile
-    // into the stage at byte `to`.
-    auto iteration = [&](auto b_c, auto mul_c, int rd, int to) {
+    // Iteration: reads half tile g, the pair's B-th (stages at bytes a_st, w_st), into fragment buffer B, multiplies half tile g - 1 from
+    // the other buffer (MUL 0: nothing to multiply yet, 1: add, 2: start the sums) and issues the cursor's loads into the
+    // stage at byte `to` (row-major: row half 1 of the next pair in a first half, row half 0 of the one after it in a second).
+    auto iteration = [&](auto b_c, auto mul_c, int a_st, int w_st, int to) {
         constexpr int B = decltype(b_c)::value, MUL = decltype(mul_c)::value;
-        const int va = a_base + rd, vw = w_base + rd;
+        constexpr int RSTEP = MB >= 5 ? 2 : 1, LSTEP = 8 * MB / NL / 2 * 2;
+        static_assert((7 + MB) * RSTEP < 8 * MB && 1 + LSTEP * (NL - 1) < 8 * MB, "reads and loads fit between the MFMAs");
+        const int va = (!KB && B == 1 ? a_base ^ 64 : a_base) + a_st, vw = (KB || B == 0 ? w_base : WKB ? w_base + 8192 : w_base ^ 64) + w_st;
         for_each_index([&](auto m_c) {
-            constexpr int m = decltype(m_c)::value, j = m >> 3, i = m & 7;
+            constexpr int m = decltype(m_c)::value, j = m / MB, i = m % MB;
             if constexpr (MUL == 1) mfma_add(acc[j][i], wf[B ^ 1][j], af[B ^ 1][i]);
             if constexpr (MUL == 2) mfma_start(acc[j][i], wf[B ^ 1][j], af[B ^ 1][i]);
             VLA_SB();
-            if constexpr (m % 2 == 0 && m < 32) {        // fragment m / 2: weight blocks and activation blocks in turn
-                constexpr int f = m / 2, blk = f >> 1;
-                if constexpr (f & 1) af[B][blk] = lds_read<blk * 1024>(va);
-                else wf[B][blk] = lds_read<blk * 1024>(vw);
+            if constexpr (m % RSTEP == 0 && m / RSTEP < 8 + MB) {        // weight and activation blocks in turn, the weights' rest last
+                constexpr int f = m / RSTEP, blk = f < 2 * MB ? f >> 1 : f - MB;
+                if constexpr (f < 2 * MB && (f & 1)) af[B][blk] = lds_read<blk * A_BLK>(va);
+                else wf[B][blk] = lds_read<blk * W_BLK>(vw);
                 VLA_SB();
             }
-            if constexpr (m % 8 == 1) {
-                dma(std::integral_constant<int, m / 8>{}, to);
+            if constexpr (m % LSTEP == 1 && m / LSTEP < NL) {
+                dma(std::integral_constant<int, m / LSTEP>{}, std::integral_constant<int, 1 - B>{}, to);
                 VLA_SB();
             }
-        }, std::make_integer_sequence<int, 64>{});
+        }, std::make_integer_sequence<int, 8 * MB>{});
         // this wave's fragment reads have landed; the fragments pass through so that no MFMA moves above the wait
-        asm volatile("s_waitcnt lgkmcnt(0)"
-                     : "+v"(af[B][0]), "+v"(af[B][1]), "+v"(af[B][2]), "+v"(af[B][3]), "+v"(af[B][4]), "+v"(af[B][5]),
-                       "+v"(af[B][6]), "+v"(af[B][7]), "+v"(wf[B][0]), "+v"(wf[B][1]), "+v"(wf[B][2]), "+v"(wf[B][3]),
-                       "+v"(wf[B][4]), "+v"(wf[B][5]), "+v"(wf[B][6]), "+v"(wf[B][7]));
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        pass_frags(af[B]);
+        pass_frags(wf[B]);
         VLA_SB();
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
-    int s0 = 0, s1 = STAGE, s2 = 2 * STAGE, s3 = 3 * STAGE, s4 = 4 * STAGE;   // stages of half tiles g .. g + 4, g the pair's first
-    // the pair's two half tiles have landed: at most the eight loads of g + 2 may still be in flight (vmcnt counts in issue
+    // s0, s1: the stages of the pair being read; s2, s3: of the next one; s4: the first of the one after that
+    int s0 = 0, s1 = STAGE, s2 = 2 * STAGE, s3 = 3 * STAGE, s4 = 4 * STAGE;
+    // the pair's two half tiles have landed: at most the NL loads of the third stage may still be in flight (vmcnt counts in issue
     // order; right after an epilogue this also waits for its stores)
     auto arrive = [&]() {
-        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         VLA_SB();
     };
-    auto first_half = [&](auto mul_c) { iteration(I0{}, mul_c, s0, s3); };
+    auto first_half = [&](auto mul_c) { iteration(I0{}, mul_c, KB || !wm ? s0 : s1, KB || !wn ? s0 : s1, s3); };
     auto second_half = [&](auto mul_c) {
-        iteration(I1{}, mul_c, s1, s4);
+        iteration(I1{}, mul_c, KB || wm ? s1 : s0, KB || wn ? s1 : s0, s4);
         const int t0 = s0, t1 = s1;
         s0 = s2; s1 = s3; s2 = s4; s3 = t0; s4 = t1;
     };
 
     setup_load(item);
     int tm = nx_tm, tn = nx_tn, split = nx_split;
-    for (int s = 0; s < 3; s++) for_each_index([&](auto i_c) { dma(i_c, s * STAGE); }, std::make_integer_sequence<int, 8>{});
+    for_each_index([&](auto i_c) { dma(i_c, I0{}, s0); }, std::make_integer_sequence<int, NL>{});
+    for_each_index([&](auto i_c) { dma(i_c, I1{}, s1); }, std::make_integer_sequence<int, NL>{});
+    for_each_index([&](auto i_c) { dma(i_c, I0{}, s2); }, std::make_integer_sequence<int, NL>{});
     // Half tile h of the workgroup's n-th item is stream element g = n * nh + h; it is read in iteration g and multiplied in
     // iteration g + 1, so an item is complete after the first iteration of the next one (behind the last item: of the half tiles
     // fetched again).  nh is even, so that iteration is always a pair's first.
@@ -475,16 +499,18 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
         for (int pr = 1; pr < np; pr++) {
             arrive();
             first_half(I1{});
-            if (pr == np - 2) next_item();           // the cursor is four half tiles ahead in a pair's second half
+            if (pr == np - 2) next_item();           // the cursor is two pairs ahead in a pair's second half
             second_half(I1{});
         }
         item += grid;
         arrive();
         first_half(I1{});
-        // every wave is done reading stage s0: it becomes the panel
-        asm volatile("s_barrier" ::: "memory");
+        // the staging panel: k-blocked, stage s0, which every wave is through with after one more barrier; row-major, where s0 holds
+        // the pair's second half tile as well, s4, free since the pair's barrier until its loads go out in the second half
+        if (KB) asm volatile("s_barrier" ::: "memory");
         acc_settle();
-        epilogue<EPI, KB>(acc, p, tm * BM, tn, wm, wn, lane, (float *)(lds + s0) + wave * (16 * 128), (size_t)split * p.M * p.N);
+        epilogue<EPI, KB, MB>(acc, p, tm * ROWS + wm * 16 * MB, tn, wn, lane, (float *)(lds + (KB ? s0 : s4)) + wave * (16 * 128), (size_t)split * p.M * p.N);
+        if (!KB) asm volatile("s_barrier" ::: "memory");
         if (item >= n_items) break;
         tm = nx_tm; tn = nx_tn; split = nx_split;
     }
@@ -496,12 +522,6 @@ template <int BASE, int STRIDE, int... I>
 __device__ __forceinline__ void read_frags(bf16x8_t (&f)[sizeof...(I)], int addr, std::integer_sequence<int, I...>) {
     ((f[I] = lds_read<BASE + I * STRIDE>(addr)), ...);
 }
-template <int N>
-__device__ __forceinline__ void pass_frags(bf16x8_t (&f)[N]) {
-#pragma unroll
-    for (int i = 0; i < N; i++) asm volatile("" : "+v"(f[i]));
-}
-
 // Small-tile form for products whose 256 x 256 tiles would leave most of the chip idle: BMT x BNT outputs (SwiGLU: half of
 // them gate, half up rows), 4 waves of a quarter each, one tile per workgroup, one or two workgroups per CU.  Same
 // operands, same v_mfma_f32_16x16x32_bf16 over K in the same order and the same epilogue arithmetic as the 256 x 256
@@ -530,11 +550,12 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
     if ((int)(blockIdx.x >> 3) >= per_xcd || tile >= total || units < NS) return;
     const int tn = tile / p.tiles_m, tm = tile - tn * p.tiles_m;
 
-    // ---- loads: an instruction covers 16 rows of one half (see the 256 x 256 kernel for the swizzle)
-    const int chunk_off = ((lane & 3) ^ ((lane >> 3) & 3)) << 4;
+    // ---- loads: an instruction covers 16 rows of one half, or 8 rows of both, a whole line each (see the 256 x 256 kernel)
+    const int kb_chunk = ((lane & 3) ^ ((lane >> 3) & 3)) << 4, rm_chunk = ((lane & 7) ^ (lane >> 3)) << 4;
     const int row_bytes = KB ? 64 : K * 2, w_row_bytes = WKB ? 64 : K * 2;
     const unsigned a_half = KB ? (unsigned)p.a_rows * 64u : 64u, w_half = WKB ? (unsigned)p.w_rows * 64u : 64u;
-    const int thread_off = (lane >> 2) * row_bytes + chunk_off, w_thread_off = (lane >> 2) * w_row_bytes + chunk_off;
+    const int thread_off = KB ? (lane >> 2) * 64 + kb_chunk : (lane >> 3) * row_bytes + rm_chunk;
+    const int w_thread_off = WKB ? (lane >> 2) * 64 + kb_chunk : (lane >> 3) * w_row_bytes + rm_chunk;
     const bf16_t *Wp;
     int w_row0;
     if (EPI == EPI_SWIGLU) {
@@ -552,29 +573,33 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
     const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(Wp + (size_t)w_row0 * w_row_elems), (short)0, WKB ? (int)(nh1 * w_half + BNT * 32u) : BNT * K, 0x00020000);   // (half the tile's rows: one wave's share)
     auto load_unit = [&](int u, int stage) {
-        char *base = lds + stage * SSTAGE;
+        char *base = lds + stage * SSTAGE, *w_base = base + 2 * A_HALF;
 #pragma unroll
         for (int i = 0; i < NA; i++) {
             const int q = wave * NA + i, half = q / (BMT / 16), blk = q % (BMT / 16);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)(base + half * A_HALF + blk * 1024), 16, thread_off,
-                                                     (int)((unsigned)(2 * u + half) * a_half) + blk * 16 * row_bytes, 0, 0);
+            if (KB) __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)(base + half * A_HALF + blk * 1024), 16, thread_off,
+                                                             (int)((unsigned)(2 * u + half) * a_half) + blk * 1024, 0, 0);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)(base + q * 1024), 16, thread_off, u * 128 + q * 8 * row_bytes, 0, 0);
         }
 #pragma unroll
         for (int i = 0; i < NWI; i++) {
-            const int half = wave >> 1, blk = (wave & 1) * NWI + i;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(base + 2 * A_HALF + half * W_HALF + blk * 1024), 16, w_thread_off,
-                                                     (int)((unsigned)(2 * u + half) * w_half) + i * 16 * w_row_bytes, 0, 0);
+            const int half = wave >> 1, blk = (wave & 1) * NWI + i, row = half * (BNT / 4) + i * 8;
+            if (WKB) __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(w_base + half * W_HALF + blk * 1024), 16, w_thread_off,
+                                                              (int)((unsigned)(2 * u + half) * w_half) + i * 1024, 0, 0);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(w_base + ((wave & 1) * (BNT / 2) + row) * 128), 16, w_thread_off,
+                                                          u * 128 + row * w_row_bytes, 0, 0);
         }
     };
 
-    const int fsw = (l16 >> 1) & 3;
-    const int lds0 = (int)(size_t)(lds_void *)lds;
-    const int a_base = lds0 + (wm * (BMT / 2) + l16) * 64 + ((kq ^ fsw) << 4);
-    const int w_base = lds0 + 2 * A_HALF + (wn * (BNT / 2) + l16) * 64 + ((kq ^ fsw) << 4);
-    // STEP: lane l reads row l % 32 of a 32-row block, from half l / 32 of the unit
+    const int lds0 = (int)(size_t)(lds_void *)lds, a_row0 = wm * (BMT / 2), w_row0_lds = wn * (BNT / 2);
+    const int kb_off = l16 * 64 + ((kq ^ ((l16 >> 1) & 3)) << 4), rm_off = l16 * 128 + ((kq ^ (l16 & 7)) << 4);
+    const int a_base = lds0 + (KB ? a_row0 * 64 + kb_off : a_row0 * 128 + rm_off);
+    const int w_base = lds0 + 2 * A_HALF + (WKB ? w_row0_lds * 64 + kb_off : w_row0_lds * 128 + rm_off);
+    // STEP: lane l reads row l % 32 of a 32-row block, from half l / 32 of the unit (chunks 4 (l / 32) .. + 3 of a whole line)
     constexpr int MB2 = MB / 2, NB2 = NB / 2;
     const int l32 = lane & 31, hh = lane >> 5, fsw32 = (l32 >> 1) & 3;
-    const int a_step = lds0 + hh * A_HALF + (wm * (BMT / 2) + l32) * 64, w_step = lds0 + 2 * A_HALF + hh * W_HALF + (wn * (BNT / 2) + l32) * 64;
+    const int a_step = lds0 + (KB ? hh * A_HALF + (a_row0 + l32) * 64 : (a_row0 + l32) * 128);
+    const int w_step = lds0 + 2 * A_HALF + (WKB ? hh * W_HALF + (w_row0_lds + l32) * 64 : (w_row0_lds + l32) * 128);
     f32x4_t acc[STEP ? 1 : NB][STEP ? 1 : MB];
     f32x16_t acc32[STEP ? NB2 : 1][STEP ? MB2 : 1], sum32[STEP ? NB2 : 1][STEP ? MB2 : 1];
     if constexpr (STEP) {
@@ -624,15 +649,15 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
         if constexpr (STEP) {
 #pragma unroll
             for (int q = 0; q < 2; q++) {
-                const int c = ((2 * h + q) ^ fsw32) << 4;
+                const int ck = ((2 * h + q) ^ fsw32) << 4, cr = ((4 * hh + 2 * h + q) ^ (l32 & 7)) << 4;
 #pragma unroll
-                for (int j = 0; j < NB2; j++) wf[h][q * NB2 + j] = lds_read<0>(w_step + so + c + j * 2048);
+                for (int j = 0; j < NB2; j++) wf[h][q * NB2 + j] = lds_read<0>(w_step + so + (WKB ? ck + j * 2048 : cr + j * 4096));
 #pragma unroll
-                for (int i = 0; i < MB2; i++) af[h][q * MB2 + i] = lds_read<0>(a_step + so + c + i * 2048);
+                for (int i = 0; i < MB2; i++) af[h][q * MB2 + i] = lds_read<0>(a_step + so + (KB ? ck + i * 2048 : cr + i * 4096));
             }
         } else {
-            read_frags<h * W_HALF, 1024>(wf[h], w_base + so, std::make_integer_sequence<int, NB>{});
-            read_frags<h * A_HALF, 1024>(af[h], a_base + so, std::make_integer_sequence<int, MB>{});
+            read_frags<WKB ? h * W_HALF : 0, WKB ? 1024 : 2048>(wf[h], (WKB || h == 0 ? w_base : w_base ^ 64) + so, std::make_integer_sequence<int, NB>{});
+            read_frags<KB ? h * A_HALF : 0, KB ? 1024 : 2048>(af[h], (KB || h == 0 ? a_base : a_base ^ 64) + so, std::make_integer_sequence<int, MB>{});
         }
     };
     // STEP: the sums of a part join those of the parts before
@@ -749,13 +774,13 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
     }
 }
 
-template <int EPI, bool KB>
+template <int EPI, bool KB, bool WKB = KB, int MB = 8>
 int launch_plain(const DmaGemmParams &p, hipStream_t st) {
     static bool attr_set = false;
     static int n_cu = 0;
     const size_t lds = NSTAGES * (size_t)STAGE;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_dma_kernel<EPI, KB>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_dma_kernel<EPI, KB, WKB, MB>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) {
             vla_set_error("hipFuncSetAttribute(gemm_bf16_dma) failed: %s", hipGetErrorString(e));
             return VLA_EHIP;
@@ -773,7 +798,7 @@ int launch_plain(const DmaGemmParams &p, hipStream_t st) {
     const int n_items = p.tiles_m * p.tiles_n * p.splits;
     int grid = n_items;
     if (n_cu % 8 == 0 && n_items > n_cu) grid = n_cu;
-    gemm_bf16_dma_kernel<EPI, KB><<<grid, 256, lds, st>>>(p);
+    gemm_bf16_dma_kernel<EPI, KB, WKB, MB><<<grid, 256, lds, st>>>(p);
     int rc = vla_check_launch("gemm_bf16_dma");
     return rc ? rc : 1;
 }
@@ -963,17 +988,18 @@ int try_gemm_bf16_dma_splitk(const GemmArgs &g, void *scratch, size_t scratch_by
     p.C = scratch; p.M = g.M; p.K = g.K; p.segN = g.segN;
     p.a_rows = g.a_rows; p.w_rows = 0; p.group = 4; p.splits = splits;
     p.tiles_m = 1; p.N = N; p.tiles_n = tiles;
-    // repacked copies of the weights, where the caller has them and the 32-bit offsets of the loads cover a segment
-    bool have_kb = g.Wkb[0] && (size_t)(g.segN + VLA_KB_PAD_ROWS) * g.K * 2 < ((size_t)1 << 31);
-    for (int i = 1; i < n_seg; i++) have_kb = have_kb && g.Wkb[i];
-    if (have_kb) {
+    // repacked copies of the weights, where the caller has them and the 32-bit offsets of the loads cover a segment: the gate/up
+    // projection of 256 rows 61 us with them, 66 without
+    bool wkb = g.Wkb[0] && (size_t)(g.segN + VLA_KB_PAD_ROWS) * g.K * 2 < ((size_t)1 << 31);
+    for (int i = 1; i < n_seg; i++) wkb = wkb && g.Wkb[i];
+    if (wkb) {
         p.W0 = (const bf16_t *)g.Wkb[0]; p.W1 = (const bf16_t *)g.Wkb[1]; p.W2 = (const bf16_t *)g.Wkb[2];
-        p.w_rows = g.segN + VLA_KB_PAD_ROWS; p.wkb = 1;
+        p.w_rows = g.segN + VLA_KB_PAD_ROWS;
     }
     int rc;
     {
         ProfScope ps(g.epilogue == EPI_SWIGLU ? "gemm_dma_splitk<swiglu>" : "gemm_dma_splitk<store>", 2.0 * g.M * g.K * (double)N, st);
-        rc = launch_plain<EPI_STORE, false>(p, st);
+        rc = wkb ? launch_plain<EPI_STORE, false, true>(p, st) : launch_plain<EPI_STORE, false>(p, st);
         if (rc != 1) return rc;
     }
     if (g.deferred_splits && g.epilogue == EPI_STORE) *g.deferred_splits = splits;
