@@ -3,8 +3,8 @@
 // equal ranges whose fp32 partial products go to a scratch buffer, of the QKV and gate/up projections of decode
 // forwards of 129..256 rows.
 //
-// Tiling: 256 x 256 output tiles, 4 waves (one per SIMD), 128 x 128 per wave as 8 x 8 blocks of
-// v_mfma_f32_16x16x32_bf16 (256 fp32 accumulators per lane).  The weight rows are the MFMA's row
+// Tiling: 256 x 256 output tiles (or 32 MB x 256, MB = 5 .. 7, see choose_tile), 4 waves (one per SIMD), 128 x 128 per wave as 8 x 8
+// blocks of v_mfma_f32_16x16x32_bf16 (256 fp32 accumulators per lane).  The weight rows are the MFMA's row
 // operand and the activation rows its column operand: a lane ends up with activation row (lane % 16) of
 // a block and four consecutive output columns.
 //
@@ -803,12 +803,19 @@ int launch_plain(const DmaGemmParams &p, hipStream_t st) {
     return rc ? rc : 1;
 }
 
+// mb (5 .. 8): 16-row blocks per wave, i.e. tiles of 32 mb rows
 template <int EPI, bool KB>
-int launch(const DmaGemmParams &p, hipStream_t st) {
+int launch(DmaGemmParams p, int mb, hipStream_t st) {
     const double flops = 2.0 * p.M * p.K * (EPI == EPI_SWIGLU ? 2.0 * p.N : (double)p.N);
     ProfScope ps(EPI == EPI_SWIGLU ? "gemm_bf16_dma<swiglu>" : EPI == EPI_RESIDUAL ? "gemm_bf16_dma<residual>"
                  : EPI == EPI_QKV_ROPE ? "gemm_bf16_dma<qkv_rope>" : "gemm_bf16_dma<store>", flops, st);
-    return launch_plain<EPI, KB>(p, st);
+    p.tiles_m = (p.M + 32 * mb - 1) / (32 * mb);
+    switch (mb) {
+        case 5: return launch_plain<EPI, KB, KB, 5>(p, st);
+        case 6: return launch_plain<EPI, KB, KB, 6>(p, st);
+        case 7: return launch_plain<EPI, KB, KB, 7>(p, st);
+        default: return launch_plain<EPI, KB>(p, st);
+    }
 }
 
 template <int EPI, bool KB, bool WKB, int BMT, int BNT, int NS, bool STEP>
@@ -832,28 +839,36 @@ int launch_small(DmaGemmParams p, hipStream_t st) {
 }
 
 // Which kernel takes a product of M rows, N columns (tile columns are 128 weight rows; SwiGLU counts gate and up) and K:
-// 0 the 256 x 256 one, else a small tile.  All give the same bits; the rule compares estimates in ns, fitted to what the
-// four projections of the 7B shape took at 64 .. 6912 rows (per unit of K = 64 and launch):
-//   256 x 256       a round of 256 tiles 1190 per unit + 8000 (prologue and epilogue)
+// the large one with tiles of 32 mb x 256, or a small tile.  All give the same bits; the rule compares estimates in ns, fitted to
+// what the four projections of the 7B shape took at 64 .. 18432 rows (per unit of K = 64 and launch):
+//   32 mb x 256     a round of 256 tiles 333 + 107 mb per unit (mb = 8: 1190) + 8000 (prologue and epilogue)
 //   64 x 64         310 up to 150 tiles, then 120 + 1.25 per tile (plain and residual outputs only)
 //   64 x 128        470 up to 276 tiles, then 1.7 per tile (SwiGLU, two weight panels per tile: 620, at least 1000)
 //   128 x 128       640 with one workgroup per CU (3 stages of LDS), 950 for every 512 with two (2 stages)
 // E.g. 288 rows, K = 4096: QKV 86 -> 55 us, O 76 -> 33, down (K = 11008) 190 -> 79; gate/up 86 with 256 x 256, 100 with 64 x 128.
-enum SmallTile { TILE_256 = 0, TILE_64x64, TILE_64x128, TILE_128x128_1, TILE_128x128_2 };
+// Tiles lower than 256 rows where the rounds of 256 tiles come out fuller: 2,304 rows, O and down on average 154 -> 133 us (160 rows
+// per tile); 4,608 rows 301 -> 250 (160); 3,384 rows, QKV 258 -> 243 (224); 7,150 rows 514 -> 484 and 339 -> 326 (224).  Their
+// rounds cost more per row, as each loads all of the tile's weights: below 160 rows the small tiles are faster.
+enum SmallTile { TILE_LARGE = 0, TILE_64x64, TILE_64x128, TILE_128x128_1, TILE_128x128_2 };
+struct TileChoice { SmallTile small; int mb; };
 template <int EPI>
-SmallTile choose_tile(const DmaGemmParams &p) {
+TileChoice choose_tile(const DmaGemmParams &p, int mb_low) {          // large tiles of 32 mb_low .. 256 rows
     const long units = p.K / 64, cols = EPI == EPI_SWIGLU ? 2L * p.N : p.N;
-    const long t256 = (p.M + 255L) / 256 * (cols / 256), t64 = (p.M + 63L) / 64 * (cols / 128), t128 = (p.M + 127L) / 128 * (cols / 128);
-    SmallTile best = TILE_256;
-    long best_ns = (t256 + 255) / 256 * (1190 * units + 8000);
-    auto offer = [&](SmallTile tile, long ns) {
-        if (ns < best_ns) { best = tile; best_ns = ns; }
+    const long t64 = (p.M + 63L) / 64 * (cols / 128), t128 = (p.M + 127L) / 128 * (cols / 128);
+    TileChoice best{TILE_LARGE, 8};
+    long best_ns = -1;
+    auto offer = [&](TileChoice tile, long ns) {
+        if (best_ns < 0 || ns < best_ns) { best = tile; best_ns = ns; }
     };
-    if (EPI == EPI_STORE || EPI == EPI_RESIDUAL) offer(TILE_64x64, units * (2 * t64 <= 150 ? 310 : 120 + 5 * (2 * t64) / 4));
-    if (EPI == EPI_SWIGLU) offer(TILE_64x128, units * (t64 <= 276 ? 620 : t64 <= 588 ? 1000 : 17 * t64 / 10));
-    else offer(TILE_64x128, units * (t64 <= 276 ? 470 : 17 * t64 / 10));
-    if (t128 <= 256) offer(TILE_128x128_1, units * 640);
-    offer(TILE_128x128_2, units * 950 * ((t128 + 511) / 512));
+    for (int mb = 8; mb >= mb_low; mb--) {
+        const long tiles = (p.M + 32L * mb - 1) / (32L * mb) * (cols / 256);
+        offer({TILE_LARGE, mb}, (tiles + 255) / 256 * (units * (333 + 107 * mb) + 8000));
+    }
+    if (EPI == EPI_STORE || EPI == EPI_RESIDUAL) offer({TILE_64x64, 0}, units * (2 * t64 <= 150 ? 310 : 120 + 5 * (2 * t64) / 4));
+    if (EPI == EPI_SWIGLU) offer({TILE_64x128, 0}, units * (t64 <= 276 ? 620 : t64 <= 588 ? 1000 : 17 * t64 / 10));
+    else offer({TILE_64x128, 0}, units * (t64 <= 276 ? 470 : 17 * t64 / 10));
+    if (t128 <= 256) offer({TILE_128x128_1, 0}, units * 640);
+    offer({TILE_128x128_2, 0}, units * 950 * ((t128 + 511) / 512));
     return best;
 }
 
@@ -872,9 +887,9 @@ int launch_tile(const DmaGemmParams &p, SmallTile tile, hipStream_t st) {
 
 template <int EPI>
 int launch_kb(const DmaGemmParams &p, bool kb, hipStream_t st) {
-    const SmallTile tile = choose_tile<EPI>(p);
-    if (tile != TILE_256) return kb ? launch_tile<EPI, true>(p, tile, st) : launch_tile<EPI, false>(p, tile, st);
-    return kb ? launch<EPI, true>(p, st) : launch<EPI, false>(p, st);
+    const TileChoice t = choose_tile<EPI>(p, 5);
+    if (t.small != TILE_LARGE) return kb ? launch_tile<EPI, true>(p, t.small, st) : launch_tile<EPI, false>(p, t.small, st);
+    return kb ? launch<EPI, true>(p, t.mb, st) : launch<EPI, false>(p, t.mb, st);
 }
 
 }  // namespace
@@ -950,8 +965,8 @@ int try_gemm_bf16_dma_step(const GemmArgs &g, hipStream_t st) {
     p.parts = gemm_decode_parts(p.N, p.K);
     auto go = [&](auto epi) {
         constexpr int EPI = decltype(epi)::value;
-        const SmallTile tile = choose_tile<EPI>(p);
-        if (tile == TILE_256) return 0;
+        const SmallTile tile = choose_tile<EPI>(p, 8).small;
+        if (tile == TILE_LARGE) return 0;
         return wkb ? launch_tile<EPI, false, true, true>(p, tile, st) : launch_tile<EPI, false, false, true>(p, tile, st);
     };
     return g.epilogue == EPI_SWIGLU ? go(std::integral_constant<int, EPI_SWIGLU>{}) : go(std::integral_constant<int, EPI_STORE>{});
