@@ -29,6 +29,15 @@ int vla_check_launch(const char *what) {
     return 0;
 }
 
+int vla_allow_lds(const void *kernel, size_t bytes) {
+    if (bytes <= 64 * 1024) return 0;
+    hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) {
+        vla_set_error("%zu bytes of LDS: %s", bytes, hipGetErrorString(e));
+        return VLA_EHIP;
+    }
+    return 0;
+}
 
 // ------------------------------------------------------------------------------------------ profiling
 struct ProfRecord { const char *label; double work; hipEvent_t e0, e1; };

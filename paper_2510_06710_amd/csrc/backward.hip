@@ -14,7 +14,8 @@
 // goes through the library's GEMM dispatch (MFMA kernels for bf16 shapes they cover).  Attention (scores, softmax,
 // its backward) runs on materialised [rows x rows] matrices per (rollout, head) with a batched tile kernel (matrix
 // cores for bf16 storage, fp32 ALU for fp32 storage); the four skinny LoRA products per projection group
-// (X A^T, dY B, dY^T (X A^T), (dY B)^T X) run as GEMMs on stacked, zero-padded factors.  Gradient operands of
+// (X A^T, dY B, dY^T (X A^T), (dY B)^T X) are one pass over X or dY each for bf16 storage (lora_grad.hip), GEMMs on stacked,
+// zero-padded factors otherwise.  Gradient operands of
 // the GEMMs are rounded to the storage type like every other GEMM operand; all sums are fp32 and taken in a fixed
 // order (no atomics), so the result is reproducible bit for bit.
 #include <type_traits>
@@ -838,7 +839,8 @@ struct Backward {
     }
 
     // LoRA gradients of a group of projections that share their input X [M, in] (storage type, contiguous rows) and
-    // whose output gradients sit side by side in dY [M, n_p * out]: four GEMMs on the MFMA path where the shape allows,
+    // whose output gradients sit side by side in dY [M, n_p * out]: lora_grad.hip's passes where it takes the group (bf16, widths
+    // that are multiples of 128, up to 128 factor rows), else four GEMMs,
     //   U = X Wa^T, V = dY Wb^T                                   [M, 256]   (Wa, Wb: the stacked, zero-padded factors)
     //   Cb = dY^T U = (dY^T)[n_p * out, kp] . (U^T)[256, kp]^T    -> dB_p = scale * its block p
     //   Ca = X^T V  = (X^T)[in, kp] . (V^T)[256, kp]^T            -> dA_p = scale * its block p, transposed
@@ -851,6 +853,13 @@ struct Backward {
         return vla_gemm_dispatch(c, g, st);
     }
     int lora_group(LoraGroup lg, const void *X, const void *dY, bool first, int M) {        // M rows
+        if constexpr (MF) {
+            LoraProducts g{};
+            for (int p = 0; p < lg.n_p; p++) { g.a[p] = lg.a[p]; g.b[p] = lg.b[p]; g.da[p] = lg.da[p]; g.db[p] = lg.db[p]; }
+            g.n_p = lg.n_p; g.in = lg.in; g.out = lg.out; g.rank = rank;
+            const int r = try_lora_products_bf16(g, X, dY, M, scale, !first, ws.split, ws.split_bytes, st);
+            if (r != 0) return r < 0 ? r : 0;
+        }
         const int in = lg.in, wout = lg.n_p * lg.out, kp = M == this->M ? ws.kp : kp_of(M);
         const int pad_rows = 256 + VLA_KB_PAD_ROWS;
         float *U = ws.UV, *V = ws.UV + (size_t)M * 256, *Cb = ws.Cab, *Ca = ws.Cab + (size_t)((wout + 255) / 256 * 256 + VLA_KB_PAD_ROWS) * 256;

@@ -13,6 +13,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef int i32x4_v __attribute__((ext_vector_type(4)));
 
 #define VLA_WAVE 64
 
@@ -210,7 +211,14 @@ int launch_attention_decode_qkv(bf16_t *out, const float *qkv, const float2 *tab
                                 int H, hipStream_t st);
 size_t attention_prefill_scratch_bytes(int n_seq, int n_heads, int d, int n_keys);
 
+// LoRA gradients of n_p projections that share their input (factors a[p] [rank, in], b[p] [out, rank] in the storage type,
+// gradients da[p], db[p] fp32 of the same shapes): lora_grad.hip
+struct LoraProducts { const void *a[3], *b[3]; float *da[3], *db[3]; int n_p, in, out, rank; };
+int try_lora_products_bf16(const LoraProducts &g, const void *X, const void *dY, int M, float scale, bool accumulate, void *scratch,
+                           size_t bytes, hipStream_t st);
+
 int vla_check_launch(const char *what);
+int vla_allow_lds(const void *kernel, size_t bytes);       // dynamic LDS of a kernel beyond the default limit; 0 or VLA_EHIP
 void vla_set_error(const char *fmt, ...);
 
 // The host-side model object behind the opaque handle of the C ABI.
