@@ -843,13 +843,15 @@ int launch_small(DmaGemmParams p, hipStream_t st) {
 // what the four projections of the 7B shape took at 64 .. 18432 rows (per unit of K = 64 and launch):
 //   32 mb x 256     a round of 256 tiles 333 + 107 mb per unit (mb = 8: 1190) + 8000 (prologue and epilogue)
 //   64 x 64         310 up to 150 tiles, then 120 + 1.25 per tile (plain and residual outputs only)
+//   128 x 64        445 where one workgroup per CU takes all tiles (plain and residual outputs, more than 128 rows)
 //   64 x 128        470 up to 276 tiles, then 1.7 per tile (SwiGLU, two weight panels per tile: 620, at least 1000)
 //   128 x 128       640 with one workgroup per CU (3 stages of LDS), 950 for every 512 with two (2 stages)
-// E.g. 288 rows, K = 4096: QKV 86 -> 55 us, O 76 -> 33, down (K = 11008) 190 -> 79; gate/up 86 with 256 x 256, 100 with 64 x 128.
+// E.g. 288 rows, K = 4096: QKV 86 -> 55 us (64 x 128), O and down (K = 11008) on average 133 -> 58 (64 x 64 and 64 x 128) -> 52
+// (128 x 64); gate/up 76 with 160 x 256, 86 with 256 x 256, 100 with 64 x 128.
 // Tiles lower than 256 rows where the rounds of 256 tiles come out fuller: 2,304 rows, O and down on average 154 -> 133 us (160 rows
 // per tile); 4,608 rows 301 -> 250 (160); 3,384 rows, QKV 258 -> 243 (224); 7,150 rows 514 -> 484 and 339 -> 326 (224).  Their
 // rounds cost more per row, as each loads all of the tile's weights: below 160 rows the small tiles are faster.
-enum SmallTile { TILE_LARGE = 0, TILE_64x64, TILE_64x128, TILE_128x128_1, TILE_128x128_2 };
+enum SmallTile { TILE_LARGE = 0, TILE_64x64, TILE_128x64, TILE_64x128, TILE_128x128_1, TILE_128x128_2 };
 struct TileChoice { SmallTile small; int mb; };
 template <int EPI>
 TileChoice choose_tile(const DmaGemmParams &p, int mb_low) {          // large tiles of 32 mb_low .. 256 rows
@@ -865,6 +867,7 @@ TileChoice choose_tile(const DmaGemmParams &p, int mb_low) {          // large t
         offer({TILE_LARGE, mb}, (tiles + 255) / 256 * (units * (333 + 107 * mb) + 8000));
     }
     if (EPI == EPI_STORE || EPI == EPI_RESIDUAL) offer({TILE_64x64, 0}, units * (2 * t64 <= 150 ? 310 : 120 + 5 * (2 * t64) / 4));
+    if ((EPI == EPI_STORE || EPI == EPI_RESIDUAL) && p.M > 128 && 2 * t128 <= 256) offer({TILE_128x64, 0}, units * 445);
     if (EPI == EPI_SWIGLU) offer({TILE_64x128, 0}, units * (t64 <= 276 ? 620 : t64 <= 588 ? 1000 : 17 * t64 / 10));
     else offer({TILE_64x128, 0}, units * (t64 <= 276 ? 470 : 17 * t64 / 10));
     if (t128 <= 256) offer({TILE_128x128_1, 0}, units * 640);
@@ -879,6 +882,9 @@ int launch_tile(const DmaGemmParams &p, SmallTile tile, hipStream_t st) {
                  : EPI == EPI_QKV_ROPE ? "gemm_small<qkv_rope>" : "gemm_small<store>", flops, st);
     if constexpr (EPI == EPI_STORE || EPI == EPI_RESIDUAL) {
         if (tile == TILE_64x64) return launch_small<EPI, KB, WKB, 64, 64, 4, STEP>(p, st);
+        if constexpr (!STEP) {
+            if (tile == TILE_128x64) return launch_small<EPI, KB, WKB, 128, 64, 4, STEP>(p, st);
+        }
     }
     if (tile == TILE_64x128) return launch_small<EPI, KB, WKB, 64, 128, 3, STEP>(p, st);
     if (tile == TILE_128x128_1) return launch_small<EPI, KB, WKB, 128, 128, 3, STEP>(p, st);
