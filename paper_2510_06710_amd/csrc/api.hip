@@ -404,6 +404,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
     // Steps of few rows: the QKV and gate/up GEMMs form the norm of their input themselves
     const bool norms = c.dtype == VLA_DTYPE_BF16 && ra.R == 1 && ws.skinny && !(force_generic() & (2 | 16));
     const bool qkv_norms = norms && gemm_stream_norms(M, H, H), ffn_norms = norms && gemm_stream_norms(M, H, F);
+    const bool f32_step = c.dtype == VLA_DTYPE_F32 && ra.R == 1;          // (the attention takes the QKV projection as it is)
     auto give_norm = [&](GemmArgs &g, const void *gain) { g.norm_x = ws.X; g.norm_gain = (const float *)gain; g.norm_eps = c.rms_eps; };
     bool have_nrm = false;                 // the previous layer's down projection already wrote this layer's Nrm
     const bool tail_form = use_tail(tail, ra.R) && ws.tail_rows == tail->count && ra.R > 1;
@@ -447,13 +448,14 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
             if (fuse_reduce && !attends) g.deferred_splits = &ds;
             if ((rc = run_gemm<T>(c, g, ws.skinny, st))) return rc;
             if (attends) rc = launch_attention_decode_qkv((bf16_t *)ws.AO, ws.QKV, ws.rope, kv, kl, ra, H, st);
+            else if (f32_step) rc = launch_attention_step_qkv((float *)ws.AO, ws.QKV, ws.rope, kv, kl, ra, H, st);
             else if (c.dtype == VLA_DTYPE_BF16 && !(force_generic() & 16))
                 rc = launch_rope_kv_write_bf16((bf16_t *)ws.Q, ds ? (const float *)ws.skinny : ws.QKV, ds ? ds : 1, (size_t)M * 3 * H,
                                                ws.rope, kv, kl, ra, H, st);
             else rc = launch_rope_kv_write<T>((T *)ws.Q, ws.QKV, ws.rope, kv, kl, ra, H, st);
             if (rc) return rc;
         }
-        int done = attends ? 1 : 0;
+        int done = attends || f32_step ? 1 : 0;
         if (c.dtype == VLA_DTYPE_BF16 && !done) {
             if (ra.R == 1)
                 done = (force_generic() & 8) ? 0 : try_attention_decode_bf16((bf16_t *)ws.AO, (const bf16_t *)ws.Q, kv, kl, ra, H, st);

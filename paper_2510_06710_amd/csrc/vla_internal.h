@@ -101,6 +101,9 @@ int launch_rope_kv_write(T *q_out, const float *qkv, const float2 *table, const 
 template <typename T>
 int launch_attention_generic(T *out, const T *q, const KvView &kv, int layer, const RowsArgs &ra,
                              int H, hipStream_t st);
+// fp32 decode step (one row per sequence): the same straight from the QKV projection [n_seq, 3H], with rotation and KV write
+int launch_attention_step_qkv(float *out, const float *qkv, const float2 *table, const KvView &kv, int layer, const RowsArgs &ra, int H,
+                              hipStream_t st);
 // rows first .. first + count - 1 of each of n_seq sequences of R rows, packed
 int launch_gather_rows(float *Xt, const float *X, int n_seq, int R, int first, int count, int H, hipStream_t st);
 // rotary on q alone: qf fp32 [n_seq * count, H]; packed row m sits at table row first + m % count
