@@ -507,6 +507,9 @@ int vla_check_rows_per_pass(const vla_config &c, long n_seq, long rows_per_seq) 
 int vla_gemm_dispatch(const vla_config &c, const GemmArgs &g, hipStream_t st) {
     return c.dtype == VLA_DTYPE_F32 ? run_gemm<float>(c, g, nullptr, st) : run_gemm<bf16_t>(c, g, nullptr, st);
 }
+int vla_gemm_fused(const vla_config &c, const GemmArgs &g, hipStream_t st) {
+    return c.dtype == VLA_DTYPE_BF16 && !(force_generic() & 1) ? try_gemm_bf16_dma(g, st) : 0;
+}
 
 static int prefill_tail_rows(int S) { const TailSpec t{S - 1, 1}; return use_tail(&t, S) ? 1 : 0; }
 // recompute, autoregressive mode: rows S - 1 .. S + A - 2 are read (the value head reads the first of them)

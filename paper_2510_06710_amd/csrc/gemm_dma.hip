@@ -66,8 +66,9 @@ struct DmaGemmParams {
     int tiles_m, tiles_n;
     int a_rows;      // k-blocked layout: rows per 32-column block of A (and of the SwiGLU output)
     int w_rows;      // k-blocked layout: rows per 32-column block of each weight matrix
-    // EPI_QKV_ROPE
+    // EPI_QKV_ROPE, EPI_QKV_ROWS
     bf16_t *q_out, *kc, *vc;
+    float *pre;      // EPI_SWIGLU_KEEP
     const float2 *table;
     int R, pos0, n_heads, pos_stride, H;
     int seg0;        // EPI_QKV_ROPE: what the first weight segment is (0 = q, k, v follow; 1 = k, v only)
@@ -130,7 +131,9 @@ __device__ __forceinline__ void panel_wait(f32x4_t (&v)[N]) {
     for (int i = 0; i < N; i++) asm volatile("" : "+v"(v[i]));
 }
 
-// One 16-row block of a wave's QKV output, from its panel: the wave's 128 columns are one head of q, k or v (head_dim 128).
+// One 16-row block of a wave's QKV output, from its panel: the wave's 128 columns are one head of q, k or v (head_dim 128).  ROWS: all
+// three go to q_out as rows of 3H.
+template <bool ROWS>
 __device__ __forceinline__ void qkv_block_out(const DmaGemmParams &p, float *panel, int mblock, int n0, int lane) {
     const int seg_in = n0 / p.H, head = (n0 - seg_in * p.H) >> 7, seg = seg_in + p.seg0;
     f32x4_t v[8];
@@ -150,16 +153,22 @@ __device__ __forceinline__ void qkv_block_out(const DmaGemmParams &p, float *pan
             for (int e = 0; e < 4; e++) { o[e] = (bf16_t)v[2 * it][e]; o[4 + e] = (bf16_t)v[2 * it + 1][e]; }
             if (m < p.M) {
                 const int sq = m / p.R, pos = p.pos0 + (m - sq * p.R);
-                *(bf16x8_t *)(p.vc + (((size_t)sq * p.n_heads + head) * p.pos_stride + pos) * 128 + c * 8) = o;
+                if (ROWS) *(bf16x8_t *)(p.q_out + (size_t)m * 3 * p.H + 2 * p.H + head * 128 + c * 8) = o;
+                else *(bf16x8_t *)(p.vc + (((size_t)sq * p.n_heads + head) * p.pos_stride + pos) * 128 + c * 8) = o;
             }
         }
     } else {
+        f32x4_t cs[2][4];
 #pragma unroll
         for (int it = 0; it < 2; it++) {
             // q: consecutive lanes take consecutive chunks of a row; k: consecutive positions of a chunk
             const int item = it * 64 + lane;
-            const int row = (seg == 0) ? (item >> 3) : (item & 15);
-            const int c = (seg == 0) ? (item & 7) : (item >> 4);
+            const int row = (ROWS || seg == 0) ? (item >> 3) : (item & 15);
+            const int c = (ROWS || seg == 0) ? (item & 7) : (item >> 4);
+            // (cos, sin) of the chunk's eight dims, two per piece, on their way while the panel is read
+            const f32x4_t *tb = (const f32x4_t *)(p.table + (size_t)((mblock + row) % p.R) * 64 + c * 8);
+#pragma unroll
+            for (int e2 = 0; e2 < 4; e2++) cs[it][e2] = tb[e2];
             v[4 * it] = panel_get(panel, row, 2 * c);
             v[4 * it + 1] = panel_get(panel, row, 2 * c + 1);
             v[4 * it + 2] = panel_get(panel, row, 16 + 2 * c);
@@ -169,28 +178,22 @@ __device__ __forceinline__ void qkv_block_out(const DmaGemmParams &p, float *pan
 #pragma unroll
         for (int it = 0; it < 2; it++) {
             const int item = it * 64 + lane;
-            const int row = (seg == 0) ? (item >> 3) : (item & 15);
-            const int c = (seg == 0) ? (item & 7) : (item >> 4);
+            const int row = (ROWS || seg == 0) ? (item >> 3) : (item & 15);
+            const int c = (ROWS || seg == 0) ? (item & 7) : (item >> 4);
             const int m = mblock + row;
             const f32x4_t lo0 = v[4 * it], lo1 = v[4 * it + 1], hi0 = v[4 * it + 2], hi1 = v[4 * it + 3];
             if (m < p.M) {
                 const int sq = m / p.R, rr = m - sq * p.R, pos = p.pos0 + rr;
-                const f32x4_t *tb = (const f32x4_t *)(p.table + (size_t)rr * 64 + c * 8);
                 bf16x8_t olo, ohi;
 #pragma unroll
-                for (int e2 = 0; e2 < 4; e2++) {
-                    const f32x4_t cs = tb[e2];        // (cos, sin) of dims 2 e2 and 2 e2 + 1 of the chunk
-#pragma unroll
-                    for (int u = 0; u < 2; u++) {
-                        const int e = 2 * e2 + u;
-                        const float co = cs[2 * u], si = cs[2 * u + 1];
-                        const float a = e < 4 ? lo0[e & 3] : lo1[e & 3], b = e < 4 ? hi0[e & 3] : hi1[e & 3];
-                        olo[e] = (bf16_t)(a * co - b * si);
-                        ohi[e] = (bf16_t)(b * co + a * si);
-                    }
+                for (int e = 0; e < 8; e++) {
+                    const float co = cs[it][e >> 1][2 * (e & 1)], si = cs[it][e >> 1][2 * (e & 1) + 1];
+                    const float a = e < 4 ? lo0[e & 3] : lo1[e & 3], b = e < 4 ? hi0[e & 3] : hi1[e & 3];
+                    olo[e] = (bf16_t)(a * co - b * si);
+                    ohi[e] = (bf16_t)(b * co + a * si);
                 }
-                if (seg == 0) {
-                    bf16_t *q = p.q_out + (size_t)m * p.H + head * 128 + c * 8;
+                if (ROWS || seg == 0) {
+                    bf16_t *q = p.q_out + (ROWS ? (size_t)m * 3 * p.H + seg * p.H : (size_t)m * p.H) + head * 128 + c * 8;
                     *(bf16x8_t *)q = olo;
                     *(bf16x8_t *)(q + 64) = ohi;
                 } else {
@@ -228,6 +231,43 @@ __device__ __forceinline__ void swiglu_block_out(const DmaGemmParams &p, float *
     }
 }
 
+// One 16-row block of raw gate (panel columns 0 .. 63) and up values, output columns from c0: fp32 [M, 2N], gate then up.
+__device__ __forceinline__ void pre_block_out(const DmaGemmParams &p, float *panel, int mblock, int c0, int lane) {
+    const int cb = lane & 31;
+    float *out = p.pre + (cb < 16 ? c0 + cb * 4 : p.N + c0 + (cb - 16) * 4);
+    f32x4_t v[8];
+#pragma unroll
+    for (int it = 0; it < 8; it++) v[it] = panel_get(panel, it * 2 + (lane >> 5), cb);
+    panel_wait(v);
+#pragma unroll
+    for (int it = 0; it < 8; it++) {
+        const int m = mblock + it * 2 + (lane >> 5);
+        if (m < p.M) *(f32x4_t *)(out + (size_t)m * 2 * p.N) = v[it];
+    }
+}
+// ... and its SwiGLU outputs, bf16 [M, N]
+__device__ __forceinline__ void swiglu_of_pre_out(const DmaGemmParams &p, float *panel, int mblock, int c0, int lane) {
+    f32x4_t v[8];
+#pragma unroll
+    for (int it = 0; it < 2; it++) {
+        const int row = it * 8 + (lane >> 3), c2 = lane & 7;
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            v[4 * it + u] = panel_get(panel, row, 2 * c2 + u);
+            v[4 * it + 2 + u] = panel_get(panel, row, 16 + 2 * c2 + u);
+        }
+    }
+    panel_wait(v);
+#pragma unroll
+    for (int it = 0; it < 2; it++) {
+        const int m = mblock + it * 8 + (lane >> 3);
+        bf16x8_t o;
+#pragma unroll
+        for (int e = 0; e < 8; e++) o[e] = (bf16_t)vla_silu_mul(v[4 * it + (e >> 2)][e & 3], v[4 * it + 2 + (e >> 2)][e & 3]);
+        if (m < p.M) *(bf16x8_t *)((bf16_t *)p.C + (size_t)m * p.N + c0 + (lane & 7) * 8) = o;
+    }
+}
+
 // Output of one wave.  Per 16-row activation block i a lane holds row (lane % 16) and, per weight block j
 // and register r, column 16 j + 4 (lane / 16) + r.  Each block goes through the panel and leaves as whole
 // rows.
@@ -235,7 +275,7 @@ template <int EPI, bool KB, int MB>
 __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][MB], const DmaGemmParams &p, int m0, int tn, int wn,
                                          int lane, float *panel, size_t c_off) {
     const int l16 = lane & 15, kq = lane >> 4;
-    if (EPI == EPI_QKV_ROPE) {
+    if (epi_qkv(EPI)) {
         const int n0 = tn * BN + wn * 128;
 #pragma unroll
         for (int i = 0; i < MB; i++) {
@@ -243,7 +283,19 @@ __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][MB], const DmaGemmPar
 #pragma unroll
             for (int j = 0; j < 8; j++) panel_put_acc(panel, l16, j * 4 + kq, acc[j][i]);
             panel_written();
-            qkv_block_out(p, panel, m0 + i * 16, n0, lane);
+            qkv_block_out<EPI == EPI_QKV_ROWS>(p, panel, m0 + i * 16, n0, lane);
+        }
+        return;
+    }
+    if (EPI == EPI_SWIGLU_KEEP) {
+#pragma unroll
+        for (int i = 0; i < MB; i++) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 8; j++) panel_put_acc(panel, l16, j * 4 + kq, acc[j][i]);
+            panel_written();
+            pre_block_out(p, panel, m0 + i * 16, tn * 128 + wn * 64, lane);
+            swiglu_of_pre_out(p, panel, m0 + i * 16, tn * 128 + wn * 64, lane);
         }
         return;
     }
@@ -361,7 +413,7 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     const int row_bytes = KB ? 64 : K * 2;       // distance of consecutive tile rows
     const int up = KB ? wave & 1 : wave >> 1;    // SwiGLU: which matrix this wave loads from, and which 64 (32) of its rows
     const int a_thread_off = KB ? (wave * 16 * NA + (lane >> 2)) * 64 + chunk_off : (wave * 8 * NA + (lane >> 3)) * row_bytes + chunk_off;
-    const int w_part = EPI == EPI_SWIGLU ? (KB ? wave >> 1 : wave & 1) : wave;
+    const int w_part = epi_swiglu(EPI) ? (KB ? wave >> 1 : wave & 1) : wave;
     const int w_thread_off = KB ? (w_part * 64 + (lane >> 2)) * 64 + chunk_off
                              : WKB ? ((wave & 1) * 64 + (lane >> 2)) * 64 + (((lane & 3) ^ ((lane >> 3) & 3)) << 4) + (wave >> 1) * p.w_rows * 64
                                    : (w_part * 32 + (lane >> 3)) * row_bytes + chunk_off;
@@ -377,14 +429,14 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
         vla_tile_of_block(it - split * n_tiles, p.tiles_m, p.tiles_n, tm, tn, p.group);
         const bf16_t *Wp;
         int w_row;
-        if (EPI == EPI_SWIGLU) { Wp = up ? p.W1 : p.W0; w_row = tn * 128; }
+        if (epi_swiglu(EPI)) { Wp = up ? p.W1 : p.W0; w_row = tn * 128; }
         else {
             const int n = tn * BN, seg = __builtin_amdgcn_readfirstlane(n / p.segN);
             Wp = seg == 0 ? p.W0 : (seg == 1 ? p.W1 : p.W2);
             w_row = n - seg * p.segN;
         }
         // (rows behind the activation buffer's last: the range check takes the scalar offset into account, those loads return zero)
-        const unsigned w_tile_rows = EPI == EPI_SWIGLU ? 128u : 256u;
+        const unsigned w_tile_rows = epi_swiglu(EPI) ? 128u : 256u;
         if (KB) {            // first element of this item's K range: whole 32-column blocks
             const unsigned avail = MB == 8 ? 256u : (unsigned)min(64 * NA, p.a_rows - tm * ROWS);
             a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(p.A + (size_t)tm * ROWS * 32 + (size_t)split * nh * (a_step / 2)), (short)0, (int)((unsigned)(nh - 1) * a_step + avail * 64u), 0x00020000);
@@ -407,7 +459,7 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
             if (i < NA) __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)base, 16, a_thread_off, (int)a_soff, q * 1024, 0);
             else __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)base, 16, w_thread_off, (int)w_soff, q * 1024, 0);
         } else {
-            constexpr int a_row = RH * 16 * MB + q * 8, w_row = RH * (EPI == EPI_SWIGLU ? 64 : 128) + q * 8;
+            constexpr int a_row = RH * 16 * MB + q * 8, w_row = RH * (epi_swiglu(EPI) ? 64 : 128) + q * 8;
             if (i < NA) __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)(base + q * 1024), 16, a_thread_off, (int)a_soff + a_row * row_bytes, 0, 0);
             else if (WKB) __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)base, 16, w_thread_off, (int)w_soff + RH * 128 * 64, q * 1024, 0);
             else __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(base + q * 1024), 16, w_thread_off, (int)w_soff + w_row * row_bytes, 0, 0);
@@ -558,7 +610,7 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
     const int w_thread_off = WKB ? (lane >> 2) * 64 + kb_chunk : (lane >> 3) * w_row_bytes + rm_chunk;
     const bf16_t *Wp;
     int w_row0;
-    if (EPI == EPI_SWIGLU) {
+    if (epi_swiglu(EPI)) {
         Wp = (wave & 1) ? p.W1 : p.W0;                   // instruction blocks 0..3 gate rows, 4..7 up rows
         w_row0 = tn * 64;
     } else {
@@ -735,8 +787,11 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
         float *pb = panel + b * 16 * 128;
         const int mblock = m0 + b * 16;
         if (mblock >= p.M) break;
-        if (EPI == EPI_QKV_ROPE) {
-            qkv_block_out(p, pb, mblock, tn * 128, lane);
+        if (epi_qkv(EPI)) {
+            qkv_block_out<EPI == EPI_QKV_ROWS>(p, pb, mblock, tn * 128, lane);
+        } else if (EPI == EPI_SWIGLU_KEEP) {
+            pre_block_out(p, pb, mblock, tn * 64, lane);
+            swiglu_of_pre_out(p, pb, mblock, tn * 64, lane);
         } else if (EPI == EPI_SWIGLU) {
 #pragma unroll
             for (int it = 0; it < 2; it++) {
@@ -806,9 +861,9 @@ int launch_plain(const DmaGemmParams &p, hipStream_t st) {
 // mb (5 .. 8): 16-row blocks per wave, i.e. tiles of 32 mb rows
 template <int EPI, bool KB>
 int launch(DmaGemmParams p, int mb, hipStream_t st) {
-    const double flops = 2.0 * p.M * p.K * (EPI == EPI_SWIGLU ? 2.0 * p.N : (double)p.N);
-    ProfScope ps(EPI == EPI_SWIGLU ? "gemm_bf16_dma<swiglu>" : EPI == EPI_RESIDUAL ? "gemm_bf16_dma<residual>"
-                 : EPI == EPI_QKV_ROPE ? "gemm_bf16_dma<qkv_rope>" : "gemm_bf16_dma<store>", flops, st);
+    const double flops = 2.0 * p.M * p.K * (epi_swiglu(EPI) ? 2.0 * p.N : (double)p.N);
+    ProfScope ps(epi_swiglu(EPI) ? "gemm_bf16_dma<swiglu>" : EPI == EPI_RESIDUAL ? "gemm_bf16_dma<residual>"
+                 : epi_qkv(EPI) ? "gemm_bf16_dma<qkv_rope>" : "gemm_bf16_dma<store>", flops, st);
     p.tiles_m = (p.M + 32 * mb - 1) / (32 * mb);
     switch (mb) {
         case 5: return launch_plain<EPI, KB, KB, 5>(p, st);
@@ -831,7 +886,7 @@ int launch_small(DmaGemmParams p, hipStream_t st) {
         attr_set = true;
     }
     p.tiles_m = (p.M + BMT - 1) / BMT;
-    p.tiles_n = EPI == EPI_SWIGLU ? p.N / (BNT / 2) : p.N / BNT;
+    p.tiles_n = epi_swiglu(EPI) ? p.N / (BNT / 2) : p.N / BNT;
     const int per_xcd = (p.tiles_m * p.tiles_n + 7) / 8;
     gemm_bf16_small_kernel<EPI, KB, WKB, BMT, BNT, NS, STEP><<<8 * per_xcd, 256, lds, st>>>(p);
     int rc = vla_check_launch("gemm_bf16_small");
@@ -855,7 +910,7 @@ enum SmallTile { TILE_LARGE = 0, TILE_64x64, TILE_128x64, TILE_64x128, TILE_128x
 struct TileChoice { SmallTile small; int mb; };
 template <int EPI>
 TileChoice choose_tile(const DmaGemmParams &p, int mb_low) {          // large tiles of 32 mb_low .. 256 rows
-    const long units = p.K / 64, cols = EPI == EPI_SWIGLU ? 2L * p.N : p.N;
+    const long units = p.K / 64, cols = epi_swiglu(EPI) ? 2L * p.N : p.N;
     const long t64 = (p.M + 63L) / 64 * (cols / 128), t128 = (p.M + 127L) / 128 * (cols / 128);
     TileChoice best{TILE_LARGE, 8};
     long best_ns = -1;
@@ -868,7 +923,7 @@ TileChoice choose_tile(const DmaGemmParams &p, int mb_low) {          // large t
     }
     if (EPI == EPI_STORE || EPI == EPI_RESIDUAL) offer({TILE_64x64, 0}, units * (2 * t64 <= 150 ? 310 : 120 + 5 * (2 * t64) / 4));
     if ((EPI == EPI_STORE || EPI == EPI_RESIDUAL) && p.M > 128 && 2 * t128 <= 256) offer({TILE_128x64, 0}, units * 445);
-    if (EPI == EPI_SWIGLU) offer({TILE_64x128, 0}, units * (t64 <= 276 ? 620 : t64 <= 588 ? 1000 : 17 * t64 / 10));
+    if (epi_swiglu(EPI)) offer({TILE_64x128, 0}, units * (t64 <= 276 ? 620 : t64 <= 588 ? 1000 : 17 * t64 / 10));
     else offer({TILE_64x128, 0}, units * (t64 <= 276 ? 470 : 17 * t64 / 10));
     if (t128 <= 256) offer({TILE_128x128_1, 0}, units * 640);
     offer({TILE_128x128_2, 0}, units * 950 * ((t128 + 511) / 512));
@@ -877,9 +932,9 @@ TileChoice choose_tile(const DmaGemmParams &p, int mb_low) {          // large t
 
 template <int EPI, bool KB, bool WKB = KB, bool STEP = false>
 int launch_tile(const DmaGemmParams &p, SmallTile tile, hipStream_t st) {
-    const double flops = 2.0 * p.M * p.K * (EPI == EPI_SWIGLU ? 2.0 * p.N : (double)p.N);
-    ProfScope ps(EPI == EPI_SWIGLU ? "gemm_small<swiglu>" : EPI == EPI_RESIDUAL ? "gemm_small<residual>"
-                 : EPI == EPI_QKV_ROPE ? "gemm_small<qkv_rope>" : "gemm_small<store>", flops, st);
+    const double flops = 2.0 * p.M * p.K * (epi_swiglu(EPI) ? 2.0 * p.N : (double)p.N);
+    ProfScope ps(epi_swiglu(EPI) ? "gemm_small<swiglu>" : EPI == EPI_RESIDUAL ? "gemm_small<residual>"
+                 : epi_qkv(EPI) ? "gemm_small<qkv_rope>" : "gemm_small<store>", flops, st);
     if constexpr (EPI == EPI_STORE || EPI == EPI_RESIDUAL) {
         if (tile == TILE_64x64) return launch_small<EPI, KB, WKB, 64, 64, 4, STEP>(p, st);
         if constexpr (!STEP) {
@@ -894,8 +949,13 @@ int launch_tile(const DmaGemmParams &p, SmallTile tile, hipStream_t st) {
 template <int EPI>
 int launch_kb(const DmaGemmParams &p, bool kb, hipStream_t st) {
     const TileChoice t = choose_tile<EPI>(p, 5);
-    if (t.small != TILE_LARGE) return kb ? launch_tile<EPI, true>(p, t.small, st) : launch_tile<EPI, false>(p, t.small, st);
-    return kb ? launch<EPI, true>(p, t.mb, st) : launch<EPI, false>(p, t.mb, st);
+    if constexpr (EPI == EPI_QKV_ROWS || EPI == EPI_SWIGLU_KEEP || EPI == EPI_STORE) {          // row-major operands only
+        if (kb) return 0;
+        return t.small != TILE_LARGE ? launch_tile<EPI, false>(p, t.small, st) : launch<EPI, false>(p, t.mb, st);
+    } else {
+        if (t.small != TILE_LARGE) return kb ? launch_tile<EPI, true>(p, t.small, st) : launch_tile<EPI, false>(p, t.small, st);
+        return kb ? launch<EPI, true>(p, t.mb, st) : launch<EPI, false>(p, t.mb, st);
+    }
 }
 
 }  // namespace
@@ -918,7 +978,7 @@ int try_gemm_bf16_dma(const GemmArgs &g, hipStream_t st) {
     {
         // tile rows per column panel of the walk: 4, except for the QKV projection (1.9 % faster with 2 at
         // M = 73728: 5.73 against 5.84 ms; the other projections within 0.5 % either way)
-        p.group = g.epilogue == EPI_QKV_ROPE ? 2 : 4;
+        p.group = epi_qkv(g.epilogue) ? 2 : 4;
     }
     p.tiles_m = (g.M + BM - 1) / BM;
     if (g.epilogue == EPI_SWIGLU) {
@@ -927,7 +987,24 @@ int try_gemm_bf16_dma(const GemmArgs &g, hipStream_t st) {
         p.tiles_n = g.segN / 128;
         return launch_kb<EPI_SWIGLU>(p, kb, st);
     }
+    if (g.epilogue == EPI_SWIGLU_KEEP) {
+        if (g.segN % 128 != 0) return 0;
+        p.N = g.segN;
+        p.tiles_n = g.segN / 128;
+        p.pre = g.pre;
+        return launch_kb<EPI_SWIGLU_KEEP>(p, kb, st);
+    }
     if (g.segN % BN != 0) return 0;
+    if (g.epilogue == EPI_QKV_ROWS) {
+        const QkvRopeArgs *ra = g.rope;
+        if (!ra || ra->kv->d != 128 || g.n_seg != 3 || g.segN != ra->kv->n_heads * 128) return 0;
+        p.q_out = (bf16_t *)ra->q_out;
+        p.table = ra->table;
+        p.R = ra->rows->R; p.H = g.segN;
+        p.N = 3 * g.segN;
+        p.tiles_n = p.N / BN;
+        return launch_kb<EPI_QKV_ROWS>(p, kb, st);
+    }
     if (g.epilogue == EPI_QKV_ROPE) {
         const QkvRopeArgs *ra = g.rope;
         if (!ra || ra->kv->d != 128 || (g.n_seg != 3 && g.n_seg != 2) || g.segN != ra->kv->n_heads * 128) return 0;

@@ -34,7 +34,11 @@ struct RowsArgs {           // one forward over n_seq sequences x R new rows eac
                             // rows below attend causally (keys 0..position)
 };
 
-enum GemmEpilogue { EPI_STORE = 0, EPI_RESIDUAL = 1, EPI_SWIGLU = 2, EPI_QKV_ROPE = 3 };
+// EPI_QKV_ROWS and EPI_SWIGLU_KEEP are those of the gradient pass (row-major operands, direct-to-LDS kernels only): rotated q | k | v
+// as rows of 3H instead of the KV layout, and SwiGLU with its pre-activations.
+enum GemmEpilogue { EPI_STORE = 0, EPI_RESIDUAL = 1, EPI_SWIGLU = 2, EPI_QKV_ROPE = 3, EPI_QKV_ROWS = 4, EPI_SWIGLU_KEEP = 5 };
+constexpr bool epi_swiglu(int e) { return e == EPI_SWIGLU || e == EPI_SWIGLU_KEEP; }
+constexpr bool epi_qkv(int e) { return e == EPI_QKV_ROPE || e == EPI_QKV_ROWS; }
 
 // Extra arguments of EPI_QKV_ROPE: the QKV projection whose epilogue rotates q and k and writes q to
 // q_out [M, H] and k, v straight into layer `layer` of the KV buffer (head_dim 128 only).
@@ -61,7 +65,8 @@ struct GemmArgs {
     void *C;                // EPI_STORE: fp32 [M, N]; EPI_SWIGLU: storage dtype [M, N]; EPI_RESIDUAL: fp32 [M, N] +=
     int M, K;
     int epilogue;
-    const QkvRopeArgs *rope;   // EPI_QKV_ROPE only
+    const QkvRopeArgs *rope;   // EPI_QKV_ROPE, EPI_QKV_ROWS (q_out [M, 3H]; of kv only n_heads and d)
+    float *pre;             // EPI_SWIGLU_KEEP: gate | up pre-activations, fp32 [M, 2N]
     int kblocked;           // A (a_rows rows per 32-column block), the weights (segN rows per block, each segment
                             // on its own) and a SwiGLU output are stored [K / 32][rows][32]: direct-to-LDS kernel only
     int a_rows;             // rows of A that may be read (>= M; contents past M arbitrary): the MFMA kernel
@@ -235,6 +240,8 @@ int vla_check_config(const vla_config *c);                                   // 
 int vla_check_rows_per_pass(const vla_config &c, long n_seq, long rows_per_seq);
 // C = A . W^T of a multi-row forward (row-major operands): the MFMA kernels where the shape allows, else the generic one
 int vla_gemm_dispatch(const vla_config &c, const GemmArgs &g, hipStream_t st);
+// The same with one of the gradient pass's epilogues: 1 if handled, 0 if declined, < 0 on a launch error
+int vla_gemm_fused(const vla_config &c, const GemmArgs &g, hipStream_t st);
 // The teacher-forced forward of the log-prob recompute over n rollouts (the kernels vla_logprob_recompute runs), keeping
 // the fp32 residual stream at the input of layer l in keep + l * n * R * H ([n * R, H] each).  tail_rows: 0, or how many of
 // every rollout's last rows the caller reads after the last layer, which then computes those alone (at most a quarter of the
