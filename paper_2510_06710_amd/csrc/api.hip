@@ -383,14 +383,20 @@ static int run_last_layer_tail(const vla_model *m, const Workspace &ws, const Ro
     return run_gemm<T>(c, g, ws.tskinny, st);
 }
 
+// Steps of few rows: whether the QKV (N = hidden) and gate/up (N = ffn) GEMMs form the norm of their input themselves.
+static bool step_norms(const vla_config &c, const Workspace &ws, int M, int N) {
+    return c.dtype == VLA_DTYPE_BF16 && ws.skinny && !(force_generic() & (2 | 16)) && gemm_stream_norms(M, c.hidden, N);
+}
+
 // `tail` (may be NULL): the rows whose final hidden state the caller reads.  Where use_tail() holds, the last layer
-// is run in its tail form and the result of those rows is in ws.tX (packed), not in ws.X.
+// is run in its tail form and the result of those rows is in ws.tX (packed), not in ws.X.  `prepared`: ws.rope and, where
+// the QKV projection does not form it itself, the first layer's norm are there (NextStep).
 template <typename T>
 static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &ra, const KvView &kv,
-                      bool kv_single_layer, hipStream_t st, const TailSpec *tail = nullptr, float *keep = nullptr) {
+                      bool kv_single_layer, hipStream_t st, const TailSpec *tail = nullptr, float *keep = nullptr, bool prepared = false) {
     const vla_config &c = m->cfg;
     int H = c.hidden, F = c.ffn, M = ra.n_seq * ra.R, d = H / c.n_heads, rc;
-    if ((rc = launch_rope_table(ws.rope, ra.R, ra.pos0, d, c.rope_theta, st))) return rc;
+    if (!prepared && (rc = launch_rope_table(ws.rope, ra.R, ra.pos0, d, c.rope_theta, st))) return rc;
     // k-blocked operands: repacked weights present, a multi-row forward, every fast path available and the
     // 32-bit offsets of the loads sufficient
     const bool kb = !m->packed.empty() && ra.R > 1 && kblocked_shape_ok(c) && force_generic() == 0 &&
@@ -401,12 +407,10 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
     // in the order the stand-alone reduction would.
     const bool fuse_reduce = c.dtype == VLA_DTYPE_BF16 && ra.R == 1 && ws.skinny && !(force_generic() & (2 | 16)) &&
                              H % 1024 == 0 && H <= 8192;
-    // Steps of few rows: the QKV and gate/up GEMMs form the norm of their input themselves
-    const bool norms = c.dtype == VLA_DTYPE_BF16 && ra.R == 1 && ws.skinny && !(force_generic() & (2 | 16));
-    const bool qkv_norms = norms && gemm_stream_norms(M, H, H), ffn_norms = norms && gemm_stream_norms(M, H, F);
+    const bool qkv_norms = ra.R == 1 && step_norms(c, ws, M, H), ffn_norms = ra.R == 1 && step_norms(c, ws, M, F);
     const bool f32_step = c.dtype == VLA_DTYPE_F32 && ra.R == 1;          // (the attention takes the QKV projection as it is)
     auto give_norm = [&](GemmArgs &g, const void *gain) { g.norm_x = ws.X; g.norm_gain = (const float *)gain; g.norm_eps = c.rms_eps; };
-    bool have_nrm = false;                 // the previous layer's down projection already wrote this layer's Nrm
+    bool have_nrm = prepared && !qkv_norms;          // the sampler or the previous layer's down projection already wrote this layer's Nrm
     const bool tail_form = use_tail(tail, ra.R) && ws.tail_rows == tail->count && ra.R > 1;
     for (int l = 0; l < c.n_layers; l++) {
         const vla_layer_weights &lw = m->layers[l];
@@ -560,11 +564,13 @@ static int decode_impl(vla_model *m, void *kvbuf, void *wsbuf, const float *h_la
         const float *h = h_last;
         for (int j = 0; j < A; j++) {
             bool more = j + 1 < A;
+            const NextStep next{ws.Nrm, step_norms(c, ws, B, H) ? nullptr : (const float *)m->layers[0].attn_norm, c.rms_eps, ws.rope, S + j, H / c.n_heads, c.rope_theta};
+            const bool prepares = more && B <= VLA_HEAD_PARTIAL_ROWS;
             if ((rc = launch_head_sample<T>(h, head, B, H, temperature, gumbel, nullptr, bins, logp, entropy, logits, A, j,
-                                            more ? ws.X : nullptr, (const T *)m->w.embed, c.vocab, ws.QKV, st))) return rc;
+                                            more ? ws.X : nullptr, (const T *)m->w.embed, c.vocab, ws.QKV, st, prepares ? &next : nullptr))) return rc;
             if (!more) break;
             RowsArgs ra{B, 1, S + j, 0x7fffffff};
-            if ((rc = run_layers<T>(m, ws, ra, kv, false, st))) return rc;
+            if ((rc = run_layers<T>(m, ws, ra, kv, false, st, nullptr, nullptr, prepares))) return rc;
             if ((rc = launch_final_norm_rows(ws.Hb, ws.X, (const float *)m->w.final_norm, B, 1, 0, 1, H, c.rms_eps, st))) return rc;
             h = ws.Hb;
         }

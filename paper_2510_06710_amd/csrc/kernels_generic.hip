@@ -93,7 +93,6 @@ __global__ void embed_slots_kernel(float *X, const T *slot_embed, int A, int row
 template <typename T>
 __device__ __forceinline__ void norm_row(T *o, const float *x, const float *gain, int H, float eps, float *red) {
     f32x4_t v[8], g[8];
-    float ss = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; j++) {
         const int i = (j * 256 + threadIdx.x) * 4;
@@ -102,27 +101,8 @@ __device__ __forceinline__ void norm_row(T *o, const float *x, const float *gain
             g[j] = *(const f32x4_u *)(gain + i);
         }
     }
-#pragma unroll
-    for (int j = 0; j < 8; j++)
-        if ((j * 256 + (int)threadIdx.x) * 4 < H) {
-#pragma unroll
-            for (int e = 0; e < 4; e++) ss += v[j][e] * v[j][e];
-        }
-    ss = block_sum_256(ss, red);
-    const float r = 1.0f / sqrtf(ss / (float)H + eps);
-    typedef T t4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
-#pragma unroll
-    for (int j = 0; j < 8; j++) {
-        const int i = (j * 256 + threadIdx.x) * 4;
-        if (i < H) {
-            t4 w;
-#pragma unroll
-            for (int e = 0; e < 4; e++) w[e] = from_f<T>(v[j][e] * r * g[j][e]);
-            *(t4 *)(o + i) = w;
-        }
-    }
+    vla_norm_held<T>(o, v, g, H, eps, red);
 }
-
 template <typename T>
 __global__ void __launch_bounds__(256) rmsnorm_kernel(T *out, const float *X, const float *gain, int H, float eps) {
     __shared__ float red[4];
@@ -259,15 +239,13 @@ __global__ void __launch_bounds__(512) gemm_generic_kernel(const T *A, const T *
 }
 
 // ---------------------------------------------------------------------------------- rotary
-// table[r][i] = (cos, sin)(phi), phi = (pos0 + r) * theta^(-2i/d), evaluated in fp64.
+// table[r][i] = (cos, sin)(phi), phi = (pos0 + r) * theta^(-2i/d).
 __global__ void rope_table_kernel(float2 *table, int R, int pos0, int d, float theta) {
     int idx = blockIdx.x * blockDim.x + threadIdx.x;
     int half = d / 2;
     if (idx >= R * half) return;
     int r = idx / half, i = idx % half;
-    double inv = pow((double)theta, -2.0 * (double)i / (double)d);
-    double phi = (double)(pos0 + r) * inv;
-    table[idx] = make_float2((float)cos(phi), (float)sin(phi));
+    table[idx] = vla_rope_entry(pos0 + r, i, d, theta);
 }
 
 // Rotate q and k of every new row (pairs (i, i + d/2)) from the fp32 QKV projection, write q to its

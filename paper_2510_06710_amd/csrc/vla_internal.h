@@ -119,11 +119,14 @@ int launch_rope_q(T *q_out, const float *qf, const float2 *table, int n_seq, int
 // logits[o * 256 ..]; it reads gumbel[o * 256 ..] (if any) and given_bins[o] (if any: then the
 // log-prob is that of the given bin and nothing is sampled).  If X_next is not NULL the embedding
 // of token vocab - 256 + bin is written to X_next[i * H ..] as fp32.
+// next (with X_next, up to VLA_HEAD_PARTIAL_ROWS rows): what the next decode step needs besides its residual rows, its first
+// norm (gain NULL: not wanted) and its row of the rotation table
+struct NextStep { void *nrm; const float *gain; float eps; float2 *table; int pos, d; float theta; };
 template <typename T>
 int launch_head_sample(const float *h, const T *lm_head_bins, int n_rows, int H, float temperature,
                        const float *gumbel, const int32_t *given_bins, int32_t *bins_out, float *logp,
                        float *ent, float *logits, int out_stride, int out_off, float *X_next,
-                       const T *embed, int vocab, float *scratch, hipStream_t st);
+                       const T *embed, int vocab, float *scratch, hipStream_t st, const NextStep *next = nullptr);
 // Partial logits h . W^T of n_rows rows, P[head_chunks(H)][n_rows][256] to be added in chunk order.
 int head_chunks(int H);
 template <typename T>
@@ -138,6 +141,44 @@ int launch_value_head(float *value, const float *h, const float *w, float b, con
 // agree bit for bit (the compiler fuses either product of a sum of two).
 __device__ __forceinline__ float vla_rotate_lo(float a, float b, float co, float si) { return __builtin_fmaf(a, co, -(b * si)); }
 __device__ __forceinline__ float vla_rotate_hi(float a, float b, float co, float si) { return __builtin_fmaf(b, co, a * si); }
+
+// (cos, sin) of pair i at a position, evaluated in fp64
+__device__ __forceinline__ float2 vla_rope_entry(int pos, int i, int d, float theta) {
+    const double inv = pow((double)theta, -2.0 * (double)i / (double)d), phi = (double)pos * inv;
+    return make_float2((float)cos(phi), (float)sin(phi));
+}
+
+// RMSNorm of a row held by 256 threads: piece j of thread t is elements 4 (256 j + t) .. + 3 (those below H), g the gain's.
+// red: 4 floats of LDS.  The one order of sums of all norms by 256 threads.
+template <typename T>
+__device__ __forceinline__ void vla_norm_held(T *o, const f32x4_t (&v)[8], const f32x4_t (&g)[8], int H, float eps, float *red) {
+    typedef T t4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+    const int t = threadIdx.x;
+    float ss = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; j++)
+        if ((j * 256 + t) * 4 < H) {
+#pragma unroll
+            for (int e = 0; e < 4; e++) ss += v[j][e] * v[j][e];
+        }
+#pragma unroll
+    for (int k = 32; k > 0; k >>= 1) ss += __shfl_xor(ss, k, 64);
+    __syncthreads();
+    if ((t & 63) == 0) red[t >> 6] = ss;
+    __syncthreads();
+    ss = red[0] + red[1] + red[2] + red[3];
+    const float r = 1.0f / sqrtf(ss / (float)H + eps);
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+        const int i = (j * 256 + t) * 4;
+        if (i < H) {
+            t4 w;
+#pragma unroll
+            for (int e = 0; e < 4; e++) w[e] = (T)(v[j][e] * r * g[j][e]);
+            *(t4 *)(o + i) = w;
+        }
+    }
+}
 
 // silu(gate) * up of the bf16 fast paths: hardware exponential and reciprocal (1 ulp each, far below
 // the bf16 rounding that follows); one formula for the prefill and the decode GEMMs so that both
