@@ -12,8 +12,9 @@
 // intermediates in a set of its own (one per layer, for one micro-batch), and (3) runs no layer a second time.  Every large contraction -- the seven forward projections and the four input-gradient products
 // dY . W, which run as the same "activation x weight^T" GEMM on a transposed copy of the weights made per layer --
 // goes through the library's GEMM dispatch (MFMA kernels for bf16 shapes they cover).  Attention (scores, softmax,
-// its backward) runs on materialised [rows x rows] matrices per (rollout, head) with a batched tile kernel (matrix
-// cores for bf16 storage, fp32 ALU for fp32 storage); the four skinny LoRA products per projection group
+// its backward) runs on materialised [rows x rows] matrices per (rollout, head): 64 query rows at a time from scores to output
+// (attn_rows.hip: bf16, head_dim 128, up to 316 rows), otherwise, and for the products that contract over the queries, with a batched
+// tile kernel (matrix cores for bf16 storage, fp32 ALU for fp32 storage); the four skinny LoRA products per projection group
 // (X A^T, dY B, dY^T (X A^T), (dY B)^T X) are one pass over X or dY each for bf16 storage (lora_grad.hip), GEMMs on stacked,
 // zero-padded factors otherwise.  Gradient operands of
 // the GEMMs are rounded to the storage type like every other GEMM operand; all sums are fp32 and taken in a fixed
@@ -830,15 +831,21 @@ struct Backward {
             if ((rc = vla_check_launch("rope_rows"))) return rc;
         }
         // scores = q k^T / sqrt(d) per (sequence, head); softmax under the mask; output = P v
-        BgemmArgs g = heads(Q + (size_t)(R - Rq) * 3 * H, 3 * H, rowsH3, d, Q + H, 3 * H, rowsH3, d, a.SP, Rp, RR * nh, RR, Rq, R, d, 0, 1,
-                            1.0f / sqrtf((float)d), causal ? 2 : 0);
-        if ((rc = bgemm<T, T, MF>(g, n * nh, st))) return rc;
-        attn_softmax_kernel<<<(unsigned)(((size_t)n * nh * Rq + 3) / 4), 256, 0, st>>>(a.SP, (size_t)n * nh * Rq, Rq, R - Rq, R, Rp, full_from);
-        if ((rc = vla_check_launch("attn_softmax"))) return rc;
-        g = heads(a.SP, Rp, RR * nh, RR, Q + 2 * H, 3 * H, rowsH3, d, MF ? (float *)a.AO : ws.Tmp, H, (long)Rq * H, d, Rq, d, R, 0, 0, 1.0f, causal ? 1 : 0);
-        g.c_bf16 = MF;                               // the matrix-core kernel rounds the output to the storage type itself
-        if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
-        if (!MF && (rc = cast(a.AO, ws.Tmp, H, Mq))) return rc;
+        rc = 0;
+        if constexpr (MF) {
+            if ((rc = try_attention_rows_forward(AttnRowsArgs{Q, (const bf16_t *)Q, a.SP, nullptr, a.AO, R, Rq, Rp, nh, H, full_from, 1.0f / sqrtf((float)d)}, n, st)) < 0) return rc;
+        }
+        if (rc == 0) {
+            BgemmArgs g = heads(Q + (size_t)(R - Rq) * 3 * H, 3 * H, rowsH3, d, Q + H, 3 * H, rowsH3, d, a.SP, Rp, RR * nh, RR, Rq, R, d, 0, 1,
+                                1.0f / sqrtf((float)d), causal ? 2 : 0);
+            if ((rc = bgemm<T, T, MF>(g, n * nh, st))) return rc;
+            attn_softmax_kernel<<<(unsigned)(((size_t)n * nh * Rq + 3) / 4), 256, 0, st>>>(a.SP, (size_t)n * nh * Rq, Rq, R - Rq, R, Rp, full_from);
+            if ((rc = vla_check_launch("attn_softmax"))) return rc;
+            g = heads(a.SP, Rp, RR * nh, RR, Q + 2 * H, 3 * H, rowsH3, d, MF ? (float *)a.AO : ws.Tmp, H, (long)Rq * H, d, Rq, d, R, 0, 0, 1.0f, causal ? 1 : 0);
+            g.c_bf16 = MF;                               // the matrix-core kernel rounds the output to the storage type itself
+            if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
+            if (!MF && (rc = cast(a.AO, ws.Tmp, H, Mq))) return rc;
+        }
         if (Rq != R && (rc = launch_gather_rows(ws.X, a.x_in, n, R, R - Rq, Rq, H, st))) return rc;
         if ((rc = gemm(a.AO, lw.wo, nullptr, nullptr, 1, H, ws.X, H, Mq, EPI_RESIDUAL))) return rc;     // x_mid = x_in + O(...)
         if ((rc = copy_stream(a.x_mid, ws.X, Mq))) return rc;
@@ -954,14 +961,21 @@ struct Backward {
         if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, H, d_ao, H, Mq))) return rc;
         float *dqkv = ws.Tmp;                        // [M, 3H] fp32: d q | d k | d v (q, k still in the rotated frame)
         // dP = dO v^T ; dV = P^T dO ; dS = P (dP - rowsum(P dP)) ; dQ = dS k / sqrt(d) ; dK = dS^T q / sqrt(d)
-        BgemmArgs g = heads(d_ao, H, (long)Rq * H, d, Q + 2 * H, 3 * H, rowsH3, d, ws.dP, Rp, RR * nh, RR, Rq, R, d, 0, 1, 1.0f, causal ? 2 : 0);
-        if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
+        rc = 0;
+        if constexpr (MF) {
+            if ((rc = try_attention_rows_backward(AttnRowsArgs{d_ao, (const bf16_t *)Q, ws.dP, a.SP, dqkv, R, Rq, Rp, nh, H, full_from, isd}, n, st)) < 0) return rc;
+        }
+        BgemmArgs g{};
+        if (rc == 0) {
+            g = heads(d_ao, H, (long)Rq * H, d, Q + 2 * H, 3 * H, rowsH3, d, ws.dP, Rp, RR * nh, RR, Rq, R, d, 0, 1, 1.0f, causal ? 2 : 0);
+            if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
+            attn_ds_kernel<<<(unsigned)(((size_t)n * nh * Rq + 3) / 4), 256, 0, st>>>(ws.dP, a.SP, (size_t)n * nh * Rq, Rq, R - Rq, R, Rp, full_from);
+            if ((rc = vla_check_launch("attn_ds"))) return rc;
+            g = heads(ws.dP, Rp, RR * nh, RR, Q + H, 3 * H, rowsH3, d, dqkv + (size_t)(R - Rq) * 3 * H, 3 * H, rowsH3, d, Rq, d, R, 0, 0, isd, causal ? 1 : 0);
+            if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
+        }
         g = heads(a.SP, Rp, RR * nh, RR, d_ao, H, (long)Rq * H, d, dqkv + 2 * H, 3 * H, rowsH3, d, R, d, Rq, 1, 0, 1.0f, 0);
         if ((rc = bgemm<float, float, MF>(g, n * nh, st))) return rc;
-        attn_ds_kernel<<<(unsigned)(((size_t)n * nh * Rq + 3) / 4), 256, 0, st>>>(ws.dP, a.SP, (size_t)n * nh * Rq, Rq, R - Rq, R, Rp, full_from);
-        if ((rc = vla_check_launch("attn_ds"))) return rc;
-        g = heads(ws.dP, Rp, RR * nh, RR, Q + H, 3 * H, rowsH3, d, dqkv + (size_t)(R - Rq) * 3 * H, 3 * H, rowsH3, d, Rq, d, R, 0, 0, isd, causal ? 1 : 0);
-        if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
         g = heads(ws.dP, Rp, RR * nh, RR, Qt, 3 * H, rowsH3, d, dqkv + H, 3 * H, rowsH3, d, R, d, Rq, 1, 0, isd, 0);
         if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
         rope_rows_kernel<T><<<M, 256, 0, st>>>((T *)ws.dQKVb, dqkv, ws.rope, R, H, d, -1.0f, R - Rq);

@@ -260,6 +260,16 @@ int launch_attention_decode_qkv(bf16_t *out, const float *qkv, const float2 *tab
                                 int H, hipStream_t st);
 size_t attention_prefill_scratch_bytes(int n_seq, int n_heads, int d, int n_keys);
 
+// Attention of the gradient pass with its [rows x keys] matrices kept (attn_rows.hip).  qkv: rotated q | k | v, bf16 [n_seq * R, 3H];
+// the queries are the last Rq rows of every sequence; P, S: [n_seq * n_heads][Rq][ldp] fp32.
+//   forward: rows = qkv, S = the probabilities (out), out = bf16 [n_seq * Rq, H];  scale: of the scores
+//   backward: rows = d out, fp32 [n_seq * Rq, H], P the probabilities, S = the scores' gradients (out), out = d q, fp32 [n_seq * R, 3H], the
+//   queries' rows;  scale: of d q
+// Return 1 if handled, 0 if declined, < 0 on a launch error.
+struct AttnRowsArgs { const void *rows; const bf16_t *qkv; float *S; const float *P; void *out; int R, Rq, ldp, n_heads, H, full_from; float scale; };
+int try_attention_rows_forward(const AttnRowsArgs &a, int n_seq, hipStream_t st);
+int try_attention_rows_backward(const AttnRowsArgs &a, int n_seq, hipStream_t st);
+
 // LoRA gradients of n_p projections that share their input (factors a[p] [rank, in], b[p] [out, rank] in the storage type,
 // gradients da[p], db[p] fp32 of the same shapes): lora_grad.hip
 struct LoraProducts { const void *a[3], *b[3]; float *da[3], *db[3]; int n_p, in, out, rank; };
