@@ -206,7 +206,8 @@ int vla_profile_report(char *buf, size_t n);
 
 /* Triage aid (process-wide, not thread safe): a bit mask of steps that take the shape-generic kernel even where a
  * gfx950 fast path applies -- 1 large GEMM, 2 decode GEMM, 4 multi-row attention, 8 decode attention, 16 rotary / KV
- * write / RMSNorm; 0 (the default) selects every fast path.  Results stay within the parity tolerances either way;
+ * write / RMSNorm; in the gradient pass 1 also takes the LoRA products, 4 the attention, 16 the rotation and SwiGLU that
+ * ride their projections; 0 (the default) selects every fast path.  Results stay within the parity tolerances either way;
  * the tests use it to run the generic kernels on shapes that would otherwise never reach them. */
 int vla_debug_force_generic(int mask);
 

@@ -204,9 +204,11 @@ static int recompute_micro_batch(const vla_config &c, int N, int R) {
 // ------------------------------------------------------------------------------------------ forward
 // Triage switch (vla_debug_force_generic): a bit mask that sends a step to the shape-generic kernel even when a
 // gfx950 fast path applies (1 large GEMM, 2 decode GEMM, 4 multi-row attention, 8 decode attention, 16 rotary / KV
-// write / RMSNorm).  Process-wide; 0 unless the caller sets it.
+// write / RMSNorm).  In the gradient pass 1 also sends the LoRA products to the GEMMs on padded factors, 4 the attention to
+// the batched products, 16 the rotation and SwiGLU to passes of their own.  Process-wide; 0 unless the caller sets it.
 static int g_force_generic = 0;
 static int force_generic() { return g_force_generic; }
+int vla_force_generic() { return g_force_generic; }
 
 // The multi-row bf16 forwards can run on k-blocked operands ([K / 32][rows][32], see gemm_dma.hip): needs
 // head_dim 128 (fused rotation epilogue), tile-aligned widths and repacked weights.
@@ -512,7 +514,7 @@ int vla_gemm_dispatch(const vla_config &c, const GemmArgs &g, hipStream_t st) {
     return c.dtype == VLA_DTYPE_F32 ? run_gemm<float>(c, g, nullptr, st) : run_gemm<bf16_t>(c, g, nullptr, st);
 }
 int vla_gemm_fused(const vla_config &c, const GemmArgs &g, hipStream_t st) {
-    return c.dtype == VLA_DTYPE_BF16 && !(force_generic() & 1) ? try_gemm_bf16_dma(g, st) : 0;
+    return c.dtype == VLA_DTYPE_BF16 && !(force_generic() & (1 | 16)) ? try_gemm_bf16_dma(g, st) : 0;
 }
 
 static int prefill_tail_rows(int S) { const TailSpec t{S - 1, 1}; return use_tail(&t, S) ? 1 : 0; }

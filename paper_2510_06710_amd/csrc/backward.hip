@@ -833,7 +833,7 @@ struct Backward {
         // scores = q k^T / sqrt(d) per (sequence, head); softmax under the mask; output = P v
         rc = 0;
         if constexpr (MF) {
-            if ((rc = try_attention_rows_forward(AttnRowsArgs{Q, (const bf16_t *)Q, a.SP, nullptr, a.AO, R, Rq, Rp, nh, H, full_from, 1.0f / sqrtf((float)d)}, n, st)) < 0) return rc;
+            if (!(vla_force_generic() & 4) && (rc = try_attention_rows_forward(AttnRowsArgs{Q, (const bf16_t *)Q, a.SP, nullptr, a.AO, R, Rq, Rp, nh, H, full_from, 1.0f / sqrtf((float)d)}, n, st)) < 0) return rc;
         }
         if (rc == 0) {
             BgemmArgs g = heads(Q + (size_t)(R - Rq) * 3 * H, 3 * H, rowsH3, d, Q + H, 3 * H, rowsH3, d, a.SP, Rp, RR * nh, RR, Rq, R, d, 0, 1,
@@ -885,7 +885,7 @@ struct Backward {
             LoraProducts g{};
             for (int p = 0; p < lg.n_p; p++) { g.a[p] = lg.a[p]; g.b[p] = lg.b[p]; g.da[p] = lg.da[p]; g.db[p] = lg.db[p]; }
             g.n_p = lg.n_p; g.in = lg.in; g.out = lg.out; g.rank = rank;
-            const int r = try_lora_products_bf16(g, X, dY, M, scale, !first, ws.split, ws.split_bytes, st);
+            const int r = vla_force_generic() & 1 ? 0 : try_lora_products_bf16(g, X, dY, M, scale, !first, ws.split, ws.split_bytes, st);
             if (r != 0) return r < 0 ? r : 0;
         }
         const int in = lg.in, wout = lg.n_p * lg.out, kp = M == this->M ? ws.kp : kp_of(M);
@@ -963,7 +963,7 @@ struct Backward {
         // dP = dO v^T ; dV = P^T dO ; dS = P (dP - rowsum(P dP)) ; dQ = dS k / sqrt(d) ; dK = dS^T q / sqrt(d)
         rc = 0;
         if constexpr (MF) {
-            if ((rc = try_attention_rows_backward(AttnRowsArgs{d_ao, (const bf16_t *)Q, ws.dP, a.SP, dqkv, R, Rq, Rp, nh, H, full_from, isd}, n, st)) < 0) return rc;
+            if (!(vla_force_generic() & 4) && (rc = try_attention_rows_backward(AttnRowsArgs{d_ao, (const bf16_t *)Q, ws.dP, a.SP, dqkv, R, Rq, Rp, nh, H, full_from, isd}, n, st)) < 0) return rc;
         }
         BgemmArgs g{};
         if (rc == 0) {

@@ -276,6 +276,7 @@ struct LoraProducts { const void *a[3], *b[3]; float *da[3], *db[3]; int n_p, in
 int try_lora_products_bf16(const LoraProducts &g, const void *X, const void *dY, int M, float scale, bool accumulate, void *scratch,
                            size_t bytes, hipStream_t st);
 
+int vla_force_generic();                                   // the mask of vla_debug_force_generic
 int vla_check_launch(const char *what);
 int vla_allow_lds(const void *kernel, size_t bytes);       // dynamic LDS of a kernel beyond the default limit; 0 or VLA_EHIP
 void vla_set_error(const char *fmt, ...);
