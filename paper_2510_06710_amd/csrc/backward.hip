@@ -312,8 +312,8 @@ __global__ void __launch_bounds__(256) rope_rows_kernel(T *out, const float *in,
 #pragma unroll
             for (int u = 0; u < 4; u++) {
                 const float co = seg == 2 ? 1.f : cs[u].x, si = seg == 2 ? 0.f : sign * cs[u].y;
-                lo[u] = cvt<T>(seg == 2 ? a[u] : a[u] * co - b[u] * si);
-                hi[u] = cvt<T>(seg == 2 ? b[u] : b[u] * co + a[u] * si);
+                lo[u] = cvt<T>(seg == 2 ? a[u] : vla_rotate_lo(a[u], b[u], co, si));
+                hi[u] = cvt<T>(seg == 2 ? b[u] : vla_rotate_hi(a[u], b[u], co, si));
             }
         }
         *(t4 *)(out + base) = lo;

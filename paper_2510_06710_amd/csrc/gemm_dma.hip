@@ -189,8 +189,8 @@ __device__ __forceinline__ void qkv_block_out(const DmaGemmParams &p, float *pan
                 for (int e = 0; e < 8; e++) {
                     const float co = cs[it][e >> 1][2 * (e & 1)], si = cs[it][e >> 1][2 * (e & 1) + 1];
                     const float a = e < 4 ? lo0[e & 3] : lo1[e & 3], b = e < 4 ? hi0[e & 3] : hi1[e & 3];
-                    olo[e] = (bf16_t)(a * co - b * si);
-                    ohi[e] = (bf16_t)(b * co + a * si);
+                    olo[e] = (bf16_t)(ROWS ? vla_rotate_lo(a, b, co, si) : a * co - b * si);      // (ROWS: as rope_rows_kernel rounds)
+                    ohi[e] = (bf16_t)(ROWS ? vla_rotate_hi(a, b, co, si) : b * co + a * si);
                 }
                 if (ROWS || seg == 0) {
                     bf16_t *q = p.q_out + (ROWS ? (size_t)m * 3 * p.H + seg * p.H : (size_t)m * p.H) + head * 128 + c * 8;

@@ -3,6 +3,7 @@ the launches show, and the gradients stay within the bounds of test_gpu_backward
 import ctypes
 
 import pytest
+import torch
 
 import vla_inputs as vi
 from paper_2510_06710_amd import binding as vb
@@ -39,3 +40,17 @@ def test_a_bit_sends_its_step_to_the_general_kernels(mask, gone, there):
     ref, ref_logp = _oracle(WL, 11, lora, bins, coef, WL.batch, 0.5, operand_dtype="bf16")
     _assert_logp_bf16(logp, ref_logp)
     print(_compare(grads, ref, 2e-2, 1e-2), flush=True)
+
+
+# (an FFN width that is no multiple of 128: the gate / up product and SwiGLU are separate either way)
+@pytest.mark.parametrize("n,hidden,ffn,S,A,mode", [(37, 2048, 320, 92, 8, 0), (4, 256, 320, 30, 40, 1)])
+def test_epilogues_give_the_bits_of_the_separate_passes(n, hidden, ffn, S, A, mode):
+    """The rotation on the way out of its projection rounds as the kernel that takes the shapes this one declines: which of the two a
+    model's widths select cannot be seen in its gradients."""
+    shape = vi.ModelShape(n_layers=2, hidden=hidden, n_heads=hidden // 128, ffn=ffn, vocab=640, dtype="bf16")
+    wl = vi.Workload("epilogues", shape, batch=n, n_patches=S - 9, n_instr=9, n_action=A, mode=mode)
+    usual, apart = (forced(mask, wl, 13, 8, keep=True)[0] for mask in (0, 16))
+    assert torch.equal(torch.from_numpy(usual[5]), torch.from_numpy(apart[5]))
+    differ = {(l, p): max(float((x != y).float().mean()) for x, y in zip(a[p], b[p]))
+              for l, (a, b) in enumerate(zip(usual[4], apart[4])) for p in a}
+    assert not any(differ.values()), differ
