@@ -390,7 +390,7 @@ __global__ void __launch_bounds__(256) swiglu_fwd_kernel(T *act, const float *GU
         const fv g = *(const fv *)src, u = *(const fv *)(src + F);
         tv o;
 #pragma unroll
-        for (int e = 0; e < V; e++) o[e] = cvt<T>(g[e] / (1.0f + expf(-g[e])) * u[e]);
+        for (int e = 0; e < V; e++) o[e] = cvt<T>(vla_silu_mul_exact(g[e], u[e]));
         *(tv *)(act + (size_t)m * F + f) = o;
     }
 }
@@ -851,7 +851,8 @@ struct Backward {
         if ((rc = copy_stream(a.x_mid, ws.X, Mq))) return rc;
         if ((rc = launch_rmsnorm<T>((T *)a.Nrm2, ws.X, (const float *)lw.ffn_norm, Mq, H, c.rms_eps, st))) return rc;
         {   // ... and SwiGLU that of the gate / up projection (1,981 rows of 2 x 11008: a pass of 31 us less; both: 32 rollouts of two
-            // layers 14.56 -> 14.17 ms, 7 rollouts 3.59 -> 3.48)
+            // layers 14.56 -> 14.17 ms, 7 rollouts 3.59 -> 3.48; the library's exponential and a division, as in swiglu_fwd_kernel, take
+            // 0.03 and 0.02 ms of that back)
             GemmArgs g{};
             g.A = a.Nrm2; g.W[0] = lw.w_gate; g.W[1] = lw.w_up; g.n_seg = 2; g.segN = F; g.C = a.ACT; g.pre = a.GU; g.M = Mq; g.K = H;
             g.epilogue = EPI_SWIGLU_KEEP; g.a_rows = ws.a_rows;

@@ -263,7 +263,7 @@ __device__ __forceinline__ void swiglu_of_pre_out(const DmaGemmParams &p, float 
         const int m = mblock + it * 8 + (lane >> 3);
         bf16x8_t o;
 #pragma unroll
-        for (int e = 0; e < 8; e++) o[e] = (bf16_t)vla_silu_mul(v[4 * it + (e >> 2)][e & 3], v[4 * it + 2 + (e >> 2)][e & 3]);
+        for (int e = 0; e < 8; e++) o[e] = (bf16_t)vla_silu_mul_exact(v[4 * it + (e >> 2)][e & 3], v[4 * it + 2 + (e >> 2)][e & 3]);
         if (m < p.M) *(bf16x8_t *)((bf16_t *)p.C + (size_t)m * p.N + c0 + (lane & 7) * 8) = o;
     }
 }

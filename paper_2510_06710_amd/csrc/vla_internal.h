@@ -186,6 +186,9 @@ __device__ __forceinline__ void vla_norm_held(T *o, const f32x4_t (&v)[8], const
 __device__ __forceinline__ float vla_silu_mul(float gate, float up) {
     return gate * __builtin_amdgcn_rcpf(1.0f + __expf(-gate)) * up;
 }
+// ... and that of the gradient pass, whose backward differentiates it at the kept pre-activations: the library's exponential
+// and a division.
+__device__ __forceinline__ float vla_silu_mul_exact(float gate, float up) { return gate / (1.0f + expf(-gate)) * up; }
 
 // Maps a linear work-item id of the large-tile GEMMs to an output tile.  Workgroups are dealt round-robin to
 // the eight XCDs, each with its own L2.  The ids of XCD y, taken in order, walk the tile rows y, y + 8, y + 16, ...

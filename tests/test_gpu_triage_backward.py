@@ -42,11 +42,15 @@ def test_a_bit_sends_its_step_to_the_general_kernels(mask, gone, there):
     print(_compare(grads, ref, 2e-2, 1e-2), flush=True)
 
 
-# (an FFN width that is no multiple of 128: the gate / up product and SwiGLU are separate either way)
-@pytest.mark.parametrize("n,hidden,ffn,S,A,mode", [(37, 2048, 320, 92, 8, 0), (4, 256, 320, 30, 40, 1)])
+# (an FFN width that is no multiple of 128: the gate / up product and SwiGLU are separate either way; a multiple of 256: both forms
+# take the product from the same tiles)
+@pytest.mark.parametrize("n,hidden,ffn,S,A,mode", [(37, 2048, 320, 92, 8, 0), (4, 256, 320, 30, 40, 1),
+                                                   (3, 512, 768, 69, 5, 0),          # small tiles, the top layer on its read rows
+                                                   (37, 2048, 2304, 92, 8, 0),       # large tiles
+                                                   (4, 256, 512, 30, 40, 1)])        # every row through the top layer
 def test_epilogues_give_the_bits_of_the_separate_passes(n, hidden, ffn, S, A, mode):
-    """The rotation on the way out of its projection rounds as the kernel that takes the shapes this one declines: which of the two a
-    model's widths select cannot be seen in its gradients."""
+    """Rotation and SwiGLU on the way out of their projections round and evaluate as the kernels that take the shapes those decline:
+    which of the two a model's widths select cannot be seen in its gradients."""
     shape = vi.ModelShape(n_layers=2, hidden=hidden, n_heads=hidden // 128, ffn=ffn, vocab=640, dtype="bf16")
     wl = vi.Workload("epilogues", shape, batch=n, n_patches=S - 9, n_instr=9, n_action=A, mode=mode)
     usual, apart = (forced(mask, wl, 13, 8, keep=True)[0] for mask in (0, 16))
