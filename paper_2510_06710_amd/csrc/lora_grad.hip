@@ -91,6 +91,7 @@ __global__ void __launch_bounds__(512) lora_thin_kernel(ThinArgs a) {
         for (int i = 0; i < RB; i++) acc[b][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int read0 = (int)(size_t)(lds_void *)lds + l16 * ROW + wave * 128 + kq * 16;
     load_x(0, 0);
+    asm volatile("" ::: "memory");               // (the first wait below counts what is issued after chunk 0)
     load_x(min(1, chunks - 1), 1);
     load_w(0, 0);
     int stage = 0;
