@@ -54,7 +54,9 @@ struct ThinArgs {
 // LDS, 512 columns at a time, three such chunks in turn: a load instruction takes 1 KB of one row (as MFMA operands straight from
 // memory, 16 rows x 64 bytes that lie a row's length apart, X arrived at 1.2 TB/s), rows 16 bytes further apart in LDS so
 // that the operand reads meet no bank conflict.  Wave w multiplies columns 64 w .. + 63 of a chunk with factors on their way
-// since the chunk before; the waves' sums meet in LDS.
+// since the chunk before (through a buffer descriptor: their addresses stay scalar.  As vector registers those took registers of
+// factors still on their way, and every other step waited for all but its own loads; 41.7 us for X A^T of q | k | v at 9,408 rows, rank 32,
+// either way, two workgroups on a CU cover it); the waves' sums meet in LDS.
 template <int RB, int NB>
 __global__ void __launch_bounds__(512) lora_thin_kernel(ThinArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -77,12 +79,13 @@ __global__ void __launch_bounds__(512) lora_thin_kernel(ThinArgs a) {
                                                      min(row, rows_in - 1) * a.ldx * 2 + c * 1024, 0, 0);
         }
     };
-    const bf16_t *wp = a.W + (size_t)gr * (a.K / 32) * NB * 512 + lane * 8;
+    const int w_bytes = a.K / 32 * NB * 1024;
+    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc((void *)((const char *)a.W + (size_t)gr * w_bytes), (short)0, w_bytes, 0x00020000);
     bf16x8_t wf[2][NW];
     auto load_w = [&](int s, int c) {
-        const int sl = min(c * 8 + wave, slices - 1);
+        const int at = min(c * 8 + wave, slices - 1) * NW * 1024;
 #pragma unroll
-        for (int q = 0; q < NW; q++) wf[s][q] = *(const bf16x8_t *)(wp + ((size_t)sl * NW + q) * 512);
+        for (int q = 0; q < NW; q++) wf[s][q] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, at + q * 1024, 0));
     };
     f32x4_t acc[NB][RB];
 #pragma unroll

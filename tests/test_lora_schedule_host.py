@@ -30,3 +30,11 @@ def test_the_first_chunk_is_loaded_first(kernels):
         before = [x for x in ops[:ops.index("s_barrier")] if "_load" in x]
         assert len(before) == 4 * rb + 2 * nb and all(x.endswith(" lds") for x in before[: 2 * rb]), (rb, nb, before)
         assert sum(x.endswith(" lds") for x in before) == 4 * rb, (rb, nb, before)
+
+
+def test_no_step_waits_for_the_loads_behind_its_own(kernels):
+    """In the loop every wait leaves the next chunk's loads and factors in flight: the ring is three chunks deep."""
+    for (rb, nb), ops in kernels.items():
+        last = max(i for i, x in enumerate(ops) if x.startswith("v_mfma"))
+        waits = [int(n) for x in ops[ops.index("s_barrier"):last] for n in re.findall(r"vmcnt\((\d+)\)", x)]
+        assert waits and min(waits) >= 2 * rb + 2 * nb, (rb, nb, waits)
