@@ -55,8 +55,8 @@ struct ThinArgs {
 // memory, 16 rows x 64 bytes that lie a row's length apart, X arrived at 1.2 TB/s), rows 16 bytes further apart in LDS so
 // that the operand reads meet no bank conflict.  Wave w multiplies columns 64 w .. + 63 of a chunk with factors on their way
 // since the chunk before (through a buffer descriptor: their addresses stay scalar.  As vector registers those took registers of
-// factors still on their way, and every other step waited for all but its own loads; 41.7 us for X A^T of q | k | v at 9,408 rows, rank 32,
-// either way, two workgroups on a CU cover it); the waves' sums meet in LDS.
+// factors still on their way, and every other step waited for all but its own loads; X A^T of q | k | v at 9,408 rows, rank 32, takes
+// 41.7 us either way); the waves' sums meet in LDS.
 template <int RB, int NB>
 __global__ void __launch_bounds__(512) lora_thin_kernel(ThinArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
