@@ -144,8 +144,9 @@ def _stream(stream) -> Optional[int]:
     if stream is not None:
         return stream.cuda_stream or None
     import torch
-    if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw and device and torch.cuda.is_initialized():          # (no public interface: other versions may lack them)
+        return raw(device()) or None
     return torch.cuda.current_stream().cuda_stream or None
 
 
