@@ -617,7 +617,7 @@ int launch_attention_generic(T *out, const T *q, const KvView &kv, int layer, co
 int launch_attention_step_qkv(float *out, const float *qkv, const float2 *table, const KvView &kv, int layer, const RowsArgs &ra, int H, hipStream_t st) {
     const int n_items = ra.n_seq * kv.n_heads;
     if (n_items == 0) return 0;
-    ProfScope ps("attention_generic", 0.0, st);
+    ProfScope ps("attention_step", 0.0, st);
     const size_t lds = (size_t)(7 * kv.d + 8 + ra.pos0 + 1) * sizeof(float);   // (at most 40 KB: 8192 keys at head_dim 256)
     attention_step_kernel<<<n_items, 256, lds, st>>>(out, qkv, table, (float *)kv.k + (size_t)layer * kv.layer_elems, (float *)kv.v + (size_t)layer * kv.layer_elems,
                                                      ra.pos0, kv.n_heads, kv.d, kv.pos_stride, H);
