@@ -491,7 +491,7 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     // stage at byte `to` (row-major: row half 1 of the next pair in a first half, row half 0 of the one after it in a second).
     auto iteration = [&](auto b_c, auto mul_c, int a_st, int w_st, int to) {
         constexpr int B = decltype(b_c)::value, MUL = decltype(mul_c)::value;
-        constexpr int RSTEP = MB >= 5 ? 2 : 1, LSTEP = 8 * MB / NL / 2 * 2;
+        constexpr int RSTEP = 2, LSTEP = 8 * MB / NL / 2 * 2;
         static_assert((7 + MB) * RSTEP < 8 * MB && 1 + LSTEP * (NL - 1) < 8 * MB, "reads and loads fit between the MFMAs");
         const int va = (!KB && B == 1 ? a_base ^ 64 : a_base) + a_st, vw = (KB || B == 0 ? w_base : WKB ? w_base + 8192 : w_base ^ 64) + w_st;
         for_each_index([&](auto m_c) {

@@ -384,32 +384,45 @@ __global__ void __launch_bounds__(256) attention_generic_kernel(T *out, const T 
 }
 
 // The attention of an fp32 decode step (one new row per sequence) straight from the QKV projection: rotation, KV write and the
-// kernel above in one.  Bound by latency: one workgroup per (sequence, head), a key per thread, V dealt to the four waves in parts
-// of 32 positions whose sums are added in wave order; the first K and V loads leave before the rotation.  The new position's k
-// and v come from LDS.  Tiny decoder, 8 environments, 68 keys: 8.5 + 9 us in two launches, 12.6 as one wave, 8.3 here; six steps
-// of a width-1024 decoder of four layers, 700 keys: 4.15 -> 1.66 ms at 8 environments, 6.99 -> 5.84 at 128.
+// kernel above in one.  Bound by latency: WAVES waves per (sequence, head), a key per thread, V in four parts of 32 positions whose
+// sums are added in order; the first K and V loads leave before the rotation.  The new position's k and v come from LDS.  Four waves:
+// tiny decoder, 8 environments, 68 keys: 8.5 + 9 us in two launches, 8.3 here; six steps of a width-1024 decoder of four layers, 700
+// keys: 4.15 -> 1.66 ms at 8 environments, 6.99 -> 5.84 at 128.  One wave, for many pairs of few keys: four pairs share a workgroup, with
+// half the loads in flight a pair's registers shrink from 4 x 162 to 89 a lane, so that 4096 pairs run at once and not in five
+// rounds, and no wave is there for keys that are not.  Either forms every sum in the same order: same bits.
+template <int WAVES>
 __global__ void __launch_bounds__(256) attention_step_kernel(float *out, const float *qkv, const float2 *table, float *kc, float *vc, int pos,
-                                                             int n_heads, int d, int pos_stride, int H) {
+                                                             int n_items, int n_heads, int d, int pos_stride, int H) {
     extern __shared__ float smem[];
     typedef float t8 __attribute__((ext_vector_type(8), aligned(4)));            // (the caller's KV buffer: element alignment)
-    constexpr int NC = 8, NP = 32;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, s = blockIdx.x / n_heads, h = blockIdx.x - s * n_heads;
+    constexpr bool ALONE = WAVES == 1;                                           // a pair per wave, else one per workgroup of four
+    constexpr int NC = ALONE ? 4 : 8, NP = 32, NL = ALONE ? 16 : NP, NT = 64 * WAVES, NV = 4 / WAVES;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = ALONE ? lane : (int)threadIdx.x, part0 = ALONE ? 0 : wave;
+    const int item = ALONE ? blockIdx.x * 4 + wave : blockIdx.x;
+    if (ALONE && item >= n_items) return;
+    auto meet = [&]() {
+        if constexpr (ALONE) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        } else __syncthreads();
+    };
+    const int s = item / n_heads, h = item - s * n_heads;
     const int nk = pos + 1, last = max(pos - 1, 0), half = d / 2, nc = d / 8;    // (addresses past the last stored key: clamped, not used)
-    float *qs = smem, *ks = qs + d, *vs = ks + d, *part = vs + d, *red = part + 4 * d, *sc = red + 8;
+    float *qs = smem + (ALONE ? (size_t)wave * (3 * d + nk) : 0), *ks = qs + d, *vs = ks + d, *sc = vs + d, *part = sc + nk, *red = part + 4 * d;
     const float *row = qkv + (size_t)s * 3 * H + (size_t)h * d;
     const size_t head = (size_t)s * n_heads + h;
     float *kh = kc + head * (size_t)d * pos_stride, *vh = vc + head * (size_t)pos_stride * d;
-    const int i0 = min(tid, half - 1);
+    const int i0 = min(t, half - 1);
     const float2 cs = table[i0];
     const float qa = row[i0], qb = row[i0 + half], ka = row[H + i0], kb = row[H + i0 + half], va = row[2 * H + i0], vb = row[2 * H + i0 + half];
     t8 kr[NC];
-    float vr[NP];
+    float vr[NL];
 #pragma unroll
-    for (int c = 0; c < NC; c++) kr[c] = *(const t8 *)(kh + ((size_t)min(c, nc - 1) * pos_stride + min(tid, last)) * 8);
+    for (int c = 0; c < NC; c++) kr[c] = *(const t8 *)(kh + ((size_t)min(c, nc - 1) * pos_stride + min(t, last)) * 8);
 #pragma unroll
-    for (int u = 0; u < NP; u++) vr[u] = vh[(size_t)min(wave * NP + u, last) * d + min(lane, d - 1)];
-    if (tid < half) {
-        const int i = tid;
+    for (int u = 0; u < NL; u++) vr[u] = vh[(size_t)min(part0 * NP + u, last) * d + min(lane, d - 1)];
+    auto rotate = [&](int i, float2 cs, float qa, float qb, float ka, float kb, float va, float vb) {
         const float k0 = ka * cs.x - kb * cs.y, k1 = kb * cs.x + ka * cs.y;
         qs[i] = qa * cs.x - qb * cs.y;
         qs[i + half] = qb * cs.x + qa * cs.y;
@@ -419,14 +432,19 @@ __global__ void __launch_bounds__(256) attention_step_kernel(float *out, const f
         kh[((size_t)((i + half) >> 3) * pos_stride + pos) * 8 + (i & 7)] = k1;
         vh[(size_t)pos * d + i] = va;
         vh[(size_t)pos * d + i + half] = vb;
+    };
+    if (t < half) rotate(t, cs, qa, qb, ka, kb, va, vb);
+    if (ALONE && t + 64 < half) {                // (head_dim above 128)
+        const int i = t + 64;
+        rotate(i, table[i], row[i], row[i + half], row[H + i], row[H + i + half], row[2 * H + i], row[2 * H + i + half]);
     }
-    __syncthreads();
+    meet();
     const float scale = 1.0f / sqrtf((float)d);
     float mx = -INFINITY;
-    for (int p = tid; p < nk; p += 256) {
+    for (int p = t; p < nk; p += NT) {
         float acc = 0.f;
         for (int c0 = 0; c0 < nc; c0 += NC) {
-            if (p != tid || c0)
+            if (p != t || c0)
 #pragma unroll
                 for (int c = 0; c < NC; c++) kr[c] = *(const t8 *)(kh + ((size_t)min(c0 + c, nc - 1) * pos_stride + min(p, last)) * 8);
 #pragma unroll
@@ -443,33 +461,58 @@ __global__ void __launch_bounds__(256) attention_step_kernel(float *out, const f
         mx = fmaxf(mx, acc);
     }
     mx = wave_max(mx);
-    if (lane == 0) red[wave] = mx;
-    __syncthreads();
-    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    float sum = 0.f;
-    for (int p = tid; p < nk; p += 256) {
-        const float e = expf(sc[p] - mx);
-        sc[p] = e;
-        sum += e;
+    if constexpr (!ALONE) {
+        if (lane == 0) red[wave] = mx;
+        __syncthreads();
+        mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
     }
-    sum = wave_sum(sum);
-    if (lane == 0) red[4 + wave] = sum;
-    __syncthreads();
-    const float inv = 1.0f / (red[4] + red[5] + red[6] + red[7]);
-    for (int i = lane; i < d; i += 64) {
-        float acc = 0.f;
-        for (int p0 = wave * NP; p0 < nk; p0 += 4 * NP) {
-            if (i != lane || p0 != wave * NP)
+    // four sums of every fourth 64 keys, then their sum: the same whichever waves form them
+    float sum[NV];
 #pragma unroll
-                for (int u = 0; u < NP; u++) vr[u] = vh[(size_t)min(p0 + u, last) * d + i];
-#pragma unroll
-            for (int u = 0; u < NP; u++)
-                if (p0 + u < nk) acc += sc[p0 + u] * (p0 + u < pos ? vr[u] : vs[i]);
+    for (int v = 0; v < NV; v++) {
+        sum[v] = 0.f;
+        if (ALONE && v * 64 >= nk) continue;
+        for (int p = v * 64 + t; p < nk; p += 256) {
+            const float e = expf(sc[p] - mx);
+            sc[p] = e;
+            sum[v] += e;
         }
-        part[wave * d + i] = acc;
+        sum[v] = wave_sum(sum[v]);
     }
-    __syncthreads();
-    if (tid < d) out[(size_t)s * H + (size_t)h * d + tid] = (part[tid] + part[d + tid] + part[2 * d + tid] + part[3 * d + tid]) * inv;
+    if constexpr (!ALONE)
+        if (lane == 0) red[4 + wave] = sum[0];
+    meet();
+    float total;
+    if constexpr (ALONE) total = sum[0] + sum[1] + sum[2] + sum[3];
+    else total = red[4] + red[5] + red[6] + red[7];
+    const float inv = 1.0f / total;
+    for (int i = lane; i < d; i += 64) {
+        float acc[NV];
+#pragma unroll
+        for (int v = 0; v < NV; v++) {
+            acc[v] = 0.f;
+            for (int p0 = (part0 + v) * NP; p0 < nk; p0 += 4 * NP) {
+#pragma unroll
+                for (int l = 0; l < NP; l += NL) {
+                    if (l && p0 + l >= nk) break;
+                    if (i != lane || p0 + l != part0 * NP)
+#pragma unroll
+                        for (int u = 0; u < NL; u++) vr[u] = vh[(size_t)min(p0 + l + u, last) * d + i];
+#pragma unroll
+                    for (int u = 0; u < NL; u++) {
+                        const int p = p0 + l + u;
+                        if (p < nk) acc[v] += sc[p] * (p < pos ? vr[u] : vs[i]);
+                    }
+                }
+            }
+        }
+        if constexpr (ALONE) out[(size_t)s * H + (size_t)h * d + i] = (acc[0] + acc[1] + acc[2] + acc[3]) * inv;
+        else part[wave * d + i] = acc[0];
+    }
+    if constexpr (!ALONE) {
+        __syncthreads();
+        if (t < d) out[(size_t)s * H + (size_t)h * d + t] = (part[t] + part[d + t] + part[2 * d + t] + part[3 * d + t]) * inv;
+    }
 }
 
 // ---------------------------------------------------------------------------------- value head
@@ -618,9 +661,20 @@ int launch_attention_step_qkv(float *out, const float *qkv, const float2 *table,
     const int n_items = ra.n_seq * kv.n_heads;
     if (n_items == 0) return 0;
     ProfScope ps("attention_step", 0.0, st);
-    const size_t lds = (size_t)(7 * kv.d + 8 + ra.pos0 + 1) * sizeof(float);   // (at most 40 KB: 8192 keys at head_dim 256)
-    attention_step_kernel<<<n_items, 256, lds, st>>>(out, qkv, table, (float *)kv.k + (size_t)layer * kv.layer_elems, (float *)kv.v + (size_t)layer * kv.layer_elems,
-                                                     ra.pos0, kv.n_heads, kv.d, kv.pos_stride, H);
+    float *k = (float *)kv.k + (size_t)layer * kv.layer_elems, *v = (float *)kv.v + (size_t)layer * kv.layer_elems;
+    const int nk = ra.pos0 + 1;
+    // One wave per pair from eight pairs per key on, up to 80 KB of K per pair (us per step with one and with four waves, in brackets
+    // rotation and attention apart).  head_dim 64: 4096 pairs of 23 keys 15.5 and 42 (28), 103 keys 37 and 52 (58), 303 keys 120 and 129
+    // (139), 1003 keys 369 and 364 (384); 1024 pairs of 23, 103, 303 and 1003 keys 9.6 and 17 (25), 18 and 20, 35 and 38, 119 and 103;
+    // 128 pairs of 23 and 103 keys 10.4 and 9.7, 14 and 10.  8192 pairs: head_dim 16, 1003 keys 241 and 324 (272), 256, 23 keys 41 and 119 (83).
+    // head_dim 256, 1024 pairs of 103 keys: 57 and 52 (95).
+    if (kv.d * nk <= 20480 && n_items >= 8 * nk) {
+        const size_t lds = (size_t)4 * (3 * kv.d + nk) * sizeof(float);    // (at most 21 KB)
+        attention_step_kernel<1><<<(n_items + 3) / 4, 256, lds, st>>>(out, qkv, table, k, v, ra.pos0, n_items, kv.n_heads, kv.d, kv.pos_stride, H);
+    } else {
+        const size_t lds = (size_t)(7 * kv.d + 8 + nk) * sizeof(float);    // (at most 40 KB: 8192 keys at head_dim 256)
+        attention_step_kernel<4><<<n_items, 256, lds, st>>>(out, qkv, table, k, v, ra.pos0, n_items, kv.n_heads, kv.d, kv.pos_stride, H);
+    }
     return vla_check_launch("attention_step");
 }
 int launch_value_head(float *value, const float *h, const float *w, float b, const float *bias, int vd, int n,

@@ -4,9 +4,11 @@ later round."""
 import ctypes
 
 import pytest
+import torch
 
 import vla_inputs as vi
 from paper_2510_06710_amd import binding as vb
+from paper_2510_06710_amd.harness import Rollout
 from parity import GpuCase, compare_rollout, oracle_rollout
 
 pytestmark = pytest.mark.gpu
@@ -37,3 +39,22 @@ def test_a_step_has_a_label_of_its_own():
     counts = {line.rsplit(" ", 3)[0]: int(line.rsplit(" ", 3)[1]) for line in buf.value.decode().splitlines()}
     layers, steps = wl.shape.n_layers, wl.n_action - 1
     assert counts["attention_step"] == layers * steps and counts["attention_generic"] == layers, counts
+
+
+# keys of the three steps: S + 1 .. S + 3.  Many environments take a wave per (environment, head), few take four.
+@pytest.mark.parametrize("S,hidden,heads,many,few", [(1, 16, 1, 71, 7), (30, 512, 32, 33, 1), (62, 1024, 16, 67, 3), (127, 1040, 13, 90, 5),
+                                                     (125, 2048, 16, 65, 2), (77, 768, 3, 220, 40), (30, 1024, 4, 67, 5), (508, 256, 16, 257, 31)])
+def test_a_step_does_not_depend_on_the_batch(S, hidden, heads, many, few):
+    """The four sums of a head's keys and of its values are formed by one wave or by four: the same bits."""
+    shape = _shape(hidden, heads, 64)
+    wl = vi.Workload("waves", shape, batch=many, n_patches=0, n_instr=S, n_action=4)
+    patch, ids = vi.observation(wl, 3, device="cuda:0")
+    run = Rollout(vi.SynthModel(shape, 3, device="cuda:0"), many, S + 4)
+
+    def outputs(n):
+        h, _ = run.prefill(patch[:n].contiguous(), ids[:n].contiguous())
+        return [x[:few].clone() for x in (h, *run.decode(h, S, 4))]
+
+    assert many * heads >= 8 * (S + 3) and few * heads < 8 * (S + 1) and hidden // heads * (S + 3) <= 20480
+    for a, b in zip(outputs(many), outputs(few)):
+        assert torch.equal(a, b)
