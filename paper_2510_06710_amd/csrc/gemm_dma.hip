@@ -602,12 +602,16 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
     if ((int)(blockIdx.x >> 3) >= per_xcd || tile >= total || units < NS) return;
     const int tn = tile / p.tiles_m, tm = tile - tn * p.tiles_m;
 
-    // ---- loads: an instruction covers 16 rows of one half, or 8 rows of both, a whole line each (see the 256 x 256 kernel)
+    // ---- loads: an instruction covers 16 rows of one half (AH, WH), or 8 rows of both, a whole line each (see the 256 x 256 kernel).
+    // Row-major operands are read as whole lines except by 64 x 64 tiles, whose steps are too short for the second half's own
+    // addresses: 40 x 256, K = 9536 36.2 us as halves and 39.6 as lines, 113 x 1792, K = 6336 26.2 and 28.6; 64 x 128 tiles 2 % faster as lines
+    // (median of 69 sizes), 128 x 128 the same.
+    constexpr bool AH = KB || (BMT == 64 && BNT == 64), WH = WKB || (BMT == 64 && BNT == 64);
     const int kb_chunk = ((lane & 3) ^ ((lane >> 3) & 3)) << 4, rm_chunk = ((lane & 7) ^ (lane >> 3)) << 4;
     const int row_bytes = KB ? 64 : K * 2, w_row_bytes = WKB ? 64 : K * 2;
     const unsigned a_half = KB ? (unsigned)p.a_rows * 64u : 64u, w_half = WKB ? (unsigned)p.w_rows * 64u : 64u;
-    const int thread_off = KB ? (lane >> 2) * 64 + kb_chunk : (lane >> 3) * row_bytes + rm_chunk;
-    const int w_thread_off = WKB ? (lane >> 2) * 64 + kb_chunk : (lane >> 3) * w_row_bytes + rm_chunk;
+    const int thread_off = AH ? (lane >> 2) * row_bytes + kb_chunk : (lane >> 3) * row_bytes + rm_chunk;
+    const int w_thread_off = WH ? (lane >> 2) * w_row_bytes + kb_chunk : (lane >> 3) * w_row_bytes + rm_chunk;
     const bf16_t *Wp;
     int w_row0;
     if (epi_swiglu(EPI)) {
@@ -629,15 +633,15 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
 #pragma unroll
         for (int i = 0; i < NA; i++) {
             const int q = wave * NA + i, half = q / (BMT / 16), blk = q % (BMT / 16);
-            if (KB) __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)(base + half * A_HALF + blk * 1024), 16, thread_off,
-                                                             (int)((unsigned)(2 * u + half) * a_half) + blk * 1024, 0, 0);
+            if (AH) __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)(base + half * A_HALF + blk * 1024), 16, thread_off,
+                                                             (int)((unsigned)(2 * u + half) * a_half) + blk * 16 * row_bytes, 0, 0);
             else __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)(base + q * 1024), 16, thread_off, u * 128 + q * 8 * row_bytes, 0, 0);
         }
 #pragma unroll
         for (int i = 0; i < NWI; i++) {
             const int half = wave >> 1, blk = (wave & 1) * NWI + i, row = half * (BNT / 4) + i * 8;
-            if (WKB) __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(w_base + half * W_HALF + blk * 1024), 16, w_thread_off,
-                                                              (int)((unsigned)(2 * u + half) * w_half) + i * 1024, 0, 0);
+            if (WH) __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(w_base + half * W_HALF + blk * 1024), 16, w_thread_off,
+                                                             (int)((unsigned)(2 * u + half) * w_half) + i * 16 * w_row_bytes, 0, 0);
             else __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(w_base + ((wave & 1) * (BNT / 2) + row) * 128), 16, w_thread_off,
                                                           u * 128 + row * w_row_bytes, 0, 0);
         }
@@ -645,13 +649,13 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
 
     const int lds0 = (int)(size_t)(lds_void *)lds, a_row0 = wm * (BMT / 2), w_row0_lds = wn * (BNT / 2);
     const int kb_off = l16 * 64 + ((kq ^ ((l16 >> 1) & 3)) << 4), rm_off = l16 * 128 + ((kq ^ (l16 & 7)) << 4);
-    const int a_base = lds0 + (KB ? a_row0 * 64 + kb_off : a_row0 * 128 + rm_off);
-    const int w_base = lds0 + 2 * A_HALF + (WKB ? w_row0_lds * 64 + kb_off : w_row0_lds * 128 + rm_off);
+    const int a_base = lds0 + (AH ? a_row0 * 64 + kb_off : a_row0 * 128 + rm_off);
+    const int w_base = lds0 + 2 * A_HALF + (WH ? w_row0_lds * 64 + kb_off : w_row0_lds * 128 + rm_off);
     // STEP: lane l reads row l % 32 of a 32-row block, from half l / 32 of the unit (chunks 4 (l / 32) .. + 3 of a whole line)
     constexpr int MB2 = MB / 2, NB2 = NB / 2;
     const int l32 = lane & 31, hh = lane >> 5, fsw32 = (l32 >> 1) & 3;
-    const int a_step = lds0 + (KB ? hh * A_HALF + (a_row0 + l32) * 64 : (a_row0 + l32) * 128);
-    const int w_step = lds0 + 2 * A_HALF + (WKB ? hh * W_HALF + (w_row0_lds + l32) * 64 : (w_row0_lds + l32) * 128);
+    const int a_step = lds0 + (AH ? hh * A_HALF + (a_row0 + l32) * 64 : (a_row0 + l32) * 128);
+    const int w_step = lds0 + 2 * A_HALF + (WH ? hh * W_HALF + (w_row0_lds + l32) * 64 : (w_row0_lds + l32) * 128);
     f32x4_t acc[STEP ? 1 : NB][STEP ? 1 : MB];
     f32x16_t acc32[STEP ? NB2 : 1][STEP ? MB2 : 1], sum32[STEP ? NB2 : 1][STEP ? MB2 : 1];
     if constexpr (STEP) {
@@ -703,13 +707,13 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
             for (int q = 0; q < 2; q++) {
                 const int ck = ((2 * h + q) ^ fsw32) << 4, cr = ((4 * hh + 2 * h + q) ^ (l32 & 7)) << 4;
 #pragma unroll
-                for (int j = 0; j < NB2; j++) wf[h][q * NB2 + j] = lds_read<0>(w_step + so + (WKB ? ck + j * 2048 : cr + j * 4096));
+                for (int j = 0; j < NB2; j++) wf[h][q * NB2 + j] = lds_read<0>(w_step + so + (WH ? ck + j * 2048 : cr + j * 4096));
 #pragma unroll
-                for (int i = 0; i < MB2; i++) af[h][q * MB2 + i] = lds_read<0>(a_step + so + (KB ? ck + i * 2048 : cr + i * 4096));
+                for (int i = 0; i < MB2; i++) af[h][q * MB2 + i] = lds_read<0>(a_step + so + (AH ? ck + i * 2048 : cr + i * 4096));
             }
         } else {
-            read_frags<WKB ? h * W_HALF : 0, WKB ? 1024 : 2048>(wf[h], (WKB || h == 0 ? w_base : w_base ^ 64) + so, std::make_integer_sequence<int, NB>{});
-            read_frags<KB ? h * A_HALF : 0, KB ? 1024 : 2048>(af[h], (KB || h == 0 ? a_base : a_base ^ 64) + so, std::make_integer_sequence<int, MB>{});
+            read_frags<WH ? h * W_HALF : 0, WH ? 1024 : 2048>(wf[h], (WH || h == 0 ? w_base : w_base ^ 64) + so, std::make_integer_sequence<int, NB>{});
+            read_frags<AH ? h * A_HALF : 0, AH ? 1024 : 2048>(af[h], (AH || h == 0 ? a_base : a_base ^ 64) + so, std::make_integer_sequence<int, MB>{});
         }
     };
     // STEP: the sums of a part join those of the parts before
