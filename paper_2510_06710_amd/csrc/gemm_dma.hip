@@ -902,7 +902,7 @@ int launch_small(DmaGemmParams p, hipStream_t st) {
 // what the four projections of the 7B shape took at 64 .. 18432 rows (per unit of K = 64 and launch):
 //   32 mb x 256     a round of 256 tiles 333 + 107 mb per unit (mb = 8: 1190) + 8000 (prologue and epilogue)
 //   64 x 64         310 up to 150 tiles, then 120 + 1.25 per tile (plain and residual outputs only)
-//   128 x 64        445 where one workgroup per CU takes all tiles (plain and residual outputs, more than 128 rows)
+//   128 x 64        445 where one workgroup per CU takes all tiles (plain and residual outputs, more than 128 rows, see below)
 //   64 x 128        470 up to 276 tiles, then 1.7 per tile (SwiGLU, two weight panels per tile: 620, at least 1000)
 //   128 x 128       640 with one workgroup per CU (3 stages of LDS), 950 for every 512 with two (2 stages)
 // E.g. 288 rows, K = 4096: QKV 86 -> 55 us (64 x 128), O and down (K = 11008) on average 133 -> 58 (64 x 64 and 64 x 128) -> 52
@@ -910,6 +910,12 @@ int launch_small(DmaGemmParams p, hipStream_t st) {
 // Tiles lower than 256 rows where the rounds of 256 tiles come out fuller: 2,304 rows, O and down on average 154 -> 133 us (160 rows
 // per tile); 4,608 rows 301 -> 250 (160); 3,384 rows, QKV 258 -> 243 (224); 7,150 rows 514 -> 484 and 339 -> 326 (224).  Their
 // rounds cost more per row, as each loads all of the tile's weights: below 160 rows the small tiles are faster.
+// Where the estimates alone would take a slower tile than there was before (1,500 sizes, weights from HBM; now none): 128 x 64
+// moves as many bytes as 64 x 128 and wins only where most of them are weights (not more rows than columns) and the steps are many (K
+// from 1024): 7,639 x 256, K = 768 8.2 us with 64 x 128, 10.6 with 128 x 64; 829 x 1792, K = 8768 63 and 56.  64 x 64 tiles of at most
+// 288 keep a CU each, all but a few: 315 x 3584, K = 896 6.3 us, 7.3 with 128 x 64.  Low large tiles that do not fill a round stream
+// at a lower rate than a single round of 128 x 128: 1,421 x 4096, K = 11008 152 us, 198 with 160 x 256; not so where the columns are few (7,208
+// x 1024: 160 x 256 28 % faster).
 enum SmallTile { TILE_LARGE = 0, TILE_64x64, TILE_128x64, TILE_64x128, TILE_128x128_1, TILE_128x128_2 };
 struct TileChoice { SmallTile small; int mb; };
 template <int EPI>
@@ -921,12 +927,14 @@ TileChoice choose_tile(const DmaGemmParams &p, int mb_low) {          // large t
     auto offer = [&](TileChoice tile, long ns) {
         if (best_ns < 0 || ns < best_ns) { best = tile; best_ns = ns; }
     };
+    if (t128 <= 512 && p.M <= cols) mb_low = 8;
     for (int mb = 8; mb >= mb_low; mb--) {
         const long tiles = (p.M + 32L * mb - 1) / (32L * mb) * (cols / 256);
         offer({TILE_LARGE, mb}, (tiles + 255) / 256 * (units * (333 + 107 * mb) + 8000));
     }
     if (EPI == EPI_STORE || EPI == EPI_RESIDUAL) offer({TILE_64x64, 0}, units * (2 * t64 <= 150 ? 310 : 120 + 5 * (2 * t64) / 4));
-    if ((EPI == EPI_STORE || EPI == EPI_RESIDUAL) && p.M > 128 && 2 * t128 <= 256) offer({TILE_128x64, 0}, units * 445);
+    if ((EPI == EPI_STORE || EPI == EPI_RESIDUAL) && p.M > 128 && p.M <= cols && units >= 16 && 2 * t64 > 288 && 2 * t128 <= 256)
+        offer({TILE_128x64, 0}, units * 445);
     if (epi_swiglu(EPI)) offer({TILE_64x128, 0}, units * (t64 <= 276 ? 620 : t64 <= 588 ? 1000 : 17 * t64 / 10));
     else offer({TILE_64x128, 0}, units * (t64 <= 276 ? 470 : 17 * t64 / 10));
     if (t128 <= 256) offer({TILE_128x128_1, 0}, units * 640);
