@@ -144,7 +144,7 @@ def bench_recompute(args, wl, torch, vi, vb, Rollout):
     roofline = None
     if dom:
         ach = dom["work"] / (dom["ms"] * 1e-3) / 1e12
-        roofline = {"bound": "mfma", "kernel": "gemm_bf16_dma_kernel<EPI_SWIGLU, k-blocked, unit barrier> (gate/up projection)",
+        roofline = {"bound": "mfma", "kernel": "gemm_bf16_dma_kernel<EPI_SWIGLU, k-blocked> (gate/up projection)",
                     "achieved": ach, "peak": MI355X_BF16_TFLOPS, "unit": "TFLOP/s", "frac": ach / MI355X_BF16_TFLOPS,
                     "launches": dom["count"], "avg_launch_ms": dom["ms"] / dom["count"], "traffic": None}
     out = {"metric": "stored rollouts/sec, log-prob recompute (7B shape), % MFMA roofline", "value": N / (ms * 1e-3),
@@ -392,9 +392,9 @@ def main():
         r = prof_prefill[dom]
         achieved = r["work"] / (r["ms"] * 1e-3) / 1e12
         traffic, traffic_source = read_traffic(os.path.join(ROOT, "profiles", "gemm_swiglu_cfg3_traffic.txt"),
-                                               "gemm_bf16_dma_kernel<2, true, true>",
+                                               "gemm_bf16_dma_kernel<2, true, true, 8>",
                                                os.path.join(ROOT, "paper_2510_06710_amd", "csrc", "gemm_dma.hip"))
-        roofline = {"bound": "mfma", "kernel": "gemm_bf16_dma_kernel<EPI_SWIGLU, k-blocked, unit barrier> (gate/up projection, prefill)",
+        roofline = {"bound": "mfma", "kernel": "gemm_bf16_dma_kernel<EPI_SWIGLU, k-blocked> (gate/up projection, prefill)",
                     "achieved": achieved, "peak": MI355X_BF16_TFLOPS, "unit": "TFLOP/s",
                     "frac": achieved / MI355X_BF16_TFLOPS, "launches": r["count"],
                     "avg_launch_ms": r["ms"] / r["count"],

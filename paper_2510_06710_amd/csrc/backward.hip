@@ -5,10 +5,10 @@
 // Structure.  Stored rollouts are processed in micro-batches.  For one micro-batch: (1) the forward pass of the
 // recompute (its own fused kernels), keeping the residual stream at the input of every layer (fp32 [layers][rows, H]),
 // and the head, which also returns logp; (2) the head's backward puts d L / d x on the rows that predict action
-// tokens; (3) layers in reverse: the layer's forward is run again from its kept input, this time with unfused
+// tokens; (3) layers in reverse: the layer's forward is run again from its kept input, this time with
 // kernels that leave every intermediate the chain rule needs, then the chain rule walks back through the
 // down projection, SwiGLU, gate / up, the FFN norm, the O projection, attention, the rotation, Q / K / V and the
-// attention norm.  With keep_activations, (1) is instead a forward with the unfused kernels that leaves every layer's
+// attention norm.  With keep_activations, (1) is instead a forward with these kernels that leaves every layer's
 // intermediates in a set of its own (one per layer, for one micro-batch), and (3) runs no layer a second time.  Every large contraction -- the seven forward projections and the four input-gradient products
 // dY . W, which run as the same "activation x weight^T" GEMM on a transposed copy of the weights made per layer --
 // goes through the library's GEMM dispatch (MFMA kernels for bf16 shapes they cover).  Attention (scores, softmax,
@@ -803,7 +803,7 @@ struct Backward {
     // 117.6 -> 104.3; a layer in between takes 14.4).
     int rows_of(int l) const { return tail && l == L - 1 ? A : R; }      // rows per sequence after K and V
 
-    // Layer l forward on the stream in ws.X with unfused kernels that leave in `a` everything its backward reads.
+    // Layer l forward on the stream in ws.X with kernels that leave in `a` everything its backward reads.
     // with_down = false stops at the SwiGLU output (a layer run again for its backward: nothing reads its output) and
     // leaves ws.X = the stream after the attention block.
     int layer_forward(int l, const Acts &a, bool with_down) {

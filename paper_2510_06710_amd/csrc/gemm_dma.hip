@@ -910,12 +910,13 @@ int launch_small(DmaGemmParams p, hipStream_t st) {
 // Tiles lower than 256 rows where the rounds of 256 tiles come out fuller: 2,304 rows, O and down on average 154 -> 133 us (160 rows
 // per tile); 4,608 rows 301 -> 250 (160); 3,384 rows, QKV 258 -> 243 (224); 7,150 rows 514 -> 484 and 339 -> 326 (224).  Their
 // rounds cost more per row, as each loads all of the tile's weights: below 160 rows the small tiles are faster.
-// Where the estimates alone would take a slower tile than there was before (1,500 sizes, weights from HBM; now none): 128 x 64
+// Where the estimates alone would take a slower tile than there was before: 128 x 64
 // moves as many bytes as 64 x 128 and wins only where most of them are weights (not more rows than columns) and the steps are many (K
 // from 1024): 7,639 x 256, K = 768 8.2 us with 64 x 128, 10.6 with 128 x 64; 829 x 1792, K = 8768 63 and 56.  64 x 64 tiles of at most
 // 288 keep a CU each, all but a few: 315 x 3584, K = 896 6.3 us, 7.3 with 128 x 64.  Low large tiles that do not fill a round stream
-// at a lower rate than a single round of 128 x 128: 1,421 x 4096, K = 11008 152 us, 198 with 160 x 256; not so where the columns are few (7,208
-// x 1024: 160 x 256 28 % faster).
+// at a lower rate than a single round of 128 x 128: 1,421 x 4096, K = 11008 152 us, 198 with 160 x 256 (whole calls, up to 448 such tiles:
+// gradient pass of three layers, 1,415 rows 5.12 ms, 5.30 with low tiles; prefill of 1,132 rows 1.87 and 2.01; at 512, 1,981 rows, 6.00 and
+// 5.84); not so where the columns are few (7,208 x 1024: 160 x 256 28 % faster).
 enum SmallTile { TILE_LARGE = 0, TILE_64x64, TILE_128x64, TILE_64x128, TILE_128x128_1, TILE_128x128_2 };
 struct TileChoice { SmallTile small; int mb; };
 template <int EPI>
@@ -927,7 +928,7 @@ TileChoice choose_tile(const DmaGemmParams &p, int mb_low) {          // large t
     auto offer = [&](TileChoice tile, long ns) {
         if (best_ns < 0 || ns < best_ns) { best = tile; best_ns = ns; }
     };
-    if (t128 <= 512 && p.M <= cols) mb_low = 8;
+    if (t128 <= 448 && p.M <= cols) mb_low = 8;
     for (int mb = 8; mb >= mb_low; mb--) {
         const long tiles = (p.M + 32L * mb - 1) / (32L * mb) * (cols / 256);
         offer({TILE_LARGE, mb}, (tiles + 255) / 256 * (units * (333 + 107 * mb) + 8000));
