@@ -238,6 +238,7 @@ template <typename T>
 static int run_gemm(const vla_config &c, GemmArgs g, void *skinny_scratch, hipStream_t st) {
     if (c.dtype == VLA_DTYPE_BF16) {
         int r = 0;
+        if (skinny_scratch && g.res && g.res != g.C) { vla_set_error("internal: a step's product is added in place"); return VLA_ESHAPE; }
         if (skinny_scratch && !(force_generic() & 2)) {
             // above 128 rows the work is MFMA bound and the large tile with split K does better
             if (g.M > 128 && !(force_generic() & 1)) {
@@ -273,9 +274,10 @@ static int run_rmsnorm(const vla_config &c, void *out, const float *X, const voi
 }
 
 // One decoder layer on k-blocked activations and repacked weights: every GEMM is the direct-to-LDS kernel,
-// whose operands are then whole cache lines (multi-row bf16 forwards at head_dim 128 only).
+// whose operands are then whole cache lines (multi-row bf16 forwards at head_dim 128 only).  The residual stream comes from x_in,
+// is in ws.X after the attention block and goes to x_out (any of them may be the same).
 static int run_layer_kblocked(const vla_model *m, const Workspace &ws, const RowsArgs &ra, const KvView &kv, int l, int kl,
-                              hipStream_t st) {
+                              const float *x_in, float *x_out, hipStream_t st) {
     const vla_config &c = m->cfg;
     const int H = c.hidden, F = c.ffn, M = ra.n_seq * ra.R;
     const vla_layer_weights &lw = m->layers[l], &pk = m->packed[l];
@@ -284,7 +286,7 @@ static int run_layer_kblocked(const vla_model *m, const Workspace &ws, const Row
         if (r == 0) { vla_set_error("internal: k-blocked path declined at %s", what); return (int)VLA_ESHAPE; }
         return r < 0 ? r : 0;
     };
-    if ((rc = must(try_rmsnorm_bf16((bf16_t *)ws.Nrm, ws.X, (const float *)lw.attn_norm, M, H, c.rms_eps, ws.a_rows, st), "attn norm"))) return rc;
+    if ((rc = must(try_rmsnorm_bf16((bf16_t *)ws.Nrm, x_in, (const float *)lw.attn_norm, M, H, c.rms_eps, ws.a_rows, st), "attn norm"))) return rc;
     QkvRopeArgs qa{ws.Q, ws.rope, &kv, kl, &ra};
     GemmArgs g{};
     g.A = ws.Nrm; g.W[0] = pk.wq; g.W[1] = pk.wk; g.W[2] = pk.wv; g.n_seg = 3; g.segN = H; g.C = nullptr; g.M = M; g.K = H;
@@ -292,7 +294,7 @@ static int run_layer_kblocked(const vla_model *m, const Workspace &ws, const Row
     if ((rc = must(try_gemm_bf16_dma(g, st), "QKV projection"))) return rc;
     if ((rc = must(try_attention_prefill_bf16((bf16_t *)ws.AO, (const bf16_t *)ws.Q, kv, kl, ra, H, ws.vt, ws.a_rows, st), "attention"))) return rc;
     g = GemmArgs{};
-    g.A = ws.AO; g.W[0] = pk.wo; g.n_seg = 1; g.segN = H; g.C = ws.X; g.M = M; g.K = H; g.epilogue = EPI_RESIDUAL;
+    g.A = ws.AO; g.W[0] = pk.wo; g.n_seg = 1; g.segN = H; g.C = ws.X; g.res = x_in; g.M = M; g.K = H; g.epilogue = EPI_RESIDUAL;
     g.a_rows = ws.a_rows; g.kblocked = 1;
     if ((rc = must(try_gemm_bf16_dma(g, st), "O projection"))) return rc;
     if ((rc = must(try_rmsnorm_bf16((bf16_t *)ws.Nrm, ws.X, (const float *)lw.ffn_norm, M, H, c.rms_eps, ws.a_rows, st), "ffn norm"))) return rc;
@@ -301,7 +303,7 @@ static int run_layer_kblocked(const vla_model *m, const Workspace &ws, const Row
     g.epilogue = EPI_SWIGLU; g.a_rows = ws.a_rows; g.kblocked = 1;
     if ((rc = must(try_gemm_bf16_dma(g, st), "gate/up projection"))) return rc;
     g = GemmArgs{};
-    g.A = ws.ACT; g.W[0] = pk.w_down; g.n_seg = 1; g.segN = H; g.C = ws.X; g.M = M; g.K = F; g.epilogue = EPI_RESIDUAL;
+    g.A = ws.ACT; g.W[0] = pk.w_down; g.n_seg = 1; g.segN = H; g.C = x_out; g.res = ws.X; g.M = M; g.K = F; g.epilogue = EPI_RESIDUAL;
     g.a_rows = ws.a_rows; g.kblocked = 1;
     return must(try_gemm_bf16_dma(g, st), "down projection");
 }
@@ -316,11 +318,11 @@ struct TailSpec { int first, count; };
 // 32-layer prefill.  Not worth it when the tail is a large share of the rows.
 static bool use_tail(const TailSpec *tail, int R) { return tail && tail->count >= 1 && tail->count * 4 <= R; }
 
-// Last layer, tail form: K, V of all rows (ws.X / ws.Nrm as in any layer), then the rest of the layer on the packed
+// Last layer, tail form: K, V of all rows (stream x_in, ws.Nrm as in any layer), then the rest of the layer on the packed
 // tail rows (ws.tX and friends) with the kernels a forward of that many rows would use.
 template <typename T>
 static int run_last_layer_tail(const vla_model *m, const Workspace &ws, const RowsArgs &ra, const KvView &kv, int l, int kl,
-                               const TailSpec &tail, bool kb, hipStream_t st) {
+                               const TailSpec &tail, bool kb, const float *x_in, hipStream_t st) {
     const vla_config &c = m->cfg;
     const int H = c.hidden, F = c.ffn, M = ra.n_seq * ra.R, d = H / c.n_heads, Mt = ra.n_seq * tail.count;
     const vla_layer_weights &lw = m->layers[l];
@@ -332,11 +334,11 @@ static int run_last_layer_tail(const vla_model *m, const Workspace &ws, const Ro
         GemmArgs g{};
         g.A = ws.Nrm; g.n_seg = 2; g.segN = H; g.C = nullptr; g.M = M; g.K = H; g.epilogue = EPI_QKV_ROPE; g.rope = &qa; g.a_rows = ws.a_rows;
         if (kb) {
-            if ((rc = try_rmsnorm_bf16((bf16_t *)ws.Nrm, ws.X, (const float *)lw.attn_norm, M, H, c.rms_eps, ws.a_rows, st)) <= 0)
+            if ((rc = try_rmsnorm_bf16((bf16_t *)ws.Nrm, x_in, (const float *)lw.attn_norm, M, H, c.rms_eps, ws.a_rows, st)) <= 0)
                 return rc < 0 ? rc : (vla_set_error("internal: k-blocked RMSNorm declined"), (int)VLA_ESHAPE);
             g.W[0] = m->packed[l].wk; g.W[1] = m->packed[l].wv; g.kblocked = 1;
         } else {
-            if ((rc = run_rmsnorm<T>(c, ws.Nrm, ws.X, lw.attn_norm, M, 0, st))) return rc;
+            if ((rc = run_rmsnorm<T>(c, ws.Nrm, x_in, lw.attn_norm, M, 0, st))) return rc;
             g.W[0] = lw.wk; g.W[1] = lw.wv;
         }
         rc = try_gemm_bf16_dma(g, st);
@@ -345,7 +347,7 @@ static int run_last_layer_tail(const vla_model *m, const Workspace &ws, const Ro
         kv_done = rc == 1;
     }
     if (!kv_done) {          // plain path: the full projection (its q rows are not used), rotation and KV write
-        if ((rc = run_rmsnorm<T>(c, ws.Nrm, ws.X, lw.attn_norm, M, 0, st))) return rc;
+        if ((rc = run_rmsnorm<T>(c, ws.Nrm, x_in, lw.attn_norm, M, 0, st))) return rc;
         GemmArgs g{};
         g.A = ws.Nrm; g.W[0] = lw.wq; g.W[1] = lw.wk; g.W[2] = lw.wv; g.n_seg = 3; g.segN = H; g.C = ws.QKV; g.M = M; g.K = H;
         g.epilogue = EPI_STORE; g.a_rows = ws.a_rows;
@@ -356,7 +358,7 @@ static int run_last_layer_tail(const vla_model *m, const Workspace &ws, const Ro
         if (rc) return rc;
     }
     // ---- the tail rows: q, attention against the layer's K and V, O projection, feed-forward block
-    if ((rc = launch_gather_rows(ws.tX, ws.X, ra.n_seq, ra.R, tail.first, tail.count, H, st))) return rc;
+    if ((rc = launch_gather_rows(ws.tX, x_in, ra.n_seq, ra.R, tail.first, tail.count, H, st))) return rc;
     if ((rc = run_rmsnorm<T>(c, ws.tNrm, ws.tX, lw.attn_norm, Mt, 0, st))) return rc;
     GemmArgs g{};
     g.A = ws.tNrm; g.W[0] = lw.wq; g.n_seg = 1; g.segN = H; g.C = ws.tQf; g.M = Mt; g.K = H; g.epilogue = EPI_STORE; g.a_rows = ws.t_a_rows;
@@ -392,7 +394,8 @@ static bool step_norms(const vla_config &c, const Workspace &ws, int M, int N) {
 
 // `tail` (may be NULL): the rows whose final hidden state the caller reads.  Where use_tail() holds, the last layer
 // is run in its tail form and the result of those rows is in ws.tX (packed), not in ws.X.  `prepared`: ws.rope and, where
-// the QKV projection does not form it itself, the first layer's norm are there (NextStep).
+// the QKV projection does not form it itself, the first layer's norm are there (NextStep).  keep (may be NULL): [layers][M, H], the
+// stream at the input of every layer, the first one's put there by the caller (otherwise in ws.X).
 template <typename T>
 static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &ra, const KvView &kv,
                       bool kv_single_layer, hipStream_t st, const TailSpec *tail = nullptr, float *keep = nullptr, bool prepared = false) {
@@ -414,21 +417,32 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
     auto give_norm = [&](GemmArgs &g, const void *gain) { g.norm_x = ws.X; g.norm_gain = (const float *)gain; g.norm_eps = c.rms_eps; };
     bool have_nrm = prepared && !qkv_norms;          // the sampler or the previous layer's down projection already wrote this layer's Nrm
     const bool tail_form = use_tail(tail, ra.R) && ws.tail_rows == tail->count && ra.R > 1;
+    const bool copies = keep && ra.R == 1;
+    auto copy_stream = [&](float *dst, const float *src) {
+        if (dst != src && hipMemcpyAsync(dst, src, (size_t)M * H * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) {
+            vla_set_error("copy of the residual stream failed");
+            return (int)VLA_EHIP;
+        }
+        return 0;
+    };
     for (int l = 0; l < c.n_layers; l++) {
         const vla_layer_weights &lw = m->layers[l];
         int kl = kv_single_layer ? 0 : l;
-        // keep: the caller wants the residual stream at the input of every layer
-        if (keep && hipMemcpyAsync(keep + (size_t)l * M * H, ws.X, (size_t)M * H * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) {
-            vla_set_error("copy of the residual stream failed");
-            return VLA_EHIP;
+        // keep: the layers read their input there, and write their output to the next one's (one row per sequence: the kernels of
+        // decode steps add in place, so the stream is copied)
+        const float *x_in = keep ? keep + (size_t)l * M * H : ws.X;
+        float *x_out = keep && l + 1 < c.n_layers ? keep + (size_t)(l + 1) * M * H : ws.X;
+        if (copies) {
+            if ((rc = copy_stream(ws.X, x_in))) return rc;
+            x_in = ws.X;
         }
-        if (tail_form && l == c.n_layers - 1) return run_last_layer_tail<T>(m, ws, ra, kv, l, kl, *tail, kb, st);
+        if (tail_form && l == c.n_layers - 1) return run_last_layer_tail<T>(m, ws, ra, kv, l, kl, *tail, kb, x_in, st);
         if (kb) {
-            if ((rc = run_layer_kblocked(m, ws, ra, kv, l, kl, st))) return rc;
+            if ((rc = run_layer_kblocked(m, ws, ra, kv, l, kl, x_in, x_out, st))) return rc;
             continue;
         }
         const bool qkv_norm = qkv_norms && !have_nrm;
-        if (!have_nrm && !qkv_norm && (rc = run_rmsnorm<T>(c, ws.Nrm, ws.X, lw.attn_norm, M, 0, st))) return rc;
+        if (!have_nrm && !qkv_norm && (rc = run_rmsnorm<T>(c, ws.Nrm, x_in, lw.attn_norm, M, 0, st))) return rc;
         have_nrm = false;
         // single-row forwards stream the weights from HBM: hand the GEMMs the repacked copies as well, where they exist
         const vla_layer_weights *pk = (ra.R == 1 && !m->packed.empty() && kblocked_shape_ok(c)) ? &m->packed[l] : nullptr;
@@ -471,7 +485,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         }
         if (!done && (rc = launch_attention_generic<T>((T *)ws.AO, (const T *)ws.Q, kv, kl, ra, H, st))) return rc;
         g = GemmArgs{};
-        g.A = ws.AO; g.W[0] = lw.wo; g.n_seg = 1; g.segN = H; g.C = ws.X; g.M = M; g.K = H; g.epilogue = EPI_RESIDUAL; g.a_rows = ws.a_rows;
+        g.A = ws.AO; g.W[0] = lw.wo; g.n_seg = 1; g.segN = H; g.C = ws.X; g.res = x_in; g.M = M; g.K = H; g.epilogue = EPI_RESIDUAL; g.a_rows = ws.a_rows;
         g.step = ra.R == 1;
         if (pk) g.Wkb[0] = pk->wo;
         ds = 0;
@@ -491,7 +505,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         if (pk) { g.Wkb[0] = pk->w_gate; g.Wkb[1] = pk->w_up; }
         if ((rc = run_gemm<T>(c, g, ws.skinny, st))) return rc;
         g = GemmArgs{};
-        g.A = ws.ACT; g.W[0] = lw.w_down; g.n_seg = 1; g.segN = H; g.C = ws.X; g.M = M; g.K = F; g.epilogue = EPI_RESIDUAL; g.a_rows = ws.a_rows;
+        g.A = ws.ACT; g.W[0] = lw.w_down; g.n_seg = 1; g.segN = H; g.C = copies ? ws.X : x_out; g.res = ws.X; g.M = M; g.K = F; g.epilogue = EPI_RESIDUAL; g.a_rows = ws.a_rows;
         g.step = ra.R == 1;
         if (pk) g.Wkb[0] = pk->w_down;
         ds = 0;
@@ -504,6 +518,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
             if (rc < 0) return rc;
             have_nrm = next_gain != nullptr;
         }
+        if (copies && (rc = copy_stream(x_out, ws.X))) return rc;
     }
     return 0;
 }
@@ -643,10 +658,10 @@ static int forward_streams_impl(vla_model *m, void *fw_ws, int n_max, const void
     const int S = P + T_, H = c.hidden, R = (mode == VLA_MODE_AR) ? S + A - 1 : S + A;
     int rc;
     Workspace ws = plan_workspace(c, (char *)fw_ws, n_max, R, R, 0, true, tail_rows);
-    if ((rc = launch_embed_prefix<T>(ws.X, (const T *)patch, ids, (const T *)m->w.embed, n, P, T_, R, H, c.vocab, st))) return rc;
+    if ((rc = launch_embed_prefix<T>(keep, (const T *)patch, ids, (const T *)m->w.embed, n, P, T_, R, H, c.vocab, st))) return rc;
     if (mode == VLA_MODE_AR) {
-        if ((rc = launch_embed_tokens<T>(ws.X, bins, A, A - 1, (const T *)m->w.embed, n, R, S, H, c.vocab, st))) return rc;
-    } else if ((rc = launch_embed_slots<T>(ws.X, (const T *)slot_embed, n, A, R, S, H, st))) return rc;
+        if ((rc = launch_embed_tokens<T>(keep, bins, A, A - 1, (const T *)m->w.embed, n, R, S, H, c.vocab, st))) return rc;
+    } else if ((rc = launch_embed_slots<T>(keep, (const T *)slot_embed, n, A, R, S, H, st))) return rc;
     RowsArgs ra{n, R, 0, (mode == VLA_MODE_AR) ? 0x7fffffff : S};
     KvView kv;
     kv.layer_elems = kv_layer_elems(c, n_max);

@@ -741,10 +741,10 @@ struct Backward {
     int ws_mb;       // rollouts per micro-batch the workspace is laid out for
     static constexpr bool MF = sizeof(T) == 2;      // bf16 storage: attention matrices on the matrix cores
 
-    int gemm(const void *A, const void *W0, const void *W1, const void *W2, int n_seg, int segN, float *C, int K, int rows, int epilogue = EPI_STORE) {
+    int gemm(const void *A, const void *W0, const void *W1, const void *W2, int n_seg, int segN, float *C, int K, int rows, int epilogue = EPI_STORE, const float *res = nullptr) {
         GemmArgs g{};
         g.A = A; g.W[0] = W0; g.W[1] = W1; g.W[2] = W2; g.n_seg = n_seg; g.segN = segN; g.C = C; g.M = rows; g.K = K;
-        g.epilogue = epilogue; g.a_rows = ws.a_rows;
+        g.epilogue = epilogue; g.a_rows = ws.a_rows; g.res = res;
         return vla_gemm_dispatch(c, g, st);
     }
     int transpose(const void *W, int N, int K, int ldt, int col0) {
@@ -789,11 +789,6 @@ struct Backward {
         if (F % 4 == 0) launch(std::integral_constant<int, 4>{}, dim3((F / 4 + 255) / 256, y));
         else launch(std::integral_constant<int, 1>{}, dim3((F + 255) / 256, y));
     }
-    int copy_stream(float *dst, const float *src, int rows) {
-        if (dst == src) return 0;
-        if (hipMemcpyAsync(dst, src, (size_t)rows * H * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) { vla_set_error("backward: copy failed"); return VLA_EHIP; }
-        return 0;
-    }
 
     // The top layer.  Its output is read on the last A rows of every sequence only, so everything after its q | k | v projection
     // and rotation is computed, and differentiated, for those rows alone, packed [n * A, ...]: attention, O projection,
@@ -803,18 +798,17 @@ struct Backward {
     // 117.6 -> 104.3; a layer in between takes 14.4).
     int rows_of(int l) const { return tail && l == L - 1 ? A : R; }      // rows per sequence after K and V
 
-    // Layer l forward on the stream in ws.X with kernels that leave in `a` everything its backward reads.
-    // with_down = false stops at the SwiGLU output (a layer run again for its backward: nothing reads its output) and
-    // leaves ws.X = the stream after the attention block.
-    int layer_forward(int l, const Acts &a, bool with_down) {
+    // Layer l forward on the stream in a.x_in with kernels that leave in `a` everything its backward reads; its output goes to x_out
+    // (the layer's rows, packed in the top layer).  NULL stops at the SwiGLU output (a layer run again for its backward: nothing
+    // reads its output).
+    int layer_forward(int l, const Acts &a, float *x_out) {
         const vla_layer_weights &lw = m->layers[l];
         const T *Q = (const T *)a.QKVr;
         const int Rp = (R + 3) & ~3, Rq = rows_of(l), Mq = n * Rq;
         const long RR = (long)Rq * Rp, rowsH3 = (long)R * 3 * H;
         const bool causal = full_from >= R && Rq == R;
         int rc;
-        if (ws.keep && (rc = copy_stream(a.x_in, ws.X, M))) return rc;       // (otherwise ws.X was loaded from there)
-        if ((rc = launch_rmsnorm<T>((T *)a.Nrm, ws.X, (const float *)lw.attn_norm, M, H, c.rms_eps, st))) return rc;
+        if ((rc = launch_rmsnorm<T>((T *)a.Nrm, a.x_in, (const float *)lw.attn_norm, M, H, c.rms_eps, st))) return rc;
         {   // the rotation rides the projection's epilogue where that kernel takes the shape: no fp32 q | k | v in memory (9,408 rows
             // of 3 x 4096: the pass over it took 174 us; 665 for both now)
             const KvView heads_of{nullptr, nullptr, 0, n, nh, d, 0};
@@ -846,10 +840,9 @@ struct Backward {
             if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
             if (!MF && (rc = cast(a.AO, ws.Tmp, H, Mq))) return rc;
         }
-        if (Rq != R && (rc = launch_gather_rows(ws.X, a.x_in, n, R, R - Rq, Rq, H, st))) return rc;
-        if ((rc = gemm(a.AO, lw.wo, nullptr, nullptr, 1, H, ws.X, H, Mq, EPI_RESIDUAL))) return rc;     // x_mid = x_in + O(...)
-        if ((rc = copy_stream(a.x_mid, ws.X, Mq))) return rc;
-        if ((rc = launch_rmsnorm<T>((T *)a.Nrm2, ws.X, (const float *)lw.ffn_norm, Mq, H, c.rms_eps, st))) return rc;
+        if (Rq != R && (rc = launch_gather_rows(a.x_mid, a.x_in, n, R, R - Rq, Rq, H, st))) return rc;
+        if ((rc = gemm(a.AO, lw.wo, nullptr, nullptr, 1, H, a.x_mid, H, Mq, EPI_RESIDUAL, Rq != R ? a.x_mid : a.x_in))) return rc;     // x_mid = x_in + O(...)
+        if ((rc = launch_rmsnorm<T>((T *)a.Nrm2, a.x_mid, (const float *)lw.ffn_norm, Mq, H, c.rms_eps, st))) return rc;
         {   // ... and SwiGLU that of the gate / up projection (1,981 rows of 2 x 11008: a pass of 31 us less; both: 32 rollouts of two
             // layers 14.56 -> 14.17 ms, 7 rollouts 3.59 -> 3.48; the library's exponential and a division, as in swiglu_fwd_kernel, take
             // 0.03 and 0.02 ms of that back)
@@ -863,8 +856,8 @@ struct Backward {
             swiglu([&](auto v, dim3 grid) { swiglu_fwd_kernel<T, decltype(v)::value><<<grid, 256, 0, st>>>((T *)a.ACT, a.GU, Mq, F); }, Mq);
             if ((rc = vla_check_launch("swiglu_fwd"))) return rc;
         }
-        if (!with_down) return 0;
-        return gemm(a.ACT, lw.w_down, nullptr, nullptr, 1, H, ws.X, F, Mq, EPI_RESIDUAL);
+        if (!x_out) return 0;
+        return gemm(a.ACT, lw.w_down, nullptr, nullptr, 1, H, x_out, F, Mq, EPI_RESIDUAL, a.x_mid);
     }
 
     // LoRA gradients of a group of projections that share their input X [M, in] (storage type, contiguous rows) and
@@ -941,8 +934,7 @@ struct Backward {
         const float isd = 1.0f / sqrtf((float)d);
         int rc;
         if (!ws.keep) {                              // run the layer again from its kept input
-            if ((rc = copy_stream(ws.X, a.x_in, M))) return rc;
-            if ((rc = layer_forward(l, a, false))) return rc;
+            if ((rc = layer_forward(l, a, nullptr))) return rc;
         }
         // ---- down projection and SwiGLU (ws.dXb: dx in the storage type, left by the head or the layer above)
         if ((rc = lora_group(group_of(1, &lo.down, &gr.down, F, H), a.ACT, ws.dXb, first, Mq))) return rc;
@@ -1013,12 +1005,13 @@ int backward_impl(vla_model *m, void *wsbuf, bool keep, const void *patch, const
         const float *x_final = nullptr;
         if (keep) {
             // (1) forward with the unfused kernels, every layer leaving what its backward reads in a set of its own
-            if ((rc = launch_embed_prefix<T>(bw.ws.X, pp, ii, (const T *)m->w.embed, n, P, T_, R, H, c.vocab, st))) return rc;
+            float *x = bw.acts(0).x_in;
+            if ((rc = launch_embed_prefix<T>(x, pp, ii, (const T *)m->w.embed, n, P, T_, R, H, c.vocab, st))) return rc;
             if (mode == VLA_MODE_AR) {
-                if ((rc = launch_embed_tokens<T>(bw.ws.X, bins + (size_t)n0 * A, A, A - 1, (const T *)m->w.embed, n, R, S, H, c.vocab, st))) return rc;
-            } else if ((rc = launch_embed_slots<T>(bw.ws.X, (const T *)slot_embed, n, A, R, S, H, st))) return rc;
+                if ((rc = launch_embed_tokens<T>(x, bins + (size_t)n0 * A, A, A - 1, (const T *)m->w.embed, n, R, S, H, c.vocab, st))) return rc;
+            } else if ((rc = launch_embed_slots<T>(x, (const T *)slot_embed, n, A, R, S, H, st))) return rc;
             for (int l = 0; l < L; l++)
-                if ((rc = bw.layer_forward(l, bw.acts(l), true))) return rc;
+                if ((rc = bw.layer_forward(l, bw.acts(l), l + 1 < L ? bw.acts(l + 1).x_in : bw.ws.X))) return rc;
             x_final = bw.ws.X;
         } else {
             // (1) the forward pass of the recompute itself (its fused kernels), keeping every layer's input

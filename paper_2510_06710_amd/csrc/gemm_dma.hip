@@ -62,6 +62,7 @@ struct DmaGemmParams {
     const bf16_t *A;
     const bf16_t *W0, *W1, *W2;
     void *C;
+    const float *res;   // EPI_RESIDUAL: what the product is added to
     int M, N, K, segN;
     int tiles_m, tiles_n;
     int a_rows;      // k-blocked layout: rows per 32-column block of A (and of the SwiGLU output)
@@ -324,6 +325,8 @@ __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][MB], const DmaGemmPar
     const int rows_in = min(16 * MB, p.M - m0);
     float *wave_out = (float *)p.C + c_off + (size_t)m0 * p.N + (size_t)tn * BN + wn * 128;
     __amdgpu_buffer_rsrc_t c_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)wave_out, (short)0, rows_in > 0 ? rows_in * p.N * 4 : 0, 0x00020000);
+    __amdgpu_buffer_rsrc_t x_rsrc = c_rsrc;
+    if (EPI == EPI_RESIDUAL) x_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(p.res + (size_t)m0 * p.N + (size_t)tn * BN + wn * 128), (short)0, rows_in > 0 ? rows_in * p.N * 4 : 0, 0x00020000);
     const int voff = ((lane >> 5) * p.N + (lane & 31) * 4) * 4;
     const int row2 = 2 * p.N * 4;                      // bytes between the row pairs of consecutive instructions
     constexpr int XD = 2;
@@ -334,7 +337,7 @@ __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][MB], const DmaGemmPar
         int r2 = row2;
         asm volatile("" : "+s"(r2));
 #pragma unroll
-        for (int it = 0; it < 8; it++) xb[it] = __builtin_amdgcn_raw_buffer_load_b128(c_rsrc, voff, (i * 8 + it) * r2, 0);
+        for (int it = 0; it < 8; it++) xb[it] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, voff, (i * 8 + it) * r2, 0);
     };
     if (EPI == EPI_RESIDUAL) {
 #pragma unroll
@@ -814,7 +817,8 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
             swiglu_block_out<KB>(p, pb, mblock, tn * 64, lane);
         } else {
             constexpr int LPR = BNT / 4, RPI = 64 / LPR;      // lanes per row, rows per instruction
-            float *out = (float *)p.C + (size_t)mblock * p.N + (size_t)tn * BNT + (lane % LPR) * 4;
+            const size_t out0 = (size_t)mblock * p.N + (size_t)tn * BNT + (lane % LPR) * 4;
+            float *out = (float *)p.C + out0;
 #pragma unroll
             for (int it = 0; it < 16 / RPI; it++) {
                 const int row = it * RPI + lane / LPR;
@@ -822,7 +826,7 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
                 if (mblock + row < p.M) {
                     f32x4_t *dst = (f32x4_t *)(out + (size_t)row * p.N);
                     if (EPI == EPI_RESIDUAL) {
-                        const f32x4_t x = *dst;
+                        const f32x4_t x = *(const f32x4_t *)(p.res + out0 + (size_t)row * p.N);
 #pragma unroll
                         for (int e = 0; e < 4; e++) v[e] += x[e];
                     }
@@ -985,7 +989,7 @@ int try_gemm_bf16_dma(const GemmArgs &g, hipStream_t st) {
     DmaGemmParams p{};
     p.A = (const bf16_t *)g.A;
     p.W0 = (const bf16_t *)g.W[0]; p.W1 = (const bf16_t *)g.W[1]; p.W2 = (const bf16_t *)g.W[2];
-    p.C = g.C; p.M = g.M; p.K = g.K; p.segN = g.segN;
+    p.C = g.C; p.res = g.res ? g.res : (const float *)g.C; p.M = g.M; p.K = g.K; p.segN = g.segN;
     p.a_rows = g.a_rows; p.w_rows = g.segN + VLA_KB_PAD_ROWS;
     p.splits = 1;
     {

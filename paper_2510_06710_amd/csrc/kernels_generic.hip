@@ -148,7 +148,7 @@ __device__ __forceinline__ f32x4_t load4(const T *p, int k, int K) {
 
 template <typename T, int EPI, bool VEC, int MB, int NBK>
 __global__ void __launch_bounds__(512) gemm_generic_kernel(const T *A, const T *W0, const T *W1, const T *W2, int segN, void *Cv,
-                                                           int M, int N, int K) {
+                                                           const float *res, int M, int N, int K) {
     constexpr int NW = 8, NP = (EPI == EPI_SWIGLU) ? 2 : 1, UN = MB * NBK > 1 ? 1 : 4;
     __shared__ __attribute__((aligned(16))) f32x4_t part[NW][NP * MB * NBK][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
@@ -228,7 +228,7 @@ __global__ void __launch_bounds__(512) gemm_generic_kernel(const T *A, const T *
         if (col >= N) continue;
         const size_t o = (size_t)m * N + col;
         if (EPI == EPI_RESIDUAL) {
-            ((float *)Cv)[o] += sum[0][r];
+            ((float *)Cv)[o] = res[o] + sum[0][r];
         } else if (EPI == EPI_SWIGLU) {
             const float g = sum[0][r];
             ((T *)Cv)[o] = from_f<T>(g / (1.0f + expf(-g)) * sum[NP - 1][r]);
@@ -573,13 +573,14 @@ template <typename T, int EPI, bool VEC>
 static void gemm_generic_tile(const GemmArgs &g, int N, hipStream_t st) {
     constexpr int MB = (EPI == EPI_SWIGLU) ? 2 : 4, NBK = 2;
     const T *A = (const T *)g.A, *W0 = (const T *)g.W[0], *W1 = (const T *)g.W[1], *W2 = (const T *)g.W[2];
+    const float *res = g.res ? g.res : (const float *)g.C;
     const dim3 big((N + 16 * NBK - 1) / (16 * NBK), (g.M + 16 * MB - 1) / (16 * MB));
     // The large tile wants two workgroups per CU; its sums are those of the small one.  (Fewer than 512 large tiles are
     // at most 4096 + a few rows of small ones.)
     if ((size_t)big.x * big.y < 512)
-        gemm_generic_kernel<T, EPI, VEC, 1, 1><<<dim3((N + 15) / 16, (g.M + 15) / 16), 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, g.M, N, g.K);
+        gemm_generic_kernel<T, EPI, VEC, 1, 1><<<dim3((N + 15) / 16, (g.M + 15) / 16), 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, res, g.M, N, g.K);
     else
-        gemm_generic_kernel<T, EPI, VEC, MB, NBK><<<big, 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, g.M, N, g.K);
+        gemm_generic_kernel<T, EPI, VEC, MB, NBK><<<big, 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, res, g.M, N, g.K);
 }
 template <typename T, int EPI>
 static void gemm_generic_epi(const GemmArgs &g, int N, hipStream_t st) {

@@ -62,7 +62,8 @@ struct GemmArgs {
     const void *Wkb[3];     // the same segments repacked k-blocked ([K / 32][segN + pad][32]) or NULL: kernels that stream
                             // the weights from HBM with row-major activations (decode forwards) prefer these
     int n_seg, segN;        // N = n_seg * segN (EPI_SWIGLU: W[0] = gate, W[1] = up, N = segN)
-    void *C;                // EPI_STORE: fp32 [M, N]; EPI_SWIGLU: storage dtype [M, N]; EPI_RESIDUAL: fp32 [M, N] +=
+    void *C;                // EPI_STORE: fp32 [M, N]; EPI_SWIGLU: storage dtype [M, N]; EPI_RESIDUAL: fp32 [M, N]
+    const float *res;       // EPI_RESIDUAL: what the product is added to, fp32 [M, N]; NULL: C (multi-row kernels alone: any other array)
     int M, K;
     int epilogue;
     const QkvRopeArgs *rope;   // EPI_QKV_ROPE, EPI_QKV_ROWS (q_out [M, 3H]; of kv only n_heads and d)
@@ -298,7 +299,7 @@ int vla_gemm_dispatch(const vla_config &c, const GemmArgs &g, hipStream_t st);
 // The same with one of the gradient pass's epilogues: 1 if handled, 0 if declined, < 0 on a launch error
 int vla_gemm_fused(const vla_config &c, const GemmArgs &g, hipStream_t st);
 // The teacher-forced forward of the log-prob recompute over n rollouts (the kernels vla_logprob_recompute runs), keeping
-// the fp32 residual stream at the input of layer l in keep + l * n * R * H ([n * R, H] each).  tail_rows: 0, or how many of
+// the fp32 residual stream at the input of layer l in keep + l * n * R * H ([n * R, H] each; the layers read and write it there).  tail_rows: 0, or how many of
 // every rollout's last rows the caller reads after the last layer, which then computes those alone (at most a quarter of the
 // rows, see run_layers).  *x_final: the residual stream after the last layer ([n * R, H], or [n * tail_rows, H] packed,
 // inside fw_ws).  fw_ws: device scratch of vla_forward_streams_bytes(c, n_max, R, tail_rows) bytes with n <= n_max.
