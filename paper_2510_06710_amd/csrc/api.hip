@@ -394,11 +394,13 @@ static bool step_norms(const vla_config &c, const Workspace &ws, int M, int N) {
 
 // `tail` (may be NULL): the rows whose final hidden state the caller reads.  Where use_tail() holds, the last layer
 // is run in its tail form and the result of those rows is in ws.tX (packed), not in ws.X.  `prepared`: ws.rope and, where
-// the QKV projection does not form it itself, the first layer's norm are there (NextStep).  keep (may be NULL): [layers][M, H], the
-// stream at the input of every layer, the first one's put there by the caller (otherwise in ws.X).
+// the QKV projection does not form it itself, the first layer's norm are there (NextStep).  keep (may be NULL): [n_layers + 1][M, H],
+// the stream at the input of every layer, the first one's put there by the caller, and after the last one (otherwise in ws.X).
+// n_layers: the first so many layers alone (-1: all).
 template <typename T>
 static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &ra, const KvView &kv,
-                      bool kv_single_layer, hipStream_t st, const TailSpec *tail = nullptr, float *keep = nullptr, bool prepared = false) {
+                      bool kv_single_layer, hipStream_t st, const TailSpec *tail = nullptr, float *keep = nullptr, bool prepared = false,
+                      int n_layers = -1) {
     const vla_config &c = m->cfg;
     int H = c.hidden, F = c.ffn, M = ra.n_seq * ra.R, d = H / c.n_heads, rc;
     if (!prepared && (rc = launch_rope_table(ws.rope, ra.R, ra.pos0, d, c.rope_theta, st))) return rc;
@@ -425,13 +427,14 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         }
         return 0;
     };
-    for (int l = 0; l < c.n_layers; l++) {
+    const int layers = n_layers < 0 ? c.n_layers : n_layers;
+    for (int l = 0; l < layers; l++) {
         const vla_layer_weights &lw = m->layers[l];
         int kl = kv_single_layer ? 0 : l;
         // keep: the layers read their input there, and write their output to the next one's (one row per sequence: the kernels of
         // decode steps add in place, so the stream is copied)
         const float *x_in = keep ? keep + (size_t)l * M * H : ws.X;
-        float *x_out = keep && l + 1 < c.n_layers ? keep + (size_t)(l + 1) * M * H : ws.X;
+        float *x_out = keep ? keep + (size_t)(l + 1) * M * H : ws.X;
         if (copies) {
             if ((rc = copy_stream(ws.X, x_in))) return rc;
             x_in = ws.X;
@@ -646,37 +649,34 @@ static int recompute_impl(vla_model *m, void *wsbuf, const void *patch, const in
     return 0;
 }
 
-size_t vla_forward_streams_bytes(const vla_config &c, int n_max, int R, int tail_rows) {
-    return plan_workspace(c, nullptr, n_max, R, R, 0, true, tail_rows).total;
+size_t vla_forward_streams_bytes(const vla_config &c, int n_max, int R) {
+    return plan_workspace(c, nullptr, n_max, R, R, 0, true).total;
 }
 
 template <typename T>
 static int forward_streams_impl(vla_model *m, void *fw_ws, int n_max, const void *patch, const int32_t *ids, const int32_t *bins, int n,
-                                int P, int T_, int A, int mode, const void *slot_embed, int tail_rows, float *keep, const float **x_final,
-                                hipStream_t st) {
+                                int P, int T_, int A, int mode, const void *slot_embed, int n_layers, float *keep, hipStream_t st) {
     const vla_config &c = m->cfg;
     const int S = P + T_, H = c.hidden, R = (mode == VLA_MODE_AR) ? S + A - 1 : S + A;
     int rc;
-    Workspace ws = plan_workspace(c, (char *)fw_ws, n_max, R, R, 0, true, tail_rows);
     if ((rc = launch_embed_prefix<T>(keep, (const T *)patch, ids, (const T *)m->w.embed, n, P, T_, R, H, c.vocab, st))) return rc;
     if (mode == VLA_MODE_AR) {
         if ((rc = launch_embed_tokens<T>(keep, bins, A, A - 1, (const T *)m->w.embed, n, R, S, H, c.vocab, st))) return rc;
     } else if ((rc = launch_embed_slots<T>(keep, (const T *)slot_embed, n, A, R, S, H, st))) return rc;
+    if (n_layers == 0) return 0;
+    const Workspace ws = plan_workspace(c, (char *)fw_ws, n_max, R, R, 0, true);
     RowsArgs ra{n, R, 0, (mode == VLA_MODE_AR) ? 0x7fffffff : S};
     KvView kv;
     kv.layer_elems = kv_layer_elems(c, n_max);
     kv.k = ws.kvs_k; kv.v = ws.kvs_v; kv.n_seq = n; kv.n_heads = c.n_heads; kv.d = H / c.n_heads; kv.pos_stride = c.max_seq;
-    const TailSpec tail{R - tail_rows, tail_rows};
-    if ((rc = run_layers<T>(m, ws, ra, kv, true, st, tail_rows ? &tail : nullptr, keep))) return rc;
-    *x_final = tail_rows ? ws.tX : ws.X;
-    return 0;
+    return run_layers<T>(m, ws, ra, kv, true, st, nullptr, keep, false, n_layers);
 }
 
 int vla_forward_streams(vla_model *m, void *fw_ws, int n_max, const void *patch, const int32_t *ids, const int32_t *bins, int n,
-                        int P, int T, int A, int mode, const void *slot_embed, int tail_rows, float *keep, const float **x_final, hipStream_t st) {
+                        int P, int T, int A, int mode, const void *slot_embed, int n_layers, float *keep, hipStream_t st) {
     return m->cfg.dtype == VLA_DTYPE_F32
-               ? forward_streams_impl<float>(m, fw_ws, n_max, patch, ids, bins, n, P, T, A, mode, slot_embed, tail_rows, keep, x_final, st)
-               : forward_streams_impl<bf16_t>(m, fw_ws, n_max, patch, ids, bins, n, P, T, A, mode, slot_embed, tail_rows, keep, x_final, st);
+               ? forward_streams_impl<float>(m, fw_ws, n_max, patch, ids, bins, n, P, T, A, mode, slot_embed, n_layers, keep, st)
+               : forward_streams_impl<bf16_t>(m, fw_ws, n_max, patch, ids, bins, n, P, T, A, mode, slot_embed, n_layers, keep, st);
 }
 
 // ------------------------------------------------------------------------------------------ C ABI

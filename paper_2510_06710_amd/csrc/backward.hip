@@ -2,14 +2,15 @@
 // factors of the seven projections of every decoder layer (the policy update of appendix I-B / I-C differentiates
 // the clipped surrogate through rho = exp(logp - logp_old) only; LoRA adapters: section IV-B.2).
 //
-// Structure.  Stored rollouts are processed in micro-batches.  For one micro-batch: (1) the forward pass of the
-// recompute (its own fused kernels), keeping the residual stream at the input of every layer (fp32 [layers][rows, H]),
-// and the head, which also returns logp; (2) the head's backward puts d L / d x on the rows that predict action
-// tokens; (3) layers in reverse: the layer's forward is run again from its kept input, this time with
-// kernels that leave every intermediate the chain rule needs, then the chain rule walks back through the
-// down projection, SwiGLU, gate / up, the FFN norm, the O projection, attention, the rotation, Q / K / V and the
-// attention norm.  With keep_activations, (1) is instead a forward with these kernels that leaves every layer's
-// intermediates in a set of its own (one per layer, for one micro-batch), and (3) runs no layer a second time.  Every large contraction -- the seven forward projections and the four input-gradient products
+// Structure.  Stored rollouts are processed in micro-batches.  For one micro-batch: (1) the forward pass of the recompute (its
+// own fused kernels) through the lower layers, keeping the residual stream at the input of every layer (fp32 [layers][rows, H]),
+// then the top one or two layers with kernels that leave every intermediate the chain rule needs, and the head, which also
+// returns logp; (2) the head's backward puts d L / d x on the rows that predict action tokens; (3) layers in reverse: the forward
+// of a layer whose intermediates are not there is run again from its kept input with the same kernels, then the chain rule walks
+// back through the down projection, SwiGLU, gate / up, the FFN norm, the O projection, attention, the rotation, Q / K / V and the
+// attention norm.  With keep_activations, (1) runs all layers with the latter kernels and every layer leaves its intermediates in
+// a set of its own (one per layer, for one micro-batch), and (3) runs no layer a second time.  Every large contraction -- the
+// seven forward projections and the four input-gradient products
 // dY . W, which run as the same "activation x weight^T" GEMM on a transposed copy of the weights made per layer --
 // goes through the library's GEMM dispatch (MFMA kernels for bf16 shapes they cover).  Attention (scores, softmax,
 // its backward) runs on materialised [rows x rows] matrices per (rollout, head): 64 query rows at a time from scores to output
@@ -420,7 +421,7 @@ __global__ void __launch_bounds__(256) swiglu_bwd_kernel(T *dGU, const float *d_
 // dX[m] += r (g dn) - x r^3 mean(x g dn), r = (mean(x^2) + eps)^(-1/2): the backward of n = RMSNorm(x) g.  The new
 // dX is also written in the storage type to dXb (the operand of the GEMMs that follow).  prev: the gradient that the
 // norm's is added to, rows_prev rows for each sequence's last positions out of `rows` (zero for the others); dX itself when
-// rows_prev == rows.
+// rows_prev == rows.  X may be dX.
 template <typename T>
 __global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(float *dX, T *dXb, const float *prev, int rows, int rows_prev, const float *X,
                                                          const float *gain, const float *dn, int H, float eps) {
@@ -624,15 +625,19 @@ inline unsigned blocks_for(size_t n) { size_t b = (n + 255) / 256; return (unsig
 struct Acts {
     float *x_in, *x_mid, *GU, *SP;
     void *Nrm, *QKVr, *AO, *Nrm2, *ACT;
+    int q_rows;      // rows allocated for AO, Nrm2 and ACT
 };
 
 struct BwSpace {
     float *X, *dX, *dXt, *ckpt, *QKV, *Tmp, *dP, *UV, *Cab;
     void *dGU, *dXb, *dQKVb, *Wt, *Wa, *Wb, *UVt, *Xt, *dYt;
     // keep = false: one Acts set, refilled per layer by running the layer again from ckpt[l] (the first pass is the
-    // recompute's fused forward, its scratch is fw).  keep = true: one set per layer, filled by the first pass.
-    bool keep;
-    Acts one;
+    // recompute's fused forward, its scratch is fw).  Where the top layer works on the read rows alone and its set fits
+    // into fw, which is free once the fused forward is through, it has one of its own there (top): the first pass then fills
+    // that and, for the layer below, the shared one, and neither layer is run again.  Otherwise the first pass fills the shared
+    // one for the top layer.  keep = true: one set per layer, filled by the first pass.
+    bool keep, own_top;
+    Acts one, top;
     char *acts_base;
     size_t acts_stride;
     void *fw;        // scratch of the first forward pass (vla_forward_streams)
@@ -646,20 +651,24 @@ struct BwSpace {
 
 size_t al(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// One Acts set laid out from `base` (NULL: only sized); with_streams: the set owns x_in and x_mid.
-Acts plan_acts(const vla_config &c, char *base, size_t M, size_t Mp, int mb, int R, bool with_streams, size_t *bytes) {
+// One Acts set laid out from `base` (NULL: only sized); with_streams: the set owns x_in and x_mid.  Rq: the rows per sequence that
+// have a query (fewer than R: the top layer's, packed; the set then owns x_mid).
+Acts plan_acts(const vla_config &c, char *base, size_t M, size_t Mp, int mb, int R, int Rq, bool with_streams, size_t *bytes) {
     Acts a{};
     size_t off = 0;
     const size_t es = c.dtype == VLA_DTYPE_F32 ? 4 : 2, H = c.hidden, F = c.ffn, Rp = ((size_t)R + 3) & ~(size_t)3;
     auto take = [&](size_t b) { char *p = base ? base + off : nullptr; off += al(b); return (void *)p; };
-    if (with_streams) { a.x_in = (float *)take(M * H * 4); a.x_mid = (float *)take(M * H * 4); }
-    a.GU = (float *)take(M * (2 * F > H ? 2 * F : H) * 4);         // (also [M, H] of gradients, layer_backward's d_ao and d n)
-    a.SP = (float *)take((size_t)mb * c.n_heads * R * Rp * 4);     // score rows start 16-byte aligned
+    const size_t Mq = (size_t)mb * Rq, Mqp = Rq == R ? Mp : (Mq + 255) / 256 * 256 + VLA_KB_PAD_ROWS;
+    a.q_rows = (int)Mqp;
+    if (with_streams) a.x_in = (float *)take(M * H * 4);
+    if (with_streams || Rq != R) a.x_mid = (float *)take(Mq * H * 4);
+    a.GU = (float *)take((Mq * 2 * F > M * H ? Mq * 2 * F : M * H) * 4);         // (also [M, H] of gradients, layer_backward's d_ao and d n)
+    a.SP = (float *)take((size_t)mb * c.n_heads * Rq * Rp * 4);    // score rows start 16-byte aligned
     a.Nrm = take(Mp * H * es);
     a.QKVr = take(Mp * 3 * H * es);
-    a.AO = take(Mp * H * es);
-    a.Nrm2 = take(Mp * H * es);
-    a.ACT = take(Mp * F * es);
+    a.AO = take(Mqp * H * es);
+    a.Nrm2 = take(Mqp * H * es);
+    a.ACT = take(Mqp * F * es);
     *bytes = off;
     return a;
 }
@@ -676,6 +685,7 @@ BwSpace plan_bw(const vla_config &c, char *base, int mb, int R, int A, bool keep
     auto take = [&](size_t bytes) { char *p = base ? base + off : nullptr; off += al(bytes); return (void *)p; };
     w.a_rows = (int)Mp;
     w.keep = keep;
+    w.own_top = false;
     w.X = (float *)take(M * H * 4);
     w.dX = (float *)take(M * H * 4);
     w.dXt = tail_form(R, A) ? (float *)take((size_t)mb * A * H * 4) : nullptr;
@@ -705,20 +715,25 @@ BwSpace plan_bw(const vla_config &c, char *base, int mb, int R, int A, bool keep
     w.split = take(w.split_bytes);
     size_t set_bytes = 0;
     if (keep) {
-        plan_acts(c, nullptr, M, Mp, mb, R, true, &set_bytes);
+        plan_acts(c, nullptr, M, Mp, mb, R, R, true, &set_bytes);
         w.acts_stride = set_bytes;
         w.acts_base = (char *)take(set_bytes * L);
         w.one = Acts{};
         w.ckpt = nullptr;
         w.fw = nullptr;
     } else {
-        plan_acts(c, nullptr, M, Mp, mb, R, false, &set_bytes);
+        plan_acts(c, nullptr, M, Mp, mb, R, R, false, &set_bytes);
         char *b = (char *)take(set_bytes);
-        w.one = plan_acts(c, b, M, Mp, mb, R, false, &set_bytes);
+        w.one = plan_acts(c, b, M, Mp, mb, R, R, false, &set_bytes);
         w.acts_base = nullptr;
         w.acts_stride = 0;
         w.ckpt = (float *)take(L * M * H * 4);
-        w.fw = take(vla_forward_streams_bytes(c, mb, R, tail_form(R, A) ? A : 0));
+        const size_t fw_bytes = vla_forward_streams_bytes(c, mb, R);
+        w.fw = take(fw_bytes);
+        if (tail_form(R, A)) {
+            w.top = plan_acts(c, (char *)w.fw, M, Mp, mb, R, A, false, &set_bytes);
+            w.own_top = set_bytes <= fw_bytes;
+        }
     }
     w.total = off;
     return w;
@@ -741,10 +756,11 @@ struct Backward {
     int ws_mb;       // rollouts per micro-batch the workspace is laid out for
     static constexpr bool MF = sizeof(T) == 2;      // bf16 storage: attention matrices on the matrix cores
 
-    int gemm(const void *A, const void *W0, const void *W1, const void *W2, int n_seg, int segN, float *C, int K, int rows, int epilogue = EPI_STORE, const float *res = nullptr) {
+    int gemm(const void *A, const void *W0, const void *W1, const void *W2, int n_seg, int segN, float *C, int K, int rows, int a_rows,
+             int epilogue = EPI_STORE, const float *res = nullptr) {
         GemmArgs g{};
         g.A = A; g.W[0] = W0; g.W[1] = W1; g.W[2] = W2; g.n_seg = n_seg; g.segN = segN; g.C = C; g.M = rows; g.K = K;
-        g.epilogue = epilogue; g.a_rows = ws.a_rows; g.res = res;
+        g.epilogue = epilogue; g.a_rows = a_rows; g.res = res;
         return vla_gemm_dispatch(c, g, st);
     }
     int transpose(const void *W, int N, int K, int ldt, int col0) {
@@ -772,15 +788,20 @@ struct Backward {
         return g;
     }
 
-    // The activation set of layer l: its own (keep) or the shared one, whose streams are ckpt[l] and ws.X.
+    // The top layers whose activation sets the first pass fills: layer_backward does not run them again.  (A layer's forward is a
+    // third of its share of the pass.)
+    int live() const { return ws.keep ? L : ws.own_top && L > 1 ? 2 : 1; }
+    // The activation set of layer l: its own (keep; the top layer's where there is one), or the shared one, whose streams are ckpt[l]
+    // and ws.X.
     Acts acts(int l) const {
         if (ws.keep) {
             size_t bytes;
-            return plan_acts(c, ws.acts_base + (size_t)l * ws.acts_stride, (size_t)ws_mb * R, (size_t)ws.a_rows, ws_mb, R, true, &bytes);
+            return plan_acts(c, ws.acts_base + (size_t)l * ws.acts_stride, (size_t)ws_mb * R, (size_t)ws.a_rows, ws_mb, R, R, true, &bytes);
         }
-        Acts a = ws.one;
+        const bool top = ws.own_top && l == L - 1;
+        Acts a = top ? ws.top : ws.one;
         a.x_in = ws.ckpt + (size_t)l * M * H;        // (the first pass packs the streams of the current micro-batch)
-        a.x_mid = ws.X;
+        if (!top) a.x_mid = ws.X;
         return a;
     }
     template <typename L_>
@@ -820,7 +841,7 @@ struct Backward {
             if ((rc = vla_gemm_fused(c, g, st)) < 0) return rc;
         }
         if (rc == 0) {
-            if ((rc = gemm(a.Nrm, lw.wq, lw.wk, lw.wv, 3, H, ws.QKV, H, M))) return rc;
+            if ((rc = gemm(a.Nrm, lw.wq, lw.wk, lw.wv, 3, H, ws.QKV, H, M, ws.a_rows))) return rc;
             rope_rows_kernel<T><<<M, 256, 0, st>>>((T *)a.QKVr, ws.QKV, ws.rope, R, H, d, 1.0f, 0);
             if ((rc = vla_check_launch("rope_rows"))) return rc;
         }
@@ -841,23 +862,23 @@ struct Backward {
             if (!MF && (rc = cast(a.AO, ws.Tmp, H, Mq))) return rc;
         }
         if (Rq != R && (rc = launch_gather_rows(a.x_mid, a.x_in, n, R, R - Rq, Rq, H, st))) return rc;
-        if ((rc = gemm(a.AO, lw.wo, nullptr, nullptr, 1, H, a.x_mid, H, Mq, EPI_RESIDUAL, Rq != R ? a.x_mid : a.x_in))) return rc;     // x_mid = x_in + O(...)
+        if ((rc = gemm(a.AO, lw.wo, nullptr, nullptr, 1, H, a.x_mid, H, Mq, a.q_rows, EPI_RESIDUAL, Rq != R ? a.x_mid : a.x_in))) return rc;     // x_mid = x_in + O(...)
         if ((rc = launch_rmsnorm<T>((T *)a.Nrm2, a.x_mid, (const float *)lw.ffn_norm, Mq, H, c.rms_eps, st))) return rc;
         {   // ... and SwiGLU that of the gate / up projection (1,981 rows of 2 x 11008: a pass of 31 us less; both: 32 rollouts of two
             // layers 14.56 -> 14.17 ms, 7 rollouts 3.59 -> 3.48; the library's exponential and a division, as in swiglu_fwd_kernel, take
             // 0.03 and 0.02 ms of that back)
             GemmArgs g{};
             g.A = a.Nrm2; g.W[0] = lw.w_gate; g.W[1] = lw.w_up; g.n_seg = 2; g.segN = F; g.C = a.ACT; g.pre = a.GU; g.M = Mq; g.K = H;
-            g.epilogue = EPI_SWIGLU_KEEP; g.a_rows = ws.a_rows;
+            g.epilogue = EPI_SWIGLU_KEEP; g.a_rows = a.q_rows;
             if ((rc = vla_gemm_fused(c, g, st)) < 0) return rc;
         }
         if (rc == 0) {
-            if ((rc = gemm(a.Nrm2, lw.w_gate, lw.w_up, nullptr, 2, F, a.GU, H, Mq))) return rc;
+            if ((rc = gemm(a.Nrm2, lw.w_gate, lw.w_up, nullptr, 2, F, a.GU, H, Mq, a.q_rows))) return rc;
             swiglu([&](auto v, dim3 grid) { swiglu_fwd_kernel<T, decltype(v)::value><<<grid, 256, 0, st>>>((T *)a.ACT, a.GU, Mq, F); }, Mq);
             if ((rc = vla_check_launch("swiglu_fwd"))) return rc;
         }
         if (!x_out) return 0;
-        return gemm(a.ACT, lw.w_down, nullptr, nullptr, 1, H, x_out, F, Mq, EPI_RESIDUAL, a.x_mid);
+        return gemm(a.ACT, lw.w_down, nullptr, nullptr, 1, H, x_out, F, Mq, a.q_rows, EPI_RESIDUAL, a.x_mid);
     }
 
     // LoRA gradients of a group of projections that share their input X [M, in] (storage type, contiguous rows) and
@@ -874,7 +895,7 @@ struct Backward {
         g.split_scratch = ws.split; g.split_scratch_bytes = ws.split_bytes;     // few output tiles: cut K into parts
         return vla_gemm_dispatch(c, g, st);
     }
-    int lora_group(LoraGroup lg, const void *X, const void *dY, bool first, int M) {        // M rows
+    int lora_group(LoraGroup lg, const void *X, int x_rows, const void *dY, bool first, int M) {        // M rows; x_rows: those allocated for X
         if constexpr (MF) {
             LoraProducts g{};
             for (int p = 0; p < lg.n_p; p++) { g.a[p] = lg.a[p]; g.b[p] = lg.b[p]; g.da[p] = lg.da[p]; g.db[p] = lg.db[p]; }
@@ -889,7 +910,7 @@ struct Backward {
         int rc;
         pack_factors_kernel<T><<<blocks_for((size_t)256 * (in + wout)), 256, 0, st>>>((T *)ws.Wa, (T *)ws.Wb, lg, rank);
         if ((rc = vla_check_launch("pack_factors"))) return rc;
-        if ((rc = gemm_rows(X, ws.Wa, U, M, ws.a_rows, in)) || (rc = gemm_rows(dY, ws.Wb, V, M, ws.a_rows, wout))) return rc;
+        if ((rc = gemm_rows(X, ws.Wa, U, M, x_rows, in)) || (rc = gemm_rows(dY, ws.Wb, V, M, ws.a_rows, wout))) return rc;
         auto tp = [&](auto *dst, auto *src, int rows, int cols, int ld_src) {
             ProfScope ps("bw_transpose", 0.0, st);
             using D = std::remove_pointer_t<decltype(dst)>;
@@ -933,25 +954,25 @@ struct Backward {
         const bool causal = full_from >= R && Rq == R;
         const float isd = 1.0f / sqrtf((float)d);
         int rc;
-        if (!ws.keep) {                              // run the layer again from its kept input
+        if (l < L - live()) {                        // run the layer again from its kept input
             if ((rc = layer_forward(l, a, nullptr))) return rc;
         }
         // ---- down projection and SwiGLU (ws.dXb: dx in the storage type, left by the head or the layer above)
-        if ((rc = lora_group(group_of(1, &lo.down, &gr.down, F, H), a.ACT, ws.dXb, first, Mq))) return rc;
+        if ((rc = lora_group(group_of(1, &lo.down, &gr.down, F, H), a.ACT, a.q_rows, ws.dXb, first, Mq))) return rc;
         if ((rc = transpose(lw.w_down, H, F, H, 0))) return rc;                               // [F, H]
-        if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, F, ws.Tmp, H, Mq))) return rc;      // d act [Mq, F]
+        if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, F, ws.Tmp, H, Mq, ws.a_rows))) return rc;      // d act [Mq, F]
         swiglu([&](auto v, dim3 grid) { swiglu_bwd_kernel<T, decltype(v)::value><<<grid, 256, 0, st>>>((T *)ws.dGU, ws.Tmp, a.GU, Mq, F); }, Mq);
         if ((rc = vla_check_launch("swiglu_bwd"))) return rc;
-        if ((rc = lora_group(group_of(2, &lo.gate, &gr.gate, H, F), a.Nrm2, ws.dGU, first, Mq))) return rc;   // gate, up adjacent in the structs
+        if ((rc = lora_group(group_of(2, &lo.gate, &gr.gate, H, F), a.Nrm2, a.q_rows, ws.dGU, first, Mq))) return rc;   // gate, up adjacent in the structs
         if ((rc = transpose(lw.w_gate, F, H, 2 * F, 0)) || (rc = transpose(lw.w_up, F, H, 2 * F, F))) return rc;   // [H, 2F]
-        if ((rc = gemm(ws.dGU, ws.Wt, nullptr, nullptr, 1, H, ws.Tmp, 2 * F, Mq))) return rc;  // d n2 [Mq, H]
+        if ((rc = gemm(ws.dGU, ws.Wt, nullptr, nullptr, 1, H, ws.Tmp, 2 * F, Mq, ws.a_rows))) return rc;  // d n2 [Mq, H]
         rmsnorm_bwd_kernel<T><<<Mq, 256, 0, st>>>(dx, (T *)ws.dXb, dx, Rq, Rq, a.x_mid, (const float *)lw.ffn_norm, ws.Tmp, H, c.rms_eps);
         if ((rc = vla_check_launch("rmsnorm_bwd"))) return rc;
         // ---- O projection and attention (dx, ws.dXb are now d L / d x_mid)
-        if ((rc = lora_group(group_of(1, &lo.o, &gr.o, H, H), a.AO, ws.dXb, first, Mq))) return rc;
+        if ((rc = lora_group(group_of(1, &lo.o, &gr.o, H, H), a.AO, a.q_rows, ws.dXb, first, Mq))) return rc;
         if ((rc = transpose(lw.wo, H, H, H, 0))) return rc;
         float *d_ao = a.GU;                          // [Mq, H] fp32; the gate / up pre-activations are no longer needed
-        if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, H, d_ao, H, Mq))) return rc;
+        if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, H, d_ao, H, Mq, ws.a_rows))) return rc;
         float *dqkv = ws.Tmp;                        // [M, 3H] fp32: d q | d k | d v (q, k still in the rotated frame)
         // dP = dO v^T ; dV = P^T dO ; dS = P (dP - rowsum(P dP)) ; dQ = dS k / sqrt(d) ; dK = dS^T q / sqrt(d)
         rc = 0;
@@ -974,10 +995,10 @@ struct Backward {
         rope_rows_kernel<T><<<M, 256, 0, st>>>((T *)ws.dQKVb, dqkv, ws.rope, R, H, d, -1.0f, R - Rq);
         if ((rc = vla_check_launch("rope_rows (transpose)"))) return rc;
         // ---- Q / K / V projections and the attention norm
-        if ((rc = lora_group(group_of(3, &lo.q, &gr.q, H, H), a.Nrm, ws.dQKVb, first, M))) return rc;    // q, k, v adjacent
+        if ((rc = lora_group(group_of(3, &lo.q, &gr.q, H, H), a.Nrm, ws.a_rows, ws.dQKVb, first, M))) return rc;    // q, k, v adjacent
         if (l == 0) return 0;
         if ((rc = transpose(lw.wq, H, H, 3 * H, 0)) || (rc = transpose(lw.wk, H, H, 3 * H, H)) || (rc = transpose(lw.wv, H, H, 3 * H, 2 * H))) return rc;
-        if ((rc = gemm(ws.dQKVb, ws.Wt, nullptr, nullptr, 1, H, a.GU, 3 * H, M))) return rc;   // d n [M, H]
+        if ((rc = gemm(ws.dQKVb, ws.Wt, nullptr, nullptr, 1, H, a.GU, 3 * H, M, ws.a_rows))) return rc;   // d n [M, H]
         rmsnorm_bwd_kernel<T><<<M, 256, 0, st>>>(ws.dX, (T *)ws.dXb, dx, R, Rq, a.x_in, (const float *)lw.attn_norm, a.GU, H, c.rms_eps);
         return vla_check_launch("rmsnorm_bwd");
     }
@@ -1002,21 +1023,13 @@ int backward_impl(vla_model *m, void *wsbuf, bool keep, const void *patch, const
         bw.n = n; bw.M = n * R;
         const T *pp = patch ? (const T *)patch + (size_t)n0 * P * H : nullptr;
         const int32_t *ii = ids ? ids + (size_t)n0 * T_ : nullptr;
-        const float *x_final = nullptr;
-        if (keep) {
-            // (1) forward with the unfused kernels, every layer leaving what its backward reads in a set of its own
-            float *x = bw.acts(0).x_in;
-            if ((rc = launch_embed_prefix<T>(x, pp, ii, (const T *)m->w.embed, n, P, T_, R, H, c.vocab, st))) return rc;
-            if (mode == VLA_MODE_AR) {
-                if ((rc = launch_embed_tokens<T>(x, bins + (size_t)n0 * A, A, A - 1, (const T *)m->w.embed, n, R, S, H, c.vocab, st))) return rc;
-            } else if ((rc = launch_embed_slots<T>(x, (const T *)slot_embed, n, A, R, S, H, st))) return rc;
-            for (int l = 0; l < L; l++)
-                if ((rc = bw.layer_forward(l, bw.acts(l), l + 1 < L ? bw.acts(l + 1).x_in : bw.ws.X))) return rc;
-            x_final = bw.ws.X;
-        } else {
-            // (1) the forward pass of the recompute itself (its fused kernels), keeping every layer's input
-            if ((rc = vla_forward_streams(m, bw.ws.fw, mb, pp, ii, bins + (size_t)n0 * A, n, P, T_, A, mode, slot_embed, bw.tail ? A : 0, bw.ws.ckpt, &x_final, st))) return rc;
-        }
+        // (1) the forward pass: the lower layers with the recompute's own fused kernels, keeping every layer's input, the others with
+        // the unfused ones, each leaving what its backward reads in its set
+        const int lower = L - bw.live();
+        float *x_final = bw.tail ? bw.ws.dXt : bw.ws.dX;      // the stream after the last layer, until its gradient takes the place
+        if ((rc = vla_forward_streams(m, bw.ws.fw, mb, pp, ii, bins + (size_t)n0 * A, n, P, T_, A, mode, slot_embed, lower, bw.acts(0).x_in, st))) return rc;
+        for (int l = lower; l < L; l++)
+            if ((rc = bw.layer_forward(l, bw.acts(l), l + 1 < L ? bw.acts(l + 1).x_in : x_final))) return rc;
         // the head's gradient on the read rows, packed; without the tail form spread over the full ws.dX (zero elsewhere)
         const int Mh = n * A, rows_h = bw.tail ? A : R;
         float *hb = bw.ws.Tmp, *dh = hb + (size_t)Mh * H, *dz = dh + (size_t)Mh * H, *part = dz + (size_t)Mh * VLA_N_BINS;

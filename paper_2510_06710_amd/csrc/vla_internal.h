@@ -298,14 +298,12 @@ int vla_check_rows_per_pass(const vla_config &c, long n_seq, long rows_per_seq);
 int vla_gemm_dispatch(const vla_config &c, const GemmArgs &g, hipStream_t st);
 // The same with one of the gradient pass's epilogues: 1 if handled, 0 if declined, < 0 on a launch error
 int vla_gemm_fused(const vla_config &c, const GemmArgs &g, hipStream_t st);
-// The teacher-forced forward of the log-prob recompute over n rollouts (the kernels vla_logprob_recompute runs), keeping
-// the fp32 residual stream at the input of layer l in keep + l * n * R * H ([n * R, H] each; the layers read and write it there).  tail_rows: 0, or how many of
-// every rollout's last rows the caller reads after the last layer, which then computes those alone (at most a quarter of the
-// rows, see run_layers).  *x_final: the residual stream after the last layer ([n * R, H], or [n * tail_rows, H] packed,
-// inside fw_ws).  fw_ws: device scratch of vla_forward_streams_bytes(c, n_max, R, tail_rows) bytes with n <= n_max.
-size_t vla_forward_streams_bytes(const vla_config &c, int n_max, int R, int tail_rows);
+// The embedded rows of n rollouts' teacher-forced forward and its first n_layers layers (the kernels vla_logprob_recompute runs;
+// n_layers 0: the rows alone): the fp32 residual stream at the input of layer l is left in keep + l * n * R * H ([n * R, H] each, n_layers
+// + 1 of them; the layers read and write it there).  fw_ws: device scratch of vla_forward_streams_bytes(c, n_max, R) bytes with n <= n_max.
+size_t vla_forward_streams_bytes(const vla_config &c, int n_max, int R);
 int vla_forward_streams(vla_model *m, void *fw_ws, int n_max, const void *patch, const int32_t *ids, const int32_t *bins, int n,
-                        int P, int T, int A, int mode, const void *slot_embed, int tail_rows, float *keep, const float **x_final, hipStream_t st);
+                        int P, int T, int A, int mode, const void *slot_embed, int n_layers, float *keep, hipStream_t st);
 
 // Profiling scope: when profiling is enabled, records an event pair around the launches issued
 // during its lifetime, tagged with `label` (a string literal) and the algorithmic work.
