@@ -327,6 +327,8 @@ static int run_last_layer_tail(const vla_model *m, const Workspace &ws, const Ro
     const int H = c.hidden, F = c.ffn, M = ra.n_seq * ra.R, d = H / c.n_heads, Mt = ra.n_seq * tail.count;
     const vla_layer_weights &lw = m->layers[l];
     int rc;
+    const bool f32 = c.dtype == VLA_DTYPE_F32;                            // (see gemm_norms)
+    auto give_norm = [&](GemmArgs &g, const float *x, const void *gain) { g.norm_x = x; g.norm_gain = (const float *)gain; g.norm_eps = c.rms_eps; };
     // ---- K and V of every row
     bool kv_done = false;
     if (c.dtype == VLA_DTYPE_BF16 && d == 128 && !(force_generic() & (1 | 16))) {
@@ -347,8 +349,9 @@ static int run_last_layer_tail(const vla_model *m, const Workspace &ws, const Ro
         kv_done = rc == 1;
     }
     if (!kv_done) {          // plain path: the full projection (its q rows are not used), rotation and KV write
-        if ((rc = run_rmsnorm<T>(c, ws.Nrm, x_in, lw.attn_norm, M, 0, st))) return rc;
+        if (!f32 && (rc = run_rmsnorm<T>(c, ws.Nrm, x_in, lw.attn_norm, M, 0, st))) return rc;
         GemmArgs g{};
+        if (f32) give_norm(g, x_in, lw.attn_norm);
         g.A = ws.Nrm; g.W[0] = lw.wq; g.W[1] = lw.wk; g.W[2] = lw.wv; g.n_seg = 3; g.segN = H; g.C = ws.QKV; g.M = M; g.K = H;
         g.epilogue = EPI_STORE; g.a_rows = ws.a_rows;
         if ((rc = run_gemm<T>(c, g, nullptr, st))) return rc;
@@ -359,8 +362,9 @@ static int run_last_layer_tail(const vla_model *m, const Workspace &ws, const Ro
     }
     // ---- the tail rows: q, attention against the layer's K and V, O projection, feed-forward block
     if ((rc = launch_gather_rows(ws.tX, x_in, ra.n_seq, ra.R, tail.first, tail.count, H, st))) return rc;
-    if ((rc = run_rmsnorm<T>(c, ws.tNrm, ws.tX, lw.attn_norm, Mt, 0, st))) return rc;
+    if (!f32 && (rc = run_rmsnorm<T>(c, ws.tNrm, ws.tX, lw.attn_norm, Mt, 0, st))) return rc;
     GemmArgs g{};
+    if (f32) give_norm(g, ws.tX, lw.attn_norm);
     g.A = ws.tNrm; g.W[0] = lw.wq; g.n_seg = 1; g.segN = H; g.C = ws.tQf; g.M = Mt; g.K = H; g.epilogue = EPI_STORE; g.a_rows = ws.t_a_rows;
     if ((rc = run_gemm<T>(c, g, ws.tskinny, st))) return rc;
     if ((rc = launch_rope_q<T>((T *)ws.tQ, ws.tQf, ws.rope, ra.n_seq, tail.count, tail.first, c.n_heads, d, H, st))) return rc;
@@ -377,8 +381,9 @@ static int run_last_layer_tail(const vla_model *m, const Workspace &ws, const Ro
     g = GemmArgs{};
     g.A = ws.tAO; g.W[0] = lw.wo; g.n_seg = 1; g.segN = H; g.C = ws.tX; g.M = Mt; g.K = H; g.epilogue = EPI_RESIDUAL; g.a_rows = ws.t_a_rows;
     if ((rc = run_gemm<T>(c, g, ws.tskinny, st))) return rc;
-    if ((rc = run_rmsnorm<T>(c, ws.tNrm, ws.tX, lw.ffn_norm, Mt, 0, st))) return rc;
+    if (!f32 && (rc = run_rmsnorm<T>(c, ws.tNrm, ws.tX, lw.ffn_norm, Mt, 0, st))) return rc;
     g = GemmArgs{};
+    if (f32) give_norm(g, ws.tX, lw.ffn_norm);
     g.A = ws.tNrm; g.W[0] = lw.w_gate; g.W[1] = lw.w_up; g.n_seg = 2; g.segN = F; g.C = ws.tACT; g.M = Mt; g.K = H;
     g.epilogue = EPI_SWIGLU; g.a_rows = ws.t_a_rows;
     if ((rc = run_gemm<T>(c, g, ws.tskinny, st))) return rc;
@@ -387,9 +392,12 @@ static int run_last_layer_tail(const vla_model *m, const Workspace &ws, const Ro
     return run_gemm<T>(c, g, ws.tskinny, st);
 }
 
-// Steps of few rows: whether the QKV (N = hidden) and gate/up (N = ffn) GEMMs form the norm of their input themselves.
-static bool step_norms(const vla_config &c, const Workspace &ws, int M, int N) {
-    return c.dtype == VLA_DTYPE_BF16 && ws.skinny && !(force_generic() & (2 | 16)) && gemm_stream_norms(M, c.hidden, N);
+// Whether the QKV (N = hidden) and gate/up (N = ffn) GEMMs form the norm of their input themselves: steps of few rows, and fp32 models,
+// whose kernel takes the norm's factors out of the product (a norm of its own is a launch of 2.7 us that nothing overlaps: rollout of
+// the tiny decoder, 8 environments, 0.522 -> 0.455 ms with the head's final norm and a share of K in one go).
+static bool gemm_norms(const vla_config &c, const Workspace &ws, int R, int M, int N) {
+    if (c.dtype == VLA_DTYPE_F32) return true;
+    return R == 1 && ws.skinny && !(force_generic() & (2 | 16)) && gemm_stream_norms(M, c.hidden, N);
 }
 
 // `tail` (may be NULL): the rows whose final hidden state the caller reads.  Where use_tail() holds, the last layer
@@ -414,9 +422,9 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
     // in the order the stand-alone reduction would.
     const bool fuse_reduce = c.dtype == VLA_DTYPE_BF16 && ra.R == 1 && ws.skinny && !(force_generic() & (2 | 16)) &&
                              H % 1024 == 0 && H <= 8192;
-    const bool qkv_norms = ra.R == 1 && step_norms(c, ws, M, H), ffn_norms = ra.R == 1 && step_norms(c, ws, M, F);
+    const bool qkv_norms = gemm_norms(c, ws, ra.R, M, H), ffn_norms = gemm_norms(c, ws, ra.R, M, F);
     const bool f32_step = c.dtype == VLA_DTYPE_F32 && ra.R == 1;          // (the attention takes the QKV projection as it is)
-    auto give_norm = [&](GemmArgs &g, const void *gain) { g.norm_x = ws.X; g.norm_gain = (const float *)gain; g.norm_eps = c.rms_eps; };
+    auto give_norm = [&](GemmArgs &g, const float *x, const void *gain) { g.norm_x = x; g.norm_gain = (const float *)gain; g.norm_eps = c.rms_eps; };
     bool have_nrm = prepared && !qkv_norms;          // the sampler or the previous layer's down projection already wrote this layer's Nrm
     const bool tail_form = use_tail(tail, ra.R) && ws.tail_rows == tail->count && ra.R > 1;
     const bool copies = keep && ra.R == 1;
@@ -454,7 +462,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         g.A = ws.Nrm; g.W[0] = lw.wq; g.W[1] = lw.wk; g.W[2] = lw.wv; g.n_seg = 3; g.segN = H;
         g.C = ws.QKV; g.M = M; g.K = H; g.epilogue = EPI_STORE; g.a_rows = ws.a_rows;
         g.step = ra.R == 1;
-        if (qkv_norm) give_norm(g, lw.attn_norm);
+        if (qkv_norm) give_norm(g, x_in, lw.attn_norm);
         if (pk) { g.Wkb[0] = pk->wq; g.Wkb[1] = pk->wk; g.Wkb[2] = pk->wv; }
         // multi-row bf16 forwards at head_dim 128: rotation and KV write ride the projection's epilogue
         int fused = 0;
@@ -504,7 +512,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         g.A = ws.Nrm; g.W[0] = lw.w_gate; g.W[1] = lw.w_up; g.n_seg = 2; g.segN = F; g.C = ws.ACT; g.M = M; g.K = H;
         g.epilogue = EPI_SWIGLU; g.a_rows = ws.a_rows;
         g.step = ra.R == 1;
-        if (ffn_norm) give_norm(g, lw.ffn_norm);
+        if (ffn_norm) give_norm(g, ws.X, lw.ffn_norm);
         if (pk) { g.Wkb[0] = pk->w_gate; g.Wkb[1] = pk->w_up; }
         if ((rc = run_gemm<T>(c, g, ws.skinny, st))) return rc;
         g = GemmArgs{};
@@ -582,17 +590,25 @@ static int decode_impl(vla_model *m, void *kvbuf, void *wsbuf, const float *h_la
     if (mode == VLA_MODE_AR) {
         Workspace ws = plan_workspace(c, (char *)wsbuf, B, 1, S + A, B, false);
         const float *h = h_last;
+        // A step's rows go to the head without their final norm, which it forms as the loads bring them (a launch of 3 to 5 us per
+        // step less); the sums of squares, a few per row, take the place of the normalised rows.
+        const HeadNorm final_norm{(const float *)m->w.final_norm, c.rms_eps, ws.Hb};
+        const bool head_norms = B <= VLA_HEAD_PARTIAL_ROWS;
         for (int j = 0; j < A; j++) {
             bool more = j + 1 < A;
-            const NextStep next{ws.Nrm, step_norms(c, ws, B, H) ? nullptr : (const float *)m->layers[0].attn_norm, c.rms_eps, ws.rope, S + j, H / c.n_heads, c.rope_theta};
-            const bool prepares = more && B <= VLA_HEAD_PARTIAL_ROWS;
+            const NextStep next{ws.Nrm, gemm_norms(c, ws, 1, B, H) ? nullptr : (const float *)m->layers[0].attn_norm, c.rms_eps, ws.rope, S + j, H / c.n_heads, c.rope_theta};
+            const bool prepares = more && head_norms;
             if ((rc = launch_head_sample<T>(h, head, B, H, temperature, gumbel, nullptr, bins, logp, entropy, logits, A, j,
-                                            more ? ws.X : nullptr, (const T *)m->w.embed, c.vocab, ws.QKV, st, prepares ? &next : nullptr))) return rc;
+                                            more ? ws.X : nullptr, (const T *)m->w.embed, c.vocab, ws.QKV, st, prepares ? &next : nullptr,
+                                            j && head_norms ? &final_norm : nullptr))) return rc;
             if (!more) break;
             RowsArgs ra{B, 1, S + j, 0x7fffffff};
             if ((rc = run_layers<T>(m, ws, ra, kv, false, st, nullptr, nullptr, prepares))) return rc;
-            if ((rc = launch_final_norm_rows(ws.Hb, ws.X, (const float *)m->w.final_norm, B, 1, 0, 1, H, c.rms_eps, st))) return rc;
-            h = ws.Hb;
+            h = ws.X;
+            if (!head_norms) {
+                if ((rc = launch_final_norm_rows(ws.Hb, ws.X, (const float *)m->w.final_norm, B, 1, 0, 1, H, c.rms_eps, st))) return rc;
+                h = ws.Hb;
+            }
         }
     } else {
         Workspace ws = plan_workspace(c, (char *)wsbuf, B, A, S + A, B * A, false);

@@ -17,17 +17,6 @@ namespace {
 
 constexpr int MAXCH = 8;   // key chunks of 64 held in registers => at most 512 keys
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
 // What the projection left for this step (FUSE): the fp32 [n_seq, 3H] QKV rows.
 struct FusedQkv {
     const float *qkv;
@@ -119,7 +108,7 @@ __global__ void __launch_bounds__(64 * NWV) attn_decode_kernel(bf16_t *out, cons
         }
     }
     // ---- 2. softmax over all keys of the workgroup ---------------------------------------------------
-    mx = wave_max(mx);
+    mx = vla_wave_max(mx);
     if (lane == 0) red[wave] = mx;
     __syncthreads();
 #pragma unroll
@@ -136,7 +125,7 @@ __global__ void __launch_bounds__(64 * NWV) attn_decode_kernel(bf16_t *out, cons
         __syncthreads();
         sum = ps[(wave & 3) * 64 + lane] + ps[((wave & 3) + 4) * 64 + lane];
     }
-    sum = wave_sum(sum);
+    sum = vla_wave_sum(sum);
     if (lane == 0) red[NWV + wave] = sum;                          // (of eight waves, 4..7 repeat 0..3)
     __syncthreads();
     float tot = red[NWV];
@@ -170,9 +159,11 @@ __global__ void __launch_bounds__(64 * NWV) attn_decode_kernel(bf16_t *out, cons
         for (int e = 0; e < VPL; e++) acc[e] += pr * (float)v[e];
     }
 #pragma unroll
-    for (int off = LPR; off < 64; off <<= 1)
-#pragma unroll
-        for (int e = 0; e < VPL; e++) acc[e] += __shfl_xor(acc[e], off, 64);
+    for (int e = 0; e < VPL; e++) {
+        if constexpr (LPR <= 8) acc[e] = vla_fold_step<8>(acc[e], VlaAdd{});
+        if constexpr (LPR <= 16) acc[e] = vla_fold_step<16>(acc[e], VlaAdd{});
+        acc[e] = vla_fold_step<32>(acc[e], VlaAdd{});
+    }
     if (lane < LPR) {
 #pragma unroll
         for (int e = 0; e < VPL; e++) part[wave][c * VPL + e] = acc[e];

@@ -126,7 +126,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))
             st[i] = v;
             bmax = fmaxf(bmax, v);
         }
-        bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+        bmax = vla_fold_step<32>(bmax, VlaMax{});
         const float m_new = fmaxf(m_run, bmax);
         // every query sees key 0, so after block 0 m_new is finite
         const float corr = __expf(m_run - m_new);
@@ -142,7 +142,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))
             pf[i >> 3][i & 7] = ph;
             pl[i >> 3][i & 7] = (bf16_t)(p - (float)ph);
         }
-        psum += __shfl_xor(psum, 32, 64);
+        psum = vla_fold_step<32>(psum, VlaAdd{});
         l_run = l_run * corr + psum;
         m_run = m_new;
         if (!__all(corr == 1.0f)) {                        // the running max moved for some query of the wave
@@ -389,7 +389,7 @@ attn_prefill_loader_kernel(bf16_t *out, const bf16_t *qbuf, const bf16_t *kc,
                 float bmax = st[0];
 #pragma unroll
                 for (int i = 1; i < 16; i++) bmax = fmaxf(bmax, st[i]);
-                bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+                bmax = vla_fold_step<32>(bmax, VlaMax{});
                 const float m_new = fmaxf(m_run, bmax);    // every query sees key 0: finite from block 0 on
                 const float corr = __builtin_amdgcn_exp2f((m_run - m_new) * c2);
                 const float mc = m_new * c2;
@@ -403,7 +403,7 @@ attn_prefill_loader_kernel(bf16_t *out, const bf16_t *qbuf, const bf16_t *kc,
                     pf[i >> 3][i & 7] = ph;
                     pl[i >> 3][i & 7] = (bf16_t)(p - (float)ph);
                 }
-                psum += __shfl_xor(psum, 32, 64);
+                psum = vla_fold_step<32>(psum, VlaAdd{});
                 l_run = l_run * corr + psum;
                 m_run = m_new;
                 if (!__all(corr == 1.0f)) {

@@ -25,12 +25,8 @@ __device__ __forceinline__ void split_bf16(const f32x4_t &a, const f32x4_t &b, b
 // Sum or maximum over the 16 lanes that share a row.
 template <bool MAX>
 __device__ __forceinline__ float reduce16(float v) {
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) {
-        const float w = __shfl_xor(v, o, 64);
-        v = MAX ? fmaxf(v, w) : v + w;
-    }
-    return v;
+    if constexpr (MAX) return vla_row_fold(v, VlaMax{});
+    else return vla_row_fold(v, VlaAdd{});
 }
 
 __device__ __forceinline__ f32x4_t pick(bool c, f32x4_t a, f32x4_t b) {

@@ -31,24 +31,12 @@ template <typename T> __device__ __forceinline__ float ld(const T *p) { return (
 template <typename T> __device__ __forceinline__ T cvt(float v) { return (T)v; }
 
 __device__ __forceinline__ float bsum256(float v, float *red) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = vla_wave_sum(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     return (red[0] + red[1]) + (red[2] + red[3]);
 }
-__device__ __forceinline__ float wsum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-__device__ __forceinline__ float wmax(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
 // ---------------------------------------------------------------------------------------------- batched tile GEMM
 // C[b] (+)= alpha * op(A[b]) . op(B[b]), fp32 accumulation and output.  op(A) is m x k (A row-major [m, k], or
 // [k, m] with transA), op(B) is k x n (B row-major [k, n], or [n, k] with transB).  Batch b = b1 * inner + b2 moves
@@ -340,13 +328,13 @@ __global__ void __launch_bounds__(256) attn_softmax_kernel(float *SP, size_t n_r
             v[u] = j < nk ? s[j] : -INFINITY;
             m8 = fmaxf(m8, v[u]);
         }
-        m8 = wmax(m8);
+        m8 = vla_wave_max(m8);
 #pragma unroll
         for (int u = 0; u < 8; u++) {
             v[u] = u * 64 + lane < nk ? expf(v[u] - m8) : 0.f;
             sum8 += v[u];
         }
-        const float inv8 = 1.0f / wsum(sum8);
+        const float inv8 = 1.0f / vla_wave_sum(sum8);
 #pragma unroll
         for (int u = 0; u < 8; u++)
             if (u * 64 + lane < R) s[u * 64 + lane] = v[u] * inv8;
@@ -354,10 +342,10 @@ __global__ void __launch_bounds__(256) attn_softmax_kernel(float *SP, size_t n_r
     }
     float mx = -INFINITY;
     for (int j = lane; j < nk; j += 64) mx = fmaxf(mx, s[j]);
-    mx = wmax(mx);
+    mx = vla_wave_max(mx);
     float sum = 0.f;
     for (int j = lane; j < nk; j += 64) { const float e = expf(s[j] - mx); s[j] = e; sum += e; }
-    sum = wsum(sum);
+    sum = vla_wave_sum(sum);
     const float inv = 1.0f / sum;
     for (int j = lane; j < R; j += 64) s[j] = j < nk ? s[j] * inv : 0.f;
 }
@@ -372,7 +360,7 @@ __global__ void __launch_bounds__(256) attn_ds_kernel(float *dP, const float *P,
     const float *p = P + row * ldp;
     float dot = 0.f;
     for (int j = lane; j < nk; j += 64) dot += p[j] * d[j];
-    dot = wsum(dot);
+    dot = vla_wave_sum(dot);
     for (int j = lane; j < R; j += 64) d[j] = j < nk ? p[j] * (d[j] - dot) : 0.f;
 }
 
@@ -458,7 +446,7 @@ __global__ void __launch_bounds__(256) head_dz_kernel(float *dz, float *logp_out
 #pragma unroll 15
     for (int c = 1; c < n_part; c++) z += src[(size_t)c * M * VLA_N_BINS];
     const float y = z * inv_tau;
-    const float mw = wmax(y);
+    const float mw = vla_wave_max(y);
     if ((t & 63) == 0) zmax[t >> 6] = mw;
     __syncthreads();
     const float mx = fmaxf(fmaxf(zmax[0], zmax[1]), fmaxf(zmax[2], zmax[3]));
@@ -974,7 +962,7 @@ struct Backward {
         float *d_ao = a.GU;                          // [Mq, H] fp32; the gate / up pre-activations are no longer needed
         if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, H, d_ao, H, Mq, ws.a_rows))) return rc;
         float *dqkv = ws.Tmp;                        // [M, 3H] fp32: d q | d k | d v (q, k still in the rotated frame)
-        // dP = dO v^T ; dV = P^T dO ; dS = P (dP - rowsum(P dP)) ; dQ = dS k / sqrt(d) ; dK = dS^T q / sqrt(d)
+        // dP = dO v^T ; dV = P^T dO ; dS = P (dP - rovla_wave_sum(P dP)) ; dQ = dS k / sqrt(d) ; dK = dS^T q / sqrt(d)
         rc = 0;
         if constexpr (MF) {
             if (!(vla_force_generic() & 4) && (rc = try_attention_rows_backward(AttnRowsArgs{d_ao, (const bf16_t *)Q, ws.dP, a.SP, dqkv, R, Rq, Rp, nh, H, full_from, isd}, n, st)) < 0) return rc;

@@ -98,8 +98,7 @@ __global__ void __launch_bounds__(256) rmsnorm_bf16_kernel(bf16_t *out, const fl
 #pragma unroll
         for (int e = 0; e < 4; e++) ss += v[j][e] * v[j][e];
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+    ss = vla_wave_sum(ss);
     if ((t & 63) == 0) red[t >> 6] = ss;
     __syncthreads();
     ss = red[0] + red[1] + red[2] + red[3];
@@ -157,8 +156,7 @@ __global__ void __launch_bounds__(256) reduce_residual_rmsnorm_kernel(bf16_t *ou
         for (int e = 0; e < 4; e++) ss += xv[e] * xv[e];
     }
     if (!gain) return;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+    ss = vla_wave_sum(ss);
     if ((t & 63) == 0) red[t >> 6] = ss;
     __syncthreads();
     ss = red[0] + red[1] + red[2] + red[3];
@@ -202,8 +200,7 @@ __global__ void __launch_bounds__(256) rmsnorm_bf16_kb_kernel(bf16_t *out, const
 #pragma unroll
             for (int e = 0; e < 4; e++) ss += v[j][e] * v[j][e];
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+        ss = vla_wave_sum(ss);
         if ((t & 63) == 0) red[rr][t >> 6] = ss;
         __syncthreads();
         ss = red[rr][0] + red[rr][1] + red[rr][2] + red[rr][3];

@@ -155,8 +155,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
             for (int m = 0; m < NORM; m++) {
                 ss[m] = chain[m][t256];
                 add(m);
-#pragma unroll
-                for (int o = 32; o; o >>= 1) ss[m] += __shfl_xor(ss[m], o, 64);
+                ss[m] = vla_wave_sum(ss[m]);
                 if (lane == 0) squares[m][wave & 3] = ss[m];
             }
         }

@@ -26,17 +26,6 @@ constexpr int CHUNK = 256;
 
 typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // the caller's h may be aligned to 4 bytes only
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
 // x = hi + mid + lo to 24 bits; an infinite head keeps its infinity (the remainders would be NaN)
 __device__ __forceinline__ void split3(float x, bf16_t &hi, bf16_t &mid, bf16_t &lo) {
     hi = (bf16_t)x;
@@ -51,13 +40,14 @@ __device__ __forceinline__ void split3(float x, bf16_t &hi, bf16_t &mid, bf16_t 
 // UN steps are loaded together ahead of their products (a call of few rows is a chain of memory latencies: one per
 // group of steps).  FULL: the chunk is CHUNK long; otherwise the steps past k1 count as zeros.  TAME: infinite weights
 // meet the first part of h only.
-template <int RB, int CB, bool FULL, int UN, bool TAME = false>
-__device__ __forceinline__ void chunk_product(f32x4_t (&acc)[RB][CB], const float *const (&hrow)[RB], const bf16_t *const (&wrow)[CB],
-                                              int k0, int k1, int kq) {
+// NORM: the rows come as the residual stream; each element enters times `gain`, and ss[rb] gains the squares of this lane's.
+template <int RB, int CB, bool FULL, int UN, bool NORM, bool TAME = false>
+__device__ __forceinline__ void chunk_product(f32x4_t (&acc)[RB][CB], float (&ss)[RB], const float *const (&hrow)[RB], const bf16_t *const (&wrow)[CB],
+                                              const float *gain, int k0, int k1, int kq) {
 #pragma unroll 1
     for (int g = 0; g < CHUNK / 32; g += UN) {
         bf16x8_t w[UN][CB];
-        f32x4_t x[UN][RB][2];
+        f32x4_t x[UN][RB][2], gv[UN][2];
 #pragma unroll
         for (int i = 0; i < UN; i++) {
             const int kk = k0 + (g + i) * 32 + kq * 8;
@@ -72,6 +62,9 @@ __device__ __forceinline__ void chunk_product(f32x4_t (&acc)[RB][CB], const floa
                     x[i][rb][u] = *(const f32x4_u *)(hrow[rb] + ks + 4 * u);
                     if (!in) x[i][rb][u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
                 }
+            if (NORM)
+#pragma unroll
+                for (int u = 0; u < 2; u++) gv[i][u] = *(const f32x4_u *)(gain + ks + 4 * u);
             if (!in)
 #pragma unroll
                 for (int cb = 0; cb < CB; cb++)
@@ -93,6 +86,13 @@ __device__ __forceinline__ void chunk_product(f32x4_t (&acc)[RB][CB], const floa
 #pragma unroll
             for (int rb = 0; rb < RB; rb++) {
                 bf16x8_t hi, mid, lo;
+                if (NORM) {
+#pragma unroll
+                    for (int e = 0; e < 8; e++) {
+                        ss[rb] += x[i][rb][e >> 2][e & 3] * x[i][rb][e >> 2][e & 3];
+                        x[i][rb][e >> 2][e & 3] *= gv[i][e >> 2][e & 3];
+                    }
+                }
 #pragma unroll
                 for (int e = 0; e < 8; e++) {
                     bf16_t a, b, c;
@@ -109,13 +109,13 @@ __device__ __forceinline__ void chunk_product(f32x4_t (&acc)[RB][CB], const floa
         }
     }
 }
-template <int RB, int CB, bool FULL, int UN>
-__device__ __forceinline__ void chunk_product(f32x4_t (&acc)[RB][CB], const float *const (&hrow)[RB], const float *const (&wrow)[CB],
-                                              int k0, int k1, int kq) {
+template <int RB, int CB, bool FULL, int UN, bool NORM>
+__device__ __forceinline__ void chunk_product(f32x4_t (&acc)[RB][CB], float (&ss)[RB], const float *const (&hrow)[RB], const float *const (&wrow)[CB],
+                                              const float *gain, int k0, int k1, int kq) {
     // a lane's four consecutive K elements take turns as the instruction's one element per lane
 #pragma unroll 1
     for (int g = 0; g < CHUNK / 16; g += 2 * UN) {
-        f32x4_t w[2 * UN][CB], x[2 * UN][RB];
+        f32x4_t w[2 * UN][CB], x[2 * UN][RB], gv[2 * UN];
 #pragma unroll
         for (int i = 0; i < 2 * UN; i++) {
             const int kk = k0 + (g + i) * 16 + kq * 4;
@@ -131,10 +131,17 @@ __device__ __forceinline__ void chunk_product(f32x4_t (&acc)[RB][CB], const floa
                 x[i][rb] = *(const f32x4_u *)(hrow[rb] + ks);
                 if (!in) x[i][rb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             }
+            if (NORM) gv[i] = *(const f32x4_u *)(gain + ks);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < 2 * UN; i++)
+        for (int i = 0; i < 2 * UN; i++) {
+            if (NORM) {
+#pragma unroll
+                for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++) { ss[rb] += x[i][rb][e] * x[i][rb][e]; x[i][rb][e] *= gv[i][e]; }
+            }
 #pragma unroll
             for (int e = 0; e < 4; e++)
 #pragma unroll
@@ -142,6 +149,7 @@ __device__ __forceinline__ void chunk_product(f32x4_t (&acc)[RB][CB], const floa
 #pragma unroll
                     for (int cb = 0; cb < CB; cb++)
                         acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][cb][e], x[i][rb][e], acc[rb][cb], 0, 0, 0);
+        }
     }
 }
 
@@ -174,7 +182,7 @@ __device__ __forceinline__ int sample_row(const float *z, const float (&g)[4], c
         t[j] = a.gumbel ? y[j] + g[j] : y[j];
         mx = fmaxf(mx, y[j]);
     }
-    mx = wave_max(mx);
+    mx = vla_wave_max(mx);
     float se = 0.f, sy = 0.f;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
@@ -182,8 +190,8 @@ __device__ __forceinline__ int sample_row(const float *z, const float (&g)[4], c
         se += e;
         sy += e * y[j];
     }
-    se = wave_sum(se);
-    sy = wave_sum(sy);
+    se = vla_wave_sum(se);
+    sy = vla_wave_sum(sy);
     const float lse = mx + logf(se);
     // argmax of t, lowest bin index on ties
     float bt = t[0];
@@ -191,13 +199,24 @@ __device__ __forceinline__ int sample_row(const float *z, const float (&g)[4], c
 #pragma unroll
     for (int j = 1; j < 4; j++)
         if (t[j] > bt) { bt = t[j]; bk = lane + 64 * j; }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const float ot = __shfl_xor(bt, off, 64);
-        const int ok = __shfl_xor(bk, off, 64);
+    auto meet = [&](float ot, float okf) {
+        const int ok = __builtin_bit_cast(int, okf);
         if (ot > bt || (ot == bt && ok < bk)) { bt = ot; bk = ok; }
+    };
+    auto as_f = [&] { return __builtin_bit_cast(float, bk); };
+    {
+        const VlaPair t32 = vla_pair<32>(bt), k32 = vla_pair<32>(as_f());
+        bt = t32.a; bk = __builtin_bit_cast(int, k32.a);
+        meet(t32.b, k32.b);
+        const VlaPair t16 = vla_pair<16>(bt), k16 = vla_pair<16>(as_f());
+        bt = t16.a; bk = __builtin_bit_cast(int, k16.a);
+        meet(t16.b, k16.b);
     }
-    int bin = bk;
+    meet(vla_dpp<0x128>(bt), vla_dpp<0x128>(as_f()));                                        // lane ^ 8
+    meet(vla_dpp<0x1b>(vla_dpp<0x141>(bt)), vla_dpp<0x1b>(vla_dpp<0x141>(as_f())));          // lane ^ 4: reversed in eights, then in fours
+    meet(vla_dpp<0x4e>(bt), vla_dpp<0x4e>(as_f()));
+    meet(vla_dpp<0xb1>(bt), vla_dpp<0xb1>(as_f()));
+    int bin = __builtin_amdgcn_readfirstlane(bk);
     if (a.given) bin = min(max(a.given[o], 0), VLA_N_BINS - 1);
     if (lane == 0) {
         if (a.bins_out) a.bins_out[o] = bin;
@@ -222,9 +241,9 @@ __device__ __forceinline__ void next_embedding(float *dst, const T *embed, int v
 }
 
 // Products of 16 * RB rows and 16 * CB bins from bin0 over the chunks [c0, c1), added in chunk order.
-template <typename T, int RB, int CB, int UN>
-__device__ __forceinline__ void tile_logits(f32x4_t (&total)[RB][CB], const float *h, const T *Wb, int M, int H, int m0, int bin0,
-                                            int c0, int c1) {
+template <typename T, int RB, int CB, int UN, bool NORM>
+__device__ __forceinline__ void tile_logits(f32x4_t (&total)[RB][CB], float (&ss)[RB], const float *h, const float *gain, const T *Wb, int M, int H,
+                                            int m0, int bin0, int c0, int c1) {
     const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
     const T *wrow[CB];
 #pragma unroll
@@ -242,8 +261,8 @@ __device__ __forceinline__ void tile_logits(f32x4_t (&total)[RB][CB], const floa
         };
         clear();
         const int k0 = c * CHUNK, k1 = min(H, k0 + CHUNK);
-        if (k1 - k0 == CHUNK) chunk_product<RB, CB, true, UN>(acc, hrow, wrow, k0, k1, kq);
-        else chunk_product<RB, CB, false, 1>(acc, hrow, wrow, k0, k1, kq);
+        if (k1 - k0 == CHUNK) chunk_product<RB, CB, true, UN, NORM>(acc, ss, hrow, wrow, gain, k0, k1, kq);
+        else chunk_product<RB, CB, false, 1, NORM>(acc, ss, hrow, wrow, gain, k0, k1, kq);
         if constexpr (sizeof(T) == 2) {
             bool nan = false;
 #pragma unroll
@@ -254,7 +273,9 @@ __device__ __forceinline__ void tile_logits(f32x4_t (&total)[RB][CB], const floa
                     for (int r = 0; r < 4; r++) nan = nan || __builtin_isnan(acc[rb][cb][r]);
             if (__any(nan)) {
                 clear();
-                chunk_product<RB, CB, false, 1, true>(acc, hrow, wrow, k0, k1, kq);
+                float again[RB];
+                for (int rb = 0; rb < RB; rb++) again[rb] = 0.f;
+                chunk_product<RB, CB, false, 1, NORM, true>(acc, again, hrow, wrow, gain, k0, k1, kq);
             }
         }
 #pragma unroll
@@ -266,14 +287,23 @@ __device__ __forceinline__ void tile_logits(f32x4_t (&total)[RB][CB], const floa
     }
 }
 
-// Partial form: grid (n_chunks, 16-row tiles, quarters of the bins), two waves of 32 bins each, P[chunk][M][256].
-template <typename T>
-__global__ void __launch_bounds__(128) head_partial_kernel(const float *h, const T *Wb, float *P, int M, int H) {
-    constexpr int CB = 2;
+// Partial form: grid (n_chunks, 16-row tiles, parts of the bins), two waves of 16 CB bins each, P[chunk][M][256].  CB = 2; fp32, whose
+// instruction takes 128 steps of 32 cycles for a chunk of 32 bins, 1 while that leaves a CU no more than two workgroups: tiny decoder,
+// 8 rows, 5.4 -> 4.2 us (with the norm 5.6 -> 5.5).
+// NORM: h is the residual stream, whose norm's gain enters here and whose squares' sum per chunk goes to squares[chunk][M]; 1 / rms
+// is the sampler's to apply.
+template <typename T, int CB, bool NORM>
+__global__ void __launch_bounds__(128) head_partial_kernel(const float *h, const float *gain, const T *Wb, float *P, float *squares, int M, int H) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m0 = blockIdx.y * 16, m = m0 + (lane & 15);
-    const int bin0 = blockIdx.z * 64 + wave * (16 * CB);
+    const int bin0 = (blockIdx.z * 2 + wave) * (16 * CB);
     f32x4_t total[1][CB];
-    tile_logits<T, 1, CB, 8>(total, h, Wb, M, H, m0, bin0, blockIdx.x, blockIdx.x + 1);
+    float ss[1] = {0.f};
+    tile_logits<T, 1, CB, 8, NORM>(total, ss, h, gain, Wb, M, H, m0, bin0, blockIdx.x, blockIdx.x + 1);
+    if (NORM && bin0 == 0) {
+        ss[0] += __shfl_xor(ss[0], 16, 64);
+        ss[0] += __shfl_xor(ss[0], 32, 64);
+        if (lane < 16 && m < M) squares[(size_t)blockIdx.x * M + m] = ss[0];
+    }
     if (m >= M) return;
     float *out = P + ((size_t)blockIdx.x * M + m) * VLA_N_BINS + bin0 + (lane >> 4) * 4;
 #pragma unroll
@@ -286,7 +316,7 @@ __global__ void __launch_bounds__(128) head_partial_kernel(const float *h, const
 // rollout of 7 tokens 548 -> 529 us; 7B width, 8 layers, 1 environment 6.50 -> 6.48 ms; 13 environments 6.67 -> 6.63.
 template <typename T>
 __global__ void __launch_bounds__(256) sample_kernel(const float *P, int n_part, int M, SampleArgs a, float *X_next, const T *embed,
-                                                    int vocab, int H, NextStep next) {
+                                                    int vocab, int H, NextStep next, const float *squares, float eps) {
     typedef T t4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));   // the caller's embedding: element alignment
     typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
     __shared__ float z[VLA_N_BINS];
@@ -306,8 +336,15 @@ __global__ void __launch_bounds__(256) sample_kernel(const float *P, int n_part,
     float g[4];
     load_noise(g, a, row, lane);
     float s = src[0];
+    if (squares) {                               // the rows came without their norm's 1 / rms
+        float q = squares[row];
 #pragma unroll 15
-    for (int c = 1; c < n_part; c++) s += src[(size_t)c * M * VLA_N_BINS];
+        for (int c = 1; c < n_part; c++) { s += src[(size_t)c * M * VLA_N_BINS]; q += squares[(size_t)c * M + row]; }
+        s *= 1.0f / sqrtf(q / (float)H + eps);
+    } else {
+#pragma unroll 15
+        for (int c = 1; c < n_part; c++) s += src[(size_t)c * M * VLA_N_BINS];
+    }
     z[threadIdx.x] = s;
     __syncthreads();
     if (threadIdx.x < 64) {
@@ -340,7 +377,8 @@ __global__ void __launch_bounds__(256) head_whole_kernel(const float *h, const T
     __shared__ __attribute__((aligned(16))) float z[16 * RB * LD];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m0 = blockIdx.x * (16 * RB);
     f32x4_t total[RB][CB];
-    tile_logits<T, RB, CB, 2>(total, h, Wb, M, H, m0, wave * 64, 0, (H + CHUNK - 1) / CHUNK);
+    float ss[RB];
+    tile_logits<T, RB, CB, 2, false>(total, ss, h, nullptr, Wb, M, H, m0, wave * 64, 0, (H + CHUNK - 1) / CHUNK);
 #pragma unroll
     for (int rb = 0; rb < RB; rb++)
 #pragma unroll
@@ -364,28 +402,38 @@ size_t head_scratch_bytes(int n_rows, int H) {
 
 int head_chunks(int H) { return chunks_of(H); }
 
+template <typename T, bool NORM>
+static int launch_head_partial(const float *h, const float *gain, const T *Wb, float *P, float *squares, int n_rows, int H, hipStream_t st) {
+    const int tiles = (n_rows + 15) / 16, chunks = chunks_of(H);
+    if (sizeof(T) == 4 && (long)tiles * chunks * 8 <= 512) head_partial_kernel<T, 1, NORM><<<dim3(chunks, tiles, 8), 128, 0, st>>>(h, gain, Wb, P, squares, n_rows, H);
+    else head_partial_kernel<T, 2, NORM><<<dim3(chunks, tiles, 4), 128, 0, st>>>(h, gain, Wb, P, squares, n_rows, H);
+    return vla_check_launch("head_logits");
+}
+
 // Partial logits alone: P[chunk][n_rows][256], to be added in chunk order.
 template <typename T>
 int launch_head_logits(const float *h, const T *lm_head_bins, float *P, int n_rows, int H, hipStream_t st) {
     if (n_rows == 0) return 0;
-    head_partial_kernel<T><<<dim3(head_chunks(H), (n_rows + 15) / 16, 4), 128, 0, st>>>(h, lm_head_bins, P, n_rows, H);
-    return vla_check_launch("head_logits");
+    return launch_head_partial<T, false>(h, nullptr, lm_head_bins, P, nullptr, n_rows, H, st);
 }
 
 template <typename T>
 int launch_head_sample(const float *h, const T *lm_head_bins, int n_rows, int H, float temperature,
                        const float *gumbel, const int32_t *given_bins, int32_t *bins_out, float *logp,
                        float *ent, float *logits, int out_stride, int out_off, float *X_next,
-                       const T *embed, int vocab, float *scratch, hipStream_t st, const NextStep *next) {
+                       const T *embed, int vocab, float *scratch, hipStream_t st, const NextStep *next, const HeadNorm *norm) {
     if (n_rows == 0) return 0;
     ProfScope ps("head_sample", 2.0 * n_rows * H * VLA_N_BINS, st);
     const SampleArgs a{temperature, gumbel, given_bins, bins_out, logp, ent, logits, out_stride, out_off};
     if (n_rows > VLA_HEAD_PARTIAL_ROWS) {
+        if (norm) { vla_set_error("internal: the norm in the head was declined"); return VLA_ESHAPE; }
         head_whole_kernel<T><<<(n_rows + 31) / 32, 256, 0, st>>>(h, lm_head_bins, a, X_next, embed, vocab, n_rows, H);
         return vla_check_launch("head_sample");
     }
-    if (int rc = launch_head_logits<T>(h, lm_head_bins, scratch, n_rows, H, st)) return rc;
-    sample_kernel<T><<<n_rows + (next ? 1 : 0), 256, 0, st>>>(scratch, head_chunks(H), n_rows, a, X_next, embed, vocab, H, next ? *next : NextStep{});
+    if (int rc = norm ? launch_head_partial<T, true>(h, norm->gain, lm_head_bins, scratch, norm->squares, n_rows, H, st)
+                      : launch_head_logits<T>(h, lm_head_bins, scratch, n_rows, H, st)) return rc;
+    sample_kernel<T><<<n_rows + (next ? 1 : 0), 256, 0, st>>>(scratch, head_chunks(H), n_rows, a, X_next, embed, vocab, H, next ? *next : NextStep{},
+                                                              norm ? norm->squares : nullptr, norm ? norm->eps : 0.f);
     return vla_check_launch("head_sample");
 }
 
@@ -393,6 +441,6 @@ int launch_head_sample(const float *h, const T *lm_head_bins, int n_rows, int H,
     template int launch_head_logits<T>(const float *, const T *, float *, int, int, hipStream_t);             \
     template int launch_head_sample<T>(const float *, const T *, int, int, float, const float *,              \
                                        const int32_t *, int32_t *, float *, float *, float *, int, int,       \
-                                       float *, const T *, int, float *, hipStream_t, const NextStep *);
+                                       float *, const T *, int, float *, hipStream_t, const NextStep *, const HeadNorm *);
 INSTANTIATE(float)
 INSTANTIATE(bf16_t)

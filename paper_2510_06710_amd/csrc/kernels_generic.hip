@@ -4,6 +4,8 @@
 // MFMA / streaming kernels of the other translation units and keep the rest.
 #include "vla_internal.h"
 
+#include <type_traits>
+
 namespace {
 
 typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // caller-owned fp32 arrays: element alignment
@@ -14,20 +16,9 @@ template <typename T> __device__ __forceinline__ T from_f(float v);
 template <> __device__ __forceinline__ float from_f<float>(float v) { return v; }
 template <> __device__ __forceinline__ bf16_t from_f<bf16_t>(float v) { return (bf16_t)v; }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
 // Sum over a 256-thread block; `red` is 4 floats of LDS.  Every thread gets the total.
 __device__ __forceinline__ float block_sum_256(float v, float *red) {
-    v = wave_sum(v);
+    v = vla_wave_sum(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
@@ -146,12 +137,15 @@ __device__ __forceinline__ f32x4_t load4(const T *p, int k, int K) {
     return v;
 }
 
-template <typename T, int EPI, bool VEC, int MB, int NBK>
+// NORM (fp32): A is the residual stream and the product that of RMSNorm(A) gain: (A gain) . W^T as the loads bring A, each row times
+// its 1 / rms at the end, whose squares the same loads bring.
+template <typename T, int EPI, bool VEC, int MB, int NBK, int UN, bool NORM>
 __global__ void __launch_bounds__(512) gemm_generic_kernel(const T *A, const T *W0, const T *W1, const T *W2, int segN, void *Cv,
-                                                           const float *res, int M, int N, int K) {
-    constexpr int NW = 8, NP = (EPI == EPI_SWIGLU) ? 2 : 1, UN = MB * NBK > 1 ? 1 : 4;
+                                                           const float *res, int M, int N, int K, const float *gain, float eps) {
+    constexpr int NW = 8, NP = (EPI == EPI_SWIGLU) ? 2 : 1;
     __shared__ __attribute__((aligned(16))) f32x4_t part[NW][NP * MB * NBK][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
+    __shared__ float squares[NORM ? NW : 1][NORM ? MB * 16 : 1];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kq = lane >> 4;
     const int m0 = blockIdx.y * (16 * MB), n0 = blockIdx.x * (16 * NBK);
     const T *a[MB], *w[NP][NBK];
 #pragma unroll
@@ -174,14 +168,18 @@ __global__ void __launch_bounds__(512) gemm_generic_kernel(const T *A, const T *
         for (int i = 0; i < MB; i++)
 #pragma unroll
             for (int j = 0; j < NBK; j++) acc[b][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    float ss[MB];
+#pragma unroll
+    for (int i = 0; i < MB; i++) ss[i] = 0.f;
 #pragma unroll 1
     for (int g = wave * 16; g < K; g += NW * 16 * UN) {
-        f32x4_t av[UN][MB], wv[UN][NP][NBK];
+        f32x4_t av[UN][MB], wv[UN][NP][NBK], gv[UN];
 #pragma unroll
         for (int i = 0; i < UN; i++) {
             const int k = g + i * NW * 16 + kq * 4;       // (past K: zeros)
 #pragma unroll
             for (int x = 0; x < MB; x++) av[i][x] = load4<T, VEC>(a[x], k, K);
+            if (NORM) gv[i] = load4<float, VEC>(gain, k, K);
 #pragma unroll
             for (int b = 0; b < NP; b++)
 #pragma unroll
@@ -189,7 +187,14 @@ __global__ void __launch_bounds__(512) gemm_generic_kernel(const T *A, const T *
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < UN; i++)
+        for (int i = 0; i < UN; i++) {
+            if (i && g + i * NW * 16 >= K) break;
+            if (NORM) {
+#pragma unroll
+                for (int x = 0; x < MB; x++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++) { ss[x] += av[i][x][e] * av[i][x][e]; av[i][x][e] *= gv[i][e]; }
+            }
 #pragma unroll
             for (int e = 0; e < 4; e++)
 #pragma unroll
@@ -199,6 +204,15 @@ __global__ void __launch_bounds__(512) gemm_generic_kernel(const T *A, const T *
 #pragma unroll
                         for (int j = 0; j < NBK; j++)
                             acc[b][x][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[i][b][j][e], av[i][x][e], acc[b][x][j], 0, 0, 0);
+        }
+    }
+    if (NORM) {
+#pragma unroll
+        for (int x = 0; x < MB; x++) {
+            ss[x] += __shfl_xor(ss[x], 16, 64);
+            ss[x] += __shfl_xor(ss[x], 32, 64);
+            if (kq == 0) squares[wave][x * 16 + l16] = ss[x];
+        }
     }
 #pragma unroll
     for (int b = 0; b < NP; b++)
@@ -221,6 +235,16 @@ __global__ void __launch_bounds__(512) gemm_generic_kernel(const T *A, const T *
 #pragma unroll
             for (int r = 0; r < 4; r++) sum[b][r] += v[r];
         }
+    }
+    if (NORM) {
+        float q = squares[0][x * 16 + l16];
+#pragma unroll
+        for (int s = 1; s < NW; s++) q += squares[s][x * 16 + l16];
+        const float r = 1.0f / sqrtf(q / (float)K + eps);
+#pragma unroll
+        for (int b = 0; b < NP; b++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) sum[b][e] *= r;
     }
 #pragma unroll
     for (int r = 0; r < 4; r++) {
@@ -366,14 +390,14 @@ __global__ void __launch_bounds__(256) attention_generic_kernel(T *out, const T 
         sc[p] = acc;
         mx = fmaxf(mx, acc);
     }
-    mx = wave_max(mx);
+    mx = vla_wave_max(mx);
     float sum = 0.f;
     for (int p = lane; p < nk; p += 64) {
         float e = expf(sc[p] - mx);
         sc[p] = e;
         sum += e;
     }
-    sum = wave_sum(sum);
+    sum = vla_wave_sum(sum);
     __builtin_amdgcn_wave_barrier();
     float inv = 1.0f / sum;
     for (int i = lane; i < d; i += 64) {
@@ -385,11 +409,14 @@ __global__ void __launch_bounds__(256) attention_generic_kernel(T *out, const T 
 
 // The attention of an fp32 decode step (one new row per sequence) straight from the QKV projection: rotation, KV write and the
 // kernel above in one.  Bound by latency: WAVES waves per (sequence, head), a key per thread, V in four parts of 32 positions whose
-// sums are added in order; the first K and V loads leave before the rotation.  The new position's k and v come from LDS.  Four waves:
-// tiny decoder, 8 environments, 68 keys: 8.5 + 9 us in two launches, 8.3 here; six steps of a width-1024 decoder of four layers, 700
+// sums are added in order; the first K and V loads leave before the rotation.  The new position's k and v come from LDS, its k once
+// into the registers of the lane that has it; the weights are padded with zeros to whole runs, so that P.V reads four at a time without a
+// branch per position.  Four waves: tiny decoder, 8 environments, 68 keys: 8.5 + 9 us in two launches, 7.4 here, 5.3 with the padding and
+// lane moves; six steps of a width-1024 decoder of four layers, 700
 // keys: 4.15 -> 1.66 ms at 8 environments, 6.99 -> 5.84 at 128.  One wave, for many pairs of few keys: four pairs share a workgroup, with
 // half the loads in flight a pair's registers shrink from 4 x 162 to 89 a lane, so that 4096 pairs run at once and not in five
 // rounds, and no wave is there for keys that are not.  Either forms every sum in the same order: same bits.
+__host__ __device__ constexpr int attention_step_scores(int nk) { return (nk + 31) / 32 * 32; }
 template <int WAVES>
 __global__ void __launch_bounds__(256) attention_step_kernel(float *out, const float *qkv, const float2 *table, float *kc, float *vc, int pos,
                                                              int n_items, int n_heads, int d, int pos_stride, int H) {
@@ -409,7 +436,8 @@ __global__ void __launch_bounds__(256) attention_step_kernel(float *out, const f
     };
     const int s = item / n_heads, h = item - s * n_heads;
     const int nk = pos + 1, last = max(pos - 1, 0), half = d / 2, nc = d / 8;    // (addresses past the last stored key: clamped, not used)
-    float *qs = smem + (ALONE ? (size_t)wave * (3 * d + nk) : 0), *ks = qs + d, *vs = ks + d, *sc = vs + d, *part = sc + nk, *red = part + 4 * d;
+    const int nkp = attention_step_scores(nk);                                   // weights of whole runs of positions: zeros past the last
+    float *qs = smem + (ALONE ? (size_t)wave * (3 * d + nkp) : 0), *ks = qs + d, *vs = ks + d, *sc = vs + d, *part = sc + nkp, *red = part + 4 * d;
     const float *row = qkv + (size_t)s * 3 * H + (size_t)h * d;
     const size_t head = (size_t)s * n_heads + h;
     float *kh = kc + head * (size_t)d * pos_stride, *vh = vc + head * (size_t)pos_stride * d;
@@ -447,20 +475,20 @@ __global__ void __launch_bounds__(256) attention_step_kernel(float *out, const f
             if (p != t || c0)
 #pragma unroll
                 for (int c = 0; c < NC; c++) kr[c] = *(const t8 *)(kh + ((size_t)min(c0 + c, nc - 1) * pos_stride + min(p, last)) * 8);
+            if (p == pos)
+#pragma unroll
+                for (int c = 0; c < NC; c++) kr[c] = *(const t8 *)(ks + min(c0 + c, nc - 1) * 8);
 #pragma unroll
             for (int c = 0; c < NC; c++)
                 if (c0 + c < nc)
 #pragma unroll
-                    for (int e = 0; e < 8; e++) {
-                        const int i = (c0 + c) * 8 + e;
-                        acc += qs[i] * (p < pos ? kr[c][e] : ks[i]);
-                    }
+                    for (int e = 0; e < 8; e++) acc += qs[(c0 + c) * 8 + e] * kr[c][e];
         }
         acc *= scale;
         sc[p] = acc;
         mx = fmaxf(mx, acc);
     }
-    mx = wave_max(mx);
+    mx = vla_wave_max(mx);
     if constexpr (!ALONE) {
         if (lane == 0) red[wave] = mx;
         __syncthreads();
@@ -471,13 +499,13 @@ __global__ void __launch_bounds__(256) attention_step_kernel(float *out, const f
 #pragma unroll
     for (int v = 0; v < NV; v++) {
         sum[v] = 0.f;
-        if (ALONE && v * 64 >= nk) continue;
-        for (int p = v * 64 + t; p < nk; p += 256) {
-            const float e = expf(sc[p] - mx);
+        if (ALONE && v * 64 >= nkp) continue;
+        for (int p = v * 64 + t; p < nkp; p += 256) {
+            const float e = p < nk ? expf(sc[p] - mx) : 0.f;
             sc[p] = e;
             sum[v] += e;
         }
-        sum[v] = wave_sum(sum[v]);
+        sum[v] = vla_wave_sum(sum[v]);
     }
     if constexpr (!ALONE)
         if (lane == 0) red[4 + wave] = sum[0];
@@ -488,6 +516,7 @@ __global__ void __launch_bounds__(256) attention_step_kernel(float *out, const f
     const float inv = 1.0f / total;
     for (int i = lane; i < d; i += 64) {
         float acc[NV];
+        const float v_new = vs[i];
 #pragma unroll
         for (int v = 0; v < NV; v++) {
             acc[v] = 0.f;
@@ -499,9 +528,13 @@ __global__ void __launch_bounds__(256) attention_step_kernel(float *out, const f
 #pragma unroll
                         for (int u = 0; u < NL; u++) vr[u] = vh[(size_t)min(p0 + l + u, last) * d + i];
 #pragma unroll
-                    for (int u = 0; u < NL; u++) {
-                        const int p = p0 + l + u;
-                        if (p < nk) acc[v] += sc[p] * (p < pos ? vr[u] : vs[i]);
+                    for (int u = 0; u < NL; u += 4) {
+                        const f32x4_t w = *(const f32x4_t *)(sc + p0 + l + u);
+#pragma unroll
+                        for (int e = 0; e < 4; e++) {
+                            const int p = p0 + l + u + e;
+                            acc[v] += w[e] * (p < pos ? vr[u + e] : p == pos ? v_new : 0.f);
+                        }
                     }
                 }
             }
@@ -569,27 +602,39 @@ int launch_final_norm_rows(float *out, const float *X, const float *gain, int n_
     final_norm_rows_kernel<<<n_seq * n_rows, 256, 0, st>>>(out, X, gain, rows_per_seq, row0, n_rows, H, eps);
     return vla_check_launch("final_norm_rows");
 }
-template <typename T, int EPI, bool VEC>
+template <typename T, int EPI, bool VEC, bool NORM>
 static void gemm_generic_tile(const GemmArgs &g, int N, hipStream_t st) {
     constexpr int MB = (EPI == EPI_SWIGLU) ? 2 : 4, NBK = 2;
-    const T *A = (const T *)g.A, *W0 = (const T *)g.W[0], *W1 = (const T *)g.W[1], *W2 = (const T *)g.W[2];
+    const T *A = (const T *)(NORM ? (const void *)g.norm_x : g.A), *W0 = (const T *)g.W[0], *W1 = (const T *)g.W[1], *W2 = (const T *)g.W[2];
     const float *res = g.res ? g.res : (const float *)g.C;
     const dim3 big((N + 16 * NBK - 1) / (16 * NBK), (g.M + 16 * MB - 1) / (16 * MB));
     // The large tile wants two workgroups per CU; its sums are those of the small one.  (Fewer than 512 large tiles are
-    // at most 4096 + a few rows of small ones.)
-    if ((size_t)big.x * big.y < 512)
-        gemm_generic_kernel<T, EPI, VEC, 1, 1><<<dim3((N + 15) / 16, (g.M + 15) / 16), 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, res, g.M, N, g.K);
-    else
-        gemm_generic_kernel<T, EPI, VEC, MB, NBK><<<big, 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, res, g.M, N, g.K);
+    // at most 4096 + a few rows of small ones.)  A wave of the small tile loads its whole share of K at once where that is up to
+    // eight blocks: a down projection of K = 688 4.9 us as six, 5.5 as four and two.
+    if ((size_t)big.x * big.y >= 512) {
+        gemm_generic_kernel<T, EPI, VEC, MB, NBK, 1, NORM><<<big, 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, res, g.M, N, g.K, g.norm_gain, g.norm_eps);
+        return;
+    }
+    const dim3 small((N + 15) / 16, (g.M + 15) / 16);
+    auto go = [&](auto un) {
+        gemm_generic_kernel<T, EPI, VEC, 1, 1, decltype(un)::value, NORM><<<small, 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, res, g.M, N, g.K, g.norm_gain, g.norm_eps);
+    };
+    if (g.K <= 256) go(std::integral_constant<int, 2>{});
+    else if (g.K <= 768) go(std::integral_constant<int, 6>{});
+    else go(std::integral_constant<int, 8>{});
 }
 template <typename T, int EPI>
 static void gemm_generic_epi(const GemmArgs &g, int N, hipStream_t st) {
-    if (g.K % 4 == 0) gemm_generic_tile<T, EPI, true>(g, N, st);
-    else gemm_generic_tile<T, EPI, false>(g, N, st);
+    if constexpr (sizeof(T) == 4 && EPI != EPI_RESIDUAL) {
+        if (g.norm_x) return gemm_generic_tile<T, EPI, true, true>(g, N, st);
+    }
+    if (g.K % 4 == 0) gemm_generic_tile<T, EPI, true, false>(g, N, st);
+    else gemm_generic_tile<T, EPI, false, false>(g, N, st);
 }
 template <typename T>
 int launch_gemm_generic(const GemmArgs &g, hipStream_t st) {
     if (g.M == 0) return 0;
+    if (g.norm_x && (sizeof(T) != 4 || g.epilogue == EPI_RESIDUAL || g.K % 4 != 0)) { vla_set_error("internal: the norm in the GEMM was declined"); return VLA_ESHAPE; }
     ProfScope ps("gemm_generic", 2.0 * g.M * g.K * g.n_seg * g.segN, st);
     const int N = (g.epilogue == EPI_SWIGLU) ? g.segN : g.n_seg * g.segN;
     if (g.epilogue == EPI_STORE) gemm_generic_epi<T, EPI_STORE>(g, N, st);
@@ -670,10 +715,10 @@ int launch_attention_step_qkv(float *out, const float *qkv, const float2 *table,
     // 128 pairs of 23 and 103 keys 10.4 and 9.7, 14 and 10.  8192 pairs: head_dim 16, 1003 keys 241 and 324 (272), 256, 23 keys 41 and 119 (83).
     // head_dim 256, 1024 pairs of 103 keys: 57 and 52 (95).
     if (kv.d * nk <= 20480 && n_items >= 8 * nk) {
-        const size_t lds = (size_t)4 * (3 * kv.d + nk) * sizeof(float);    // (at most 21 KB)
+        const size_t lds = (size_t)4 * (3 * kv.d + attention_step_scores(nk)) * sizeof(float);    // (at most 22 KB)
         attention_step_kernel<1><<<(n_items + 3) / 4, 256, lds, st>>>(out, qkv, table, k, v, ra.pos0, n_items, kv.n_heads, kv.d, kv.pos_stride, H);
     } else {
-        const size_t lds = (size_t)(7 * kv.d + 8 + nk) * sizeof(float);    // (at most 40 KB: 8192 keys at head_dim 256)
+        const size_t lds = (size_t)(7 * kv.d + 8 + attention_step_scores(nk)) * sizeof(float);    // (at most 40 KB: 8192 keys at head_dim 256)
         attention_step_kernel<4><<<n_items, 256, lds, st>>>(out, qkv, table, k, v, ra.pos0, n_items, kv.n_heads, kv.d, kv.pos_stride, H);
     }
     return vla_check_launch("attention_step");

@@ -7,8 +7,7 @@
 namespace {
 
 __device__ __forceinline__ float block_sum_256(float v, float *red) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = vla_wave_sum(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
@@ -65,12 +64,6 @@ __global__ void __launch_bounds__(256) gae_kernel(const float *rewards, const fl
     }
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 // One wave per group: population mean / standard deviation of its G returns, lane sums added across the wave.
 __global__ void __launch_bounds__(256) grpo_advantage_kernel(const float *R, int n_groups, int G, float *adv, int32_t *keep) {
     const int g = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -78,12 +71,12 @@ __global__ void __launch_bounds__(256) grpo_advantage_kernel(const float *R, int
     const float *r = R + (size_t)g * G;
     float mean = 0.f, lo = r[0], hi = lo;
     for (int i = lane; i < G; i += 64) { mean += r[i]; lo = fminf(lo, r[i]); hi = fmaxf(hi, r[i]); }
-    mean = wave_sum(mean) / (float)G;
+    mean = vla_wave_sum(mean) / (float)G;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o, 64)); hi = fmaxf(hi, __shfl_xor(hi, o, 64)); }
     float var = 0.f;
     for (int i = lane; i < G; i += 64) var += (r[i] - mean) * (r[i] - mean);
-    const float sd = sqrtf(wave_sum(var) / (float)G);
+    const float sd = sqrtf(vla_wave_sum(var) / (float)G);
     // a group of identical returns is recognised by max == min: the rounded mean of equal values that fp32 does
     // not represent exactly (0.1 x G) can differ from them and leave a tiny non-zero deviation
     const bool spread = hi > lo && sd > 0.f;

@@ -73,8 +73,8 @@ struct GemmArgs {
     int a_rows;             // rows of A that may be read (>= M; contents past M arbitrary): the MFMA kernel
                             // loads whole 256-row tiles and declines if the buffer does not cover them
     int step;               // a decode step (one row per sequence): the weight-streaming kernel of few rows may take it
-    const float *norm_x, *norm_gain;   // not NULL (steps for which gemm_stream_norms): A is RMSNorm(norm_x) norm_gain, formed by
-    float norm_eps;                    // the kernel from the fp32 rows [M, K]
+    const float *norm_x, *norm_gain;   // not NULL (steps for which gemm_stream_norms; fp32 models, K a multiple of 4): A is
+    float norm_eps;                    // RMSNorm(norm_x) norm_gain, formed by the kernel from the fp32 rows [M, K]
     int *deferred_splits;   // not NULL (EPI_STORE and EPI_RESIDUAL of the split-K kernels): the kernel leaves its n
                             // partial products [n][M][N] at the start of the scratch buffer, puts n here and does not
                             // reduce them (the caller's next kernel adds them in order); 0 here: C is complete
@@ -123,11 +123,13 @@ int launch_rope_q(T *q_out, const float *qf, const float2 *table, int n_seq, int
 // next (with X_next, up to VLA_HEAD_PARTIAL_ROWS rows): what the next decode step needs besides its residual rows, its first
 // norm (gain NULL: not wanted) and its row of the rotation table
 struct NextStep { void *nrm; const float *gain; float eps; float2 *table; int pos, d; float theta; };
+// norm (up to VLA_HEAD_PARTIAL_ROWS rows): h is the residual stream and its final norm the head's to form; squares: [head_chunks(H)][n_rows]
+struct HeadNorm { const float *gain; float eps; float *squares; };
 template <typename T>
 int launch_head_sample(const float *h, const T *lm_head_bins, int n_rows, int H, float temperature,
                        const float *gumbel, const int32_t *given_bins, int32_t *bins_out, float *logp,
                        float *ent, float *logits, int out_stride, int out_off, float *X_next,
-                       const T *embed, int vocab, float *scratch, hipStream_t st, const NextStep *next = nullptr);
+                       const T *embed, int vocab, float *scratch, hipStream_t st, const NextStep *next = nullptr, const HeadNorm *norm = nullptr);
 // Partial logits h . W^T of n_rows rows, P[head_chunks(H)][n_rows][256] to be added in chunk order.
 int head_chunks(int H);
 template <typename T>
@@ -137,6 +139,45 @@ constexpr int VLA_HEAD_PARTIAL_ROWS = 4096;
 size_t head_scratch_bytes(int n_rows, int H);
 int launch_value_head(float *value, const float *h, const float *w, float b, const float *bias, int vd, int n,
                       int H, int h_stride, hipStream_t st);
+
+// Sums and maxima over lanes by lane moves of the vector ALU instead of through LDS, a latency of 60 cycles and more a step; the order of
+// additions is that of __shfl_xor over the same distances.  One step with lane ^ O (O = 8, 16 or 32; f is symmetric):
+template <int CTRL> __device__ __forceinline__ float vla_dpp(float v) {
+    const int i = __builtin_bit_cast(int, v);
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, CTRL, 0xf, 0xf, false));
+}
+// The values of the two lanes that differ in O (32 or 16), the lower lane's first.
+struct VlaPair { float a, b; };
+template <int O> __device__ __forceinline__ VlaPair vla_pair(float v) {
+    static_assert(O == 16 || O == 32, "distance");
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    if constexpr (O == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        return {__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1])};
+    } else {
+        const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        return {__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1])};
+    }
+}
+template <int O, typename F> __device__ __forceinline__ float vla_fold_step(float v, F f) {
+    if constexpr (O == 8) return f(v, vla_dpp<0x128>(v));          // row_ror:8
+    else {
+        const VlaPair p = vla_pair<O>(v);
+        return f(p.a, p.b);
+    }
+}
+// Over the 16 lanes of a row, distances 8, 4, 2, 1 (lane ^ 12 has what lane ^ 4 has once lanes ^ 8 agree: a rotation will do), and over all 64.
+template <typename F> __device__ __forceinline__ float vla_row_fold(float v, F f) {
+    v = vla_fold_step<8>(v, f);
+    v = f(v, vla_dpp<0x124>(v));        // row_ror:4
+    v = f(v, vla_dpp<0x4e>(v));         // quad_perm 2 3 0 1
+    return f(v, vla_dpp<0xb1>(v));      // quad_perm 1 0 3 2
+}
+template <typename F> __device__ __forceinline__ float vla_wave_fold(float v, F f) { return vla_row_fold(vla_fold_step<16>(vla_fold_step<32>(v, f), f), f); }
+struct VlaAdd { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+struct VlaMax { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+__device__ __forceinline__ float vla_wave_sum(float v) { return vla_wave_fold(v, VlaAdd{}); }
+__device__ __forceinline__ float vla_wave_max(float v) { return vla_wave_fold(v, VlaMax{}); }
 
 // One pair (a, b) rotated by (cos, sin), rounded once after one fused multiply-add each: written out where two kernels must
 // agree bit for bit (the compiler fuses either product of a sum of two).
@@ -162,8 +203,7 @@ __device__ __forceinline__ void vla_norm_held(T *o, const f32x4_t (&v)[8], const
 #pragma unroll
             for (int e = 0; e < 4; e++) ss += v[j][e] * v[j][e];
         }
-#pragma unroll
-    for (int k = 32; k > 0; k >>= 1) ss += __shfl_xor(ss, k, 64);
+    ss = vla_wave_sum(ss);
     __syncthreads();
     if ((t & 63) == 0) red[t >> 6] = ss;
     __syncthreads();

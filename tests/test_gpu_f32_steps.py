@@ -58,3 +58,12 @@ def test_a_step_does_not_depend_on_the_batch(S, hidden, heads, many, few):
     assert many * heads >= 8 * (S + 3) and few * heads < 8 * (S + 1) and hidden // heads * (S + 3) <= 20480
     for a, b in zip(outputs(many), outputs(few)):
         assert torch.equal(a, b)
+
+
+# The norms inside the products: rows that fill the large tile of the generic kernel and leave a remainder, widths that are no multiple
+# of a wave's share of K (two, six and eight blocks of 16 at a time), a head whose rows exceed the narrow form's 512 workgroups.
+@pytest.mark.parametrize("B,S,hidden,heads,ffn", [(5, 221, 528, 11, 1040), (1, 3, 272, 17, 700), (515, 2, 272, 17, 36), (3, 40, 784, 7, 1200)])
+def test_norms_in_the_products(B, S, hidden, heads, ffn):
+    wl = vi.Workload("norms", _shape(hidden, heads, ffn), batch=B, n_patches=S - 1, n_instr=1, n_action=3)
+    print(compare_rollout(GpuCase(wl, 9).rollout(), oracle_rollout(wl, 9), "f32", autoregressive=True), flush=True)
+
