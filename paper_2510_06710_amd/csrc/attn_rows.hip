@@ -245,7 +245,169 @@ __global__ void __launch_bounds__(256, 2) attn_rows_kernel(AttnRowsArgs a, int n
     }
 }
 
+// dV = P^T dO and dK = dS^T q / sqrt(d), the contractions over the queries, and the transposed rotation with the rounding of all three
+// gradients: bf16 d q | d k | d v rows from P, d S, d O and the fp32 d q.  A wave takes 32 keys of a (sequence, head) and either d V or,
+// with the 32 rows of d q, d K; it walks the queries that see its keys, 32 at a time.  A lane loads eight queries x two keys of P (d S) and
+// eight queries x four neighbouring dims of d O (q), twice: the eight values of a key or a dim are then an operand's eight elements
+// as they lie in the registers (q's 16-bit values after one byte permutation a pair).  Dims i and i + 64 of a pair end in one lane.
+// Splits as everywhere here: P, d S, d O as bf16 head + tail, their products but tail x tail.
+// Bound by memory (P and d S once, at 294 rows little more than their lower halves): as two batched products with fp32 outputs and a pass
+// over all of q | k | v for the rotation, 294 rows of 32 x 32 heads took 607 us, now 319; 283 rows of 7 x 32 heads 153, now 65; the top layer's seven queries of 294 204 -> 97.
+template <bool KEY>
+__device__ __forceinline__ void attn_cols(const AttnColsArgs &a, int s, int h, int kw0) {
+    const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
+    const int R = a.R, Rq = a.Rq, first = R - Rq, head_id = s * a.n_heads + h, H3 = 3 * a.H;
+    const int key = kw0 + 2 * l16;                                        // this lane's keys: key, key + 1
+    const float *P = (KEY ? a.dS : a.P) + (size_t)head_id * Rq * a.ldp + key;
+    const float *d_o = a.dO + (size_t)s * Rq * a.H + h * HD + 4 * l16;
+    const bf16_t *q = a.qkv + ((size_t)s * R + first) * H3 + h * HD + 4 * l16;
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef int i32x2_t __attribute__((ext_vector_type(2)));
+    f32x2_t p[8];
+    f32x4_t dv[KEY ? 1 : 2][8];
+    i32x2_t qv[KEY ? 2 : 1][8];
+    auto load_p = [&](int q0) {
+#pragma unroll
+        for (int t = 0; t < 8; t++) {
+            const int row = q0 + 8 * kq + t;
+            p[t] = f32x2_t{0.f, 0.f};
+            if (row < Rq && key < a.ldp) p[t] = *(const f32x2_t *)(P + (size_t)row * a.ldp);
+        }
+    };
+    auto load_d = [&](int half, int q0) {                // (rows past the last: that one's, their P is zero)
+#pragma unroll
+        for (int t = 0; t < 8; t++) {
+            const size_t row = min(q0 + 8 * kq + t, Rq - 1);
+            if (KEY) qv[KEY ? half : 0][t] = *(const i32x2_t *)(q + row * H3 + 64 * half);
+            else dv[KEY ? 0 : half][t] = *(const f32x4_t *)(d_o + row * a.H + 64 * half);
+        }
+    };
+    f32x4_t acc[2][8];
+#pragma unroll
+    for (int e = 0; e < 2; e++)
+#pragma unroll
+        for (int f = 0; f < 8; f++) acc[e][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    bf16x8_t ph[2], pl[2];
+    auto multiply = [&](int half) {
+#pragma unroll
+        for (int f = 0; f < 4; f++) {
+            bf16x8_t hi, lo;
+            if (KEY) {
+                i32x4_v w;
+#pragma unroll
+                for (int u = 0; u < 4; u++)
+                    w[u] = (int)__builtin_amdgcn_perm((unsigned)qv[KEY ? half : 0][2 * u + 1][f / 2], (unsigned)qv[KEY ? half : 0][2 * u][f / 2], f & 1 ? 0x07060302u : 0x05040100u);
+                hi = __builtin_bit_cast(bf16x8_t, w);
+            } else {
+#pragma unroll
+                for (int t = 0; t < 8; t++) {
+                    const float v = dv[KEY ? 0 : half][t][f];
+                    hi[t] = (bf16_t)v;
+                    lo[t] = (bf16_t)(v - (float)hi[t]);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 2; e++) {
+                f32x4_t &c = acc[e][4 * half + f];
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, pl[e], c, 0, 0, 0);
+                if (!KEY) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, ph[e], c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, ph[e], c, 0, 0, 0);
+            }
+        }
+    };
+    const int q_begin = max(0, min(kw0, a.full_from) - first);           // the first query that sees one of the wave's keys
+    load_p(q_begin);
+    load_d(0, q_begin);
+    for (int q0 = q_begin; q0 < Rq; q0 += 32) {
+        load_d(1, q0);
+#pragma unroll
+        for (int e = 0; e < 2; e++)
+#pragma unroll
+            for (int t = 0; t < 8; t++) {
+                ph[e][t] = (bf16_t)p[t][e];
+                pl[e][t] = (bf16_t)(p[t][e] - (float)ph[e][t]);
+            }
+        load_p(q0 + 32);
+        multiply(0);
+        load_d(0, q0 + 32);
+        multiply(1);
+    }
+    // ---- a lane: keys key + e, dims 16 kq + 4 r + f and those + 64
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+        if (key + e >= R) break;
+        bf16x8_t lo[2], hi[2];
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            f32x4_t cs[2] = {};
+            if (KEY) {
+                const f32x4_t *tb = (const f32x4_t *)(a.table + (size_t)(key + e) * (HD / 2) + 16 * kq + 4 * r);
+                cs[0] = tb[0];
+                cs[1] = tb[1];
+            }
+#pragma unroll
+            for (int f = 0; f < 4; f++) {
+                const float x = acc[e][f][r], y = acc[e][4 + f][r], co = cs[f >> 1][2 * (f & 1)], si = -cs[f >> 1][2 * (f & 1) + 1];
+                lo[r >> 1][4 * (r & 1) + f] = (bf16_t)(KEY ? vla_rotate_lo(x * a.scale, y * a.scale, co, si) : x);
+                hi[r >> 1][4 * (r & 1) + f] = (bf16_t)(KEY ? vla_rotate_hi(x * a.scale, y * a.scale, co, si) : y);
+            }
+        }
+        bf16_t *o = a.out + ((size_t)s * R + key + e) * H3 + (KEY ? 1 : 2) * a.H + h * HD + 16 * kq;
+        *(bf16x8_t *)o = lo[0];
+        *(bf16x8_t *)(o + 8) = lo[1];
+        *(bf16x8_t *)(o + 64) = hi[0];
+        *(bf16x8_t *)(o + 72) = hi[1];
+    }
+    if (!KEY) return;
+    // ---- the same rows of d q (none below the first query: zeros, nothing is read there)
+#pragma unroll
+    for (int it = 0; it < 8; it++) {
+        const int row = kw0 + it * 4 + kq;
+        if (row >= R) break;
+        bf16x4_t lo, hi;
+        if (row >= first) {
+            const float *x = a.dq + ((size_t)s * R + row) * H3 + h * HD + 4 * l16;
+            const f32x4_t x0 = *(const f32x4_t *)x, x1 = *(const f32x4_t *)(x + 64);
+            const f32x4_t *tb = (const f32x4_t *)(a.table + (size_t)row * (HD / 2) + 4 * l16);
+            const f32x4_t cs[2] = {tb[0], tb[1]};
+#pragma unroll
+            for (int f = 0; f < 4; f++) {
+                const float co = cs[f >> 1][2 * (f & 1)], si = -cs[f >> 1][2 * (f & 1) + 1];
+                lo[f] = (bf16_t)vla_rotate_lo(x0[f], x1[f], co, si);
+                hi[f] = (bf16_t)vla_rotate_hi(x0[f], x1[f], co, si);
+            }
+        } else {
+#pragma unroll
+            for (int f = 0; f < 4; f++) lo[f] = hi[f] = (bf16_t)0.f;
+        }
+        bf16_t *o = a.out + ((size_t)s * R + row) * H3 + h * HD + 4 * l16;
+        *(bf16x4_t *)o = lo;
+        *(bf16x4_t *)(o + 64) = hi;
+    }
+}
+__global__ void __launch_bounds__(256, 2) attn_cols_kernel(AttnColsArgs a, int n_heads_total, int tiles) {
+    // both products of all tiles of a (sequence, head) on one XCD, the tiles with the most queries first
+    const int items = 2 * tiles, group = blockIdx.x / (8 * items), in_group = blockIdx.x - group * 8 * items;
+    const int head_id = group * 8 + (in_group & 7), item = in_group >> 3;
+    const int kw0 = (item >> 1) * 128 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 32;
+    if (head_id >= n_heads_total || kw0 >= a.R) return;
+    const int s = head_id / a.n_heads, h = head_id - s * a.n_heads;
+    if (item & 1) attn_cols<true>(a, s, h, kw0);
+    else attn_cols<false>(a, s, h, kw0);
+}
+
 }  // namespace
+
+// Returns 1 if handled, 0 if declined, < 0 on a launch error.  head_dim 128; any number of rows.
+int try_attention_cols(const AttnColsArgs &a, int n_seq, hipStream_t st) {
+    if (a.H != a.n_heads * HD || a.ldp % 4 != 0 || a.ldp < a.R) return 0;
+    if (((size_t)a.P | (size_t)a.dS | (size_t)a.dO | (size_t)a.dq | (size_t)a.qkv | (size_t)a.table | (size_t)a.out) % 16 != 0) return 0;
+    const int heads = n_seq * a.n_heads, tiles = (a.R + 127) / 128;
+    ProfScope ps("bw_attention_cols", 4.0 * heads * a.Rq * (double)a.R * HD * (a.Rq == a.R ? 0.5 : 1.0), st);
+    attn_cols_kernel<<<(heads + 7) / 8 * 8 * 2 * tiles, 256, 0, st>>>(a, heads, tiles);
+    const int rc = vla_check_launch("attn_cols");
+    return rc ? rc : 1;
+}
 
 // Returns 1 if handled, 0 if declined, < 0 on a launch error.  head_dim 128 and up to 316 keys: then two workgroups of 64 rows share
 // a CU's LDS.

@@ -962,7 +962,7 @@ struct Backward {
         float *d_ao = a.GU;                          // [Mq, H] fp32; the gate / up pre-activations are no longer needed
         if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, H, d_ao, H, Mq, ws.a_rows))) return rc;
         float *dqkv = ws.Tmp;                        // [M, 3H] fp32: d q | d k | d v (q, k still in the rotated frame)
-        // dP = dO v^T ; dV = P^T dO ; dS = P (dP - rovla_wave_sum(P dP)) ; dQ = dS k / sqrt(d) ; dK = dS^T q / sqrt(d)
+        // dP = dO v^T ; dV = P^T dO ; dS = P (dP - rowsum(P dP)) ; dQ = dS k / sqrt(d) ; dK = dS^T q / sqrt(d)
         rc = 0;
         if constexpr (MF) {
             if (!(vla_force_generic() & 4) && (rc = try_attention_rows_backward(AttnRowsArgs{d_ao, (const bf16_t *)Q, ws.dP, a.SP, dqkv, R, Rq, Rp, nh, H, full_from, isd}, n, st)) < 0) return rc;
@@ -976,12 +976,18 @@ struct Backward {
             g = heads(ws.dP, Rp, RR * nh, RR, Q + H, 3 * H, rowsH3, d, dqkv + (size_t)(R - Rq) * 3 * H, 3 * H, rowsH3, d, Rq, d, R, 0, 0, isd, causal ? 1 : 0);
             if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
         }
-        g = heads(a.SP, Rp, RR * nh, RR, d_ao, H, (long)Rq * H, d, dqkv + 2 * H, 3 * H, rowsH3, d, R, d, Rq, 1, 0, 1.0f, 0);
-        if ((rc = bgemm<float, float, MF>(g, n * nh, st))) return rc;
-        g = heads(ws.dP, Rp, RR * nh, RR, Qt, 3 * H, rowsH3, d, dqkv + H, 3 * H, rowsH3, d, R, d, Rq, 1, 0, isd, 0);
-        if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
-        rope_rows_kernel<T><<<M, 256, 0, st>>>((T *)ws.dQKVb, dqkv, ws.rope, R, H, d, -1.0f, R - Rq);
-        if ((rc = vla_check_launch("rope_rows (transpose)"))) return rc;
+        rc = 0;
+        if constexpr (MF) {
+            if (!(vla_force_generic() & 4) && (rc = try_attention_cols(AttnColsArgs{a.SP, ws.dP, d_ao, dqkv, (const bf16_t *)Q, ws.rope, (bf16_t *)ws.dQKVb, R, Rq, Rp, nh, H, full_from, isd}, n, st)) < 0) return rc;
+        }
+        if (rc == 0) {
+            g = heads(a.SP, Rp, RR * nh, RR, d_ao, H, (long)Rq * H, d, dqkv + 2 * H, 3 * H, rowsH3, d, R, d, Rq, 1, 0, 1.0f, 0);
+            if ((rc = bgemm<float, float, MF>(g, n * nh, st))) return rc;
+            g = heads(ws.dP, Rp, RR * nh, RR, Qt, 3 * H, rowsH3, d, dqkv + H, 3 * H, rowsH3, d, R, d, Rq, 1, 0, isd, 0);
+            if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
+            rope_rows_kernel<T><<<M, 256, 0, st>>>((T *)ws.dQKVb, dqkv, ws.rope, R, H, d, -1.0f, R - Rq);
+            if ((rc = vla_check_launch("rope_rows (transpose)"))) return rc;
+        }
         // ---- Q / K / V projections and the attention norm
         if ((rc = lora_group(group_of(3, &lo.q, &gr.q, H, H), a.Nrm, ws.a_rows, ws.dQKVb, first, M))) return rc;    // q, k, v adjacent
         if (l == 0) return 0;

@@ -313,6 +313,11 @@ size_t attention_prefill_scratch_bytes(int n_seq, int n_heads, int d, int n_keys
 struct AttnRowsArgs { const void *rows; const bf16_t *qkv; float *S; const float *P; void *out; int R, Rq, ldp, n_heads, H, full_from; float scale; };
 int try_attention_rows_forward(const AttnRowsArgs &a, int n_seq, hipStream_t st);
 int try_attention_rows_backward(const AttnRowsArgs &a, int n_seq, hipStream_t st);
+// The contractions over the queries that follow, the transposed rotation and the rounding: out = d q | d k | d v, bf16 [n_seq * R, 3H], from
+// P, dS ([n_seq * n_heads][Rq][ldp] fp32, zero outside the mask), dO (fp32 [n_seq * Rq, H]), dq (fp32 [n_seq * R, 3H], the queries' rows of its
+// first third) and q of qkv.  scale: of d k.  Same return values.
+struct AttnColsArgs { const float *P, *dS, *dO, *dq; const bf16_t *qkv; const float2 *table; bf16_t *out; int R, Rq, ldp, n_heads, H, full_from; float scale; };
+int try_attention_cols(const AttnColsArgs &a, int n_seq, hipStream_t st);
 
 // LoRA gradients of n_p projections that share their input (factors a[p] [rank, in], b[p] [out, rank] in the storage type,
 // gradients da[p], db[p] fp32 of the same shapes): lora_grad.hip
