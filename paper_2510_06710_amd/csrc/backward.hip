@@ -11,7 +11,7 @@
 // attention norm.  With keep_activations, (1) runs all layers with the latter kernels and every layer leaves its intermediates in
 // a set of its own (one per layer, for one micro-batch), and (3) runs no layer a second time.  Every large contraction -- the
 // seven forward projections and the four input-gradient products
-// dY . W, which run as the same "activation x weight^T" GEMM on a transposed copy of the weights made per layer --
+// dY . W (on the weights as they lie where the direct-to-LDS kernels take the shape, else as the forward's product on transposed copies) --
 // goes through the library's GEMM dispatch (MFMA kernels for bf16 shapes they cover).  Attention (scores, softmax,
 // its backward) runs on materialised [rows x rows] matrices per (rollout, head): 64 query rows at a time from scores to output
 // (attn_rows.hip: bf16, head_dim 128, up to 316 rows), otherwise, and for the products that contract over the queries, with a batched
@@ -20,6 +20,7 @@
 // zero-padded factors otherwise.  Gradient operands of
 // the GEMMs are rounded to the storage type like every other GEMM operand; all sums are fp32 and taken in a fixed
 // order (no atomics), so the result is reproducible bit for bit.
+#include <initializer_list>
 #include <type_traits>
 #include <vector>
 
@@ -763,6 +764,22 @@ struct Backward {
         transpose_kernel<T><<<grid, 256, 0, st>>>((T *)ws.Wt, (const T *)W, N, K, ldt, col0);
         return vla_check_launch("transpose");
     }
+    // C [rows, in] = dY [rows, n_seg out] . [W0; W1; ..]: the gradient of a projection's input, weights [out, in] each.  The direct-to-LDS
+    // kernels take them as they lie; for shapes and alignments outside theirs they are transposed side by side into ws.Wt.
+    int input_grad(const void *dY, std::initializer_list<const void *> W, int out, int in, float *C, int rows) {
+        int rc, i = 0;
+        const int k = (int)W.size() * out;
+        if constexpr (MF) {
+            GemmArgs g{};
+            g.A = dY; g.n_seg = (int)W.size(); g.segK = out; g.segN = in; g.M = rows; g.K = k; g.C = C; g.epilogue = EPI_STORE; g.a_rows = ws.a_rows;
+            for (const void *w : W) g.W[i++] = w;
+            if ((rc = vla_gemm_fused(c, g, st)) != 0) return rc < 0 ? rc : 0;
+        }
+        i = 0;
+        for (const void *w : W)
+            if ((rc = transpose(w, out, in, k, out * i++))) return rc;
+        return gemm(dY, ws.Wt, nullptr, nullptr, 1, in, C, k, rows, ws.a_rows);
+    }
     int cast(void *out, const float *in, int cols, int rows) {
         cast_rows_kernel<T><<<blocks_for((size_t)rows * cols), 256, 0, st>>>((T *)out, in, (size_t)rows, cols, cols, cols);
         return vla_check_launch("cast_rows");
@@ -947,20 +964,17 @@ struct Backward {
         }
         // ---- down projection and SwiGLU (ws.dXb: dx in the storage type, left by the head or the layer above)
         if ((rc = lora_group(group_of(1, &lo.down, &gr.down, F, H), a.ACT, a.q_rows, ws.dXb, first, Mq))) return rc;
-        if ((rc = transpose(lw.w_down, H, F, H, 0))) return rc;                               // [F, H]
-        if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, F, ws.Tmp, H, Mq, ws.a_rows))) return rc;      // d act [Mq, F]
+        if ((rc = input_grad(ws.dXb, {lw.w_down}, H, F, ws.Tmp, Mq))) return rc;              // d act [Mq, F]
         swiglu([&](auto v, dim3 grid) { swiglu_bwd_kernel<T, decltype(v)::value><<<grid, 256, 0, st>>>((T *)ws.dGU, ws.Tmp, a.GU, Mq, F); }, Mq);
         if ((rc = vla_check_launch("swiglu_bwd"))) return rc;
         if ((rc = lora_group(group_of(2, &lo.gate, &gr.gate, H, F), a.Nrm2, a.q_rows, ws.dGU, first, Mq))) return rc;   // gate, up adjacent in the structs
-        if ((rc = transpose(lw.w_gate, F, H, 2 * F, 0)) || (rc = transpose(lw.w_up, F, H, 2 * F, F))) return rc;   // [H, 2F]
-        if ((rc = gemm(ws.dGU, ws.Wt, nullptr, nullptr, 1, H, ws.Tmp, 2 * F, Mq, ws.a_rows))) return rc;  // d n2 [Mq, H]
+        if ((rc = input_grad(ws.dGU, {lw.w_gate, lw.w_up}, F, H, ws.Tmp, Mq))) return rc;     // d n2 [Mq, H]
         rmsnorm_bwd_kernel<T><<<Mq, 256, 0, st>>>(dx, (T *)ws.dXb, dx, Rq, Rq, a.x_mid, (const float *)lw.ffn_norm, ws.Tmp, H, c.rms_eps);
         if ((rc = vla_check_launch("rmsnorm_bwd"))) return rc;
         // ---- O projection and attention (dx, ws.dXb are now d L / d x_mid)
         if ((rc = lora_group(group_of(1, &lo.o, &gr.o, H, H), a.AO, a.q_rows, ws.dXb, first, Mq))) return rc;
-        if ((rc = transpose(lw.wo, H, H, H, 0))) return rc;
         float *d_ao = a.GU;                          // [Mq, H] fp32; the gate / up pre-activations are no longer needed
-        if ((rc = gemm(ws.dXb, ws.Wt, nullptr, nullptr, 1, H, d_ao, H, Mq, ws.a_rows))) return rc;
+        if ((rc = input_grad(ws.dXb, {lw.wo}, H, H, d_ao, Mq))) return rc;
         float *dqkv = ws.Tmp;                        // [M, 3H] fp32: d q | d k | d v (q, k still in the rotated frame)
         // dP = dO v^T ; dV = P^T dO ; dS = P (dP - rowsum(P dP)) ; dQ = dS k / sqrt(d) ; dK = dS^T q / sqrt(d)
         rc = 0;
@@ -991,8 +1005,7 @@ struct Backward {
         // ---- Q / K / V projections and the attention norm
         if ((rc = lora_group(group_of(3, &lo.q, &gr.q, H, H), a.Nrm, ws.a_rows, ws.dQKVb, first, M))) return rc;    // q, k, v adjacent
         if (l == 0) return 0;
-        if ((rc = transpose(lw.wq, H, H, 3 * H, 0)) || (rc = transpose(lw.wk, H, H, 3 * H, H)) || (rc = transpose(lw.wv, H, H, 3 * H, 2 * H))) return rc;
-        if ((rc = gemm(ws.dQKVb, ws.Wt, nullptr, nullptr, 1, H, a.GU, 3 * H, M, ws.a_rows))) return rc;   // d n [M, H]
+        if ((rc = input_grad(ws.dQKVb, {lw.wq, lw.wk, lw.wv}, H, H, a.GU, M))) return rc;     // d n [M, H]
         rmsnorm_bwd_kernel<T><<<M, 256, 0, st>>>(ws.dX, (T *)ws.dXb, dx, R, Rq, a.x_in, (const float *)lw.attn_norm, a.GU, H, c.rms_eps);
         return vla_check_launch("rmsnorm_bwd");
     }

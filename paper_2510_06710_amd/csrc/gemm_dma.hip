@@ -38,6 +38,12 @@
 // alone runs at 46-53 GB/s per CU where lines reach 65-84.  9,408 rows, fp32 output: 940 -> 817 us on average over the
 // gradient products of the 7B shape.)
 //
+// The gradient of a product's input contracts over the weights' rows: its operands need eight of those rows per column.  The weights
+// are read as they lie ([K, N]: runs of 256 bytes, of 128 in 64 x 64 tiles) and transposed on the way out of LDS (ds_read_b64_tr_b16, two for
+// the eight rows that a row-major operand's one read brings): the same operands in the same order, the same bits as on transposed copies of the
+// weights, without the copies.  us with them and so, weights from memory, 2 x 11008 rows onto 4096 columns: 49 rows 152 + 66 and 148, 1,000 266 +
+// 66 and 246, 9,408 1368 + 66 and 1412; 4096 onto 11008: 34 + 30 and 35, 97 + 30 and 93, 671 + 30 and 714.
+//
 // One workgroup per CU walks its tiles in turn (tile i of a workgroup = id + grid * i, which keeps the
 // XCD-contiguous tile order); the half-tile stream simply continues into the next tile, so that only the
 // first tile pays an empty pipeline.  A tile's last MFMAs run in the next tile's first iteration, whose loads go out as
@@ -57,6 +63,10 @@ constexpr int NSTAGES = 5;
 
 typedef __attribute__((address_space(3))) void lds_void;
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
+typedef int i32x2_t __attribute__((ext_vector_type(2)));
+
+// How the weights lie: rows of K, k-blocked, or (EPI_STORE) as [K, N], for the gradient of a product's input.
+enum WeightLayout { W_ROWS = 0, W_KBLOCKED = 1, W_COLUMNS = 2 };
 
 struct DmaGemmParams {
     const bf16_t *A;
@@ -67,6 +77,7 @@ struct DmaGemmParams {
     int tiles_m, tiles_n;
     int a_rows;      // k-blocked layout: rows per 32-column block of A (and of the SwiGLU output)
     int w_rows;      // k-blocked layout: rows per 32-column block of each weight matrix
+    int segK;        // W_COLUMNS: rows of K per weight segment
     // EPI_QKV_ROPE, EPI_QKV_ROWS
     bf16_t *q_out, *kc, *vc;
     float *pre;      // EPI_SWIGLU_KEEP
@@ -85,6 +96,21 @@ __device__ __forceinline__ bf16x8_t lds_read(int addr) {
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
     return __builtin_bit_cast(bf16x8_t, v);
 }
+
+// W_COLUMNS: eight rows of K of 16 columns, transposed on the way: of 16 lanes, lane l names four columns 4 (l % 4) .. of row l / 4 and gets
+// the four rows of column l, from OFF rows 0 .. 3 of its eight and from OFF + STEP rows 4 .. 7.  The halves become one operand only behind the
+// wait, so that no copy of a register still to be written comes in between.
+struct ColumnFrag { i32x2_t lo, hi; };
+template <int OFF, int STEP>
+__device__ __forceinline__ ColumnFrag lds_read_columns(int addr) {
+    ColumnFrag f;
+    asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4" : "=&v"(f.lo), "=&v"(f.hi) : "v"(addr), "n"(OFF), "n"(OFF + STEP));
+    return f;
+}
+__device__ __forceinline__ bf16x8_t frag_of(const ColumnFrag &f) {
+    return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(f.lo, f.hi, 0, 1, 2, 3));
+}
+__device__ __forceinline__ bf16x8_t frag_of(const bf16x8_t &f) { return f; }
 
 // One accumulator element, moved out of its accumulation register exactly where the epilogue consumes it
 // (left to the compiler all 256 moves are hoisted to the top of the epilogue and spill the fragments that
@@ -388,10 +414,17 @@ __device__ __forceinline__ void pass_frags(bf16x8_t (&f)[N]) {
 #pragma unroll
     for (int i = 0; i < N; i++) asm volatile("" : "+v"(f[i]));
 }
+template <int N>
+__device__ __forceinline__ void pass_frags(ColumnFrag (&f)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; i++) asm volatile("" : "+v"(f[i].lo), "+v"(f[i].hi));
+}
 
-template <int EPI, bool KB, bool WKB, int MB>
+template <int EPI, bool KB, int WL, int MB>
 __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    constexpr bool WKB = WL == W_KBLOCKED, WCOL = WL == W_COLUMNS;
+    static_assert(!WCOL || (EPI == EPI_STORE && !KB), "weights as columns");
     constexpr int ROWS = 32 * MB, NA = (MB + 1) / 2, NL = NA + 4;     // tile rows; load instructions per wave and half tile
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave >> 1, wn = wave & 1;
@@ -417,22 +450,37 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     const int up = KB ? wave & 1 : wave >> 1;    // SwiGLU: which matrix this wave loads from, and which 64 (32) of its rows
     const int a_thread_off = KB ? (wave * 16 * NA + (lane >> 2)) * 64 + chunk_off : (wave * 8 * NA + (lane >> 3)) * row_bytes + chunk_off;
     const int w_part = epi_swiglu(EPI) ? (KB ? wave >> 1 : wave & 1) : wave;
-    const int w_thread_off = KB ? (w_part * 64 + (lane >> 2)) * 64 + chunk_off
+    // W_COLUMNS: a stage holds 64 rows of K of the 128 columns that one half of the waves multiplies, an instruction four of them, 256 bytes
+    // each: lane l -> row l / 16, position l % 16; the 32 bytes that a fragment takes of a row, piece b, lie at position b ^ s of the row's
+    // eight with s = row % 4 + 4 (row / 8 % 2), so that the reads of four rows, and of eight further ones, meet no bank conflict.
+    const int col_bytes = p.N * 2;
+    const int w_thread_off = WCOL ? (wave * 16 + (lane >> 4)) * col_bytes + (((lane & 15) ^ ((lane >> 4) << 1)) << 4)
+                             : KB ? (w_part * 64 + (lane >> 2)) * 64 + chunk_off
                              : WKB ? ((wave & 1) * 64 + (lane >> 2)) * 64 + (((lane & 3) ^ ((lane >> 3) & 3)) << 4) + (wave >> 1) * p.w_rows * 64
                                    : (w_part * 32 + (lane >> 3)) * row_bytes + chunk_off;
     // distance of what the cursor steps over: one 32-column block of all rows (mixed: two), or 128 bytes along the row
-    const unsigned a_step = KB ? (unsigned)p.a_rows * 64u : 128u, w_step = WKB ? (unsigned)p.w_rows * (KB ? 64u : 128u) : 128u;
+    const unsigned a_step = KB ? (unsigned)p.a_rows * 64u : 128u, w_step = WKB ? (unsigned)p.w_rows * (KB ? 64u : 128u) : WCOL ? (unsigned)col_bytes * 64u : 128u;
     __amdgpu_buffer_rsrc_t a_rsrc, w_rsrc;
     int ld_item;
     unsigned a_soff, w_soff;
     int nx_tm, nx_tn, nx_split;
+    // W_COLUMNS: the cursor's pair at which the next segment of K begins, and that segment
+    int seg_end = 0, seg = 0;
+    auto set_segment = [&](int s) {
+        const bf16_t *Wp = s == 0 ? p.W0 : (s == 1 ? p.W1 : p.W2);
+        w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(Wp + (size_t)nx_tn * BN), (short)0, (p.segK - 1) * col_bytes + BN * 2, 0x00020000);
+        w_soff = 0;
+        seg = s;
+        seg_end = (s + 1) * (p.segK / 64);
+    };
     auto setup_load = [&](int it) {
         int tm, tn;
         const int split = __builtin_amdgcn_readfirstlane(it / n_tiles);
         vla_tile_of_block(it - split * n_tiles, p.tiles_m, p.tiles_n, tm, tn, p.group);
         const bf16_t *Wp;
         int w_row;
-        if (epi_swiglu(EPI)) { Wp = up ? p.W1 : p.W0; w_row = tn * 128; }
+        if (WCOL) { Wp = p.W0; w_row = 0; }
+        else if (epi_swiglu(EPI)) { Wp = up ? p.W1 : p.W0; w_row = tn * 128; }
         else {
             const int n = tn * BN, seg = __builtin_amdgcn_readfirstlane(n / p.segN);
             Wp = seg == 0 ? p.W0 : (seg == 1 ? p.W1 : p.W2);
@@ -446,12 +494,13 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
         } else {             // ... columns
             const unsigned k0 = (unsigned)split * nh * HK, avail = MB == 8 ? 256u : (unsigned)min(16 * MB + 32 * NA, p.a_rows - tm * ROWS);
             a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(p.A + (size_t)tm * ROWS * K + k0), (short)0, (int)(avail * (unsigned)K * 2u - k0 * 2u), 0x00020000);
-            if (!WKB) w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(Wp + (size_t)w_row * K + k0), (short)0, (int)(w_tile_rows * (unsigned)K * 2u - k0 * 2u), 0x00020000);
+            if (WL == W_ROWS) w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(Wp + (size_t)w_row * K + k0), (short)0, (int)(w_tile_rows * (unsigned)K * 2u - k0 * 2u), 0x00020000);
         }
         if (WKB) w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(Wp + (size_t)w_row * 32 + (size_t)split * nh * p.w_rows * 32), (short)0, (int)((unsigned)(nh - 1) * p.w_rows * 64u + w_tile_rows * 64u), 0x00020000);
         ld_item = it;
         a_soff = w_soff = 0;
         nx_tm = tm; nx_tn = tn; nx_split = split;
+        if (WCOL) set_segment(0);
     };
     // piece i (below NA: activations, then weights) of the cursor's next stage (row-major: of row half RH) into the stage at byte
     // `st`.  In the k-blocked layout the instruction's own offset moves both the address in memory and the one in LDS.
@@ -465,6 +514,8 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
             constexpr int a_row = RH * 16 * MB + q * 8, w_row = RH * (epi_swiglu(EPI) ? 64 : 128) + q * 8;
             if (i < NA) __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void *)(base + q * 1024), 16, a_thread_off, (int)a_soff + a_row * row_bytes, 0, 0);
             else if (WKB) __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)base, 16, w_thread_off, (int)w_soff + RH * 128 * 64, q * 1024, 0);
+            else if (WCOL) __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(base + q * 1024), 16, q & 2 ? w_thread_off ^ 128 : w_thread_off,
+                                                                    (int)w_soff + q * 4 * col_bytes + RH * 256, 0, 0);
             else __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(base + q * 1024), 16, w_thread_off, (int)w_soff + w_row * row_bytes, 0, 0);
         }
         if (i == NL - 1 && (KB || RH == 1)) { a_soff += a_step; w_soff += w_step; }
@@ -483,10 +534,12 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     const int l16 = lane & 15, kq = lane >> 4;
     const int lds0 = (int)(size_t)(lds_void *)lds;
     const int kb_off = l16 * 64 + ((kq ^ ((l16 >> 1) & 3)) << 4), rm_off = l16 * 128 + ((kq ^ (l16 & 7)) << 4);
-    const int a_base = lds0 + (KB ? wm * 16 * MB * 64 + kb_off : rm_off), w_base = lds0 + REGION + (KB ? wn * 128 * 64 : 0) + (WKB ? kb_off : rm_off);
+    const int a_base = lds0 + (KB ? wm * 16 * MB * 64 + kb_off : rm_off), w_base = lds0 + REGION + (KB ? wn * 128 * 64 : 0)
+        + (WCOL ? (kq * 8 + (l16 >> 2)) * 256 + (((l16 >> 2) + 4 * (kq & 1)) << 5) + (l16 & 3) * 8 : WKB ? kb_off : rm_off);
     constexpr int A_BLK = KB ? 1024 : 2048, W_BLK = WKB ? 1024 : 2048;
     f32x4_t acc[8][MB];                  // [weight block][activation block]
-    bf16x8_t af[2][MB], wf[2][8];
+    bf16x8_t af[2][MB];
+    std::conditional_t<WCOL, ColumnFrag, bf16x8_t> wf[2][8];
 
 #define VLA_SB() __builtin_amdgcn_sched_barrier(0)
     // Iteration: reads half tile g, the pair's B-th (stages at bytes a_st, w_st), into fragment buffer B, multiplies half tile g - 1 from
@@ -496,15 +549,16 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
         constexpr int B = decltype(b_c)::value, MUL = decltype(mul_c)::value;
         constexpr int RSTEP = 2, LSTEP = 8 * MB / NL / 2 * 2;
         static_assert((7 + MB) * RSTEP < 8 * MB && 1 + LSTEP * (NL - 1) < 8 * MB, "reads and loads fit between the MFMAs");
-        const int va = (!KB && B == 1 ? a_base ^ 64 : a_base) + a_st, vw = (KB || B == 0 ? w_base : WKB ? w_base + 8192 : w_base ^ 64) + w_st;
+        const int va = (!KB && B == 1 ? a_base ^ 64 : a_base) + a_st, vw = (KB || B == 0 ? w_base : WKB || WCOL ? w_base + 8192 : w_base ^ 64) + w_st;
         for_each_index([&](auto m_c) {
             constexpr int m = decltype(m_c)::value, j = m / MB, i = m % MB;
-            if constexpr (MUL == 1) mfma_add(acc[j][i], wf[B ^ 1][j], af[B ^ 1][i]);
-            if constexpr (MUL == 2) mfma_start(acc[j][i], wf[B ^ 1][j], af[B ^ 1][i]);
+            if constexpr (MUL == 1) mfma_add(acc[j][i], frag_of(wf[B ^ 1][j]), af[B ^ 1][i]);
+            if constexpr (MUL == 2) mfma_start(acc[j][i], frag_of(wf[B ^ 1][j]), af[B ^ 1][i]);
             VLA_SB();
             if constexpr (m % RSTEP == 0 && m / RSTEP < 8 + MB) {        // weight and activation blocks in turn, the weights' rest last
                 constexpr int f = m / RSTEP, blk = f < 2 * MB ? f >> 1 : f - MB;
                 if constexpr (f < 2 * MB && (f & 1)) af[B][blk] = lds_read<blk * A_BLK>(va);
+                else if constexpr (WCOL) wf[B][blk] = lds_read_columns<0, 1024>(vw ^ (blk << 5));
                 else wf[B][blk] = lds_read<blk * W_BLK>(vw);
                 VLA_SB();
             }
@@ -555,6 +609,7 @@ __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
             arrive();
             first_half(I1{});
             if (pr == np - 2) next_item();           // the cursor is two pairs ahead in a pair's second half
+            else if (WCOL && pr + 2 == seg_end) set_segment(seg + 1);
             second_half(I1{});
         }
         item += grid;
@@ -591,9 +646,11 @@ __device__ __forceinline__ void read_frags(bf16x8_t (&f)[sizeof...(I)], int addr
 //
 // STEP (QKV and gate/up of decode steps): instead the sums of gemm_skinny.hip, bit for bit: v_mfma_f32_32x32x16_bf16 on its
 // columns (operand j of a unit: 8 j .. + 7 of either half), K in p.parts parts that are added in order.
-template <int EPI, bool KB, bool WKB, int BMT, int BNT, int NS, bool STEP>
+template <int EPI, bool KB, int WL, int BMT, int BNT, int NS, bool STEP>
 __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    constexpr bool WKB = WL == W_KBLOCKED, WCOL = WL == W_COLUMNS;
+    static_assert(!WCOL || (EPI == EPI_STORE && !KB && !STEP), "weights as columns");
     constexpr int MB = BMT / 32, NB = BNT / 32;          // 16-row / 16-column blocks per wave
     constexpr int A_HALF = BMT * 64, W_HALF = BNT * 64, SSTAGE = 2 * (A_HALF + W_HALF);
     constexpr int NA = BMT / 32, NWI = BNT / 32;                // load instructions per wave and unit
@@ -609,15 +666,23 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
     // Row-major operands are read as whole lines except by 64 x 64 tiles, whose steps are too short for the second half's own
     // addresses: 40 x 256, K = 9536 36.2 us as halves and 39.6 as lines, 113 x 1792, K = 6336 26.2 and 28.6; 64 x 128 tiles 2 % faster as lines
     // (median of 69 sizes), 128 x 128 the same.
-    constexpr bool AH = KB || (BMT == 64 && BNT == 64), WH = WKB || (BMT == 64 && BNT == 64);
+    constexpr bool AH = KB || (BMT == 64 && BNT == 64), WH = WKB || (WL == W_ROWS && BMT == 64 && BNT == 64);
     const int kb_chunk = ((lane & 3) ^ ((lane >> 3) & 3)) << 4, rm_chunk = ((lane & 7) ^ (lane >> 3)) << 4;
     const int row_bytes = KB ? 64 : K * 2, w_row_bytes = WKB ? 64 : K * 2;
     const unsigned a_half = KB ? (unsigned)p.a_rows * 64u : 64u, w_half = WKB ? (unsigned)p.w_rows * 64u : 64u;
     const int thread_off = AH ? (lane >> 2) * row_bytes + kb_chunk : (lane >> 3) * row_bytes + rm_chunk;
-    const int w_thread_off = WH ? (lane >> 2) * w_row_bytes + kb_chunk : (lane >> 3) * w_row_bytes + rm_chunk;
+    // W_COLUMNS: 64 rows of K of BNT columns, an instruction 1 KB of whole rows of 2 BNT bytes; piece b (32 bytes) of a row at position b ^ s,
+    // s = row % 4 + 4 (row / 8 % 2) of eight (BNT = 128) or row % 4 ^ (row / 8 % 2) of four
+    constexpr int CROW = 2 * BNT, CPR = CROW / 16, CRI = 1024 / CROW;        // bytes and 16-byte chunks of a row, rows of an instruction
+    const int col_bytes = p.N * 2;
+    const int w_thread_off = WCOL ? (wave * 16 + lane / CPR) * col_bytes + (((lane % CPR) ^ ((lane / CPR & 3) << 1)) << 4)
+                             : WH ? (lane >> 2) * w_row_bytes + kb_chunk : (lane >> 3) * w_row_bytes + rm_chunk;
     const bf16_t *Wp;
     int w_row0;
-    if (epi_swiglu(EPI)) {
+    if (WCOL) {
+        Wp = p.W0;
+        w_row0 = 0;
+    } else if (epi_swiglu(EPI)) {
         Wp = (wave & 1) ? p.W1 : p.W0;                   // instruction blocks 0..3 gate rows, 4..7 up rows
         w_row0 = tn * 64;
     } else {
@@ -633,6 +698,9 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
         (void *)(Wp + (size_t)w_row0 * w_row_elems), (short)0, WKB ? (int)(nh1 * w_half + BNT * 32u) : BNT * K, 0x00020000);   // (half the tile's rows: one wave's share)
     auto load_unit = [&](int u, int stage) {
         char *base = lds + stage * SSTAGE, *w_base = base + 2 * A_HALF;
+        const int seg = WCOL ? (u * 64 >= p.segK) + (u * 64 >= 2 * p.segK) : 0;
+        const __amdgpu_buffer_rsrc_t c_rsrc = WCOL ? __builtin_amdgcn_make_buffer_rsrc(
+            (void *)((seg == 0 ? p.W0 : seg == 1 ? p.W1 : p.W2) + (size_t)tn * BNT), (short)0, (p.segK - 1) * col_bytes + CROW, 0x00020000) : w_rsrc;
 #pragma unroll
         for (int i = 0; i < NA; i++) {
             const int q = wave * NA + i, half = q / (BMT / 16), blk = q % (BMT / 16);
@@ -643,7 +711,10 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
 #pragma unroll
         for (int i = 0; i < NWI; i++) {
             const int half = wave >> 1, blk = (wave & 1) * NWI + i, row = half * (BNT / 4) + i * 8;
-            if (WH) __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(w_base + half * W_HALF + blk * 1024), 16, w_thread_off,
+            if (WCOL) __builtin_amdgcn_raw_ptr_buffer_load_lds(c_rsrc, (lds_void *)(w_base + (wave * NWI + i) * 1024), 16,
+                                                               (i * CRI) & 8 ? w_thread_off ^ (BNT == 128 ? 128 : 32) : w_thread_off,
+                                                               (u * 64 - seg * p.segK + i * CRI) * col_bytes, 0, 0);
+            else if (WH) __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(w_base + half * W_HALF + blk * 1024), 16, w_thread_off,
                                                              (int)((unsigned)(2 * u + half) * w_half) + i * 16 * w_row_bytes, 0, 0);
             else __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(w_base + ((wave & 1) * (BNT / 2) + row) * 128), 16, w_thread_off,
                                                           u * 128 + row * w_row_bytes, 0, 0);
@@ -653,7 +724,9 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
     const int lds0 = (int)(size_t)(lds_void *)lds, a_row0 = wm * (BMT / 2), w_row0_lds = wn * (BNT / 2);
     const int kb_off = l16 * 64 + ((kq ^ ((l16 >> 1) & 3)) << 4), rm_off = l16 * 128 + ((kq ^ (l16 & 7)) << 4);
     const int a_base = lds0 + (AH ? a_row0 * 64 + kb_off : a_row0 * 128 + rm_off);
-    const int w_base = lds0 + 2 * A_HALF + (WH ? w_row0_lds * 64 + kb_off : w_row0_lds * 128 + rm_off);
+    const int w_swizzle = BNT == 128 ? (l16 >> 2) + 4 * (kq & 1) : (l16 >> 2) ^ (kq & 1);
+    const int w_base = lds0 + 2 * A_HALF + (WCOL ? (kq * 8 + (l16 >> 2)) * CROW + ((w_swizzle ^ (wn * NB)) << 5) + (l16 & 3) * 8
+                                            : WH ? w_row0_lds * 64 + kb_off : w_row0_lds * 128 + rm_off);
     // STEP: lane l reads row l % 32 of a 32-row block, from half l / 32 of the unit (chunks 4 (l / 32) .. + 3 of a whole line)
     constexpr int MB2 = MB / 2, NB2 = NB / 2;
     const int l32 = lane & 31, hh = lane >> 5, fsw32 = (l32 >> 1) & 3;
@@ -675,15 +748,19 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
             for (int i = 0; i < MB; i++) acc[j][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
 
-    bf16x8_t af[2][MB], wf[2][NB];                       // (the first multiply, before any second half, adds zeros)
+    bf16x8_t af[2][MB];                                  // (the first multiply, before any second half, adds zeros)
+    std::conditional_t<WCOL, ColumnFrag, bf16x8_t> wf[2][NB];
 #pragma unroll
     for (int i = 0; i < MB; i++)
 #pragma unroll
         for (int e = 0; e < 8; e++) af[1][i][e] = (bf16_t)0.f;
 #pragma unroll
-    for (int j = 0; j < NB; j++)
+    for (int j = 0; j < NB; j++) {
+        if constexpr (WCOL) wf[1][j] = ColumnFrag{{0, 0}, {0, 0}};
+        else
 #pragma unroll
-        for (int e = 0; e < 8; e++) wf[1][j][e] = (bf16_t)0.f;
+            for (int e = 0; e < 8; e++) wf[1][j][e] = (bf16_t)0.f;
+    }
     auto multiply = [&](int h) {
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (STEP) {
@@ -698,7 +775,7 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
 #pragma unroll
             for (int j = 0; j < NB; j++)
 #pragma unroll
-                for (int i = 0; i < MB; i++) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[h][j], af[h][i], acc[j][i], 0, 0, 0);
+                for (int i = 0; i < MB; i++) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_of(wf[h][j]), af[h][i], acc[j][i], 0, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -715,7 +792,10 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
                 for (int i = 0; i < MB2; i++) af[h][q * MB2 + i] = lds_read<0>(a_step + so + (AH ? ck + i * 2048 : cr + i * 4096));
             }
         } else {
-            read_frags<WH ? h * W_HALF : 0, WH ? 1024 : 2048>(wf[h], (WH || h == 0 ? w_base : w_base ^ 64) + so, std::make_integer_sequence<int, NB>{});
+            if constexpr (WCOL) {
+#pragma unroll
+                for (int j = 0; j < NB; j++) wf[h][j] = lds_read_columns<h * 32 * CROW, 4 * CROW>((w_base ^ (j << 5)) + so);
+            } else read_frags<WH ? h * W_HALF : 0, WH ? 1024 : 2048>(wf[h], (WH || h == 0 ? w_base : w_base ^ 64) + so, std::make_integer_sequence<int, NB>{});
             read_frags<AH ? h * A_HALF : 0, AH ? 1024 : 2048>(af[h], (AH || h == 0 ? a_base : a_base ^ 64) + so, std::make_integer_sequence<int, MB>{});
         }
     };
@@ -837,13 +917,13 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
     }
 }
 
-template <int EPI, bool KB, bool WKB = KB, int MB = 8>
+template <int EPI, bool KB, int WL = KB, int MB = 8>
 int launch_plain(const DmaGemmParams &p, hipStream_t st) {
     static bool attr_set = false;
     static int n_cu = 0;
     const size_t lds = NSTAGES * (size_t)STAGE;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_dma_kernel<EPI, KB, WKB, MB>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_dma_kernel<EPI, KB, WL, MB>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) {
             vla_set_error("hipFuncSetAttribute(gemm_bf16_dma) failed: %s", hipGetErrorString(e));
             return VLA_EHIP;
@@ -861,32 +941,32 @@ int launch_plain(const DmaGemmParams &p, hipStream_t st) {
     const int n_items = p.tiles_m * p.tiles_n * p.splits;
     int grid = n_items;
     if (n_cu % 8 == 0 && n_items > n_cu) grid = n_cu;
-    gemm_bf16_dma_kernel<EPI, KB, WKB, MB><<<grid, 256, lds, st>>>(p);
+    gemm_bf16_dma_kernel<EPI, KB, WL, MB><<<grid, 256, lds, st>>>(p);
     int rc = vla_check_launch("gemm_bf16_dma");
     return rc ? rc : 1;
 }
 
 // mb (5 .. 8): 16-row blocks per wave, i.e. tiles of 32 mb rows
-template <int EPI, bool KB>
+template <int EPI, bool KB, int WL = KB>
 int launch(DmaGemmParams p, int mb, hipStream_t st) {
     const double flops = 2.0 * p.M * p.K * (epi_swiglu(EPI) ? 2.0 * p.N : (double)p.N);
     ProfScope ps(epi_swiglu(EPI) ? "gemm_bf16_dma<swiglu>" : EPI == EPI_RESIDUAL ? "gemm_bf16_dma<residual>"
                  : epi_qkv(EPI) ? "gemm_bf16_dma<qkv_rope>" : "gemm_bf16_dma<store>", flops, st);
     p.tiles_m = (p.M + 32 * mb - 1) / (32 * mb);
     switch (mb) {
-        case 5: return launch_plain<EPI, KB, KB, 5>(p, st);
-        case 6: return launch_plain<EPI, KB, KB, 6>(p, st);
-        case 7: return launch_plain<EPI, KB, KB, 7>(p, st);
-        default: return launch_plain<EPI, KB>(p, st);
+        case 5: return launch_plain<EPI, KB, WL, 5>(p, st);
+        case 6: return launch_plain<EPI, KB, WL, 6>(p, st);
+        case 7: return launch_plain<EPI, KB, WL, 7>(p, st);
+        default: return launch_plain<EPI, KB, WL>(p, st);
     }
 }
 
-template <int EPI, bool KB, bool WKB, int BMT, int BNT, int NS, bool STEP>
+template <int EPI, bool KB, int WL, int BMT, int BNT, int NS, bool STEP>
 int launch_small(DmaGemmParams p, hipStream_t st) {
     static bool attr_set = false;
     const size_t lds = (size_t)NS * 2 * (BMT * 64 + BNT * 64);
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_small_kernel<EPI, KB, WKB, BMT, BNT, NS, STEP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_small_kernel<EPI, KB, WL, BMT, BNT, NS, STEP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) {
             vla_set_error("hipFuncSetAttribute(gemm_bf16_small) failed: %s", hipGetErrorString(e));
             return VLA_EHIP;
@@ -896,7 +976,7 @@ int launch_small(DmaGemmParams p, hipStream_t st) {
     p.tiles_m = (p.M + BMT - 1) / BMT;
     p.tiles_n = epi_swiglu(EPI) ? p.N / (BNT / 2) : p.N / BNT;
     const int per_xcd = (p.tiles_m * p.tiles_n + 7) / 8;
-    gemm_bf16_small_kernel<EPI, KB, WKB, BMT, BNT, NS, STEP><<<8 * per_xcd, 256, lds, st>>>(p);
+    gemm_bf16_small_kernel<EPI, KB, WL, BMT, BNT, NS, STEP><<<8 * per_xcd, 256, lds, st>>>(p);
     int rc = vla_check_launch("gemm_bf16_small");
     return rc ? rc : 1;
 }
@@ -947,20 +1027,20 @@ TileChoice choose_tile(const DmaGemmParams &p, int mb_low) {          // large t
     return best;
 }
 
-template <int EPI, bool KB, bool WKB = KB, bool STEP = false>
+template <int EPI, bool KB, int WL = KB, bool STEP = false>
 int launch_tile(const DmaGemmParams &p, SmallTile tile, hipStream_t st) {
     const double flops = 2.0 * p.M * p.K * (epi_swiglu(EPI) ? 2.0 * p.N : (double)p.N);
     ProfScope ps(epi_swiglu(EPI) ? "gemm_small<swiglu>" : EPI == EPI_RESIDUAL ? "gemm_small<residual>"
                  : epi_qkv(EPI) ? "gemm_small<qkv_rope>" : "gemm_small<store>", flops, st);
     if constexpr (EPI == EPI_STORE || EPI == EPI_RESIDUAL) {
-        if (tile == TILE_64x64) return launch_small<EPI, KB, WKB, 64, 64, 4, STEP>(p, st);
+        if (tile == TILE_64x64) return launch_small<EPI, KB, WL, 64, 64, 4, STEP>(p, st);
         if constexpr (!STEP) {
-            if (tile == TILE_128x64) return launch_small<EPI, KB, WKB, 128, 64, 4, STEP>(p, st);
+            if (tile == TILE_128x64) return launch_small<EPI, KB, WL, 128, 64, 4, STEP>(p, st);
         }
     }
-    if (tile == TILE_64x128) return launch_small<EPI, KB, WKB, 64, 128, 3, STEP>(p, st);
-    if (tile == TILE_128x128_1) return launch_small<EPI, KB, WKB, 128, 128, 3, STEP>(p, st);
-    return launch_small<EPI, KB, WKB, 128, 128, 2, STEP>(p, st);
+    if (tile == TILE_64x128) return launch_small<EPI, KB, WL, 64, 128, 3, STEP>(p, st);
+    if (tile == TILE_128x128_1) return launch_small<EPI, KB, WL, 128, 128, 3, STEP>(p, st);
+    return launch_small<EPI, KB, WL, 128, 128, 2, STEP>(p, st);
 }
 
 template <int EPI>
@@ -968,6 +1048,9 @@ int launch_kb(const DmaGemmParams &p, bool kb, hipStream_t st) {
     const TileChoice t = choose_tile<EPI>(p, 5);
     if constexpr (EPI == EPI_QKV_ROWS || EPI == EPI_SWIGLU_KEEP || EPI == EPI_STORE) {          // row-major operands only
         if (kb) return 0;
+        if constexpr (EPI == EPI_STORE) {
+            if (p.segK) return t.small != TILE_LARGE ? launch_tile<EPI, false, W_COLUMNS>(p, t.small, st) : launch<EPI, false, W_COLUMNS>(p, t.mb, st);
+        }
         return t.small != TILE_LARGE ? launch_tile<EPI, false>(p, t.small, st) : launch<EPI, false>(p, t.mb, st);
     } else {
         if (t.small != TILE_LARGE) return kb ? launch_tile<EPI, true>(p, t.small, st) : launch_tile<EPI, false>(p, t.small, st);
@@ -1012,6 +1095,15 @@ int try_gemm_bf16_dma(const GemmArgs &g, hipStream_t st) {
         return launch_kb<EPI_SWIGLU_KEEP>(p, kb, st);
     }
     if (g.segN % BN != 0) return 0;
+    if (g.segK) {
+        if (kb || g.epilogue != EPI_STORE || g.segK % 64 != 0 || g.segK < 256 || g.K != g.n_seg * g.segK || (size_t)g.segK * g.segN * 2 >= ((size_t)1 << 31)) return 0;
+        for (int i = 0; i < g.n_seg; i++)
+            if ((size_t)g.W[i] % 16 != 0) return 0;
+        p.segK = g.segK;
+        p.N = g.segN;
+        p.tiles_n = p.N / BN;
+        return launch_kb<EPI_STORE>(p, false, st);
+    }
     if (g.epilogue == EPI_QKV_ROWS) {
         const QkvRopeArgs *ra = g.rope;
         if (!ra || ra->kv->d != 128 || g.n_seg != 3 || g.segN != ra->kv->n_heads * 128) return 0;

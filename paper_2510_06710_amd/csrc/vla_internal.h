@@ -78,6 +78,8 @@ struct GemmArgs {
     int *deferred_splits;   // not NULL (EPI_STORE and EPI_RESIDUAL of the split-K kernels): the kernel leaves its n
                             // partial products [n][M][N] at the start of the scratch buffer, puts n here and does not
                             // reduce them (the caller's next kernel adds them in order); 0 here: C is complete
+    int segK;               // not 0 (EPI_STORE, bf16): an input gradient, C[M, segN] = A[M, n_seg segK] . [W[0]; W[1]; ..] with segments
+                            // [segK, segN] as the forward has them; K = n_seg segK
     void *split_scratch;    // not NULL (EPI_STORE, row-major bf16): device scratch of split_scratch_bytes through which a
     size_t split_scratch_bytes;   // multi-row problem with few output tiles may cut its K range into parts
 };
