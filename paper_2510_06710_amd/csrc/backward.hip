@@ -632,6 +632,7 @@ struct BwSpace {
     void *fw;        // scratch of the first forward pass (vla_forward_streams)
     void *split;     // partial products of the split-K LoRA GEMMs
     size_t split_bytes;
+    size_t pack_bytes;   // Wa and Wb together
     int kp;          // rows of a micro-batch rounded up to what a GEMM's K extent accepts
     float2 *rope;
     int a_rows;
@@ -690,8 +691,10 @@ BwSpace plan_bw(const vla_config &c, char *base, int mb, int R, int A, bool keep
     w.kp = (int)kp;
     w.UV = (float *)take(2 * M * 256 * 4);
     w.Cab = (float *)take(2 * dim_p * 256 * 4);
+    const size_t factors_from = off;
     w.Wa = take((size_t)(256 + VLA_KB_PAD_ROWS) * (H > F ? H : F) * es);
     w.Wb = take((size_t)(256 + VLA_KB_PAD_ROWS) * wide * es);
+    w.pack_bytes = off - factors_from;
     w.UVt = take(2 * (size_t)(256 + VLA_KB_PAD_ROWS) * kp * es);
     w.Xt = take(dim_p * kp * es);
     w.dYt = take(dim_p * kp * es);
@@ -743,6 +746,7 @@ struct Backward {
     bool tail;       // the top layer works on those rows alone where it can (see below)
     float scale;
     int ws_mb;       // rollouts per micro-batch the workspace is laid out for
+    bool packs_there = false;
     static constexpr bool MF = sizeof(T) == 2;      // bf16 storage: attention matrices on the matrix cores
 
     int gemm(const void *A, const void *W0, const void *W1, const void *W2, int n_seg, int segN, float *C, int K, int rows, int a_rows,
@@ -900,16 +904,41 @@ struct Backward {
         g.split_scratch = ws.split; g.split_scratch_bytes = ws.split_bytes;     // few output tiles: cut K into parts
         return vla_gemm_dispatch(c, g, st);
     }
-    int lora_group(LoraGroup lg, const void *X, int x_rows, const void *dY, bool first, int M) {        // M rows; x_rows: those allocated for X
+    LoraProducts products_of(const LoraGroup &lg) const {
+        LoraProducts g{};
+        for (int p = 0; p < lg.n_p; p++) { g.a[p] = lg.a[p]; g.b[p] = lg.b[p]; g.da[p] = lg.da[p]; g.db[p] = lg.db[p]; }
+        g.n_p = lg.n_p; g.in = lg.in; g.out = lg.out; g.rank = rank;
+        return g;
+    }
+    // The packed factors of a layer's four groups in one launch (ws.Wa and ws.Wb, which only the GEMM form below uses otherwise); where a
+    // group does not take that form or they do not fit: none, each group packs its own.
+    int pack_layer(const LoraGroup (&lg)[4], const void *(&packed)[4]) {
+        for (const void *&p : packed) p = nullptr;
+        if (!MF || vla_force_generic() & 1) return 0;
+        LoraProducts g[4];
+        size_t bytes = 0;
+        for (int i = 0; i < 4; i++) {
+            g[i] = products_of(lg[i]);
+            const size_t b = lora_packed_bytes(g[i]);
+            if (!b) return 0;
+            packed[i] = (const char *)ws.Wa + bytes;
+            bytes += b;
+        }
+        if (bytes > ws.pack_bytes) {
+            for (const void *&p : packed) p = nullptr;
+            return 0;
+        }
+        packs_there = true;
+        return launch_lora_pack(g, 4, ws.Wa, st);
+    }
+    int lora_group(LoraGroup lg, const void *X, int x_rows, const void *dY, bool first, int M, const void *packed) {        // M rows; x_rows: those allocated for X
         if constexpr (MF) {
-            LoraProducts g{};
-            for (int p = 0; p < lg.n_p; p++) { g.a[p] = lg.a[p]; g.b[p] = lg.b[p]; g.da[p] = lg.da[p]; g.db[p] = lg.db[p]; }
-            g.n_p = lg.n_p; g.in = lg.in; g.out = lg.out; g.rank = rank;
-            const int r = vla_force_generic() & 1 ? 0 : try_lora_products_bf16(g, X, dY, M, scale, !first, ws.split, ws.split_bytes, st);
+            const int r = vla_force_generic() & 1 ? 0 : try_lora_products_bf16(products_of(lg), X, dY, M, scale, !first, ws.split, ws.split_bytes, st, packs_there ? packed : nullptr);
             if (r != 0) return r < 0 ? r : 0;
         }
         const int in = lg.in, wout = lg.n_p * lg.out, kp = M == this->M ? ws.kp : kp_of(M);
         const int pad_rows = 256 + VLA_KB_PAD_ROWS;
+        packs_there = false;                          // (Wa and Wb are about to be written)
         float *U = ws.UV, *V = ws.UV + (size_t)M * 256, *Cb = ws.Cab, *Ca = ws.Cab + (size_t)((wout + 255) / 256 * 256 + VLA_KB_PAD_ROWS) * 256;
         T *Ut = (T *)ws.UVt, *Vt = Ut + (size_t)pad_rows * kp;
         int rc;
@@ -962,17 +991,21 @@ struct Backward {
         if (l < L - live()) {                        // run the layer again from its kept input
             if ((rc = layer_forward(l, a, nullptr))) return rc;
         }
+        const LoraGroup groups[4] = {group_of(1, &lo.down, &gr.down, F, H), group_of(2, &lo.gate, &gr.gate, H, F),      // gate, up adjacent in the structs
+                                     group_of(1, &lo.o, &gr.o, H, H), group_of(3, &lo.q, &gr.q, H, H)};                 // ... and q, k, v
+        const void *packed[4];
+        if ((rc = pack_layer(groups, packed))) return rc;
         // ---- down projection and SwiGLU (ws.dXb: dx in the storage type, left by the head or the layer above)
-        if ((rc = lora_group(group_of(1, &lo.down, &gr.down, F, H), a.ACT, a.q_rows, ws.dXb, first, Mq))) return rc;
+        if ((rc = lora_group(groups[0], a.ACT, a.q_rows, ws.dXb, first, Mq, packed[0]))) return rc;
         if ((rc = input_grad(ws.dXb, {lw.w_down}, H, F, ws.Tmp, Mq))) return rc;              // d act [Mq, F]
         swiglu([&](auto v, dim3 grid) { swiglu_bwd_kernel<T, decltype(v)::value><<<grid, 256, 0, st>>>((T *)ws.dGU, ws.Tmp, a.GU, Mq, F); }, Mq);
         if ((rc = vla_check_launch("swiglu_bwd"))) return rc;
-        if ((rc = lora_group(group_of(2, &lo.gate, &gr.gate, H, F), a.Nrm2, a.q_rows, ws.dGU, first, Mq))) return rc;   // gate, up adjacent in the structs
+        if ((rc = lora_group(groups[1], a.Nrm2, a.q_rows, ws.dGU, first, Mq, packed[1]))) return rc;
         if ((rc = input_grad(ws.dGU, {lw.w_gate, lw.w_up}, F, H, ws.Tmp, Mq))) return rc;     // d n2 [Mq, H]
         rmsnorm_bwd_kernel<T><<<Mq, 256, 0, st>>>(dx, (T *)ws.dXb, dx, Rq, Rq, a.x_mid, (const float *)lw.ffn_norm, ws.Tmp, H, c.rms_eps);
         if ((rc = vla_check_launch("rmsnorm_bwd"))) return rc;
         // ---- O projection and attention (dx, ws.dXb are now d L / d x_mid)
-        if ((rc = lora_group(group_of(1, &lo.o, &gr.o, H, H), a.AO, a.q_rows, ws.dXb, first, Mq))) return rc;
+        if ((rc = lora_group(groups[2], a.AO, a.q_rows, ws.dXb, first, Mq, packed[2]))) return rc;
         float *d_ao = a.GU;                          // [Mq, H] fp32; the gate / up pre-activations are no longer needed
         if ((rc = input_grad(ws.dXb, {lw.wo}, H, H, d_ao, Mq))) return rc;
         float *dqkv = ws.Tmp;                        // [M, 3H] fp32: d q | d k | d v (q, k still in the rotated frame)
@@ -1003,7 +1036,7 @@ struct Backward {
             if ((rc = vla_check_launch("rope_rows (transpose)"))) return rc;
         }
         // ---- Q / K / V projections and the attention norm
-        if ((rc = lora_group(group_of(3, &lo.q, &gr.q, H, H), a.Nrm, ws.a_rows, ws.dQKVb, first, M))) return rc;    // q, k, v adjacent
+        if ((rc = lora_group(groups[3], a.Nrm, ws.a_rows, ws.dQKVb, first, M, packed[3]))) return rc;
         if (l == 0) return 0;
         if ((rc = input_grad(ws.dQKVb, {lw.wq, lw.wk, lw.wv}, H, H, a.GU, M))) return rc;     // d n [M, H]
         rmsnorm_bwd_kernel<T><<<M, 256, 0, st>>>(ws.dX, (T *)ws.dXb, dx, R, Rq, a.x_in, (const float *)lw.attn_norm, a.GU, H, c.rms_eps);

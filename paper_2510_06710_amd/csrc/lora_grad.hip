@@ -22,8 +22,11 @@ typedef __attribute__((address_space(3))) void lds_void;
 // The factors as the MFMA's row operands, 16 factor rows x 32 columns of a contraction in 1 KB: lane (l16, kq) holds the eight
 // columns from 8 kq of row l16.  Wu: blocks of [A_0; A_1; ..] per 32 columns of the input, nj per projection; Wv: per projection
 // blocks of B_p^T per 32 of its outputs.  Rows from the rank on are zeros.
-__global__ void __launch_bounds__(256) lora_pack_kernel(bf16_t *Wu, bf16_t *Wv, LoraProducts g, int nj) {
-    const int nb = g.n_p * nj, nu = (g.in / 32) * nb * 64, nv = (g.out / 32) * nj * 64;
+struct LoraPack { LoraProducts g[4]; bf16_t *Wu[4], *Wv[4]; int nj; };           // (blockIdx.y: which of a layer's groups)
+__global__ void __launch_bounds__(256) lora_pack_kernel(LoraPack pk) {
+    const LoraProducts &g = pk.g[blockIdx.y];
+    bf16_t *Wu = pk.Wu[blockIdx.y], *Wv = pk.Wv[blockIdx.y];
+    const int nj = pk.nj, nb = g.n_p * nj, nu = (g.in / 32) * nb * 64, nv = (g.out / 32) * nj * 64;
     for (int i = blockIdx.x * 256 + threadIdx.x; i < nu + g.n_p * nv; i += gridDim.x * 256) {
         const bool u = i < nu;
         const int p_v = u ? 0 : (i - nu) / nv, e = u ? i : (i - nu) - p_v * nv;
@@ -57,12 +60,15 @@ struct ThinArgs {
 // since the chunk before (through a buffer descriptor: their addresses stay scalar.  As vector registers those took registers of
 // factors still on their way, and every other step waited for all but its own loads; X A^T of q | k | v at 9,408 rows, rank 32, takes
 // 41.7 us either way); the waves' sums meet in LDS.
+// The first n_u of the grid's columns are group 0 of u, the others the groups of v.
 template <int RB, int NB>
-__global__ void __launch_bounds__(512) lora_thin_kernel(ThinArgs a) {
+__global__ void __launch_bounds__(512) lora_thin_kernel(ThinArgs u, ThinArgs v, int n_u) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    const bool of_u = (int)blockIdx.y < n_u;
+    const ThinArgs a = of_u ? u : v;
     constexpr int ROWS = 16 * RB, ROW = 1024 + 16, STG = ROWS * ROW, NX = ROWS / 8, NW = 2 * NB;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kq = lane >> 4;
-    const int m0 = blockIdx.x * ROWS, gr = blockIdx.y, slices = a.K / 64, chunks = (slices + 7) / 8;
+    const int m0 = blockIdx.x * ROWS, gr = of_u ? 0 : (int)blockIdx.y - n_u, slices = a.K / 64, chunks = (slices + 7) / 8;
     if (m0 >= a.M) {             // (16-row form: kp ends in a block of padding)
         for (int e = threadIdx.x; e < NB * 16 * 16; e += 512) a.out[((size_t)gr * NB * 16 + (e >> 4)) * a.kp + m0 + (e & 15)] = (bf16_t)0.f;
         return;
@@ -169,20 +175,22 @@ __global__ void __launch_bounds__(512) lora_thin_kernel(ThinArgs a) {
 struct RowsArgsT {
     const bf16_t *Y;         // [M, w] row-major
     const bf16_t *Ut;        // [..][kp]: blocks of 16 columns of U, transposed
-    float *part;             // [gridDim.y][w][NB * 16]
+    float *part;             // [parts][w][NB * 16]
     int M, w, kp;
     int out;                 // columns of Y that share their blocks of U: column c takes blocks (c / out) * NB .. + NB - 1
+    int parts;
 };
 
 // part[s][c][j] = sum over the rows m of part s of Y[m][c] U[m][j], for 16 IW columns of Y and NB blocks of 16 columns of U per
 // workgroup.  A lane reads IW neighbouring columns of eight rows, whole lines among 16 lanes, and turns them in its registers
 // into IW operands of eight rows each; operand e holds the columns IW l + e (l = 0 .. 15).
+constexpr int lora_columns(int nb) { return nb <= 4 ? 8 : 4; }         // IW for NB blocks
 template <int IW, int NB>
-__global__ void __launch_bounds__(256) lora_rows_kernel(RowsArgsT a) {
+__device__ __forceinline__ void lora_rows(const RowsArgsT &a, int item, f32x4_t (*sums)[64]) {
     typedef int piece_t __attribute__((ext_vector_type(IW / 2)));
-    __shared__ f32x4_t sums[2][NB * IW][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
-    const int c0 = blockIdx.x * 16 * IW, steps = (a.M + 31) / 32, stride = 4 * gridDim.y;
+    const int blocks = a.w / (16 * IW), by = item / blocks;
+    const int c0 = (item - by * blocks) * 16 * IW, steps = (a.M + 31) / 32, stride = 4 * a.parts;
     const bf16_t *y = a.Y + c0 + IW * l16 + (size_t)(8 * kq) * a.w;
     const bf16_t *u = a.Ut + ((size_t)(c0 / a.out) * NB * 16 + l16) * a.kp + 8 * kq;
     f32x4_t acc[NB][IW];
@@ -215,7 +223,7 @@ __global__ void __launch_bounds__(256) lora_rows_kernel(RowsArgsT a) {
             for (int b = 0; b < NB; b++) acc[b][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(uf[s][b], __builtin_bit_cast(bf16x8_t, f), acc[b][e], 0, 0, 0);
         }
     };
-    int st = blockIdx.y * 4 + wave;
+    int st = by * 4 + wave;
     if (st < steps) {
         load(0, st);
         for (; st < steps; st += 2 * stride) {
@@ -232,27 +240,35 @@ __global__ void __launch_bounds__(256) lora_rows_kernel(RowsArgsT a) {
 #pragma unroll
             for (int b = 0; b < NB; b++)
 #pragma unroll
-                for (int e = 0; e < IW; e++) sums[wave - half][b * IW + e][lane] = acc[b][e];
+                for (int e = 0; e < IW; e++) sums[((wave - half) * NB + b) * IW + e][lane] = acc[b][e];
         __syncthreads();
         if (wave < half)
 #pragma unroll
             for (int b = 0; b < NB; b++)
 #pragma unroll
-                for (int e = 0; e < IW; e++) acc[b][e] += sums[wave][b * IW + e][lane];
+                for (int e = 0; e < IW; e++) acc[b][e] += sums[(wave * NB + b) * IW + e][lane];
         __syncthreads();
     }
     if (wave) return;
     // lane: column IW l16 + e, columns 4 kq .. 4 kq + 3 of a block of U
-    float *out = a.part + ((size_t)blockIdx.y * a.w + c0 + IW * l16) * (NB * 16) + 4 * kq;
+    float *out = a.part + ((size_t)by * a.w + c0 + IW * l16) * (NB * 16) + 4 * kq;
 #pragma unroll
     for (int e = 0; e < IW; e++)
 #pragma unroll
         for (int b = 0; b < NB; b++) *(f32x4_t *)(out + (size_t)e * (NB * 16) + b * 16) = acc[b][e];
 }
+// dB's products and dA's in one launch: blocks below n_b are those of `b` (NJ blocks of U each), the others those of `a` (all NJ NP of V).
+template <int NJ, int NP>
+__global__ void __launch_bounds__(256) lora_rows_kernel(RowsArgsT b, RowsArgsT a, int n_b) {
+    constexpr int NB = NJ * NP, IB = lora_columns(NJ), IA = lora_columns(NB), SB = 2 * NJ * IB, SA = 2 * NB * IA;
+    __shared__ f32x4_t sums[SB > SA ? SB : SA][64];
+    if ((int)blockIdx.x < n_b) lora_rows<IB, NJ>(b, blockIdx.x, sums);
+    else lora_rows<IA, NB>(a, blockIdx.x - n_b, sums);
+}
 
 // dB_p[o][j] (+)= scale * sum_s Cb[s][p * out + o][j]
-__global__ void __launch_bounds__(256) lora_finish_b_kernel(LoraProducts g, const float *Cb, int parts, int jp, float scale, int accumulate) {
-    const int p = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void lora_finish_b(const LoraProducts &g, const float *Cb, int parts, int jp, float scale, int accumulate, int p, int block) {
+    const int i = block * 256 + threadIdx.x;
     if (i >= g.out * g.rank) return;
     const int o = i / g.rank, j = i - o * g.rank, w = g.n_p * g.out;
     float v = 0.f;
@@ -261,9 +277,8 @@ __global__ void __launch_bounds__(256) lora_finish_b_kernel(LoraProducts g, cons
     g.db[p][i] = accumulate ? g.db[p][i] + v : v;
 }
 // dA_p[j][i] (+)= scale * sum_s Ca[s][i][p * jp + j]: 16 columns i per workgroup, turned in LDS
-__global__ void __launch_bounds__(256) lora_finish_a_kernel(LoraProducts g, const float *Ca, int parts, int jp, float scale, int accumulate) {
-    __shared__ float tile[16][129];
-    const int i0 = blockIdx.x * 16, n = g.n_p * jp, n4 = n / 4;
+__device__ __forceinline__ void lora_finish_a(const LoraProducts &g, const float *Ca, int parts, int jp, float scale, int accumulate, int block, float (*tile)[129]) {
+    const int i0 = block * 16, n = g.n_p * jp, n4 = n / 4;
     for (int e = threadIdx.x; e < 16 * n4; e += 256) {
         const int i = e / n4, j = (e - i * n4) * 4;
         const float *src = Ca + (size_t)(i0 + i) * n + j;
@@ -281,12 +296,19 @@ __global__ void __launch_bounds__(256) lora_finish_a_kernel(LoraProducts g, cons
         *d = accumulate ? *d + v : v;
     }
 }
+// Blocks below n_b (per projection) finish dB, the others dA.
+__global__ void __launch_bounds__(256) lora_finish_kernel(LoraProducts g, const float *Cb, int pb, const float *Ca, int pa, int jp, float scale, int accumulate, int n_b) {
+    __shared__ float tile[16][129];
+    const int b = blockIdx.x;
+    if (b < n_b * g.n_p) lora_finish_b(g, Cb, pb, jp, scale, accumulate, b / n_b, b % n_b);
+    else lora_finish_a(g, Ca, pa, jp, scale, accumulate, b - n_b * g.n_p, tile);
+}
 
 template <int RB, int NB>
-int launch_thin(const ThinArgs &a, int groups, hipStream_t st) {
+int launch_thin(const ThinArgs &u, int n_u, const ThinArgs &v, int n_v, hipStream_t st) {
     const size_t ring = (size_t)3 * 16 * RB * (1024 + 16), sums = (size_t)4 * NB * RB * 1024, lds = ring > sums ? ring : sums;
     if (int rc = vla_allow_lds((const void *)lora_thin_kernel<RB, NB>, lds)) return rc;
-    lora_thin_kernel<RB, NB><<<dim3(a.kp / (16 * RB), groups), 512, lds, st>>>(a);
+    lora_thin_kernel<RB, NB><<<dim3(v.kp / (16 * RB), n_u + n_v), 512, lds, st>>>(u, v, n_u);
     return vla_check_launch("lora_thin");
 }
 // f(integral_constant) of the block count nb, 1 .. 8
@@ -297,11 +319,11 @@ int with_blocks(int nb, F f) {
     }
     return f(std::integral_constant<int, N>{});
 }
-// 32 rows of X per workgroup, 16 where that leaves CUs idle
-int thin(const ThinArgs &a, int nb, int groups, hipStream_t st) {
+// nb blocks of factor rows for n_u x u and n_v groups of v (the same rows); 32 rows of X per workgroup, 16 where that leaves CUs idle
+int thin(const ThinArgs &u, int n_u, const ThinArgs &v, int n_v, int nb, hipStream_t st) {
     return with_blocks(nb, [&](auto n) {
         constexpr int NB = decltype(n)::value;
-        return (a.M + 31) / 32 * groups >= 192 ? launch_thin<2, NB>(a, groups, st) : launch_thin<1, NB>(a, groups, st);
+        return (v.M + 31) / 32 * (n_u + n_v) >= 192 ? launch_thin<2, NB>(u, n_u, v, n_v, st) : launch_thin<1, NB>(u, n_u, v, n_v, st);
     });
 }
 int parts_of(int w, int iw, int M, size_t row_bytes, size_t bytes) {
@@ -312,43 +334,78 @@ int parts_of(int w, int iw, int M, size_t row_bytes, size_t bytes) {
     while (s > 1 && (size_t)s * w * row_bytes > bytes) s--;
     return s < 1 ? 1 : s;
 }
-int rows_product(const RowsArgsT &a, int nb, int parts, hipStream_t st) {
-    return with_blocks(nb, [&](auto n) {
-        constexpr int NB = decltype(n)::value, IW = NB <= 4 ? 8 : 4;
-        lora_rows_kernel<IW, NB><<<dim3(a.w / (16 * IW), parts), 256, 0, st>>>(a);
+int rows_products(const RowsArgsT &b, const RowsArgsT &a, int nj, int n_p, hipStream_t st) {
+    return with_blocks(nj, [&](auto n) {
+        constexpr int NJ = decltype(n)::value;
+        const int n_b = b.w / (16 * lora_columns(NJ)) * b.parts, n_a = a.w / (16 * lora_columns(NJ * n_p)) * a.parts;
+        if (n_p == 1) lora_rows_kernel<NJ, 1><<<n_b + n_a, 256, 0, st>>>(b, a, n_b);
+        if constexpr (NJ <= 4)
+            if (n_p == 2) lora_rows_kernel<NJ, 2><<<n_b + n_a, 256, 0, st>>>(b, a, n_b);
+        if constexpr (NJ <= 2)
+            if (n_p == 3) lora_rows_kernel<NJ, 3><<<n_b + n_a, 256, 0, st>>>(b, a, n_b);
         return vla_check_launch("lora_rows");
     });
 }
 
+size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
+size_t packed_u(const LoraProducts &g) { return up256((size_t)g.n_p * ((g.rank + 15) / 16) * 16 * g.in * 2); }
+size_t packed_v(const LoraProducts &g) { return up256((size_t)g.n_p * ((g.rank + 15) / 16) * 16 * g.out * 2); }
+bool takes(const LoraProducts &g) {
+    if (g.rank < 1 || g.n_p < 1 || g.n_p > 3 || g.n_p * ((g.rank + 15) / 16) > 8 || g.in % 128 != 0 || g.out % 128 != 0) return false;
+    for (int p = 0; p < g.n_p; p++)
+        if ((size_t)g.a[p] % 16 != 0) return false;
+    return true;
+}
+int pack(const LoraProducts *g, int n, char *base, hipStream_t st) {
+    LoraPack pk{};
+    int pieces = 0;
+    pk.nj = (g[0].rank + 15) / 16;
+    for (int i = 0; i < n; i++) {
+        pk.g[i] = g[i];
+        pk.Wu[i] = (bf16_t *)base;
+        pk.Wv[i] = (bf16_t *)(base + packed_u(g[i]));
+        base += packed_u(g[i]) + packed_v(g[i]);
+        const int here = g[i].n_p * pk.nj * 2 * (g[i].in + g[i].out);
+        if (here > pieces) pieces = here;
+    }
+    lora_pack_kernel<<<dim3((pieces + 255) / 256, n), 256, 0, st>>>(pk);             // (a piece of eight columns per thread)
+    return vla_check_launch("lora_pack");
+}
+
 }  // namespace
 
-// Returns 1 if handled, 0 if declined (more than 128 factor rows, widths that are no multiple of 128, unaligned operands), < 0 on
+size_t lora_packed_bytes(const LoraProducts &g) { return takes(g) ? packed_u(g) + packed_v(g) : 0; }
+// The packed factors of up to four groups of one rank, one behind the other (lora_packed_bytes of each) from `packed`, for
+// try_lora_products_bf16.
+int launch_lora_pack(const LoraProducts *g, int n, void *packed, hipStream_t st) { return pack(g, n, (char *)packed, st); }
+
+// packed: the group's factors by launch_lora_pack, or NULL (packed here).  Returns 1 if handled, 0 if declined (more than 128 factor rows, widths that are no multiple of 128, unaligned operands), < 0 on
 // a launch error.  scratch: 16-byte aligned, `bytes` of it; declines if that does not hold one part of each product.
-int try_lora_products_bf16(const LoraProducts &g, const void *X, const void *dY, int M, float scale, bool accumulate, void *scratch, size_t bytes, hipStream_t st) {
+int try_lora_products_bf16(const LoraProducts &g, const void *X, const void *dY, int M, float scale, bool accumulate, void *scratch, size_t bytes, hipStream_t st, const void *packed) {
     const int nj = (g.rank + 15) / 16, jp = nj * 16, wout = g.n_p * g.out, nb = g.n_p * nj, kp = (M + 31) / 32 * 32;
-    if (M < 1 || g.rank < 1 || nb > 8 || g.in % 128 != 0 || g.out % 128 != 0 || ((size_t)X | (size_t)dY | (size_t)scratch) % 16 != 0) return 0;
-    for (int p = 0; p < g.n_p; p++)
-        if ((size_t)g.a[p] % 16 != 0) return 0;
-    auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    const size_t wu_bytes = up((size_t)nb * 16 * g.in * 2), wv_bytes = up((size_t)g.n_p * jp * g.out * 2), t_bytes = up((size_t)nb * 16 * kp * 2);
-    const size_t used = wu_bytes + wv_bytes + 2 * t_bytes, row_b = (size_t)jp * 4, row_a = (size_t)nb * 64;
-    if (bytes < used || bytes - used < wout * row_b || bytes - used < g.in * row_a) return 0;
+    if (M < 1 || !takes(g) || ((size_t)X | (size_t)dY | (size_t)scratch | (size_t)packed) % 16 != 0) return 0;
+    const size_t wu_bytes = packed_u(g), w_bytes = wu_bytes + packed_v(g), t_bytes = up256((size_t)nb * 16 * kp * 2);
+    const size_t used = w_bytes + 2 * t_bytes, row_b = (size_t)jp * 4, row_a = (size_t)nb * 64;
+    if (bytes < used || bytes - used < wout * row_b + g.in * row_a) return 0;
     char *base = (char *)scratch;
-    bf16_t *Wu = (bf16_t *)base, *Wv = (bf16_t *)(base + wu_bytes), *Ut = (bf16_t *)(base + wu_bytes + wv_bytes), *Vt = (bf16_t *)((char *)Ut + t_bytes);
-    float *part = (float *)(base + used);
+    const bf16_t *Wu = packed ? (const bf16_t *)packed : (const bf16_t *)base, *Wv = (const bf16_t *)((const char *)Wu + wu_bytes);
+    bf16_t *Ut = (bf16_t *)(base + w_bytes), *Vt = (bf16_t *)((char *)Ut + t_bytes);
     const size_t left = bytes - used;
     ProfScope ps("lora_products", 8.0 * M * g.rank * ((double)g.n_p * g.in + wout), st);
     int rc;
-    lora_pack_kernel<<<(nb * 2 * (g.in + g.out) + 255) / 256, 256, 0, st>>>(Wu, Wv, g, nj);          // (a piece of eight columns per thread)
-    if ((rc = vla_check_launch("lora_pack"))) return rc;
-    if ((rc = thin(ThinArgs{(const bf16_t *)X, Wu, Ut, M, g.in, g.in, kp, 0}, nb, 1, st))) return rc;
-    if ((rc = thin(ThinArgs{(const bf16_t *)dY, Wv, Vt, M, g.out, wout, kp, g.out}, nj, g.n_p, st))) return rc;
-    const int pb = parts_of(wout, nj <= 4 ? 8 : 4, M, row_b, left), pa = parts_of(g.in, nb <= 4 ? 8 : 4, M, row_a, left);
-    if ((rc = rows_product(RowsArgsT{(const bf16_t *)dY, Ut, part, M, wout, kp, g.out}, nj, pb, st))) return rc;
-    lora_finish_b_kernel<<<dim3((g.out * g.rank + 255) / 256, g.n_p), 256, 0, st>>>(g, part, pb, jp, scale, accumulate);
-    if ((rc = vla_check_launch("lora_finish_b"))) return rc;
-    if ((rc = rows_product(RowsArgsT{(const bf16_t *)X, Vt, part, M, g.in, kp, g.in}, nb, pa, st))) return rc;
-    lora_finish_a_kernel<<<g.in / 16, 256, 0, st>>>(g, part, pa, jp, scale, accumulate);
-    rc = vla_check_launch("lora_finish_a");
+    if (!packed && (rc = pack(&g, 1, base, st))) return rc;
+    const ThinArgs u{(const bf16_t *)X, Wu, Ut, M, g.in, g.in, kp, 0}, v{(const bf16_t *)dY, Wv, Vt, M, g.out, wout, kp, g.out};
+    if (g.n_p == 1) rc = thin(u, 1, v, 1, nb, st);               // (as many blocks of factors in both: one launch)
+    else if ((rc = thin(u, 1, u, 0, nb, st)) == 0) rc = thin(v, 0, v, g.n_p, nj, st);
+    if (rc) return rc;
+    // the partial products of dB and of dA, one behind the other
+    const int pb = parts_of(wout, lora_columns(nj), M, row_b, left - g.in * row_a);
+    const size_t b_bytes = (size_t)pb * wout * row_b;
+    const int pa = parts_of(g.in, lora_columns(nb), M, row_a, left - b_bytes);
+    float *part_b = (float *)(base + used), *part_a = (float *)((char *)part_b + b_bytes);
+    if ((rc = rows_products(RowsArgsT{(const bf16_t *)dY, Ut, part_b, M, wout, kp, g.out, pb}, RowsArgsT{(const bf16_t *)X, Vt, part_a, M, g.in, kp, g.in, pa}, nj, g.n_p, st))) return rc;
+    const int n_b = (g.out * g.rank + 255) / 256;
+    lora_finish_kernel<<<n_b * g.n_p + g.in / 16, 256, 0, st>>>(g, part_b, pb, part_a, pa, jp, scale, accumulate, n_b);
+    rc = vla_check_launch("lora_finish");
     return rc ? rc : 1;
 }

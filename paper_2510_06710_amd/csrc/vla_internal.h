@@ -325,7 +325,9 @@ int try_attention_cols(const AttnColsArgs &a, int n_seq, hipStream_t st);
 // gradients da[p], db[p] fp32 of the same shapes): lora_grad.hip
 struct LoraProducts { const void *a[3], *b[3]; float *da[3], *db[3]; int n_p, in, out, rank; };
 int try_lora_products_bf16(const LoraProducts &g, const void *X, const void *dY, int M, float scale, bool accumulate, void *scratch,
-                           size_t bytes, hipStream_t st);
+                           size_t bytes, hipStream_t st, const void *packed);
+size_t lora_packed_bytes(const LoraProducts &g);           // 0: a group that try_lora_products_bf16 declines
+int launch_lora_pack(const LoraProducts *g, int n, void *packed, hipStream_t st);
 
 int vla_force_generic();                                   // the mask of vla_debug_force_generic
 int vla_check_launch(const char *what);
