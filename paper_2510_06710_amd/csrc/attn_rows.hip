@@ -352,18 +352,19 @@ __device__ __forceinline__ void attn_cols(const AttnColsArgs &a, int s, int h, i
                 hi[r >> 1][4 * (r & 1) + f] = (bf16_t)(KEY ? vla_rotate_hi(x * a.scale, y * a.scale, co, si) : y);
             }
         }
-        bf16_t *o = a.out + ((size_t)s * R + key + e) * H3 + (KEY ? 1 : 2) * a.H + h * HD + 16 * kq;
+        bf16_t *o = a.out_k + ((size_t)s * R + key + e) * a.ld_kv + (KEY ? 0 : a.H) + h * HD + 16 * kq;
         *(bf16x8_t *)o = lo[0];
         *(bf16x8_t *)(o + 8) = lo[1];
         *(bf16x8_t *)(o + 64) = hi[0];
         *(bf16x8_t *)(o + 72) = hi[1];
     }
     if (!KEY) return;
-    // ---- the same rows of d q (none below the first query: zeros, nothing is read there)
+    // ---- the same rows of d q (none below the first query: nothing is read there, and zeros written unless d q is packed)
 #pragma unroll
     for (int it = 0; it < 8; it++) {
         const int row = kw0 + it * 4 + kq;
         if (row >= R) break;
+        if (a.q_packed && row < first) continue;
         bf16x4_t lo, hi;
         if (row >= first) {
             const float *x = a.dq + ((size_t)s * R + row) * H3 + h * HD + 4 * l16;
@@ -380,7 +381,7 @@ __device__ __forceinline__ void attn_cols(const AttnColsArgs &a, int s, int h, i
 #pragma unroll
             for (int f = 0; f < 4; f++) lo[f] = hi[f] = (bf16_t)0.f;
         }
-        bf16_t *o = a.out + ((size_t)s * R + row) * H3 + h * HD + 4 * l16;
+        bf16_t *o = a.out_q + (a.q_packed ? (size_t)s * Rq + row - first : (size_t)s * R + row) * a.ld_q + h * HD + 4 * l16;
         *(bf16x4_t *)o = lo;
         *(bf16x4_t *)(o + 64) = hi;
     }
@@ -401,7 +402,8 @@ __global__ void __launch_bounds__(256, 2) attn_cols_kernel(AttnColsArgs a, int n
 // Returns 1 if handled, 0 if declined, < 0 on a launch error.  head_dim 128; any number of rows.
 int try_attention_cols(const AttnColsArgs &a, int n_seq, hipStream_t st) {
     if (a.H != a.n_heads * HD || a.ldp % 4 != 0 || a.ldp < a.R) return 0;
-    if (((size_t)a.P | (size_t)a.dS | (size_t)a.dO | (size_t)a.dq | (size_t)a.qkv | (size_t)a.table | (size_t)a.out) % 16 != 0) return 0;
+    if (((size_t)a.P | (size_t)a.dS | (size_t)a.dO | (size_t)a.dq | (size_t)a.qkv | (size_t)a.table | (size_t)a.out_q | (size_t)a.out_k) % 16 != 0) return 0;
+    if (a.ld_q % 8 != 0 || a.ld_kv % 8 != 0) return 0;
     const int heads = n_seq * a.n_heads, tiles = (a.R + 127) / 128;
     ProfScope ps("bw_attention_cols", 4.0 * heads * a.Rq * (double)a.R * HD * (a.Rq == a.R ? 0.5 : 1.0), st);
     attn_cols_kernel<<<(heads + 7) / 8 * 8 * 2 * tiles, 256, 0, st>>>(a, heads, tiles);

@@ -311,6 +311,29 @@ __global__ void __launch_bounds__(256) rope_rows_kernel(T *out, const float *in,
     }
 }
 
+// Rotary on packed q rows, the last Rq of every sequence's R, into the q third of the [n * R, 3H] rows: as rope_rows_kernel.
+template <typename T>
+__global__ void __launch_bounds__(256) rope_q_rows_kernel(T *out, const float *in, const float2 *table, int R, int Rq, int H, int d) {
+    typedef T t4 __attribute__((ext_vector_type(4)));
+    const int half = d >> 1, quads = half >> 2, per = (H / d) * quads;
+    const int sq = blockIdx.x / Rq, r = blockIdx.x - sq * Rq + R - Rq;
+    for (int e = threadIdx.x; e < per; e += 256) {
+        const int h = e / quads, i = (e - h * quads) * 4;
+        const float *src = in + (size_t)blockIdx.x * H + h * d + i;
+        T *dst = out + ((size_t)sq * R + r) * 3 * H + h * d + i;
+        const f32x4_t a = *(const f32x4_t *)src, b = *(const f32x4_t *)(src + half);
+        const float2 *cs = table + (size_t)r * half + i;
+        t4 lo, hi;
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            lo[u] = cvt<T>(vla_rotate_lo(a[u], b[u], cs[u].x, cs[u].y));
+            hi[u] = cvt<T>(vla_rotate_hi(a[u], b[u], cs[u].x, cs[u].y));
+        }
+        *(t4 *)dst = lo;
+        *(t4 *)(dst + half) = hi;
+    }
+}
+
 // In-place masked softmax of the score rows of one (sequence, head), rows ldp floats apart, `rows` of them per head, the
 // first at position pos0: position i sees keys 0..i, or all R keys from full_from on.  One wave per row; entries outside
 // the mask become 0.  Up to 512 keys the row stays in registers, one read and one write (32 x 32 heads x 294 rows: 249 us
@@ -410,26 +433,48 @@ __global__ void __launch_bounds__(256) swiglu_bwd_kernel(T *dGU, const float *d_
 // dX[m] += r (g dn) - x r^3 mean(x g dn), r = (mean(x^2) + eps)^(-1/2): the backward of n = RMSNorm(x) g.  The new
 // dX is also written in the storage type to dXb (the operand of the GEMMs that follow).  prev: the gradient that the
 // norm's is added to, rows_prev rows for each sequence's last positions out of `rows` (zero for the others); dX itself when
-// rows_prev == rows.  X may be dX.
+// rows_prev == rows.  dn_tail (may be NULL): more of dn for those rows.  X may be dX.  Bound by memory (a row stays in registers, 16 bytes
+// a thread and load): 9,408 rows of 4096 149 -> 104 us (4-byte loads, twice).
 template <typename T>
 __global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(float *dX, T *dXb, const float *prev, int rows, int rows_prev, const float *X,
-                                                         const float *gain, const float *dn, int H, float eps) {
+                                                         const float *gain, const float *dn, const float *dn_tail, int H, float eps) {
+    typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));       // (the caller's gain: element alignment)
+    typedef T t4 __attribute__((ext_vector_type(4)));
     __shared__ float red[4];
-    const float *x = X + (size_t)blockIdx.x * H, *d = dn + (size_t)blockIdx.x * H;
+    const size_t at = (size_t)blockIdx.x * H;
+    const int sq = blockIdx.x / rows, row = blockIdx.x - sq * rows - (rows - rows_prev);
+    const size_t at_tail = ((size_t)sq * rows_prev + max(row, 0)) * H;
+    f32x4_t x[8], gd[8], pv[8];                  // (H is a multiple of 16 and at most 8192)
     float ss = 0.f, xd = 0.f;
-    for (int i = threadIdx.x; i < H; i += 256) { ss += x[i] * x[i]; xd += x[i] * gain[i] * d[i]; }
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+        const int i = (j * 256 + threadIdx.x) * 4;
+        pv[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if (i < H) {
+            x[j] = *(const f32x4_t *)(X + at + i);
+            gd[j] = *(const f32x4_t *)(dn + at + i);
+            if (dn_tail && row >= 0) gd[j] += *(const f32x4_t *)(dn_tail + at_tail + i);
+            gd[j] *= (f32x4_t)*(const f32x4_u *)(gain + i);
+            if (prev && row >= 0) pv[j] = *(const f32x4_t *)(prev + at_tail + i);
+#pragma unroll
+            for (int e = 0; e < 4; e++) { ss += x[j][e] * x[j][e]; xd += x[j][e] * gd[j][e]; }
+        }
+    }
     ss = bsum256(ss, red);
     xd = bsum256(xd, red);
     const float r = 1.0f / sqrtf(ss / (float)H + eps);
     const float k = r * r * r * xd / (float)H;
-    float *o = dX + (size_t)blockIdx.x * H;
-    T *ob = dXb + (size_t)blockIdx.x * H;
-    const int sq = blockIdx.x / rows, row = blockIdx.x - sq * rows - (rows - rows_prev);
-    const float *pv = row >= 0 ? prev + ((size_t)sq * rows_prev + row) * H : nullptr;
-    for (int i = threadIdx.x; i < H; i += 256) {
-        const float v = (pv ? pv[i] : 0.f) + (r * gain[i] * d[i] - x[i] * k);
-        o[i] = v;
-        ob[i] = cvt<T>(v);
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+        const int i = (j * 256 + threadIdx.x) * 4;
+        if (i < H) {
+            f32x4_t v;
+            t4 b;
+#pragma unroll
+            for (int e = 0; e < 4; e++) { v[e] = pv[j][e] + (r * gd[j][e] - x[j][e] * k); b[e] = cvt<T>(v[e]); }
+            *(f32x4_t *)(dX + at + i) = v;
+            *(t4 *)(dXb + at + i) = b;
+        }
     }
 }
 
@@ -746,7 +791,7 @@ struct Backward {
     bool tail;       // the top layer works on those rows alone where it can (see below)
     float scale;
     int ws_mb;       // rollouts per micro-batch the workspace is laid out for
-    bool packs_there = false;
+    bool packs_there = false;      // the current layer's packed factors are in Wa and Wb
     static constexpr bool MF = sizeof(T) == 2;      // bf16 storage: attention matrices on the matrix cores
 
     int gemm(const void *A, const void *W0, const void *W1, const void *W2, int n_seg, int segN, float *C, int K, int rows, int a_rows,
@@ -788,6 +833,10 @@ struct Backward {
         cast_rows_kernel<T><<<blocks_for((size_t)rows * cols), 256, 0, st>>>((T *)out, in, (size_t)rows, cols, cols, cols);
         return vla_check_launch("cast_rows");
     }
+    // the last Rq rows of every sequence of [n * R, H] in the storage type, packed (H is a multiple of 16)
+    int gather_storage(void *out, const void *in, int Rq) {
+        return launch_gather_rows((float *)out, (const float *)in, n, R, R - Rq, Rq, (int)(H * sizeof(T) / 4), st);
+    }
     BgemmArgs heads(const void *A, int lda, long sA1, long sA2, const void *B, int ldb, long sB1, long sB2, float *C, int ldc,
                     long sC1, long sC2, int mm, int nn, int kk, int tA, int tB, float alpha, int tri) {
         BgemmArgs g{};
@@ -820,10 +869,10 @@ struct Backward {
         else launch(std::integral_constant<int, 1>{}, dim3((F + 255) / 256, y));
     }
 
-    // The top layer.  Its output is read on the last A rows of every sequence only, so everything after its q | k | v projection
-    // and rotation is computed, and differentiated, for those rows alone, packed [n * A, ...]: attention, O projection,
-    // feed-forward block and their gradients.  The projection, its gradients (q's are zero below those rows), its LoRA product
-    // and the gradient of the layer's input stay [n * R, ...].  This, and the input gradient of the first layer that nothing
+    // The top layer.  Its output is read on the last A rows of every sequence only, so everything after its k | v projection
+    // and rotation is computed, and differentiated, for those rows alone, packed [n * A, ...]: q, attention, O projection,
+    // feed-forward block and their gradients.  The projections of k and v, their gradients, their LoRA products
+    // and the gradient of the layer's input stay [n * R, ...] (q with them outside the matrix-core kernels; taken apart it saves 0.4 ms at 32 rollouts and 0.08 at 7).  This, and the input gradient of the first layer that nothing
     // reads, save a pass about 12 ms whatever its number of layers (7B shape, 32 rollouts: 2 layers 29.8 -> 18.0 ms, 8 layers
     // 117.6 -> 104.3; a layer in between takes 14.4).
     int rows_of(int l) const { return tail && l == L - 1 ? A : R; }      // rows per sequence after K and V
@@ -847,7 +896,14 @@ struct Backward {
             GemmArgs g{};
             g.A = a.Nrm; g.W[0] = lw.wq; g.W[1] = lw.wk; g.W[2] = lw.wv; g.n_seg = 3; g.segN = H; g.M = M; g.K = H;
             g.epilogue = EPI_QKV_ROWS; g.a_rows = ws.a_rows; g.rope = &qa;
+            if (Rq != R) { g.W[0] = lw.wk; g.W[1] = lw.wv; g.W[2] = nullptr; g.n_seg = 2; }
             if ((rc = vla_gemm_fused(c, g, st)) < 0) return rc;
+        }
+        if (rc == 1 && Rq != R) {                    // the read rows' q: the same sums, rotated and rounded alike
+            if ((rc = gather_storage(a.AO, a.Nrm, Rq)) || (rc = gemm(a.AO, lw.wq, nullptr, nullptr, 1, H, ws.QKV, H, Mq, a.q_rows))) return rc;
+            rope_q_rows_kernel<T><<<Mq, 256, 0, st>>>((T *)a.QKVr, ws.QKV, ws.rope, R, Rq, H, d);
+            if ((rc = vla_check_launch("rope_q_rows"))) return rc;
+            rc = 1;
         }
         if (rc == 0) {
             if ((rc = gemm(a.Nrm, lw.wq, lw.wk, lw.wv, 3, H, ws.QKV, H, M, ws.a_rows))) return rc;
@@ -910,26 +966,22 @@ struct Backward {
         g.n_p = lg.n_p; g.in = lg.in; g.out = lg.out; g.rank = rank;
         return g;
     }
-    // The packed factors of a layer's four groups in one launch (ws.Wa and ws.Wb, which only the GEMM form below uses otherwise); where a
+    // The packed factors of a layer's groups in one launch (ws.Wa and ws.Wb, which only the GEMM form below uses otherwise); where a
     // group does not take that form or they do not fit: none, each group packs its own.
-    int pack_layer(const LoraGroup (&lg)[4], const void *(&packed)[4]) {
-        for (const void *&p : packed) p = nullptr;
+    int pack_layer(const LoraGroup *lg, int n_groups, const void *(&packed)[5]) {
+        packs_there = false;
         if (!MF || vla_force_generic() & 1) return 0;
-        LoraProducts g[4];
+        LoraProducts g[5];
         size_t bytes = 0;
-        for (int i = 0; i < 4; i++) {
+        for (int i = 0; i < n_groups; i++) {
             g[i] = products_of(lg[i]);
             const size_t b = lora_packed_bytes(g[i]);
-            if (!b) return 0;
+            if (!b || bytes + b > ws.pack_bytes) return 0;
             packed[i] = (const char *)ws.Wa + bytes;
             bytes += b;
         }
-        if (bytes > ws.pack_bytes) {
-            for (const void *&p : packed) p = nullptr;
-            return 0;
-        }
         packs_there = true;
-        return launch_lora_pack(g, 4, ws.Wa, st);
+        return launch_lora_pack(g, n_groups, ws.Wa, st);
     }
     int lora_group(LoraGroup lg, const void *X, int x_rows, const void *dY, bool first, int M, const void *packed) {        // M rows; x_rows: those allocated for X
         if constexpr (MF) {
@@ -991,10 +1043,12 @@ struct Backward {
         if (l < L - live()) {                        // run the layer again from its kept input
             if ((rc = layer_forward(l, a, nullptr))) return rc;
         }
-        const LoraGroup groups[4] = {group_of(1, &lo.down, &gr.down, F, H), group_of(2, &lo.gate, &gr.gate, H, F),      // gate, up adjacent in the structs
-                                     group_of(1, &lo.o, &gr.o, H, H), group_of(3, &lo.q, &gr.q, H, H)};                 // ... and q, k, v
-        const void *packed[4];
-        if ((rc = pack_layer(groups, packed))) return rc;
+        // q apart from k and v (adjacent in the structs, as gate and up are) where only the read rows have one
+        const bool q_apart = MF && Rq != R && d == 128 && !(vla_force_generic() & 4);
+        const LoraGroup groups[5] = {group_of(1, &lo.down, &gr.down, F, H), group_of(2, &lo.gate, &gr.gate, H, F), group_of(1, &lo.o, &gr.o, H, H),
+                                     q_apart ? group_of(2, &lo.k, &gr.k, H, H) : group_of(3, &lo.q, &gr.q, H, H), group_of(1, &lo.q, &gr.q, H, H)};
+        const void *packed[5] = {};
+        if ((rc = pack_layer(groups, q_apart ? 5 : 4, packed))) return rc;
         // ---- down projection and SwiGLU (ws.dXb: dx in the storage type, left by the head or the layer above)
         if ((rc = lora_group(groups[0], a.ACT, a.q_rows, ws.dXb, first, Mq, packed[0]))) return rc;
         if ((rc = input_grad(ws.dXb, {lw.w_down}, H, F, ws.Tmp, Mq))) return rc;              // d act [Mq, F]
@@ -1002,7 +1056,7 @@ struct Backward {
         if ((rc = vla_check_launch("swiglu_bwd"))) return rc;
         if ((rc = lora_group(groups[1], a.Nrm2, a.q_rows, ws.dGU, first, Mq, packed[1]))) return rc;
         if ((rc = input_grad(ws.dGU, {lw.w_gate, lw.w_up}, F, H, ws.Tmp, Mq))) return rc;     // d n2 [Mq, H]
-        rmsnorm_bwd_kernel<T><<<Mq, 256, 0, st>>>(dx, (T *)ws.dXb, dx, Rq, Rq, a.x_mid, (const float *)lw.ffn_norm, ws.Tmp, H, c.rms_eps);
+        rmsnorm_bwd_kernel<T><<<Mq, 256, 0, st>>>(dx, (T *)ws.dXb, dx, Rq, Rq, a.x_mid, (const float *)lw.ffn_norm, ws.Tmp, nullptr, H, c.rms_eps);
         if ((rc = vla_check_launch("rmsnorm_bwd"))) return rc;
         // ---- O projection and attention (dx, ws.dXb are now d L / d x_mid)
         if ((rc = lora_group(groups[2], a.AO, a.q_rows, ws.dXb, first, Mq, packed[2]))) return rc;
@@ -1023,10 +1077,14 @@ struct Backward {
             g = heads(ws.dP, Rp, RR * nh, RR, Q + H, 3 * H, rowsH3, d, dqkv + (size_t)(R - Rq) * 3 * H, 3 * H, rowsH3, d, Rq, d, R, 0, 0, isd, causal ? 1 : 0);
             if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
         }
+        // the gradients' rows: d q | d k | d v, or d k | d v and behind them the packed d q
+        T *dkv = (T *)ws.dQKVb + (q_apart ? 0 : H), *dq = (T *)ws.dQKVb + (q_apart ? (size_t)ws.a_rows * 2 * H : 0);
         rc = 0;
         if constexpr (MF) {
-            if (!(vla_force_generic() & 4) && (rc = try_attention_cols(AttnColsArgs{a.SP, ws.dP, d_ao, dqkv, (const bf16_t *)Q, ws.rope, (bf16_t *)ws.dQKVb, R, Rq, Rp, nh, H, full_from, isd}, n, st)) < 0) return rc;
+            const AttnColsArgs cols{a.SP, ws.dP, d_ao, dqkv, (const bf16_t *)Q, ws.rope, dq, dkv, q_apart ? H : 3 * H, q_apart ? 2 * H : 3 * H, q_apart, R, Rq, Rp, nh, H, full_from, isd};
+            if (!(vla_force_generic() & 4) && (rc = try_attention_cols(cols, n, st)) < 0) return rc;
         }
+        if (q_apart && rc == 0) { vla_set_error("internal: the attention gradient of the top layer was declined"); return VLA_ESHAPE; }
         if (rc == 0) {
             g = heads(a.SP, Rp, RR * nh, RR, d_ao, H, (long)Rq * H, d, dqkv + 2 * H, 3 * H, rowsH3, d, R, d, Rq, 1, 0, 1.0f, 0);
             if ((rc = bgemm<float, float, MF>(g, n * nh, st))) return rc;
@@ -1037,9 +1095,15 @@ struct Backward {
         }
         // ---- Q / K / V projections and the attention norm
         if ((rc = lora_group(groups[3], a.Nrm, ws.a_rows, ws.dQKVb, first, M, packed[3]))) return rc;
+        if (q_apart) {
+            if ((rc = gather_storage(ws.dGU, a.Nrm, Rq)) || (rc = lora_group(groups[4], ws.dGU, ws.a_rows, dq, first, Mq, packed[4]))) return rc;
+        }
         if (l == 0) return 0;
-        if ((rc = input_grad(ws.dQKVb, {lw.wq, lw.wk, lw.wv}, H, H, a.GU, M))) return rc;     // d n [M, H]
-        rmsnorm_bwd_kernel<T><<<M, 256, 0, st>>>(ws.dX, (T *)ws.dXb, dx, R, Rq, a.x_in, (const float *)lw.attn_norm, a.GU, H, c.rms_eps);
+        float *dn_q = q_apart ? ws.Tmp : nullptr;    // q's part of d n, the read rows'
+        if (q_apart) rc = input_grad(dq, {lw.wq}, H, H, dn_q, Mq);
+        if (rc == 0) rc = q_apart ? input_grad(ws.dQKVb, {lw.wk, lw.wv}, H, H, a.GU, M) : input_grad(ws.dQKVb, {lw.wq, lw.wk, lw.wv}, H, H, a.GU, M);   // d n [M, H]
+        if (rc) return rc;
+        rmsnorm_bwd_kernel<T><<<M, 256, 0, st>>>(ws.dX, (T *)ws.dXb, dx, R, Rq, a.x_in, (const float *)lw.attn_norm, a.GU, dn_q, H, c.rms_eps);
         return vla_check_launch("rmsnorm_bwd");
     }
 };
@@ -1087,7 +1151,7 @@ int backward_impl(vla_model *m, void *wsbuf, bool keep, const void *patch, const
         if ((rc = vla_check_launch("head_dz"))) return rc;
         head_dh_kernel<T><<<dim3((H + 255) / 256, (Mh + 3) / 4), 256, 0, st>>>(dh, dz, head, Mh, H);
         if ((rc = vla_check_launch("head_dh"))) return rc;
-        rmsnorm_bwd_kernel<T><<<Mh, 256, 0, st>>>(dx, (T *)bw.ws.dXb, nullptr, 1, 0, xh, (const float *)m->w.final_norm, dh, H, c.rms_eps);
+        rmsnorm_bwd_kernel<T><<<Mh, 256, 0, st>>>(dx, (T *)bw.ws.dXb, nullptr, 1, 0, xh, (const float *)m->w.final_norm, dh, nullptr, H, c.rms_eps);
         if ((rc = vla_check_launch("head rmsnorm_bwd"))) return rc;
         if (!bw.tail) {
             scatter_rows_kernel<T><<<bw.M, 256, 0, st>>>(bw.ws.dX, (T *)bw.ws.dXb, dx, R, A, H);

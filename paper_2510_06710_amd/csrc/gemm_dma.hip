@@ -83,7 +83,7 @@ struct DmaGemmParams {
     float *pre;      // EPI_SWIGLU_KEEP
     const float2 *table;
     int R, pos0, n_heads, pos_stride, H;
-    int seg0;        // EPI_QKV_ROPE: what the first weight segment is (0 = q, k, v follow; 1 = k, v only)
+    int seg0;        // EPI_QKV_ROPE, EPI_QKV_ROWS: what the first weight segment is (0 = q, k, v follow; 1 = k, v only)
     int group;
     int splits;      // > 1: K is cut into `splits` equal ranges; item = range * tiles + tile, and range r of an
                      // EPI_STORE launch writes its fp32 partial product to C + r * M * N
@@ -1106,11 +1106,12 @@ int try_gemm_bf16_dma(const GemmArgs &g, hipStream_t st) {
     }
     if (g.epilogue == EPI_QKV_ROWS) {
         const QkvRopeArgs *ra = g.rope;
-        if (!ra || ra->kv->d != 128 || g.n_seg != 3 || g.segN != ra->kv->n_heads * 128) return 0;
+        if (!ra || ra->kv->d != 128 || (g.n_seg != 3 && g.n_seg != 2) || g.segN != ra->kv->n_heads * 128) return 0;
+        p.seg0 = 3 - g.n_seg;
         p.q_out = (bf16_t *)ra->q_out;
         p.table = ra->table;
         p.R = ra->rows->R; p.H = g.segN;
-        p.N = 3 * g.segN;
+        p.N = g.n_seg * g.segN;
         p.tiles_n = p.N / BN;
         return launch_kb<EPI_QKV_ROWS>(p, kb, st);
     }

@@ -22,7 +22,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 // The factors as the MFMA's row operands, 16 factor rows x 32 columns of a contraction in 1 KB: lane (l16, kq) holds the eight
 // columns from 8 kq of row l16.  Wu: blocks of [A_0; A_1; ..] per 32 columns of the input, nj per projection; Wv: per projection
 // blocks of B_p^T per 32 of its outputs.  Rows from the rank on are zeros.
-struct LoraPack { LoraProducts g[4]; bf16_t *Wu[4], *Wv[4]; int nj; };           // (blockIdx.y: which of a layer's groups)
+struct LoraPack { LoraProducts g[5]; bf16_t *Wu[5], *Wv[5]; int nj; };           // (blockIdx.y: which of a layer's groups)
 __global__ void __launch_bounds__(256) lora_pack_kernel(LoraPack pk) {
     const LoraProducts &g = pk.g[blockIdx.y];
     bf16_t *Wu = pk.Wu[blockIdx.y], *Wv = pk.Wv[blockIdx.y];
@@ -375,7 +375,7 @@ int pack(const LoraProducts *g, int n, char *base, hipStream_t st) {
 }  // namespace
 
 size_t lora_packed_bytes(const LoraProducts &g) { return takes(g) ? packed_u(g) + packed_v(g) : 0; }
-// The packed factors of up to four groups of one rank, one behind the other (lora_packed_bytes of each) from `packed`, for
+// The packed factors of up to five groups of one rank, one behind the other (lora_packed_bytes of each) from `packed`, for
 // try_lora_products_bf16.
 int launch_lora_pack(const LoraProducts *g, int n, void *packed, hipStream_t st) { return pack(g, n, (char *)packed, st); }
 

@@ -66,7 +66,7 @@ struct GemmArgs {
     const float *res;       // EPI_RESIDUAL: what the product is added to, fp32 [M, N]; NULL: C (multi-row kernels alone: any other array)
     int M, K;
     int epilogue;
-    const QkvRopeArgs *rope;   // EPI_QKV_ROPE, EPI_QKV_ROWS (q_out [M, 3H]; of kv only n_heads and d)
+    const QkvRopeArgs *rope;   // EPI_QKV_ROPE, EPI_QKV_ROWS (q_out [M, 3H]; of kv only n_heads and d; two segments: k and v, q's third stays)
     float *pre;             // EPI_SWIGLU_KEEP: gate | up pre-activations, fp32 [M, 2N]
     int kblocked;           // A (a_rows rows per 32-column block), the weights (segN rows per block, each segment
                             // on its own) and a SwiGLU output are stored [K / 32][rows][32]: direct-to-LDS kernel only
@@ -315,10 +315,11 @@ size_t attention_prefill_scratch_bytes(int n_seq, int n_heads, int d, int n_keys
 struct AttnRowsArgs { const void *rows; const bf16_t *qkv; float *S; const float *P; void *out; int R, Rq, ldp, n_heads, H, full_from; float scale; };
 int try_attention_rows_forward(const AttnRowsArgs &a, int n_seq, hipStream_t st);
 int try_attention_rows_backward(const AttnRowsArgs &a, int n_seq, hipStream_t st);
-// The contractions over the queries that follow, the transposed rotation and the rounding: out = d q | d k | d v, bf16 [n_seq * R, 3H], from
+// The contractions over the queries that follow, the transposed rotation and the rounding: bf16 d k | d v in rows of ld_kv, d v H columns
+// behind d k, and d q in rows of ld_q, all n_seq * R of them (zeros where there is no query) or q_packed: the n_seq * Rq that have one; from
 // P, dS ([n_seq * n_heads][Rq][ldp] fp32, zero outside the mask), dO (fp32 [n_seq * Rq, H]), dq (fp32 [n_seq * R, 3H], the queries' rows of its
 // first third) and q of qkv.  scale: of d k.  Same return values.
-struct AttnColsArgs { const float *P, *dS, *dO, *dq; const bf16_t *qkv; const float2 *table; bf16_t *out; int R, Rq, ldp, n_heads, H, full_from; float scale; };
+struct AttnColsArgs { const float *P, *dS, *dO, *dq; const bf16_t *qkv; const float2 *table; bf16_t *out_q, *out_k; int ld_q, ld_kv, q_packed, R, Rq, ldp, n_heads, H, full_from; float scale; };
 int try_attention_cols(const AttnColsArgs &a, int n_seq, hipStream_t st);
 
 // LoRA gradients of n_p projections that share their input (factors a[p] [rank, in], b[p] [out, rank] in the storage type,

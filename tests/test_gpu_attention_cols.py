@@ -18,8 +18,8 @@ pytestmark = pytest.mark.gpu
 
 
 class AttnColsArgs(ctypes.Structure):               # csrc/vla_internal.h
-    _fields_ = [(n, ctypes.c_void_p) for n in ("P", "dS", "dO", "dq", "qkv", "table", "out")] + \
-               [(n, ctypes.c_int) for n in ("R", "Rq", "ldp", "n_heads", "H", "full_from")] + [("scale", ctypes.c_float)]
+    _fields_ = [(n, ctypes.c_void_p) for n in ("P", "dS", "dO", "dq", "qkv", "table", "out_q", "out_k")] + \
+               [(n, ctypes.c_int) for n in ("ld_q", "ld_kv", "q_packed", "R", "Rq", "ldp", "n_heads", "H", "full_from")] + [("scale", ctypes.c_float)]
 
 
 def _call(n, **fields):
@@ -47,7 +47,7 @@ def test_kernel(R, Rq, full_from, heads):
     ang = torch.arange(R, device="cuda:0", dtype=torch.float64)[:, None] * 10000.0 ** (-torch.arange(0, D, 2, device="cuda:0", dtype=torch.float64) / D)
     table = torch.stack((ang.cos(), ang.sin()), -1).float().contiguous()
     out = torch.full((n, R, 3, heads, D), 9.0, device="cuda:0").bfloat16()
-    assert _call(n, P=P, dS=dS, dO=dO, dq=dq, qkv=qkv, table=table, out=out, R=R, Rq=Rq, ldp=ldp, n_heads=heads, H=H, full_from=full_from, scale=scale) == 1
+    assert _call(n, P=P, dS=dS, dO=dO, dq=dq, qkv=qkv, table=table, out_q=out, out_k=out[:, :, 1:], ld_q=3 * H, ld_kv=3 * H, q_packed=0, R=R, Rq=Rq, ldp=ldp, n_heads=heads, H=H, full_from=full_from, scale=scale) == 1
 
     def back(x):                                     # [n, R, heads, D], the transposed rotation
         co, si = table[:, None, :, 0].double(), -table[:, None, :, 1].double()
@@ -63,10 +63,14 @@ def test_kernel(R, Rq, full_from, heads):
         print(f"{name}: {_rel(got, want):.2e}, {100 * flips:.3f} % round the other way", flush=True)
         assert _rel(got, want) <= 2.0 ** -9 and flips <= 0.01
     assert not out[:, :first, 0].any()
+    apart, packed = torch.full((n, R, 2, heads, D), 9.0, device="cuda:0").bfloat16(), torch.full((n, Rq, heads, D), 9.0, device="cuda:0").bfloat16()
+    assert _call(n, P=P, dS=dS, dO=dO, dq=dq, qkv=qkv, table=table, out_q=packed, out_k=apart, ld_q=H, ld_kv=2 * H, q_packed=1, R=R, Rq=Rq, ldp=ldp, n_heads=heads, H=H,
+                 full_from=full_from, scale=scale) == 1
+    assert torch.equal(apart, out[:, :, 1:]) and torch.equal(packed, out[:, first:, 0])
 
 
 def test_declined():
     """head_dim 64, and rows that do not end on 16 bytes."""
     z = torch.zeros(1 << 16, device="cuda:0")
-    common = dict(P=z, dS=z, dO=z, dq=z, qkv=z, table=z, out=z, R=6, Rq=6, n_heads=2, full_from=CAUSAL, scale=1.0)
+    common = dict(P=z, dS=z, dO=z, dq=z, qkv=z, table=z, out_q=z, out_k=z, ld_q=384, ld_kv=384, q_packed=0, R=6, Rq=6, n_heads=2, full_from=CAUSAL, scale=1.0)
     assert _call(1, **common, ldp=8, H=128) == 0 and _call(1, **common, ldp=6, H=256) == 0 and _call(1, **common, ldp=4, H=256) == 0
