@@ -632,7 +632,7 @@ template <int BASE, int STRIDE, int... I>
 __device__ __forceinline__ void read_frags(bf16x8_t (&f)[sizeof...(I)], int addr, std::integer_sequence<int, I...>) {
     ((f[I] = lds_read<BASE + I * STRIDE>(addr)), ...);
 }
-// Small-tile form for products whose 256 x 256 tiles would leave most of the chip idle: BMT x BNT outputs (SwiGLU: half of
+// Small-tile form for products whose 256 x 256 tiles would leave most of the chip idle: BMT (64, 96, 128, 160) x BNT outputs (SwiGLU: half of
 // them gate, half up rows), 4 waves of a quarter each, one tile per workgroup, one or two workgroups per CU.  Same
 // operands, same v_mfma_f32_16x16x32_bf16 over K in the same order and the same epilogue arithmetic as the 256 x 256
 // kernel: results are identical bit for bit, so the choice between them (choose_tile) is one of speed alone.
@@ -692,8 +692,9 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
     }
     const size_t row_elems = KB ? 32 : (size_t)K, w_row_elems = WKB ? 32 : (size_t)K;
     const unsigned nh1 = (unsigned)(K / HK - 1);
+    const int a_avail = min(BMT, p.a_rows - tm * BMT);   // (a tile may reach past the activation buffer's last row: those loads return zero)
     const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(p.A + (size_t)tm * BMT * row_elems), (short)0, KB ? (int)(nh1 * a_half + BMT * 64u) : BMT * K * 2, 0x00020000);
+        (void *)(p.A + (size_t)tm * BMT * row_elems), (short)0, KB ? (int)(nh1 * a_half + a_avail * 64u) : a_avail * K * 2, 0x00020000);
     const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(Wp + (size_t)w_row0 * w_row_elems), (short)0, WKB ? (int)(nh1 * w_half + BNT * 32u) : BNT * K, 0x00020000);   // (half the tile's rows: one wave's share)
     auto load_unit = [&](int u, int stage) {
@@ -985,10 +986,15 @@ int launch_small(DmaGemmParams p, hipStream_t st) {
 // the large one with tiles of 32 mb x 256, or a small tile.  All give the same bits; the rule compares estimates in ns, fitted to
 // what the four projections of the 7B shape took at 64 .. 18432 rows (per unit of K = 64 and launch):
 //   32 mb x 256     a round of 256 tiles 333 + 107 mb per unit (mb = 8: 1190) + 8000 (prologue and epilogue)
-//   64 x 64         310 up to 150 tiles, then 120 + 1.25 per tile (plain and residual outputs only)
+//   64 x 64         310 up to 150 tiles, 345 up to 256, then 120 + 1.25 per tile (plain and residual outputs only)
 //   128 x 64        445 where one workgroup per CU takes all tiles (plain and residual outputs, more than 128 rows, see below)
 //   64 x 128        470 up to 276 tiles, then 1.7 per tile (SwiGLU, two weight panels per tile: 620, at least 1000)
-//   128 x 128       640 with one workgroup per CU (3 stages of LDS), 950 for every 512 with two (2 stages)
+//   128 x 128       640 with one workgroup per CU (3 stages of LDS; SwiGLU 735), 950 for every 512 with two (2 stages)
+//   96 x 64 394, 160 x 64 525 (as 128 x 64), 96 x 128 570, 160 x 128 765 (SwiGLU 680, 790): one workgroup per CU, K from 1024
+// The heights of 96 and 160 rows fill a round where 64 and 128 leave a second one nearly empty or pad the rows: what a CU loads decides, 59 GB/s
+// with one workgroup.  Weights from memory, before and with them, us: 288 rows, O 28.7 and 25.2, down 73.1 and 62.1, QKV 59 and 51.5, k and v 50.3 and
+// 36.9; 160 rows, QKV 52.4 and 38.6, gate/up 77.6 and 47.9; 72 rows, gate/up 45.3 and 41.7; 700 rows, O 50.0 and 36.9, down 131.9 and 91.4.
+// (288 x 128, three stages: no better than the large tile of 160 rows or 128 x 128 with two workgroups, but for gate/up at 200 rows, 77 and 72.5.)
 // E.g. 288 rows, K = 4096: QKV 86 -> 55 us (64 x 128), O and down (K = 11008) on average 133 -> 58 (64 x 64 and 64 x 128) -> 52
 // (128 x 64); gate/up 76 with 160 x 256, 86 with 256 x 256, 100 with 64 x 128.
 // Tiles lower than 256 rows where the rounds of 256 tiles come out fuller: 2,304 rows, O and down on average 154 -> 133 us (160 rows
@@ -1001,10 +1007,10 @@ int launch_small(DmaGemmParams p, hipStream_t st) {
 // at a lower rate than a single round of 128 x 128: 1,421 x 4096, K = 11008 152 us, 198 with 160 x 256 (whole calls, up to 448 such tiles:
 // gradient pass of three layers, 1,415 rows 5.12 ms, 5.30 with low tiles; prefill of 1,132 rows 1.87 and 2.01; at 512, 1,981 rows, 6.00 and
 // 5.84); not so where the columns are few (7,208 x 1024: 160 x 256 28 % faster).
-enum SmallTile { TILE_LARGE = 0, TILE_64x64, TILE_128x64, TILE_64x128, TILE_128x128_1, TILE_128x128_2 };
+enum SmallTile { TILE_LARGE = 0, TILE_64x64, TILE_128x64, TILE_64x128, TILE_128x128_1, TILE_128x128_2, TILE_96x64, TILE_160x64, TILE_96x128, TILE_160x128 };
 struct TileChoice { SmallTile small; int mb; };
 template <int EPI>
-TileChoice choose_tile(const DmaGemmParams &p, int mb_low) {          // large tiles of 32 mb_low .. 256 rows
+TileChoice choose_tile(const DmaGemmParams &p, int mb_low, bool step = false) {          // large tiles of 32 mb_low .. 256 rows; step: those of decode steps
     const long units = p.K / 64, cols = epi_swiglu(EPI) ? 2L * p.N : p.N;
     const long t64 = (p.M + 63L) / 64 * (cols / 128), t128 = (p.M + 127L) / 128 * (cols / 128);
     TileChoice best{TILE_LARGE, 8};
@@ -1017,12 +1023,21 @@ TileChoice choose_tile(const DmaGemmParams &p, int mb_low) {          // large t
         const long tiles = (p.M + 32L * mb - 1) / (32L * mb) * (cols / 256);
         offer({TILE_LARGE, mb}, (tiles + 255) / 256 * (units * (333 + 107 * mb) + 8000));
     }
-    if (EPI == EPI_STORE || EPI == EPI_RESIDUAL) offer({TILE_64x64, 0}, units * (2 * t64 <= 150 ? 310 : 120 + 5 * (2 * t64) / 4));
+    if (EPI == EPI_STORE || EPI == EPI_RESIDUAL) offer({TILE_64x64, 0}, units * (2 * t64 <= 150 ? 310 : 2 * t64 <= 256 && !step ? 345 : 120 + 5 * (2 * t64) / 4));
     if ((EPI == EPI_STORE || EPI == EPI_RESIDUAL) && p.M > 128 && p.M <= cols && units >= 16 && 2 * t64 > 288 && 2 * t128 <= 256)
         offer({TILE_128x64, 0}, units * 445);
     if (epi_swiglu(EPI)) offer({TILE_64x128, 0}, units * (t64 <= 276 ? 620 : t64 <= 588 ? 1000 : 17 * t64 / 10));
     else offer({TILE_64x128, 0}, units * (t64 <= 276 ? 470 : 17 * t64 / 10));
-    if (t128 <= 256) offer({TILE_128x128_1, 0}, units * 640);
+    if (t128 <= 256) offer({TILE_128x128_1, 0}, units * (epi_swiglu(EPI) && !step ? 735 : 640));
+    if (!step && units >= 16) {
+        const long t96 = (p.M + 95L) / 96 * (cols / 128), t160 = (p.M + 159L) / 160 * (cols / 128);
+        if ((EPI == EPI_STORE || EPI == EPI_RESIDUAL) && p.M > 128 && p.M <= cols && 2 * t64 > 288) {
+            if (2 * t96 <= 256) offer({TILE_96x64, 0}, units * 394);
+            if (2 * t160 <= 256) offer({TILE_160x64, 0}, units * 525);
+        }
+        if (t96 <= 256) offer({TILE_96x128, 0}, units * (epi_swiglu(EPI) ? 680 : 570));
+        if (t160 <= 256) offer({TILE_160x128, 0}, units * (epi_swiglu(EPI) ? 790 : 765));
+    }
     offer({TILE_128x128_2, 0}, units * 950 * ((t128 + 511) / 512));
     return best;
 }
@@ -1037,6 +1052,14 @@ int launch_tile(const DmaGemmParams &p, SmallTile tile, hipStream_t st) {
         if constexpr (!STEP) {
             if (tile == TILE_128x64) return launch_small<EPI, KB, WL, 128, 64, 4, STEP>(p, st);
         }
+    }
+    if constexpr (!STEP) {
+        if constexpr (EPI == EPI_STORE || EPI == EPI_RESIDUAL) {
+            if (tile == TILE_96x64) return launch_small<EPI, KB, WL, 96, 64, 5, STEP>(p, st);
+            if (tile == TILE_160x64) return launch_small<EPI, KB, WL, 160, 64, 4, STEP>(p, st);
+        }
+        if (tile == TILE_96x128) return launch_small<EPI, KB, WL, 96, 128, 4, STEP>(p, st);
+        if (tile == TILE_160x128) return launch_small<EPI, KB, WL, 160, 128, 4, STEP>(p, st);
     }
     if (tile == TILE_64x128) return launch_small<EPI, KB, WL, 64, 128, 3, STEP>(p, st);
     if (tile == TILE_128x128_1) return launch_small<EPI, KB, WL, 128, 128, 3, STEP>(p, st);
@@ -1158,7 +1181,7 @@ int try_gemm_bf16_dma_step(const GemmArgs &g, hipStream_t st) {
     p.parts = gemm_decode_parts(p.N, p.K);
     auto go = [&](auto epi) {
         constexpr int EPI = decltype(epi)::value;
-        const SmallTile tile = choose_tile<EPI>(p, 8).small;
+        const SmallTile tile = choose_tile<EPI>(p, 8, true).small;
         if (tile == TILE_LARGE) return 0;
         return wkb ? launch_tile<EPI, false, true, true>(p, tile, st) : launch_tile<EPI, false, false, true>(p, tile, st);
     };

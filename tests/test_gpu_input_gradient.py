@@ -1,5 +1,5 @@
 """Input gradients C = A . [W0; W1; ..] on weights as they lie ([K, N] each): the same products on the same matrix operands in the same
-order as on a transposed copy, so the same bits, in every tile (40 to 1400 rows: 64 x 64, 128 x 64, 64 x 128, 128 x 128 with one and
+order as on a transposed copy, so the same bits, in every tile (40 to 1400 rows: 64 to 160 rows of 64 and 128 columns, 128 x 128 with one and
 two workgroups per CU; more: the large ones), with segments of K that end after four pairs of half tiles, the least, and after five."""
 import ctypes
 
@@ -31,7 +31,8 @@ def _gemm(A, W, out, M, N, segK=0):
     return rc
 
 
-@pytest.mark.parametrize("M,N,n_seg,segK", [(1, 256, 1, 256), (40, 256, 3, 256), (65, 512, 2, 320), (300, 3584, 1, 1024), (315, 4096, 1, 1024), (600, 4096, 2, 512),
+@pytest.mark.parametrize("M,N,n_seg,segK", [(1, 256, 1, 256), (40, 256, 3, 256), (65, 512, 2, 320), (300, 3584, 1, 1024), (315, 4096, 1, 1024), (400, 4096, 1, 1024), (600, 4096, 2, 512),
+                                            (700, 4096, 1, 1024), (288, 12288, 1, 1024), (193, 12288, 3, 512),
                                             (900, 4096, 1, 1088), (1400, 4096, 3, 320), (2304, 4096, 2, 256), (3000, 4096, 2, 320), (3390, 4096, 3, 256),
                                             (4095, 4096, 1, 256), (5000, 1024, 1, 576), (7150, 1280, 3, 320)])
 def test_same_bits_as_on_transposed_weights(M, N, n_seg, segK):
