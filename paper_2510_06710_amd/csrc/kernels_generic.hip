@@ -349,19 +349,26 @@ __global__ void rope_q_kernel(T *q_out, const float *qf, const float2 *table, si
 }
 
 // ---------------------------------------------------------------------------------- attention
+// Room for the weights of nk keys: whole runs of positions, zeros past the last.
+__host__ __device__ constexpr int attention_scores(int nk) { return (nk + 31) / 32 * 32; }
+
 // One wave per (sequence, head, new row): scores over the allowed keys into LDS, softmax, then
-// the weighted sum of V rows with each lane owning head dims lane, lane+64, ...
+// the weighted sum of V rows with each lane owning head dims lane, lane+64, ...  Few rows are a chain of memory latencies: four pieces
+// of K and sixteen rows of V are asked for together (tiny decoder, 8 environments: last row over 64 keys 9.6 -> 6.8 us, all 64 rows 9.9 -> 7.5).
 template <typename T>
 __global__ void __launch_bounds__(256) attention_generic_kernel(T *out, const T *qbuf, const T *kc,
                                                                const T *vc, int n_seq, int R, int pos0,
                                                                int full_from, int n_heads, int d,
                                                                int pos_stride, int H) {
     extern __shared__ float smem[];
+    typedef T t8 __attribute__((ext_vector_type(8), aligned(sizeof(T))));        // (the caller's KV buffer: element alignment)
+    constexpr int NC = 4, NP = 16;
+    const int nc = d / 8;
     int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n_keys = pos0 + R;            // the most keys any row of this launch sees
-    int per_wave = n_keys + d;
+    const int room = attention_scores(n_keys), per_wave = room + d;
     float *sc = smem + (size_t)wave * per_wave;
-    float *qs = sc + n_keys;
+    float *qs = sc + room;
     size_t item = (size_t)blockIdx.x * 4 + wave;
     size_t total = (size_t)n_seq * n_heads * R;
     if (item >= total) return;      // whole wave leaves together; no block-level barrier below
@@ -381,10 +388,16 @@ __global__ void __launch_bounds__(256) attention_generic_kernel(T *out, const T 
     float mx = -INFINITY;
     for (int p = lane; p < nk; p += 64) {
         float acc = 0.f;
-        for (int c = 0; c < d / 8; c++) {
-            const T *kp = kh + ((size_t)c * pos_stride + p) * 8;
+#pragma unroll 1
+        for (int c0 = 0; c0 < nc; c0 += NC) {
+            t8 kr[NC];
 #pragma unroll
-            for (int e = 0; e < 8; e++) acc += qs[c * 8 + e] * to_f(kp[e]);
+            for (int c = 0; c < NC; c++) kr[c] = *(const t8 *)(kh + ((size_t)min(c0 + c, nc - 1) * pos_stride + p) * 8);
+#pragma unroll
+            for (int c = 0; c < NC; c++)
+                if (c0 + c < nc)
+#pragma unroll
+                    for (int e = 0; e < 8; e++) acc += qs[(c0 + c) * 8 + e] * to_f((T)kr[c][e]);
         }
         acc *= scale;
         sc[p] = acc;
@@ -392,8 +405,8 @@ __global__ void __launch_bounds__(256) attention_generic_kernel(T *out, const T 
     }
     mx = vla_wave_max(mx);
     float sum = 0.f;
-    for (int p = lane; p < nk; p += 64) {
-        float e = expf(sc[p] - mx);
+    for (int p = lane; p < attention_scores(nk); p += 64) {
+        float e = p < nk ? expf(sc[p] - mx) : 0.f;
         sc[p] = e;
         sum += e;
     }
@@ -402,7 +415,18 @@ __global__ void __launch_bounds__(256) attention_generic_kernel(T *out, const T 
     float inv = 1.0f / sum;
     for (int i = lane; i < d; i += 64) {
         float acc = 0.f;
-        for (int p = 0; p < nk; p++) acc += sc[p] * to_f(vh[(size_t)p * d + i]);
+#pragma unroll 1
+        for (int p0 = 0; p0 < nk; p0 += NP) {
+            T vr[NP];
+#pragma unroll
+            for (int u = 0; u < NP; u++) vr[u] = vh[(size_t)min(p0 + u, nk - 1) * d + i];
+#pragma unroll
+            for (int u = 0; u < NP; u += 4) {                                    // (weights past the last key: zeros)
+                const f32x4_t w = *(const f32x4_t *)(sc + p0 + u);
+#pragma unroll
+                for (int e = 0; e < 4; e++) acc += w[e] * (p0 + u + e < nk ? to_f(vr[u + e]) : 0.f);
+            }
+        }
         out[m * (size_t)H + (size_t)h * d + i] = from_f<T>(acc * inv);
     }
 }
@@ -416,7 +440,6 @@ __global__ void __launch_bounds__(256) attention_generic_kernel(T *out, const T 
 // keys: 4.15 -> 1.66 ms at 8 environments, 6.99 -> 5.84 at 128.  One wave, for many pairs of few keys: four pairs share a workgroup, with
 // half the loads in flight a pair's registers shrink from 4 x 162 to 89 a lane, so that 4096 pairs run at once and not in five
 // rounds, and no wave is there for keys that are not.  Either forms every sum in the same order: same bits.
-__host__ __device__ constexpr int attention_step_scores(int nk) { return (nk + 31) / 32 * 32; }
 template <int WAVES>
 __global__ void __launch_bounds__(256) attention_step_kernel(float *out, const float *qkv, const float2 *table, float *kc, float *vc, int pos,
                                                              int n_items, int n_heads, int d, int pos_stride, int H) {
@@ -436,7 +459,7 @@ __global__ void __launch_bounds__(256) attention_step_kernel(float *out, const f
     };
     const int s = item / n_heads, h = item - s * n_heads;
     const int nk = pos + 1, last = max(pos - 1, 0), half = d / 2, nc = d / 8;    // (addresses past the last stored key: clamped, not used)
-    const int nkp = attention_step_scores(nk);                                   // weights of whole runs of positions: zeros past the last
+    const int nkp = attention_scores(nk);                                   // weights of whole runs of positions: zeros past the last
     float *qs = smem + (ALONE ? (size_t)wave * (3 * d + nkp) : 0), *ks = qs + d, *vs = ks + d, *sc = vs + d, *part = sc + nkp, *red = part + 4 * d;
     const float *row = qkv + (size_t)s * 3 * H + (size_t)h * d;
     const size_t head = (size_t)s * n_heads + h;
@@ -686,7 +709,7 @@ int launch_attention_generic(T *out, const T *q, const KvView &kv, int layer, co
     const T *vc = (const T *)kv.v + (size_t)layer * kv.layer_elems;
     // scores of the visible keys + the query, per wave; above the 64 KB default the limit is raised once per
     // instantiation (8192 keys at head_dim 256 need 132 KB of the CU's 160 KB)
-    size_t lds = (size_t)4 * (ra.pos0 + ra.R + kv.d) * sizeof(float);
+    size_t lds = (size_t)4 * (attention_scores(ra.pos0 + ra.R) + kv.d) * sizeof(float);
     if (lds > 64 * 1024) {
         static bool raised = false;
         if (lds > 160 * 1024) { vla_set_error("attention_generic: %d keys need %zu bytes of LDS", ra.pos0 + ra.R, lds); return VLA_ESHAPE; }
@@ -715,10 +738,10 @@ int launch_attention_step_qkv(float *out, const float *qkv, const float2 *table,
     // 128 pairs of 23 and 103 keys 10.4 and 9.7, 14 and 10.  8192 pairs: head_dim 16, 1003 keys 241 and 324 (272), 256, 23 keys 41 and 119 (83).
     // head_dim 256, 1024 pairs of 103 keys: 57 and 52 (95).
     if (kv.d * nk <= 20480 && n_items >= 8 * nk) {
-        const size_t lds = (size_t)4 * (3 * kv.d + attention_step_scores(nk)) * sizeof(float);    // (at most 22 KB)
+        const size_t lds = (size_t)4 * (3 * kv.d + attention_scores(nk)) * sizeof(float);    // (at most 22 KB)
         attention_step_kernel<1><<<(n_items + 3) / 4, 256, lds, st>>>(out, qkv, table, k, v, ra.pos0, n_items, kv.n_heads, kv.d, kv.pos_stride, H);
     } else {
-        const size_t lds = (size_t)(7 * kv.d + 8 + attention_step_scores(nk)) * sizeof(float);    // (at most 40 KB: 8192 keys at head_dim 256)
+        const size_t lds = (size_t)(7 * kv.d + 8 + attention_scores(nk)) * sizeof(float);    // (at most 40 KB: 8192 keys at head_dim 256)
         attention_step_kernel<4><<<n_items, 256, lds, st>>>(out, qkv, table, k, v, ra.pos0, n_items, kv.n_heads, kv.d, kv.pos_stride, H);
     }
     return vla_check_launch("attention_step");
