@@ -408,7 +408,7 @@ __global__ void __launch_bounds__(256) swiglu_fwd_kernel(T *act, const float *GU
     }
 }
 
-// d gate = d act * up * silu'(gate), d up = d act * silu(gate); silu'(t) = s (1 + t (1 - s)), s = sigmoid(t)
+// d gate and d up of every row
 template <typename T, int V>
 __global__ void __launch_bounds__(256) swiglu_bwd_kernel(T *dGU, const float *d_act, const float *GU, int M, int F) {
     typedef T tv __attribute__((ext_vector_type(V)));
@@ -421,9 +421,10 @@ __global__ void __launch_bounds__(256) swiglu_bwd_kernel(T *dGU, const float *d_
         tv dg, du;
 #pragma unroll
         for (int e = 0; e < V; e++) {
-            const float s = 1.0f / (1.0f + expf(-g[e]));
-            dg[e] = cvt<T>(da[e] * u[e] * s * (1.0f + g[e] * (1.0f - s)));
-            du[e] = cvt<T>(da[e] * g[e] * s);
+            float a, b;
+            vla_swiglu_grad(g[e], u[e], da[e], a, b);
+            dg[e] = cvt<T>(a);
+            du[e] = cvt<T>(b);
         }
         *(tv *)(dGU + o) = dg;
         *(tv *)(dGU + o + F) = du;
@@ -1051,9 +1052,17 @@ struct Backward {
         if ((rc = pack_layer(groups, q_apart ? 5 : 4, packed))) return rc;
         // ---- down projection and SwiGLU (ws.dXb: dx in the storage type, left by the head or the layer above)
         if ((rc = lora_group(groups[0], a.ACT, a.q_rows, ws.dXb, first, Mq, packed[0]))) return rc;
-        if ((rc = input_grad(ws.dXb, {lw.w_down}, H, F, ws.Tmp, Mq))) return rc;              // d act [Mq, F]
-        swiglu([&](auto v, dim3 grid) { swiglu_bwd_kernel<T, decltype(v)::value><<<grid, 256, 0, st>>>((T *)ws.dGU, ws.Tmp, a.GU, Mq, F); }, Mq);
-        if ((rc = vla_check_launch("swiglu_bwd"))) return rc;
+        {   // SwiGLU's gradient rides the product's epilogue where that kernel takes the shape: no fp32 d act in memory
+            GemmArgs g{};
+            g.A = ws.dXb; g.W[0] = lw.w_down; g.n_seg = 1; g.segK = H; g.segN = F; g.M = Mq; g.K = H; g.C = ws.dGU; g.pre = a.GU;
+            g.epilogue = EPI_SWIGLU_GRAD; g.a_rows = ws.a_rows;
+            if ((rc = vla_gemm_fused(c, g, st)) < 0) return rc;
+        }
+        if (rc == 0) {
+            if ((rc = input_grad(ws.dXb, {lw.w_down}, H, F, ws.Tmp, Mq))) return rc;          // d act [Mq, F]
+            swiglu([&](auto v, dim3 grid) { swiglu_bwd_kernel<T, decltype(v)::value><<<grid, 256, 0, st>>>((T *)ws.dGU, ws.Tmp, a.GU, Mq, F); }, Mq);
+            if ((rc = vla_check_launch("swiglu_bwd"))) return rc;
+        }
         if ((rc = lora_group(groups[1], a.Nrm2, a.q_rows, ws.dGU, first, Mq, packed[1]))) return rc;
         if ((rc = input_grad(ws.dGU, {lw.w_gate, lw.w_up}, F, H, ws.Tmp, Mq))) return rc;     // d n2 [Mq, H]
         rmsnorm_bwd_kernel<T><<<Mq, 256, 0, st>>>(dx, (T *)ws.dXb, dx, Rq, Rq, a.x_mid, (const float *)lw.ffn_norm, ws.Tmp, nullptr, H, c.rms_eps);

@@ -80,7 +80,7 @@ struct DmaGemmParams {
     int segK;        // W_COLUMNS: rows of K per weight segment
     // EPI_QKV_ROPE, EPI_QKV_ROWS
     bf16_t *q_out, *kc, *vc;
-    float *pre;      // EPI_SWIGLU_KEEP
+    float *pre;      // EPI_SWIGLU_KEEP, EPI_SWIGLU_GRAD
     const float2 *table;
     int R, pos0, n_heads, pos_stride, H;
     int seg0;        // EPI_QKV_ROPE, EPI_QKV_ROWS: what the first weight segment is (0 = q, k, v follow; 1 = k, v only)
@@ -344,6 +344,57 @@ __device__ __forceinline__ void epilogue(f32x4_t (&acc)[8][MB], const DmaGemmPar
         }
         return;
     }
+    if (EPI == EPI_SWIGLU_GRAD) {
+        // d act of 16 rows from the panel with their pre-activations, fp32 [M, 2N], to d gate | d up, bf16 [M, 2N].  Rows past M: outside the
+        // descriptors.
+        const int rows_in = min(16 * MB, p.M - m0), lane_at = (lane >> 5) * 2 * p.N + (lane & 31) * 4;
+        const size_t at = (size_t)m0 * 2 * p.N + (size_t)tn * BN + wn * 128;
+        const __amdgpu_buffer_rsrc_t gu_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(p.pre + at), (short)0, rows_in > 0 ? rows_in * p.N * 8 : 0, 0x00020000);
+        const __amdgpu_buffer_rsrc_t d_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)((bf16_t *)p.C + at), (short)0, rows_in > 0 ? rows_in * p.N * 4 : 0, 0x00020000);
+        i32x4_t gu[2][2][4];
+        auto load = [&](i32x4_t (&x)[2][4], int half) {          // eight rows
+            int r2 = 4 * p.N * 4;
+            asm volatile("" : "+s"(r2));
+#pragma unroll
+            for (int it = 0; it < 4; it++)
+#pragma unroll
+                for (int u = 0; u < 2; u++) x[u][it] = __builtin_amdgcn_raw_buffer_load_b128(gu_rsrc, lane_at * 4, (half * 4 + it) * r2 + u * p.N * 4, 0);
+        };
+        load(gu[0], 0);
+#pragma unroll
+        for (int i = 0; i < MB; i++) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 8; j++) panel_put_acc(panel, l16, j * 4 + kq, acc[j][i]);
+            panel_written();
+            f32x4_t v[8];
+#pragma unroll
+            for (int it = 0; it < 8; it++) v[it] = panel_get(panel, it * 2 + (lane >> 5), lane & 31);
+            panel_wait(v);
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                if (i * 2 + h + 1 < 2 * MB) load(gu[1 - h], i * 2 + h + 1);
+                int r2 = 4 * p.N * 2;
+                asm volatile("" : "+s"(r2));
+#pragma unroll
+                for (int it = 0; it < 4; it++) {
+                    const f32x4_t g = __builtin_bit_cast(f32x4_t, gu[h][0][it]), u = __builtin_bit_cast(f32x4_t, gu[h][1][it]);
+                    bf16x4_t dg, du;
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        float a, b;
+                        vla_swiglu_grad(g[e], u[e], v[h * 4 + it][e], a, b);
+                        dg[e] = (bf16_t)a;
+                        du[e] = (bf16_t)b;
+                    }
+                    const int row = ((i * 2 + h) * 4 + it) * r2;
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(i32x2_t, dg), d_rsrc, lane_at * 2, row, 0);
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(i32x2_t, du), d_rsrc, lane_at * 2, row + p.N * 2, 0);
+                }
+            }
+        }
+        return;
+    }
     // fp32 store, or read-modify-write of the fp32 residual stream: whole 512-byte rows, two rows per instruction,
     // through a buffer descriptor over this wave's block (rows past M fall outside it: their loads
     // return zero and their stores are dropped, so no clamp and no predicate).  x is read XD 16-row blocks ahead of
@@ -424,7 +475,7 @@ template <int EPI, bool KB, int WL, int MB>
 __global__ void __launch_bounds__(256) gemm_bf16_dma_kernel(DmaGemmParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr bool WKB = WL == W_KBLOCKED, WCOL = WL == W_COLUMNS;
-    static_assert(!WCOL || (EPI == EPI_STORE && !KB), "weights as columns");
+    static_assert(!WCOL || ((EPI == EPI_STORE || EPI == EPI_SWIGLU_GRAD) && !KB), "weights as columns");
     constexpr int ROWS = 32 * MB, NA = (MB + 1) / 2, NL = NA + 4;     // tile rows; load instructions per wave and half tile
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave >> 1, wn = wave & 1;
@@ -650,7 +701,7 @@ template <int EPI, bool KB, int WL, int BMT, int BNT, int NS, bool STEP>
 __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr bool WKB = WL == W_KBLOCKED, WCOL = WL == W_COLUMNS;
-    static_assert(!WCOL || (EPI == EPI_STORE && !KB && !STEP), "weights as columns");
+    static_assert(!WCOL || ((EPI == EPI_STORE || EPI == EPI_SWIGLU_GRAD) && !KB && !STEP), "weights as columns");
     constexpr int MB = BMT / 32, NB = BNT / 32;          // 16-row / 16-column blocks per wave
     constexpr int A_HALF = BMT * 64, W_HALF = BNT * 64, SSTAGE = 2 * (A_HALF + W_HALF);
     constexpr int NA = BMT / 32, NWI = BNT / 32;                // load instructions per wave and unit
@@ -904,7 +955,22 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
             for (int it = 0; it < 16 / RPI; it++) {
                 const int row = it * RPI + lane / LPR;
                 f32x4_t v = *(const f32x4_t *)panel_at(pb, row, lane % LPR);
-                if (mblock + row < p.M) {
+                if (EPI == EPI_SWIGLU_GRAD) {
+                    if (mblock + row < p.M) {
+                        const size_t at = (size_t)(mblock + row) * 2 * p.N + (size_t)tn * BNT + (lane % LPR) * 4;
+                        const f32x4_t g = *(const f32x4_t *)(p.pre + at), u = *(const f32x4_t *)(p.pre + at + p.N);
+                        bf16x4_t dg, du;
+#pragma unroll
+                        for (int e = 0; e < 4; e++) {
+                            float a, b;
+                            vla_swiglu_grad(g[e], u[e], v[e], a, b);
+                            dg[e] = (bf16_t)a;
+                            du[e] = (bf16_t)b;
+                        }
+                        *(bf16x4_t *)((bf16_t *)p.C + at) = dg;
+                        *(bf16x4_t *)((bf16_t *)p.C + at + p.N) = du;
+                    }
+                } else if (mblock + row < p.M) {
                     f32x4_t *dst = (f32x4_t *)(out + (size_t)row * p.N);
                     if (EPI == EPI_RESIDUAL) {
                         const f32x4_t x = *(const f32x4_t *)(p.res + out0 + (size_t)row * p.N);
@@ -952,7 +1018,7 @@ template <int EPI, bool KB, int WL = KB>
 int launch(DmaGemmParams p, int mb, hipStream_t st) {
     const double flops = 2.0 * p.M * p.K * (epi_swiglu(EPI) ? 2.0 * p.N : (double)p.N);
     ProfScope ps(epi_swiglu(EPI) ? "gemm_bf16_dma<swiglu>" : EPI == EPI_RESIDUAL ? "gemm_bf16_dma<residual>"
-                 : epi_qkv(EPI) ? "gemm_bf16_dma<qkv_rope>" : "gemm_bf16_dma<store>", flops, st);
+                 : epi_qkv(EPI) ? "gemm_bf16_dma<qkv_rope>" : EPI == EPI_SWIGLU_GRAD ? "gemm_bf16_dma<swiglu_grad>" : "gemm_bf16_dma<store>", flops, st);
     p.tiles_m = (p.M + 32 * mb - 1) / (32 * mb);
     switch (mb) {
         case 5: return launch_plain<EPI, KB, WL, 5>(p, st);
@@ -1023,15 +1089,15 @@ TileChoice choose_tile(const DmaGemmParams &p, int mb_low, bool step = false) { 
         const long tiles = (p.M + 32L * mb - 1) / (32L * mb) * (cols / 256);
         offer({TILE_LARGE, mb}, (tiles + 255) / 256 * (units * (333 + 107 * mb) + 8000));
     }
-    if (EPI == EPI_STORE || EPI == EPI_RESIDUAL) offer({TILE_64x64, 0}, units * (2 * t64 <= 150 ? 310 : 2 * t64 <= 256 && !step ? 345 : 120 + 5 * (2 * t64) / 4));
-    if ((EPI == EPI_STORE || EPI == EPI_RESIDUAL) && p.M > 128 && p.M <= cols && units >= 16 && 2 * t64 > 288 && 2 * t128 <= 256)
+    if (epi_plain(EPI)) offer({TILE_64x64, 0}, units * (2 * t64 <= 150 ? 310 : 2 * t64 <= 256 && !step ? 345 : 120 + 5 * (2 * t64) / 4));
+    if (epi_plain(EPI) && p.M > 128 && p.M <= cols && units >= 16 && 2 * t64 > 288 && 2 * t128 <= 256)
         offer({TILE_128x64, 0}, units * 445);
     if (epi_swiglu(EPI)) offer({TILE_64x128, 0}, units * (t64 <= 276 ? 620 : t64 <= 588 ? 1000 : 17 * t64 / 10));
     else offer({TILE_64x128, 0}, units * (t64 <= 276 ? 470 : 17 * t64 / 10));
     if (t128 <= 256) offer({TILE_128x128_1, 0}, units * (epi_swiglu(EPI) && !step ? 735 : 640));
     if (!step && units >= 16) {
         const long t96 = (p.M + 95L) / 96 * (cols / 128), t160 = (p.M + 159L) / 160 * (cols / 128);
-        if ((EPI == EPI_STORE || EPI == EPI_RESIDUAL) && p.M > 128 && p.M <= cols && 2 * t64 > 288) {
+        if (epi_plain(EPI) && p.M > 128 && p.M <= cols && 2 * t64 > 288) {
             if (2 * t96 <= 256) offer({TILE_96x64, 0}, units * 394);
             if (2 * t160 <= 256) offer({TILE_160x64, 0}, units * 525);
         }
@@ -1046,15 +1112,15 @@ template <int EPI, bool KB, int WL = KB, bool STEP = false>
 int launch_tile(const DmaGemmParams &p, SmallTile tile, hipStream_t st) {
     const double flops = 2.0 * p.M * p.K * (epi_swiglu(EPI) ? 2.0 * p.N : (double)p.N);
     ProfScope ps(epi_swiglu(EPI) ? "gemm_small<swiglu>" : EPI == EPI_RESIDUAL ? "gemm_small<residual>"
-                 : epi_qkv(EPI) ? "gemm_small<qkv_rope>" : "gemm_small<store>", flops, st);
-    if constexpr (EPI == EPI_STORE || EPI == EPI_RESIDUAL) {
+                 : epi_qkv(EPI) ? "gemm_small<qkv_rope>" : EPI == EPI_SWIGLU_GRAD ? "gemm_small<swiglu_grad>" : "gemm_small<store>", flops, st);
+    if constexpr (epi_plain(EPI)) {
         if (tile == TILE_64x64) return launch_small<EPI, KB, WL, 64, 64, 4, STEP>(p, st);
         if constexpr (!STEP) {
             if (tile == TILE_128x64) return launch_small<EPI, KB, WL, 128, 64, 4, STEP>(p, st);
         }
     }
     if constexpr (!STEP) {
-        if constexpr (EPI == EPI_STORE || EPI == EPI_RESIDUAL) {
+        if constexpr (epi_plain(EPI)) {
             if (tile == TILE_96x64) return launch_small<EPI, KB, WL, 96, 64, 5, STEP>(p, st);
             if (tile == TILE_160x64) return launch_small<EPI, KB, WL, 160, 64, 4, STEP>(p, st);
         }
@@ -1069,7 +1135,9 @@ int launch_tile(const DmaGemmParams &p, SmallTile tile, hipStream_t st) {
 template <int EPI>
 int launch_kb(const DmaGemmParams &p, bool kb, hipStream_t st) {
     const TileChoice t = choose_tile<EPI>(p, 5);
-    if constexpr (EPI == EPI_QKV_ROWS || EPI == EPI_SWIGLU_KEEP || EPI == EPI_STORE) {          // row-major operands only
+    if constexpr (EPI == EPI_SWIGLU_GRAD) {
+        return t.small != TILE_LARGE ? launch_tile<EPI, false, W_COLUMNS>(p, t.small, st) : launch<EPI, false, W_COLUMNS>(p, t.mb, st);
+    } else if constexpr (EPI == EPI_QKV_ROWS || EPI == EPI_SWIGLU_KEEP || EPI == EPI_STORE) {          // row-major operands only
         if (kb) return 0;
         if constexpr (EPI == EPI_STORE) {
             if (p.segK) return t.small != TILE_LARGE ? launch_tile<EPI, false, W_COLUMNS>(p, t.small, st) : launch<EPI, false, W_COLUMNS>(p, t.mb, st);
@@ -1119,14 +1187,17 @@ int try_gemm_bf16_dma(const GemmArgs &g, hipStream_t st) {
     }
     if (g.segN % BN != 0) return 0;
     if (g.segK) {
-        if (kb || g.epilogue != EPI_STORE || g.segK % 64 != 0 || g.segK < 256 || g.K != g.n_seg * g.segK || (size_t)g.segK * g.segN * 2 >= ((size_t)1 << 31)) return 0;
+        const bool grad = g.epilogue == EPI_SWIGLU_GRAD;
+        if (kb || !(grad || g.epilogue == EPI_STORE) || g.segK % 64 != 0 || g.segK < 256 || g.K != g.n_seg * g.segK || (size_t)g.segK * g.segN * 2 >= ((size_t)1 << 31)) return 0;
         for (int i = 0; i < g.n_seg; i++)
             if ((size_t)g.W[i] % 16 != 0) return 0;
         p.segK = g.segK;
         p.N = g.segN;
         p.tiles_n = p.N / BN;
-        return launch_kb<EPI_STORE>(p, false, st);
+        p.pre = g.pre;
+        return grad ? launch_kb<EPI_SWIGLU_GRAD>(p, false, st) : launch_kb<EPI_STORE>(p, false, st);
     }
+    if (g.epilogue == EPI_SWIGLU_GRAD) return 0;
     if (g.epilogue == EPI_QKV_ROWS) {
         const QkvRopeArgs *ra = g.rope;
         if (!ra || ra->kv->d != 128 || (g.n_seg != 3 && g.n_seg != 2) || g.segN != ra->kv->n_heads * 128) return 0;

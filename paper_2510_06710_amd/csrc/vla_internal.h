@@ -35,8 +35,10 @@ struct RowsArgs {           // one forward over n_seq sequences x R new rows eac
 };
 
 // EPI_QKV_ROWS and EPI_SWIGLU_KEEP are those of the gradient pass (row-major operands, direct-to-LDS kernels only): rotated q | k | v
-// as rows of 3H instead of the KV layout, and SwiGLU with its pre-activations.
-enum GemmEpilogue { EPI_STORE = 0, EPI_RESIDUAL = 1, EPI_SWIGLU = 2, EPI_QKV_ROPE = 3, EPI_QKV_ROWS = 4, EPI_SWIGLU_KEEP = 5 };
+// as rows of 3H instead of the KV layout, and SwiGLU with its pre-activations.  EPI_SWIGLU_GRAD is the input gradient of the down projection (segK)
+// with SwiGLU's own behind it: from the product d act and the pre-activations, d gate | d up.
+enum GemmEpilogue { EPI_STORE = 0, EPI_RESIDUAL = 1, EPI_SWIGLU = 2, EPI_QKV_ROPE = 3, EPI_QKV_ROWS = 4, EPI_SWIGLU_KEEP = 5, EPI_SWIGLU_GRAD = 6 };
+constexpr bool epi_plain(int e) { return e == EPI_STORE || e == EPI_RESIDUAL || e == EPI_SWIGLU_GRAD; }
 constexpr bool epi_swiglu(int e) { return e == EPI_SWIGLU || e == EPI_SWIGLU_KEEP; }
 constexpr bool epi_qkv(int e) { return e == EPI_QKV_ROPE || e == EPI_QKV_ROWS; }
 
@@ -62,12 +64,12 @@ struct GemmArgs {
     const void *Wkb[3];     // the same segments repacked k-blocked ([K / 32][segN + pad][32]) or NULL: kernels that stream
                             // the weights from HBM with row-major activations (decode forwards) prefer these
     int n_seg, segN;        // N = n_seg * segN (EPI_SWIGLU: W[0] = gate, W[1] = up, N = segN)
-    void *C;                // EPI_STORE: fp32 [M, N]; EPI_SWIGLU: storage dtype [M, N]; EPI_RESIDUAL: fp32 [M, N]
+    void *C;                // EPI_STORE: fp32 [M, N]; EPI_SWIGLU: storage dtype [M, N], EPI_SWIGLU_GRAD: [M, 2N]; EPI_RESIDUAL: fp32 [M, N]
     const float *res;       // EPI_RESIDUAL: what the product is added to, fp32 [M, N]; NULL: C (multi-row kernels alone: any other array)
     int M, K;
     int epilogue;
     const QkvRopeArgs *rope;   // EPI_QKV_ROPE, EPI_QKV_ROWS (q_out [M, 3H]; of kv only n_heads and d; two segments: k and v, q's third stays)
-    float *pre;             // EPI_SWIGLU_KEEP: gate | up pre-activations, fp32 [M, 2N]
+    float *pre;             // EPI_SWIGLU_KEEP (out), EPI_SWIGLU_GRAD (in): gate | up pre-activations, fp32 [M, 2N]
     int kblocked;           // A (a_rows rows per 32-column block), the weights (segN rows per block, each segment
                             // on its own) and a SwiGLU output are stored [K / 32][rows][32]: direct-to-LDS kernel only
     int a_rows;             // rows of A that may be read (>= M; contents past M arbitrary): the MFMA kernel
@@ -78,7 +80,7 @@ struct GemmArgs {
     int *deferred_splits;   // not NULL (EPI_STORE and EPI_RESIDUAL of the split-K kernels): the kernel leaves its n
                             // partial products [n][M][N] at the start of the scratch buffer, puts n here and does not
                             // reduce them (the caller's next kernel adds them in order); 0 here: C is complete
-    int segK;               // not 0 (EPI_STORE, bf16): an input gradient, C[M, segN] = A[M, n_seg segK] . [W[0]; W[1]; ..] with segments
+    int segK;               // not 0 (EPI_STORE or EPI_SWIGLU_GRAD, bf16): an input gradient, C[M, segN] = A[M, n_seg segK] . [W[0]; W[1]; ..] with segments
                             // [segK, segN] as the forward has them; K = n_seg segK
     void *split_scratch;    // not NULL (EPI_STORE, row-major bf16): device scratch of split_scratch_bytes through which a
     size_t split_scratch_bytes;   // multi-row problem with few output tiles may cut its K range into parts
@@ -232,6 +234,12 @@ __device__ __forceinline__ float vla_silu_mul(float gate, float up) {
 // ... and that of the gradient pass, whose backward differentiates it at the kept pre-activations: the library's exponential
 // and a division.
 __device__ __forceinline__ float vla_silu_mul_exact(float gate, float up) { return gate / (1.0f + expf(-gate)) * up; }
+// ... which is d gate = d act up silu'(gate), d up = d act silu(gate); silu'(t) = s (1 + t (1 - s)), s = sigmoid(t).
+__device__ __forceinline__ void vla_swiglu_grad(float gate, float up, float d_act, float &d_gate, float &d_up) {
+    const float s = 1.0f / (1.0f + expf(-gate));
+    d_gate = d_act * up * s * (1.0f + gate * (1.0f - s));
+    d_up = d_act * gate * s;
+}
 
 // Maps a linear work-item id of the large-tile GEMMs to an output tile.  Workgroups are dealt round-robin to
 // the eight XCDs, each with its own L2.  The ids of XCD y, taken in order, walk the tile rows y, y + 8, y + 16, ...
