@@ -8,12 +8,13 @@
 // The sums are those of gemm_skinny.hip bit for bit: v_mfma_f32_32x32x16_bf16 on the same columns (8 j .. + 7 of either half
 // of a 64-column tile) in the same order.  That operand is a 16-byte piece of every 64: a lane that loaded it alone would
 // leave the rest of the line to three more instructions.  Two loads fetch the whole lines of 16 rows instead and the pieces
-// change places between lane rows afterwards (v_permlane16_swap).  With 16 activation rows half of the instruction's columns
+// change places between lane rows afterwards (v_permlane16_swap).  Of k-blocked weights each load brings 1 KB by itself, read past
+// the caches (WHOLE).  With 16 activation rows half of the instruction's columns
 // are idle, with 16 weight rows half of its rows: the matrix cores have the time.
 //
 // What counts is the number of waves with loads in flight, not the loads per wave: with one tile each in flight, about 64
 // registers, three or four workgroups share a CU.  Measured on the 7B shape with repacked weights (time between events around
-// the launch, at 1 / 16 rows): QKV 24 / 26 us, O and down 16 / 20 (mean; 23 at 32 rows), gate/up 35 / 38; two or three tiles in
+// the launch, at 1 / 16 rows): QKV 24 / 26 us, O and down 16 / 20 (mean; 23 at 32 rows), gate/up 35 / 38 (30 / 32 in the kernel since WHOLE); two or three tiles in
 // flight cost gate/up 0 / 2 us more.  The split-K form takes 25 / 26, 22 / 23 (23) and 45 / 47 us and leaves 26 to 33 us of
 // reductions a layer that this one does not need.
 //
@@ -21,6 +22,8 @@
 // forms for itself in LDS, with the sums of the norm kernels, while its first weights are on the way: 0 to 2 us more in the
 // kernel for a launch of 6 us less.  The rows that a thread holds end the rule at four.
 #include "vla_internal.h"
+
+#include <type_traits>
 
 namespace {
 
@@ -36,6 +39,7 @@ struct StreamParams {
     int parts;                 // K parts of the sums (1, 2, 4 or 8), one wave each
     int groups;                // blocks of columns per workgroup, at most NW / parts (waves beyond them only help with the norm)
     size_t w_row, w_step;      // elements between weight rows and between 32-column steps of one row
+    bool whole;                // k-blocked weights
 };
 
 // A 64-column tile of 16 * B rows as it was loaded (x[c][b]: lane l holds columns 32 (l / 32) + 16 c + 8 (l / 16 % 2) .. + 7 of row
@@ -58,9 +62,30 @@ __device__ __forceinline__ void operands(bf16x8_t (&op)[4], const bf16x8_t (&x)[
     }
 }
 
+// x[c][b]: lane l holds columns 32 c + 8 (l / 16) .. + 7 of row l % 16 -> as above (lane 32 + l of x[0] against lane l of x[1])
+template <int B>
+__device__ __forceinline__ void change_halves(bf16x8_t (&x)[2][B]) {
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int b = 0; b < B; b++) {
+        u4 v0 = __builtin_bit_cast(u4, x[0][b]), v1 = __builtin_bit_cast(u4, x[1][b]);
+#pragma unroll
+        for (int d = 0; d < 4; d++) {
+            const auto r = __builtin_amdgcn_permlane32_swap(v0[d], v1[d], false, false);
+            v0[d] = r[0]; v1[d] = r[1];
+        }
+        x[0][b] = __builtin_bit_cast(bf16x8_t, v0);
+        x[1][b] = __builtin_bit_cast(bf16x8_t, v1);
+    }
+}
+
 // A wave multiplies 32 weight rows (SwiGLU: 16 gate and the matching up rows; NB = 1: 16 rows, twice) by 16 * MB activation
 // rows.  UN: tiles of 64 columns in flight, NORM: activation rows that the kernel norms itself (0: none).
-template <int EPI, int NB, int MB, int UN, int NORM>
+// WHOLE (k-blocked weights): a load brings 1 KB, 16 rows' whole 64 bytes of one 32-column step, and the steps change places between
+// the halves of the wave afterwards; as all of a line is used at once, it may leave the caches at once, and the K and V of the step's environments
+// (4.7 MB an environment of 289 keys and layer) find more of them there.  7B width, 1 environment: gate/up 32.7 -> 30.0 us, attention
+// 9.3 -> 7.1; 13: 35.1 -> 31.6 and 14.3 -> 10.6.  (Whole pieces without the hint: as before; the hint on halves of pieces: gate/up 36.8.)
+template <int EPI, int NB, int MB, int UN, int NORM, bool WHOLE>
 __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
     constexpr bool SW = EPI == EPI_SWIGLU;
     constexpr int COLS = SW ? 16 : 16 * NB, LDW = 16 * NB + 4;          // output columns, floats of a row of sums
@@ -75,7 +100,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
 #pragma unroll
     for (int i = 0; i < MB; i++) a[i] = p.A + (size_t)min(i * 16 + l16, p.M - 1) * K + hh * 32 + c1 * 8;
     const bf16_t *xrow = xs + min(l32, p.M - 1) * (K + 32) + hh * 32;
-    const size_t w_off = hh * p.w_step + c1 * 8 + (size_t)l16 * p.w_row;
+    const size_t w_off = (WHOLE ? (size_t)(lane >> 4) * 8 : hh * p.w_step + c1 * 8) + (size_t)l16 * p.w_row;
     if (SW) {
         w[0] = p.W0 + (size_t)n0 * p.w_row + w_off;
         w[NB - 1] = p.W1 + (size_t)n0 * p.w_row + w_off;
@@ -94,7 +119,10 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
 #pragma unroll
         for (int c = 0; c < 2; c++)
 #pragma unroll
-            for (int r = 0; r < NB; r++) wf[u][c][r] = *(const bf16x8_t *)(w[r] + wo + c * 16);
+            for (int r = 0; r < NB; r++) {
+                if (WHOLE) wf[u][c][r] = __builtin_bit_cast(bf16x8_t, __builtin_nontemporal_load((const i32x4_v *)(w[r] + wo + c * p.w_step)));
+                else wf[u][c][r] = *(const bf16x8_t *)(w[r] + wo + c * 16);
+            }
         if (!NORM)
 #pragma unroll
             for (int c = 0; c < 2; c++)
@@ -109,6 +137,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
         } else {
             operands<MB>(ao, af[u]);
         }
+        if (WHOLE) change_halves<NB>(wf[u]);
         operands<NB>(wo, wf[u]);
 #pragma unroll
         for (int j = 0; j < 4; j++) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wo[j], ao[j], acc, 0, 0, 0);
@@ -247,8 +276,13 @@ int launch(StreamParams p, hipStream_t st) {
     // each tile brings twice the activations, and one is better: 7B shape, O and down at 32 rows 23 us against 25).
     p.groups = (blocks + 255) / 256 < NW / p.parts ? (blocks + 255) / 256 : NW / p.parts;
     const int grid = (blocks + p.groups - 1) / p.groups;
-    if (MB == 1 && grid <= 256) gemm_stream_kernel<EPI, NB, MB, MB == 1 ? 2 : 1, NORM><<<grid, 64 * NW, lds, st>>>(p);
-    else gemm_stream_kernel<EPI, NB, MB, 1, NORM><<<grid, 64 * NW, lds, st>>>(p);
+    auto go = [&](auto whole) {
+        constexpr bool WHOLE = decltype(whole)::value;
+        if (MB == 1 && grid <= 256) gemm_stream_kernel<EPI, NB, MB, MB == 1 ? 2 : 1, NORM, WHOLE><<<grid, 64 * NW, lds, st>>>(p);
+        else gemm_stream_kernel<EPI, NB, MB, 1, NORM, WHOLE><<<grid, 64 * NW, lds, st>>>(p);
+    };
+    if (p.whole) go(std::true_type{});
+    else go(std::false_type{});
     return vla_check_launch("gemm_stream");
 }
 
@@ -291,6 +325,7 @@ int try_gemm_bf16_stream(const GemmArgs &g, hipStream_t st) {
     for (int i = 0; i < n_seg; i++) kb = kb && g.Wkb[i];
     const void *const *W = kb ? g.Wkb : g.W;
     p.W0 = (const bf16_t *)W[0]; p.W1 = (const bf16_t *)W[1]; p.W2 = (const bf16_t *)W[2];
+    p.whole = kb;
     p.w_row = kb ? 32 : (size_t)g.K;
     p.w_step = kb ? (size_t)(g.segN + VLA_KB_PAD_ROWS) * 32 : 32;
     p.C = g.C; p.M = g.M; p.K = g.K; p.segN = g.segN;
