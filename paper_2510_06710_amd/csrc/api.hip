@@ -478,7 +478,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         if (!fused) {
             if (fuse_reduce && !attends) g.deferred_splits = &ds;
             if ((rc = run_gemm<T>(c, g, ws.skinny, st))) return rc;
-            if (attends) rc = launch_attention_decode_qkv((bf16_t *)ws.AO, ws.QKV, ws.rope, kv, kl, ra, H, st);
+            if (attends) rc = launch_attention_decode_qkv((bf16_t *)ws.AO, ws.QKV, ws.rope, kv, kl, ra, H, c.n_layers, st);
             else if (f32_step) rc = launch_attention_step_qkv((float *)ws.AO, ws.QKV, ws.rope, kv, kl, ra, H, st);
             else if (c.dtype == VLA_DTYPE_BF16 && !(force_generic() & 16))
                 rc = launch_rope_kv_write_bf16((bf16_t *)ws.Q, ds ? (const float *)ws.skinny : ws.QKV, ds ? ds : 1, (size_t)M * 3 * H,

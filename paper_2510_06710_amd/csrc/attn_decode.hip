@@ -11,7 +11,11 @@
 //      loads, the wave covers 8 / 4 rows per instruction (1 KB contiguous), probabilities come from
 //      LDS, and the row groups are summed by lane-xor steps and a four-way add through LDS.
 // Of few pairs each gets eight waves (see FEW_PAIRS), half the V columns per lane.
+// NT: K and V, whole lines per instruction and used once a step, carry the non-temporal hint: 2048 pairs of 290 keys 64.8 -> 54.6 us (5.6 TB/s),
+// 8192 pairs 224 -> 206 (5.9; few pairs: see KV_KEPT).
 #include "vla_internal.h"
+
+#include <type_traits>
 
 namespace {
 
@@ -30,7 +34,7 @@ struct FusedQkv {
 // chain over the dims; the softmax's sum adds key chunks w and w + 4 lane by lane, then the lanes, then w = 0..3; P.V has
 // one chain for every 4 * (512 / D) th position (eight waves hold the same chains with half the columns per lane) and a
 // fixed tree over the chains.
-template <int D, int NWV, bool FUSE>
+template <int D, int NWV, bool FUSE, bool NT>
 __global__ void __launch_bounds__(64 * NWV) attn_decode_kernel(bf16_t *out, const bf16_t *qbuf, bf16_t *kc, bf16_t *vc, FusedQkv f,
                                                               int n_heads, int nk, int pos_stride, int H) {
     static_assert(NWV == 4 || (NWV == 8 && MAXCH == 8), "the order of the sums");
@@ -88,7 +92,10 @@ __global__ void __launch_bounds__(64 * NWV) attn_decode_kernel(bf16_t *out, cons
             bf16x8_t kv[DC];
             if (!FUSE || p < n_old) {
 #pragma unroll
-                for (int c = 0; c < DC; c++) kv[c] = *(const bf16x8_t *)(kh + ((size_t)c * pos_stride + p) * 8);
+                for (int c = 0; c < DC; c++) {
+                    const i32x4_v *src = (const i32x4_v *)(kh + ((size_t)c * pos_stride + p) * 8);
+                    kv[c] = __builtin_bit_cast(bf16x8_t, NT ? __builtin_nontemporal_load(src) : *src);
+                }
             } else {
 #pragma unroll
                 for (int c = 0; c < DC; c++) kv[c] = *(const bf16x8_t *)&knew[c * 8];
@@ -147,7 +154,8 @@ __global__ void __launch_bounds__(64 * NWV) attn_decode_kernel(bf16_t *out, cons
     float acc[VPL] = {};
 #pragma unroll 4
     for (int pos = slot; pos < n_old; pos += NWV * RPI) {
-        const bf16v v = *(const bf16v *)(vh + (size_t)pos * D + c * VPL);
+        const bf16v *src = (const bf16v *)(vh + (size_t)pos * D + c * VPL);
+        const bf16v v = NT ? __builtin_nontemporal_load(src) : *src;
         const float pr = probability(pos);
 #pragma unroll
         for (int e = 0; e < VPL; e++) acc[e] += pr * (float)v[e];
@@ -192,6 +200,10 @@ __global__ void __launch_bounds__(64 * NWV) attn_decode_kernel(bf16_t *out, cons
 // now; 13 environments 17.4 + 9.5 -> 18 us.  From FEW_PAIRS on the chip is full with four waves, and the extra
 // latency ahead of the first key costs more than the launch (2048 pairs 62 + 5 against 74 us, 8192 225 + 13 against 271).
 constexpr int FEW_PAIRS = 1024;
+// Bytes of K and V of all layers up to which a step leaves them to the memory-side cache (256 MB) for the next; more are read past the
+// caches.  Six steps of the 7B width, kept and not, ms: 4 layers, 4 environments (77 MB) 2.23 and 2.28, 13 (249 MB) 2.59 and 2.67, 16 (306 MB) 2.88 and
+// 2.84, 28 3.57 and 3.48; 8 layers, 4 4.48 and 4.58, 8 (306 MB) 4.97 and 4.91, 13 5.41 and 5.27.
+constexpr double KV_KEPT = 256e6;
 
 }  // namespace
 
@@ -207,8 +219,8 @@ int try_attention_decode_bf16(bf16_t *out, const bf16_t *q, const KvView &kv, in
     bf16_t *kc = (bf16_t *)kv.k + (size_t)layer * kv.layer_elems, *vc = (bf16_t *)kv.v + (size_t)layer * kv.layer_elems;
     // algorithmic bytes: K and V tiles of every (sequence, head) pair, read once
     ProfScope ps("attn_decode", 2.0 * n_items * (double)nk * kv.d * 2.0, st);
-    if (kv.d == 128) attn_decode_kernel<128, 4, false><<<n_items, 256, 0, st>>>(out, q, kc, vc, FusedQkv{}, kv.n_heads, nk, kv.pos_stride, H);
-    else attn_decode_kernel<64, 4, false><<<n_items, 256, 0, st>>>(out, q, kc, vc, FusedQkv{}, kv.n_heads, nk, kv.pos_stride, H);
+    if (kv.d == 128) attn_decode_kernel<128, 4, false, true><<<n_items, 256, 0, st>>>(out, q, kc, vc, FusedQkv{}, kv.n_heads, nk, kv.pos_stride, H);
+    else attn_decode_kernel<64, 4, false, true><<<n_items, 256, 0, st>>>(out, q, kc, vc, FusedQkv{}, kv.n_heads, nk, kv.pos_stride, H);
     int rc = vla_check_launch("attn_decode");
     return rc ? rc : 1;
 }
@@ -220,13 +232,20 @@ bool attention_decode_fuses_qkv(const KvView &kv, const RowsArgs &ra) {
 // The decode step's attention straight from the QKV projection, fp32 [n_seq, 3H] rows.  Only where
 // attention_decode_fuses_qkv().
 int launch_attention_decode_qkv(bf16_t *out, const float *qkv, const float2 *table, const KvView &kv, int layer, const RowsArgs &ra,
-                                int H, hipStream_t st) {
+                                int H, int n_layers, hipStream_t st) {
     const int nk = ra.pos0 + 1, n_items = ra.n_seq * kv.n_heads;
     if (n_items == 0) return 0;
     bf16_t *kc = (bf16_t *)kv.k + (size_t)layer * kv.layer_elems, *vc = (bf16_t *)kv.v + (size_t)layer * kv.layer_elems;
     ProfScope ps("attn_decode", 2.0 * n_items * (double)nk * kv.d * 2.0, st);
     const FusedQkv f{qkv, table};
-    if (kv.d == 128) attn_decode_kernel<128, 8, true><<<n_items, 512, 0, st>>>(out, nullptr, kc, vc, f, kv.n_heads, nk, kv.pos_stride, H);
-    else attn_decode_kernel<64, 8, true><<<n_items, 512, 0, st>>>(out, nullptr, kc, vc, f, kv.n_heads, nk, kv.pos_stride, H);
+    auto go = [&](auto dim, auto nt) {
+        attn_decode_kernel<decltype(dim)::value, 8, true, decltype(nt)::value><<<n_items, 512, 0, st>>>(out, nullptr, kc, vc, f, kv.n_heads, nk, kv.pos_stride, H);
+    };
+    auto width = [&](auto nt) {
+        if (kv.d == 128) go(std::integral_constant<int, 128>{}, nt);
+        else go(std::integral_constant<int, 64>{}, nt);
+    };
+    if (4.0 * n_items * nk * kv.d * n_layers > KV_KEPT) width(std::true_type{});
+    else width(std::false_type{});
     return vla_check_launch("attn_decode_qkv");
 }

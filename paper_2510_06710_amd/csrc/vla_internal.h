@@ -311,7 +311,7 @@ int try_attention_decode_bf16(bf16_t *out, const bf16_t *q, const KvView &kv, in
                               const RowsArgs &ra, int H, hipStream_t st);
 bool attention_decode_fuses_qkv(const KvView &kv, const RowsArgs &ra);
 int launch_attention_decode_qkv(bf16_t *out, const float *qkv, const float2 *table, const KvView &kv, int layer, const RowsArgs &ra,
-                                int H, hipStream_t st);
+                                int H, int n_layers, hipStream_t st);
 size_t attention_prefill_scratch_bytes(int n_seq, int n_heads, int d, int n_keys);
 
 // Attention of the gradient pass with its [rows x keys] matrices kept (attn_rows.hip).  qkv: rotated q | k | v, bf16 [n_seq * R, 3H];
