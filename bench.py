@@ -392,7 +392,7 @@ def main():
         r = prof_prefill[dom]
         achieved = r["work"] / (r["ms"] * 1e-3) / 1e12
         traffic, traffic_source = read_traffic(os.path.join(ROOT, "profiles", "gemm_swiglu_cfg3_traffic.txt"),
-                                               "gemm_bf16_dma_kernel<2, true, true, 8>",
+                                               "gemm_bf16_dma_kernel<2, true, 1, 8>",
                                                os.path.join(ROOT, "paper_2510_06710_amd", "csrc", "gemm_dma.hip"))
         roofline = {"bound": "mfma", "kernel": "gemm_bf16_dma_kernel<EPI_SWIGLU, k-blocked> (gate/up projection, prefill)",
                     "achieved": achieved, "peak": MI355X_BF16_TFLOPS, "unit": "TFLOP/s",
