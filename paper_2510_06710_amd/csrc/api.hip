@@ -593,22 +593,17 @@ static int decode_impl(vla_model *m, void *kvbuf, void *wsbuf, const float *h_la
         // A step's rows go to the head without their final norm, which it forms as the loads bring them (a launch of 3 to 5 us per
         // step less); the sums of squares, a few per row, take the place of the normalised rows.
         const HeadNorm final_norm{(const float *)m->w.final_norm, c.rms_eps, ws.Hb};
-        const bool head_norms = B <= VLA_HEAD_PARTIAL_ROWS;
         for (int j = 0; j < A; j++) {
             bool more = j + 1 < A;
             const NextStep next{ws.Nrm, gemm_norms(c, ws, 1, B, H) ? nullptr : (const float *)m->layers[0].attn_norm, c.rms_eps, ws.rope, S + j, H / c.n_heads, c.rope_theta};
-            const bool prepares = more && head_norms;
+            const bool prepares = more && B <= VLA_HEAD_PARTIAL_ROWS;
             if ((rc = launch_head_sample<T>(h, head, B, H, temperature, gumbel, nullptr, bins, logp, entropy, logits, A, j,
                                             more ? ws.X : nullptr, (const T *)m->w.embed, c.vocab, ws.QKV, st, prepares ? &next : nullptr,
-                                            j && head_norms ? &final_norm : nullptr))) return rc;
+                                            j ? &final_norm : nullptr))) return rc;
             if (!more) break;
             RowsArgs ra{B, 1, S + j, 0x7fffffff};
             if ((rc = run_layers<T>(m, ws, ra, kv, false, st, nullptr, nullptr, prepares))) return rc;
             h = ws.X;
-            if (!head_norms) {
-                if ((rc = launch_final_norm_rows(ws.Hb, ws.X, (const float *)m->w.final_norm, B, 1, 0, 1, H, c.rms_eps, st))) return rc;
-                h = ws.Hb;
-            }
         }
     } else {
         Workspace ws = plan_workspace(c, (char *)wsbuf, B, A, S + A, B * A, false);

@@ -240,9 +240,10 @@ __device__ __forceinline__ void next_embedding(float *dst, const T *embed, int v
     }
 }
 
-// Products of 16 * RB rows and 16 * CB bins from bin0 over the chunks [c0, c1), added in chunk order.
+// Products of 16 * RB rows and 16 * CB bins from bin0 over the chunks [c0, c1), added in chunk order.  NORM: squares[rb] is the sum of
+// the squares of row rb * 16 + lane % 16, a chunk's sum at a time like the products.
 template <typename T, int RB, int CB, int UN, bool NORM>
-__device__ __forceinline__ void tile_logits(f32x4_t (&total)[RB][CB], float (&ss)[RB], const float *h, const float *gain, const T *Wb, int M, int H,
+__device__ __forceinline__ void tile_logits(f32x4_t (&total)[RB][CB], float (&squares)[RB], const float *h, const float *gain, const T *Wb, int M, int H,
                                             int m0, int bin0, int c0, int c1) {
     const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
     const T *wrow[CB];
@@ -260,6 +261,9 @@ __device__ __forceinline__ void tile_logits(f32x4_t (&total)[RB][CB], float (&ss
                 for (int cb = 0; cb < CB; cb++) acc[rb][cb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         };
         clear();
+        float ss[RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; rb++) ss[rb] = 0.f;
         const int k0 = c * CHUNK, k1 = min(H, k0 + CHUNK);
         if (k1 - k0 == CHUNK) chunk_product<RB, CB, true, UN, NORM>(acc, ss, hrow, wrow, gain, k0, k1, kq);
         else chunk_product<RB, CB, false, 1, NORM>(acc, ss, hrow, wrow, gain, k0, k1, kq);
@@ -276,6 +280,14 @@ __device__ __forceinline__ void tile_logits(f32x4_t (&total)[RB][CB], float (&ss
                 float again[RB];
                 for (int rb = 0; rb < RB; rb++) again[rb] = 0.f;
                 chunk_product<RB, CB, false, 1, NORM, true>(acc, again, hrow, wrow, gain, k0, k1, kq);
+            }
+        }
+        if (NORM) {
+#pragma unroll
+            for (int rb = 0; rb < RB; rb++) {
+                ss[rb] += __shfl_xor(ss[rb], 16, 64);
+                ss[rb] += __shfl_xor(ss[rb], 32, 64);
+                squares[rb] = c == c0 ? ss[rb] : squares[rb] + ss[rb];
             }
         }
 #pragma unroll
@@ -297,13 +309,9 @@ __global__ void __launch_bounds__(128) head_partial_kernel(const float *h, const
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m0 = blockIdx.y * 16, m = m0 + (lane & 15);
     const int bin0 = (blockIdx.z * 2 + wave) * (16 * CB);
     f32x4_t total[1][CB];
-    float ss[1] = {0.f};
+    float ss[1];
     tile_logits<T, 1, CB, 8, NORM>(total, ss, h, gain, Wb, M, H, m0, bin0, blockIdx.x, blockIdx.x + 1);
-    if (NORM && bin0 == 0) {
-        ss[0] += __shfl_xor(ss[0], 16, 64);
-        ss[0] += __shfl_xor(ss[0], 32, 64);
-        if (lane < 16 && m < M) squares[(size_t)blockIdx.x * M + m] = ss[0];
-    }
+    if (NORM && bin0 == 0 && lane < 16 && m < M) squares[(size_t)blockIdx.x * M + m] = ss[0];
     if (m >= M) return;
     float *out = P + ((size_t)blockIdx.x * M + m) * VLA_N_BINS + bin0 + (lane >> 4) * 4;
 #pragma unroll
@@ -369,21 +377,28 @@ __global__ void __launch_bounds__(256) sample_kernel(const float *P, int n_part,
     }
 }
 
-// Whole form: 32 rows per workgroup over all chunks, then each wave samples a quarter of the rows.
-template <typename T>
-__global__ void __launch_bounds__(256) head_whole_kernel(const float *h, const T *Wb, SampleArgs a, float *X_next, const T *embed,
+// Whole form: 32 rows per workgroup over all chunks, then each wave samples a quarter of the rows.  NORM: as in the partial form, every
+// wave with the squares of its own.
+template <typename T, bool NORM>
+__global__ void __launch_bounds__(256) head_whole_kernel(const float *h, const float *gain, float eps, const T *Wb, SampleArgs a, float *X_next, const T *embed,
                                                         int vocab, int M, int H) {
     constexpr int RB = 2, CB = 4, LD = VLA_N_BINS + 4;
     __shared__ __attribute__((aligned(16))) float z[16 * RB * LD];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m0 = blockIdx.x * (16 * RB);
     f32x4_t total[RB][CB];
     float ss[RB];
-    tile_logits<T, RB, CB, 2, false>(total, ss, h, nullptr, Wb, M, H, m0, wave * 64, 0, (H + CHUNK - 1) / CHUNK);
+    tile_logits<T, RB, CB, 2, NORM>(total, ss, h, gain, Wb, M, H, m0, wave * 64, 0, (H + CHUNK - 1) / CHUNK);
 #pragma unroll
-    for (int rb = 0; rb < RB; rb++)
+    for (int rb = 0; rb < RB; rb++) {
+        const float inv = NORM ? 1.0f / sqrtf(ss[rb] / (float)H + eps) : 1.0f;
 #pragma unroll
-        for (int cb = 0; cb < CB; cb++)
+        for (int cb = 0; cb < CB; cb++) {
+            if (NORM)
+#pragma unroll
+                for (int r = 0; r < 4; r++) total[rb][cb][r] *= inv;
             *(f32x4_t *)(z + (rb * 16 + (lane & 15)) * LD + wave * 64 + cb * 16 + (lane >> 4) * 4) = total[rb][cb];
+        }
+    }
     __syncthreads();
     for (int r = wave; r < 16 * RB && m0 + r < M; r += 4) {
         float g[4];
@@ -426,8 +441,9 @@ int launch_head_sample(const float *h, const T *lm_head_bins, int n_rows, int H,
     ProfScope ps("head_sample", 2.0 * n_rows * H * VLA_N_BINS, st);
     const SampleArgs a{temperature, gumbel, given_bins, bins_out, logp, ent, logits, out_stride, out_off};
     if (n_rows > VLA_HEAD_PARTIAL_ROWS) {
-        if (norm) { vla_set_error("internal: the norm in the head was declined"); return VLA_ESHAPE; }
-        head_whole_kernel<T><<<(n_rows + 31) / 32, 256, 0, st>>>(h, lm_head_bins, a, X_next, embed, vocab, n_rows, H);
+        const int grid = (n_rows + 31) / 32;
+        if (norm) head_whole_kernel<T, true><<<grid, 256, 0, st>>>(h, norm->gain, norm->eps, lm_head_bins, a, X_next, embed, vocab, n_rows, H);
+        else head_whole_kernel<T, false><<<grid, 256, 0, st>>>(h, nullptr, 0.f, lm_head_bins, a, X_next, embed, vocab, n_rows, H);
         return vla_check_launch("head_sample");
     }
     if (int rc = norm ? launch_head_partial<T, true>(h, norm->gain, lm_head_bins, scratch, norm->squares, n_rows, H, st)

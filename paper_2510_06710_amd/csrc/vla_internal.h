@@ -127,7 +127,7 @@ int launch_rope_q(T *q_out, const float *qf, const float2 *table, int n_seq, int
 // next (with X_next, up to VLA_HEAD_PARTIAL_ROWS rows): what the next decode step needs besides its residual rows, its first
 // norm (gain NULL: not wanted) and its row of the rotation table
 struct NextStep { void *nrm; const float *gain; float eps; float2 *table; int pos, d; float theta; };
-// norm (up to VLA_HEAD_PARTIAL_ROWS rows): h is the residual stream and its final norm the head's to form; squares: [head_chunks(H)][n_rows]
+// norm: h is the residual stream and its final norm the head's to form; squares (up to VLA_HEAD_PARTIAL_ROWS rows): [head_chunks(H)][n_rows]
 struct HeadNorm { const float *gain; float eps; float *squares; };
 template <typename T>
 int launch_head_sample(const float *h, const T *lm_head_bins, int n_rows, int H, float temperature,
