@@ -399,11 +399,16 @@ __global__ void __launch_bounds__(256, 2) attn_cols_kernel(AttnColsArgs a, int n
 
 }  // namespace
 
-// Returns 1 if handled, 0 if declined, < 0 on a launch error.  head_dim 128; any number of rows.
+// head_dim 128; any number of rows; arrays on 16 bytes.
+bool attention_cols_takes(const AttnColsArgs &a) {
+    if (a.H != a.n_heads * HD || a.ldp % 4 != 0 || a.ldp < a.R) return false;
+    if (((size_t)a.P | (size_t)a.dS | (size_t)a.dO | (size_t)a.dq | (size_t)a.qkv | (size_t)a.table | (size_t)a.out_q | (size_t)a.out_k) % 16 != 0) return false;
+    return a.ld_q % 8 == 0 && a.ld_kv % 8 == 0;
+}
+
+// Returns 1 if handled, 0 if declined, < 0 on a launch error.
 int try_attention_cols(const AttnColsArgs &a, int n_seq, hipStream_t st) {
-    if (a.H != a.n_heads * HD || a.ldp % 4 != 0 || a.ldp < a.R) return 0;
-    if (((size_t)a.P | (size_t)a.dS | (size_t)a.dO | (size_t)a.dq | (size_t)a.qkv | (size_t)a.table | (size_t)a.out_q | (size_t)a.out_k) % 16 != 0) return 0;
-    if (a.ld_q % 8 != 0 || a.ld_kv % 8 != 0) return 0;
+    if (!attention_cols_takes(a)) return 0;
     const int heads = n_seq * a.n_heads, tiles = (a.R + 127) / 128;
     ProfScope ps("bw_attention_cols", 4.0 * heads * a.Rq * (double)a.R * HD * (a.Rq == a.R ? 0.5 : 1.0), st);
     attn_cols_kernel<<<(heads + 7) / 8 * 8 * 2 * tiles, 256, 0, st>>>(a, heads, tiles);

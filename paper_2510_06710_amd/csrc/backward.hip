@@ -1044,8 +1044,17 @@ struct Backward {
         if (l < L - live()) {                        // run the layer again from its kept input
             if ((rc = layer_forward(l, a, nullptr))) return rc;
         }
-        // q apart from k and v (adjacent in the structs, as gate and up are) where only the read rows have one
-        const bool q_apart = MF && Rq != R && d == 128 && !(vla_force_generic() & 4);
+        float *d_ao = a.GU;                          // [Mq, H] fp32, from the O projection's on: the gate / up pre-activations are no longer needed
+        float *dqkv = ws.Tmp;                        // [M, 3H] fp32: d q | d k | d v (q, k still in the rotated frame)
+        // the gradients' rows: d q | d k | d v, or d k | d v and behind them the packed d q
+        auto cols_of = [&](bool apart) {
+            T *dkv = (T *)ws.dQKVb + (apart ? 0 : H), *dq = (T *)ws.dQKVb + (apart ? (size_t)ws.a_rows * 2 * H : 0);
+            return AttnColsArgs{a.SP, ws.dP, d_ao, dqkv, (const bf16_t *)Q, ws.rope, (bf16_t *)dq, (bf16_t *)dkv, apart ? H : 3 * H, apart ? 2 * H : 3 * H, apart, R, Rq, Rp, nh, H, full_from, isd};
+        };
+        // q apart from k and v (adjacent in the structs, as gate and up are) where only the read rows have one and the kernel that writes
+        // the gradients so takes them (a workspace off 16 bytes: the batched products)
+        const bool q_apart = MF && Rq != R && !(vla_force_generic() & 4) && attention_cols_takes(cols_of(true));
+        const AttnColsArgs cols = cols_of(q_apart);
         const LoraGroup groups[5] = {group_of(1, &lo.down, &gr.down, F, H), group_of(2, &lo.gate, &gr.gate, H, F), group_of(1, &lo.o, &gr.o, H, H),
                                      q_apart ? group_of(2, &lo.k, &gr.k, H, H) : group_of(3, &lo.q, &gr.q, H, H), group_of(1, &lo.q, &gr.q, H, H)};
         const void *packed[5] = {};
@@ -1069,9 +1078,7 @@ struct Backward {
         if ((rc = vla_check_launch("rmsnorm_bwd"))) return rc;
         // ---- O projection and attention (dx, ws.dXb are now d L / d x_mid)
         if ((rc = lora_group(groups[2], a.AO, a.q_rows, ws.dXb, first, Mq, packed[2]))) return rc;
-        float *d_ao = a.GU;                          // [Mq, H] fp32; the gate / up pre-activations are no longer needed
         if ((rc = input_grad(ws.dXb, {lw.wo}, H, H, d_ao, Mq))) return rc;
-        float *dqkv = ws.Tmp;                        // [M, 3H] fp32: d q | d k | d v (q, k still in the rotated frame)
         // dP = dO v^T ; dV = P^T dO ; dS = P (dP - rowsum(P dP)) ; dQ = dS k / sqrt(d) ; dK = dS^T q / sqrt(d)
         rc = 0;
         if constexpr (MF) {
@@ -1086,14 +1093,10 @@ struct Backward {
             g = heads(ws.dP, Rp, RR * nh, RR, Q + H, 3 * H, rowsH3, d, dqkv + (size_t)(R - Rq) * 3 * H, 3 * H, rowsH3, d, Rq, d, R, 0, 0, isd, causal ? 1 : 0);
             if ((rc = bgemm<float, T, MF>(g, n * nh, st))) return rc;
         }
-        // the gradients' rows: d q | d k | d v, or d k | d v and behind them the packed d q
-        T *dkv = (T *)ws.dQKVb + (q_apart ? 0 : H), *dq = (T *)ws.dQKVb + (q_apart ? (size_t)ws.a_rows * 2 * H : 0);
         rc = 0;
         if constexpr (MF) {
-            const AttnColsArgs cols{a.SP, ws.dP, d_ao, dqkv, (const bf16_t *)Q, ws.rope, dq, dkv, q_apart ? H : 3 * H, q_apart ? 2 * H : 3 * H, q_apart, R, Rq, Rp, nh, H, full_from, isd};
             if (!(vla_force_generic() & 4) && (rc = try_attention_cols(cols, n, st)) < 0) return rc;
         }
-        if (q_apart && rc == 0) { vla_set_error("internal: the attention gradient of the top layer was declined"); return VLA_ESHAPE; }
         if (rc == 0) {
             g = heads(a.SP, Rp, RR * nh, RR, d_ao, H, (long)Rq * H, d, dqkv + 2 * H, 3 * H, rowsH3, d, R, d, Rq, 1, 0, 1.0f, 0);
             if ((rc = bgemm<float, float, MF>(g, n * nh, st))) return rc;
@@ -1105,11 +1108,11 @@ struct Backward {
         // ---- Q / K / V projections and the attention norm
         if ((rc = lora_group(groups[3], a.Nrm, ws.a_rows, ws.dQKVb, first, M, packed[3]))) return rc;
         if (q_apart) {
-            if ((rc = gather_storage(ws.dGU, a.Nrm, Rq)) || (rc = lora_group(groups[4], ws.dGU, ws.a_rows, dq, first, Mq, packed[4]))) return rc;
+            if ((rc = gather_storage(ws.dGU, a.Nrm, Rq)) || (rc = lora_group(groups[4], ws.dGU, ws.a_rows, cols.out_q, first, Mq, packed[4]))) return rc;
         }
         if (l == 0) return 0;
         float *dn_q = q_apart ? ws.Tmp : nullptr;    // q's part of d n, the read rows'
-        if (q_apart) rc = input_grad(dq, {lw.wq}, H, H, dn_q, Mq);
+        if (q_apart) rc = input_grad(cols.out_q, {lw.wq}, H, H, dn_q, Mq);
         if (rc == 0) rc = q_apart ? input_grad(ws.dQKVb, {lw.wk, lw.wv}, H, H, a.GU, M) : input_grad(ws.dQKVb, {lw.wq, lw.wk, lw.wv}, H, H, a.GU, M);   // d n [M, H]
         if (rc) return rc;
         rmsnorm_bwd_kernel<T><<<M, 256, 0, st>>>(ws.dX, (T *)ws.dXb, dx, R, Rq, a.x_in, (const float *)lw.attn_norm, a.GU, dn_q, H, c.rms_eps);

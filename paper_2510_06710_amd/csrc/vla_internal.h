@@ -326,8 +326,9 @@ int try_attention_rows_backward(const AttnRowsArgs &a, int n_seq, hipStream_t st
 // The contractions over the queries that follow, the transposed rotation and the rounding: bf16 d k | d v in rows of ld_kv, d v H columns
 // behind d k, and d q in rows of ld_q, all n_seq * R of them (zeros where there is no query) or q_packed: the n_seq * Rq that have one; from
 // P, dS ([n_seq * n_heads][Rq][ldp] fp32, zero outside the mask), dO (fp32 [n_seq * Rq, H]), dq (fp32 [n_seq * R, 3H], the queries' rows of its
-// first third) and q of qkv.  scale: of d k.  Same return values.
+// first third) and q of qkv.  scale: of d k.  Same return values; attention_cols_takes: whether it does, before anything is launched.
 struct AttnColsArgs { const float *P, *dS, *dO, *dq; const bf16_t *qkv; const float2 *table; bf16_t *out_q, *out_k; int ld_q, ld_kv, q_packed, R, Rq, ldp, n_heads, H, full_from; float scale; };
+bool attention_cols_takes(const AttnColsArgs &a);
 int try_attention_cols(const AttnColsArgs &a, int n_seq, hipStream_t st);
 
 // LoRA gradients of n_p projections that share their input (factors a[p] [rank, in], b[p] [out, rank] in the storage type,
