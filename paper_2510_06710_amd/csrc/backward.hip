@@ -1108,7 +1108,8 @@ struct Backward {
         // ---- Q / K / V projections and the attention norm
         if ((rc = lora_group(groups[3], a.Nrm, ws.a_rows, ws.dQKVb, first, M, packed[3]))) return rc;
         if (q_apart) {
-            if ((rc = gather_storage(ws.dGU, a.Nrm, Rq)) || (rc = lora_group(groups[4], ws.dGU, ws.a_rows, cols.out_q, first, Mq, packed[4]))) return rc;
+            // (the read rows of the norm: where the attention's output was, as large and no longer needed)
+            if ((rc = gather_storage(a.AO, a.Nrm, Rq)) || (rc = lora_group(groups[4], a.AO, a.q_rows, cols.out_q, first, Mq, packed[4]))) return rc;
         }
         if (l == 0) return 0;
         float *dn_q = q_apart ? ws.Tmp : nullptr;    // q's part of d n, the read rows'
