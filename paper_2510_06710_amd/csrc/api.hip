@@ -372,7 +372,7 @@ static int run_last_layer_tail(const vla_model *m, const Workspace &ws, const Ro
     int done = 0;
     if (c.dtype == VLA_DTYPE_BF16) {
         if (tail.count == 1)
-            done = (force_generic() & 8) ? 0 : try_attention_decode_bf16((bf16_t *)ws.tAO, (const bf16_t *)ws.tQ, kv, kl, rt, H, st);
+            done = (force_generic() & 8) ? 0 : try_attention_decode_bf16((bf16_t *)ws.tAO, (const bf16_t *)ws.tQ, kv, kl, rt, H, false, st);
         else
             done = (force_generic() & 4) ? 0 : try_attention_prefill_bf16((bf16_t *)ws.tAO, (const bf16_t *)ws.tQ, kv, kl, rt, H, ws.vt, 0, st);
         if (done < 0) return done;
@@ -398,6 +398,18 @@ static int run_last_layer_tail(const vla_model *m, const Workspace &ws, const Ro
 static bool gemm_norms(const vla_config &c, const Workspace &ws, int R, int M, int N) {
     if (c.dtype == VLA_DTYPE_F32) return true;
     return R == 1 && ws.skinny && !(force_generic() & (2 | 16)) && gemm_stream_norms(M, c.hidden, N);
+}
+
+// Bytes up to which a step of one row per sequence leaves K and V of all layers to the memory-side cache (256 MB) for the next step; more are
+// read past the caches, and so are they where the weights that every step brings through the caches leave them no room (row-major ones, those of
+// more than 128 rows, O and down of more than 32).  Six steps of the 7B width, kept and not, ms: 4 layers, 4 environments (77 MB) 2.23 and 2.28, 13
+// (249 MB) 2.59 and 2.67, 16 (306 MB) 2.88 and 2.84, 28 3.57 and 3.48; 32 environments of 70 keys (147 MB) 2.95 and 3.00, of 110 (231) 3.02 and 3.08, 40 of
+// 90 (236) 3.29 and 3.27, 64 of 40 (168) 3.40 and 3.39; 8 layers, 4 4.48 and 4.58, 8 (306 MB) 4.97 and 4.91, 13 5.41 and 5.27.
+constexpr double KV_KEPT = 256e6;
+static bool reads_kv_past(const vla_config &c, bool packed, int n_seq, int n_keys) {
+    const double H = c.hidden, F = c.ffn, L = c.n_layers;
+    const double fixed = !packed || n_seq > 128 ? 2.0 * L * (4.0 * H * H + 3.0 * H * F) : n_seq > 32 ? 2.0 * L * (H * H + H * F) : 0.0;
+    return fixed + 4.0 * n_seq * n_keys * H * L > KV_KEPT;
 }
 
 // `tail` (may be NULL): the rows whose final hidden state the caller reads.  Where use_tail() holds, the last layer
@@ -428,6 +440,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
     bool have_nrm = prepared && !qkv_norms;          // the sampler or the previous layer's down projection already wrote this layer's Nrm
     const bool tail_form = use_tail(tail, ra.R) && ws.tail_rows == tail->count && ra.R > 1;
     const bool copies = keep && ra.R == 1;
+    const bool kv_past = reads_kv_past(c, !m->packed.empty(), ra.n_seq, ra.pos0 + 1);          // (one row per sequence)
     auto copy_stream = [&](float *dst, const float *src) {
         if (dst != src && hipMemcpyAsync(dst, src, (size_t)M * H * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) {
             vla_set_error("copy of the residual stream failed");
@@ -478,7 +491,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         if (!fused) {
             if (fuse_reduce && !attends) g.deferred_splits = &ds;
             if ((rc = run_gemm<T>(c, g, ws.skinny, st))) return rc;
-            if (attends) rc = launch_attention_decode_qkv((bf16_t *)ws.AO, ws.QKV, ws.rope, kv, kl, ra, H, c.n_layers, st);
+            if (attends) rc = launch_attention_decode_qkv((bf16_t *)ws.AO, ws.QKV, ws.rope, kv, kl, ra, H, kv_past, st);
             else if (f32_step) rc = launch_attention_step_qkv((float *)ws.AO, ws.QKV, ws.rope, kv, kl, ra, H, st);
             else if (c.dtype == VLA_DTYPE_BF16 && !(force_generic() & 16))
                 rc = launch_rope_kv_write_bf16((bf16_t *)ws.Q, ds ? (const float *)ws.skinny : ws.QKV, ds ? ds : 1, (size_t)M * 3 * H,
@@ -489,7 +502,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         int done = attends || f32_step ? 1 : 0;
         if (c.dtype == VLA_DTYPE_BF16 && !done) {
             if (ra.R == 1)
-                done = (force_generic() & 8) ? 0 : try_attention_decode_bf16((bf16_t *)ws.AO, (const bf16_t *)ws.Q, kv, kl, ra, H, st);
+                done = (force_generic() & 8) ? 0 : try_attention_decode_bf16((bf16_t *)ws.AO, (const bf16_t *)ws.Q, kv, kl, ra, H, kv_past, st);
             else
                 done = (force_generic() & 4) ? 0 : try_attention_prefill_bf16((bf16_t *)ws.AO, (const bf16_t *)ws.Q, kv, kl, ra, H, ws.vt, 0, st);
             if (done < 0) return done;

@@ -11,8 +11,8 @@
 //      loads, the wave covers 8 / 4 rows per instruction (1 KB contiguous), probabilities come from
 //      LDS, and the row groups are summed by lane-xor steps and a four-way add through LDS.
 // Of few pairs each gets eight waves (see FEW_PAIRS), half the V columns per lane.
-// NT: K and V, whole lines per instruction and used once a step, carry the non-temporal hint: 2048 pairs of 290 keys 64.8 -> 54.6 us (5.6 TB/s),
-// 8192 pairs 224 -> 206 (5.9; few pairs: see KV_KEPT).
+// NT: K and V, whole lines per instruction and used once a step, carry the non-temporal hint: 2048 pairs of 290 keys of 4 layers 64.8 -> 54.6 us
+// (5.6 TB/s), 8192 pairs 224 -> 206 (5.9).  The caller's to choose: K and V that fit the memory-side cache are better left to it.
 #include "vla_internal.h"
 
 #include <type_traits>
@@ -200,10 +200,17 @@ __global__ void __launch_bounds__(64 * NWV) attn_decode_kernel(bf16_t *out, cons
 // now; 13 environments 17.4 + 9.5 -> 18 us.  From FEW_PAIRS on the chip is full with four waves, and the extra
 // latency ahead of the first key costs more than the launch (2048 pairs 62 + 5 against 74 us, 8192 225 + 13 against 271).
 constexpr int FEW_PAIRS = 1024;
-// Bytes of K and V of all layers up to which a step leaves them to the memory-side cache (256 MB) for the next; more are read past the
-// caches.  Six steps of the 7B width, kept and not, ms: 4 layers, 4 environments (77 MB) 2.23 and 2.28, 13 (249 MB) 2.59 and 2.67, 16 (306 MB) 2.88 and
-// 2.84, 28 3.57 and 3.48; 8 layers, 4 4.48 and 4.58, 8 (306 MB) 4.97 and 4.91, 13 5.41 and 5.27.
-constexpr double KV_KEPT = 256e6;
+
+// f(integral_constant head_dim, bool_constant NT)
+template <typename F>
+void with_form(int d, bool past_caches, F f) {
+    auto width = [&](auto nt) {
+        if (d == 128) f(std::integral_constant<int, 128>{}, nt);
+        else f(std::integral_constant<int, 64>{}, nt);
+    };
+    if (past_caches) width(std::true_type{});
+    else width(std::false_type{});
+}
 
 }  // namespace
 
@@ -212,15 +219,16 @@ static bool decode_shape_ok(const KvView &kv, const RowsArgs &ra) {
 }
 
 int try_attention_decode_bf16(bf16_t *out, const bf16_t *q, const KvView &kv, int layer, const RowsArgs &ra,
-                              int H, hipStream_t st) {
+                              int H, bool past_caches, hipStream_t st) {
     if (!decode_shape_ok(kv, ra)) return 0;
     const int nk = ra.pos0 + 1, n_items = ra.n_seq * kv.n_heads;
     if (n_items == 0) return 1;
     bf16_t *kc = (bf16_t *)kv.k + (size_t)layer * kv.layer_elems, *vc = (bf16_t *)kv.v + (size_t)layer * kv.layer_elems;
     // algorithmic bytes: K and V tiles of every (sequence, head) pair, read once
     ProfScope ps("attn_decode", 2.0 * n_items * (double)nk * kv.d * 2.0, st);
-    if (kv.d == 128) attn_decode_kernel<128, 4, false, true><<<n_items, 256, 0, st>>>(out, q, kc, vc, FusedQkv{}, kv.n_heads, nk, kv.pos_stride, H);
-    else attn_decode_kernel<64, 4, false, true><<<n_items, 256, 0, st>>>(out, q, kc, vc, FusedQkv{}, kv.n_heads, nk, kv.pos_stride, H);
+    with_form(kv.d, past_caches, [&](auto dim, auto nt) {
+        attn_decode_kernel<decltype(dim)::value, 4, false, decltype(nt)::value><<<n_items, 256, 0, st>>>(out, q, kc, vc, FusedQkv{}, kv.n_heads, nk, kv.pos_stride, H);
+    });
     int rc = vla_check_launch("attn_decode");
     return rc ? rc : 1;
 }
@@ -232,20 +240,14 @@ bool attention_decode_fuses_qkv(const KvView &kv, const RowsArgs &ra) {
 // The decode step's attention straight from the QKV projection, fp32 [n_seq, 3H] rows.  Only where
 // attention_decode_fuses_qkv().
 int launch_attention_decode_qkv(bf16_t *out, const float *qkv, const float2 *table, const KvView &kv, int layer, const RowsArgs &ra,
-                                int H, int n_layers, hipStream_t st) {
+                                int H, bool past_caches, hipStream_t st) {
     const int nk = ra.pos0 + 1, n_items = ra.n_seq * kv.n_heads;
     if (n_items == 0) return 0;
     bf16_t *kc = (bf16_t *)kv.k + (size_t)layer * kv.layer_elems, *vc = (bf16_t *)kv.v + (size_t)layer * kv.layer_elems;
     ProfScope ps("attn_decode", 2.0 * n_items * (double)nk * kv.d * 2.0, st);
     const FusedQkv f{qkv, table};
-    auto go = [&](auto dim, auto nt) {
+    with_form(kv.d, past_caches, [&](auto dim, auto nt) {
         attn_decode_kernel<decltype(dim)::value, 8, true, decltype(nt)::value><<<n_items, 512, 0, st>>>(out, nullptr, kc, vc, f, kv.n_heads, nk, kv.pos_stride, H);
-    };
-    auto width = [&](auto nt) {
-        if (kv.d == 128) go(std::integral_constant<int, 128>{}, nt);
-        else go(std::integral_constant<int, 64>{}, nt);
-    };
-    if (4.0 * n_items * nk * kv.d * n_layers > KV_KEPT) width(std::true_type{});
-    else width(std::false_type{});
+    });
     return vla_check_launch("attn_decode_qkv");
 }

@@ -307,11 +307,12 @@ size_t gemm_skinny_scratch_bytes(int M, int max_n);
 // out_kb_rows = 0: row-major output [M, H]; else k-blocked [H / 32][out_kb_rows][32]
 int try_attention_prefill_bf16(bf16_t *out, const bf16_t *q, const KvView &kv, int layer,
                                const RowsArgs &ra, int H, void *vt_scratch, int out_kb_rows, hipStream_t st);
+// one new row per sequence; past_caches: K and V are read past the caches
 int try_attention_decode_bf16(bf16_t *out, const bf16_t *q, const KvView &kv, int layer,
-                              const RowsArgs &ra, int H, hipStream_t st);
+                              const RowsArgs &ra, int H, bool past_caches, hipStream_t st);
 bool attention_decode_fuses_qkv(const KvView &kv, const RowsArgs &ra);
 int launch_attention_decode_qkv(bf16_t *out, const float *qkv, const float2 *table, const KvView &kv, int layer, const RowsArgs &ra,
-                                int H, int n_layers, hipStream_t st);
+                                int H, bool past_caches, hipStream_t st);
 size_t attention_prefill_scratch_bytes(int n_seq, int n_heads, int d, int n_keys);
 
 // Attention of the gradient pass with its [rows x keys] matrices kept (attn_rows.hip).  qkv: rotated q | k | v, bf16 [n_seq * R, 3H];
