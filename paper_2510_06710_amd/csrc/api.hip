@@ -400,16 +400,23 @@ static bool gemm_norms(const vla_config &c, const Workspace &ws, int R, int M, i
     return R == 1 && ws.skinny && !(force_generic() & (2 | 16)) && gemm_stream_norms(M, c.hidden, N);
 }
 
-// Bytes up to which a step of one row per sequence leaves K and V of all layers to the memory-side cache (256 MB) for the next step; more are
-// read past the caches, and so are they where the weights that every step brings through the caches leave them no room (row-major ones, those of
-// more than 128 rows, O and down of more than 32).  Six steps of the 7B width, kept and not, ms: 4 layers, 4 environments (77 MB) 2.23 and 2.28, 13
-// (249 MB) 2.59 and 2.67, 16 (306 MB) 2.88 and 2.84, 28 3.57 and 3.48; 32 environments of 70 keys (147 MB) 2.95 and 3.00, of 110 (231) 3.02 and 3.08, 40 of
-// 90 (236) 3.29 and 3.27, 64 of 40 (168) 3.40 and 3.39; 8 layers, 4 4.48 and 4.58, 8 (306 MB) 4.97 and 4.91, 13 5.41 and 5.27.
-constexpr double KV_KEPT = 256e6;
-static bool reads_kv_past(const vla_config &c, bool packed, int n_seq, int n_keys) {
-    const double H = c.hidden, F = c.ffn, L = c.n_layers;
-    const double fixed = !packed || n_seq > 128 ? 2.0 * L * (4.0 * H * H + 3.0 * H * F) : n_seq > 32 ? 2.0 * L * (H * H + H * F) : 0.0;
-    return fixed + 4.0 * n_seq * n_keys * H * L > KV_KEPT;
+// What a step of one row per sequence reads past the caches, so that the rest is still in the memory-side cache (256 MB) at the next step: K and V
+// of all layers and the repacked weights are both kept where they fit together, else K and V where these fit beside the weights that come
+// through the caches anyway (row-major ones, those of more than 128 rows, O and down of more than 32), else the weights where they fit.
+// Six steps, ms.  K and V kept and not, 7B width: 4 layers, 4 environments (77 MB) 2.23 and 2.28, 13 (249 MB) 2.59 and 2.67, 16 (306 MB) 2.88 and
+// 2.84, 28 3.57 and 3.48; 32 environments of 70 keys (147 MB) 2.95 and 3.00, of 110 (231) 3.02 and 3.08, 40 of 90 (236) 3.29 and 3.27, 64 of 40 (168) 3.40
+// and 3.39; 8 layers, 4 4.48 and 4.58, 8 (306 MB) 4.97 and 4.91, 13 5.41 and 5.27.
+// Weights kept and not, width 1024, FFN 2816, 70 keys (MB of weights + K and V): 4 layers, 1 environment (103 + 1) 0.75 and 0.83, 32 (103 + 37) 1.03 and 1.16; 8
+// layers, 13 (206 + 30) 1.69 and 1.87, 32 (206 + 73) 2.31 and 2.27, 64 (206 + 147) 2.93 and 2.67; 10 layers, 1 (257 + 3) 1.85 and 2.00, 13 (257 + 37) 2.42 and 2.33; 12, 1
+// (308 + 3) 2.53 and 2.39.  Width 2048, FFN 5504: 2 layers, 13 (202 + 15) 0.60 and 0.66; 3, 1 (304 + 2) 0.83 and 0.79.
+constexpr double KV_KEPT = 256e6, WEIGHTS_KEPT = 268e6;
+struct StepReads { bool kv_past, weights_past; };
+static StepReads step_reads(const vla_config &c, bool packed, int n_seq, int n_keys) {
+    const double H = c.hidden, F = c.ffn, kv = 4.0 * n_seq * n_keys * H * c.n_layers, o_down = 2.0 * c.n_layers * (H * H + H * F);
+    const double weights = 2.0 * c.n_layers * (4.0 * H * H + 3.0 * H * F), fixed = !packed || n_seq > 128 ? weights : n_seq > 32 ? o_down : 0.0;
+    if (weights + kv <= WEIGHTS_KEPT) return {false, false};
+    if (fixed + kv <= KV_KEPT) return {false, true};
+    return {true, weights > WEIGHTS_KEPT};
 }
 
 // `tail` (may be NULL): the rows whose final hidden state the caller reads.  Where use_tail() holds, the last layer
@@ -440,7 +447,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
     bool have_nrm = prepared && !qkv_norms;          // the sampler or the previous layer's down projection already wrote this layer's Nrm
     const bool tail_form = use_tail(tail, ra.R) && ws.tail_rows == tail->count && ra.R > 1;
     const bool copies = keep && ra.R == 1;
-    const bool kv_past = reads_kv_past(c, !m->packed.empty(), ra.n_seq, ra.pos0 + 1);          // (one row per sequence)
+    const StepReads reads = step_reads(c, !m->packed.empty(), ra.n_seq, ra.pos0 + 1);          // (one row per sequence)
     auto copy_stream = [&](float *dst, const float *src) {
         if (dst != src && hipMemcpyAsync(dst, src, (size_t)M * H * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) {
             vla_set_error("copy of the residual stream failed");
@@ -474,7 +481,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         GemmArgs g{};
         g.A = ws.Nrm; g.W[0] = lw.wq; g.W[1] = lw.wk; g.W[2] = lw.wv; g.n_seg = 3; g.segN = H;
         g.C = ws.QKV; g.M = M; g.K = H; g.epilogue = EPI_STORE; g.a_rows = ws.a_rows;
-        g.step = ra.R == 1;
+        g.step = ra.R == 1; g.past_caches = reads.weights_past;
         if (qkv_norm) give_norm(g, x_in, lw.attn_norm);
         if (pk) { g.Wkb[0] = pk->wq; g.Wkb[1] = pk->wk; g.Wkb[2] = pk->wv; }
         // multi-row bf16 forwards at head_dim 128: rotation and KV write ride the projection's epilogue
@@ -491,7 +498,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         if (!fused) {
             if (fuse_reduce && !attends) g.deferred_splits = &ds;
             if ((rc = run_gemm<T>(c, g, ws.skinny, st))) return rc;
-            if (attends) rc = launch_attention_decode_qkv((bf16_t *)ws.AO, ws.QKV, ws.rope, kv, kl, ra, H, kv_past, st);
+            if (attends) rc = launch_attention_decode_qkv((bf16_t *)ws.AO, ws.QKV, ws.rope, kv, kl, ra, H, reads.kv_past, st);
             else if (f32_step) rc = launch_attention_step_qkv((float *)ws.AO, ws.QKV, ws.rope, kv, kl, ra, H, st);
             else if (c.dtype == VLA_DTYPE_BF16 && !(force_generic() & 16))
                 rc = launch_rope_kv_write_bf16((bf16_t *)ws.Q, ds ? (const float *)ws.skinny : ws.QKV, ds ? ds : 1, (size_t)M * 3 * H,
@@ -502,7 +509,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         int done = attends || f32_step ? 1 : 0;
         if (c.dtype == VLA_DTYPE_BF16 && !done) {
             if (ra.R == 1)
-                done = (force_generic() & 8) ? 0 : try_attention_decode_bf16((bf16_t *)ws.AO, (const bf16_t *)ws.Q, kv, kl, ra, H, kv_past, st);
+                done = (force_generic() & 8) ? 0 : try_attention_decode_bf16((bf16_t *)ws.AO, (const bf16_t *)ws.Q, kv, kl, ra, H, reads.kv_past, st);
             else
                 done = (force_generic() & 4) ? 0 : try_attention_prefill_bf16((bf16_t *)ws.AO, (const bf16_t *)ws.Q, kv, kl, ra, H, ws.vt, 0, st);
             if (done < 0) return done;
@@ -510,7 +517,7 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         if (!done && (rc = launch_attention_generic<T>((T *)ws.AO, (const T *)ws.Q, kv, kl, ra, H, st))) return rc;
         g = GemmArgs{};
         g.A = ws.AO; g.W[0] = lw.wo; g.n_seg = 1; g.segN = H; g.C = ws.X; g.res = x_in; g.M = M; g.K = H; g.epilogue = EPI_RESIDUAL; g.a_rows = ws.a_rows;
-        g.step = ra.R == 1;
+        g.step = ra.R == 1; g.past_caches = reads.weights_past;
         if (pk) g.Wkb[0] = pk->wo;
         ds = 0;
         if (fuse_reduce) g.deferred_splits = &ds;
@@ -524,13 +531,13 @@ static int run_layers(const vla_model *m, const Workspace &ws, const RowsArgs &r
         g = GemmArgs{};
         g.A = ws.Nrm; g.W[0] = lw.w_gate; g.W[1] = lw.w_up; g.n_seg = 2; g.segN = F; g.C = ws.ACT; g.M = M; g.K = H;
         g.epilogue = EPI_SWIGLU; g.a_rows = ws.a_rows;
-        g.step = ra.R == 1;
+        g.step = ra.R == 1; g.past_caches = reads.weights_past;
         if (ffn_norm) give_norm(g, ws.X, lw.ffn_norm);
         if (pk) { g.Wkb[0] = pk->w_gate; g.Wkb[1] = pk->w_up; }
         if ((rc = run_gemm<T>(c, g, ws.skinny, st))) return rc;
         g = GemmArgs{};
         g.A = ws.ACT; g.W[0] = lw.w_down; g.n_seg = 1; g.segN = H; g.C = copies ? ws.X : x_out; g.res = ws.X; g.M = M; g.K = F; g.epilogue = EPI_RESIDUAL; g.a_rows = ws.a_rows;
-        g.step = ra.R == 1;
+        g.step = ra.R == 1; g.past_caches = reads.weights_past;
         if (pk) g.Wkb[0] = pk->w_down;
         ds = 0;
         if (fuse_reduce) g.deferred_splits = &ds;

@@ -66,7 +66,8 @@ typedef int i32x4_t __attribute__((ext_vector_type(4)));
 typedef int i32x2_t __attribute__((ext_vector_type(2)));
 
 // How the weights lie: rows of K, k-blocked, or (EPI_STORE) as [K, N], for the gradient of a product's input.
-enum WeightLayout { W_ROWS = 0, W_KBLOCKED = 1, W_COLUMNS = 2 };
+// W_KBLOCKED_PAST (decode steps): k-blocked, read past the caches.
+enum WeightLayout { W_ROWS = 0, W_KBLOCKED = 1, W_COLUMNS = 2, W_KBLOCKED_PAST = 3 };
 
 struct DmaGemmParams {
     const bf16_t *A;
@@ -696,12 +697,13 @@ __device__ __forceinline__ void read_frags(bf16x8_t (&f)[sizeof...(I)], int addr
 // L2 only (the activations, few rows, into all).
 //
 // STEP (QKV and gate/up of decode steps): instead the sums of gemm_skinny.hip, bit for bit: v_mfma_f32_32x32x16_bf16 on its
-// columns (operand j of a unit: 8 j .. + 7 of either half), K in p.parts parts that are added in order.  Repacked weights carry the
-// non-temporal hint there (64 rows: QKV 26.2 -> 25.7 us, gate/up 39.7 -> 39.2; in the split-K form of the large tile it costs 1 to 3 %).
+// columns (operand j of a unit: 8 j .. + 7 of either half), K in p.parts parts that are added in order.  Repacked weights are read past
+// the caches there where the caller says so (64 rows of the 7B width: QKV 26.2 -> 25.7 us, gate/up 39.7 -> 39.2; in the split-K form of the large
+// tile it costs 1 to 3 %).
 template <int EPI, bool KB, int WL, int BMT, int BNT, int NS, bool STEP>
 __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    constexpr bool WKB = WL == W_KBLOCKED, WCOL = WL == W_COLUMNS;
+    constexpr bool WKB = WL == W_KBLOCKED || WL == W_KBLOCKED_PAST, WCOL = WL == W_COLUMNS;
     static_assert(!WCOL || ((EPI == EPI_STORE || EPI == EPI_SWIGLU_GRAD) && !KB && !STEP), "weights as columns");
     constexpr int MB = BMT / 32, NB = BNT / 32;          // 16-row / 16-column blocks per wave
     constexpr int A_HALF = BMT * 64, W_HALF = BNT * 64, SSTAGE = 2 * (A_HALF + W_HALF);
@@ -768,7 +770,7 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(DmaGemmParams p
                                                                (i * CRI) & 8 ? w_thread_off ^ (BNT == 128 ? 128 : 32) : w_thread_off,
                                                                (u * 64 - seg * p.segK + i * CRI) * col_bytes, 0, 0);
             else if (WH) __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(w_base + half * W_HALF + blk * 1024), 16, w_thread_off,
-                                                             (int)((unsigned)(2 * u + half) * w_half) + i * 16 * w_row_bytes, 0, STEP && WKB ? 2 : 0);
+                                                             (int)((unsigned)(2 * u + half) * w_half) + i * 16 * w_row_bytes, 0, WL == W_KBLOCKED_PAST ? 2 : 0);
             else __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void *)(w_base + ((wave & 1) * (BNT / 2) + row) * 128), 16, w_thread_off,
                                                           u * 128 + row * w_row_bytes, 0, 0);
         }
@@ -1255,7 +1257,8 @@ int try_gemm_bf16_dma_step(const GemmArgs &g, hipStream_t st) {
         constexpr int EPI = decltype(epi)::value;
         const SmallTile tile = choose_tile<EPI>(p, 8, true).small;
         if (tile == TILE_LARGE) return 0;
-        return wkb ? launch_tile<EPI, false, true, true>(p, tile, st) : launch_tile<EPI, false, false, true>(p, tile, st);
+        if (!wkb) return launch_tile<EPI, false, W_ROWS, true>(p, tile, st);
+        return g.past_caches ? launch_tile<EPI, false, W_KBLOCKED_PAST, true>(p, tile, st) : launch_tile<EPI, false, W_KBLOCKED, true>(p, tile, st);
     };
     return g.epilogue == EPI_SWIGLU ? go(std::integral_constant<int, EPI_SWIGLU>{}) : go(std::integral_constant<int, EPI_STORE>{});
 }

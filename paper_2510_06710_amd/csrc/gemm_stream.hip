@@ -8,8 +8,8 @@
 // The sums are those of gemm_skinny.hip bit for bit: v_mfma_f32_32x32x16_bf16 on the same columns (8 j .. + 7 of either half
 // of a 64-column tile) in the same order.  That operand is a 16-byte piece of every 64: a lane that loaded it alone would
 // leave the rest of the line to three more instructions.  Two loads fetch the whole lines of 16 rows instead and the pieces
-// change places between lane rows afterwards (v_permlane16_swap).  Of k-blocked weights each load brings 1 KB by itself, read past
-// the caches (WHOLE).  With 16 activation rows half of the instruction's columns
+// change places between lane rows afterwards (v_permlane16_swap).  Of k-blocked weights each load brings 1 KB by itself (WHOLE),
+// past the caches where they are more than these keep until the next step.  With 16 activation rows half of the instruction's columns
 // are idle, with 16 weight rows half of its rows: the matrix cores have the time.
 //
 // What counts is the number of waves with loads in flight, not the loads per wave: with one tile each in flight, about 64
@@ -29,6 +29,9 @@ namespace {
 
 constexpr int NW = 8;                  // waves of a workgroup
 
+// Row-major weights half a line per load; k-blocked ones whole kilobytes (WHOLE), past the caches or through them.
+enum WeightRead { READ_ROWS = 0, READ_WHOLE = 1, READ_PAST = 2 };
+
 struct StreamParams {
     const bf16_t *A;
     const bf16_t *W0, *W1, *W2;
@@ -39,7 +42,7 @@ struct StreamParams {
     int parts;                 // K parts of the sums (1, 2, 4 or 8), one wave each
     int groups;                // blocks of columns per workgroup, at most NW / parts (waves beyond them only help with the norm)
     size_t w_row, w_step;      // elements between weight rows and between 32-column steps of one row
-    bool whole;                // k-blocked weights
+    int read;                  // how they are loaded
 };
 
 // A 64-column tile of 16 * B rows as it was loaded (x[c][b]: lane l holds columns 32 (l / 32) + 16 c + 8 (l / 16 % 2) .. + 7 of row
@@ -82,12 +85,12 @@ __device__ __forceinline__ void change_halves(bf16x8_t (&x)[2][B]) {
 // A wave multiplies 32 weight rows (SwiGLU: 16 gate and the matching up rows; NB = 1: 16 rows, twice) by 16 * MB activation
 // rows.  UN: tiles of 64 columns in flight, NORM: activation rows that the kernel norms itself (0: none).
 // WHOLE (k-blocked weights): a load brings 1 KB, 16 rows' whole 64 bytes of one 32-column step, and the steps change places between
-// the halves of the wave afterwards; as all of a line is used at once, it may leave the caches at once, and the K and V of the step's environments
-// (4.7 MB an environment of 289 keys and layer) find more of them there.  7B width, 1 environment: gate/up 32.7 -> 30.0 us, attention
+// the halves of the wave afterwards; as all of a line is used at once, it may leave the caches at once (READ_PAST, the caller's to choose), and the K
+// and V of the step's environments (4.7 MB an environment of 289 keys and layer) find more of them there.  7B width, 1 environment: gate/up 32.7 -> 30.0 us, attention
 // 9.3 -> 7.1; 13: 35.1 -> 31.6 and 14.3 -> 10.6.  (Whole pieces without the hint: as before; the hint on halves of pieces: gate/up 36.8.)
-template <int EPI, int NB, int MB, int UN, int NORM, bool WHOLE>
+template <int EPI, int NB, int MB, int UN, int NORM, int READ>
 __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
-    constexpr bool SW = EPI == EPI_SWIGLU;
+    constexpr bool SW = EPI == EPI_SWIGLU, WHOLE = READ != READ_ROWS;
     constexpr int COLS = SW ? 16 : 16 * NB, LDW = 16 * NB + 4;          // output columns, floats of a row of sums
     __shared__ float squares[NORM ? NORM : 1][4], chain[NORM ? NORM : 1][256];
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -120,7 +123,8 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(StreamParams p) {
         for (int c = 0; c < 2; c++)
 #pragma unroll
             for (int r = 0; r < NB; r++) {
-                if (WHOLE) wf[u][c][r] = __builtin_bit_cast(bf16x8_t, __builtin_nontemporal_load((const i32x4_v *)(w[r] + wo + c * p.w_step)));
+                if (READ == READ_PAST) wf[u][c][r] = __builtin_bit_cast(bf16x8_t, __builtin_nontemporal_load((const i32x4_v *)(w[r] + wo + c * p.w_step)));
+                else if (WHOLE) wf[u][c][r] = *(const bf16x8_t *)(w[r] + wo + c * p.w_step);
                 else wf[u][c][r] = *(const bf16x8_t *)(w[r] + wo + c * 16);
             }
         if (!NORM)
@@ -276,13 +280,14 @@ int launch(StreamParams p, hipStream_t st) {
     // each tile brings twice the activations, and one is better: 7B shape, O and down at 32 rows 23 us against 25).
     p.groups = (blocks + 255) / 256 < NW / p.parts ? (blocks + 255) / 256 : NW / p.parts;
     const int grid = (blocks + p.groups - 1) / p.groups;
-    auto go = [&](auto whole) {
-        constexpr bool WHOLE = decltype(whole)::value;
-        if (MB == 1 && grid <= 256) gemm_stream_kernel<EPI, NB, MB, MB == 1 ? 2 : 1, NORM, WHOLE><<<grid, 64 * NW, lds, st>>>(p);
-        else gemm_stream_kernel<EPI, NB, MB, 1, NORM, WHOLE><<<grid, 64 * NW, lds, st>>>(p);
+    auto go = [&](auto read) {
+        constexpr int READ = decltype(read)::value;
+        if (MB == 1 && grid <= 256) gemm_stream_kernel<EPI, NB, MB, MB == 1 ? 2 : 1, NORM, READ><<<grid, 64 * NW, lds, st>>>(p);
+        else gemm_stream_kernel<EPI, NB, MB, 1, NORM, READ><<<grid, 64 * NW, lds, st>>>(p);
     };
-    if (p.whole) go(std::true_type{});
-    else go(std::false_type{});
+    if (p.read == READ_PAST) go(std::integral_constant<int, READ_PAST>{});
+    else if (p.read == READ_WHOLE) go(std::integral_constant<int, READ_WHOLE>{});
+    else go(std::integral_constant<int, READ_ROWS>{});
     return vla_check_launch("gemm_stream");
 }
 
@@ -325,7 +330,7 @@ int try_gemm_bf16_stream(const GemmArgs &g, hipStream_t st) {
     for (int i = 0; i < n_seg; i++) kb = kb && g.Wkb[i];
     const void *const *W = kb ? g.Wkb : g.W;
     p.W0 = (const bf16_t *)W[0]; p.W1 = (const bf16_t *)W[1]; p.W2 = (const bf16_t *)W[2];
-    p.whole = kb;
+    p.read = !kb ? READ_ROWS : g.past_caches ? READ_PAST : READ_WHOLE;
     p.w_row = kb ? 32 : (size_t)g.K;
     p.w_step = kb ? (size_t)(g.segN + VLA_KB_PAD_ROWS) * 32 : 32;
     p.C = g.C; p.M = g.M; p.K = g.K; p.segN = g.segN;

@@ -75,6 +75,7 @@ struct GemmArgs {
     int a_rows;             // rows of A that may be read (>= M; contents past M arbitrary): the MFMA kernel
                             // loads whole 256-row tiles and declines if the buffer does not cover them
     int step;               // a decode step (one row per sequence): the weight-streaming kernel of few rows may take it
+    int past_caches;        // ... whose weights, where they are repacked, are read past the caches
     const float *norm_x, *norm_gain;   // not NULL (steps for which gemm_stream_norms; fp32 models, K a multiple of 4): A is
     float norm_eps;                    // RMSNorm(norm_x) norm_gain, formed by the kernel from the fp32 rows [M, K]
     int *deferred_splits;   // not NULL (EPI_STORE and EPI_RESIDUAL of the split-K kernels): the kernel leaves its n

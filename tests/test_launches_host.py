@@ -61,21 +61,21 @@ def test_read_rows_of_the_norm_stay_in_their_buffer(tmp_path):
             assert not any(dst < x < dst + 8 * 15 * 1024 * 2 for x in dxb)
 
 
-# layers, hidden, heads, FFN, environments, keys of the step, repacked weights: whether K and V are read past the caches ("k").  MB of weights
-# and of K and V behind each.
+# layers, hidden, heads, FFN, environments, keys of the step, repacked weights: what is read past the caches, K and V ("k"), the repacked
+# weights ("w").  MB of weights and of K and V behind each.
 STEPS = [((4, 1024, 8, 2816, 1, 71, True), ""),          # 103, 1
          ((8, 1024, 8, 2816, 13, 71, True), ""),         # 206, 30
-         ((8, 1024, 8, 2816, 64, 71, True), ""),        # 206, 149
-         ((12, 1024, 8, 2816, 1, 71, True), ""),        # 308, 3
+         ((8, 1024, 8, 2816, 64, 71, True), "w"),        # 206, 149
+         ((12, 1024, 8, 2816, 1, 71, True), "w"),        # 308, 3
          ((4, 1024, 8, 2816, 64, 290, True), "k"),       # 103, 304
          ((2, 1024, 8, 2816, 256, 61, True), ""),        # 51, 128
-         ((4, 4096, 32, 11008, 1, 289, True), ""),      # 1619, 19 (and so on)
-         ((4, 4096, 32, 11008, 13, 289, True), ""),     # 246
-         ((4, 4096, 32, 11008, 16, 289, True), "k"),    # 303
-         ((4, 4096, 32, 11008, 32, 71, True), ""),      # 149
-         ((4, 4096, 32, 11008, 32, 131, True), "k"),    # 275
-         ((4, 4096, 32, 11008, 40, 71, True), "k"),     # 186, and 495 of O and down, which come through the caches above 32 rows
-         ((4, 4096, 32, 11008, 256, 289, True), "k"),
+         ((4, 4096, 32, 11008, 1, 289, True), "w"),      # 1619, 19 (and so on)
+         ((4, 4096, 32, 11008, 13, 289, True), "w"),     # 246
+         ((4, 4096, 32, 11008, 16, 289, True), "kw"),    # 303
+         ((4, 4096, 32, 11008, 32, 71, True), "w"),      # 149
+         ((4, 4096, 32, 11008, 32, 131, True), "kw"),    # 275
+         ((4, 4096, 32, 11008, 40, 71, True), "kw"),     # 186, and 495 of O and down, which come through the caches above 32 rows
+         ((4, 4096, 32, 11008, 256, 289, True), "kw"),
          ((4, 4096, 32, 11008, 4, 289, False), "k"),     # row-major weights come through the caches
          ((1, 4096, 64, 512, 3, 511, False), ""), ((1, 4096, 64, 512, 15, 511, False), "k"),      # (test_gpu_decode_past_caches.py's sizes)
          ((1, 4096, 32, 256, 3, 509, True), ""), ((1, 4096, 32, 256, 31, 509, True), "k")]
@@ -93,10 +93,16 @@ for L, H, heads, F, B, keys, packed in %r:
 
 
 def test_what_a_step_reads_past_the_caches(tmp_path):
-    """K and V that fit the memory-side cache until the next step reads them again are left to it; the last read row of a prefill, whose
-    K and V the launch before wrote and the first step reads, leaves them there at any size."""
+    """K and V, and repacked weights, that fit the memory-side cache until the next step reads them again are left to it; the last read row of a
+    prefill, whose K and V the launch before wrote and the first step reads, leaves them there at any size."""
     for (case, past), (prefill, step) in zip(STEPS, record(STEP % ([c for c, _ in STEPS],), tmp_path)):
         L, H, heads, F, B, keys, packed = case
         form = f"attn_decode_kernelILi{H // heads}ELi" + ("8ELb1E" if B * heads < 1024 else "4ELb0E")
         assert count(step, form + f"Lb{int('k' in past)}E") == L and count(step, "attn_decode") == L, case
         assert count(prefill, f"attn_decode_kernelILi{H // heads}ELi4ELb0ELb0E") == count(prefill, "attn_decode") == 1, case
+        if B <= 16:                                  # all four products of a layer are the streaming kernel's: the last argument of its template
+            stream = [n for n in step if "gemm_stream" in n]
+            assert len(stream) == 4 * L and all(f"ELi{2 if 'w' in past else int(packed)}EEEv" in n for n in stream), case
+        elif B <= 128 and packed:                    # QKV or gate/up on the small tiles: the third argument
+            small = [n for n in step if "gemm_bf16_small" in n]
+            assert small and all(f"ELb0ELi{3 if 'w' in past else 1}E" in n for n in small), case
