@@ -143,6 +143,7 @@ template <typename T, int EPI, bool VEC, int MB, int NBK, int UN, bool NORM>
 __global__ void __launch_bounds__(512) gemm_generic_kernel(const T *A, const T *W0, const T *W1, const T *W2, int segN, void *Cv,
                                                            const float *res, int M, int N, int K, const float *gain, float eps) {
     constexpr int NW = 8, NP = (EPI == EPI_SWIGLU) ? 2 : 1;
+    constexpr bool WIDE = sizeof(T) == 4 && VEC;
     __shared__ __attribute__((aligned(16))) f32x4_t part[NW][NP * MB * NBK][64];
     __shared__ float squares[NORM ? NW : 1][NORM ? MB * 16 : 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kq = lane >> 4;
@@ -188,7 +189,7 @@ __global__ void __launch_bounds__(512) gemm_generic_kernel(const T *A, const T *
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < UN; i++) {
-            if (i && g + i * NW * 16 >= K) break;
+            if (WIDE && i && g + i * NW * 16 >= K) break;
             if (NORM) {
 #pragma unroll
                 for (int x = 0; x < MB; x++)
@@ -643,7 +644,9 @@ static void gemm_generic_tile(const GemmArgs &g, int N, hipStream_t st) {
     const dim3 big((N + 16 * NBK - 1) / (16 * NBK), (g.M + 16 * MB - 1) / (16 * MB));
     // The large tile wants two workgroups per CU; its sums are those of the small one.  (Fewer than 512 large tiles are
     // at most 4096 + a few rows of small ones.)  A wave of the small tile loads its whole share of K at once where that is up to
-    // eight blocks: a down projection of K = 688 4.9 us as six, 5.5 as four and two.
+    // eight blocks: a down projection of K = 688 4.9 us as six, 5.5 as four and two.  Of narrower loads (bf16, rows that do not end on
+    // 16 bytes) four blocks, and no way out between them: decode of width 2048, FFN 5461, 25 environments 2.43 ms, with eight 2.63; gradient pass of an fp32
+    // decoder of width 1024, FFN 2731, 1.85 and 1.92.
     if ((size_t)big.x * big.y >= 512) {
         gemm_generic_kernel<T, EPI, VEC, MB, NBK, 1, NORM><<<big, 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, res, g.M, N, g.K, g.norm_gain, g.norm_eps);
         return;
@@ -652,7 +655,8 @@ static void gemm_generic_tile(const GemmArgs &g, int N, hipStream_t st) {
     auto go = [&](auto un) {
         gemm_generic_kernel<T, EPI, VEC, 1, 1, decltype(un)::value, NORM><<<small, 512, 0, st>>>(A, W0, W1, W2, g.segN, g.C, res, g.M, N, g.K, g.norm_gain, g.norm_eps);
     };
-    if (g.K <= 256) go(std::integral_constant<int, 2>{});
+    if constexpr (sizeof(T) == 2 || !VEC) go(std::integral_constant<int, 4>{});
+    else if (g.K <= 256) go(std::integral_constant<int, 2>{});
     else if (g.K <= 768) go(std::integral_constant<int, 6>{});
     else go(std::integral_constant<int, 8>{});
 }

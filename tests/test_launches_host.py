@@ -106,3 +106,20 @@ def test_what_a_step_reads_past_the_caches(tmp_path):
         elif B <= 128 and packed:                    # QKV or gate/up on the small tiles: the third argument
             small = [n for n in step if "gemm_bf16_small" in n]
             assert small and all(f"ELb0ELi{3 if 'w' in past else 1}E" in n for n in small), case
+
+
+GENERIC = """
+result = []
+for dtype, F in (("bf16", 5461), ("bf16", 5460), ("f32", 2731), ("f32", 2732)):
+    cfg = vb.make_config(shape(1, 1024, 16, F, dtype), 2, 20)
+    m = model(cfg)
+    vb.vla_prefill(m.handle, t(vb.vla_kv_bytes(cfg, 2, 20)), t(vb.vla_workspace_bytes(cfg, 0, 2, 12, 0)), t(), t(), 2, 10, 2, t(), None)
+    result.append(launches())
+"""
+
+
+def test_blocks_in_flight_of_the_generic_product(tmp_path):
+    """A wave of the small tile: its share of K in up to eight blocks where a load brings 16 bytes, else four."""
+    for names, blocks in zip(record(GENERIC, tmp_path), ({4}, {4}, {4, 8}, {8})):
+        generic = [n for n in names if "gemm_generic" in n]
+        assert generic and {b for n in generic for b in (2, 4, 6, 8) if f"ELi1ELi1ELi{b}E" in n} == blocks, names
