@@ -318,6 +318,9 @@ struct TailSpec { int first, count; };
 // 32-layer prefill.  Not worth it when the tail is a large share of the rows.
 static bool use_tail(const TailSpec *tail, int R) { return tail && tail->count >= 1 && tail->count * 4 <= R; }
 
+// Bytes of K and V, and of these and the weights, that the memory-side cache (256 MB) keeps for a kernel that reads them again (see step_reads).
+constexpr double KV_KEPT = 256e6, WEIGHTS_KEPT = 268e6;
+
 // Last layer, tail form: K, V of all rows (stream x_in, ws.Nrm as in any layer), then the rest of the layer on the packed
 // tail rows (ws.tX and friends) with the kernels a forward of that many rows would use.
 template <typename T>
@@ -371,8 +374,8 @@ static int run_last_layer_tail(const vla_model *m, const Workspace &ws, const Ro
     const RowsArgs rt{ra.n_seq, tail.count, ra.pos0 + tail.first, ra.full_from};
     int done = 0;
     if (c.dtype == VLA_DTYPE_BF16) {
-        if (tail.count == 1)
-            done = (force_generic() & 8) ? 0 : try_attention_decode_bf16((bf16_t *)ws.tAO, (const bf16_t *)ws.tQ, kv, kl, rt, H, false, st);
+        if (tail.count == 1)          // (the layer's K and V have just been written, and the first decode step reads them again)
+            done = (force_generic() & 8) ? 0 : try_attention_decode_bf16((bf16_t *)ws.tAO, (const bf16_t *)ws.tQ, kv, kl, rt, H, 4.0 * Mt * H * (rt.pos0 + 1) > KV_KEPT, st);
         else
             done = (force_generic() & 4) ? 0 : try_attention_prefill_bf16((bf16_t *)ws.tAO, (const bf16_t *)ws.tQ, kv, kl, rt, H, ws.vt, 0, st);
         if (done < 0) return done;
@@ -409,7 +412,6 @@ static bool gemm_norms(const vla_config &c, const Workspace &ws, int R, int M, i
 // Weights kept and not, width 1024, FFN 2816, 70 keys (MB of weights + K and V): 4 layers, 1 environment (103 + 1) 0.75 and 0.83, 32 (103 + 37) 1.03 and 1.16; 8
 // layers, 13 (206 + 30) 1.69 and 1.87, 32 (206 + 73) 2.31 and 2.27, 64 (206 + 147) 2.93 and 2.67; 10 layers, 1 (257 + 3) 1.85 and 2.00, 13 (257 + 37) 2.42 and 2.33; 12, 1
 // (308 + 3) 2.53 and 2.39.  Width 2048, FFN 5504: 2 layers, 13 (202 + 15) 0.60 and 0.66; 3, 1 (304 + 2) 0.83 and 0.79.
-constexpr double KV_KEPT = 256e6, WEIGHTS_KEPT = 268e6;
 struct StepReads { bool kv_past, weights_past; };
 static StepReads step_reads(const vla_config &c, bool packed, int n_seq, int n_keys) {
     const double H = c.hidden, F = c.ffn, kv = 4.0 * n_seq * n_keys * H * c.n_layers, o_down = 2.0 * c.n_layers * (H * H + H * F);

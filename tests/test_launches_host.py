@@ -75,10 +75,12 @@ STEPS = [((4, 1024, 8, 2816, 1, 71, True), ""),          # 103, 1
          ((4, 4096, 32, 11008, 32, 71, True), "w"),      # 149
          ((4, 4096, 32, 11008, 32, 131, True), "kw"),    # 275
          ((4, 4096, 32, 11008, 40, 71, True), "kw"),     # 186, and 495 of O and down, which come through the caches above 32 rows
-         ((4, 4096, 32, 11008, 256, 289, True), "kw"),
+         ((4, 4096, 32, 11008, 256, 289, True), "tkw"),
+         ((4, 4096, 32, 11008, 54, 289, True), "kw"),     # 1023, 256 of one layer without the step's key
+         ((4, 4096, 32, 11008, 55, 289, True), "tkw"),
          ((4, 4096, 32, 11008, 4, 289, False), "k"),     # row-major weights come through the caches
          ((1, 4096, 64, 512, 3, 511, False), ""), ((1, 4096, 64, 512, 15, 511, False), "k"),      # (test_gpu_decode_past_caches.py's sizes)
-         ((1, 4096, 32, 256, 3, 509, True), ""), ((1, 4096, 32, 256, 31, 509, True), "k")]
+         ((1, 4096, 32, 256, 3, 509, True), ""), ((1, 4096, 32, 256, 31, 509, True), "tk")]
 STEP = """
 result = []
 for L, H, heads, F, B, keys, packed in %r:
@@ -94,12 +96,12 @@ for L, H, heads, F, B, keys, packed in %r:
 
 def test_what_a_step_reads_past_the_caches(tmp_path):
     """K and V, and repacked weights, that fit the memory-side cache until the next step reads them again are left to it; the last read row of a
-    prefill, whose K and V the launch before wrote and the first step reads, leaves them there at any size."""
+    prefill ("t"), whose K and V the launch before wrote and the first step reads, leaves them there where those of one layer fit."""
     for (case, past), (prefill, step) in zip(STEPS, record(STEP % ([c for c, _ in STEPS],), tmp_path)):
         L, H, heads, F, B, keys, packed = case
         form = f"attn_decode_kernelILi{H // heads}ELi" + ("8ELb1E" if B * heads < 1024 else "4ELb0E")
         assert count(step, form + f"Lb{int('k' in past)}E") == L and count(step, "attn_decode") == L, case
-        assert count(prefill, f"attn_decode_kernelILi{H // heads}ELi4ELb0ELb0E") == count(prefill, "attn_decode") == 1, case
+        assert count(prefill, f"attn_decode_kernelILi{H // heads}ELi4ELb0ELb{int('t' in past)}E") == count(prefill, "attn_decode") == 1, case
         if B <= 16:                                  # all four products of a layer are the streaming kernel's: the last argument of its template
             stream = [n for n in step if "gemm_stream" in n]
             assert len(stream) == 4 * L and all(f"ELi{2 if 'w' in past else int(packed)}EEEv" in n for n in stream), case
