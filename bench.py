@@ -160,12 +160,28 @@ def bench_recompute(args, wl, torch, vi, vb, Rollout):
     print(json.dumps(out))
 
 
+def backward_projection_flops(shape, rows, read, keep):
+    """Projection flops that vla_logprob_backward executes for one rollout of `rows` rows whose last `read` the loss reads: every layer's
+    forward, its input-gradient products, and the forward again, without the down projection, of the layers whose intermediates the first
+    pass does not leave.  Where 4 read <= rows the top layer works on the read rows alone but for k and v, and the top two layers are
+    not run again (one otherwise; none with the activations kept).  The first layer's q, k and v have no input gradient."""
+    H, F, L = shape.hidden, shape.ffn, shape.n_layers
+    top_rows = read if 4 * read <= rows else rows
+    again = 0 if keep else max(0, L - (2 if top_rows < rows else 1))
+    total = 0.0
+    for l in range(L):
+        r = top_rows if l == L - 1 else rows
+        kv, rest = 2 * H * H * rows, (2 * H * H + 3 * H * F) * r          # k and v; q, O and the feed-forward block
+        total += 2 * (kv + rest)                                           # forward and input gradients
+        total -= kv + H * H * r if l == 0 else 0
+        total += kv + rest - H * F * r if l < again else 0
+    return 2.0 * total
+
+
 def bench_backward(args, wl, torch, vi, vb, Rollout):
     """LoRA-gradient pass (vla_logprob_backward) over a sample of the recompute workload's stored rollouts: a step is
     one call over `--backward-rollouts` rollouts in micro-batches of `--backward-micro-batch`.  Reports rollouts/s and
-    the rate of the projection flops it executes (the forward once, every layer again without its down projection, and
-    the input-gradient products once; with --backward-keep the forward once and the input-gradient products), against
-    the bf16 MFMA peak."""
+    the rate of the projection flops it executes (backward_projection_flops), against the bf16 MFMA peak."""
     dev = "cuda:0"
     torch.cuda.set_device(0)
     N, mb, rank = args.backward_rollouts, args.backward_micro_batch, args.lora_rank
@@ -203,9 +219,7 @@ def bench_backward(args, wl, torch, vi, vb, Rollout):
     prof = profile_report(vb)
     vb.lib().vla_profile_enable(0)
     rows = S + A - 1 if wl.mode == 0 else S + A
-    down_share = shape.hidden * shape.ffn / shape.layer_params          # the recomputed forward skips the down projection
-    passes = 2.0 if args.backward_keep else 3.0 - down_share            # forward (+ forward again) + input gradients
-    flops = passes * N * rows * 2.0 * shape.layer_params * shape.n_layers
+    flops = N * backward_projection_flops(shape, rows, A, args.backward_keep)
     out = {"metric": "stored rollouts/sec, LoRA-gradient pass of the log-prob recompute (7B shape)", "value": N / (ms * 1e-3),
            "unit": "rollouts/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms,
            "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
@@ -280,7 +294,7 @@ def main():
     ap.add_argument("--lora-rank", type=int, default=32)
     ap.add_argument("--backward-keep", action="store_true",
                     help="--backward: keep every layer's activations in the first pass (larger workspace) instead of "
-                         "running each layer a second time")
+                         "running all but the top ones a second time")
     ap.add_argument("--calibration-copy", action="store_true",
                     help="also launch one 1 GiB plain copy kernel (reference for rocprofv3 --pmc traffic counters)")
     args = ap.parse_args()
