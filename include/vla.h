@@ -273,12 +273,13 @@ int vla_logp_aggregate(const float *logp, size_t n_out, int inner, float *out, v
  *   vla_logprob_recompute up to the rounding differences of two evaluations).  Rollouts are processed in
  *   micro-batches of max_batch; gradients are summed over micro-batches in order, every sum in a fixed order, so the
  *   result is reproducible bit for bit.  Gradient operands of the GEMMs are rounded to the storage dtype.
- *   keep_activations = 0: the first pass is the forward of vla_logprob_recompute keeping the residual stream at every
- *   layer input, and every layer is run a second time for its backward; ws: DEVICE, at least
- *   vla_backward_workspace_bytes(cfg, N, P + T, A, rank) bytes (grows with max_batch; 11.7 GB at the 7B shape with
- *   max_batch 32).  keep_activations = 1: the first pass keeps what every layer's backward reads for one micro-batch
- *   and no layer is run twice; ws at least vla_backward_keep_workspace_bytes(...) bytes (78 GB there): for GPUs with
- *   memory to spare.  Same gradients up to rounding (the first pass then uses the unfused kernels). */
+ *   keep_activations = 0: the first pass runs the lower layers with the kernels of vla_logprob_recompute, keeping the
+ *   residual stream at every layer input, and the top one or two (two where 4 A is at most the rows of a rollout and the
+ *   workspace has room) with the unfused kernels, which leave what their backward reads; the lower ones are run a second
+ *   time for theirs.  ws: DEVICE, at least vla_backward_workspace_bytes(cfg, N, P + T, A, rank) bytes (grows with
+ *   max_batch; 11.7 GB at the 7B shape with max_batch 32).  keep_activations = 1: the first pass keeps what every layer's
+ *   backward reads for one micro-batch and no layer is run twice; ws at least vla_backward_keep_workspace_bytes(...) bytes
+ *   (78 GB there): for GPUs with memory to spare.  Same gradients up to rounding (all layers then use the unfused kernels). */
 typedef struct { const void *a, *b; } vla_lora_factor;
 typedef struct { vla_lora_factor q, k, v, o, gate, up, down; } vla_lora_layer;
 typedef struct { float *da, *db; } vla_lora_grad;

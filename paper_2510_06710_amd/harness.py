@@ -89,7 +89,7 @@ class Rollout:
                  keep_activations=False):
         """LoRA gradients of sum(coef * logp): lora[l][p] = (a, b) device tensors in the storage dtype.  Returns
         (grads, logp) with grads[l][p] = (da, db) fp32 device tensors.  keep_activations: hand the library the larger
-        workspace with which it keeps every layer's activations instead of running each layer a second time."""
+        workspace with which it keeps every layer's activations instead of running all but the top ones a second time."""
         N, P = patch.shape[0], patch.shape[1]
         T = ids.shape[1]
         size = vb.vla_backward_keep_workspace_bytes if keep_activations else vb.vla_backward_workspace_bytes

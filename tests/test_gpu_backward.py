@@ -8,7 +8,7 @@ rounded to bf16 (2^-9 relative per element, averaged down by the sums over rows)
 with the oracle that rounds the forward's stored tensors (straight-through): relative RMS error at most 1e-2 and
 largest deviation at most 2e-2 of the tensor's largest entry (observed: 4e-3 and 5e-3).
 
-The log-probs the pass returns come from the recompute's own forward kernels.  Here they are taken at seeded random
+The log-probs the pass returns come from its own forward: the recompute's kernels in the lower layers, the unfused ones in the top one or two.  Here they are taken at seeded random
 bins, not at sampled ones: such a bin can sit far in the tail (log-prob below -9 where a flat distribution gives
 -ln 256 = -5.5), and a bf16 logit error grows with the distance z_j - logsumexp(z) = logp_j it is measured over, so
 the bf16 bound of 1e-2 is scaled by max(1, |logp| / ln 256) per token."""
